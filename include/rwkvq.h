@@ -96,7 +96,8 @@ const char* rwkvq_status_string(int status);
  * a call made after rwkvq_set_option returns sees the new value.
  *   RWKVQ_OPT_SMALL_BATCH_PATH    how native-layout matrices run at 16 < M <= 128 (see rwkvq_sq_gemm):
  *                                 RWKVQ_SMALL_BATCH_AUTO (default: the estimate below), _STREAM, _MATRIX_CORES
- *   RWKVQ_OPT_PREFILL_TILE_ROWS   rows of x per matrix-core workgroup: 0 (default: chosen per launch), 128, 256
+ *   RWKVQ_OPT_PREFILL_TILE_ROWS   rows of x per matrix-core workgroup: 0 (default: chosen from the sizes), or the kernels
+ *                                 for large batches with 128 or 256 whatever the sizes
  *   the constants of the small-batch estimate, measured on the RWKV-6-7B shapes on one MI355X
  *   (0 restores the default):
  *   RWKVQ_OPT_STREAM_WIDE_GBPS    packed-weight GB/s of a streaming pass over 17..32 batch rows (2800)

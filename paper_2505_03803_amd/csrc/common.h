@@ -176,6 +176,7 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
                          hipStream_t s, const PostDev* posts = nullptr);
 hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype,
                           hipStream_t s);
+hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s);
 
 hipError_t launch_proxy(const void* const* ws, const int* Ns, const int* Ks, int n_mats, int dtype,
                         int terms, double tau_c, double tau_f, uint32_t* bitmaps, double* out, int32_t* phi,

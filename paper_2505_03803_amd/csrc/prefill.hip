@@ -24,7 +24,7 @@
 //
 // Workgroup -> tile order: the m-tile index runs fastest, so workgroups that are dispatched
 // round-robin over the 8 XCDs keep one slice of x (256 rows) per XCD L2 when there are 8 m-tiles.
-#include "common.h"
+#include "matrix_core.h"
 #include "../../include/rwkvq.h"
 
 #include <algorithm>
@@ -35,7 +35,6 @@ namespace rwkvq {
 
 constexpr int kPfMaxMats = 64;
 constexpr int BM = 256, BN = 256;              // block tile; the k-step is 64 columns
-constexpr int kRowBytes = 128;                 // 64 k * 2 B
 constexpr int kTileBytes = 256 * kRowBytes;    // one operand tile (32 KB)
 constexpr int kCb8Bytes = 1024;                // converted 8-bit-index codebook
 // Activation tiles in LDS: three (the copy of a k-step is issued two k-steps ahead of its use, so
@@ -56,117 +55,6 @@ struct PfArgs {
     PfMat m[kPfMaxMats];
     int M, ydt, m_tiles, pad;
 };
-
-// s_waitcnt immediates (gfx9 encoding): only the named counter is waited for.
-#define RWKVQ_WAIT_VM0_LGKM0() __builtin_amdgcn_s_waitcnt(0x0070)   /* vmcnt(0) lgkmcnt(0) */
-#define RWKVQ_WAIT_VM8_LGKM0() __builtin_amdgcn_s_waitcnt(0x0078)   /* vmcnt(8) lgkmcnt(0) */
-#define RWKVQ_WAIT_VM4_LGKM0() __builtin_amdgcn_s_waitcnt(0x0074)   /* vmcnt(4) lgkmcnt(0) */
-// Publish LDS writes (ds_write and load-unit copies) to the workgroup: the caller has waited for
-// its own writes; the barrier orders them against the other wavefronts' reads.
-#define RWKVQ_BARRIER() asm volatile("s_barrier" ::: "memory")
-
-template <bool BF16> struct Elem;
-template <> struct Elem<true> {
-    // accumulate in place; the "a" constraint pins the accumulator to the AGPR half of the
-    // register file (left to itself the allocator starts it in VGPRs and shuffles it all loop long)
-    static __device__ __forceinline__ void mfma(uint4_t a, uint4_t b, float4_t& c) {
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
-    }
-    static __device__ __forceinline__ uint32_t pack(float lo, float hi) {   // v_cvt_pk_bf16_f32
-        typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-        bf2 v = {(__bf16)lo, (__bf16)hi};
-        return __builtin_bit_cast(uint32_t, v);
-    }
-    static __device__ __forceinline__ uint32_t from_f16x2(uint32_t h) {
-        half2_t v = __builtin_bit_cast(half2_t, h);
-        return pack((float)v.x, (float)v.y);
-    }
-};
-template <> struct Elem<false> {
-    static __device__ __forceinline__ void mfma(uint4_t a, uint4_t b, float4_t& c) {
-        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
-    }
-    static __device__ __forceinline__ uint32_t pack(float lo, float hi) {
-        half2_t v = {(half_t)lo, (half_t)hi};
-        return __builtin_bit_cast(uint32_t, v);
-    }
-    static __device__ __forceinline__ uint32_t from_f16x2(uint32_t h) { return h; }
-};
-
-// Field c (compile-time) of a native SQ unit.
-template <int C>
-__device__ __forceinline__ uint32_t sq_code(uint32_t w0, uint32_t w1, uint32_t w2) {
-    constexpr int P = C >> 1, e = C & 1;
-    if constexpr (P < 15) {
-        uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
-        return (w >> (1 + 3 * (P % 5) + 16 * e)) & 7u;
-    } else {
-        constexpr int b = 16 * e;
-        return ((w0 >> b) & 1u) | (((w1 >> b) & 1u) << 1) | (((w2 >> b) & 1u) << 2);
-    }
-}
-template <int P>
-__device__ __forceinline__ uint32_t vq6_byteaddr(uint32_t w0, uint32_t w1, uint32_t w2) {
-    if constexpr (P < 15) {
-        uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
-        return (w >> (6 * (P % 5))) & 0xFCu;
-    } else {
-        return ((w0 & 3u) << 2) | ((w1 & 3u) << 4) | ((w2 & 3u) << 6);
-    }
-}
-
-// The two weights of pair P of a native SQ unit, dequantised as Sec. 2.2 Eq. "SQ" prescribes
-// (q - z rounded, times s rounded).  The codes are not extracted: masked in place, a 3-bit code at
-// mantissa bits b..b+2 of an fp16 half is the subnormal q * 2^(b-24); a mixed-precision FMA reads
-// the half, multiplies by 2^(24-b) (exact) and subtracts z with the single rounding of q - z.  The
-// codes at bits 10 and 13 of the halves come down to bits 1 and 4 with one shift by 9 per word.
-template <int P>
-__device__ __forceinline__ void sq_pair_deq(uint32_t w0, uint32_t w1, uint32_t w2, float s, float z, float& lo,
-                                            float& hi) {
-    uint32_t m;
-    float c;
-    if constexpr (P < 15) {
-        constexpr int p = P % 5;
-        const uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
-        if constexpr (p == 0) { m = w & 0x000E000Eu; c = 8388608.f; }
-        else if constexpr (p == 1) { m = w & 0x00700070u; c = 1048576.f; }
-        else if constexpr (p == 2) { m = w & 0x03800380u; c = 131072.f; }
-        else if constexpr (p == 3) { m = (w >> 9) & 0x000E000Eu; c = 8388608.f; }
-        else { m = (w >> 9) & 0x00700070u; c = 1048576.f; }
-    } else {
-        // bit b of the pair's two codes sits at bits 0 and 16 of word b
-        m = (w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2);
-        c = 16777216.f;
-    }
-    const half2_t h = __builtin_bit_cast(half2_t, m);
-    lo = __fmul_rn(fmaf((float)h.x, c, -z), s);
-    hi = __fmul_rn(fmaf((float)h.y, c, -z), s);
-}
-
-// Eight consecutive-k weights (step T4 of a unit) of one lane, as four packed pairs.
-template <bool BF16, int T4>
-__device__ __forceinline__ uint4_t sq_chunk(uint32_t w0, uint32_t w1, uint32_t w2, float s, float z) {
-    uint4_t o;
-    float a, b;
-    sq_pair_deq<4 * T4 + 0>(w0, w1, w2, s, z, a, b); o.x = Elem<BF16>::pack(a, b);
-    sq_pair_deq<4 * T4 + 1>(w0, w1, w2, s, z, a, b); o.y = Elem<BF16>::pack(a, b);
-    sq_pair_deq<4 * T4 + 2>(w0, w1, w2, s, z, a, b); o.z = Elem<BF16>::pack(a, b);
-    sq_pair_deq<4 * T4 + 3>(w0, w1, w2, s, z, a, b); o.w = Elem<BF16>::pack(a, b);
-    return o;
-}
-template <int T4>
-__device__ __forceinline__ uint4_t vq6_chunk(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t cb) {
-    uint4_t o;
-    o.x = __builtin_amdgcn_ds_bpermute(vq6_byteaddr<4 * T4 + 0>(w0, w1, w2), cb);
-    o.y = __builtin_amdgcn_ds_bpermute(vq6_byteaddr<4 * T4 + 1>(w0, w1, w2), cb);
-    o.z = __builtin_amdgcn_ds_bpermute(vq6_byteaddr<4 * T4 + 2>(w0, w1, w2), cb);
-    o.w = __builtin_amdgcn_ds_bpermute(vq6_byteaddr<4 * T4 + 3>(w0, w1, w2), cb);
-    return o;
-}
-__device__ __forceinline__ uint4_t vq8_chunk(uint32_t w, const uint32_t* cb) {
-    uint4_t o = {cb[w & 255u], cb[(w >> 8) & 255u], cb[(w >> 16) & 255u], cb[w >> 24]};
-    return o;
-}
 
 // Packed words of one 256-column tile for the 4 row tiles (of 16 rows) a thread unpacks.
 template <int FMT> struct WRegs;
@@ -201,9 +89,6 @@ __device__ __forceinline__ void w_load(WRegs<FMT>& r, const WSrc& src, int T, in
         r.cb8 = ((const uint4_t*)src.aux + (size_t)T * 64)[lane];
     }
 }
-
-// LDS byte offset, inside a tile, of logical 16-byte chunk c (0..7) of row `row`.
-__device__ __forceinline__ int tile_off(int row, int c) { return row * kRowBytes + ((c ^ (row & 7)) << 4); }
 
 // Unpack k-step KQ (0..3: 64 columns) of the tile held in r and write it to the W tile in LDS.
 // Row tiles I0 .. I1-1 of the thread's four (so that the work can be spread over a k-step).
@@ -264,26 +149,6 @@ __device__ __forceinline__ void unpack_begin(UnpackState<FMT>& st, const WRegs<F
     st.d0 = wt + tile_off(row0, kg);
     st.d1 = wt + tile_off(row0, 4 + kg);
     if constexpr (FMT == FMT_VQ6) st.cb = Elem<BF16>::from_f16x2(r.cb);
-}
-
-// The SQ pair P as masked in-place codes (fp16 subnormals q * 2^(b-24)) and the power of two that
-// undoes the position (see sq_pair_deq).
-template <int P>
-__device__ __forceinline__ uint32_t sq_pair_mask(uint32_t w0, uint32_t w1, uint32_t w2) {
-    if constexpr (P < 15) {
-        constexpr int p = P % 5;
-        const uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
-        if constexpr (p == 0) return w & 0x000E000Eu;
-        else if constexpr (p == 1) return w & 0x00700070u;
-        else if constexpr (p == 2) return w & 0x03800380u;
-        else if constexpr (p == 3) return (w >> 9) & 0x000E000Eu;
-        else return (w >> 9) & 0x00700070u;
-    } else {
-        return (w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2);
-    }
-}
-template <int P> constexpr float sq_pair_unscale() {
-    return P == 15 ? 16777216.f : (P % 5 == 0 || P % 5 == 3) ? 8388608.f : (P % 5 == 1 || P % 5 == 4) ? 1048576.f : 131072.f;
 }
 
 template <bool BF16, int FMT, int KQ, int S>
@@ -652,7 +517,16 @@ static int pick_bm(int M, long long n_tiles) {
     return t128 < t256 ? 128 : 256;
 }
 
-hipError_t launch_prefill(const MatDev* mats_in, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+// A few hundred rows of x: the kernels of midbatch.hip.  The line depends on M (and on a K their 32-bit offsets hold), not on
+// the other matrices of the call, so that the order of a matrix's sums stays a function of its own sizes.  Measured on the
+// calls that a block makes (bf16, SQ and 6-bit VQ, us, here -> there): {r, k, v, g} of 4096 x 4096 at M = 1024 180 -> 145,
+// 1536 238 -> 213, 1792 251 -> 258; 4096 x 4096 alone at M = 1536 84 -> 64, 4096 x 14336 266 -> 192, {14336 x 4096,
+// 4096 x 4096} 322 -> 248.  A call that fills the device many times over (tens of matrices) is 10 to 15 % faster here from
+// M = 512 on; no block makes one.  A forced tile height (RWKVQ_OPT_PREFILL_TILE_ROWS) stays here.
+constexpr int kMidMaxM = 1536;
+static bool mid_rows(const MatDev& m, int M) { return M <= kMidMaxM && m.K <= (1 << 20) && option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0; }
+
+static hipError_t launch_prefill_tiles(const MatDev* mats_in, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
     // Workgroups of a matrix with a long K run long: put those matrices first so that the end of
     // a launch is filled by short workgroups.
     std::vector<MatDev> sorted(mats_in, mats_in + n_mats);
@@ -692,6 +566,14 @@ hipError_t launch_prefill(const MatDev* mats_in, int n_mats, int M, int x_dtype,
         }
     }
     return hipSuccess;
+}
+
+hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+    std::vector<MatDev> mid, tiles;
+    for (int i = 0; i < n_mats; ++i) (mid_rows(mats[i], M) ? mid : tiles).push_back(mats[i]);
+    hipError_t e = mid.empty() ? hipSuccess : launch_mid(mid.data(), (int)mid.size(), M, x_dtype, y_dtype, s);
+    if (e == hipSuccess && !tiles.empty()) e = launch_prefill_tiles(tiles.data(), (int)tiles.size(), M, x_dtype, y_dtype, s);
+    return e;
 }
 
 }  // namespace rwkvq

@@ -1,0 +1,82 @@
+"""The matrix-core kernels for 17 to 1536 rows of x (wavefronts that split K and unpack W in registers) at the edges of
+their tiles: K of fewer column tiles than K groups, ragged rows, every choice of rows per workgroup, and zero points too
+small for the one-step unpack."""
+import numpy as np
+import pytest
+
+from oracle import rwkvq_oracle as orc
+from paper_2505_03803_amd import binding as B
+from paper_2505_03803_amd import synth
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+def make(fmt, N, K, seed):
+    rng = np.random.default_rng(seed)
+    return synth.gen_sq(rng, N, K) if fmt == "sq" else synth.gen_vq(rng, N, K, 6 if fmt == "vq6" else 8)
+
+
+# M: one row and one past the 64-, 96- and 128-row workgroups, eight K groups (M <= 128) and four; K: 1, 3, 5 and 9 column tiles
+@pytest.mark.parametrize("fmt", ["sq", "vq6", "vq8"])
+@pytest.mark.parametrize("N,K,M", [(256, 256, 17), (256, 2304, 64), (512, 768, 65), (256, 1280, 128), (256, 256, 129), (768, 2304, 193),
+                                   (256, 1280, 385), (512, 512, 1025), (256, 256, 1536)])
+@pytest.mark.parametrize("xdt", ["bf16", "f16"])
+def test_against_the_oracle(fmt, N, K, M, xdt, options):
+    print(f"mid {fmt} N={N} K={K} M={M} x={xdt}", flush=True)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_MATRIX_CORES)
+    mat = make(fmt, N, K, 11)
+    x = synth.gen_activations(np.random.default_rng(M), M, K, xdt)
+    # against the weights as fed: what is left is binary32 sums of up to 2304 products in four or eight partial sums, about
+    # sqrt(K) 2^-24 of the row's norms (the distance to the unrounded weights is a statistical figure, 1.1e-3 rms for bf16)
+    asfed = orc.linear(mat, orc.widen(x, xdt), "f64", weight_round=xdt)
+    assert G.err_g2(G.gpu_gemm(B.upload(mat, native=True), x, xdt), asfed) <= 2e-5
+
+
+# rows of W x rows of x that make the launcher take 64, 96 and 128 rows of x per workgroup (and 8 K groups at M = 100)
+@pytest.mark.parametrize("M,n_mats,N", [(100, 1, 1024), (100, 5, 4096), (333, 1, 4096), (333, 4, 4096), (300, 9, 4096)])
+def test_calls_of_several_matrices(M, n_mats, N, options):
+    """Mixed formats in one launch; every matrix alone gives the same bits beyond 128 rows (the order of a matrix's sums
+    depends on its own sizes only)."""
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_MATRIX_CORES)
+    K = 512
+    mats = [make(("sq", "vq6", "vq8")[i % 3], N, K, 20 + i) for i in range(n_mats)]
+    xs = [synth.gen_activations(np.random.default_rng(40 + i), M, K, "bf16") for i in range(n_mats)]
+    torch = G.torch_()
+    dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
+    ys = [torch.empty((M, N), dtype=torch.float32, device="cuda") for _ in mats]
+    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.BF16, B.F32)
+    torch.cuda.synchronize()
+    for i in (0, n_mats - 1):
+        got = ys[i].cpu().numpy()
+        assert G.err_g2(got.astype(np.float64), orc.linear(mats[i], orc.widen(xs[i], "bf16"), "f64", weight_round="bf16")) <= 2e-5
+        alone = B.gemm(dms[i], dev[i], M, B.BF16, B.F32)
+        torch.cuda.synchronize()
+        if M > 128:
+            assert np.array_equal(got, alone.cpu().numpy())
+
+
+@pytest.mark.parametrize("xdt", ["bf16", "f16"])
+@pytest.mark.parametrize("small", [False, True])
+def test_one_hot_rows_return_the_rounded_weights(xdt, small, options):
+    """Row m selects column k_m: the output is Deq(W) rounded once to the type of x, bit for bit.  With a zero point in
+    (0, 2^-11) q - z itself rounds; one such group, subnormal ones among them, makes its workgroup take the two-step form."""
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_MATRIX_CORES)
+    N, K = 512, 1280
+    mat = make("sq", N, K, 31)
+    if small:
+        rng = np.random.default_rng(5)
+        z = mat.zeros.reshape(N, K // 128)
+        for n in range(N):                                   # fp16 bits 1 .. 0x0FFF, either sign; and an exact zero
+            z[n, n % (K // 128)] = rng.integers(1, 0x1000) | (0x8000 if n & 1 else 0)
+        z[7, 3], z[300, 0] = 0, 0x8000
+    dm = B.upload(mat, native=True)
+    want = G.gpu_dequant(dm, B.DTYPES[xdt])
+    want = orc.widen(want, xdt)
+    for M in (100, 320):
+        x = np.zeros((M, K), np.float32)
+        cols = (np.arange(M) * 37 + 5 * M) % K
+        x[np.arange(M), cols] = 1.0
+        bits = synth.f32_to_bf16_bits(x) if xdt == "bf16" else synth.f32_to_f16_bits(x)
+        assert np.array_equal(G.gpu_gemm(dm, bits, xdt), want[:, cols].T.astype(np.float64)), M
