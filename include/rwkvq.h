@@ -109,11 +109,13 @@ const char* rwkvq_status_string(int status);
  *                                 (two stretches that share each staged activation tile) when the launch
  *                                 still has at least this many workgroups that way, and 128 rows otherwise
  *                                 (2048; 1 = always 256 rows, 1000000 = never)
- *   RWKVQ_OPT_STREAM_SPLIT_MAX_WORK    batch 2..32 on the streaming kernels: a launch takes the small-launch form (one
+ *   RWKVQ_OPT_STREAM_SPLIT_MAX_WORK    batch 2..16 on the streaming kernels: a launch takes the small-launch form (one
  *                                 workgroup per 32 rows of W, its wavefronts split the columns, every workgroup
  *                                 reads all of x) when (rows of all its matrices / 32) x (16 + M) is at most this
- *                                 (65536: one RWKV-6-7B layer at any M <= 16, two layers up to M = 8; 1 = never;
- *                                 at M = 17..32 a third of the value is the limit unless it is 1000000 or more)
+ *                                 (65536: one RWKV-6-7B layer at any M <= 16, two layers up to M = 8; 1 = never).
+ *                                 At the default, the streaming path at M = 17..32 (up to two such layers per call) and
+ *                                 33..128 runs on kernels that split K on the matrix cores, weights exact as well;
+ *                                 any other value keeps it on passes over 32 rows of x
  *   RWKVQ_OPT_SPLIT_GRID_2D       batch 1, launches of at most eight matrices with few rows (the stages of a block): 1 = a
  *                                 workgroup takes its matrix and row tile from a two-dimensional grid, 2 = from the
  *                                 table of first-workgroup indices that larger launches use (1; same output bits)
@@ -156,12 +158,11 @@ int rwkvq_vq_dequant(const void* indices, const void* codebooks, int layout, int
  *   native layout, M <= 16: streaming dequant-GEMV kernels bound by HBM bandwidth;
  *   native layout, M  > 16: tiles dequantized into LDS and multiplied on the matrix cores in
  *                           the type of x, weights rounded to that type;
- *   native layout, 16 < M <= 128: the matrix cores (M padded to 128 rows), or ceil(M / 32) passes
- *                           of the streaming kernels over blocks of 32 rows of x (weights exact),
- *                           whichever is estimated cheaper for the matrices of the call: a call
- *                           of few matrices gives the matrix-core kernel few tiles.  A matrix
- *                           whose N is not a multiple of 256 has no matrix-core tiles: streaming
- *                           passes up to M = 128, beyond that the plain reference kernel.
+ *   native layout, 16 < M <= 128: the matrix cores with weights rounded, or the streaming path (weights
+ *                           exact: one or several passes over W), whichever is estimated cheaper
+ *                           for the matrices of the call.  A matrix whose N is not a multiple of 256 has
+ *                           no tiles of the first: streaming path up to M = 128, beyond that the
+ *                           plain reference kernel.
  * x and y must not overlap. */
 int rwkvq_sq_gemm(const void* codes, const void* scales, const void* zeros, int layout,
                   const void* x, void* y, int M, int N, int K, int bits, int group, int x_dtype,
@@ -178,9 +179,9 @@ int rwkvq_vq_gemm(const void* indices, const void* codebooks, int layout, const 
  * Reproducibility: a call gives the same bits every time.  At M = 1 the kernel is chosen by the
  * number of rows in the call (small calls split each row's columns over several wavefronts), so
  * the same matrix dispatched alone and inside a large call may differ in the order of its
- * binary32 sums (a few units in the last place); for 2 <= M <= 16 and for M > 128 the order is
- * fixed; for 16 < M <= 128 the path (see rwkvq_sq_gemm) is chosen from the sizes of the call's
- * matrices, not from their values.
+ * binary32 sums (a few units in the last place); the same holds for 2 <= M <= 128, where the kernel
+ * (and for 16 < M the path, see rwkvq_sq_gemm) is chosen from the sizes of the call's matrices, not
+ * from their values; for M > 128 the order is fixed.
  * No scratch memory; safe to record into a HIP graph. */
 int rwkvq_linear_dispatch(const rwkvq_matrix* mats, const void* const* xs, void* const* ys,
                           int n_mats, int M, int x_dtype, int y_dtype, void* stream);
@@ -190,7 +191,7 @@ int rwkvq_linear_dispatch(const rwkvq_matrix* mats, const void* const* xs, void*
  * paths[i], HOST, one of:
  *   RWKVQ_PATH_REFERENCE     plain reference kernel (canonical layout; shapes no other path takes);
  *   RWKVQ_PATH_STREAM        streaming kernels, M <= 16: weights exact;
- *   RWKVQ_PATH_STREAM_PASSES ceil(M / 32) passes of the streaming kernels, 16 < M <= 128: weights exact;
+ *   RWKVQ_PATH_STREAM_PASSES streaming path, 16 < M <= 128: weights exact;
  *   RWKVQ_PATH_MATRIX_CORES  matrix-core kernels: weights rounded once to the type of x.
  * The path depends on M and on the sizes and layouts of the call's matrices only (see rwkvq_sq_gemm),
  * so a caller can learn beforehand how the weights of a call will be fed.  Errors: RWKVQ_ERR_NULL,

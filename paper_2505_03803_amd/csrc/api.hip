@@ -102,6 +102,24 @@ bool stream_passes_cheaper(const std::vector<MatDev>& mats, int M) {
     return t_stream < t_mfma;
 }
 
+// Matrices of a streaming path on the kernels that split K over a workgroup's wavefronts (midbatch.hip, weights exact, one
+// pass over W per 64 rows of x) instead of the streaming kernels (one per 32, rows staged per workgroup)?  Measured on the 7B
+// shapes, fp16 / bf16, us, streaming -> split:
+//   M = 17..32: one layer in a call (832 workgroups of 64 rows of W) 66 -> 37 at 32, two layers 79 -> 68, four layers 116 -> 163:
+//   large launches fill the device either way, and there the streaming kernels read W faster;
+//   M > 32: they need two to four passes: four layers 207 -> 183 at 48, 237 -> 204 at 64, 320 -> 321 at 80, 455 -> 368 at 128;
+//   M <= 16: a layer whose weights are in the cache 41 -> 30, but 67 -> 70 from memory (a step is then so short that the
+//   words of one column tile ahead do not cover the trip), so they stay.
+// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK away from its default forces one of the streaming kernels' forms.
+constexpr int kSplitKMaxWgs = 1792;
+bool split_k_cheaper(const std::vector<MatDev>& mats, int M) {
+    if (option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK) != kStreamSplitMaxWork) return false;
+    if (M > kStreamPassRows) return true;
+    long long wgs = 0;
+    for (const MatDev& d : mats) wgs += (d.N + 63) / 64;
+    return wgs <= kSplitKMaxWgs;
+}
+
 // Which kernels run each matrix of a call (values of RWKVQ_PATH_*): the one place that decides.
 void plan_paths(const std::vector<MatDev>& devs, int M, std::vector<int>* path) {
     path->assign(devs.size(), RWKVQ_PATH_REFERENCE);
@@ -124,8 +142,8 @@ void plan_paths(const std::vector<MatDev>& devs, int M, std::vector<int>* path) 
 }  // namespace
 
 namespace rwkvq {
-static const int kOptionDefault[kOptionCount] = {RWKVQ_SMALL_BATCH_AUTO, 0, 2800, 4100, 24, 12, 1500, 2048, 65536, 1};
-static std::atomic<int> g_option[kOptionCount] = {{RWKVQ_SMALL_BATCH_AUTO}, {0}, {2800}, {4100}, {24}, {12}, {1500}, {2048}, {65536}, {1}};
+static const int kOptionDefault[kOptionCount] = {RWKVQ_SMALL_BATCH_AUTO, 0, 2800, 4100, 24, 12, 1500, 2048, kStreamSplitMaxWork, 1};
+static std::atomic<int> g_option[kOptionCount] = {{RWKVQ_SMALL_BATCH_AUTO}, {0}, {2800}, {4100}, {24}, {12}, {1500}, {2048}, {kStreamSplitMaxWork}, {1}};
 int option(int which) { return g_option[which].load(std::memory_order_relaxed); }
 }  // namespace rwkvq
 
@@ -235,6 +253,10 @@ int rwkvq_linear_dispatch(const rwkvq_matrix* mats, const void* const* xs, void*
     for (const MatDev& d : ref) {
         hipError_t e = launch_ref_gemm(d, M, x_dtype, y_dtype, s);
         if (e != hipSuccess) return RWKVQ_ERR_DEVICE;
+    }
+    if (!passes.empty() && split_k_cheaper(passes, M)) {
+        if (launch_mid(passes.data(), (int)passes.size(), M, x_dtype, y_dtype, true, s) != hipSuccess) return RWKVQ_ERR_DEVICE;
+        passes.clear();
     }
     if (!decode.empty()) {
         hipError_t e = launch_decode(decode.data(), (int)decode.size(), M, x_dtype, y_dtype, s);

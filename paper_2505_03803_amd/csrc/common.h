@@ -176,7 +176,8 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
                          hipStream_t s, const PostDev* posts = nullptr);
 hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype,
                           hipStream_t s);
-hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s);
+// Splits K over the wavefronts of a workgroup (midbatch.hip): exact = false, the feed of launch_prefill; true, weights unrounded.
+hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, bool exact, hipStream_t s);
 
 hipError_t launch_proxy(const void* const* ws, const int* Ns, const int* Ks, int n_mats, int dtype,
                         int terms, double tau_c, double tau_f, uint32_t* bitmaps, double* out, int32_t* phi,
@@ -206,6 +207,7 @@ hipError_t launch_pointwise(int op, const void* x, const void* y, int dt, long l
 // Process-wide settings behind rwkvq_set_option (values of RWKVQ_OPT_* in rwkvq.h); option() is an atomic load.
 constexpr int kOptionCount = 10;
 int option(int which);
+constexpr int kStreamSplitMaxWork = 65536;   // default of RWKVQ_OPT_STREAM_SPLIT_MAX_WORK
 
 constexpr int kDecodeMaxM = 16;    // native layout: M <= this goes to the streaming kernels
 constexpr int kDecodeMaxK = 20480; // ... whose per-group activation sums for K columns fit their LDS

@@ -1389,7 +1389,7 @@ __global__ void __launch_bounds__(64 * S) decode_splitk_kernel(Args a) {
 // staged for the workgroup and no barrier sits in the tile loop; the partial sums meet in LDS in a fixed order.
 template <int MT, int S, bool GRID2D>
 __global__ void __launch_bounds__(64 * S, 1) decode_splitk_batched_kernel(DecodeArgs a) {
-    static_assert(MT == 16 || MT == 32, "one or two groups of sixteen batch rows");
+    static_assert(MT == 16, "one group of sixteen batch rows");
     constexpr int G = groups_of(MT);
     __shared__ __attribute__((aligned(1024))) uint32_t cb_all[S][512];
     __shared__ __attribute__((aligned(16))) float xsc[S][2 * 16 * G];
@@ -1640,16 +1640,13 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         for (int i = 0; i < cnt; ++i) tiles += (mats[order[i]].N + 15) / 16;
         int split = 0;
         if (M == 1 && tiles < kSplitTarget) split = pick_split(tiles);
-        // batch 2..32 with few rows in the launch: one workgroup per 32 rows, S wavefronts over its column tiles
-        if (M > 1 && M <= 32) {
+        // batch 2..16 with few rows in the launch: one workgroup per 32 rows, S wavefronts over its column tiles
+        if (M > 1 && M <= 16) {
             long long stretches = 0;
             for (int i = 0; i < cnt; ++i) stretches += (mats[order[i]].N + 16 * kBRT - 1) / (16 * kBRT);
             // measured on the RWKV-6-7B shapes: the form wins up to about 2000 stretches at batch 16 and 3500 at batch <= 8
             // (what it pays is every workgroup's own read of x, which grows with the batch)
-            // (above batch 16 a workgroup carries two groups of fragments and the row-workgroup form catches up at a
-            // third of that: one 4096-row matrix still gains 25-35 %, the two 14336-row matrices of channel mixing lose)
-            const long long max_work = option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK);
-            if (stretches * (16 + M) <= (M <= 16 || max_work >= 1000000 ? max_work : max_work / 3)) {
+            if (stretches * (16 + M) <= option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK)) {
                 const int S = stretches * 8 >= kSplitTarget ? 4 : 8;      // sixteen wavefronts would leave 128 registers each
                 int wgs = 0;
                 for (int i = 0; i < cnt; ++i) {
@@ -1667,14 +1664,10 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
                     int longest = 0;
                     for (int i = 0; i < cnt; ++i) longest = std::max(longest, a.wg_end[i] - (i ? a.wg_end[i - 1] : 0));
                     const dim3 grid(longest, cnt);
-                    if (M <= 16 && S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 4, true>), grid, dim3(256), 0, s, a);
-                    else if (M <= 16) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 8, true>), grid, dim3(512), 0, s, a);
-                    else if (S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<32, 4, true>), grid, dim3(256), 0, s, a);
-                    else hipLaunchKernelGGL((decode_splitk_batched_kernel<32, 8, true>), grid, dim3(512), 0, s, a);
-                } else if (M <= 16 && S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 4, false>), dim3(wgs), dim3(256), 0, s, a);
-                else if (M <= 16) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 8, false>), dim3(wgs), dim3(512), 0, s, a);
-                else if (S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<32, 4, false>), dim3(wgs), dim3(256), 0, s, a);
-                else hipLaunchKernelGGL((decode_splitk_batched_kernel<32, 8, false>), dim3(wgs), dim3(512), 0, s, a);
+                    if (S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 4, true>), grid, dim3(256), 0, s, a);
+                    else hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 8, true>), grid, dim3(512), 0, s, a);
+                } else if (S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 4, false>), dim3(wgs), dim3(256), 0, s, a);
+                else hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 8, false>), dim3(wgs), dim3(512), 0, s, a);
                 hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
                 continue;

@@ -15,6 +15,11 @@
 // MF = 4 takes 1.2 us, of MF = 8 1.5 us, of which the MFMAs are 0.45 and 0.9), then the activation reads from the L2.
 // Measured (bf16, SQ and 6-bit VQ, us; prefill.hip -> here): 4096 x 4096 at M = 333 83 -> 26, at M = 1024 85 -> 40;
 // 4096 x 14336 at M = 333 266 -> 72, at M = 1024 265 -> 115; four 4096 x 4096 at M = 333 171 -> 64, at M = 1024 184 -> 145.
+// EXACT instances (17 <= M <= 128 where the streaming kernels' contract holds: weights unrounded, fp16 or bf16 x multiplied as it
+// is): NW = 1, 32 to 64 rows of x per workgroup, so a call that took ceil(M / 32) passes over W takes one (M <= 64).  SQ: codes as
+// 8 + q with the scale and zero point applied to the group's sums; VQ: the fp16 entries, for bf16 x as the sum of two bf16.
+// Measured (fp16, us; streaming kernels -> here): {r, k, v, g} of 4096 x 4096 at M = 32 21.3 -> 12.6, 48 34.8 -> 15.4, 64
+// 41 -> 17.6, 128 83 -> 31; 4096 x 14336 38 -> 24, 59 -> 29, 75 -> 33, 152 -> 36.
 // Tried and slower or equal: wavefronts of 32 instead of 64 rows of W with sixteen per workgroup (the fragment reads from
 // LDS double: - 8 % at M = 64, + 20 % at M = 1024), fragment reads three and four rows ahead (equal), an MFMA / vector
 // instruction interleave fixed with scheduling groups (equal at MF = 4, spills at MF = 8).
@@ -47,12 +52,15 @@ struct MidArgs {
 
 // Per kernel instance: activation tiles in the ring of a K group, register sets of packed words (two: the next tile's words
 // are asked for a whole tile ahead; MF = 8 has no registers for that and asks half a step ahead), bytes of LDS.
-constexpr int mid_sets(int MF) { return MF <= 6 ? 2 : 1; }
+constexpr int mid_sets(int MF, bool EXACT) { return MF <= (EXACT ? 3 : 6) ? 2 : 1; }
 constexpr int mid_stage(int MF) { return 16 * MF * kRowBytes; }
-constexpr int mid_stages(int MF, int NW) { return std::min(4, 144 * 1024 / (kMidWaves / NW * mid_stage(MF))); }
-constexpr int mid_ring(int MF, int NW) { return kMidWaves / NW * mid_stages(MF, NW) * mid_stage(MF); }
+constexpr int mid_book(bool EXACT) { return EXACT ? 2 * kMidBook : kMidBook; }       // EXACT, bf16: two words per entry
+constexpr int mid_stages(int MF, int NW, bool EXACT) { return std::min(4, (EXACT ? 128 : 144) * 1024 / (kMidWaves / NW * mid_stage(MF))); }
+constexpr int mid_ring(int MF, int NW, bool EXACT) { return kMidWaves / NW * mid_stages(MF, NW, EXACT) * mid_stage(MF); }
 constexpr int mid_red() { return kMidWaves * 4 * kMidNF * 1024; }      // partial sums of four subtile rows of every wavefront
-constexpr int mid_lds(int MF, int NW) { return std::max(mid_ring(MF, NW) + kMidWaves * mid_sets(MF) * kMidBook, mid_red()); }
+constexpr int mid_lds(int MF, int NW, bool EXACT) {
+    return std::max(mid_ring(MF, NW, EXACT) + kMidWaves * mid_sets(MF, EXACT) * mid_book(EXACT), mid_red());
+}
 
 // Buffer loads: a descriptor and the moving offset in scalar registers, one 32-bit offset per lane (global loads came out
 // as 64-bit lane addresses, an addition and two registers each), and reads past `bytes` return zero.
@@ -130,6 +138,41 @@ __device__ __forceinline__ bool mid_small_zero(const void* sz, int bytes, int ti
     return __builtin_amdgcn_readfirstlane(all) != 0;
 }
 
+// EXACT (weights enter unrounded, as in the streaming kernels): SQ codes as 8 + q, exact in either type - fp16 8.0 with the code
+// at mantissa bits 7..9, bf16 2^-9 with the code at bits 4..6, i.e. 2^-12 (8 + q), so that no group's sum overflows before
+// the finite bf16 range of x ends - and y += s (acc - (8 + z) X) per group, X from an MFMA against ones (2^-12 for bf16).
+template <bool BF16, int P>
+__device__ __forceinline__ uint32_t mid_sq_code(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask, uint32_t magic) {
+    constexpr int at = BF16 ? 4 : 7;
+    if constexpr (P < 15) {
+        constexpr int sh = at - 1 - 3 * (P % 5);
+        const uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
+        return ((sh > 0 ? w << (sh > 0 ? sh : 0) : sh < 0 ? w >> (sh < 0 ? -sh : 0) : w) & mask) | magic;
+    } else {                                   // bit b of the pair's two codes sits at bits 0 and 16 of word b
+        return (((w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2)) << at) | magic;
+    }
+}
+template <bool BF16, int H>
+__device__ __forceinline__ uint32_t mid_code_pair(const MidRegs<FMT_SQ3>& r, int i, int p, uint32_t mask, uint32_t magic) {
+    constexpr int u = H >> 2, t = H & 3;
+    const uint32_t w0 = u == 0 ? r.a[i].x : r.a[i].w, w1 = u == 0 ? r.a[i].y : r.b[i].x, w2 = u == 0 ? r.a[i].z : r.b[i].y;
+    return p == 0 ? mid_sq_code<BF16, 4 * t>(w0, w1, w2, mask, magic) : p == 1 ? mid_sq_code<BF16, 4 * t + 1>(w0, w1, w2, mask, magic)
+         : p == 2 ? mid_sq_code<BF16, 4 * t + 2>(w0, w1, w2, mask, magic) : mid_sq_code<BF16, 4 * t + 3>(w0, w1, w2, mask, magic);
+}
+// Index of weight pair p of step H, row tile i.
+template <int FMT, int H>
+__device__ __forceinline__ uint32_t mid_index(const MidRegs<FMT>& r, int i, int p) {
+    constexpr int u = H >> 2, t = H & 3;
+    if constexpr (FMT == FMT_VQ8) {
+        const uint4_t q = u == 0 ? r.a[i] : r.b[i];
+        return ((t == 0 ? q.x : t == 1 ? q.y : t == 2 ? q.z : q.w) >> (8 * p)) & 255u;
+    } else {
+        const uint32_t w0 = u == 0 ? r.a[i].x : r.a[i].w, w1 = u == 0 ? r.a[i].y : r.b[i].x, w2 = u == 0 ? r.a[i].z : r.b[i].y;
+        return (p == 0 ? vq6_byteaddr<4 * t>(w0, w1, w2) : p == 1 ? vq6_byteaddr<4 * t + 1>(w0, w1, w2)
+              : p == 2 ? vq6_byteaddr<4 * t + 2>(w0, w1, w2) : vq6_byteaddr<4 * t + 3>(w0, w1, w2)) >> 2;
+    }
+}
+
 // Weight pair p (0..3) of 32-column step H (0..7) of the 256-column tile, row tile i: two weights as they are multiplied.
 template <bool BF16, int FMT, bool ROUND, int H>
 __device__ __forceinline__ uint32_t mid_pair(const MidRegs<FMT>& r, int i, int p, const uint32_t* book) {
@@ -159,10 +202,10 @@ __device__ __forceinline__ void mid_pairs(uint32_t (&b)[kMidNF][4], const MidReg
     for (int n = n0; n < n1; ++n) b[n >> 2][n & 3] = mid_pair<BF16, FMT, ROUND, H>(r, n >> 2, n & 3, book);
 }
 
-template <bool BF16, int FMT, bool ROUND, int MF, int NW>
+template <bool BF16, int FMT, bool ROUND, int MF, int NW, bool EXACT>
 __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, char* lds, int m0, int n0, int wave, int lane,
                                          float4_t (&acc)[MF][kMidNF]) {
-    constexpr int KW = kMidWaves / NW, ST = mid_stages(MF, NW), SETS = mid_sets(MF), AHEAD = ST - 1, kStage = mid_stage(MF);
+    constexpr int KW = kMidWaves / NW, ST = mid_stages(MF, NW, EXACT), SETS = mid_sets(MF, EXACT), AHEAD = ST - 1, kStage = mid_stage(MF);
     constexpr int tw = FMT == FMT_VQ8 ? 512 : 384, kBook = FMT == FMT_VQ8 ? 1024 : 256;
     constexpr bool SQ = FMT == FMT_SQ3;
     static_assert(ST >= 2 && ST <= 4, "one activation tile is copied while one is multiplied");
@@ -170,7 +213,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
     const int K = mt.K, KT = K >> 8, R0 = (n0 >> 4) + kMidNF * nw;
     const int nt = kg < KT ? (KT - kg + KW - 1) / KW : 0, rounds = (KT + KW - 1) / KW;   // column tiles of this group, of the longest
     char* const ring = lds + kg * ST * kStage;
-    uint32_t* const books = (uint32_t*)(lds + mid_ring(MF, NW)) + wave * (SETS * kMidBook / 4);
+    uint32_t* const books = (uint32_t*)(lds + mid_ring(MF, NW, EXACT)) + wave * (SETS * mid_book(EXACT) / 4);
 
     // the group's wavefronts copy its activation tile together: copy i of this one brings rows 8 (NW i + nw) .. + 7 (rows
     // past M repeat row M - 1)
@@ -183,8 +226,9 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         xoff[i] = (uint32_t)rr * (uint32_t)K * 2u + 16u * c;
     }
     const __amdgpu_buffer_rsrc_t xbuf = mid_buffer((const char*)mt.x + (size_t)m0 * K * 2, (uint32_t)std::min(a.M - m0, 16 * MF) * (uint32_t)K * 2u);
-    const __amdgpu_buffer_rsrc_t wbuf = mid_buffer(mt.codes + (size_t)R0 * KT * tw, (uint32_t)(kMidNF * KT * tw * 4));
-    const __amdgpu_buffer_rsrc_t abuf = SQ ? mid_buffer((const uint2_t*)mt.aux + (size_t)R0 * KT * 16, (uint32_t)(kMidNF * KT * 128))
+    const int tiles = std::min(kMidNF, (mt.N >> 4) - R0);              // EXACT: N is any multiple of 16; words past the end read as zero
+    const __amdgpu_buffer_rsrc_t wbuf = mid_buffer(mt.codes + (size_t)R0 * KT * tw, (uint32_t)(tiles * KT * tw * 4));
+    const __amdgpu_buffer_rsrc_t abuf = SQ ? mid_buffer((const uint2_t*)mt.aux + (size_t)R0 * KT * 16, (uint32_t)(tiles * KT * 128))
                                            : mid_buffer((const char*)mt.aux + (size_t)(R0 >> 4) * KT * kBook, (uint32_t)(KT * kBook));
     const int last = 4 * nt - 1;
     auto copy = [&](int step, int stage) {     // step = 4 j + KQ of this group's sequence; past its end the last one again
@@ -211,15 +255,52 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         if constexpr (FMT == FMT_VQ8) r.cb8 = __builtin_amdgcn_raw_buffer_load_b128(abuf, at, T * kBook, 0);
     };
     constexpr int kLoads = SQ ? 3 * kMidNF : 2 * kMidNF + 1;
-    auto stage_book = [&](const MidRegs<FMT>& r, uint32_t* to) {   // VQ: the tile's codebook, rounded to the operand type
-        if constexpr (FMT == FMT_VQ6) to[lane] = Elem<BF16>::from_f16x2(r.cb);
-        if constexpr (FMT == FMT_VQ8)
-            *(uint4_t*)(to + 4 * lane) = uint4_t{Elem<BF16>::from_f16x2(r.cb8.x), Elem<BF16>::from_f16x2(r.cb8.y),
-                                                 Elem<BF16>::from_f16x2(r.cb8.z), Elem<BF16>::from_f16x2(r.cb8.w)};
+    constexpr bool SPLIT = EXACT && BF16 && !SQ;   // fp16 entries as the sum of two bf16 (8 + 3 of the 11 bits, exact), multiplied in turn
+    auto high = [](uint32_t e) { return Elem<true>::from_f16x2(e); };
+    auto low = [](uint32_t e) {
+        const half2_t v = __builtin_bit_cast(half2_t, e);
+        const uint32_t h = Elem<true>::from_f16x2(e);
+        return Elem<true>::pack((float)v.x - __uint_as_float(h << 16), (float)v.y - __uint_as_float(h & 0xFFFF0000u));
     };
+    auto stage_book = [&](const MidRegs<FMT>& r, uint32_t* to) {   // VQ: the tile's codebook as it is multiplied
+        if constexpr (FMT == FMT_VQ6) {
+            if constexpr (SPLIT) *(uint2_t*)(to + 2 * lane) = uint2_t{high(r.cb), low(r.cb)};
+            else to[lane] = Elem<BF16>::from_f16x2(r.cb);
+        }
+        if constexpr (FMT == FMT_VQ8) {
+            const uint32_t c[4] = {r.cb8.x, r.cb8.y, r.cb8.z, r.cb8.w};
+            if constexpr (SPLIT) {
+                *(uint4_t*)(to + 8 * lane) = uint4_t{high(c[0]), low(c[0]), high(c[1]), low(c[1])};
+                *(uint4_t*)(to + 8 * lane + 4) = uint4_t{high(c[2]), low(c[2]), high(c[3]), low(c[3])};
+            } else {
+                *(uint4_t*)(to + 4 * lane) = uint4_t{Elem<BF16>::from_f16x2(c[0]), Elem<BF16>::from_f16x2(c[1]), Elem<BF16>::from_f16x2(c[2]), Elem<BF16>::from_f16x2(c[3])};
+            }
+        }
+    };
+    uint32_t mask, magic;                      // EXACT SQ: in registers (the and-or takes no literals)
+    asm("v_mov_b32 %0, %1" : "=v"(mask) : "n"(BF16 ? 0x00700070 : 0x03800380));
+    asm("s_mov_b32 %0, %1" : "=s"(magic) : "n"(BF16 ? 0x3B003B00 : 0x48004800));
 
     const int row = lane & 15, q = lane >> 4;
-    uint32_t b[2][kMidNF][4];                  // operands of the two halves (32 columns) of a step
+    uint32_t b[2][kMidNF][4], bl[SPLIT ? 2 : 1][kMidNF][4];            // operands of the two halves (32 columns) of a step; SPLIT: low parts
+    // pairs n0 .. n1 - 1 of step H into b[h]
+    auto pairs = [&](auto step, int h, const MidRegs<FMT>& r, int n0, int n1, const uint32_t* book) {
+        constexpr int H = decltype(step)::value;
+        if constexpr (EXACT && SQ) {
+#pragma unroll
+            for (int n = n0; n < n1; ++n) b[h][n >> 2][n & 3] = mid_code_pair<BF16, H>(r, n >> 2, n & 3, mask, magic);
+        } else if constexpr (SPLIT) {
+#pragma unroll
+            for (int n = n0; n < n1; ++n) {
+                const uint2_t e = *(const uint2_t*)(book + 2 * mid_index<FMT, H>(r, n >> 2, n & 3));
+                b[h][n >> 2][n & 3] = e.x;
+                bl[h][n >> 2][n & 3] = e.y;
+            }
+        } else {
+            mid_pairs<BF16, FMT, ROUND, H>(b[h], r, n0, n1, book);
+        }
+    };
+    float4_t part[EXACT && SQ ? MF : 1][kMidNF], X[EXACT && SQ ? MF : 1];   // EXACT SQ: the group's products and activation sums
     MidRegs<FMT> r0, r1;
     int stage = 0;                             // ring slot of the current step
 
@@ -236,33 +317,64 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (SETS == 2 && KQ == 0) { load(r1, j + 1); __builtin_amdgcn_sched_barrier(0); }
     };
+    auto operand = [](const uint32_t (&v)[4]) { return uint4_t{v[0], v[1], v[2], v[3]}; };
     auto body = [&](auto tag, int j) {
         constexpr int KQ = decltype(tag)::value;
         const char* xt = ring + stage * kStage;
         stage = stage + 1 < ST ? stage + 1 : 0;
         const char* const p[2] = {xt + tile_off(row, q), xt + tile_off(row, 4 + q)};
         // the first operands of a tile: with two register sets they are made during the last half step of the tile before
-        uint32_t* const book = books + (SETS == 2 ? (j & 1) * (kMidBook / 4) : 0);
-        uint32_t* const next = books + (SETS == 2 ? (~j & 1) * (kMidBook / 4) : 0);
+        uint32_t* const book = books + (SETS == 2 ? (j & 1) * (mid_book(EXACT) / 4) : 0);
+        uint32_t* const next = books + (SETS == 2 ? (~j & 1) * (mid_book(EXACT) / 4) : 0);
         if constexpr (SETS == 1 && KQ == 0) {
             stage_book(r0, book);
-            mid_pairs<BF16, FMT, ROUND, 0>(b[0], r0, 0, 4 * kMidNF, book);
+            pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * kMidNF, book);
         }
         if constexpr (SETS == 2 && KQ == 3) stage_book(r1, next);
+        uint32_t szu[kMidNF];                  // EXACT SQ: the group's scale and zero point (one register set: reloaded below)
+        if constexpr (EXACT && SQ) {
+#pragma unroll
+            for (int i = 0; i < kMidNF; ++i) szu[i] = KQ < 2 ? r0.sz[i].x : r0.sz[i].y;
+        }
         uint4_t af[2 * MF];                    // activation fragments, read two rows ahead of their MFMAs
 #pragma unroll
-        for (int f = 0; f < 2; ++f) af[f] = *(const uint4_t*)(p[0] + 16 * f * kRowBytes);
+        for (int f = 0; f < 2; ++f) af[f] = *(const uint4_t*)(p[f / MF] + 16 * (f % MF) * kRowBytes);
 #pragma unroll
         for (int f = 0; f < 2 * MF; ++f) {
             const int h = f / MF, fm = f % MF;
             if (f + 2 < 2 * MF) af[f + 2] = *(const uint4_t*)(p[(f + 2) / MF] + 16 * ((f + 2) % MF) * kRowBytes);
+            if constexpr (EXACT && SQ) {
+                const bool first = KQ % 2 == 0 && h == 0;
+                const float4_t zero = {0, 0, 0, 0};
 #pragma unroll
-            for (int i = 0; i < kMidNF; ++i)
-                acc[fm][i] = mid_mfma<BF16>(uint4_t{b[h][i][0], b[h][i][1], b[h][i][2], b[h][i][3]}, af[f], acc[fm][i]);
+                for (int i = 0; i < kMidNF; ++i) part[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), first ? zero : part[fm][i]);
+                const uint32_t one = BF16 ? 0x39803980u : 0x3C003C00u;
+                X[fm] = mid_mfma<BF16>(af[f], uint4_t{one, one, one, one}, first ? zero : X[fm]);
+            } else if constexpr (EXACT) {      // x first: a lane holds one row of W and four rows of x, as its scale and zero point are laid out
+#pragma unroll
+                for (int i = 0; i < kMidNF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), acc[fm][i]);
+                if constexpr (SPLIT) {
+#pragma unroll
+                    for (int i = 0; i < kMidNF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(bl[h][i]), acc[fm][i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kMidNF; ++i) acc[fm][i] = mid_mfma<BF16>(operand(b[h][i]), af[f], acc[fm][i]);
+            }
             const int n0 = 4 * kMidNF * fm / MF, n1 = 4 * kMidNF * (fm + 1) / MF;
-            if (h == 0) mid_pairs<BF16, FMT, ROUND, 2 * KQ + 1>(b[1], r0, n0, n1, book);
-            else if constexpr (KQ < 3) mid_pairs<BF16, FMT, ROUND, 2 * KQ + 2>(b[0], r0, n0, n1, book);
-            else if constexpr (SETS == 2) mid_pairs<BF16, FMT, ROUND, 0>(b[0], r1, n0, n1, next);
+            if (h == 0) pairs(std::integral_constant<int, 2 * KQ + 1>{}, 1, r0, n0, n1, book);
+            else if constexpr (KQ < 3) pairs(std::integral_constant<int, 2 * KQ + 2>{}, 0, r0, n0, n1, book);
+            else if constexpr (SETS == 2) pairs(std::integral_constant<int, 0>{}, 0, r1, n0, n1, next);
+            if constexpr (EXACT && SQ) {       // the group is complete: into the output
+                if (KQ % 2 == 1 && h == 1) {
+#pragma unroll
+                    for (int i = 0; i < kMidNF; ++i) {
+                        const float s = f16_bits_to_f32((uint16_t)(szu[i] & 0xFFFFu)) * (BF16 ? 4096.0f : 1.0f), z8 = f16_bits_to_f32((uint16_t)(szu[i] >> 16)) + 8.0f;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[fm][i][e] = fmaf(s, fmaf(-z8, X[fm][e], part[fm][i][e]), acc[fm][i][e]);
+                    }
+                }
+            }
             if (SETS == 1 && KQ == 3 && f == MF - 1) load(r0, j + 1);   // the packed words are spent
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -274,7 +386,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         for (int i = 0; i < AHEAD; ++i) copy(i, i);
         if constexpr (SETS == 2) {
             stage_book(r0, books);
-            mid_pairs<BF16, FMT, ROUND, 0>(b[0], r0, 0, 4 * kMidNF, books);
+            pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * kMidNF, books);
         }
     }
     for (int j = 0; j < nt; ++j) {             // nothing conditional inside: the compiler then counts the loads in flight exactly
@@ -293,7 +405,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
     mid_wait<0>();                             // no copy may still land in LDS below
 }
 
-template <bool BF16, int MF, int NW>
+template <bool BF16, int MF, int NW, bool EXACT>
 __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     constexpr int KW = kMidWaves / NW;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -312,13 +424,13 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
         for (int i = 0; i < kMidNF; ++i) acc[f][i] = float4_t{0, 0, 0, 0};
     if (mt.fmt == FMT_SQ3) {
         const int KT = mt.K >> 8;
-        if (mid_small_zero((const uint2_t*)mt.aux + (size_t)(n0 >> 4) * KT * 16, kMidNF * NW * KT * 128, threadIdx.x, (uint32_t*)lds))
-            mid_loop<BF16, FMT_SQ3, true, MF, NW>(a, mt, lds, m0, n0, wave, lane, acc);
-        else mid_loop<BF16, FMT_SQ3, false, MF, NW>(a, mt, lds, m0, n0, wave, lane, acc);
+        if (!EXACT && mid_small_zero((const uint2_t*)mt.aux + (size_t)(n0 >> 4) * KT * 16, kMidNF * NW * KT * 128, threadIdx.x, (uint32_t*)lds))
+            mid_loop<BF16, FMT_SQ3, true, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
+        else mid_loop<BF16, FMT_SQ3, false, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
     } else if (mt.fmt == FMT_VQ6) {
-        mid_loop<BF16, FMT_VQ6, false, MF, NW>(a, mt, lds, m0, n0, wave, lane, acc);
+        mid_loop<BF16, FMT_VQ6, false, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
     } else {
-        mid_loop<BF16, FMT_VQ8, false, MF, NW>(a, mt, lds, m0, n0, wave, lane, acc);
+        mid_loop<BF16, FMT_VQ8, false, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
     }
 
     // The K groups' partial sums meet in LDS, four rows of subtiles at a time; each group adds up and stores one of the rows
@@ -334,7 +446,7 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
 #pragma unroll
             for (int i = 0; i < kMidNF; ++i) *(float4_t*)(lds + ((wave * PR + f) * kMidNF + i) * 1024 + 16 * lane) = acc[PR * ps + f][i];
         __syncthreads();
-        const int f = kg / SH, m = m0 + 16 * (PR * ps + f) + (lane & 15);
+        const int f = kg / SH, m = m0 + 16 * (PR * ps + f) + (EXACT ? 4 * (lane >> 4) : lane & 15);
         if (PR * ps + f < MF && m < a.M) {
 #pragma unroll
             for (int ii = 0; ii < kMidNF / SH; ++ii) {
@@ -345,6 +457,13 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
                     const float4_t o = *(const float4_t*)(lds + (((g * NW + nw) * PR + f) * kMidNF + i) * 1024 + 16 * lane);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] += o[e];
+                }
+                if constexpr (EXACT) {
+                    const int n = n0 + 16 * kMidNF * nw + 16 * i + (lane & 15);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n < mt.N && m + e < a.M) store_from_f32(mt.y, (size_t)(m + e) * mt.N + n, a.ydt, v[e]);
+                    continue;
                 }
                 const size_t o = (size_t)m * mt.N + n0 + 16 * kMidNF * nw + 16 * i + 4 * (lane >> 4);
                 if (a.ydt == DT_F32) {
@@ -360,7 +479,7 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     }
 }
 
-template <bool BF16, int MF, int NW>
+template <bool BF16, int MF, int NW, bool EXACT>
 static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
     static std::atomic<unsigned long long> raised{0ull};        // bit d: the LDS limit was raised on device d
     int dev = 0;
@@ -368,19 +487,24 @@ static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
     if (e != hipSuccess) return e;
     const unsigned long long bit = 1ull << (dev & 63);
     if (!(raised.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute((const void*)mid_kernel<BF16, MF, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, mid_lds(MF, NW));
+        e = hipFuncSetAttribute((const void*)mid_kernel<BF16, MF, NW, EXACT>, hipFuncAttributeMaxDynamicSharedMemorySize, mid_lds(MF, NW, EXACT));
         if (e != hipSuccess) return e;
         raised.fetch_or(bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL((mid_kernel<BF16, MF, NW>), dim3(wgs), dim3(64 * kMidWaves), mid_lds(MF, NW), s, a);
+    hipLaunchKernelGGL((mid_kernel<BF16, MF, NW, EXACT>), dim3(wgs), dim3(64 * kMidWaves), mid_lds(MF, NW, EXACT), s, a);
     return hipGetLastError();
 }
 template <bool BF16>
-static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, int wgs, hipStream_t s) {
-    if (nw == 1) return launch_mid_t<BF16, 4, 1>(a, wgs, s);
-    if (mf == 4) return launch_mid_t<BF16, 4, 2>(a, wgs, s);
-    if (mf == 6) return launch_mid_t<BF16, 6, 2>(a, wgs, s);
-    return launch_mid_t<BF16, 8, 2>(a, wgs, s);
+static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, bool exact, int wgs, hipStream_t s) {
+    if (exact) {
+        if (mf == 2) return launch_mid_t<BF16, 2, 1, true>(a, wgs, s);
+        if (mf == 3) return launch_mid_t<BF16, 3, 1, true>(a, wgs, s);
+        return launch_mid_t<BF16, 4, 1, true>(a, wgs, s);
+    }
+    if (nw == 1) return launch_mid_t<BF16, 4, 1, false>(a, wgs, s);
+    if (mf == 4) return launch_mid_t<BF16, 4, 2, false>(a, wgs, s);
+    if (mf == 6) return launch_mid_t<BF16, 6, 2, false>(a, wgs, s);
+    return launch_mid_t<BF16, 8, 2, false>(a, wgs, s);
 }
 
 // Rows of x and of W per workgroup for a launch over `rows` rows of W.  One workgroup runs per compute unit; a round of
@@ -399,7 +523,7 @@ static void pick_mid(int M, long long rows, int* mf, int* nw) {
     if (M <= 128 && rows / 64 * ((M + 63) / 64) <= 256) { *mf = 4; *nw = 1; }
 }
 
-hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, bool exact, hipStream_t s) {
     for (int base = 0; base < n_mats; base += kMidMaxMats) {
         MidArgs a;
         const int cnt = std::min(kMidMaxMats, n_mats - base);
@@ -407,13 +531,18 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
         long long rows = 0;
         for (int i = 0; i < cnt; ++i) { order[i] = base + i; rows += mats[base + i].N; }
         std::stable_sort(order, order + cnt, [&](int p, int q) { return mats[p].K > mats[q].K; });   // long workgroups first
-        pick_mid(M, rows, &mf, &nw);
+        if (exact) {                           // even rows over the fewest workgroups of at most 64
+            const int tiles = (M + 63) / 64;
+            nw = 1;
+            mf = std::max(2, ((M + tiles - 1) / tiles + 15) / 16);
+        }
+        else pick_mid(M, rows, &mf, &nw);
         a.m_tiles = (M + 16 * mf - 1) / (16 * mf);
         int wgs = 0;
         for (int i = 0; i < kMidMaxMats; ++i) {
             if (i < cnt) {
                 const MatDev& m = mats[order[i]];
-                wgs += a.m_tiles * (m.N / (16 * kMidNF * nw));
+                wgs += a.m_tiles * ((m.N + 16 * kMidNF * nw - 1) / (16 * kMidNF * nw));
                 a.m[i] = MidMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, 0};
                 a.wg_end[i] = wgs;
             } else {
@@ -422,7 +551,7 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
             }
         }
         a.M = M; a.ydt = y_dtype; a.pad = 0;
-        const hipError_t e = x_dtype == DT_BF16 ? launch_mid_shape<true>(a, mf, nw, wgs, s) : launch_mid_shape<false>(a, mf, nw, wgs, s);
+        const hipError_t e = x_dtype == DT_BF16 ? launch_mid_shape<true>(a, mf, nw, exact, wgs, s) : launch_mid_shape<false>(a, mf, nw, exact, wgs, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

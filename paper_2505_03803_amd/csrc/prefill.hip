@@ -571,7 +571,7 @@ static hipError_t launch_prefill_tiles(const MatDev* mats_in, int n_mats, int M,
 hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
     std::vector<MatDev> mid, tiles;
     for (int i = 0; i < n_mats; ++i) (mid_rows(mats[i], M) ? mid : tiles).push_back(mats[i]);
-    hipError_t e = mid.empty() ? hipSuccess : launch_mid(mid.data(), (int)mid.size(), M, x_dtype, y_dtype, s);
+    hipError_t e = mid.empty() ? hipSuccess : launch_mid(mid.data(), (int)mid.size(), M, x_dtype, y_dtype, false, s);
     if (e == hipSuccess && !tiles.empty()) e = launch_prefill_tiles(tiles.data(), (int)tiles.size(), M, x_dtype, y_dtype, s);
     return e;
 }

@@ -80,3 +80,35 @@ def test_one_hot_rows_return_the_rounded_weights(xdt, small, options):
         x[np.arange(M), cols] = 1.0
         bits = synth.f32_to_bf16_bits(x) if xdt == "bf16" else synth.f32_to_f16_bits(x)
         assert np.array_equal(G.gpu_gemm(dm, bits, xdt), want[:, cols].T.astype(np.float64)), M
+
+
+# 17 to 64 rows of x per workgroup and the first of the next, two workgroups of 48 and of 64; rows of W that end inside a
+# workgroup's 64 (SQ); 1, 3, 9 and 10 column tiles on eight K groups
+@pytest.mark.parametrize("fmt,N,K", [("sq", 176, 768), ("sq", 272, 2560), ("sq", 16, 256), ("vq6", 256, 2304), ("vq6", 512, 256), ("vq8", 256, 2560), ("vq8", 256, 768)])
+@pytest.mark.parametrize("M", [17, 32, 33, 48, 49, 64, 65, 97, 128])
+@pytest.mark.parametrize("xdt", ["bf16", "f16"])
+def test_unrounded_weights(fmt, N, K, M, xdt, options):
+    """The streaming path's contract (products of the unrounded weights) at 17 <= M <= 128."""
+    print(f"mid exact {fmt} N={N} K={K} M={M} x={xdt}", flush=True)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    mat = make(fmt, N, K, 12)
+    x = synth.gen_activations(np.random.default_rng(M), M, K, xdt)
+    got = G.gpu_gemm(B.upload(mat, native=True), x, xdt)
+    # binary32 sums of up to 2560 products, as for the streaming kernels
+    assert G.err_g2(got, orc.linear(mat, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
+@pytest.mark.parametrize("fmt", ["sq", "vq6", "vq8"])
+@pytest.mark.parametrize("scale", [1e-20, 1e30, 1.5e38])
+def test_unrounded_weights_at_the_ends_of_bf16(fmt, scale, options):
+    """Rows of bf16 activations far from one: their group sums stay finite and as exact as at one."""
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    N, K, M = 256, 512, 20
+    mat = make(fmt, N, K, 13)
+    x = np.random.default_rng(3).uniform(-1, 1, (M, K)).astype(np.float32) * np.float32(scale)
+    if fmt != "sq":
+        x *= np.float32(2.0 ** -4)                           # entries of 0.02: no output beyond binary32
+    bits = synth.f32_to_bf16_bits(x)
+    got = G.gpu_gemm(B.upload(mat, native=True), bits, "bf16")
+    assert np.all(np.isfinite(got))
+    assert G.err_g2(got, orc.linear(mat, orc.widen(bits, "bf16"), "f64")) <= 2e-5
