@@ -17,53 +17,123 @@
 namespace rwkvq {
 
 // ---------------------------------------------------------------------------------- clip_mean
-// The order statistics are found by rank counting (rank of sample i = number of samples that sort
-// before it, ties by sample index): B^2 comparisons per position.  B is a calibration batch (128 in
-// Sec. 4).
-//
-// clip_mean_tile_kernel<P>: a workgroup takes P consecutive positions and stages all B samples of them
-// in LDS (B x P floats); thread (position p, group g) ranks the samples g, g + G, ... of its position
-// against all B (LDS reads of one row of the tile per step: consecutive banks), the four order
-// statistics the percentiles need are left in LDS by whichever thread finds them, and one thread per
-// position then forms the clipped mean as a binary64 sum in sample order.  The same comparisons and the
-// same sum as the plain kernel below, which remains for batches too large for the tile.
-template <int P>
-__global__ void __launch_bounds__(256) clip_mean_tile_kernel(const void* __restrict__ x, int dt, int B, int n, int k_lo,
-                                                             double f_lo, int k_hi, double f_hi, float* __restrict__ out) {
-    extern __shared__ float tile[];                  // [B][P]
-    __shared__ float stat[4][P];
-    constexpr int G = 256 / P;
-    const int tid = threadIdx.x, p = tid % P, g = tid / P;
-    const int j0 = blockIdx.x * P, j = j0 + p;
-    const bool live = j < n;
-    for (int b = g; b < B; b += G) tile[b * P + p] = live ? load_as_f32(x, (size_t)b * n + j, dt) : 0.f;
-    __syncthreads();
-    const int k_lo1 = k_lo + 1 < B ? k_lo + 1 : B - 1, k_hi1 = k_hi + 1 < B ? k_hi + 1 : B - 1;
-    for (int i = g; i < B; i += G) {
-        const float vi = tile[i * P + p];
-        int rank = 0;
-        for (int b = 0; b < B; ++b) {
-            const float vb = tile[b * P + p];
-            rank += (vb < vi || (vb == vi && b < i)) ? 1 : 0;
+// clip_mean_select_kernel<NS> (B <= 16 NS): a workgroup takes 16 consecutive positions, sixteen lanes (a DPP row) each; a
+// lane holds NS samples of its position as order-preserving keys.  The percentiles need order statistics by value only (ties
+// have one value), so the k-th is built bit by bit: bit t of it is set when at most k keys lie below the prefix with that
+// bit - a count over the row per bit, 16 bits for 16-bit samples, 32 for binary32, both percentiles in one count.  Its
+// successor is the same value again or the least key above.  One thread per position then forms the clipped mean as a binary64
+// sum in sample order.  Ranking every sample by B comparisons (the kernel this replaces: 64 workgroups for 4096 positions, B^2
+// comparisons each position) took 119 us for 128 x 4096 bf16 samples, this 8.8 us: the chain of 128 binary64 additions and
+// the trips to memory are what is left.
+constexpr int kClipP = 16;                           // positions per workgroup
+__device__ __forceinline__ int clip_at(int b, int p) { return b * kClipP + (p ^ (b & 15)); }   // sixteen samples of a position: sixteen banks
+__device__ __forceinline__ int row_sum(int v) {      // over the sixteen lanes of a DPP row, in every lane
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);      // quad_perm [1, 0, 3, 2]
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);      // quad_perm [2, 3, 0, 1]
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);     // row_half_mirror
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t row_min(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));
+    return min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));
+}
+template <int NS>
+__global__ void __launch_bounds__(256) clip_mean_select_kernel(const void* __restrict__ x, int dt, int B, int n, int k_lo,
+                                                               double f_lo, int k_hi, double f_hi, float* __restrict__ out) {
+    extern __shared__ uint32_t tile[];               // [B][16] bit patterns (16-bit samples: in the high half)
+    __shared__ float stat[4][kClipP];
+    const int tid = threadIdx.x, j0 = blockIdx.x * kClipP;
+    {
+        // all of a thread's loads before the first store (one trip to memory instead of B / 16)
+        const int p = tid % kClipP, j = min(j0 + p, n - 1), b0 = tid / kClipP;
+        constexpr int kAt = NS < 16 ? NS : 16;
+        for (int i0 = 0; i0 < NS; i0 += kAt) {
+            uint32_t v[kAt];
+            if (dt == DT_F32) {
+#pragma unroll
+                for (int i = 0; i < kAt; ++i) v[i] = ((const uint32_t*)x)[(size_t)min(b0 + 16 * (i0 + i), B - 1) * n + j];
+            } else {
+#pragma unroll
+                for (int i = 0; i < kAt; ++i) v[i] = ((const uint16_t*)x)[(size_t)min(b0 + 16 * (i0 + i), B - 1) * n + j];
+            }
+#pragma unroll
+            for (int i = 0; i < kAt; ++i) {
+                const int b = b0 + 16 * (i0 + i);
+                if (b < B) tile[clip_at(b, p)] = dt == DT_F32 ? v[i] : v[i] << 16;
+            }
         }
-        if (rank == k_lo) stat[0][p] = vi;
-        if (rank == k_lo1) stat[1][p] = vi;
-        if (rank == k_hi) stat[2][p] = vi;
-        if (rank == k_hi1) stat[3][p] = vi;
     }
     __syncthreads();
-    if (g == 0 && live) {
-        const float v_lo = stat[0][p], v_lo1 = stat[1][p], v_hi = stat[2][p], v_hi1 = stat[3][p];
-        const double lo = __dadd_rn((double)v_lo, __dmul_rn(f_lo, __dsub_rn((double)v_lo1, (double)v_lo)));
-        const double hi = __dadd_rn((double)v_hi, __dmul_rn(f_hi, __dsub_rn((double)v_hi1, (double)v_hi)));
+    const int p = tid >> 4, l = tid & 15;
+    uint32_t key[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int b = l + 16 * i;
+        const uint32_t v = tile[clip_at(min(b, B - 1), p)];
+        const uint32_t k = (v & 0x80000000u) ? ~v & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u) : v | 0x80000000u;
+        key[i] = b < B ? k : 0xFFFFFFFFu;            // above every finite sample
+    }
+    uint32_t lo = 0, hi = 0;                         // keys of the k_lo-th and k_hi-th sample
+    for (int bit = 31; bit >= (dt == DT_F32 ? 0 : 16); --bit) {
+        const uint32_t tl = lo | (1u << bit), th = hi | (1u << bit);
+        int c = 0;                                   // samples below tl, and below th in the high half
+#pragma unroll
+        for (int i = 0; i < NS; ++i) c += (key[i] < tl ? 1 : 0) + (key[i] < th ? 0x10000 : 0);
+        c = row_sum(c);
+        if ((c & 0xFFFF) <= k_lo) lo = tl;
+        if ((c >> 16) <= k_hi) hi = th;
+    }
+    int at_most = 0;
+    uint32_t next_lo = 0xFFFFFFFFu, next_hi = 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        at_most += (key[i] <= lo ? 1 : 0) + (key[i] <= hi ? 0x10000 : 0);
+        if (key[i] > lo) next_lo = min(next_lo, key[i]);
+        if (key[i] > hi) next_hi = min(next_hi, key[i]);
+    }
+    at_most = row_sum(at_most);
+    next_lo = row_min(next_lo);
+    next_hi = row_min(next_hi);
+    if ((at_most & 0xFFFF) > k_lo + 1 || k_lo + 1 >= B) next_lo = lo;
+    if ((at_most >> 16) > k_hi + 1 || k_hi + 1 >= B) next_hi = hi;
+    auto value = [&](uint32_t k) {
+        const uint32_t v = (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u);
+        return dt == DT_F32 ? __uint_as_float(v) : dt == DT_BF16 ? __uint_as_float(v) : f16_bits_to_f32((uint16_t)(v >> 16));
+    };
+    if (l == 0) { stat[0][p] = value(lo); stat[1][p] = value(next_lo); stat[2][p] = value(hi); stat[3][p] = value(next_hi); }
+    __syncthreads();
+    const double f_v = (double)stat[0][p], f_w = (double)stat[2][p];
+    const double dlo = __dadd_rn(f_v, __dmul_rn(f_lo, __dsub_rn((double)stat[1][p], f_v)));
+    const double dhi = __dadd_rn(f_w, __dmul_rn(f_hi, __dsub_rn((double)stat[3][p], f_w)));
+    auto clipped = [&](uint32_t w, double at_least, double at_most) {
+        double v = (double)(dt == DT_F16 ? f16_bits_to_f32((uint16_t)(w >> 16)) : __uint_as_float(w));
+        v = v < at_least ? at_least : v;
+        return v > at_most ? at_most : v;
+    };
+    // The sum is in sample order, one binary64 addition after another: clipped by all threads first, so that the one thread
+    // per position only adds (14 -> 8.8 us; B <= 256, the doubles of more would not fit).
+    double* const limited = (double*)(tile + B * kClipP);
+    if constexpr (NS <= 16) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (l + 16 * i < B) limited[clip_at(l + 16 * i, p)] = clipped(tile[clip_at(l + 16 * i, p)], dlo, dhi);
+    } else {
+        if (l == 0) { limited[p] = dlo; limited[kClipP + p] = dhi; }
+    }
+    __syncthreads();
+    if (tid < kClipP && j0 + tid < n) {
         double acc = 0.0;
-        for (int b = 0; b < B; ++b) {                   // sample order: the sum is reproducible
-            double v = (double)tile[b * P + p];
-            v = v < lo ? lo : v;
-            v = v > hi ? hi : v;
-            acc = __dadd_rn(acc, v);
+        if constexpr (NS <= 16) {
+#pragma unroll 16
+            for (int b = 0; b < B; ++b) acc = __dadd_rn(acc, limited[clip_at(b, tid)]);
+        } else {
+            const double at_least = limited[tid], at_most = limited[kClipP + tid];
+#pragma unroll 8
+            for (int b = 0; b < B; ++b) acc = __dadd_rn(acc, clipped(tile[clip_at(b, tid)], at_least, at_most));
         }
-        out[j] = (float)(acc / (double)B);
+        out[j0 + tid] = (float)(acc / (double)B);
     }
 }
 
@@ -101,13 +171,14 @@ __global__ void __launch_bounds__(256) clip_mean_kernel(const void* __restrict__
 
 hipError_t launch_clip_mean(const void* x, int dt, int B, int n, int k_lo, double f_lo, int k_hi, double f_hi,
                             float* out, hipStream_t s) {
-    // the tile of B x P floats has to fit 64 KB of LDS: 64 positions per workgroup up to B = 256, 16 up to 1024
-    if (B <= 256)
-        hipLaunchKernelGGL(clip_mean_tile_kernel<64>, dim3((n + 63) / 64), dim3(256), (size_t)B * 64 * 4, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
-    else if (B <= 1024)
-        hipLaunchKernelGGL(clip_mean_tile_kernel<16>, dim3((n + 15) / 16), dim3(256), (size_t)B * 16 * 4, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
-    else
-        hipLaunchKernelGGL(clip_mean_kernel, dim3((n + 255) / 256), dim3(256), 0, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    // the tile of B x 16 words (with 512 bytes of order statistics and limits) has to fit 64 KB of LDS: B <= 1016
+    const dim3 grid((n + kClipP - 1) / kClipP), wg(256);
+    const size_t lds = (size_t)B * kClipP * 4 + (B <= 256 ? (size_t)B * kClipP * 8 : 2 * kClipP * 8);
+    if (B <= 64) hipLaunchKernelGGL(clip_mean_select_kernel<4>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else if (B <= 128) hipLaunchKernelGGL(clip_mean_select_kernel<8>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else if (B <= 256) hipLaunchKernelGGL(clip_mean_select_kernel<16>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else if (B <= 1016) hipLaunchKernelGGL(clip_mean_select_kernel<64>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else hipLaunchKernelGGL(clip_mean_kernel, dim3((n + 255) / 256), dim3(256), 0, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     return hipGetLastError();
 }
 
@@ -134,21 +205,36 @@ __device__ __forceinline__ uint16_t f64_to_f16_bits(double d) {
 }
 
 // One workgroup per weight tensor.  The vectors go through LDS in chunks of 2048: every vector of a chunk is
-// assigned to its cheapest entry (index, weight and value staged in LDS), then the sums of an entry's
-// coordinate are continued by S = 1024 / (2 E) threads, each over a contiguous share of the chunk in index
-// order; after the last chunk the S partial sums are added in share order.  Binary64 sums in a fixed order:
-// a call gives the same codebook every time.
+// assigned to its cheapest entry, then the sums of an entry's coordinate are continued by S = 1024 / (2 E) threads, each
+// over a contiguous share of the chunk in index order; after the last chunk the S partial sums are added in share order.
+// Binary64 sums in a fixed order: a call gives the same codebook every time.
+// A share's vectors are first put in order of their entries (stable, so an entry's vectors keep index order): one wavefront
+// per share counts rounds of 64 with ballots over the entry's bits, a running sum over the entries gives their first slots.
+// A thread then adds only its entry's vectors; scanning the whole share for them (what this replaces) was most of the time:
+// 28 tensors of 4096 weights, 64 entries, 10 iterations 290 -> 131 us.
+__device__ __forceinline__ unsigned long long same_entry_lanes(uint32_t e, int bits, bool valid) {
+    unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
+    for (int b = 0; b < bits; ++b) {
+        const bool bit = (e >> b) & 1u;
+        const unsigned long long set = __builtin_amdgcn_ballot_w64(bit);
+        m &= bit ? set : ~set;
+    }
+    return m;
+}
 template <int E>
 __global__ void __launch_bounds__(1024) mu_kmeans_kernel(MuArgs a) {
-    constexpr int S = 1024 / (2 * E);                 // threads per (entry, coordinate)
+    constexpr int S = 1024 / (2 * E);                 // threads per (entry, coordinate) = shares of a chunk
     constexpr int kChunk = 2048, kPer = kChunk / S;   // vectors per chunk and per share
-    constexpr int kRow = kPer + 1;                    // padded: the S shares of a chunk start in different LDS banks
+    constexpr int kBits = E == 64 ? 6 : 8;
+    static_assert(S <= 16 && kPer % 64 == 0, "a wavefront per share, rounds of 64 vectors");
     __shared__ float cb[E][2];
-    __shared__ uint32_t s_idx[S * kRow];
-    __shared__ float s_m[S * kRow][2], s_w[S * kRow][2];
+    __shared__ uint16_t s_idx[kChunk], s_at[kChunk];  // entry of a vector; vectors of a share in order of their entries
+    __shared__ float s_m[kChunk][2], s_w[kChunk][2];
+    __shared__ uint32_t first[S][E];                  // a share's first slot of an entry; while counting: vectors seen
+    __shared__ uint32_t count[S][E];
     __shared__ double num[2 * E][S], den[2 * E][S];
     const MuTensor t = a.t[blockIdx.x];
-    const int V = t.n >> 1, tid = threadIdx.x;
+    const int V = t.n >> 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int e = tid; e < E; e += 1024) {
         cb[e][0] = f16_bits_to_f32(t.cb[2 * e]);
         cb[e][1] = f16_bits_to_f32(t.cb[2 * e + 1]);
@@ -159,40 +245,77 @@ __global__ void __launch_bounds__(1024) mu_kmeans_kernel(MuArgs a) {
         const bool last = it == a.iters;
         double sn = 0.0, sd = 0.0;
         for (int c0 = 0; c0 < V; c0 += kChunk) {
+            const int in_chunk = V - c0 < kChunk ? V - c0 : kChunk;
 #pragma unroll
             for (int h = 0; h < kChunk / 1024; ++h) {
                 const int vl = h * 1024 + tid, v = c0 + vl;
-                const int slot = (vl / kPer) * kRow + vl % kPer;
                 if (v < V) {
                     const float m0 = load_as_f32(t.mu, 2 * (size_t)v, a.dt), m1 = load_as_f32(t.mu, 2 * (size_t)v + 1, a.dt);
                     const float x0 = t.xbar[2 * (size_t)v], x1 = t.xbar[2 * (size_t)v + 1];
                     const float w0 = __fmul_rn(x0, x0), w1 = __fmul_rn(x1, x1);
                     int best = 0;
                     float bestc = __builtin_inff();
+#pragma unroll 4
                     for (int e = 0; e < E; ++e) {
                         const float t0 = __fsub_rn(m0, cb[e][0]), t1 = __fsub_rn(m1, cb[e][1]);
                         const float c = __fadd_rn(__fmul_rn(w0, __fmul_rn(t0, t0)), __fmul_rn(w1, __fmul_rn(t1, t1)));
                         if (c < bestc) { bestc = c; best = e; }
                     }
                     if (last) t.idx[v] = (uint8_t)best;
-                    s_idx[slot] = (uint32_t)best;
-                    s_m[slot][0] = m0; s_m[slot][1] = m1; s_w[slot][0] = w0; s_w[slot][1] = w1;
-                } else {
-                    s_idx[slot] = 0xFFFFFFFFu;       // past the end: matches no entry
+                    s_idx[vl] = (uint16_t)best;
+                    s_m[vl][0] = m0; s_m[vl][1] = m1; s_w[vl][0] = w0; s_w[vl][1] = w1;
                 }
             }
             if (last) continue;                       // the final pass only assigns
+            if (tid < S * E) (&count[0][0])[tid] = 0u;
+            __syncthreads();
+            if (wave < S) {                           // order share `wave` by entries
+                uint32_t e[kPer / 64], rank[kPer / 64];
+#pragma unroll
+                for (int r = 0; r < kPer / 64; ++r) {
+                    const int vl = wave * kPer + 64 * r + lane;
+                    const bool valid = vl < in_chunk;
+                    e[r] = valid ? s_idx[vl] : 0u;
+                    const unsigned long long m = same_entry_lanes(e[r], kBits, valid);
+                    const uint32_t below = (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull)), old = count[wave][e[r]];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // a wavefront's LDS accesses are served in order
+                    __builtin_amdgcn_wave_barrier();
+                    if (valid && below == 0u) count[wave][e[r]] = old + (uint32_t)__builtin_popcountll(m);
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    rank[r] = old + below;
+                }
+                uint32_t run = 0;                     // first slots: running sum over the entries, 64 at a time
+#pragma unroll
+                for (int e0 = 0; e0 < E; e0 += 64) {
+                    const uint32_t c = count[wave][e0 + lane];
+                    uint32_t incl = c;
+#pragma unroll
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const uint32_t up = __shfl_up(incl, off, 64);
+                        if (lane >= off) incl += up;
+                    }
+                    first[wave][e0 + lane] = run + incl - c;
+                    run += __shfl(incl, 63, 64);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+                for (int r = 0; r < kPer / 64; ++r) {
+                    const int vl = wave * kPer + 64 * r + lane;
+                    if (vl < in_chunk) s_at[wave * kPer + first[wave][e[r]] + rank[r]] = (uint16_t)vl;
+                }
+            }
             __syncthreads();
             {
-                const uint32_t e = (uint32_t)(pair >> 1);
                 const int c = pair & 1;
-                for (int i = 0; i < kPer; ++i) {
-                    const int slot = seg * kRow + i;
-                    const bool mine = s_idx[slot] == e;
-                    const double w = (double)s_w[slot][c];
-                    // the product of two binary32 values is exact in binary64; vectors of other entries add +0
-                    sn += mine ? w * (double)s_m[slot][c] : 0.0;
-                    sd += mine ? w : 0.0;
+                const uint32_t at = seg * kPer + first[seg][pair >> 1], cnt = count[seg][pair >> 1];
+                for (uint32_t i = 0; i < cnt; ++i) {
+                    const int vl = s_at[at + i];
+                    const double w = (double)s_w[vl][c];
+                    sn += w * (double)s_m[vl][c];    // the product of two binary32 values is exact in binary64
+                    sd += w;
                 }
             }
             __syncthreads();

@@ -1,0 +1,63 @@
+"""Edges of the calibration kernels: batch sizes on both sides of each instance of the order-statistic selection, samples with
+ties, zeros of both signs and the largest finite values; a codebook whose vectors all fall to a few entries."""
+import numpy as np
+import pytest
+
+from oracle import mu_oracle as MO
+from oracle import rwkvq_oracle as orc
+from paper_2505_03803_amd import binding as B
+from paper_2505_03803_amd import synth
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    a = np.ascontiguousarray(a)
+    return G.torch_().from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).cuda()
+
+
+@pytest.mark.parametrize("Bn", [2, 16, 17, 64, 65, 128, 129, 256, 257, 1016, 1017])
+@pytest.mark.parametrize("dt", ["bf16", "f16", "f32"])
+def test_clip_mean_instances(Bn, dt):
+    torch = G.torch_()
+    rng = np.random.default_rng(Bn)
+    n = 33                                                    # two workgroups of positions and one more
+    x = synth.gen_calibration(rng, Bn, n, dt)
+    big = {"f16": 0x7BFF, "bf16": 0x7F7F}.get(dt)
+    if dt == "f32":
+        x[:, 0] = np.float32(0.25)                            # constant
+        x[:, 1] = np.where(np.arange(Bn) % 3 == 0, np.float32(-0.0), np.float32(0.0))
+        x[:, 2] = np.where(np.arange(Bn) % 2 == 0, np.finfo(np.float32).max / 2048, -np.finfo(np.float32).max / 2048)
+        x[:, 3] = np.round(x[:, 3])                           # many ties
+    else:
+        x[:, 0] = x[0, 0]
+        x[:, 1] = np.where(np.arange(Bn) % 3 == 0, 0x8000, 0)
+        x[:, 2] = np.where(np.arange(Bn) % 2 == 0, big, big | 0x8000) if dt == "f16" else np.where(np.arange(Bn) % 2 == 0, 0x7900, 0xF900)
+        x[:, 3] = x[rng.integers(0, min(Bn, 4), Bn), 3]
+    out = torch.empty(n, dtype=torch.float32, device="cuda")
+    for p in (0.0, 1.0, 33.0, 50.0):
+        B.rwkvq_clip_mean(dev(x), B.DTYPES[dt], Bn, n, p, out)
+        torch.cuda.synchronize()
+        want = MO.clip_mean(x if dt == "f32" else orc.widen(x, dt), p)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), p
+
+
+@pytest.mark.parametrize("kbits", [6, 8])
+def test_codebook_with_crowded_entries(kbits):
+    """Constant weights (every vector to one entry), two values, and sizes around a share (256 or 1024 vectors) and a chunk (2048)."""
+    torch = G.torch_()
+    rng = np.random.default_rng(kbits)
+    E = 1 << kbits
+    for n in (2, 510, 514, 2050, 4094, 4098, 8192):
+        for kind in range(2):
+            m = np.full(n, 0.37, np.float32) if kind == 0 else np.where(rng.random(n) < 0.9, np.float32(0.2), np.float32(0.8))
+            x = rng.standard_normal(n).astype(np.float32)
+            cb0 = synth.gen_codebook(rng, E).reshape(E, 2)
+            cb, idx = dev(cb0.copy()), torch.zeros(n // 2 + 15, dtype=torch.uint8, device="cuda")
+            B.rwkvq_mu_codebook([dev(m)], [dev(x)], [n], B.F32, kbits, 4, [cb], [idx])
+            torch.cuda.synchronize()
+            wcb, widx, _ = MO.mu_codebook(m, x, orc.widen(cb0, "f16"), 4)
+            assert np.array_equal(cb.cpu().numpy().view(np.uint16).reshape(-1), synth.f32_to_f16_bits(wcb).reshape(-1)), (n, kind)
+            assert np.array_equal(idx.cpu().numpy()[:n // 2], widx.astype(np.uint8)), (n, kind)
