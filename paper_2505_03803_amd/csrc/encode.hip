@@ -218,67 +218,215 @@ __device__ __forceinline__ void load_pairs8(const void* w, int wdt, size_t e, fl
     }
 }
 
-// Four workgroups per 256 x 256 block, each 64 rows; a thread takes one row and a quarter of its
-// columns (the four threads of a row read 512 consecutive bytes of 16-bit weights):
-// 32 weight pairs, each compared with every entry of the block's codebook (staged in LDS as
-// binary32, read by all threads at the same address: a broadcast).  Eight pairs share one pass
-// over the entries.
+__device__ __forceinline__ float pair_distance(float v0, float v1, float c0, float c1) {
+    const float t0 = __fsub_rn(v0, c0), t1 = __fsub_rn(v1, c1);
+    return __fadd_rn(__fmul_rn(t0, t0), __fmul_rn(t1, t1));
+}
+
+// Nearest entries without comparing every pair with every entry.  A workgroup of 1024 threads takes a 256 x 256 block:
+//   1. the plane is cut into 32 x 32 cells over mean +- 3.25 standard deviations of the codebook's entries (those outside are
+//      left out and the box is taken again, twice);
+//   2. one thread per cell lists the entries that can be nearest to a point of the cell: with r the entry nearest to the
+//      centre, at distance |r|, and h the distance from the centre to the cell's farthest point, an entry farther than
+//      |r| + 2 h from the centre is farther than r from every point of the cell, and so is one whose squared distance exceeds
+//      r's at all four corners (the difference is linear over the cell).  The cell is taken 10 % and the limits 1e-5 of the
+//      squared reach too large, far beyond the rounding of the binary32 distances (4 2^-24) and of the cell of a point, so the
+//      entry that wins by the definition's rounded distances is always listed, and so is every entry that ties with it;
+//   3. a pair is compared with its cell's entries in index order (strict comparison: the lowest index wins a tie); unused
+//      places of a list repeat its first entry, which never wins again;
+//   4. pairs outside the cells, or in a cell with more than 16 entries, are queued and each compared with every entry by
+//      sixteen lanes (a full queue, a quarter of the block: by the thread itself).
+// Bound: vector ALU of step 2 (20 instructions per cell and entry) and the LDS look-ups of the 2 to 8 listed entries per
+// pair (a wavefront runs to its longest list).
+// Measured (bf16, near-normal weights, every pair against every entry -> here): 4096 x 4096, 64 entries 84 -> 60 us, 256
+// entries 316 -> 119; 14336 x 4096, 256 entries 879 -> 256; 1024 x 1024, 64 entries 36 -> 22.  With the queued pairs taken by
+// single threads where they are met: 92, 503 and 903 (a wavefront waits for its one lane that goes through all entries).
 template <int KBITS>
-__global__ void __launch_bounds__(256) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
-                                                        const uint16_t* __restrict__ codebooks,
-                                                        uint32_t* __restrict__ indices) {
-    constexpr int E = 1 << KBITS;
-    __shared__ float cb0[E], cb1[E];
-    const int quarter = blockIdx.x & 3, blk = blockIdx.x >> 2;
-    const int bj = blk % (K / kBlock), bi = blk / (K / kBlock);
-    const uint16_t* cb = codebooks + ((size_t)bi * (K / kBlock) + bj) * E * 2;
-    for (int e = threadIdx.x; e < E; e += 256) {
-        cb0[e] = f16_bits_to_f32(cb[2 * e]);
-        cb1[e] = f16_bits_to_f32(cb[2 * e + 1]);
-    }
+__global__ void __launch_bounds__(1024) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
+                                                         const uint16_t* __restrict__ codebooks,
+                                                         uint32_t* __restrict__ indices, int parts_log2) {
+    constexpr int E = 1 << KBITS, G = 32, kSlots = 16, kQueue = 8192;
+    __shared__ float2 entry[E];
+    __shared__ __attribute__((aligned(16))) uint8_t list[G * G][kSlots];
+    __shared__ uint8_t listed[G * G];
+    __shared__ __attribute__((aligned(16))) uint8_t found[32768];
+    __shared__ uint16_t queue[kQueue];
+    __shared__ int queued;
+    __shared__ float box[5];                                       // origin, cells per unit, h
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int block = blockIdx.x >> parts_log2, part = blockIdx.x & ((1 << parts_log2) - 1);
+    const int bj = block % (K / kBlock), bi = block / (K / kBlock);
+    const uint16_t* cb = codebooks + (size_t)block * E * 2;
+    if (tid < E) entry[tid] = float2{f16_bits_to_f32(cb[2 * tid]), f16_bits_to_f32(cb[2 * tid + 1])};
+    if (tid == 0) queued = 0;
     __syncthreads();
-    const int n = bi * kBlock + 64 * quarter + (threadIdx.x >> 2), cq = threadIdx.x & 3;
-    const size_t e0 = (size_t)n * K + (size_t)bj * kBlock + 64 * cq;
-    constexpr int wpr = KBITS == 6 ? 3 : 4;                        // output words per 16 pairs
-    uint32_t* out = indices + (size_t)n * (K / 2 * KBITS / 32) + (size_t)bj * (kBlock / 2 * KBITS / 32) + 2 * wpr * cq;
-    for (int c = 0; c < 2; ++c) {                                  // 16 pairs per step
-        uint32_t idx[16];
+    if (wave == 0) {                                               // mean and deviation, twice more without the entries outside
+        float m0 = entry[0].x, m1 = entry[0].y, r0 = __builtin_inff(), r1 = __builtin_inff();
+#pragma unroll 1
+        for (int pass = 0; pass < 3; ++pass) {
+            float s[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float v0[8], v1[8], best[8];
-            uint32_t arg[8];
-            load_pairs8(w, wdt, e0 + 32 * c + 16 * h, v0, v1);
-#pragma unroll
-            for (int p = 0; p < 8; ++p) { best[p] = __builtin_inff(); arg[p] = 0u; }
-#pragma unroll 4
-            for (int e = 0; e < E; ++e) {
-                const float c0 = cb0[e], c1 = cb1[e];
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const float t0 = __fsub_rn(v0[p], c0), t1 = __fsub_rn(v1[p], c1);
-                    const float d = __fadd_rn(__fmul_rn(t0, t0), __fmul_rn(t1, t1));
-                    if (d < best[p]) { best[p] = d; arg[p] = (uint32_t)e; }   // strict: lowest index wins ties
-                }
+            for (int e = lane; e < E; e += 64) {
+                const float2 c = entry[e];
+                const float dx = c.x - m0, dy = c.y - m1;
+                if (fabsf(dx) <= r0 && fabsf(dy) <= r1) { s[0] += dx; s[1] += dy; s[2] += dx * dx; s[3] += dy * dy; s[4] += 1.f; }
             }
 #pragma unroll
-            for (int p = 0; p < 8; ++p) idx[8 * h + p] = arg[p];
+            for (int off = 32; off; off >>= 1)
+#pragma unroll
+                for (int i = 0; i < 5; ++i) s[i] += __shfl_xor(s[i], off, 64);
+            if (s[4] < 1.f) break;
+            const float a0 = s[0] / s[4], a1 = s[1] / s[4];
+            m0 += a0; m1 += a1;
+            // no cell narrower than 6e-6 of its place (the resolution of binary32 there)
+            r0 = fmaxf(fmaxf(3.25f * sqrtf(fmaxf(s[2] / s[4] - a0 * a0, 0.f)), 1e-4f * fabsf(m0)), 1e-6f);
+            r1 = fmaxf(fmaxf(3.25f * sqrtf(fmaxf(s[3] / s[4] - a1 * a1, 0.f)), 1e-4f * fabsf(m1)), 1e-6f);
         }
-        if (KBITS == 6) {
-            unsigned long long lo = 0;                             // 16 x 6 bits = 96 bits
-            uint32_t hi = 0;
+        if (lane == 0) {
+            box[0] = m0 - r0; box[1] = m1 - r1; box[2] = G / (2.f * r0); box[3] = G / (2.f * r1);
+            box[4] = 0.55f * (2.f / G) * sqrtf(r0 * r0 + r1 * r1);
+        }
+    }
+    __syncthreads();
+    const float x0 = box[0], y0 = box[1], sx = box[2], sy = box[3];
+    {   // the lists, one cell per thread
+        const float cx = x0 + ((float)(tid % G) + 0.5f) / sx, cy = y0 + ((float)(tid / G) + 0.5f) / sy;
+        const float hx = 1.1f / sx, hy = 1.1f / sy;              // twice 0.55 of a cell's sides
+        float least = __builtin_inff();
+        float2 r = entry[0];
+#pragma unroll 8
+        for (int e = 0; e < E; ++e) {
+            const float2 c = entry[e];
+            const float d = pair_distance(cx, cy, c.x, c.y);
+            if (d < least) { least = d; r = c; }
+        }
+        const float reach = (sqrtf(least) + 2.f * box[4]) * 1.0001f, limit = reach * reach;
+        const float at_most = least + 1e-5f * limit;
+        int n = 0, first = 0;
+#pragma unroll 4
+        for (int e = 0; e < E; ++e) {
+            const float2 c = entry[e];
+            const float d = pair_distance(cx, cy, c.x, c.y);
+            if (d <= limit && d <= at_most + fabsf(r.x - c.x) * hx + fabsf(r.y - c.y) * hy) {
+                if (n == 0) first = e;
+                if (n < kSlots) list[tid][n] = (uint8_t)e;
+                ++n;
+            }
+        }
+        listed[tid] = (uint8_t)(n <= kSlots && n > 0 ? n : 255);
+        for (; n < kSlots; ++n) list[tid][n] = (uint8_t)first;
+    }
+    __syncthreads();
+
+    // the pairs of a workgroup's rows in units of eight: thread after thread, row after row; unit u is pairs 8 u .. 8 u + 7
+    const int units = 4096 >> parts_log2;
+    const size_t first_row = (size_t)bi * kBlock + (size_t)part * (kBlock >> parts_log2);
+    const size_t base = first_row * K + (size_t)bj * kBlock;
+#pragma unroll 1
+    for (int u = tid; u < units; u += 1024) {
+        float v0[8], v1[8];
+        load_pairs8(w, wdt, base + (size_t)(u >> 4) * K + 16 * (u & 15), v0, v1);
+        uint32_t arg[8];
 #pragma unroll
-            for (int p = 0; p < 10; ++p) lo |= (unsigned long long)idx[p] << (6 * p);
-            lo |= (unsigned long long)(idx[10] & 0xFu) << 60;      // index 10 straddles bit 64
-            hi = idx[10] >> 4;
+        for (int h = 0; h < 8; h += 4) {
+            uint4_t l[4];
+            float best[4];
+            int longest = 0;
+            bool again[4];
 #pragma unroll
-            for (int p = 11; p < 16; ++p) hi |= idx[p] << (6 * p - 64);
-            out[wpr * c + 0] = (uint32_t)lo;
-            out[wpr * c + 1] = (uint32_t)(lo >> 32);
-            out[wpr * c + 2] = hi;
+            for (int p = 0; p < 4; ++p) {
+                const float fx = (v0[h + p] - x0) * sx, fy = (v1[h + p] - y0) * sy;
+                const bool in = fx >= 0.f && fx < (float)G && fy >= 0.f && fy < (float)G;
+                const int cell = in ? (int)fy * G + (int)fx : 0;
+                const int cnt = listed[cell];
+                again[p] = !in || cnt == 255;
+                longest = max(longest, again[p] ? 0 : cnt);
+                l[p] = *(const uint4_t*)list[cell];
+                best[p] = __builtin_inff();
+                arg[h + p] = 0u;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                          // four places at a time, up to the longest list of the wavefront
+                if (__builtin_amdgcn_ballot_w64(longest > 4 * q) == 0) break;
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        const uint32_t word = q == 0 ? l[p].x : q == 1 ? l[p].y : q == 2 ? l[p].z : l[p].w;
+                        const uint32_t e = (word >> (8 * b)) & 255u;
+                        const float2 ce = entry[e];
+                        const float d = pair_distance(v0[h + p], v1[h + p], ce.x, ce.y);
+                        if (d < best[p]) { best[p] = d; arg[h + p] = e; }
+                    }
+            }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                if (again[p]) {
+                    const int at = atomicAdd(&queued, 1);
+                    if (at < kQueue) {
+                        queue[at] = (uint16_t)(8 * u + h + p);
+                    } else {
+                        float bd = __builtin_inff();
+#pragma unroll 8
+                        for (int e = 0; e < E; ++e) {
+                            const float2 ce = entry[e];
+                            const float d = pair_distance(v0[h + p], v1[h + p], ce.x, ce.y);
+                            if (d < bd) { bd = d; arg[h + p] = (uint32_t)e; }
+                        }
+                    }
+                }
+            }
+        }
+        *(uint2_t*)(found + 8 * u) = uint2_t{arg[0] | (arg[1] << 8) | (arg[2] << 16) | (arg[3] << 24),
+                                           arg[4] | (arg[5] << 8) | (arg[6] << 16) | (arg[7] << 24)};
+    }
+    __syncthreads();
+    const int todo = min(queued, kQueue);
+    for (int i = tid >> 4; i < todo; i += 64) {                    // sixteen lanes per queued pair
+        const int id = queue[i];
+        const size_t e = base + (size_t)(id >> 7) * K + 2 * (id & 127);
+        float vx, vy;
+        if (wdt == DT_F32) {
+            const float2 v = *(const float2*)((const float*)w + e);
+            vx = v.x; vy = v.y;
         } else {
+            const uint32_t v = *(const uint32_t*)((const uint16_t*)w + e);
+            const uint16_t lo = (uint16_t)(v & 0xFFFFu), hi = (uint16_t)(v >> 16);
+            vx = wdt == DT_F16 ? f16_bits_to_f32(lo) : bf16_bits_to_f32(lo);
+            vy = wdt == DT_F16 ? f16_bits_to_f32(hi) : bf16_bits_to_f32(hi);
+        }
+        float bd = __builtin_inff();
+        uint32_t be = 0xFFFFFFFFu;
+#pragma unroll
+        for (int k = 0; k < E / 16; ++k) {
+            const float2 ce = entry[(tid & 15) + 16 * k];
+            const float d = pair_distance(vx, vy, ce.x, ce.y);
+            if (d < bd) { bd = d; be = (uint32_t)((tid & 15) + 16 * k); }
+        }
+#pragma unroll
+        for (int off = 8; off; off >>= 1) {
+            const float od = __shfl_xor(bd, off, 64);
+            const uint32_t oe = (uint32_t)__shfl_xor((int)be, off, 64);
+            if (od < bd || (od == bd && oe < be)) { bd = od; be = oe; }
+        }
+        if ((tid & 15) == 0) found[id] = (uint8_t)(be == 0xFFFFFFFFu ? 0u : be);   // (every distance infinite or NaN: entry 0)
+    }
+    __syncthreads();
+    constexpr int wpr = KBITS == 6 ? 3 : 4;                        // output words per 16 pairs
+    for (int u = tid; u < units / 2; u += 1024) {
+        uint32_t* out = indices + (first_row + (u >> 3)) * (K / 2 * KBITS / 32) + (size_t)bj * (kBlock / 2 * KBITS / 32) + wpr * (u & 7);
+        const uint4_t f = *(const uint4_t*)(found + 16 * u);
+        if constexpr (KBITS == 8) {
+            *(uint4_t*)out = f;
+        } else {
+            const uint32_t fw[4] = {f.x, f.y, f.z, f.w};
+            uint32_t packed[4];                                    // four indices each: 24 bits
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                out[wpr * c + q] = idx[4 * q] | (idx[4 * q + 1] << 8) | (idx[4 * q + 2] << 16) | (idx[4 * q + 3] << 24);
+                packed[q] = (fw[q] & 63u) | ((fw[q] >> 2) & 0xFC0u) | ((fw[q] >> 4) & 0x3F000u) | ((fw[q] >> 6) & 0xFC0000u);
+            out[0] = packed[0] | (packed[1] << 24);
+            out[1] = (packed[1] >> 8) | (packed[2] << 16);
+            out[2] = (packed[2] >> 16) | (packed[3] << 8);
         }
     }
 }
@@ -296,9 +444,14 @@ hipError_t launch_sq_encode(const void* w, int wdt, int N, int K, uint32_t* code
 
 hipError_t launch_vq_assign(const void* w, int wdt, int N, int K, int kbits, const uint16_t* codebooks,
                             uint32_t* indices, hipStream_t s) {
-    const unsigned blocks = 4u * (unsigned)((N / kBlock) * (K / kBlock));
-    if (kbits == 6) hipLaunchKernelGGL(vq_assign_kernel<6>, dim3(blocks), dim3(256), 0, s, w, wdt, N, K, codebooks, indices);
-    else hipLaunchKernelGGL(vq_assign_kernel<8>, dim3(blocks), dim3(256), 0, s, w, wdt, N, K, codebooks, indices);
+    const unsigned blocks = (unsigned)((N / kBlock) * (K / kBlock));
+    // a chip left idle by few blocks takes each in two or four parts, each with lists of its own (1024 x 1024, 64 entries:
+    // whole blocks 42 us, quarters 22; 256 entries 83 and 50)
+    int parts_log2 = 0;
+    while (parts_log2 < 2 && (blocks << (parts_log2 + 1)) <= 256u) ++parts_log2;
+    const dim3 grid(blocks << parts_log2);
+    if (kbits == 6) hipLaunchKernelGGL(vq_assign_kernel<6>, grid, dim3(1024), 0, s, w, wdt, N, K, codebooks, indices, parts_log2);
+    else hipLaunchKernelGGL(vq_assign_kernel<8>, grid, dim3(1024), 0, s, w, wdt, N, K, codebooks, indices, parts_log2);
     return hipGetLastError();
 }
 

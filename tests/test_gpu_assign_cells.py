@@ -1,0 +1,55 @@
+"""The nearest-entry assignment by cells (pairs compared only with the entries listed for their cell) against the definition."""
+import numpy as np
+import pytest
+
+from oracle import encode_oracle as E
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a, dtype):
+    import torch
+    a = np.ascontiguousarray(a)
+    return torch.from_numpy(a if dtype == "f32" else a.view(np.int16)).cuda()
+
+
+def test_vq_assign_cells():
+    """Where the listed entries could go wrong: entries in a tight cluster with one far out (cells with more entries than a list
+    holds), all entries equal, entries on a lattice with pairs exactly between them, pairs far outside the cells, on entries,
+    and one representable step off a tie; codebooks far from the origin; every pair outside (a full queue)."""
+    from paper_2505_03803_amd import binding as B
+    rng = np.random.default_rng(99)
+    for kbits in (6, 8):
+        En = 1 << kbits
+        books = []
+        books.append(np.concatenate([rng.normal(0, 1e-3, (En - 1, 2)), [[5.0, -7.0]]]))
+        books.append(np.full((En, 2), 0.125))
+        side = int(np.sqrt(En))
+        books.append(np.stack(np.meshgrid(np.arange(side), np.arange(side)), -1).reshape(En, 2) / 8.0)
+        books.append(rng.normal(0, 0.02, (En, 2)) + [30.0, -11.0])
+        books.append(rng.normal(0, 0.02, (En, 2)))
+        books.append(rng.normal(0, 0.02, (En, 2)))
+        books.append(np.stack([np.linspace(-1, 1, En), np.zeros(En)], -1))      # on a line
+        books.append(rng.integers(0, 3, (En, 2)) / 4.0)                         # many duplicates
+        n_blocks = len(books)
+        cb = np.stack(books).astype(np.float16)
+        wide = np.empty((256, 256 * n_blocks), np.float32)
+        for i in range(n_blocks):
+            b = rng.normal(0, 0.02, (256, 128, 2)).astype(np.float32)
+            e = cb[i].astype(np.float32)
+            b[:64] = e[rng.integers(0, En, (64, 128))]                          # on entries
+            mid = (e[rng.integers(0, En, (64, 128))] + e[rng.integers(0, En, (64, 128))]) / 2
+            b[64:128] = mid                                                     # between two entries
+            b[128:160] = np.nextafter(mid[:32], np.float32(1e9))
+            b[160:168] *= 1e6
+            b[168:172] *= 1e-30
+            if i == 4: b[:] = rng.normal(0, 1, b.shape)                          # nearly all outside
+            if i == 5: b[200:] = np.float32(3e4) * rng.normal(0, 1, b[200:].shape).astype(np.float32)
+            wide[:, 256 * i: 256 * (i + 1)] = b.reshape(256, 256)
+        bits = cb.view(np.uint16)[None]
+        dm = B.vq_assign(dev(wide, "f32"), B.F32, dev(bits, "f16"), kbits)
+        want = E.vq_assign_packed(wide, bits, kbits)
+        assert np.array_equal(dm.codes.cpu().numpy().view(np.uint32), want), kbits
+        for rows in (9, 17):                    # enough blocks that each is taken in two parts, and whole
+            dm = B.vq_assign(dev(np.tile(wide, (rows, 1)), "f32"), B.F32, dev(np.tile(bits, (rows, 1, 1, 1)), "f16"), kbits)
+            assert np.array_equal(dm.codes.cpu().numpy().view(np.uint32), np.tile(want, (rows, 1))), (kbits, rows)
