@@ -936,7 +936,7 @@ def main():
                 k += 1
             out["proxy"]["cpu_baseline"] = {"value": nb / secs / 1e9, "unit": "GB/s", "cores": 1, "kind": "oracle",
                                             "sample": "first %d of the %d matrices (%d dense bytes in %.2f s)" % (k, n, nb, secs)}
-        # ---------------- the proxy for binary32 matrices: a real sort (four radix passes) per matrix
+        # ---------------- the proxy for binary32 matrices: partitioned, each part reduced to its distinct values in order
         shapes32 = [(N, K) for _, N, K in synth.layer_shapes(4096, 14336)]
         mats32 = [torch.randn(sh, device="cuda", generator=gen) * 0.02 for sh in shapes32]
         table32 = B.ProxyTable(mats32, shapes32)
@@ -945,16 +945,16 @@ def main():
         t32, _, _ = time_steps(run32, 10, 3)
         ms32 = t32 / 10
         nw32 = sum(a * b for a, b in shapes32)
-        alg32 = nw32 * 36                      # per weight: 4 passes x (4 B read + 4 B written) + 4 B for the pass over the sorted keys
+        alg32 = nw32 * 16                      # per weight: 4 B read to count, 4 + 4 B to partition, 4 B to take the sums
         out["proxy_f32"] = {"value": nw32 / (ms32 * 1e-3) / 1e9, "unit": "G weights/s", "ms_per_call": ms32, "calls": 10, "dtype": "f64",
                             "matrices": len(shapes32), "weights_per_call": nw32,
                             "workload": "dense binary32 N(0, 0.02) weights of one RWKV-6-7B-shaped layer (8 matrices), K = 5 terms, "
-                                        "sorted by a four-pass radix sort, one matrix after another",
-                            "roofline": {"kernel": "rwkvq::sort_scatter_kernel", "bound": "hbm", "achieved": alg32 / (ms32 * 1e-3) / 1e9,
+                                        "partitioned and reduced to sets of values, one matrix after another",
+                            "roofline": {"kernel": "rwkvq::set_partition_kernel", "bound": "hbm", "achieved": alg32 / (ms32 * 1e-3) / 1e9,
                                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": alg32 / (ms32 * 1e-3) / 1e9 / HBM_PEAK_GBS,
                                          "traffic": None, "algorithmic_bytes_per_call": alg32,
-                                         "note": "algorithmic bytes = 36 per weight (4 passes x 8 B + 4 B); the histogram step re-reads "
-                                                 "the keys once per pass on top of that; achieved is over the whole call (18 launches per matrix)"}}
+                                         "note": "algorithmic bytes = 16 per weight (count 4, partition 8, sums 4); achieved is over the whole call "
+                                                 "(6 launches per matrix)"}}
         if not args.skip_cpu:
             from oracle import proxy_oracle as PO
             host32 = mats32[0].cpu().numpy()

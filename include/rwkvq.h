@@ -211,14 +211,15 @@ int rwkvq_linear_dispatch_plan(const rwkvq_matrix* mats, int n_mats, int M, int3
  * (Eqs. "interval", "interval_norm"), 0 ln 0 := 0 for the zero intervals between equal weights, and
  * a constant matrix gives P_c = P_f = 0.  All arithmetic after the pass over the weights is
  * binary64 in a fixed order.  Sixteen-bit matrices are reduced to the set of bit patterns that
- * occur (one pass over the matrix, many matrices per launch); binary32 matrices are sorted (four
- * passes of a radix sort over order-preserving keys), one matrix after another.
+ * occur (one pass over the matrix, many matrices per launch); binary32 matrices are taken one after
+ * another: sorted (four passes of a radix sort over order-preserving keys), or from 2^19 weights on
+ * partitioned by the upper 15 bits of the key and each part reduced to its sorted distinct values.
  *
  * proxies: DEVICE pointer to 2 n_mats doubles (P_c, P_f per matrix); phi: DEVICE pointer to n_mats
  * int32.  workspace: DEVICE pointer to rwkvq_proxy_workspace_size(Ns, Ks, n_mats, w_dtype) bytes of
  * scratch owned by the caller (contents irrelevant on entry, undefined on exit): 8 KiB per matrix
  * for 16-bit weights (= rwkvq_proxy_workspace_bytes(n_mats)); for binary32 about 8.3 bytes per weight
- * of the largest matrix (two key buffers, digit counts and partial sums; 0 is returned for arguments
+ * of the largest matrix (two key buffers, digit counts and partial sums, or what takes their place; 0 is returned for arguments
  * rwkvq_proxy would reject).  workspace, proxies and every ws[i] 16-byte aligned, phi 4-byte aligned.
  * The host arrays are read before return; the call is asynchronous on `stream`; calls that share a
  * workspace must be ordered by the stream.

@@ -3,7 +3,8 @@
 // the intervals between neighbours are normalised (Eqs. "interval", "interval_norm"), and the
 // entropy and the central moments of the normalised intervals give P_c and P_f (Eqs. "ie",
 // "coarse_proxy", "fine_proxy").  Sixteen-bit matrices take the shortcut of proxy.hip (the set of
-// occurring bit patterns); binary32 weights have no such shortcut, so they are really sorted:
+// occurring bit patterns); binary32 weights up to kSetMinCount are really sorted (larger
+// matrices: below, "partition and sets of values"):
 //
 //   * keys: the order-preserving map of the binary32 patterns to unsigned integers;
 //   * least-significant-digit radix sort, four passes of 8 bits, each pass three steps:
@@ -277,6 +278,529 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
     }
 }
 
+// ------------------------------------------------------------------ large matrices: partition and sets of values
+//
+// From kSetMinCount weights on nothing is sorted through memory.  The sums need the distinct values in order and the number of
+// equal neighbours, not the sorted sequence:
+//
+//   * set_count_kernel      32768 bins, a bin being the upper 15 bits of the key (sign, exponent, six bits of fraction): counts
+//                           per workgroup of a contiguous range in LDS, then one reservation per workgroup and bin;
+//   * set_plan_kernel       where each bin starts.  Bins of more than 1024 keys ("hot", of near-normal weights the ones
+//                           within some octaves of the deviation) stand behind the others, in groups of at most 2047 keys;
+//   * set_partition_kernel  every key to its bin: position = start + reservation + an LDS counter per bin.  The order inside a
+//                           bin does not matter (and is not fixed), so no ranks and no reordering are needed;
+//   * set_sum_kernel        a hot bin is 2^17 patterns of one sign and exponent: a bitmap of 16 KB in LDS.  Intervals are
+//                           distances of set bits times the exponent's unit, exact; t ln t of the small distances comes from
+//                           a table made with the same expressions.  A bin of more than 131072 keys is read by several
+//                           workgroups that join their bitmaps in memory, and the last to finish sums.  A group of small bins
+//                           is sorted in LDS;
+//   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
+//
+// The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
+// Bound: the partition's stores, four bytes each to a line of their own (470 MB at 1 TB/s for
+// 14336 x 4096), then bytes.  Measured (us; radix sort -> here): 768 x 768 159 -> 102, 1024 x 1024 164 -> 111, 4096 x 4096
+// 500 -> 207, 14336 x 4096 1954 -> 750 (count 56, plan 16, partition 460, sum 200, final 12); all weights equal 1563 -> 352,
+// values of bfloat16 1781 -> 854, half the weights zero 1866 -> 650.  Below kSetMinCount, where no such table fits the
+// workspace, the sort.
+constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
+constexpr int kBins = 32768, kBinShift = 17;
+constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
+constexpr uint32_t kPiece = 131072;                          // keys of a hot bin that one workgroup reads
+constexpr int kBitmapWords = 1 << (kBinShift - 5);           // 4096
+constexpr uint32_t kCountRange = 49152;                      // fewest keys per counting workgroup
+constexpr int kSetThreads = 1024;
+constexpr int kSetRow = kGapSums + 1;                        // partial sums and the number of intervals above zero
+constexpr int kSumThreads = 512, kSumWorkgroups = 512;
+constexpr int kTable = 512;
+
+struct SetHead { uint32_t min_key, max_key, groups, pieces, joints; };
+struct SetBuffers {
+    uint32_t* keys;          // partitioned: groups of small bins, then the hot bins, each in bin order
+    uint32_t* reserved;      // [workgroup][bin]: keys of the bin reserved before
+    SetHead* head;
+    uint32_t* counts;        // [bin]
+    uint32_t* least;         // [counting workgroup]: its smallest and largest key
+    uint32_t* most;
+    uint32_t* occupied;      // [bin / 32]: bit = the bin holds keys
+    uint32_t* start;         // [bin]: position of the bin in keys
+    uint32_t* group_from;    // [group + 1]: position of the group's first key
+    uint32_t* bin_min;       // [bin], of occupied bins
+    uint32_t* bin_max;
+    uint4_t* piece;          // [piece]: bin, first and end position, joint bitmap of a bin in several pieces
+    uint32_t* done;          // [joint]: pieces finished
+    uint32_t* joint;         // [joint][4096]
+    double* sums;            // [workgroups of set_sum_kernel, then joint bins][kSetRow]
+    size_t bytes;
+};
+static uint32_t set_workgroups(uint32_t count) { return count / kCountRange < 256u ? count / kCountRange : 256u; }
+static uint32_t set_joint_max(uint32_t count) { return count / kPiece; }
+
+static SetBuffers set_buffers(char* base, uint32_t count) {
+    SetBuffers b;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { char* p = base + o; o += (bytes + 255) & ~(size_t)255; return p; };
+    b.keys = (uint32_t*)take((size_t)count * 4);
+    b.reserved = (uint32_t*)take((size_t)set_workgroups(count) * kBins * 4);
+    b.head = (SetHead*)take(sizeof(SetHead));
+    b.counts = (uint32_t*)take(kBins * 4);
+    b.least = (uint32_t*)take(256 * 4);
+    b.most = (uint32_t*)take(256 * 4);
+    b.occupied = (uint32_t*)take(kBins / 8);
+    b.start = (uint32_t*)take(kBins * 4);
+    b.group_from = (uint32_t*)take(((size_t)count / kHot + 2) * 4);
+    b.bin_min = (uint32_t*)take(kBins * 4);
+    b.bin_max = (uint32_t*)take(kBins * 4);
+    b.piece = (uint4_t*)take(((size_t)count / kHot + set_joint_max(count)) * 16);
+    b.done = (uint32_t*)take((size_t)set_joint_max(count) * 4);
+    b.joint = (uint32_t*)take((size_t)set_joint_max(count) * kBitmapWords * 4);
+    b.sums = (double*)take((size_t)(kSumWorkgroups + set_joint_max(count)) * kSetRow * 8);
+    b.bytes = o;
+    return b;
+}
+
+__global__ void __launch_bounds__(256) set_clear_kernel(SetBuffers b, uint32_t joint_max) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
+    for (uint32_t j = i; j < (uint32_t)kBins; j += step) b.counts[j] = 0u;
+    for (uint32_t j = i; j < joint_max; j += step) b.done[j] = 0u;
+    for (size_t j = i; j < (size_t)joint_max * kBitmapWords / 4; j += step) ((uint4_t*)b.joint)[j] = uint4_t{0u, 0u, 0u, 0u};
+}
+
+// The contiguous range of keys of a counting or partitioning workgroup: [lo, hi), lo a multiple of four.
+__device__ __forceinline__ void set_range(uint32_t count, uint32_t& lo, uint32_t& hi) {
+    const uint32_t per = ((count - 1u) / gridDim.x + 4u) & ~3u;
+    const unsigned long long l = (unsigned long long)per * blockIdx.x, h = l + per;
+    lo = l < count ? (uint32_t)l : count;
+    hi = h < count ? (uint32_t)h : count;
+}
+
+// Applies f(four patterns, how many are valid) to the range, four loads of 16 bytes in flight per thread.
+template <class F>
+__device__ __forceinline__ void for_quads(const uint32_t* __restrict__ in, uint32_t lo, uint32_t hi, F f) {
+    const uint32_t quads = (hi - lo) / 4u;
+    const uint4_t* q = (const uint4_t*)(in + lo);
+    uint32_t i = threadIdx.x;
+    for (; i + 3u * kSetThreads < quads; i += 4u * kSetThreads) {
+        uint4_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = q[i + j * kSetThreads];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { f(v[j].x); f(v[j].y); f(v[j].z); f(v[j].w); }
+    }
+    for (; i < quads; i += kSetThreads) { const uint4_t v = q[i]; f(v.x); f(v.y); f(v.z); f(v.w); }
+    const uint32_t rest = lo + 4u * quads + threadIdx.x;
+    if (rest < hi) f(in[rest]);
+}
+
+// Adds one to counter[bin] and gives its value before.  A wavefront whose lanes all hold one bin (equal weights) adds once.
+__device__ __forceinline__ uint32_t count_bin(uint32_t* counter, uint32_t bin) {
+    const unsigned long long live = __builtin_amdgcn_ballot_w64(true);
+    const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+    if (__builtin_amdgcn_ballot_w64(bin == b0) == live) {
+        const uint32_t below = (uint32_t)__builtin_popcountll(live & lanes_below(threadIdx.x & 63));
+        uint32_t old = 0u;
+        if (below == 0u) old = atomicAdd(&counter[bin], (uint32_t)__builtin_popcountll(live));
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)old) + below;
+    }
+    return atomicAdd(&counter[bin], 1u);
+}
+
+__global__ void __launch_bounds__(kSetThreads) set_count_kernel(const uint32_t* __restrict__ in, uint32_t count, SetBuffers b) {
+    extern __shared__ uint32_t h[];                              // [kBins]
+    const int tid = threadIdx.x;
+    for (int j = tid; j < kBins / 4; j += kSetThreads) ((uint4_t*)h)[j] = uint4_t{0u, 0u, 0u, 0u};
+    __syncthreads();
+    uint32_t lo, hi, least = 0xFFFFFFFFu, most = 0u;
+    set_range(count, lo, hi);
+    for_quads(in, lo, hi, [&](uint32_t bits) {
+        const uint32_t k = f32_key(bits);
+        least = min(least, k); most = max(most, k);
+        count_bin(h, k >> kBinShift);
+    });
+#pragma unroll
+    for (int off = 32; off; off >>= 1) {
+        least = min(least, (uint32_t)__shfl_xor((int)least, off, 64));
+        most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+    }
+    __shared__ uint32_t wave_least[kSetThreads / 64], wave_most[kSetThreads / 64];
+    if ((tid & 63) == 0) { wave_least[tid >> 6] = least; wave_most[tid >> 6] = most; }
+    __syncthreads();
+    if (tid == 0) {                                              // (one address for all wavefronts: 90 us of additions in a row)
+        for (int w = 0; w < kSetThreads / 64; ++w) { least = min(least, wave_least[w]); most = max(most, wave_most[w]); }
+        b.least[blockIdx.x] = least;
+        b.most[blockIdx.x] = most;
+    }
+    uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
+    // sixteen reservations in flight per thread, each workgroup from another bin on
+#pragma unroll 1
+    for (int i = tid; i < kBins; i += 16 * kSetThreads) {
+        uint32_t c[16], got[16];
+        auto bin = [&](int r) { return (uint32_t)(i + r * kSetThreads + 128 * (int)blockIdx.x) & (kBins - 1); };
+#pragma unroll
+        for (int r = 0; r < 16; ++r) c[r] = h[bin(r)];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) if (c[r]) got[r] = atomicAdd(&b.counts[bin(r)], c[r]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) if (c[r]) mine[bin(r)] = got[r];
+    }
+}
+
+// One workgroup; a thread takes 32 consecutive bins.
+__global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uint32_t wgs) {
+    __shared__ uint32_t wave_sum[kSetThreads / 64][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t c[32], occupied = 0u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint4_t v = ((const uint4_t*)b.counts)[8 * tid + j];
+        c[4 * j] = v.x; c[4 * j + 1] = v.y; c[4 * j + 2] = v.z; c[4 * j + 3] = v.w;
+    }
+#pragma unroll
+    for (int j = 0; j < 32; ++j) occupied |= (c[j] ? 1u : 0u) << j;
+    b.occupied[tid] = occupied;
+    // keys in small bins, keys in hot bins, pieces, hot bins of several pieces
+    uint32_t own[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        if (c[j] <= kHot) own[0] += c[j];
+        else { own[1] += c[j]; own[2] += (c[j] - 1u) / kPiece + 1u; own[3] += c[j] > kPiece ? 1u : 0u; }
+    }
+    uint32_t run[4], total[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t v = own[i];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)v, off, 64); if (lane >= off) v += a; }
+        if (lane == 63) wave_sum[wave][i] = v;
+        run[i] = v - own[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        total[i] = 0u;
+        for (int w = 0; w < kSetThreads / 64; ++w) { if (w < wave) run[i] += wave_sum[w][i]; total[i] += wave_sum[w][i]; }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        uint32_t at[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t n = c[4 * q + j];
+            if (n <= kHot) {
+                at[j] = run[0];
+                run[0] += n;
+                // a group begins with the first bin at or behind a multiple of kHot (a bin holds no more than that)
+                if (run[0] / kHot != at[j] / kHot) b.group_from[run[0] / kHot] = run[0];
+            } else {
+                at[j] = total[0] + run[1];
+                for (uint32_t f = 0u; f < n; f += min(kPiece, n - f))
+                    b.piece[run[2]++] = uint4_t{(uint32_t)(32 * tid + 4 * q + j), at[j] + f, at[j] + f + min(kPiece, n - f),
+                                                n > kPiece ? run[3] : 0xFFFFFFFFu};
+                run[1] += n; run[3] += n > kPiece ? 1u : 0u;
+            }
+        }
+        ((uint4_t*)b.start)[8 * tid + q] = uint4_t{at[0], at[1], at[2], at[3]};
+    }
+    if (wave == 0) {
+        uint32_t least = 0xFFFFFFFFu, most = 0u;
+        for (uint32_t i = lane; i < wgs; i += 64u) { least = min(least, b.least[i]); most = max(most, b.most[i]); }
+#pragma unroll
+        for (int off = 32; off; off >>= 1) {
+            least = min(least, (uint32_t)__shfl_xor((int)least, off, 64));
+            most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+        }
+        if (lane == 0) { b.head->min_key = least; b.head->max_key = most; }
+    }
+    if (tid == 0) {
+        const uint32_t groups = total[0] ? (total[0] - 1u) / kHot + 1u : 0u;
+        b.group_from[0] = 0u;
+        if (groups) b.group_from[groups] = total[0];
+        b.head->groups = groups; b.head->pieces = total[2]; b.head->joints = total[3];
+    }
+}
+
+__global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32_t* __restrict__ in, uint32_t count, SetBuffers b) {
+    extern __shared__ uint32_t next[];                           // [kBins]: position of the workgroup's next key of the bin
+    const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
+    for (int j = threadIdx.x; j < kBins / 4; j += kSetThreads)   // (bins that the range does not hold: never read)
+        ((uint4_t*)next)[j] = ((const uint4_t*)b.start)[j] + ((const uint4_t*)mine)[j];
+    __syncthreads();
+    uint32_t lo, hi;
+    set_range(count, lo, hi);
+    uint32_t* out = b.keys;
+    for_quads(in, lo, hi, [&](uint32_t bits) {
+        const uint32_t k = f32_key(bits);
+        out[count_bin(next, k >> kBinShift)] = k;
+    });
+}
+
+__device__ __forceinline__ void add_interval(double (&s)[kSetRow], double t, int terms) {
+    const double u = t - 1.0;
+    double p = u;
+#pragma unroll
+    for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
+}
+
+// Sum over the workgroup in a fixed order; thread i < kSetRow returns with row i's total.
+template <int THREADS>
+__device__ __forceinline__ double block_sum(const double (&s)[kSetRow], double (*red)[kSetRow], int terms) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSetRow; ++k) {
+        double v = s[k];
+        if (k <= terms || k == kGapSums)                           // (the others are zero)
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+        if (lane == 0) red[wave][k] = v;
+    }
+    __syncthreads();
+    double v = 0.0;
+    if (tid < kSetRow)
+        for (int w = 0; w < THREADS / 64; ++w) v += red[w][tid];
+    return v;
+}
+
+// Sums over the intervals inside one hot bin, whose patterns are the bitmap `data`: added to s.
+__device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, double inv_mean, int terms, const SetBuffers& b,
+                                           double* table, int* wave_last, double (&s)[kSetRow]) {
+    constexpr int kWords = kBitmapWords / kSumThreads;                        // per thread: 256 patterns
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // one exponent: neighbours d patterns apart differ by d units (exactly, also in binary64)
+    const uint32_t base = bin << kBinShift, pattern = (base & 0x80000000u) ? base & 0x7FFFFFFFu : ~base;
+    const int ex = (int)((pattern >> 23) & 255u);
+    const double unit_gap = ldexp(1.0, (ex ? ex : 1) - 150);
+    for (int d = tid; d < kTable; d += kSumThreads) { const double t = (double)d * unit_gap * inv_mean; table[d] = t > 0.0 ? t * log(t) : 0.0; }
+    int last = -1;
+#pragma unroll
+    for (int j = 0; j < kWords; j += 4) {
+        const uint4_t v = *(const uint4_t*)(data + kWords * tid + j);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (w[i]) last = 32 * (kWords * tid + j + i) + 31 - __builtin_clz(w[i]);
+    }
+    // the last set bit before the thread's comes from the threads before
+    int prev = last;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { const int a = __shfl_up(prev, off, 64); if (lane >= off) prev = max(prev, a); }
+    if (lane == 63) wave_last[wave] = prev;
+    prev = __shfl_up(prev, 1, 64);
+    if (lane == 0) prev = -1;
+    __syncthreads();
+    int top = -1;
+    for (int v = 0; v < kSumThreads / 64; ++v) { if (v < wave) prev = max(prev, wave_last[v]); top = max(top, wave_last[v]); }
+    if (tid == 0) b.bin_max[bin] = base + (uint32_t)top;
+    // distances 1 .. 8 are counted for 32 patterns at once, the others taken bit by bit
+    uint32_t near[9], prior = tid ? data[kWords * tid - 1] : 0u, total = 0u;
+#pragma unroll
+    for (int d = 1; d <= 8; ++d) near[d] = 0u;
+#pragma unroll 1
+    for (int j = 0; j < kWords; ++j) {
+        const uint32_t x = data[kWords * tid + j];
+        total += __builtin_popcount(x);
+        uint32_t far = x;
+#pragma unroll
+        for (int d = 1; d <= 8; ++d) {
+            const uint32_t back = (x << d) | (prior >> (32 - d));             // pattern i: is i - d there?
+            near[d] += __builtin_popcount(far & back);
+            far &= ~back;
+        }
+#pragma unroll 1
+        while (far) {
+            const int bit = __builtin_ctz(far), at = 32 * (kWords * tid + j) + bit;
+            far &= far - 1u;
+            const uint32_t below = x & ((1u << bit) - 1u);
+            const int from = below ? 32 * (kWords * tid + j) + 31 - __builtin_clz(below) : prev;
+            if (from >= 0) {
+                const int d = at - from;
+                const double t = (double)d * unit_gap * inv_mean;
+                s[0] += d < kTable ? table[d] : t > 0.0 ? t * log(t) : 0.0;   // (t = 0: an infinite span)
+                add_interval(s, t, terms);
+            } else {
+                b.bin_min[bin] = base + (uint32_t)at;
+                total -= 1u;                                                  // no interval in front of the first
+            }
+        }
+        if (x) prev = 32 * (kWords * tid + j) + 31 - __builtin_clz(x);
+        prior = x;
+    }
+#pragma unroll
+    for (int d = 1; d <= 8; ++d) {
+        const double m = (double)near[d], u = (double)d * unit_gap * inv_mean - 1.0;
+        double p = m * u;
+        s[0] += m * table[d];
+#pragma unroll
+        for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
+    }
+    s[kGapSums] += (double)total;
+}
+
+__global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, uint32_t count, int terms) {
+    __shared__ __attribute__((aligned(16))) uint32_t data[kBitmapWords];     // a bitmap or a group's keys
+    __shared__ double table[kTable];
+    __shared__ double red[kSumThreads / 64][kSetRow];
+    __shared__ int wave_last[kSumThreads / 64];
+    __shared__ int last_piece;
+    const int tid = threadIdx.x;
+    const SetHead head = *b.head;
+    const double inv_mean = (double)(count - 1u) / (key_f64(head.max_key) - key_f64(head.min_key));
+    double s[kSetRow];                                                        // of the workgroup's units, whose choice is fixed
+#pragma unroll
+    for (int k = 0; k < kSetRow; ++k) s[k] = 0.0;
+#pragma unroll 1
+    for (uint32_t unit = blockIdx.x; unit < head.pieces + head.groups; unit += gridDim.x) {
+        __syncthreads();                                                      // data and table of the unit before are read
+        if (unit < head.pieces) {
+            const uint4_t piece = b.piece[unit];
+            const uint32_t bin = piece.x, to = piece.z;
+#pragma unroll
+            for (int j = 0; j < kBitmapWords / 4; j += kSumThreads) ((uint4_t*)data)[j + tid] = uint4_t{0u, 0u, 0u, 0u};
+            __syncthreads();
+            uint32_t i = piece.y + tid;
+            auto set = [&](uint32_t k) {                                      // (a wavefront of equal keys: one of them)
+                const unsigned long long live = __builtin_amdgcn_ballot_w64(true);
+                const bool equal = __builtin_amdgcn_ballot_w64(k == (uint32_t)__builtin_amdgcn_readfirstlane((int)k)) == live;
+                if (!equal || (live & lanes_below(tid & 63)) == 0ull) atomicOr(&data[(k >> 5) & (kBitmapWords - 1)], 1u << (k & 31u));
+            };
+#pragma unroll 1
+            for (; (unsigned long long)i + 7u * kSumThreads < to; i += 8u * kSumThreads) {
+                uint32_t k[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) k[j] = b.keys[i + j * kSumThreads];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) set(k[j]);
+            }
+            for (; i < to; i += kSumThreads) set(b.keys[i]);
+            __syncthreads();
+            const bool joined = piece.w != 0xFFFFFFFFu;
+            if (joined) {
+                uint32_t* joint = b.joint + (size_t)piece.w * kBitmapWords;
+                for (int j = tid; j < kBitmapWords; j += kSumThreads)
+                    if (data[j]) atomicOr(&joint[j], data[j]);
+                __threadfence();
+                __syncthreads();
+                if (tid == 0) last_piece = atomicAdd(&b.done[piece.w], 1u) == (b.counts[bin] - 1u) / kPiece;
+                __syncthreads();
+                if (!last_piece) continue;
+                __threadfence();
+                for (int j = tid; j < kBitmapWords; j += kSumThreads)
+                    data[j] = __hip_atomic_load(&joint[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __syncthreads();
+            }
+            double own[kSetRow];
+#pragma unroll
+            for (int k = 0; k < kSetRow; ++k) own[k] = 0.0;
+            add_bitmap(data, bin, inv_mean, terms, b, table, wave_last, own);
+            if (joined) {                                                     // which workgroup is last is not fixed: a row of its own
+                const double v = block_sum<kSumThreads>(own, red, terms);
+                if (tid < kSetRow) b.sums[(size_t)(kSumWorkgroups + piece.w) * kSetRow + tid] = v;
+            } else {
+#pragma unroll
+                for (int k = 0; k < kSetRow; ++k) s[k] += own[k];
+            }
+        } else {
+            const uint32_t from = b.group_from[unit - head.pieces], to = b.group_from[unit - head.pieces + 1u];
+            const uint32_t n = to - from;                                     // at most 2047
+            uint32_t size = 2u;
+            while (size < n) size *= 2u;
+            for (uint32_t i = tid; i < size; i += kSumThreads) data[i] = i < n ? b.keys[from + i] : 0xFFFFFFFFu;
+            for (uint32_t len = 2u; len <= size; len *= 2u)
+                for (uint32_t step = len / 2u; step; step /= 2u) {
+                    __syncthreads();
+                    for (uint32_t p = tid; p < size / 2u; p += kSumThreads) {
+                        const uint32_t lo = 2u * p - (p & (step - 1u)), hi = lo + step;
+                        const uint32_t x = data[lo], y = data[hi];
+                        if ((x > y) == ((lo & len) == 0u)) { data[lo] = y; data[hi] = x; }
+                    }
+                }
+            __syncthreads();
+#pragma unroll 1
+            for (uint32_t i = tid; i < n; i += kSumThreads) {
+                const uint32_t k = data[i], bin = k >> kBinShift;
+                if (i == 0u || data[i - 1u] >> kBinShift != bin) b.bin_min[bin] = k;
+                if (i + 1u == n || data[i + 1u] >> kBinShift != bin) { b.bin_max[bin] = k; continue; }
+                const uint32_t k1 = data[i + 1u];
+                if (k1 == k) continue;
+                const double t = (key_f64(k1) - key_f64(k)) * inv_mean;
+                if (t > 0.0) s[0] += t * log(t);
+                s[kGapSums] += 1.0;
+                add_interval(s, t, terms);
+            }
+        }
+    }
+    const double v = block_sum<kSumThreads>(s, red, terms);
+    if (tid < kSetRow) b.sums[(size_t)blockIdx.x * kSetRow + tid] = v;
+}
+
+__global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetBuffers b, uint32_t count, int terms, double tau_c, double tau_f,
+                                                                double* __restrict__ out, int32_t* __restrict__ phi) {
+    extern __shared__ uint32_t next[];
+    uint16_t* list = (uint16_t*)next;                                         // [kBins]: the occupied bins
+    __shared__ double red[kSetThreads / 64][kSetRow];
+    __shared__ double tot[kSetRow];
+    __shared__ uint32_t wave_sum[kSetThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const SetHead head = *b.head;
+    const double span = key_f64(head.max_key) - key_f64(head.min_key);
+    const double inv_mean = (double)(count - 1u) / span;
+    double s[kSetRow];
+#pragma unroll
+    for (int k = 0; k < kSetRow; ++k) s[k] = 0.0;
+    for (uint32_t i = tid; i < kSumWorkgroups + head.joints; i += kSetThreads) {
+#pragma unroll
+        for (int k = 0; k < kSetRow; ++k) s[k] += b.sums[(size_t)i * kSetRow + k];
+    }
+    uint32_t occupied = b.occupied[tid];                                      // of 32 consecutive bins
+    const uint32_t own = __builtin_popcount(occupied);
+    uint32_t at = own, bins = 0u;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)at, off, 64); if (lane >= off) at += a; }
+    if (lane == 63) wave_sum[wave] = at;
+    at -= own;
+    __syncthreads();
+    for (int v = 0; v < kSetThreads / 64; ++v) { if (v < wave) at += wave_sum[v]; bins += wave_sum[v]; }
+    for (; occupied; occupied &= occupied - 1u) list[at++] = (uint16_t)(32 * tid + __builtin_ctz(occupied));
+    __syncthreads();
+    // the interval in front of every occupied bin but the first
+    for (uint32_t i = tid + 1u; i < bins; i += kSetThreads) {
+        const double t = (key_f64(b.bin_min[list[i]]) - key_f64(b.bin_max[list[i - 1u]])) * inv_mean;     // (zero between -0 and +0)
+        if (t > 0.0) s[0] += t * log(t);
+        s[kGapSums] += 1.0;
+        add_interval(s, t, terms);
+    }
+    const double v = block_sum<kSetThreads>(s, red, terms);
+    if (tid < kSetRow) tot[tid] = v;
+    __syncthreads();
+    if (tid == 0) {
+        const double n = (double)(count - 1u), equal = n - tot[kGapSums];                         // intervals between equal weights
+        double Pc = 0.0, Pf = 0.0;
+        if (span > 0.0) {                        // a constant matrix has no intervals to normalise: both proxies 0
+            Pc = tot[0] / n;
+            for (int k = 2; k <= terms; ++k) Pf += fabs(tot[k] + (k & 1 ? -equal : equal)) / (n * (double)(k * (k - 1)));
+        }
+        out[0] = Pc;
+        out[1] = Pf;
+        *phi = (Pc < tau_c && Pf < tau_f) ? 1 : 0;
+    }
+}
+
+static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, double tau_c, double tau_f, void* workspace,
+                              double* out, int32_t* phi, hipStream_t s) {
+    const SetBuffers b = set_buffers((char*)workspace, count);
+    const uint32_t wgs = set_workgroups(count);
+    constexpr int lds = kBins * 4;                               // 128 of the 160 KB of a compute unit
+    for (const void* f : {(const void*)set_count_kernel, (const void*)set_partition_kernel, (const void*)set_final_kernel}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(set_clear_kernel, dim3(256), dim3(256), 0, s, b, set_joint_max(count));
+    hipLaunchKernelGGL(set_count_kernel, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
+    hipLaunchKernelGGL(set_plan_kernel, dim3(1), dim3(kSetThreads), 0, s, b, wgs);
+    hipLaunchKernelGGL(set_partition_kernel, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
+    hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups), dim3(kSumThreads), 0, s, b, count, terms);
+    hipLaunchKernelGGL(set_final_kernel, dim3(1), dim3(kSetThreads), kBins * 2, s, b, count, terms, tau_c, tau_f, out, phi);
+    return hipGetLastError();
+}
+
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct F32Layout { size_t keys_a, keys_b, counts, totals, partial, bytes; };
@@ -320,6 +844,12 @@ hipError_t launch_proxy_f32(const void* const* ws, const int* Ns, const int* Ks,
         const uint32_t count = (uint32_t)((unsigned long long)Ns[i] * (unsigned long long)Ks[i]);
         const uint32_t tiles = (uint32_t)(((unsigned long long)count + kSortTile - 1) / kSortTile);   // count may be 2^32 - 1
         const uint32_t* src = (const uint32_t*)ws[i];
+        // (the workspace is sized for the sort's two key buffers and its counts; the sets take less from kSetMinCount on)
+        if (count >= kSetMinCount && set_buffers(nullptr, count).bytes <= L.bytes) {
+            const hipError_t e = launch_sets(src, count, terms, tau_c, tau_f, workspace, out + 2 * i, phi + i, s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         for (int pass = 0; pass < 4; ++pass) {
             uint32_t* dst = buf[pass & 1];
             if (pass == 0) hipLaunchKernelGGL(sort_hist_kernel<true>, dim3(tiles), dim3(kSortThreads), 0, s, src, count, 0, counts, tiles);

@@ -1,0 +1,82 @@
+"""The binary32 proxy from 2^19 weights on (partition into bins, sets of values) against the definition: every kind of bin (sorted
+groups, bitmaps, bitmaps joined from several pieces), ties, both zeros, subnormals, ragged sizes; and the same answers as the
+radix sort of smaller matrices where the definition has none."""
+import numpy as np
+import pytest
+
+from oracle import proxy_oracle as PO
+from paper_2505_03803_amd import synth
+
+pytestmark = pytest.mark.gpu
+REL = 1e-9
+BIG = 1 << 19
+
+
+def run(w, terms=5):
+    import torch
+    from paper_2505_03803_amd import binding as B
+    w = np.ascontiguousarray(w, dtype=np.float32).reshape(1, -1)
+    return B.proxy([torch.from_numpy(w).cuda()], B.F32, terms, 1.5, 50.0)[0]
+
+
+def check(w, terms=5):
+    ePc, ePf = PO.proxies(np.asarray(w, np.float32).reshape(1, -1).astype(np.float64), terms)
+    Pc, Pf, _ = got = run(w, terms)
+    assert Pc == pytest.approx(ePc, rel=REL, abs=1e-12), (Pc, ePc)
+    assert Pf == pytest.approx(ePf, rel=REL, abs=1e-12), (Pf, ePf)
+    assert run(w, terms) == got                                 # the same bits again
+
+
+@pytest.mark.parametrize("n", [BIG - 1, BIG, BIG + 1, BIG + 3 * 4096 + 2, 3 * BIG + 5])
+def test_proxy_sets_sizes(n):
+    rng = np.random.default_rng(n)
+    for terms in (2, 5, 8):
+        check(synth.gen_dense_weights(rng, 1, n, "f32", outlier_fraction=1e-3), terms)
+
+
+@pytest.mark.parametrize("kind", ["patterns", "zeros", "bf16", "spaced", "two", "one_bin", "few_bins"])
+def test_proxy_sets_kinds(kind):
+    rng = np.random.default_rng(31)
+    n = BIG + 777
+    w = rng.standard_normal(n).astype(np.float32)
+    if kind == "patterns":                                      # bits at random: thousands of small bins, subnormals
+        bits = rng.integers(0, 1 << 32, n, dtype=np.uint32)
+        bits &= np.where((bits >> 23) & 255 == 255, np.uint32(0xBFFFFFFF), np.uint32(0xFFFFFFFF)).astype(np.uint32)
+        w = bits.view(np.float32)
+    elif kind == "zeros":                                       # bins of several pieces, one value and two zeros
+        w[rng.random(n) < 0.7] = 0.0
+        w[::11] = -0.0
+        w[::101] = 1e-45
+    elif kind == "bf16":
+        w = (w.view(np.uint32) & 0xFFFF0000).view(np.float32)
+    elif kind == "spaced":
+        w = rng.permutation(np.arange(n, dtype=np.float32) * 0.25 - 1000.0)
+    elif kind == "two":
+        w = np.where(rng.random(n) < 0.5, np.float32(1.0), np.float32(2.0))
+    elif kind == "one_bin":                                     # one bin of several pieces, dense
+        w = (1.0 + rng.integers(0, 1 << 17, n) * 2.0 ** -23).astype(np.float32)
+    elif kind == "few_bins":                                    # around 4096 and 131072 keys per bin
+        sizes = [4095, 4096, 4097, 8191, 131071, 131072, 131073, 262145]
+        m = np.repeat(np.arange(len(sizes)), sizes)
+        fine = rng.integers(0, 1 << 17, m.size)
+        a = (((127 << 6) + m) << 17 | fine).astype(np.uint32)
+        w = np.concatenate([a, a | np.uint32(0x80000000)]).view(np.float32)
+        w = rng.permutation(w)
+    assert w.size >= BIG
+    if kind == "spaced":
+        Pc, Pf, _ = run(w)
+        assert abs(Pc) < 1e-12 and abs(Pf) < 1e-9
+    else:
+        check(w)
+    check(np.full(BIG, 0.375, np.float32)) if kind == "two" else None
+
+
+def test_proxy_sets_not_finite():
+    rng = np.random.default_rng(8)
+    for bad in ([np.inf], [-np.inf], [np.inf, -np.inf], [np.nan], [-np.nan, np.inf]):
+        out = []
+        for n in (4096, BIG):
+            w = rng.standard_normal(n).astype(np.float32)
+            w[5:5 + len(bad)] = bad
+            out.append(run(w))
+        assert np.array_equal(np.array(out[0]), np.array(out[1]), equal_nan=True), (bad, out)
