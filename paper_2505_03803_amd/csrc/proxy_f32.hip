@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //   * set_plan_kernel       where each bin starts.  Bins of more than 1024 keys ("hot", of near-normal weights the ones
 //                           within some octaves of the deviation) stand behind the others, in groups of at most 2047 keys;
 //   * set_partition_kernel  every key to its bin: position = start + reservation + an LDS counter per bin.  The order inside a
-//                           bin does not matter (and is not fixed), so no ranks and no reordering are needed;
+//                           bin does not matter (and is not fixed), so no ranks are needed;
 //   * set_sum_kernel        a hot bin is 2^17 patterns of one sign and exponent: a bitmap of 16 KB in LDS.  Intervals are
 //                           distances of set bits times the exponent's unit, exact; t ln t of the small distances comes from
 //                           a table made with the same expressions.  A bin of more than 131072 keys is read by several
@@ -297,11 +297,10 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
-// Bound: the partition's stores, four bytes each to a line of their own (470 MB at 1 TB/s for
-// 14336 x 4096), then bytes.  Measured (us; radix sort -> here): 768 x 768 159 -> 102, 1024 x 1024 164 -> 111, 4096 x 4096
-// 500 -> 207, 14336 x 4096 1954 -> 750 (count 56, plan 16, partition 460, sum 200, final 12); all weights equal 1563 -> 352,
-// values of bfloat16 1781 -> 854, half the weights zero 1866 -> 650.  Below kSetMinCount, where no such table fits the
-// workspace, the sort.
+// Bound: LDS (the partition's counters and reordering, the bitmaps' additions), not memory: 16 bytes per weight at 1.7 TB/s
+// for 14336 x 4096.  Measured (us; radix sort -> here): 768 x 768 159 -> 102, 1024 x 1024 164 -> 111, 4096 x 4096 500 -> 177,
+// 14336 x 4096 1954 -> 545 (count 63, plan 16, partition 239, sum 208, final 12); there with all weights equal 1563 -> 404,
+// values of bfloat16 1781 -> 641, half the weights zero 1866 -> 551.  Below kSetMinCount the sort.
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
 constexpr int kBins = 32768, kBinShift = 17;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
@@ -518,19 +517,81 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
     }
 }
 
+// Stored where it is met, a key is a request of four bytes to a line of its own.  TILED: 4096 keys at a time are brought into
+// the order of their class first (the lower 11 bits of the bin: keys of one bin stand together, whatever else is in the class),
+// so that a wavefront's store meets runs.  Measured (us; not tiled, tiled): 1280 x 1280 35, 44; 2048 x 2048 even; 4096 x 4096
+// 103, 70; 14336 x 4096 460, 239: tiled from kTiledMinCount on.
+constexpr int kClasses = 2048;
+constexpr uint32_t kTiledMinCount = 1u << 22;
+template <bool TILED>
 __global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32_t* __restrict__ in, uint32_t count, SetBuffers b) {
     extern __shared__ uint32_t next[];                           // [kBins]: position of the workgroup's next key of the bin
+    uint32_t* tile = next + kBins;                               // [4 kSetThreads]
+    uint32_t* cls = tile + 4 * kSetThreads;                      // [kClasses]: keys of the class, then their first place
+    uint32_t* wave_sum = cls + kClasses;                         // [kSetThreads / 64]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
-    for (int j = threadIdx.x; j < kBins / 4; j += kSetThreads)   // (bins that the range does not hold: never read)
+    for (int j = tid; j < kBins / 4; j += kSetThreads)           // (bins that the range does not hold: never read)
         ((uint4_t*)next)[j] = ((const uint4_t*)b.start)[j] + ((const uint4_t*)mine)[j];
-    __syncthreads();
     uint32_t lo, hi;
     set_range(count, lo, hi);
     uint32_t* out = b.keys;
-    for_quads(in, lo, hi, [&](uint32_t bits) {
-        const uint32_t k = f32_key(bits);
-        out[count_bin(next, k >> kBinShift)] = k;
-    });
+    if constexpr (!TILED) {
+        __syncthreads();
+        for_quads(in, lo, hi, [&](uint32_t bits) {
+            const uint32_t k = f32_key(bits);
+            out[count_bin(next, k >> kBinShift)] = k;
+        });
+        return;
+    }
+    static_assert(kClasses == 2 * kSetThreads, "two classes per thread");
+    *(uint2_t*)(cls + 2 * tid) = uint2_t{0u, 0u};
+    const uint32_t quads = (hi - lo) / 4u;
+    const uint4_t* src = (const uint4_t*)(in + lo);
+    uint4_t v = tid < (int)min(quads, (uint32_t)kSetThreads) ? src[tid] : uint4_t{0u, 0u, 0u, 0u};
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t base = 0u; base < quads; base += kSetThreads) {
+        const uint32_t in_tile = 4u * min(quads - base, (uint32_t)kSetThreads);
+        const bool valid = 4u * tid < in_tile;
+        const uint32_t k[4] = {f32_key(v.x), f32_key(v.y), f32_key(v.z), f32_key(v.w)};
+        uint32_t rank[4];
+        if (valid)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rank[j] = count_bin(cls, (k[j] >> kBinShift) & (kClasses - 1));
+        if (base + kSetThreads + tid < quads) v = src[base + kSetThreads + tid];
+        __syncthreads();
+        const uint2_t n = *(const uint2_t*)(cls + 2 * tid);
+        uint32_t at = n.x + n.y;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)at, off, 64); if (lane >= off) at += a; }
+        if (lane == 63) wave_sum[wave] = at;
+        at -= n.x + n.y;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSetThreads / 64; ++w) at += w < wave ? wave_sum[w] : 0u;
+        *(uint2_t*)(cls + 2 * tid) = uint2_t{at, at + n.x};
+        __syncthreads();
+        if (valid)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) tile[cls[(k[j] >> kBinShift) & (kClasses - 1)] + rank[j]] = k[j];
+        __syncthreads();
+        *(uint2_t*)(cls + 2 * tid) = uint2_t{0u, 0u};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t i = (uint32_t)(tid + j * kSetThreads);
+            if (i < in_tile) {
+                const uint32_t key = tile[i];
+                out[count_bin(next, key >> kBinShift)] = key;
+            }
+        }
+        __syncthreads();
+    }
+    const uint32_t rest = lo + 4u * quads + tid;
+    if (rest < hi) {
+        const uint32_t key = f32_key(in[rest]);
+        out[count_bin(next, key >> kBinShift)] = key;
+    }
 }
 
 __device__ __forceinline__ void add_interval(double (&s)[kSetRow], double t, int terms) {
@@ -787,15 +848,18 @@ static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, doub
                               double* out, int32_t* phi, hipStream_t s) {
     const SetBuffers b = set_buffers((char*)workspace, count);
     const uint32_t wgs = set_workgroups(count);
-    constexpr int lds = kBins * 4;                               // 128 of the 160 KB of a compute unit
-    for (const void* f : {(const void*)set_count_kernel, (const void*)set_partition_kernel, (const void*)set_final_kernel}) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    constexpr int lds = kBins * 4, lds_partition = lds + (4 * kSetThreads + kClasses + kSetThreads / 64) * 4;   // 128 and 152 KB
+    static_assert(lds_partition <= 160 * 1024, "LDS of a compute unit");
+    for (const void* f : {(const void*)set_count_kernel, (const void*)set_partition_kernel<false>, (const void*)set_partition_kernel<true>,
+                          (const void*)set_final_kernel}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_partition);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(set_clear_kernel, dim3(256), dim3(256), 0, s, b, set_joint_max(count));
     hipLaunchKernelGGL(set_count_kernel, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
     hipLaunchKernelGGL(set_plan_kernel, dim3(1), dim3(kSetThreads), 0, s, b, wgs);
-    hipLaunchKernelGGL(set_partition_kernel, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
+    if (count > kTiledMinCount) hipLaunchKernelGGL(set_partition_kernel<true>, dim3(wgs), dim3(kSetThreads), lds_partition, s, w, count, b);
+    else hipLaunchKernelGGL(set_partition_kernel<false>, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
     hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups), dim3(kSumThreads), 0, s, b, count, terms);
     hipLaunchKernelGGL(set_final_kernel, dim3(1), dim3(kSetThreads), kBins * 2, s, b, count, terms, tau_c, tau_f, out, phi);
     return hipGetLastError();

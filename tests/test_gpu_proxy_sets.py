@@ -27,10 +27,10 @@ def check(w, terms=5):
     assert run(w, terms) == got                                 # the same bits again
 
 
-@pytest.mark.parametrize("n", [BIG - 1, BIG, BIG + 1, BIG + 3 * 4096 + 2, 3 * BIG + 5])
+@pytest.mark.parametrize("n", [BIG - 1, BIG, BIG + 1, BIG + 3 * 4096 + 2, 3 * BIG + 5, 8 * BIG, 8 * BIG + 4099])
 def test_proxy_sets_sizes(n):
     rng = np.random.default_rng(n)
-    for terms in (2, 5, 8):
+    for terms in (2, 5, 8) if n < 8 * BIG else (5,):          # (8 BIG + 1 on: the keys reordered in tiles)
         check(synth.gen_dense_weights(rng, 1, n, "f32", outlier_fraction=1e-3), terms)
 
 
@@ -63,6 +63,8 @@ def test_proxy_sets_kinds(kind):
         w = np.concatenate([a, a | np.uint32(0x80000000)]).view(np.float32)
         w = rng.permutation(w)
     assert w.size >= BIG
+    if kind != "spaced":                                        # the same kind large enough for the tiled partition, ragged
+        check(np.concatenate([np.resize(w, 8 * BIG), w[:4099]]))
     if kind == "spaced":
         Pc, Pf, _ = run(w)
         assert abs(Pc) < 1e-12 and abs(Pf) < 1e-9
