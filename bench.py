@@ -988,24 +988,25 @@ def main():
             vms = vt / 10
             nw = sum(a * b for a, b in shapes)
             sq_bytes = nw * 2 + nw * 3 // 8 + nw // 128 * 4          # dense in, codes + scale + zero out
-            vq_flop = (nw // 2) * 64 * 5                             # 2 sub, 2 mul, 1 add per pair and entry
+            vq_bytes = nw * 2 + nw * 3 // 8                          # dense in, indices out
             out["encode"] = {
                 "sq": {"value": sq_bytes / (sms * 1e-3) / 1e9, "unit": "GB/s", "ms_per_step": sms, "dtype": "f32",
                        "bytes_per_step": sq_bytes},
-                "vq6": {"value": vq_flop / (vms * 1e-3) / 1e12, "unit": "TFLOP/s", "ms_per_step": vms, "dtype": "f32",
-                        "flop_per_step": vq_flop},
+                "vq6": {"value": vq_bytes / (vms * 1e-3) / 1e9, "unit": "GB/s", "ms_per_step": vms, "dtype": "f32",
+                        "bytes_per_step": vq_bytes},
                 "workload": "the proxy leg's %d dense bf16 matrices: round-to-nearest SQ (3 bit, g128) and "
                             "nearest-entry assignment to 64-entry codebooks" % n}
             out["roofline_sq_encode"] = {"kernel": "rwkvq::sq_encode_kernel", "bound": "hbm",
                                          "achieved": sq_bytes / (sms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                          "frac": sq_bytes / (sms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
                                          "avg_launch_ms": sms / n}
-            out["roofline_vq_assign"] = {"kernel": "rwkvq::vq_assign_kernel<6>", "bound": "alu",
-                                         "achieved": vq_flop / (vms * 1e-3) / 1e12, "peak": 157.3, "unit": "TFLOP/s",
-                                         "frac": vq_flop / (vms * 1e-3) / 1e12 / 157.3, "traffic": None,
+            out["roofline_vq_assign"] = {"kernel": "rwkvq::vq_assign_kernel<6>", "bound": "hbm",
+                                         "achieved": vq_bytes / (vms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                                         "frac": vq_bytes / (vms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
                                          "avg_launch_ms": vms / n,
-                                         "note": "no step of the distance is a fused multiply-add (each is rounded "
-                                                 "separately), so the reachable rate is half the FMA-counted peak"}
+                                         "note": "a pair is compared with the entries listed for its cell, 3 of 64 on average: "
+                                                 "operations per pair depend on the data, so the rate is of dense and index bytes; "
+                                                 "vector ALU and LDS look-ups bound it"}
             del codes, sc, zr, idx, cbs
         del mats, table, wsp, pout, pphi
         torch.cuda.empty_cache()
