@@ -21,6 +21,7 @@
 //
 // Matrices of a call are processed one after another on the stream and share the sort buffers.
 #include "common.h"
+#include "proxy_ranges.h"
 #include "../../include/rwkvq.h"
 
 namespace rwkvq {
@@ -304,9 +305,7 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
 constexpr int kBins = 32768, kBinShift = 17;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
-constexpr uint32_t kPiece = 131072;                          // keys of a hot bin that one workgroup reads
 constexpr int kBitmapWords = 1 << (kBinShift - 5);           // 4096
-constexpr uint32_t kCountRange = 49152;                      // fewest keys per counting workgroup
 constexpr int kSetThreads = 1024;
 constexpr int kSetRow = kGapSums + 1;                        // partial sums and the number of intervals above zero
 constexpr int kSumThreads = 512, kSumWorkgroups = 512;
@@ -325,13 +324,12 @@ struct SetBuffers {
     uint32_t* group_from;    // [group + 1]: position of the group's first key
     uint32_t* bin_min;       // [bin], of occupied bins
     uint32_t* bin_max;
-    uint4_t* piece;          // [piece]: bin, first and end position, joint bitmap of a bin in several pieces
+    uint4_t* piece;          // [piece]: bin, first position, keys, joint bitmap of a bin in several pieces
     uint32_t* done;          // [joint]: pieces finished
     uint32_t* joint;         // [joint][4096]
     double* sums;            // [workgroups of set_sum_kernel, then joint bins][kSetRow]
     size_t bytes;
 };
-static uint32_t set_workgroups(uint32_t count) { return count / kCountRange < 256u ? count / kCountRange : 256u; }
 static uint32_t set_joint_max(uint32_t count) { return count / kPiece; }
 
 static SetBuffers set_buffers(char* base, uint32_t count) {
@@ -364,30 +362,20 @@ __global__ void __launch_bounds__(256) set_clear_kernel(SetBuffers b, uint32_t j
     for (size_t j = i; j < (size_t)joint_max * kBitmapWords / 4; j += step) ((uint4_t*)b.joint)[j] = uint4_t{0u, 0u, 0u, 0u};
 }
 
-// The contiguous range of keys of a counting or partitioning workgroup: [lo, hi), lo a multiple of four.
-__device__ __forceinline__ void set_range(uint32_t count, uint32_t& lo, uint32_t& hi) {
-    const uint32_t per = ((count - 1u) / gridDim.x + 4u) & ~3u;
-    const unsigned long long l = (unsigned long long)per * blockIdx.x, h = l + per;
-    lo = l < count ? (uint32_t)l : count;
-    hi = h < count ? (uint32_t)h : count;
-}
-
-// Applies f(four patterns, how many are valid) to the range, four loads of 16 bytes in flight per thread.
+// Applies f to every pattern of the range, four loads of 16 bytes in flight per thread.
 template <class F>
-__device__ __forceinline__ void for_quads(const uint32_t* __restrict__ in, uint32_t lo, uint32_t hi, F f) {
-    const uint32_t quads = (hi - lo) / 4u;
-    const uint4_t* q = (const uint4_t*)(in + lo);
+__device__ __forceinline__ void for_quads(const uint32_t* __restrict__ in, const SetRange& r, F f) {
+    const uint4_t* q = (const uint4_t*)(in + r.lo);
     uint32_t i = threadIdx.x;
-    for (; i + 3u * kSetThreads < quads; i += 4u * kSetThreads) {
+    for (; i + 3u * kSetThreads < r.quads; i += 4u * kSetThreads) {
         uint4_t v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = q[i + j * kSetThreads];
 #pragma unroll
         for (int j = 0; j < 4; ++j) { f(v[j].x); f(v[j].y); f(v[j].z); f(v[j].w); }
     }
-    for (; i < quads; i += kSetThreads) { const uint4_t v = q[i]; f(v.x); f(v.y); f(v.z); f(v.w); }
-    const uint32_t rest = lo + 4u * quads + threadIdx.x;
-    if (rest < hi) f(in[rest]);
+    for (; i < r.quads; i += kSetThreads) { const uint4_t v = q[i]; f(v.x); f(v.y); f(v.z); f(v.w); }
+    if (threadIdx.x < r.rest) f(in[r.tail(threadIdx.x)]);
 }
 
 // Adds one to counter[bin] and gives its value before.  A wavefront whose lanes all hold one bin (equal weights) adds once.
@@ -408,9 +396,8 @@ __global__ void __launch_bounds__(kSetThreads) set_count_kernel(const uint32_t* 
     const int tid = threadIdx.x;
     for (int j = tid; j < kBins / 4; j += kSetThreads) ((uint4_t*)h)[j] = uint4_t{0u, 0u, 0u, 0u};
     __syncthreads();
-    uint32_t lo, hi, least = 0xFFFFFFFFu, most = 0u;
-    set_range(count, lo, hi);
-    for_quads(in, lo, hi, [&](uint32_t bits) {
+    uint32_t least = 0xFFFFFFFFu, most = 0u;
+    for_quads(in, set_range(count, blockIdx.x, gridDim.x), [&](uint32_t bits) {
         const uint32_t k = f32_key(bits);
         least = min(least, k); most = max(most, k);
         count_bin(h, k >> kBinShift);
@@ -491,9 +478,8 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
                 if (run[0] / kHot != at[j] / kHot) b.group_from[run[0] / kHot] = run[0];
             } else {
                 at[j] = total[0] + run[1];
-                for (uint32_t f = 0u; f < n; f += min(kPiece, n - f))
-                    b.piece[run[2]++] = uint4_t{(uint32_t)(32 * tid + 4 * q + j), at[j] + f, at[j] + f + min(kPiece, n - f),
-                                                n > kPiece ? run[3] : 0xFFFFFFFFu};
+                for (uint32_t f = 0u; f < n; f += piece_keys(n, f))
+                    b.piece[run[2]++] = uint4_t{(uint32_t)(32 * tid + 4 * q + j), at[j] + f, piece_keys(n, f), n > kPiece ? run[3] : 0xFFFFFFFFu};
                 run[1] += n; run[3] += n > kPiece ? 1u : 0u;
             }
         }
@@ -533,12 +519,11 @@ __global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32
     const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
     for (int j = tid; j < kBins / 4; j += kSetThreads)           // (bins that the range does not hold: never read)
         ((uint4_t*)next)[j] = ((const uint4_t*)b.start)[j] + ((const uint4_t*)mine)[j];
-    uint32_t lo, hi;
-    set_range(count, lo, hi);
+    const SetRange r = set_range(count, blockIdx.x, gridDim.x);
     uint32_t* out = b.keys;
     if constexpr (!TILED) {
         __syncthreads();
-        for_quads(in, lo, hi, [&](uint32_t bits) {
+        for_quads(in, r, [&](uint32_t bits) {
             const uint32_t k = f32_key(bits);
             out[count_bin(next, k >> kBinShift)] = k;
         });
@@ -546,8 +531,8 @@ __global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32
     }
     static_assert(kClasses == 2 * kSetThreads, "two classes per thread");
     *(uint2_t*)(cls + 2 * tid) = uint2_t{0u, 0u};
-    const uint32_t quads = (hi - lo) / 4u;
-    const uint4_t* src = (const uint4_t*)(in + lo);
+    const uint32_t quads = r.quads;
+    const uint4_t* src = (const uint4_t*)(in + r.lo);
     uint4_t v = tid < (int)min(quads, (uint32_t)kSetThreads) ? src[tid] : uint4_t{0u, 0u, 0u, 0u};
     __syncthreads();
 #pragma unroll 1
@@ -587,9 +572,8 @@ __global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32
         }
         __syncthreads();
     }
-    const uint32_t rest = lo + 4u * quads + tid;
-    if (rest < hi) {
-        const uint32_t key = f32_key(in[rest]);
+    if (threadIdx.x < r.rest) {
+        const uint32_t key = f32_key(in[r.tail(threadIdx.x)]);
         out[count_bin(next, key >> kBinShift)] = key;
     }
 }
@@ -712,25 +696,26 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, u
         __syncthreads();                                                      // data and table of the unit before are read
         if (unit < head.pieces) {
             const uint4_t piece = b.piece[unit];
-            const uint32_t bin = piece.x, to = piece.z;
+            const uint32_t bin = piece.x, n = piece.z;
+            const uint32_t* keys = b.keys + piece.y;                          // n <= kPiece: counters from here on cannot wrap
 #pragma unroll
             for (int j = 0; j < kBitmapWords / 4; j += kSumThreads) ((uint4_t*)data)[j + tid] = uint4_t{0u, 0u, 0u, 0u};
             __syncthreads();
-            uint32_t i = piece.y + tid;
+            uint32_t i = tid;
             auto set = [&](uint32_t k) {                                      // (a wavefront of equal keys: one of them)
                 const unsigned long long live = __builtin_amdgcn_ballot_w64(true);
                 const bool equal = __builtin_amdgcn_ballot_w64(k == (uint32_t)__builtin_amdgcn_readfirstlane((int)k)) == live;
                 if (!equal || (live & lanes_below(tid & 63)) == 0ull) atomicOr(&data[(k >> 5) & (kBitmapWords - 1)], 1u << (k & 31u));
             };
 #pragma unroll 1
-            for (; (unsigned long long)i + 7u * kSumThreads < to; i += 8u * kSumThreads) {
+            for (; i + 7u * kSumThreads < n; i += 8u * kSumThreads) {
                 uint32_t k[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) k[j] = b.keys[i + j * kSumThreads];
+                for (int j = 0; j < 8; ++j) k[j] = keys[i + j * kSumThreads];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) set(k[j]);
             }
-            for (; i < to; i += kSumThreads) set(b.keys[i]);
+            for (; i < n; i += kSumThreads) set(keys[i]);
             __syncthreads();
             const bool joined = piece.w != 0xFFFFFFFFu;
             if (joined) {

@@ -1,0 +1,29 @@
+// How the keys of a binary32 matrix are dealt to workgroups (proxy_f32.hip, "partition and sets of values").  A matrix may have
+// 2^32 - 1 of them, so no sum below may pass 2^32.  Plain constant expressions, which the kernels and host code both evaluate.
+#pragma once
+#include <stdint.h>
+
+namespace rwkvq {
+
+constexpr uint32_t kCountRange = 49152;        // fewest keys per counting workgroup
+constexpr uint32_t kPiece = 131072;            // keys of a hot bin that one workgroup reads
+
+constexpr uint32_t set_workgroups(uint32_t count) { return count / kCountRange < 256u ? count / kCountRange : 256u; }
+
+// The contiguous range of keys of a counting or partitioning workgroup: quads groups of four from lo (a multiple of four) on,
+// then rest < 4 single keys.
+struct SetRange {
+    uint32_t lo, quads, rest;
+    constexpr uint32_t tail(uint32_t i) const { return lo + 4u * quads + i; }      // i < rest
+};
+constexpr SetRange set_range(uint32_t count, uint32_t wg, uint32_t wgs) {
+    const uint32_t per = ((count - 1u) / wgs + 4u) & ~3u;
+    const unsigned long long l = (unsigned long long)per * wg, h = l + per;
+    const uint32_t lo = l < count ? (uint32_t)l : count, hi = h < count ? (uint32_t)h : count;
+    return SetRange{lo, (hi - lo) / 4u, (hi - lo) % 4u};
+}
+
+// Keys of the piece of a hot bin of n keys that begins with its key f < n.
+constexpr uint32_t piece_keys(uint32_t n, uint32_t f) { return n - f < kPiece ? n - f : kPiece; }
+
+}  // namespace rwkvq

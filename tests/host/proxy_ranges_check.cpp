@@ -1,0 +1,43 @@
+// The ranges that the binary32 proxy deals to its workgroups (csrc/proxy_ranges.h), up to the largest matrix of 2^32 - 1 weights:
+// together they are the keys 0 .. count - 1, each once, in 32-bit arithmetic that never wraps; and so are the pieces of a bin.
+#include "proxy_ranges.h"
+
+#include <cstdio>
+
+using namespace rwkvq;
+typedef unsigned long long u64;
+
+int main() {
+    int bad = 0;
+    u64 checked = 0;
+    auto check = [&](uint32_t count) {
+        const uint32_t wgs = set_workgroups(count);
+        u64 next = 0;
+        for (uint32_t wg = 0; wg < wgs; ++wg) {
+            const SetRange r = set_range(count, wg, wgs);
+            if (next != r.lo || (r.lo % 4u && r.quads) || r.rest > 3u) ++bad;
+            next += 4ull * r.quads;
+            // every thread of a workgroup of 1024 that takes a single key takes the next one
+            for (uint32_t tid = 0; tid < 1024u; ++tid)
+                if (tid < r.rest && (u64)r.tail(tid) != next + tid) ++bad;
+            next += r.rest;
+            // the counter of a thread's strided loop over the quads
+            if (r.quads && (u64)r.quads + 4u * 1024u > 0xFFFFFFFFull) ++bad;
+        }
+        if (next != count) ++bad;
+        // a bin that holds every key
+        u64 keys = 0;
+        for (uint32_t f = 0; f < count; f += piece_keys(count, f)) {
+            if (f != keys || piece_keys(count, f) > kPiece || piece_keys(count, f) == 0u) ++bad;
+            keys += piece_keys(count, f);
+            if (keys > count) { ++bad; break; }
+        }
+        if (keys != count || (count - 1u) / kPiece + 1u != (u64)(count / kPiece) + (count % kPiece ? 1 : 0)) ++bad;
+        ++checked;
+    };
+    for (uint32_t d = 0; d < 2100u; ++d) check(0xFFFFFFFFu - d);
+    for (uint32_t d = 0; d < 600u; ++d) { check((1u << 19) + d); check((1u << 31) + d - 300u); check(256u * kCountRange + d - 300u); }
+    for (u64 c = 1u << 19; c <= 0xFFFFFFFFull; c += c / 7 + 1) check((uint32_t)c);
+    std::printf("checked %llu bad %d\n", checked, bad);
+    return bad != 0;
+}
