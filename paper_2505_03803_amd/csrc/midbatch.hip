@@ -24,6 +24,7 @@
 // LDS double: - 8 % at M = 64, + 20 % at M = 1024), fragment reads three and four rows ahead (equal), an MFMA / vector
 // instruction interleave fixed with scheduling groups (equal at MF = 4, spills at MF = 8).
 #include "matrix_core.h"
+#include "mid_tiles.h"
 #include "../../include/rwkvq.h"
 
 #include <algorithm>
@@ -33,7 +34,6 @@
 namespace rwkvq {
 
 constexpr int kMidWaves = 8;
-constexpr int kMidNF = 4;                      // 16-row tiles of W per wavefront
 constexpr int kMidBook = 1024;                 // bytes of a converted 8-bit-index codebook
 constexpr int kMidMaxMats = 64;
 
@@ -63,7 +63,8 @@ constexpr int mid_lds(int MF, int NW, bool EXACT) {
 }
 
 // Buffer loads: a descriptor and the moving offset in scalar registers, one 32-bit offset per lane (global loads came out
-// as 64-bit lane addresses, an addition and two registers each), and reads past `bytes` return zero.
+// as 64-bit lane addresses, an addition and two registers each).  The hardware's check against `bytes` leaves the scalar offset
+// out, so every offset below lies inside the matrix by itself.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t mid_buffer(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
 }
@@ -226,7 +227,8 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         xoff[i] = (uint32_t)rr * (uint32_t)K * 2u + 16u * c;
     }
     const __amdgpu_buffer_rsrc_t xbuf = mid_buffer((const char*)mt.x + (size_t)m0 * K * 2, (uint32_t)std::min(a.M - m0, 16 * MF) * (uint32_t)K * 2u);
-    const int tiles = std::min(kMidNF, (mt.N >> 4) - R0);              // EXACT: N is any multiple of 16; words past the end read as zero
+    // EXACT: N is any multiple of 16; row tiles past the end repeat the last one and are not stored
+    const int tiles = EXACT ? mid_row_tiles(mt.N, R0) : kMidNF;
     const __amdgpu_buffer_rsrc_t wbuf = mid_buffer(mt.codes + (size_t)R0 * KT * tw, (uint32_t)(tiles * KT * tw * 4));
     const __amdgpu_buffer_rsrc_t abuf = SQ ? mid_buffer((const uint2_t*)mt.aux + (size_t)R0 * KT * 16, (uint32_t)(tiles * KT * 128))
                                            : mid_buffer((const char*)mt.aux + (size_t)(R0 >> 4) * KT * kBook, (uint32_t)(KT * kBook));
@@ -245,11 +247,12 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         const int at = 16 * lane;
 #pragma unroll
         for (int i = 0; i < kMidNF; ++i) {
-            const int tile = (i * KT + T) * tw * 4;
+            const int row_tile = EXACT ? mid_row_tile(i, tiles) : i;
+            const int tile = mid_tile_offset(row_tile, T, KT, 4 * tw);
             r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, at, tile, 0);
             if constexpr (FMT == FMT_VQ8) r.b[i] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, at + 1024, tile, 0);
             else r.b[i] = __builtin_amdgcn_raw_buffer_load_b64(wbuf, (at >> 1) + 1024, tile, 0);
-            if constexpr (SQ) r.sz[i] = __builtin_amdgcn_raw_buffer_load_b64(abuf, 8 * (lane & 15), (i * KT + T) * 128, 0);
+            if constexpr (SQ) r.sz[i] = __builtin_amdgcn_raw_buffer_load_b64(abuf, 8 * (lane & 15), mid_tile_offset(row_tile, T, KT, 128), 0);
         }
         if constexpr (FMT == FMT_VQ6) r.cb = __builtin_amdgcn_raw_buffer_load_b32(abuf, at >> 2, T * kBook, 0);
         if constexpr (FMT == FMT_VQ8) r.cb8 = __builtin_amdgcn_raw_buffer_load_b128(abuf, at, T * kBook, 0);

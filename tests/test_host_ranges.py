@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "..", "paper_2505_03803_amd", "csrc")
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-@pytest.mark.parametrize("name", ["proxy_ranges_check"])
+@pytest.mark.parametrize("name", ["proxy_ranges_check", "mid_tiles_check"])
 def test_index_arithmetic(name, tmp_path):
     exe = str(tmp_path / name)
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-I", CSRC, "-o", exe, os.path.join(HERE, "host", name + ".cpp")], check=True)
