@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace rwkvq {
 
 enum Fmt : int { FMT_SQ3 = 0, FMT_VQ6 = 1, FMT_VQ8 = 2 };
@@ -203,6 +205,19 @@ hipError_t launch_token_shift_mix(const void* x, const void* x_prev, int dt, int
 hipError_t launch_wkv(const void* r, const void* k, const void* v, int dt, int M, int d, const float* w, const float* u,
                       float* state, void* out, hipStream_t s);
 hipError_t launch_pointwise(int op, const void* x, const void* y, int dt, long long n, void* out, hipStream_t s);
+
+// Lets a kernel take `bytes` of dynamic LDS (beyond 64 KB the runtime wants to be told), once per device; bit d of `raised`,
+// a static of the caller's, says that it was done on device d.
+inline hipError_t raise_lds(const void* kernel, int bytes, std::atomic<unsigned long long>& raised) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (raised.load(std::memory_order_acquire) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_release);
+    return e;
+}
 
 // Process-wide settings behind rwkvq_set_option (values of RWKVQ_OPT_* in rwkvq.h); option() is an atomic load.
 constexpr int kOptionCount = 10;

@@ -12,6 +12,7 @@
 // the same decisions.
 #include "common.h"
 
+#include <utility>
 #include <vector>
 
 namespace rwkvq {
@@ -24,8 +25,10 @@ namespace rwkvq {
 // successor is the same value again or the least key above.  One thread per position then forms the clipped mean as a binary64
 // sum in sample order.  Ranking every sample by B comparisons (the kernel this replaces: 64 workgroups for 4096 positions, B^2
 // comparisons each position) took 119 us for 128 x 4096 bf16 samples, this 8.8 us: the chain of 128 binary64 additions and
-// the trips to memory are what is left.
+// the trips to memory are what is left.  Up to 32 samples a lane counts the keys below and up to each of its own in fifteen row
+// rotations instead of 32 counts in a row (20480 positions, 16 binary32 samples: 12.5 -> 6.8 us).
 constexpr int kClipP = 16;                           // positions per workgroup
+constexpr int kClipMaxB = 1024;                      // sixteen lanes of 64 samples
 __device__ __forceinline__ int clip_at(int b, int p) { return b * kClipP + (p ^ (b & 15)); }   // sixteen samples of a position: sixteen banks
 __device__ __forceinline__ int row_sum(int v) {      // over the sixteen lanes of a DPP row, in every lane
     v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);      // quad_perm [1, 0, 3, 2]
@@ -38,6 +41,12 @@ __device__ __forceinline__ uint32_t row_min(uint32_t v) {
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true));
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));
     return min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));
+}
+template <int... R>                                  // over the sixteen values o of the DPP row: how many are below v, how many at most v
+__device__ __forceinline__ void row_rank(uint32_t o, uint32_t v, int& below, int& at_most, std::integer_sequence<int, R...>) {
+    auto other = [&](uint32_t t) { below += t < v ? 1 : 0; at_most += t <= v ? 1 : 0; };
+    other(o);
+    (other((uint32_t)__builtin_amdgcn_update_dpp(0, (int)o, 0x121 + R, 0xF, 0xF, true)), ...);     // row_ror 1 .. 15
 }
 template <int NS>
 __global__ void __launch_bounds__(256) clip_mean_select_kernel(const void* __restrict__ x, int dt, int B, int n, int k_lo,
@@ -75,34 +84,49 @@ __global__ void __launch_bounds__(256) clip_mean_select_kernel(const void* __res
         const uint32_t k = (v & 0x80000000u) ? ~v & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u) : v | 0x80000000u;
         key[i] = b < B ? k : 0xFFFFFFFFu;            // above every finite sample
     }
-    uint32_t lo = 0, hi = 0;                         // keys of the k_lo-th and k_hi-th sample
-    for (int bit = 31; bit >= (dt == DT_F32 ? 0 : 16); --bit) {
-        const uint32_t tl = lo | (1u << bit), th = hi | (1u << bit);
-        int c = 0;                                   // samples below tl, and below th in the high half
-#pragma unroll
-        for (int i = 0; i < NS; ++i) c += (key[i] < tl ? 1 : 0) + (key[i] < th ? 0x10000 : 0);
-        c = row_sum(c);
-        if ((c & 0xFFFF) <= k_lo) lo = tl;
-        if ((c >> 16) <= k_hi) hi = th;
-    }
-    int at_most = 0;
-    uint32_t next_lo = 0xFFFFFFFFu, next_hi = 0xFFFFFFFFu;
-#pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        at_most += (key[i] <= lo ? 1 : 0) + (key[i] <= hi ? 0x10000 : 0);
-        if (key[i] > lo) next_lo = min(next_lo, key[i]);
-        if (key[i] > hi) next_hi = min(next_hi, key[i]);
-    }
-    at_most = row_sum(at_most);
-    next_lo = row_min(next_lo);
-    next_hi = row_min(next_hi);
-    if ((at_most & 0xFFFF) > k_lo + 1 || k_lo + 1 >= B) next_lo = lo;
-    if ((at_most >> 16) > k_hi + 1 || k_hi + 1 >= B) next_hi = hi;
     auto value = [&](uint32_t k) {
         const uint32_t v = (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u);
         return dt == DT_F32 ? __uint_as_float(v) : dt == DT_BF16 ? __uint_as_float(v) : f16_bits_to_f32((uint16_t)(v >> 16));
     };
-    if (l == 0) { stat[0][p] = value(lo); stat[1][p] = value(next_lo); stat[2][p] = value(hi); stat[3][p] = value(next_hi); }
+    if constexpr (NS <= 2) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            int below = 0, at_most = 0;
+#pragma unroll
+            for (int j = 0; j < NS; ++j) row_rank(key[j], key[i], below, at_most, std::make_integer_sequence<int, 15>{});
+            auto is = [&](int k) { return below <= k && k < at_most; };   // the k-th, k < B (lanes that tie store the same value)
+            const float v = value(key[i]);
+            if (is(k_lo)) stat[0][p] = v;
+            if (is(min(k_lo + 1, B - 1))) stat[1][p] = v;
+            if (is(k_hi)) stat[2][p] = v;
+            if (is(min(k_hi + 1, B - 1))) stat[3][p] = v;
+        }
+    } else {
+        uint32_t lo = 0, hi = 0;                         // keys of the k_lo-th and k_hi-th sample
+        for (int bit = 31; bit >= (dt == DT_F32 ? 0 : 16); --bit) {
+            const uint32_t tl = lo | (1u << bit), th = hi | (1u << bit);
+            int c = 0;                                   // samples below tl, and below th in the high half
+#pragma unroll
+            for (int i = 0; i < NS; ++i) c += (key[i] < tl ? 1 : 0) + (key[i] < th ? 0x10000 : 0);
+            c = row_sum(c);
+            if ((c & 0xFFFF) <= k_lo) lo = tl;
+            if ((c >> 16) <= k_hi) hi = th;
+        }
+        int at_most = 0;
+        uint32_t next_lo = 0xFFFFFFFFu, next_hi = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            at_most += (key[i] <= lo ? 1 : 0) + (key[i] <= hi ? 0x10000 : 0);
+            if (key[i] > lo) next_lo = min(next_lo, key[i]);
+            if (key[i] > hi) next_hi = min(next_hi, key[i]);
+        }
+        at_most = row_sum(at_most);
+        next_lo = row_min(next_lo);
+        next_hi = row_min(next_hi);
+        if ((at_most & 0xFFFF) > k_lo + 1 || k_lo + 1 >= B) next_lo = lo;
+        if ((at_most >> 16) > k_hi + 1 || k_hi + 1 >= B) next_hi = hi;
+        if (l == 0) { stat[0][p] = value(lo); stat[1][p] = value(next_lo); stat[2][p] = value(hi); stat[3][p] = value(next_hi); }
+    }
     __syncthreads();
     const double f_v = (double)stat[0][p], f_w = (double)stat[2][p];
     const double dlo = __dadd_rn(f_v, __dmul_rn(f_lo, __dsub_rn((double)stat[1][p], f_v)));
@@ -171,14 +195,22 @@ __global__ void __launch_bounds__(256) clip_mean_kernel(const void* __restrict__
 
 hipError_t launch_clip_mean(const void* x, int dt, int B, int n, int k_lo, double f_lo, int k_hi, double f_hi,
                             float* out, hipStream_t s) {
-    // the tile of B x 16 words (with 512 bytes of order statistics and limits) has to fit 64 KB of LDS: B <= 1016
+    // a tile of B x 16 words, and up to B = 256 as many doubles (beyond, two limits per position)
     const dim3 grid((n + kClipP - 1) / kClipP), wg(256);
     const size_t lds = (size_t)B * kClipP * 4 + (B <= 256 ? (size_t)B * kClipP * 8 : 2 * kClipP * 8);
-    if (B <= 64) hipLaunchKernelGGL(clip_mean_select_kernel<4>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    if (B <= 16) hipLaunchKernelGGL(clip_mean_select_kernel<1>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else if (B <= 32) hipLaunchKernelGGL(clip_mean_select_kernel<2>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else if (B <= 64) hipLaunchKernelGGL(clip_mean_select_kernel<4>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     else if (B <= 128) hipLaunchKernelGGL(clip_mean_select_kernel<8>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     else if (B <= 256) hipLaunchKernelGGL(clip_mean_select_kernel<16>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
-    else if (B <= 1016) hipLaunchKernelGGL(clip_mean_select_kernel<64>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
-    else hipLaunchKernelGGL(clip_mean_kernel, dim3((n + 255) / 256), dim3(256), 0, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    else if (B <= kClipMaxB) {
+        // (the tile of the largest B takes all of the 64 KB that need no asking; one thread per position, the kernel below, is
+        // a hundred times slower there)
+        static std::atomic<unsigned long long> raised{0ull};
+        const hipError_t e = raise_lds((const void*)clip_mean_select_kernel<64>, kClipMaxB * kClipP * 4 + 2 * kClipP * 8, raised);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(clip_mean_select_kernel<64>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    } else hipLaunchKernelGGL(clip_mean_kernel, dim3((n + 255) / 256), dim3(256), 0, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     return hipGetLastError();
 }
 

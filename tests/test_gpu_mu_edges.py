@@ -18,7 +18,7 @@ def dev(a):
     return G.torch_().from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).cuda()
 
 
-@pytest.mark.parametrize("Bn", [2, 16, 17, 64, 65, 128, 129, 256, 257, 1016, 1017])
+@pytest.mark.parametrize("Bn", [1, 2, 16, 17, 32, 33, 64, 65, 128, 129, 256, 257, 1016, 1017, 1024, 1025])
 @pytest.mark.parametrize("dt", ["bf16", "f16", "f32"])
 def test_clip_mean_instances(Bn, dt):
     torch = G.torch_()
@@ -42,6 +42,20 @@ def test_clip_mean_instances(Bn, dt):
         torch.cuda.synchronize()
         want = MO.clip_mean(x if dt == "f32" else orc.widen(x, dt), p)
         assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), p
+
+
+def test_clip_mean_of_1024_samples_takes_the_tile():
+    """1024 samples are the most that the kernel with its samples in LDS takes; the one behind it reads them again for every rank
+    (16 positions: 0.07 and 180 ms), so a line drawn too low shows as time."""
+    torch = G.torch_()
+    x, out = torch.randn((1024, 64), device="cuda"), torch.empty(64, device="cuda")
+    B.rwkvq_clip_mean(x, B.F32, 1024, 64, 1.0, out)
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    start.record()
+    B.rwkvq_clip_mean(x, B.F32, 1024, 64, 1.0, out)
+    end.record()
+    torch.cuda.synchronize()
+    assert start.elapsed_time(end) < 10.0
 
 
 @pytest.mark.parametrize("kbits", [6, 8])
