@@ -223,6 +223,37 @@ __device__ __forceinline__ float pair_distance(float v0, float v1, float c0, flo
     return __fadd_rn(__fmul_rn(t0, t0), __fmul_rn(t1, t1));
 }
 
+// Index of the nearest of all E entries for each of P pairs (step 5 below): equal distances resolve to the lowest index, an
+// infinite or NaN distance to every entry gives 0.
+template <int P, int E>
+__device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const float* v0, const float* v1, uint32_t* arg) {
+    float best[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) { best[p] = __builtin_inff(); arg[p] = 0u; }
+#pragma unroll 2
+    for (int e = 0; e < E; e += 4) {
+        const float4_t a = *(const float4_t*)&entry[e], b = *(const float4_t*)&entry[e + 2];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const float least = min3f(min3f(pair_distance(v0[p], v1[p], a.x, a.y), pair_distance(v0[p], v1[p], a.z, a.w),
+                                            pair_distance(v0[p], v1[p], b.x, b.y)),
+                                      pair_distance(v0[p], v1[p], b.z, b.w), best[p]);
+            if (least < best[p]) arg[p] = (uint32_t)e;             // strict: the first four that hold it
+            best[p] = least;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint32_t e = arg[p];
+        arg[p] = 0u;
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            const float2 c = entry[e + q];
+            if (pair_distance(v0[p], v1[p], c.x, c.y) == best[p] && best[p] < __builtin_inff()) arg[p] = e + q;
+        }
+    }
+}
+
 // Nearest entries without comparing every pair with every entry.  A workgroup of 1024 threads takes a 256 x 256 block:
 //   1. the plane is cut into 32 x 32 cells over mean +- 3.25 standard deviations of the codebook's entries (those outside are
 //      left out and the box is taken again, twice);
@@ -234,31 +265,62 @@ __device__ __forceinline__ float pair_distance(float v0, float v1, float c0, flo
 //      entry that wins by the definition's rounded distances is always listed, and so is every entry that ties with it;
 //   3. a pair is compared with its cell's entries in index order (strict comparison: the lowest index wins a tie); unused
 //      places of a list repeat its first entry, which never wins again;
-//   4. pairs outside the cells, or in a cell with more than 16 entries, are queued and each compared with every entry by
-//      sixteen lanes (a full queue, a quarter of the block: by the thread itself).
+//   4. pairs outside the cells, or in a cell with more than 16 entries, are queued and compared with every entry: a few by
+//      sixteen lanes each, more by a thread each.  Units of eight pairs that find the queue (a quarter of the block) full are
+//      marked and done over with every entry;
+//   5. blocks for which the cells do not pay (weights far wider than the codebook, equal or crowded entries) compare every pair
+//      with every entry: when a fifth (6 bits) or a third (8 bits) of 128 sampled pairs is outside the cells, before the lists
+//      are made, or when a quarter of the first unit of every thread was queued, from there on (from the start, if half was).
+//      Four entries at a time, the smallest of them against the best, which one it was found out at the end: 6 instructions
+//      per pair and entry instead of 8.
 // Bound: vector ALU of step 2 (20 instructions per cell and entry) and the LDS look-ups of the 2 to 8 listed entries per
 // pair (a wavefront runs to its longest list).
-// Measured (bf16, near-normal weights, every pair against every entry -> here): 4096 x 4096, 64 entries 84 -> 60 us, 256
-// entries 316 -> 119; 14336 x 4096, 256 entries 879 -> 256; 1024 x 1024, 64 entries 36 -> 22.  With the queued pairs taken by
-// single threads where they are met: 92, 503 and 903 (a wavefront waits for its one lane that goes through all entries).
+// Measured (bf16, near-normal weights, every pair against every entry -> here): 4096 x 4096, 64 entries 77 -> 50 us, 256
+// entries 279 -> 92; 14336 x 4096, 256 entries 887 -> 234; 1024 x 1024, 64 entries 36 -> 23.  Without step 5 and the second
+// form of step 4, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 186 and 502 us (now 68 and
+// 219), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the entries
+// zero 162 and 170 (70 and 122).  Registers: 64, for two workgroups on a compute unit (74: 14336 x 4096,
+// 64 entries 126 -> 172).
 template <int KBITS>
-__global__ void __launch_bounds__(1024) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
+__global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
                                                          const uint16_t* __restrict__ codebooks,
                                                          uint32_t* __restrict__ indices, int parts_log2) {
     constexpr int E = 1 << KBITS, G = 32, kSlots = 16, kQueue = 8192;
-    __shared__ float2 entry[E];
+    __shared__ __attribute__((aligned(16))) float2 entry[E];
     __shared__ __attribute__((aligned(16))) uint8_t list[G * G][kSlots];
     __shared__ uint8_t listed[G * G];
     __shared__ __attribute__((aligned(16))) uint8_t found[32768];
     __shared__ uint16_t queue[kQueue];
-    __shared__ int queued;
+    __shared__ uint32_t over[128];                                 // units to be done over: a bit each
+    __shared__ int queued[2], outside;                             // by the first units, by the others
     __shared__ float box[5];                                       // origin, cells per unit, h
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int block = blockIdx.x >> parts_log2, part = blockIdx.x & ((1 << parts_log2) - 1);
     const int bj = block % (K / kBlock), bi = block / (K / kBlock);
     const uint16_t* cb = codebooks + (size_t)block * E * 2;
+    // the pairs of a workgroup's rows in units of eight: thread after thread, row after row; unit u is pairs 8 u .. 8 u + 7
+    const int units = 4096 >> parts_log2;
+    const size_t first_row = (size_t)bi * kBlock + (size_t)part * (kBlock >> parts_log2);
+    const size_t base = first_row * K + (size_t)bj * kBlock;
+    auto load_unit = [&](int u, float (&v0)[8], float (&v1)[8]) { load_pairs8(w, wdt, base + (size_t)(u >> 4) * K + 16 * (u & 15), v0, v1); };
+    auto load_pair = [&](int id, float& vx, float& vy) {
+        const size_t e = base + (size_t)(id >> 7) * K + 2 * (id & 127);
+        if (wdt == DT_F32) {
+            const float2 v = *(const float2*)((const float*)w + e);
+            vx = v.x; vy = v.y;
+        } else {
+            const uint32_t v = *(const uint32_t*)((const uint16_t*)w + e);
+            const uint16_t lo = (uint16_t)(v & 0xFFFFu), hi = (uint16_t)(v >> 16);
+            vx = wdt == DT_F16 ? f16_bits_to_f32(lo) : bf16_bits_to_f32(lo);
+            vy = wdt == DT_F16 ? f16_bits_to_f32(hi) : bf16_bits_to_f32(hi);
+        }
+    };
+    float px = 0.f, py = 0.f;
+    const bool sampled = tid < 128;                                // 128 pairs spread over the rows
+    if (sampled) load_pair((tid * (units >> 4) & ~127) + (tid * 37 & 127), px, py);
     if (tid < E) entry[tid] = float2{f16_bits_to_f32(cb[2 * tid]), f16_bits_to_f32(cb[2 * tid + 1])};
-    if (tid == 0) queued = 0;
+    if (tid < 128) over[tid] = 0u;
+    if (tid == 0) { queued[0] = 0; queued[1] = 0; outside = 0; }
     __syncthreads();
     if (wave == 0) {                                               // mean and deviation, twice more without the entries outside
         float m0 = entry[0].x, m1 = entry[0].y, r0 = __builtin_inff(), r1 = __builtin_inff();
@@ -288,128 +350,163 @@ __global__ void __launch_bounds__(1024) vq_assign_kernel(const void* __restrict_
         }
     }
     __syncthreads();
-    const float x0 = box[0], y0 = box[1], sx = box[2], sy = box[3];
-    {   // the lists, one cell per thread
-        const float cx = x0 + ((float)(tid % G) + 0.5f) / sx, cy = y0 + ((float)(tid / G) + 0.5f) / sy;
-        const float hx = 1.1f / sx, hy = 1.1f / sy;              // twice 0.55 of a cell's sides
-        float least = __builtin_inff();
-        float2 r = entry[0];
-#pragma unroll 8
-        for (int e = 0; e < E; ++e) {
-            const float2 c = entry[e];
-            const float d = pair_distance(cx, cy, c.x, c.y);
-            if (d < least) { least = d; r = c; }
-        }
-        const float reach = (sqrtf(least) + 2.f * box[4]) * 1.0001f, limit = reach * reach;
-        const float at_most = least + 1e-5f * limit;
-        int n = 0, first = 0;
-#pragma unroll 4
-        for (int e = 0; e < E; ++e) {
-            const float2 c = entry[e];
-            const float d = pair_distance(cx, cy, c.x, c.y);
-            if (d <= limit && d <= at_most + fabsf(r.x - c.x) * hx + fabsf(r.y - c.y) * hy) {
-                if (n == 0) first = e;
-                if (n < kSlots) list[tid][n] = (uint8_t)e;
-                ++n;
-            }
-        }
-        listed[tid] = (uint8_t)(n <= kSlots && n > 0 ? n : 255);
-        for (; n < kSlots; ++n) list[tid][n] = (uint8_t)first;
+    auto uniform = [](float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); };   // a scalar register
+    const float x0 = uniform(box[0]), y0 = uniform(box[1]), sx = uniform(box[2]), sy = uniform(box[3]);
+    auto cell_of = [&](float vx, float vy) {                       // -1: outside
+        const float fx = (vx - x0) * sx, fy = (vy - y0) * sy;
+        const bool in = fx >= 0.f && fx < (float)G && fy >= 0.f && fy < (float)G;
+        return in ? (int)fy * G + (int)fx : -1;
+    };
+    auto store_found = [&](int u, const uint32_t (&arg)[8]) {
+        *(uint2_t*)(found + 8 * u) = uint2_t{arg[0] | (arg[1] << 8) | (arg[2] << 16) | (arg[3] << 24),
+                                           arg[4] | (arg[5] << 8) | (arg[6] << 16) | (arg[7] << 24)};
+    };
+    {
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(sampled && cell_of(px, py) < 0));
+        if (lane == 0 && n) atomicAdd(&outside, n);
     }
     __syncthreads();
-
-    // the pairs of a workgroup's rows in units of eight: thread after thread, row after row; unit u is pairs 8 u .. 8 u + 7
-    const int units = 4096 >> parts_log2;
-    const size_t first_row = (size_t)bi * kBlock + (size_t)part * (kBlock >> parts_log2);
-    const size_t base = first_row * K + (size_t)bj * kBlock;
-#pragma unroll 1
-    for (int u = tid; u < units; u += 1024) {
-        float v0[8], v1[8];
-        load_pairs8(w, wdt, base + (size_t)(u >> 4) * K + 16 * (u & 15), v0, v1);
-        uint32_t arg[8];
-#pragma unroll
-        for (int h = 0; h < 8; h += 4) {
-            uint4_t l[4];
-            float best[4];
-            int longest = 0;
-            bool again[4];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const float fx = (v0[h + p] - x0) * sx, fy = (v1[h + p] - y0) * sy;
-                const bool in = fx >= 0.f && fx < (float)G && fy >= 0.f && fy < (float)G;
-                const int cell = in ? (int)fy * G + (int)fx : 0;
-                const int cnt = listed[cell];
-                again[p] = !in || cnt == 255;
-                longest = max(longest, again[p] ? 0 : cnt);
-                l[p] = *(const uint4_t*)list[cell];
-                best[p] = __builtin_inff();
-                arg[h + p] = 0u;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {                          // four places at a time, up to the longest list of the wavefront
-                if (__builtin_amdgcn_ballot_w64(longest > 4 * q) == 0) break;
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) {
-                        const uint32_t word = q == 0 ? l[p].x : q == 1 ? l[p].y : q == 2 ? l[p].z : l[p].w;
-                        const uint32_t e = (word >> (8 * b)) & 255u;
-                        const float2 ce = entry[e];
-                        const float d = pair_distance(v0[h + p], v1[h + p], ce.x, ce.y);
-                        if (d < best[p]) { best[p] = d; arg[h + p] = e; }
-                    }
-            }
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                if (again[p]) {
-                    const int at = atomicAdd(&queued, 1);
-                    if (at < kQueue) {
-                        queue[at] = (uint16_t)(8 * u + h + p);
-                    } else {
-                        float bd = __builtin_inff();
+    int from = outside > (KBITS == 6 ? 24 : 40) ? 0 : 4096;         // units from here on: every pair with every entry
+    int ahead = 0;                                                 // queued by the first units
+    if (from) {
+        {   // the lists, one cell per thread
+            const float cx = x0 + ((float)(tid % G) + 0.5f) / sx, cy = y0 + ((float)(tid / G) + 0.5f) / sy;
+            const float hx = 1.1f / sx, hy = 1.1f / sy;              // twice 0.55 of a cell's sides
+            float least = __builtin_inff();
+            float2 r = entry[0];
 #pragma unroll 8
-                        for (int e = 0; e < E; ++e) {
+            for (int e = 0; e < E; ++e) {
+                const float2 c = entry[e];
+                const float d = pair_distance(cx, cy, c.x, c.y);
+                if (d < least) { least = d; r = c; }
+            }
+            const float reach = (sqrtf(least) + 2.f * box[4]) * 1.0001f, limit = reach * reach;
+            const float at_most = least + 1e-5f * limit;
+            int n = 0, first = 0;
+#pragma unroll 4
+            for (int e = 0; e < E; ++e) {
+                const float2 c = entry[e];
+                const float d = pair_distance(cx, cy, c.x, c.y);
+                if (d <= limit && d <= at_most + fabsf(r.x - c.x) * hx + fabsf(r.y - c.y) * hy) {
+                    if (n == 0) first = e;
+                    if (n < kSlots) list[tid][n] = (uint8_t)e;
+                    ++n;
+                }
+            }
+            listed[tid] = (uint8_t)(n <= kSlots && n > 0 ? n : 255);
+            for (; n < kSlots; ++n) list[tid][n] = (uint8_t)first;
+        }
+        __syncthreads();
+
+#pragma unroll 1
+        for (int u = tid; u < units; u += 1024) {
+            if (u >= 1024 && u < 2048) {                           // the first units are through
+                __syncthreads();
+                ahead = queued[0];
+                if (ahead > 2048) { from = ahead > 4096 ? 0 : 1024; break; }   // (of 8192)
+            }
+            float v0[8], v1[8];
+            uint32_t arg[8];
+            load_unit(u, v0, v1);
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                uint4_t l[4];
+                float best[4];
+                int longest = 0;
+                bool again[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const int at = cell_of(v0[h + p], v1[h + p]), cell = max(at, 0);
+                    const int cnt = listed[cell];
+                    again[p] = at < 0 || cnt == 255;
+                    longest = max(longest, again[p] ? 0 : cnt);
+                    l[p] = *(const uint4_t*)list[cell];
+                    best[p] = __builtin_inff();
+                    arg[h + p] = 0u;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {                      // four places at a time, up to the longest list of the wavefront
+                    if (__builtin_amdgcn_ballot_w64(longest > 4 * q) == 0) break;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) {
+                            const uint32_t word = q == 0 ? l[p].x : q == 1 ? l[p].y : q == 2 ? l[p].z : l[p].w;
+                            const uint32_t e = (word >> (8 * b)) & 255u;
                             const float2 ce = entry[e];
                             const float d = pair_distance(v0[h + p], v1[h + p], ce.x, ce.y);
-                            if (d < bd) { bd = d; arg[h + p] = (uint32_t)e; }
+                            if (d < best[p]) { best[p] = d; arg[h + p] = e; }
                         }
+                }
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    if (again[p]) {
+                        const int at = ahead + atomicAdd(&queued[u >= 1024], 1);
+                        if (at < kQueue) queue[at] = (uint16_t)(8 * u + h + p);
+                        else atomicOr(&over[u >> 5], 1u << (u & 31));
                     }
                 }
             }
+            store_found(u, arg);
         }
-        *(uint2_t*)(found + 8 * u) = uint2_t{arg[0] | (arg[1] << 8) | (arg[2] << 16) | (arg[3] << 24),
-                                           arg[4] | (arg[5] << 8) | (arg[6] << 16) | (arg[7] << 24)};
+        __syncthreads();
     }
-    __syncthreads();
-    const int todo = min(queued, kQueue);
-    for (int i = tid >> 4; i < todo; i += 64) {                    // sixteen lanes per queued pair
-        const int id = queue[i];
-        const size_t e = base + (size_t)(id >> 7) * K + 2 * (id & 127);
-        float vx, vy;
-        if (wdt == DT_F32) {
-            const float2 v = *(const float2*)((const float*)w + e);
-            vx = v.x; vy = v.y;
+    const int all = from ? queued[0] + queued[1] : 0, todo = min(all, kQueue);
+    if (from < units) {
+#pragma unroll 1
+        for (int u = from + tid; u < units; u += 1024) {
+            float v0[8], v1[8];
+            uint32_t arg[8];
+            load_unit(u, v0, v1);
+            nearest_of_all<8>(entry, v0, v1, arg);
+            store_found(u, arg);
+        }
+    }
+    if (todo) {
+        if (todo > 192) {                                          // a thread per queued pair (a pass costs as much as 192 of the others)
+#pragma unroll 1
+            for (int i = tid; i < todo; i += 1024) {
+                const int id = queue[i];
+                float vx, vy;
+                uint32_t arg;
+                load_pair(id, vx, vy);
+                nearest_of_all<1>(entry, &vx, &vy, &arg);
+                found[id] = (uint8_t)arg;
+            }
         } else {
-            const uint32_t v = *(const uint32_t*)((const uint16_t*)w + e);
-            const uint16_t lo = (uint16_t)(v & 0xFFFFu), hi = (uint16_t)(v >> 16);
-            vx = wdt == DT_F16 ? f16_bits_to_f32(lo) : bf16_bits_to_f32(lo);
-            vy = wdt == DT_F16 ? f16_bits_to_f32(hi) : bf16_bits_to_f32(hi);
-        }
-        float bd = __builtin_inff();
-        uint32_t be = 0xFFFFFFFFu;
+            for (int i = tid >> 4; i < todo; i += 64) {            // sixteen lanes per queued pair
+                const int id = queue[i];
+                float vx, vy;
+                load_pair(id, vx, vy);
+                float bd = __builtin_inff();
+                uint32_t be = 0xFFFFFFFFu;
 #pragma unroll
-        for (int k = 0; k < E / 16; ++k) {
-            const float2 ce = entry[(tid & 15) + 16 * k];
-            const float d = pair_distance(vx, vy, ce.x, ce.y);
-            if (d < bd) { bd = d; be = (uint32_t)((tid & 15) + 16 * k); }
-        }
+                for (int k = 0; k < E / 16; ++k) {
+                    const float2 ce = entry[(tid & 15) + 16 * k];
+                    const float d = pair_distance(vx, vy, ce.x, ce.y);
+                    if (d < bd) { bd = d; be = (uint32_t)((tid & 15) + 16 * k); }
+                }
 #pragma unroll
-        for (int off = 8; off; off >>= 1) {
-            const float od = __shfl_xor(bd, off, 64);
-            const uint32_t oe = (uint32_t)__shfl_xor((int)be, off, 64);
-            if (od < bd || (od == bd && oe < be)) { bd = od; be = oe; }
+                for (int off = 8; off; off >>= 1) {
+                    const float od = __shfl_xor(bd, off, 64);
+                    const uint32_t oe = (uint32_t)__shfl_xor((int)be, off, 64);
+                    if (od < bd || (od == bd && oe < be)) { bd = od; be = oe; }
+                }
+                if ((tid & 15) == 0) found[id] = (uint8_t)(be == 0xFFFFFFFFu ? 0u : be);   // (every distance infinite or NaN: entry 0)
+            }
         }
-        if ((tid & 15) == 0) found[id] = (uint8_t)(be == 0xFFFFFFFFu ? 0u : be);   // (every distance infinite or NaN: entry 0)
+        if (all > kQueue) {                                     // (the queued pairs of such a unit come out the same again)
+            __syncthreads();
+#pragma unroll 1
+            for (int u = tid; u < units; u += 1024)
+                if ((over[u >> 5] >> (u & 31)) & 1u) {
+                    float v0[8], v1[8];
+                    uint32_t arg[8];
+                    load_unit(u, v0, v1);
+                    nearest_of_all<8>(entry, v0, v1, arg);
+                    store_found(u, arg);
+                }
+        }
     }
     __syncthreads();
     constexpr int wpr = KBITS == 6 ? 3 : 4;                        // output words per 16 pairs

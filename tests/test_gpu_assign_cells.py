@@ -53,3 +53,46 @@ def test_vq_assign_cells():
         for rows in (9, 17):                    # enough blocks that each is taken in two parts, and whole
             dm = B.vq_assign(dev(np.tile(wide, (rows, 1)), "f32"), B.F32, dev(np.tile(bits, (rows, 1, 1, 1)), "f16"), kbits)
             assert np.array_equal(dm.codes.cpu().numpy().view(np.uint32), np.tile(want, (rows, 1))), (kbits, rows)
+
+
+@pytest.mark.parametrize("kbits", [6, 8])
+@pytest.mark.parametrize("wdt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows", [1, 9, 17])                # blocks taken in quarters, halves and whole
+def test_vq_assign_many_pairs_beside_the_cells(kbits, wdt, rows):
+    """Every way that pairs without a list take: a few (sixteen lanes each), some hundreds (a thread each), more than the queue holds
+    behind a first unit without any (whole units done over), a quarter and more of the first unit (every unit with every entry, for
+    pairs outside the cells and for cells of crowded entries); with every distance infinite, entry 0."""
+    from paper_2505_03803_amd import binding as B
+    from paper_2505_03803_amd import synth
+    rng = np.random.default_rng(7 + kbits)
+    En = 1 << kbits
+    shares = [0.003, 0.02, 0.24, 0.26, "last rows", "first rows", "crowded", "equal", "infinite"]
+    cb = (rng.normal(0, 0.02, (len(shares), En, 2))).astype(np.float16)
+    wide = rng.normal(0, 0.015, (256, 256 * len(shares))).astype(np.float32)
+    for i, share in enumerate(shares):
+        b = wide[:, 256 * i: 256 * (i + 1)]
+        if isinstance(share, float):
+            b[np.repeat(rng.random((256, 128)) < share, 2, axis=1)] *= 1e3
+        elif share == "last rows":                          # (the first thread of each part sees rows 0 .. 63 of 256, 128 or 64)
+            b[np.arange(256) % 64 > 20] *= 1e3
+            b[:64] = rng.normal(0, 0.015, (64, 256))
+        elif share == "first rows":
+            b[:40] *= 1e3
+        elif share == "crowded":                            # nine places, many entries on each
+            cb[i] = rng.integers(-1, 2, (En, 2)) * 0.02
+            b[:] = rng.integers(-1, 2, (256, 256)) * 0.02 + rng.normal(0, 1e-3, (256, 256))
+        elif share == "equal":
+            cb[i] = 0.01
+        else:
+            b[::3] = 3e38
+    if wdt == "bf16":
+        bits = synth.f32_to_bf16_bits(wide)
+        wide = (bits.astype(np.uint32) << 16).view(np.float32)
+    books = cb.view(np.uint16)[None]
+    want = np.tile(E.vq_assign_packed(wide, books, kbits), (rows, 1))
+    src = np.tile(wide if wdt == "f32" else bits, (rows, 1))
+    dm = B.vq_assign(dev(src, wdt), B.DTYPES[wdt], dev(np.tile(books, (rows, 1, 1, 1)), "f16"), kbits)
+    got = dm.codes.cpu().numpy().view(np.uint32)
+    words = want.shape[1] // len(shares)
+    for i, share in enumerate(shares):
+        assert np.array_equal(got[:, words * i: words * (i + 1)], want[:, words * i: words * (i + 1)]), share
