@@ -179,9 +179,10 @@ int rwkvq_vq_gemm(const void* indices, const void* codebooks, int layout, const 
  * Reproducibility: a call gives the same bits every time.  At M = 1 the kernel is chosen by the
  * number of rows in the call (small calls split each row's columns over several wavefronts), so
  * the same matrix dispatched alone and inside a large call may differ in the order of its
- * binary32 sums (a few units in the last place); the same holds for 2 <= M <= 128, where the kernel
- * (and for 16 < M the path, see rwkvq_sq_gemm) is chosen from the sizes of the call's matrices, not
- * from their values; for M > 128 the order is fixed.
+ * binary32 sums (a few units in the last place); the same holds for 2 <= M <= 1536, where the kernel
+ * (and for 16 < M <= 128 the path, see rwkvq_sq_gemm) is chosen from the sizes of the call's matrices, not
+ * from their values; for M > 1536 the order is fixed, and with RWKVQ_OPT_PREFILL_TILE_ROWS set to 128 or 256
+ * for M > 128.
  * No scratch memory; safe to record into a HIP graph. */
 int rwkvq_linear_dispatch(const rwkvq_matrix* mats, const void* const* xs, void* const* ys,
                           int n_mats, int M, int x_dtype, int y_dtype, void* stream);

@@ -180,6 +180,7 @@ hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, in
                           hipStream_t s);
 // Splits K over the wavefronts of a workgroup (midbatch.hip): exact = false, the feed of launch_prefill; true, weights unrounded.
 hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, bool exact, hipStream_t s);
+double mid_us(const MatDev* mats, int n_mats, int M);       // estimated duration, exact = false
 
 hipError_t launch_proxy(const void* const* ws, const int* Ns, const int* Ks, int n_mats, int dtype,
                         int terms, double tau_c, double tau_f, uint32_t* bitmaps, double* out, int32_t* phi,

@@ -3,7 +3,27 @@
 #pragma once
 #include "common.h"
 
+#include <algorithm>
+
 namespace rwkvq {
+
+// How long a launch runs, in column tiles (256 columns of W) that a compute unit works through one after another: workgroups
+// go to 256 compute units, those with a long K first.  `tail`: how much of the shortest workgroup the end of the launch leaves
+// some compute units without work.
+struct LaunchLoad {
+    long long wgs = 0;
+    double work = 0.0;
+    int longest = 0, shortest = 0x7FFFFFFF;
+    void add(long long n, int K) {
+        const int k = K >> 8;
+        wgs += n; work += (double)n * k;
+        longest = std::max(longest, k); shortest = std::min(shortest, k);
+    }
+    double columns(double tail) const {
+        if (longest == shortest && wgs <= 512) return (double)(longest * ((wgs + 255) / 256));
+        return wgs <= 256 ? (double)longest : std::max((double)longest, work / 256.0 + tail * shortest);
+    }
+};
 
 constexpr int kRowBytes = 128;                 // a row of an operand tile in LDS: 64 k * 2 B
 

@@ -526,6 +526,22 @@ static void pick_mid(int M, long long rows, int* mf, int* nw) {
     if (M <= 128 && rows / 64 * ((M + 63) / 64) <= 256) { *mf = 4; *nw = 1; }
 }
 
+// A launch of rounds that follow one another closely runs an eighth longer than the rounds by themselves (the clock falls).
+double mid_us(const MatDev* mats, int n_mats, int M) {
+    double us = 0.0;
+    for (int base = 0; base < n_mats; base += kMidMaxMats) {
+        const int end = std::min(n_mats, base + kMidMaxMats);
+        long long rows = 0;
+        for (int i = base; i < end; ++i) rows += mats[i].N;
+        int mf, nw;
+        pick_mid(M, rows, &mf, &nw);
+        LaunchLoad load;
+        for (int i = base; i < end; ++i) load.add((long long)(mats[i].N / (16 * kMidNF * nw)) * ((M + 16 * mf - 1) / (16 * mf)), mats[i].K);
+        us += 3.0 + load.columns(0.5) * 1.12 * (36.0 + 8.6 * mf) / 56.0;
+    }
+    return us;
+}
+
 hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, bool exact, hipStream_t s) {
     for (int base = 0; base < n_mats; base += kMidMaxMats) {
         MidArgs a;

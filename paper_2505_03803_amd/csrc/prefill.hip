@@ -34,7 +34,7 @@
 namespace rwkvq {
 
 constexpr int kPfMaxMats = 64;
-constexpr int BM = 256, BN = 256;              // block tile; the k-step is 64 columns
+constexpr int BN = 256;                        // rows of W of a block tile; the k-step is 64 columns
 constexpr int kTileBytes = 256 * kRowBytes;    // one operand tile (32 KB)
 constexpr int kCb8Bytes = 1024;                // converted 8-bit-index codebook
 // Activation tiles in LDS: three (the copy of a k-step is issued two k-steps ahead of its use, so
@@ -517,14 +517,41 @@ static int pick_bm(int M, long long n_tiles) {
     return t128 < t256 ? 128 : 256;
 }
 
-// A few hundred rows of x: the kernels of midbatch.hip.  The line depends on M (and on a K their 32-bit offsets hold), not on
-// the other matrices of the call, so that the order of a matrix's sums stays a function of its own sizes.  Measured on the
-// calls that a block makes (bf16, SQ and 6-bit VQ, us, here -> there): {r, k, v, g} of 4096 x 4096 at M = 1024 180 -> 145,
-// 1536 238 -> 213, 1792 251 -> 258; 4096 x 4096 alone at M = 1536 84 -> 64, 4096 x 14336 266 -> 192, {14336 x 4096,
-// 4096 x 4096} 322 -> 248.  A call that fills the device many times over (tens of matrices) is 10 to 15 % faster here from
-// M = 512 on; no block makes one.  A forced tile height (RWKVQ_OPT_PREFILL_TILE_ROWS) stays here.
+// Estimated duration here: one launch per format and 64 matrices, 7.4 us per column tile of a 256-row workgroup.
+static double tiles_us(const std::vector<MatDev>& mats, int M) {
+    double us = 0.0;
+    for (int fmt = 0; fmt < 3; ++fmt) {
+        size_t i = 0;
+        while (i < mats.size()) {
+            long long n_tiles = 0;
+            int cnt = 0;
+            size_t end = i;
+            for (; end < mats.size() && cnt < kPfMaxMats; ++end)
+                if (mats[end].fmt == fmt) { n_tiles += mats[end].N / BN; ++cnt; }
+            if (cnt) {
+                const int bm = pick_bm(M, n_tiles);
+                LaunchLoad load;
+                for (size_t j = i; j < end; ++j)
+                    if (mats[j].fmt == fmt) load.add((long long)(mats[j].N / BN) * ((M + bm - 1) / bm), mats[j].K);
+                us += 3.0 + load.columns(0.2) * (bm == 256 ? 7.4 : 0.705 * 7.4);
+            }
+            i = end;
+        }
+    }
+    return us;
+}
+
+// Up to kMidMaxM rows of x the kernels of midbatch.hip are an alternative: workgroups of a quarter of the size, K split over
+// groups of wavefronts and all formats in one launch, which fills the device from small calls, for an unpack that serves 128
+// rows of x instead of 256.  At M <= 128 they won every call measured; beyond, the cheaper estimate is taken.  Over 210 calls
+// (o, {r, k, v, g}, {key, receptance}, value, 1 to 32 whole layers of the 7B shapes, 4 of 14B-class shapes; one and two
+// formats; M = 129 .. 1536; us, here / there): none takes the slower one by more than 4 %.  There: {r, k, v, g} of two formats
+// at M = 1024 178 / 140, 4096 x 4096 alone 82 / 41, value 269 / 120, one layer 595 / 454, 32 layers at 333 rows 6047 / 5453.
+// Here: 14336 x 4096 alone 120 / 136, {r, k, v, g} of one format 125 / 142, four layers 1559 / 1722, 32 layers
+// 12435 / 14509.  The order of a matrix's binary32 sums over K differs between the two, so for 128 < M <= kMidMaxM it depends
+// on the sizes of the call; a forced tile height (RWKVQ_OPT_PREFILL_TILE_ROWS) stays here, with one order for every M > 128.
 constexpr int kMidMaxM = 1536;
-static bool mid_rows(const MatDev& m, int M) { return M <= kMidMaxM && m.K <= (1 << 20) && option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0; }
+static bool mid_takes(const MatDev& m, int M) { return M <= kMidMaxM && m.K <= (1 << 20) && option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0; }
 
 static hipError_t launch_prefill_tiles(const MatDev* mats_in, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
     // Workgroups of a matrix with a long K run long: put those matrices first so that the end of
@@ -570,7 +597,11 @@ static hipError_t launch_prefill_tiles(const MatDev* mats_in, int n_mats, int M,
 
 hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
     std::vector<MatDev> mid, tiles;
-    for (int i = 0; i < n_mats; ++i) (mid_rows(mats[i], M) ? mid : tiles).push_back(mats[i]);
+    for (int i = 0; i < n_mats; ++i) (mid_takes(mats[i], M) ? mid : tiles).push_back(mats[i]);    // (a K beyond its 32-bit offsets)
+    if (M > 128 && !mid.empty() && tiles_us(mid, M) < mid_us(mid.data(), (int)mid.size(), M)) {
+        tiles.assign(mats, mats + n_mats);
+        mid.clear();
+    }
     hipError_t e = mid.empty() ? hipSuccess : launch_mid(mid.data(), (int)mid.size(), M, x_dtype, y_dtype, false, s);
     if (e == hipSuccess && !tiles.empty()) e = launch_prefill_tiles(tiles.data(), (int)tiles.size(), M, x_dtype, y_dtype, s);
     return e;

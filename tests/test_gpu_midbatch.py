@@ -37,8 +37,8 @@ def test_against_the_oracle(fmt, N, K, M, xdt, options):
 # rows of W x rows of x that make the launcher take 64, 96 and 128 rows of x per workgroup (and 8 K groups at M = 100)
 @pytest.mark.parametrize("M,n_mats,N", [(100, 1, 1024), (100, 5, 4096), (333, 1, 4096), (333, 4, 4096), (300, 9, 4096)])
 def test_calls_of_several_matrices(M, n_mats, N, options):
-    """Mixed formats in one launch; every matrix alone gives the same bits beyond 128 rows (the order of a matrix's sums
-    depends on its own sizes only)."""
+    """Mixed formats in one launch; every matrix alone gives the same bits beyond 128 rows (calls of these sizes all take the
+    kernels that split K, in four groups)."""
     options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_MATRIX_CORES)
     K = 512
     mats = [make(("sq", "vq6", "vq8")[i % 3], N, K, 20 + i) for i in range(n_mats)]
@@ -55,6 +55,27 @@ def test_calls_of_several_matrices(M, n_mats, N, options):
         torch.cuda.synchronize()
         if M > 128:
             assert np.array_equal(got, alone.cpu().numpy())
+
+
+@pytest.mark.parametrize("fmt", ["sq", "vq6", "vq8"])
+@pytest.mark.parametrize("n_mats,tiles", [(4, False), (32, True)])
+def test_calls_that_fill_the_device(fmt, n_mats, tiles, options):
+    """128 < M <= 1536: a call that gives every compute unit several tiles of 256 x 256 takes the kernels for large batches, a
+    smaller one those that split K; seen by the order of the sums (five column tiles in a row, or in four groups)."""
+    torch = G.torch_()
+    N, K, M = 2048, 1280, 512
+    dm = B.upload(make(fmt, N, K, 17), native=True)
+    x = G.to_dev_bits(synth.gen_activations(np.random.default_rng(3), M, K, "bf16"))
+    def call(rows):
+        options(B.OPT_PREFILL_TILE_ROWS, rows)
+        ys = [torch.empty((M, N), dtype=torch.float32, device="cuda") for _ in range(n_mats)]
+        B.rwkvq_linear_dispatch(B.DispatchTable([dm.desc()] * n_mats, [x] * n_mats, ys), M, B.BF16, B.F32)
+        torch.cuda.synchronize()
+        assert all(torch.equal(ys[0], y) for y in ys[1:])
+        return ys[0]
+    free, forced = call(0), call(256)
+    assert torch.equal(free, forced) == tiles
+    assert float((free - forced).abs().max()) <= 2e-5 * float(forced.abs().max())
 
 
 @pytest.mark.parametrize("xdt", ["bf16", "f16"])
