@@ -112,10 +112,11 @@ const char* rwkvq_status_string(int status);
  *   RWKVQ_OPT_STREAM_SPLIT_MAX_WORK    batch 2..16 on the streaming kernels: a launch takes the small-launch form (one
  *                                 workgroup per 32 rows of W, its wavefronts split the columns, every workgroup
  *                                 reads all of x) when (rows of all its matrices / 32) x (16 + M) is at most this
- *                                 (65536: one RWKV-6-7B layer at any M <= 16, two layers up to M = 8; 1 = never).
- *                                 At the default, the streaming path at M = 17..32 (up to two such layers per call) and
- *                                 33..128 runs on kernels that split K on the matrix cores, weights exact as well;
- *                                 any other value keeps it on passes over 32 rows of x
+ *                                 (65536: one RWKV-6-7B layer at any M <= 16, two layers up to M = 8; 1 = never,
+ *                                 1000000 = always).  The streaming path at 17..128 has such a form too (kernels that split
+ *                                 K on the matrix cores, weights exact as well): at 17..32 for launches of up to 1792
+ *                                 workgroups of 64 rows of W (two such layers), a number that moves in proportion to the
+ *                                 option; 1 keeps the path on passes over 32 rows of x
  *   RWKVQ_OPT_SPLIT_GRID_2D       batch 1, launches of at most eight matrices with few rows (the stages of a block): 1 = a
  *                                 workgroup takes its matrix and row tile from a two-dimensional grid, 2 = from the
  *                                 table of first-workgroup indices that larger launches use (1; same output bits)

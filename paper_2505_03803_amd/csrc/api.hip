@@ -110,14 +110,16 @@ bool stream_passes_cheaper(const std::vector<MatDev>& mats, int M) {
 //   M > 32: they need two to four passes: four layers 207 -> 183 at 48, 237 -> 204 at 64, 320 -> 321 at 80, 455 -> 368 at 128;
 //   M <= 16: a layer whose weights are in the cache 41 -> 30, but 67 -> 70 from memory (a step is then so short that the
 //   words of one column tile ahead do not cover the trip), so they stay.
-// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK away from its default forces one of the streaming kernels' forms.
+// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK: 1 (never the form for small launches) keeps the streaming kernels, 1000000 (always) leaves
+// them out; in between it moves the line at M = 17..32 in proportion, as it does the one at M <= 16.
 constexpr int kSplitKMaxWgs = 1792;
 bool split_k_cheaper(const std::vector<MatDev>& mats, int M) {
-    if (option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK) != kStreamSplitMaxWork) return false;
-    if (M > kStreamPassRows) return true;
+    const long long max_work = option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK);
+    if (max_work == 1) return false;
+    if (max_work >= 1000000 || M > kStreamPassRows) return true;
     long long wgs = 0;
     for (const MatDev& d : mats) wgs += (d.N + 63) / 64;
-    return wgs <= kSplitKMaxWgs;
+    return wgs * kStreamSplitMaxWork <= kSplitKMaxWgs * max_work;
 }
 
 // Which kernels run each matrix of a call (values of RWKVQ_PATH_*): the one place that decides.

@@ -133,3 +133,31 @@ def test_unrounded_weights_at_the_ends_of_bf16(fmt, scale, options):
     got = G.gpu_gemm(B.upload(mat, native=True), bits, "bf16")
     assert np.all(np.isfinite(got))
     assert G.err_g2(got, orc.linear(mat, orc.widen(bits, "bf16"), "f64")) <= 2e-5
+
+
+@pytest.mark.parametrize("fmt", ["sq", "vq6", "vq8"])
+def test_line_between_the_forms_of_the_streaming_path(fmt, options):
+    """RWKVQ_OPT_STREAM_SPLIT_MAX_WORK at 17 <= M <= 128: 1 never takes the kernels that split K, 1000000 always does, a value in
+    between moves the line at M <= 32 and leaves M > 32 alone; seen by the order of the sums."""
+    torch = G.torch_()
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    N, K = 4096, 1280
+    dm = B.upload(make(fmt, N, K, 19), native=True)
+    def call(M, n_mats, value):
+        options(B.OPT_STREAM_SPLIT_MAX_WORK, value)
+        x = G.to_dev_bits(synth.gen_activations(np.random.default_rng(M), M, K, "bf16"))
+        ys = [torch.empty((M, N), dtype=torch.float32, device="cuda") for _ in range(n_mats)]
+        B.rwkvq_linear_dispatch(B.DispatchTable([dm.desc()] * n_mats, [x] * n_mats, ys), M, B.BF16, B.F32)
+        torch.cuda.synchronize()
+        assert all(torch.equal(ys[0], y) for y in ys[1:])
+        return ys[0]
+    for M in (20, 48):
+        stream, split = call(M, 2, 1), call(M, 2, 1000000)
+        assert not torch.equal(stream, split)
+        assert float((stream - split).abs().max()) <= 2e-5 * float(split.abs().max())
+        # 64 rows of W in a workgroup: 128 workgroups, 1856 (29 matrices) over the line at M <= 32
+        for value, few, many in ((0, split, stream if M <= 32 else split), (32768, split, stream if M <= 32 else split),
+                                 (4096, stream if M <= 32 else split, None), (80000, split, split)):
+            assert torch.equal(call(M, 2, value), few), (M, value)
+            if many is not None:
+                assert torch.equal(call(M, 29, value), many), (M, value)
