@@ -116,7 +116,8 @@ const char* rwkvq_status_string(int status);
  *                                 1000000 = always).  The streaming path at 17..128 has such a form too (kernels that split
  *                                 K on the matrix cores, weights exact as well): at 17..32 for launches of up to 1792
  *                                 workgroups of 64 rows of W (two such layers), a number that moves in proportion to the
- *                                 option; 1 keeps the path on passes over 32 rows of x
+ *                                 option, beyond 32 up to 2000 to 20000 of them, by M; 1 keeps the path on passes over 32
+ *                                 rows of x
  *   RWKVQ_OPT_SPLIT_GRID_2D       batch 1, launches of at most eight matrices with few rows (the stages of a block): 1 = a
  *                                 workgroup takes its matrix and row tile from a two-dimensional grid, 2 = from the
  *                                 table of first-workgroup indices that larger launches use (1; same output bits)

@@ -104,10 +104,15 @@ bool stream_passes_cheaper(const std::vector<MatDev>& mats, int M) {
 
 // Matrices of a streaming path on the kernels that split K over a workgroup's wavefronts (midbatch.hip, weights exact, one
 // pass over W per 64 rows of x) instead of the streaming kernels (one per 32, rows staged per workgroup)?  Measured on the 7B
-// shapes, fp16 / bf16, us, streaming -> split:
-//   M = 17..32: one layer in a call (832 workgroups of 64 rows of W) 66 -> 37 at 32, two layers 79 -> 68, four layers 116 -> 163:
+// shapes, SQ and 6-bit VQ, bf16, us, streaming -> split:
+//   M = 17..32: one layer in a call (832 workgroups of 64 rows of W) 82 -> 40 at 32, two layers 87 -> 75, four layers 116 -> 163:
 //   large launches fill the device either way, and there the streaming kernels read W faster;
-//   M > 32: they need two to four passes: four layers 207 -> 183 at 48, 237 -> 204 at 64, 320 -> 321 at 80, 455 -> 368 at 128;
+//   M > 32: they need two to four passes, of which a last one of few rows is cheap: two layers 147 -> 86 at 48, 216 -> 159 at
+//   65, 347 -> 199 at 128; four layers 192 -> 186 at 33, 247 -> 223 at 64, 318 -> 345 at 65, 365 -> 345 at 81; eight layers
+//   410 -> 371 at 48, 652 -> 703 at 80, 950 -> 847 at 128; 32 layers 1365 -> 1446 at 33, 1732 -> 1783 at 64, 2342 -> 2779 at 80.
+//   The line compares both in hundredths of a 32-row streaming pass over a launch without end; fewer workgroups cost the
+//   streaming kernels 700 / workgroups more (84 calls of two to 32 layers, one and two formats, M = 33 .. 128: none takes a
+//   kernel more than 3 % slower than the streaming ones);
 //   M <= 16: a layer whose weights are in the cache 41 -> 30, but 67 -> 70 from memory (a step is then so short that the
 //   words of one column tile ahead do not cover the trip), so they stay.
 // RWKVQ_OPT_STREAM_SPLIT_MAX_WORK: 1 (never the form for small launches) keeps the streaming kernels, 1000000 (always) leaves
@@ -116,10 +121,14 @@ constexpr int kSplitKMaxWgs = 1792;
 bool split_k_cheaper(const std::vector<MatDev>& mats, int M) {
     const long long max_work = option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK);
     if (max_work == 1) return false;
-    if (max_work >= 1000000 || M > kStreamPassRows) return true;
+    if (max_work >= 1000000) return true;
     long long wgs = 0;
     for (const MatDev& d : mats) wgs += (d.N + 63) / 64;
-    return wgs * kStreamSplitMaxWork <= kSplitKMaxWgs * max_work;
+    if (M <= kStreamPassRows) return wgs * kStreamSplitMaxWork <= kSplitKMaxWgs * max_work;
+    const int rest = M % kStreamPassRows, tiles = (M + 63) / 64;
+    const int stream = M / kStreamPassRows * 100 + (rest == 0 ? 0 : rest <= 4 ? 55 : rest <= kDecodeMaxM ? 65 : 96);
+    const int split = tiles * ((M + tiles - 1) / tiles <= 48 ? 172 : 207);
+    return split * wgs <= stream * (wgs + 700);
 }
 
 // Which kernels run each matrix of a call (values of RWKVQ_PATH_*): the one place that decides.

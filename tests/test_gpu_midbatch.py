@@ -138,7 +138,8 @@ def test_unrounded_weights_at_the_ends_of_bf16(fmt, scale, options):
 @pytest.mark.parametrize("fmt", ["sq", "vq6", "vq8"])
 def test_line_between_the_forms_of_the_streaming_path(fmt, options):
     """RWKVQ_OPT_STREAM_SPLIT_MAX_WORK at 17 <= M <= 128: 1 never takes the kernels that split K, 1000000 always does, a value in
-    between moves the line at M <= 32 and leaves M > 32 alone; seen by the order of the sums."""
+    between moves the line at M <= 32 and leaves M > 32 alone, where a third pass of few rows is cheaper than a second tile
+    of the others from some 2000 workgroups on; seen by the order of the sums."""
     torch = G.torch_()
     options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
     N, K = 4096, 1280
@@ -161,3 +162,7 @@ def test_line_between_the_forms_of_the_streaming_path(fmt, options):
             assert torch.equal(call(M, 2, value), few), (M, value)
             if many is not None:
                 assert torch.equal(call(M, 29, value), many), (M, value)
+    for M, few, many in ((66, True, False), (80, True, False), (48, True, True), (100, True, True)):
+        stream, split = call(M, 2, 1), call(M, 2, 1000000)
+        assert torch.equal(call(M, 2, 0), split if few else stream), M
+        assert torch.equal(call(M, 40, 0), split if many else stream), M
