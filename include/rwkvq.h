@@ -95,12 +95,15 @@ const char* rwkvq_status_string(int status);
  * (for tests, which run both sides of each choice, and for tuning on another machine).  Thread-safe;
  * a call made after rwkvq_set_option returns sees the new value.
  *   RWKVQ_OPT_SMALL_BATCH_PATH    how native-layout matrices run at 16 < M <= 128 (see rwkvq_sq_gemm):
- *                                 RWKVQ_SMALL_BATCH_AUTO (default: the estimate below), _STREAM, _MATRIX_CORES
+ *                                 RWKVQ_SMALL_BATCH_AUTO (default: the line below), _STREAM (weights unrounded),
+ *                                 _MATRIX_CORES (weights rounded to the type of x)
  *   RWKVQ_OPT_PREFILL_TILE_ROWS   rows of x per matrix-core workgroup: 0 (default: chosen from the sizes), or the kernels
  *                                 for large batches with 128 or 256 whatever the sizes
- *   the constants of the small-batch estimate, measured on the RWKV-6-7B shapes on one MI355X
- *   (0 restores the default):
- *   RWKVQ_OPT_STREAM_WIDE_GBPS    packed-weight GB/s of a streaming pass over 17..32 batch rows (2800)
+ *   the constants of the line between the two at 16 < M <= 128 (0 restores the default).  It compares ceil(M / 32) passes over
+ *   the packed weights with 128-row matrix-core workgroups, in durations of kernels on the RWKV-6-7B shapes on one MI355X; both
+ *   ways have faster kernels since, and the line has been left where it was, so that the weights of a call are rounded, or not,
+ *   as before:
+ *   RWKVQ_OPT_STREAM_WIDE_GBPS    packed-weight GB/s of a pass over 17..32 batch rows (2800)
  *   RWKVQ_OPT_STREAM_NARROW_GBPS  ... over <= 16 batch rows (4100)
  *   RWKVQ_OPT_STREAM_WIDE_MIN_US  least duration of such a pass in microseconds (24)
  *   RWKVQ_OPT_STREAM_NARROW_MIN_US  (12)
@@ -154,15 +157,16 @@ int rwkvq_vq_dequant(const void* indices, const void* codebooks, int layout, int
  * bring bf16 activations into fp16's range group by group with exact power-of-two scales - a
  * group being the columns that share an accumulator, at most 256 consecutive ones of a row of x - so
  * an activation enters its sum exactly unless it is more than 2^29 times smaller than the largest
- * of its group, which is below the resolution of the binary32 sum); y is row-major fp16, bf16 or
+ * of its group, which is below the resolution of the binary32 sum; the kernels for M > 16 that split K
+ * multiply bf16 activations as they are); y is row-major fp16, bf16 or
  * fp32; products are accumulated in binary32 and y is rounded to nearest even.  The path is chosen from M and the layout:
  *   canonical layout: a plain reference kernel (any M);
  *   native layout, M <= 16: streaming dequant-GEMV kernels bound by HBM bandwidth;
  *   native layout, M  > 16: tiles dequantized into LDS and multiplied on the matrix cores in
  *                           the type of x, weights rounded to that type;
  *   native layout, 16 < M <= 128: the matrix cores with weights rounded, or the streaming path (weights
- *                           exact: one or several passes over W), whichever is estimated cheaper
- *                           for the matrices of the call.  A matrix whose N is not a multiple of 256 has
+ *                           exact: one or several passes over W), by the sizes of the
+ *                           call's matrices (see rwkvq_set_option).  A matrix whose N is not a multiple of 256 has
  *                           no tiles of the first: streaming path up to M = 128, beyond that the
  *                           plain reference kernel.
  * x and y must not overlap. */

@@ -74,11 +74,22 @@ rwkvq_matrix vq_desc(const void* indices, const void* codebooks, int layout, int
     return m;
 }
 
-// Estimated cost, in microseconds, of the two ways to run native-layout matrices at 16 < M <= 128:
-// a streaming pass over 17..32 batch rows moves `wide` GB/s of packed weights and costs at least
-// `wide_min` us, one over <= 16 rows `narrow` GB/s and at least `narrow_min` us; a k-step of a 128-row
-// matrix-core workgroup takes `kstep` ns, one workgroup per compute unit.  The defaults (rwkvq.h) were
-// measured on the 7B shapes on one MI355X; rwkvq_set_option replaces them, or forces one path.
+// Which calls at 16 < M <= 128 have their weights rounded to the type of x?  The line weighs ceil(M / 32) passes over W at
+// `wide` GB/s (17..32 rows, at least `wide_min` us) or `narrow` GB/s (<= 16 rows, `narrow_min`) against 128-row matrix-core
+// workgroups at `kstep` ns per 64 columns, one per compute unit: durations of the kernels that the two ways had when it was
+// drawn (7B shapes, one MI355X).  Both have become faster since, without and with rounding by kernels of midbatch.hip, and the
+// line has stayed where it was, so that a call keeps the weights it is computed with: it is no longer where the two take equally
+// long.  us, unrounded / rounded, * = what the line takes (bf16, SQ and 6-bit VQ):
+//                            M = 32         48          64          96          128
+//   4096 x 4096            *11 /  14    *12 /  14   *15 /  14   *12 /  14    15 / *15
+//   {r, k, v, g}           *14 /  15    *16 /  15   *19 /  15   *32 /  26    37 / *29
+//   4096 x 14336           *23 /  33    *28 /  33   *36 /  33   *29 /  34   *36 /  34
+//   {14336 + 4096 x 4096}  *23 /  24    *27 /  24   *32 /  24   *40 /  29    47 / *33
+//   one layer              *40 /  68    *47 /  69   *55 /  70   *91 /  83  *107 /  92
+//   four layers           *126 / 164   *193 / 169  *225 / 170   364 /*222   424 /*261
+//   32 layers             *863 / 1279 *1489 / 1272 *1769 / 1331 2804 /*1656 3327 /*1918
+//   1024 x 1024            7.5 / *7.5   7.5 / *7.6  8.1 / *7.7   7.5 / *7.7  8.2 / *7.7
+// rwkvq_set_option moves the line, or forces one way (RWKVQ_OPT_SMALL_BATCH_PATH).
 constexpr int kStreamPassesMaxM = 128;
 constexpr int kStreamPassRows = 32;    // batch rows per pass of the streaming kernels (their largest instance)
 bool stream_passes_cheaper(const std::vector<MatDev>& mats, int M) {
@@ -141,10 +152,8 @@ void plan_paths(const std::vector<MatDev>& devs, int M, std::vector<int>* path) 
         if (M <= kDecodeMaxM && d.K <= kDecodeMaxK) (*path)[i] = RWKVQ_PATH_STREAM;
         else if (M > kDecodeMaxM && d.N % 256 == 0) { (*path)[i] = RWKVQ_PATH_MATRIX_CORES; mfma.push_back(d); }
         else if (M > kDecodeMaxM && M <= kStreamPassesMaxM && d.K <= kDecodeMaxK)
-            (*path)[i] = RWKVQ_PATH_STREAM_PASSES;        // N not a multiple of 256: no matrix-core tiles
+            (*path)[i] = RWKVQ_PATH_STREAM_PASSES;        // N not a multiple of 256: no tiles of the kernels that round
     }
-    // 16 < M <= 128: the matrix-core kernel pads M to 128 rows, and a call of a few matrices gives
-    // it few tiles; ceil(M / 32) passes of the streaming kernels over row blocks of x can be cheaper.
     if (!mfma.empty() && M <= kStreamPassesMaxM && stream_passes_cheaper(mfma, M))
         for (int& p : *path)
             if (p == RWKVQ_PATH_MATRIX_CORES) p = RWKVQ_PATH_STREAM_PASSES;
