@@ -28,7 +28,6 @@
 #include "../../include/rwkvq.h"
 
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 namespace rwkvq {
@@ -484,16 +483,9 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
 
 template <bool BF16, int MF, int NW, bool EXACT>
 static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
-    static std::atomic<unsigned long long> raised{0ull};        // bit d: the LDS limit was raised on device d
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    static std::atomic<unsigned long long> raised{0ull};
+    const hipError_t e = raise_lds((const void*)mid_kernel<BF16, MF, NW, EXACT>, mid_lds(MF, NW, EXACT), raised);
     if (e != hipSuccess) return e;
-    const unsigned long long bit = 1ull << (dev & 63);
-    if (!(raised.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute((const void*)mid_kernel<BF16, MF, NW, EXACT>, hipFuncAttributeMaxDynamicSharedMemorySize, mid_lds(MF, NW, EXACT));
-        if (e != hipSuccess) return e;
-        raised.fetch_or(bit, std::memory_order_release);
-    }
     hipLaunchKernelGGL((mid_kernel<BF16, MF, NW, EXACT>), dim3(wgs), dim3(64 * kMidWaves), mid_lds(MF, NW, EXACT), s, a);
     return hipGetLastError();
 }

@@ -28,7 +28,6 @@
 #include "../../include/rwkvq.h"
 
 #include <algorithm>
-#include <atomic>
 #include <vector>
 
 namespace rwkvq {
@@ -483,17 +482,9 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
 // threads that get here together both raise it, which is harmless.
 template <bool BF16, int FMT, int MF>
 static hipError_t launch_fmt_mf(const PfArgs& a, int wgs, hipStream_t s) {
-    static std::atomic<unsigned long long> raised{0ull};        // bit d: done on device d
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    static std::atomic<unsigned long long> raised{0ull};
+    const hipError_t e = raise_lds((const void*)prefill_kernel<BF16, FMT, MF>, pf_lds_bytes(FMT), raised);
     if (e != hipSuccess) return e;
-    const unsigned long long bit = 1ull << (dev & 63);
-    if (!(raised.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute((const void*)prefill_kernel<BF16, FMT, MF>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, pf_lds_bytes(FMT));
-        if (e != hipSuccess) return e;
-        raised.fetch_or(bit, std::memory_order_release);
-    }
     hipLaunchKernelGGL((prefill_kernel<BF16, FMT, MF>), dim3(wgs), dim3(256), pf_lds_bytes(FMT), s, a);
     return hipGetLastError();
 }

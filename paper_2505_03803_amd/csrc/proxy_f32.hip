@@ -506,7 +506,7 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
 // Stored where it is met, a key is a request of four bytes to a line of its own.  TILED: 4096 keys at a time are brought into
 // the order of their class first (the lower 11 bits of the bin: keys of one bin stand together, whatever else is in the class),
 // so that a wavefront's store meets runs.  Measured (us; not tiled, tiled): 1280 x 1280 35, 44; 2048 x 2048 even; 4096 x 4096
-// 103, 70; 14336 x 4096 460, 239: tiled from kTiledMinCount on.
+// 103, 70; 14336 x 4096 460, 239: tiled beyond kTiledMinCount.
 constexpr int kClasses = 2048;
 constexpr uint32_t kTiledMinCount = 1u << 22;
 template <bool TILED>
@@ -835,9 +835,11 @@ static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, doub
     const uint32_t wgs = set_workgroups(count);
     constexpr int lds = kBins * 4, lds_partition = lds + (4 * kSetThreads + kClasses + kSetThreads / 64) * 4;   // 128 and 152 KB
     static_assert(lds_partition <= 160 * 1024, "LDS of a compute unit");
-    for (const void* f : {(const void*)set_count_kernel, (const void*)set_partition_kernel<false>, (const void*)set_partition_kernel<true>,
-                          (const void*)set_final_kernel}) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_partition);
+    const void* kernels[] = {(const void*)set_count_kernel, (const void*)set_partition_kernel<false>, (const void*)set_partition_kernel<true>,
+                             (const void*)set_final_kernel};
+    static std::atomic<unsigned long long> raised[4];
+    for (int i = 0; i < 4; ++i) {
+        const hipError_t e = raise_lds(kernels[i], lds_partition, raised[i]);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(set_clear_kernel, dim3(256), dim3(256), 0, s, b, set_joint_max(count));
