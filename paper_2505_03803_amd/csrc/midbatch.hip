@@ -114,21 +114,22 @@ __device__ __forceinline__ uint32_t mid_sq_pair(uint32_t w0, uint32_t w1, uint32
         return Elem<BF16>::pack(lo, hi);
     }
 }
-// Does any group of the workgroup's rows of W have a zero point in (0, 2^-11)?  Zero counts as one: the ROUND form covers it.
+// Does any group of the workgroup's rows of W have a zero point in (0, 2^-11) or (-2^-11, 0)?
 // The scales and zero points (8 % of W's bytes) are read here once more than by the loop, each wavefront its eighth; a test
 // per tile in the loop held both forms of the unpack in registers and spilled.
 __device__ __forceinline__ bool mid_small_zero(const void* sz, int bytes, int tid, uint32_t* lds) {
     const __amdgpu_buffer_rsrc_t buf = mid_buffer(sz, (uint32_t)bytes);
-    uint32_t least = 0x7FFFFFFFu;
+    uint32_t least = 0xFFFFFFFFu;              // of |z| - 1 (fp16 bits, high half): a zero wraps to the top
+    auto z = [](uint32_t v) { return (v & 0x7FFF0000u) - 0x00010000u; };
     for (int at = 16 * tid; at < bytes; at += 8 * 16 * 64 * kMidWaves) {
         uint4_t v[8];                          // eight loads in flight: a 4096-column workgroup's 16 KB need two
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(buf, std::min(at + k * 16 * 64 * kMidWaves, bytes - 16), 0, 0);
 #pragma unroll
         for (int k = 0; k < 8; ++k)
-            least = min(min(least, min(v[k].x & 0x7FFF0000u, v[k].y & 0x7FFF0000u)), min(v[k].z & 0x7FFF0000u, v[k].w & 0x7FFF0000u));
+            least = min(min(least, min(z(v[k].x), z(v[k].y))), min(z(v[k].z), z(v[k].w)));
     }
-    const bool any = __builtin_amdgcn_ballot_w64(least < 0x10000000u) != 0;      // fp16 0x1000 = 2^-11
+    const bool any = __builtin_amdgcn_ballot_w64(least < 0x0FFF0000u) != 0;      // fp16 0x1000 = 2^-11
     if ((tid & 63) == 0) lds[tid >> 6] = any;
     __syncthreads();
     uint32_t all = 0;

@@ -79,14 +79,18 @@ def test_calls_that_fill_the_device(fmt, n_mats, tiles, options):
 
 
 @pytest.mark.parametrize("xdt", ["bf16", "f16"])
-@pytest.mark.parametrize("small", [False, True])
+@pytest.mark.parametrize("small", [False, True, "zero"])
 def test_one_hot_rows_return_the_rounded_weights(xdt, small, options):
     """Row m selects column k_m: the output is Deq(W) rounded once to the type of x, bit for bit.  With a zero point in
-    (0, 2^-11) q - z itself rounds; one such group, subnormal ones among them, makes its workgroup take the two-step form."""
+    (0, 2^-11) q - z itself rounds; one such group, subnormal ones among them, makes its workgroup take the two-step form (a
+    zero point of zero, either sign, does not)."""
     options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_MATRIX_CORES)
     N, K = 512, 1280
     mat = make("sq", N, K, 31)
-    if small:
+    if small == "zero":
+        mat.zeros.reshape(-1)[:] = np.where(np.arange(mat.zeros.size) % 3 == 0, 0x8000, 0)
+        mat.zeros.reshape(N, -1)[300:310] = 0x1000            # and the smallest that is not small
+    elif small:
         rng = np.random.default_rng(5)
         z = mat.zeros.reshape(N, K // 128)
         for n in range(N):                                   # fp16 bits 1 .. 0x0FFF, either sign; and an exact zero
