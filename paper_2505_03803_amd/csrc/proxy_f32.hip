@@ -294,14 +294,16 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //                           distances of set bits times the exponent's unit, exact; t ln t of the small distances comes from
 //                           a table made with the same expressions.  A bin of more than 131072 keys is read by several
 //                           workgroups that join their bitmaps in memory, and the last to finish sums.  A group of small bins
-//                           is sorted in LDS;
+//                           is sorted (sort_group);
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
 // Bound: LDS (the partition's counters and reordering, the bitmaps' additions), not memory: 16 bytes per weight at 1.7 TB/s
-// for 14336 x 4096.  Measured (us; radix sort -> here): 768 x 768 159 -> 102, 1024 x 1024 164 -> 111, 4096 x 4096 500 -> 177,
-// 14336 x 4096 1954 -> 545 (count 63, plan 16, partition 239, sum 208, final 12); there with all weights equal 1563 -> 404,
-// values of bfloat16 1781 -> 641, half the weights zero 1866 -> 551.  Below kSetMinCount the sort.
+// for 14336 x 4096.  Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161,
+// 14336 x 4096 1957 -> 550 (count 63, plan 16, partition 239, sum 208, final 12); there with all weights equal 1570 -> 400,
+// values of bfloat16 1783 -> 642, half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform
+// from -40 to 20) at 3 x 2^20 weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604
+// (the one kind found that is slower here).  Below kSetMinCount the sort.
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
 constexpr int kBins = 32768, kBinShift = 17;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
@@ -609,7 +611,9 @@ __device__ __forceinline__ double block_sum(const double (&s)[kSetRow], double (
 __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, double inv_mean, int terms, const SetBuffers& b,
                                            double* table, int* wave_last, double (&s)[kSetRow]) {
     constexpr int kWords = kBitmapWords / kSumThreads;                        // per thread: 256 patterns
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));              // (what follows from it is made again per bin, not kept over the loop around)
+    const int lane = tid & 63, wave = tid >> 6;
     // one exponent: neighbours d patterns apart differ by d units (exactly, also in binary64)
     const uint32_t base = bin << kBinShift, pattern = (base & 0x80000000u) ? base & 0x7FFFFFFFu : ~base;
     const int ex = (int)((pattern >> 23) & 255u);
@@ -679,6 +683,74 @@ __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, d
     s[kGapSums] += (double)total;
 }
 
+// Bitonic sort of a group: thread t holds keys 4 t .. 4 t + 3 of up to 2048 (`size` of them, a power of two from 256 on, the rest
+// of the threads only meet the barriers).  Steps of up to 128 keys stay within a wavefront, in registers (strides 1 and 2) and
+// by lane exchanges; the six longer ones of 2048 keys go through LDS, in two buffers that alternate, a barrier each.
+// With all 66 steps through LDS, 2^24 random patterns took 1070 us instead of 604, 4096 x 4096 normal weights 173 instead of 161.
+template <int L>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t v) {
+    if constexpr (L == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);     // quad_perm [1, 0, 3, 2]
+    else if constexpr (L == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);    // [2, 3, 0, 1]
+    else if constexpr (L == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);   // row_ror 8
+    else if constexpr (L == 32) return (uint32_t)__shfl_xor((int)v, 32, 64);
+    else return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (L << 10) | 0x1F);                                  // 4, 16
+}
+__device__ __forceinline__ void in_order(uint32_t& a, uint32_t& b, bool up) {
+    const uint32_t lo = min(a, b), hi = max(a, b);
+    a = up ? lo : hi;
+    b = up ? hi : lo;
+}
+// The steps of strides S, S / 2, .., 1 of a merge, S <= 128.
+template <int S>
+__device__ __forceinline__ void merge_within(uint32_t (&k)[4], int lane, bool up) {
+    if constexpr (S >= 4) {
+        const bool least = ((lane & (S / 4)) == 0) == up;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t o = from_lane_xor<S / 4>(k[j]);
+            k[j] = least ? min(k[j], o) : max(k[j], o);
+        }
+        merge_within<S / 2>(k, lane, up);
+    } else {
+        in_order(k[0], k[2], up); in_order(k[1], k[3], up);
+        in_order(k[0], k[1], up); in_order(k[2], k[3], up);
+    }
+}
+template <int LEN>
+__device__ __forceinline__ void sort_within(uint32_t (&k)[4], uint32_t tid) {       // 4 LEN / 4 .. 256 keys in order, directions as the next merge wants
+    if constexpr (LEN == 2) {
+        in_order(k[0], k[1], true); in_order(k[2], k[3], false);
+    } else {
+        sort_within<LEN / 2>(k, tid);
+        merge_within<LEN / 2>(k, tid & 63, (4 * tid & LEN) == 0);
+    }
+}
+// Leaves the sorted keys in data (its first or its second half) and returns where, behind a barrier.
+__device__ __forceinline__ const uint32_t* sort_group(uint32_t (&k)[4], uint32_t* data, uint32_t size, uint32_t tid) {
+    const bool mine = 4u * tid < size;                                          // (whole wavefronts)
+    uint32_t* buf = data;
+    if (mine) sort_within<256>(k, tid);
+    for (uint32_t len = 512u; len <= size; len *= 2u) {
+        const bool up = (4u * tid & len) == 0u;
+        for (uint32_t stride = len / 2u; stride >= 256u; stride /= 2u) {
+            if (mine) *(uint4_t*)(buf + 4 * tid) = uint4_t{k[0], k[1], k[2], k[3]};
+            __syncthreads();
+            if (mine) {
+                const uint4_t o = *(const uint4_t*)(buf + (4u * tid ^ stride));
+                const uint32_t ov[4] = {o.x, o.y, o.z, o.w};
+                const bool least = ((4u * tid & stride) == 0u) == up;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) k[j] = least ? min(k[j], ov[j]) : max(k[j], ov[j]);
+            }
+            buf = buf == data ? data + 2048 : data;
+        }
+        if (mine) merge_within<128>(k, tid & 63, up);
+    }
+    if (mine) *(uint4_t*)(buf + 4 * tid) = uint4_t{k[0], k[1], k[2], k[3]};
+    __syncthreads();
+    return buf;
+}
+
 __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, uint32_t count, int terms) {
     __shared__ __attribute__((aligned(16))) uint32_t data[kBitmapWords];     // a bitmap or a group's keys
     __shared__ double table[kTable];
@@ -746,25 +818,18 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, u
         } else {
             const uint32_t from = b.group_from[unit - head.pieces], to = b.group_from[unit - head.pieces + 1u];
             const uint32_t n = to - from;                                     // at most 2047
-            uint32_t size = 2u;
+            uint32_t size = 256u, own[4], me = tid;
+            asm volatile("" : "+v"(me));                                    // (nothing of it kept in registers over the bitmaps)
             while (size < n) size *= 2u;
-            for (uint32_t i = tid; i < size; i += kSumThreads) data[i] = i < n ? b.keys[from + i] : 0xFFFFFFFFu;
-            for (uint32_t len = 2u; len <= size; len *= 2u)
-                for (uint32_t step = len / 2u; step; step /= 2u) {
-                    __syncthreads();
-                    for (uint32_t p = tid; p < size / 2u; p += kSumThreads) {
-                        const uint32_t lo = 2u * p - (p & (step - 1u)), hi = lo + step;
-                        const uint32_t x = data[lo], y = data[hi];
-                        if ((x > y) == ((lo & len) == 0u)) { data[lo] = y; data[hi] = x; }
-                    }
-                }
-            __syncthreads();
+#pragma unroll
+            for (uint32_t j = 0; j < 4u; ++j) own[j] = 4u * me + j < n ? b.keys[from + 4u * me + j] : 0xFFFFFFFFu;
+            const uint32_t* sorted = sort_group(own, data, size, me);
 #pragma unroll 1
-            for (uint32_t i = tid; i < n; i += kSumThreads) {
-                const uint32_t k = data[i], bin = k >> kBinShift;
-                if (i == 0u || data[i - 1u] >> kBinShift != bin) b.bin_min[bin] = k;
-                if (i + 1u == n || data[i + 1u] >> kBinShift != bin) { b.bin_max[bin] = k; continue; }
-                const uint32_t k1 = data[i + 1u];
+            for (uint32_t i = me; i < n; i += kSumThreads) {
+                const uint32_t k = sorted[i], bin = k >> kBinShift;
+                if (i == 0u || sorted[i - 1u] >> kBinShift != bin) b.bin_min[bin] = k;
+                if (i + 1u == n || sorted[i + 1u] >> kBinShift != bin) { b.bin_max[bin] = k; continue; }
+                const uint32_t k1 = sorted[i + 1u];
                 if (k1 == k) continue;
                 const double t = (key_f64(k1) - key_f64(k)) * inv_mean;
                 if (t > 0.0) s[0] += t * log(t);

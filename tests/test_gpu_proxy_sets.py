@@ -34,7 +34,7 @@ def test_proxy_sets_sizes(n):
         check(synth.gen_dense_weights(rng, 1, n, "f32", outlier_fraction=1e-3), terms)
 
 
-@pytest.mark.parametrize("kind", ["patterns", "zeros", "bf16", "spaced", "two", "one_bin", "few_bins"])
+@pytest.mark.parametrize("kind", ["patterns", "zeros", "bf16", "spaced", "two", "one_bin", "few_bins", "small_bins"])
 def test_proxy_sets_kinds(kind):
     rng = np.random.default_rng(31)
     n = BIG + 777
@@ -55,13 +55,22 @@ def test_proxy_sets_kinds(kind):
         w = np.where(rng.random(n) < 0.5, np.float32(1.0), np.float32(2.0))
     elif kind == "one_bin":                                     # one bin of several pieces, dense
         w = (1.0 + rng.integers(0, 1 << 17, n) * 2.0 ** -23).astype(np.float32)
-    elif kind == "few_bins":                                    # around 4096 and 131072 keys per bin
+    elif kind == "few_bins":                                    # around 131072 keys per bin, several pieces
         sizes = [4095, 4096, 4097, 8191, 131071, 131072, 131073, 262145]
         m = np.repeat(np.arange(len(sizes)), sizes)
         fine = rng.integers(0, 1 << 17, m.size)
         a = (((127 << 6) + m) << 17 | fine).astype(np.uint32)
         w = np.concatenate([a, a | np.uint32(0x80000000)]).view(np.float32)
         w = rng.permutation(w)
+    elif kind == "small_bins":                                  # around 1024 keys (a bin with more is a bitmap) and groups of
+        # every power of two: first one of exactly 2047 keys (1023 and 1024), then single bins that end or begin one
+        sizes = [1023, 1024, 1025, 1024, 1024, 1023, 1, 1024, 255, 769, 256, 768, 257, 767, 511, 512, 1, 1, 1022, 1024, 1025, 1026]
+        sizes += [1] * 300 + [1024] * 3 + [3, 5, 7] * 200 + [1000] * 520
+        m = np.repeat(np.arange(len(sizes)), sizes)
+        a = (((100 << 6) + m) << 17 | rng.integers(0, 1 << 17, m.size)).astype(np.uint32)
+        w = rng.permutation(a).view(np.float32)
+        check(np.concatenate([w, np.float32([1e-30])]))         # one key in front moves every group
+        check(w[: BIG + 5])                                     # a last group of any size
     assert w.size >= BIG
     if kind != "spaced":                                        # the same kind large enough for the tiled partition, ragged
         check(np.concatenate([np.resize(w, 8 * BIG), w[:4099]]))
@@ -77,8 +86,9 @@ def test_proxy_sets_not_finite():
     rng = np.random.default_rng(8)
     for bad in ([np.inf], [-np.inf], [np.inf, -np.inf], [np.nan], [-np.nan, np.inf]):
         out = []
-        for n in (4096, BIG):
+        for n in (4096, BIG, 8 * BIG + 3):                      # the radix sort, the partition, the one in tiles
             w = rng.standard_normal(n).astype(np.float32)
             w[5:5 + len(bad)] = bad
             out.append(run(w))
-        assert np.array_equal(np.array(out[0]), np.array(out[1]), equal_nan=True), (bad, out)
+        for got in out[1:]:
+            assert np.array_equal(np.array(out[0]), np.array(got), equal_nan=True), (bad, out)
