@@ -257,6 +257,15 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         if constexpr (FMT == FMT_VQ6) r.cb = __builtin_amdgcn_raw_buffer_load_b32(abuf, at >> 2, T * kBook, 0);
         if constexpr (FMT == FMT_VQ8) r.cb8 = __builtin_amdgcn_raw_buffer_load_b128(abuf, at, T * kBook, 0);
     };
+    auto keep = [](const MidRegs<FMT>& r) {
+#pragma unroll
+        for (int i = 0; i < kMidNF; ++i) {
+            asm volatile("" :: "v"(r.a[i]), "v"(r.b[i]));
+            if constexpr (SQ) asm volatile("" :: "v"(r.sz[i]));
+        }
+        if constexpr (FMT == FMT_VQ6) asm volatile("" :: "v"(r.cb));
+        if constexpr (FMT == FMT_VQ8) asm volatile("" :: "v"(r.cb8));
+    };
     constexpr int kLoads = SQ ? 3 * kMidNF : 2 * kMidNF + 1;
     constexpr bool SPLIT = EXACT && BF16 && !SQ;   // fp16 entries as the sum of two bf16 (8 + 3 of the 11 bits, exact), multiplied in turn
     auto high = [](uint32_t e) { return Elem<true>::from_f16x2(e); };
@@ -392,6 +401,10 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
             pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * kMidNF, books);
         }
     }
+    // The waits in head() count the loads of the next tile's words, those of the last tile (never used) too.  The compiler may
+    // not take an iteration out of the loop and drop its unused loads, which would leave activations unwaited for: no peeling,
+    // and every word loaded is named behind the loop's last step.
+#pragma clang loop unroll(disable)
     for (int j = 0; j < nt; ++j) {             // nothing conditional inside: the compiler then counts the loads in flight exactly
         head(std::integral_constant<int, 0>{}, j);
         body(std::integral_constant<int, 0>{}, j);
@@ -401,7 +414,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         body(std::integral_constant<int, 2>{}, j);
         head(std::integral_constant<int, 3>{}, j);
         body(std::integral_constant<int, 3>{}, j);
-        if constexpr (SETS == 2) r0 = r1;
+        if constexpr (SETS == 2) { keep(r1); r0 = r1; }
     }
     if constexpr (NW > 1)
         for (int j = 4 * nt; j < 4 * rounds; ++j) RWKVQ_BARRIER();     // a group with fewer column tiles than the longest
