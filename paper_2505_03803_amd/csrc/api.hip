@@ -79,16 +79,16 @@ rwkvq_matrix vq_desc(const void* indices, const void* codebooks, int layout, int
 // workgroups at `kstep` ns per 64 columns, one per compute unit: durations of the kernels that the two ways had when it was
 // drawn (7B shapes, one MI355X).  Both have become faster since, without and with rounding by kernels of midbatch.hip, and the
 // line has stayed where it was, so that a call keeps the weights it is computed with: it is no longer where the two take equally
-// long.  us, unrounded / rounded, * = what the line takes (bf16, SQ and 6-bit VQ):
+// long.  us, unrounded / rounded, * = what the line takes (bf16, SQ and 6-bit VQ; single matrices SQ):
 //                            M = 32         48          64          96          128
-//   4096 x 4096            *11 /  14    *12 /  14   *15 /  14   *12 /  14    15 / *15
+//   4096 x 4096           *7.5 /  14   *8.6 /  14  *9.6 /  14  *9.4 /  14    11 / *15
 //   {r, k, v, g}           *14 /  15    *16 /  15   *19 /  15   *32 /  26    37 / *29
-//   4096 x 14336           *23 /  33    *28 /  33   *36 /  33   *29 /  34   *36 /  34
+//   4096 x 14336           *16 /  33    *20 /  33   *24 /  33   *24 /  34   *30 /  34
 //   {14336 + 4096 x 4096}  *23 /  24    *27 /  24   *32 /  24   *40 /  29    47 / *33
 //   one layer              *40 /  68    *47 /  69   *55 /  70   *91 /  83  *107 /  92
 //   four layers           *126 / 164   *193 / 169  *225 / 170   364 /*222   424 /*261
 //   32 layers             *863 / 1279 *1489 / 1272 *1769 / 1331 2804 /*1656 3327 /*1918
-//   1024 x 1024            7.5 / *7.5   7.5 / *7.6  8.1 / *7.7   7.5 / *7.7  8.2 / *7.7
+//   1024 x 1024            7.2 / *7.5   7.4 / *7.6  7.4 / *7.7   7.4 / *7.7  7.4 / *7.7
 // rwkvq_set_option moves the line, or forces one way (RWKVQ_OPT_SMALL_BATCH_PATH).
 constexpr int kStreamPassesMaxM = 128;
 constexpr int kStreamPassRows = 32;    // batch rows per pass of the streaming kernels (their largest instance)

@@ -18,8 +18,11 @@
 // EXACT instances (17 <= M <= 128 where the streaming kernels' contract holds: weights unrounded, fp16 or bf16 x multiplied as it
 // is): NW = 1, 32 to 64 rows of x per workgroup, so a call that took ceil(M / 32) passes over W takes one (M <= 64).  SQ: codes as
 // 8 + q with the scale and zero point applied to the group's sums; VQ: the fp16 entries, for bf16 x as the sum of two bf16.
+// A workgroup takes 32 rows of W (NF = 2) where that gives at most one per compute unit, and 64 otherwise.
 // Measured (fp16, us; streaming kernels -> here): {r, k, v, g} of 4096 x 4096 at M = 32 21.3 -> 12.6, 48 34.8 -> 15.4, 64
-// 41 -> 17.6, 128 83 -> 31; 4096 x 14336 38 -> 24, 59 -> 29, 75 -> 33, 152 -> 36.
+// 41 -> 17.6, 128 83 -> 31; bf16, 8-bit VQ: 4096 x 4096 at M = 17 10.1 -> 8.4 (64 rows: 11.7), 4096 x 14336 at 17 26.1 -> 18.2
+// (27.6), at 64 75 -> 26 (35); SQ: 61 -> 20 at 48 (28); {r, k, v, g} are 512 workgroups of 32 rows and slower in them (SQ, M = 48
+// 16.0, 64 rows 12.9).
 // Tried and slower or equal: wavefronts of 32 instead of 64 rows of W with sixteen per workgroup (the fragment reads from
 // LDS double: - 8 % at M = 64, + 20 % at M = 1024), fragment reads three and four rows ahead (equal), an MFMA / vector
 // instruction interleave fixed with scheduling groups (equal at MF = 4, spills at MF = 8).
@@ -56,7 +59,7 @@ constexpr int mid_stage(int MF) { return 16 * MF * kRowBytes; }
 constexpr int mid_book(bool EXACT) { return EXACT ? 2 * kMidBook : kMidBook; }       // EXACT, bf16: two words per entry
 constexpr int mid_stages(int MF, int NW, bool EXACT) { return std::min(4, (EXACT ? 128 : 144) * 1024 / (kMidWaves / NW * mid_stage(MF))); }
 constexpr int mid_ring(int MF, int NW, bool EXACT) { return kMidWaves / NW * mid_stages(MF, NW, EXACT) * mid_stage(MF); }
-constexpr int mid_red() { return kMidWaves * 4 * kMidNF * 1024; }      // partial sums of four subtile rows of every wavefront
+constexpr int mid_red() { return kMidWaves * 4 * 4 * 1024; }           // partial sums of four subtile rows of every wavefront
 constexpr int mid_lds(int MF, int NW, bool EXACT) {
     return std::max(mid_ring(MF, NW, EXACT) + kMidWaves * mid_sets(MF, EXACT) * mid_book(EXACT), mid_red());
 }
@@ -80,10 +83,10 @@ __device__ __forceinline__ float4_t mid_mfma(uint4_t w, uint4_t x, float4_t c) {
 }
 
 // Packed words of one 256-column tile for the wavefront's row tiles.
-template <int FMT> struct MidRegs;
-template <> struct MidRegs<FMT_SQ3> { uint4_t a[kMidNF]; uint2_t b[kMidNF]; uint2_t sz[kMidNF]; };   // sz: (scale, zero) x 2 units
-template <> struct MidRegs<FMT_VQ6> { uint4_t a[kMidNF]; uint2_t b[kMidNF]; uint32_t cb; };
-template <> struct MidRegs<FMT_VQ8> { uint4_t a[kMidNF]; uint4_t b[kMidNF]; uint4_t cb8; };
+template <int FMT, int NF> struct MidRegs;
+template <int NF> struct MidRegs<FMT_SQ3, NF> { uint4_t a[NF]; uint2_t b[NF]; uint2_t sz[NF]; };   // sz: (scale, zero) x 2 units
+template <int NF> struct MidRegs<FMT_VQ6, NF> { uint4_t a[NF]; uint2_t b[NF]; uint32_t cb; };
+template <int NF> struct MidRegs<FMT_VQ8, NF> { uint4_t a[NF]; uint4_t b[NF]; uint4_t cb8; };
 
 // SQ pair P of a unit.  The definition rounds q - z and then the product with s (sq_pair_deq).  q s and z s are exact in
 // binary32 (3 and 11 bits times 11 bits), so q s - z s with one rounding is the same value whenever q - z is exact, which
@@ -153,16 +156,16 @@ __device__ __forceinline__ uint32_t mid_sq_code(uint32_t w0, uint32_t w1, uint32
         return (((w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2)) << at) | magic;
     }
 }
-template <bool BF16, int H>
-__device__ __forceinline__ uint32_t mid_code_pair(const MidRegs<FMT_SQ3>& r, int i, int p, uint32_t mask, uint32_t magic) {
+template <bool BF16, int H, int NF>
+__device__ __forceinline__ uint32_t mid_code_pair(const MidRegs<FMT_SQ3, NF>& r, int i, int p, uint32_t mask, uint32_t magic) {
     constexpr int u = H >> 2, t = H & 3;
     const uint32_t w0 = u == 0 ? r.a[i].x : r.a[i].w, w1 = u == 0 ? r.a[i].y : r.b[i].x, w2 = u == 0 ? r.a[i].z : r.b[i].y;
     return p == 0 ? mid_sq_code<BF16, 4 * t>(w0, w1, w2, mask, magic) : p == 1 ? mid_sq_code<BF16, 4 * t + 1>(w0, w1, w2, mask, magic)
          : p == 2 ? mid_sq_code<BF16, 4 * t + 2>(w0, w1, w2, mask, magic) : mid_sq_code<BF16, 4 * t + 3>(w0, w1, w2, mask, magic);
 }
 // Index of weight pair p of step H, row tile i.
-template <int FMT, int H>
-__device__ __forceinline__ uint32_t mid_index(const MidRegs<FMT>& r, int i, int p) {
+template <int FMT, int H, int NF>
+__device__ __forceinline__ uint32_t mid_index(const MidRegs<FMT, NF>& r, int i, int p) {
     constexpr int u = H >> 2, t = H & 3;
     if constexpr (FMT == FMT_VQ8) {
         const uint4_t q = u == 0 ? r.a[i] : r.b[i];
@@ -175,8 +178,8 @@ __device__ __forceinline__ uint32_t mid_index(const MidRegs<FMT>& r, int i, int 
 }
 
 // Weight pair p (0..3) of 32-column step H (0..7) of the 256-column tile, row tile i: two weights as they are multiplied.
-template <bool BF16, int FMT, bool ROUND, int H>
-__device__ __forceinline__ uint32_t mid_pair(const MidRegs<FMT>& r, int i, int p, const uint32_t* book) {
+template <bool BF16, int FMT, bool ROUND, int H, int NF>
+__device__ __forceinline__ uint32_t mid_pair(const MidRegs<FMT, NF>& r, int i, int p, const uint32_t* book) {
     constexpr int u = H >> 2, t = H & 3;
     if constexpr (FMT == FMT_VQ8) {
         const uint4_t q = u == 0 ? r.a[i] : r.b[i];
@@ -196,22 +199,22 @@ __device__ __forceinline__ uint32_t mid_pair(const MidRegs<FMT>& r, int i, int p
         }
     }
 }
-// Pairs n0 .. n1-1 of the sixteen (row tile, pair) that a half step takes.
-template <bool BF16, int FMT, bool ROUND, int H>
-__device__ __forceinline__ void mid_pairs(uint32_t (&b)[kMidNF][4], const MidRegs<FMT>& r, int n0, int n1, const uint32_t* book) {
+// Pairs n0 .. n1-1 of the 4 NF (row tile, pair) that a half step takes.
+template <bool BF16, int FMT, bool ROUND, int H, int NF>
+__device__ __forceinline__ void mid_pairs(uint32_t (&b)[NF][4], const MidRegs<FMT, NF>& r, int n0, int n1, const uint32_t* book) {
 #pragma unroll
     for (int n = n0; n < n1; ++n) b[n >> 2][n & 3] = mid_pair<BF16, FMT, ROUND, H>(r, n >> 2, n & 3, book);
 }
 
-template <bool BF16, int FMT, bool ROUND, int MF, int NW, bool EXACT>
+template <bool BF16, int FMT, bool ROUND, int MF, int NW, bool EXACT, int NF>
 __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, char* lds, int m0, int n0, int wave, int lane,
-                                         float4_t (&acc)[MF][kMidNF]) {
+                                         float4_t (&acc)[MF][NF]) {
     constexpr int KW = kMidWaves / NW, ST = mid_stages(MF, NW, EXACT), SETS = mid_sets(MF, EXACT), AHEAD = ST - 1, kStage = mid_stage(MF);
     constexpr int tw = FMT == FMT_VQ8 ? 512 : 384, kBook = FMT == FMT_VQ8 ? 1024 : 256;
     constexpr bool SQ = FMT == FMT_SQ3;
     static_assert(ST >= 2 && ST <= 4, "one activation tile is copied while one is multiplied");
     const int nw = wave % NW, kg = wave / NW;
-    const int K = mt.K, KT = K >> 8, R0 = (n0 >> 4) + kMidNF * nw;
+    const int K = mt.K, KT = K >> 8, R0 = (n0 >> 4) + NF * nw;
     const int nt = kg < KT ? (KT - kg + KW - 1) / KW : 0, rounds = (KT + KW - 1) / KW;   // column tiles of this group, of the longest
     char* const ring = lds + kg * ST * kStage;
     uint32_t* const books = (uint32_t*)(lds + mid_ring(MF, NW, EXACT)) + wave * (SETS * mid_book(EXACT) / 4);
@@ -228,7 +231,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
     }
     const __amdgpu_buffer_rsrc_t xbuf = mid_buffer((const char*)mt.x + (size_t)m0 * K * 2, (uint32_t)std::min(a.M - m0, 16 * MF) * (uint32_t)K * 2u);
     // EXACT: N is any multiple of 16; row tiles past the end repeat the last one and are not stored
-    const int tiles = EXACT ? mid_row_tiles(mt.N, R0) : kMidNF;
+    const int tiles = EXACT ? mid_row_tiles(mt.N, R0, NF) : NF;
     const __amdgpu_buffer_rsrc_t wbuf = mid_buffer(mt.codes + (size_t)R0 * KT * tw, (uint32_t)(tiles * KT * tw * 4));
     const __amdgpu_buffer_rsrc_t abuf = SQ ? mid_buffer((const uint2_t*)mt.aux + (size_t)R0 * KT * 16, (uint32_t)(tiles * KT * 128))
                                            : mid_buffer((const char*)mt.aux + (size_t)(R0 >> 4) * KT * kBook, (uint32_t)(KT * kBook));
@@ -242,11 +245,11 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(dst + (NW * i + nw) * 1024), 16,
                                                      xoff[i], at, 0, 0);
     };
-    auto load = [&](MidRegs<FMT>& r, int j) {  // past the last tile the last one again
+    auto load = [&](MidRegs<FMT, NF>& r, int j) {  // past the last tile the last one again
         const int T = kg + KW * (j < nt ? j : nt - 1);
         const int at = 16 * lane;
 #pragma unroll
-        for (int i = 0; i < kMidNF; ++i) {
+        for (int i = 0; i < NF; ++i) {
             const int row_tile = EXACT ? mid_row_tile(i, tiles) : i;
             const int tile = mid_tile_offset(row_tile, T, KT, 4 * tw);
             r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, at, tile, 0);
@@ -257,16 +260,16 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         if constexpr (FMT == FMT_VQ6) r.cb = __builtin_amdgcn_raw_buffer_load_b32(abuf, at >> 2, T * kBook, 0);
         if constexpr (FMT == FMT_VQ8) r.cb8 = __builtin_amdgcn_raw_buffer_load_b128(abuf, at, T * kBook, 0);
     };
-    auto keep = [](const MidRegs<FMT>& r) {
+    auto keep = [](const MidRegs<FMT, NF>& r) {
 #pragma unroll
-        for (int i = 0; i < kMidNF; ++i) {
+        for (int i = 0; i < NF; ++i) {
             asm volatile("" :: "v"(r.a[i]), "v"(r.b[i]));
             if constexpr (SQ) asm volatile("" :: "v"(r.sz[i]));
         }
         if constexpr (FMT == FMT_VQ6) asm volatile("" :: "v"(r.cb));
         if constexpr (FMT == FMT_VQ8) asm volatile("" :: "v"(r.cb8));
     };
-    constexpr int kLoads = SQ ? 3 * kMidNF : 2 * kMidNF + 1;
+    constexpr int kLoads = SQ ? 3 * NF : 2 * NF + 1;
     constexpr bool SPLIT = EXACT && BF16 && !SQ;   // fp16 entries as the sum of two bf16 (8 + 3 of the 11 bits, exact), multiplied in turn
     auto high = [](uint32_t e) { return Elem<true>::from_f16x2(e); };
     auto low = [](uint32_t e) {
@@ -274,7 +277,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         const uint32_t h = Elem<true>::from_f16x2(e);
         return Elem<true>::pack((float)v.x - __uint_as_float(h << 16), (float)v.y - __uint_as_float(h & 0xFFFF0000u));
     };
-    auto stage_book = [&](const MidRegs<FMT>& r, uint32_t* to) {   // VQ: the tile's codebook as it is multiplied
+    auto stage_book = [&](const MidRegs<FMT, NF>& r, uint32_t* to) {   // VQ: the tile's codebook as it is multiplied
         if constexpr (FMT == FMT_VQ6) {
             if constexpr (SPLIT) *(uint2_t*)(to + 2 * lane) = uint2_t{high(r.cb), low(r.cb)};
             else to[lane] = Elem<BF16>::from_f16x2(r.cb);
@@ -294,9 +297,9 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
     asm("s_mov_b32 %0, %1" : "=s"(magic) : "n"(BF16 ? 0x3B003B00 : 0x48004800));
 
     const int row = lane & 15, q = lane >> 4;
-    uint32_t b[2][kMidNF][4], bl[SPLIT ? 2 : 1][kMidNF][4];            // operands of the two halves (32 columns) of a step; SPLIT: low parts
+    uint32_t b[2][NF][4], bl[SPLIT ? 2 : 1][NF][4];            // operands of the two halves (32 columns) of a step; SPLIT: low parts
     // pairs n0 .. n1 - 1 of step H into b[h]
-    auto pairs = [&](auto step, int h, const MidRegs<FMT>& r, int n0, int n1, const uint32_t* book) {
+    auto pairs = [&](auto step, int h, const MidRegs<FMT, NF>& r, int n0, int n1, const uint32_t* book) {
         constexpr int H = decltype(step)::value;
         if constexpr (EXACT && SQ) {
 #pragma unroll
@@ -312,8 +315,8 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
             mid_pairs<BF16, FMT, ROUND, H>(b[h], r, n0, n1, book);
         }
     };
-    float4_t part[EXACT && SQ ? MF : 1][kMidNF], X[EXACT && SQ ? MF : 1];   // EXACT SQ: the group's products and activation sums
-    MidRegs<FMT> r0, r1;
+    float4_t part[EXACT && SQ ? MF : 1][NF], X[EXACT && SQ ? MF : 1];   // EXACT SQ: the group's products and activation sums
+    MidRegs<FMT, NF> r0, r1;
     int stage = 0;                             // ring slot of the current step
 
     // Step KQ of tile j.  HEAD: wait for its activations, ask for those AHEAD steps on and, at the first step, for the next
@@ -340,13 +343,13 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         uint32_t* const next = books + (SETS == 2 ? (~j & 1) * (mid_book(EXACT) / 4) : 0);
         if constexpr (SETS == 1 && KQ == 0) {
             stage_book(r0, book);
-            pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * kMidNF, book);
+            pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * NF, book);
         }
         if constexpr (SETS == 2 && KQ == 3) stage_book(r1, next);
-        uint32_t szu[kMidNF];                  // EXACT SQ: the group's scale and zero point (one register set: reloaded below)
+        uint32_t szu[NF];                  // EXACT SQ: the group's scale and zero point (one register set: reloaded below)
         if constexpr (EXACT && SQ) {
 #pragma unroll
-            for (int i = 0; i < kMidNF; ++i) szu[i] = KQ < 2 ? r0.sz[i].x : r0.sz[i].y;
+            for (int i = 0; i < NF; ++i) szu[i] = KQ < 2 ? r0.sz[i].x : r0.sz[i].y;
         }
         uint4_t af[2 * MF];                    // activation fragments, read two rows ahead of their MFMAs
 #pragma unroll
@@ -359,28 +362,28 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
                 const bool first = KQ % 2 == 0 && h == 0;
                 const float4_t zero = {0, 0, 0, 0};
 #pragma unroll
-                for (int i = 0; i < kMidNF; ++i) part[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), first ? zero : part[fm][i]);
+                for (int i = 0; i < NF; ++i) part[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), first ? zero : part[fm][i]);
                 const uint32_t one = BF16 ? 0x39803980u : 0x3C003C00u;
                 X[fm] = mid_mfma<BF16>(af[f], uint4_t{one, one, one, one}, first ? zero : X[fm]);
             } else if constexpr (EXACT) {      // x first: a lane holds one row of W and four rows of x, as its scale and zero point are laid out
 #pragma unroll
-                for (int i = 0; i < kMidNF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), acc[fm][i]);
+                for (int i = 0; i < NF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), acc[fm][i]);
                 if constexpr (SPLIT) {
 #pragma unroll
-                    for (int i = 0; i < kMidNF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(bl[h][i]), acc[fm][i]);
+                    for (int i = 0; i < NF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(bl[h][i]), acc[fm][i]);
                 }
             } else {
 #pragma unroll
-                for (int i = 0; i < kMidNF; ++i) acc[fm][i] = mid_mfma<BF16>(operand(b[h][i]), af[f], acc[fm][i]);
+                for (int i = 0; i < NF; ++i) acc[fm][i] = mid_mfma<BF16>(operand(b[h][i]), af[f], acc[fm][i]);
             }
-            const int n0 = 4 * kMidNF * fm / MF, n1 = 4 * kMidNF * (fm + 1) / MF;
+            const int n0 = 4 * NF * fm / MF, n1 = 4 * NF * (fm + 1) / MF;
             if (h == 0) pairs(std::integral_constant<int, 2 * KQ + 1>{}, 1, r0, n0, n1, book);
             else if constexpr (KQ < 3) pairs(std::integral_constant<int, 2 * KQ + 2>{}, 0, r0, n0, n1, book);
             else if constexpr (SETS == 2) pairs(std::integral_constant<int, 0>{}, 0, r1, n0, n1, next);
             if constexpr (EXACT && SQ) {       // the group is complete: into the output
                 if (KQ % 2 == 1 && h == 1) {
 #pragma unroll
-                    for (int i = 0; i < kMidNF; ++i) {
+                    for (int i = 0; i < NF; ++i) {
                         const float s = f16_bits_to_f32((uint16_t)(szu[i] & 0xFFFFu)) * (BF16 ? 4096.0f : 1.0f), z8 = f16_bits_to_f32((uint16_t)(szu[i] >> 16)) + 8.0f;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) acc[fm][i][e] = fmaf(s, fmaf(-z8, X[fm][e], part[fm][i][e]), acc[fm][i][e]);
@@ -398,7 +401,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         for (int i = 0; i < AHEAD; ++i) copy(i, i);
         if constexpr (SETS == 2) {
             stage_book(r0, books);
-            pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * kMidNF, books);
+            pairs(std::integral_constant<int, 0>{}, 0, r0, 0, 4 * NF, books);
         }
     }
     // The waits in head() count the loads of the next tile's words, those of the last tile (never used) too.  The compiler may
@@ -421,7 +424,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
     mid_wait<0>();                             // no copy may still land in LDS below
 }
 
-template <bool BF16, int MF, int NW, bool EXACT>
+template <bool BF16, int MF, int NW, bool EXACT, int NF>
 __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     constexpr int KW = kMidWaves / NW;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -430,23 +433,23 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     const int mi = __builtin_popcountll(__builtin_amdgcn_ballot_w64(wg >= a.wg_end[threadIdx.x & 63]));
     const MidMat mt = a.m[mi];
     const int local = wg - (mi ? a.wg_end[mi - 1] : 0);
-    const int m0 = (local % a.m_tiles) * 16 * MF, n0 = (local / a.m_tiles) * (16 * kMidNF * NW);
+    const int m0 = (local % a.m_tiles) * 16 * MF, n0 = (local / a.m_tiles) * (16 * NF * NW);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = wave % NW, kg = wave / NW;
-    float4_t acc[MF][kMidNF];
+    float4_t acc[MF][NF];
 #pragma unroll
     for (int f = 0; f < MF; ++f)
 #pragma unroll
-        for (int i = 0; i < kMidNF; ++i) acc[f][i] = float4_t{0, 0, 0, 0};
+        for (int i = 0; i < NF; ++i) acc[f][i] = float4_t{0, 0, 0, 0};
     if (mt.fmt == FMT_SQ3) {
         const int KT = mt.K >> 8;
-        if (!EXACT && mid_small_zero((const uint2_t*)mt.aux + (size_t)(n0 >> 4) * KT * 16, kMidNF * NW * KT * 128, threadIdx.x, (uint32_t*)lds))
-            mid_loop<BF16, FMT_SQ3, true, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
-        else mid_loop<BF16, FMT_SQ3, false, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
+        if (!EXACT && mid_small_zero((const uint2_t*)mt.aux + (size_t)(n0 >> 4) * KT * 16, NF * NW * KT * 128, threadIdx.x, (uint32_t*)lds))
+            mid_loop<BF16, FMT_SQ3, true, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
+        else mid_loop<BF16, FMT_SQ3, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
     } else if (mt.fmt == FMT_VQ6) {
-        mid_loop<BF16, FMT_VQ6, false, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
+        mid_loop<BF16, FMT_VQ6, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
     } else {
-        mid_loop<BF16, FMT_VQ8, false, MF, NW, EXACT>(a, mt, lds, m0, n0, wave, lane, acc);
+        mid_loop<BF16, FMT_VQ8, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
     }
 
     // The K groups' partial sums meet in LDS, four rows of subtiles at a time; each group adds up and stores one of the rows
@@ -460,28 +463,28 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
 #pragma unroll
         for (int f = 0; f < PR && PR * ps + f < MF; ++f)
 #pragma unroll
-            for (int i = 0; i < kMidNF; ++i) *(float4_t*)(lds + ((wave * PR + f) * kMidNF + i) * 1024 + 16 * lane) = acc[PR * ps + f][i];
+            for (int i = 0; i < NF; ++i) *(float4_t*)(lds + ((wave * PR + f) * NF + i) * 1024 + 16 * lane) = acc[PR * ps + f][i];
         __syncthreads();
         const int f = kg / SH, m = m0 + 16 * (PR * ps + f) + (EXACT ? 4 * (lane >> 4) : lane & 15);
         if (PR * ps + f < MF && m < a.M) {
 #pragma unroll
-            for (int ii = 0; ii < kMidNF / SH; ++ii) {
-                const int i = ii + kMidNF / SH * (kg % SH);
-                float4_t v = *(const float4_t*)(lds + ((nw * PR + f) * kMidNF + i) * 1024 + 16 * lane);
+            for (int ii = 0; ii < NF / SH; ++ii) {
+                const int i = ii + NF / SH * (kg % SH);
+                float4_t v = *(const float4_t*)(lds + ((nw * PR + f) * NF + i) * 1024 + 16 * lane);
 #pragma unroll
                 for (int g = 1; g < KW; ++g) {
-                    const float4_t o = *(const float4_t*)(lds + (((g * NW + nw) * PR + f) * kMidNF + i) * 1024 + 16 * lane);
+                    const float4_t o = *(const float4_t*)(lds + (((g * NW + nw) * PR + f) * NF + i) * 1024 + 16 * lane);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] += o[e];
                 }
                 if constexpr (EXACT) {
-                    const int n = n0 + 16 * kMidNF * nw + 16 * i + (lane & 15);
+                    const int n = n0 + 16 * NF * nw + 16 * i + (lane & 15);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (n < mt.N && m + e < a.M) store_from_f32(mt.y, (size_t)(m + e) * mt.N + n, a.ydt, v[e]);
                     continue;
                 }
-                const size_t o = (size_t)m * mt.N + n0 + 16 * kMidNF * nw + 16 * i + 4 * (lane >> 4);
+                const size_t o = (size_t)m * mt.N + n0 + 16 * NF * nw + 16 * i + 4 * (lane >> 4);
                 if (a.ydt == DT_F32) {
                     *(float4_t*)((float*)mt.y + o) = v;
                 } else {
@@ -495,25 +498,26 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     }
 }
 
-template <bool BF16, int MF, int NW, bool EXACT>
+template <bool BF16, int MF, int NW, bool EXACT, int NF>
 static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
     static std::atomic<unsigned long long> raised{0ull};
-    const hipError_t e = raise_lds((const void*)mid_kernel<BF16, MF, NW, EXACT>, mid_lds(MF, NW, EXACT), raised);
+    const hipError_t e = raise_lds((const void*)mid_kernel<BF16, MF, NW, EXACT, NF>, mid_lds(MF, NW, EXACT), raised);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((mid_kernel<BF16, MF, NW, EXACT>), dim3(wgs), dim3(64 * kMidWaves), mid_lds(MF, NW, EXACT), s, a);
+    hipLaunchKernelGGL((mid_kernel<BF16, MF, NW, EXACT, NF>), dim3(wgs), dim3(64 * kMidWaves), mid_lds(MF, NW, EXACT), s, a);
     return hipGetLastError();
 }
 template <bool BF16>
-static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, bool exact, int wgs, hipStream_t s) {
+static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, int nf, bool exact, int wgs, hipStream_t s) {
     if (exact) {
-        if (mf == 2) return launch_mid_t<BF16, 2, 1, true>(a, wgs, s);
-        if (mf == 3) return launch_mid_t<BF16, 3, 1, true>(a, wgs, s);
-        return launch_mid_t<BF16, 4, 1, true>(a, wgs, s);
+        if (nf == 2) return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 2>(a, wgs, s)
+                            : mf == 3 ? launch_mid_t<BF16, 3, 1, true, 2>(a, wgs, s) : launch_mid_t<BF16, 4, 1, true, 2>(a, wgs, s);
+        return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 4>(a, wgs, s)
+               : mf == 3 ? launch_mid_t<BF16, 3, 1, true, 4>(a, wgs, s) : launch_mid_t<BF16, 4, 1, true, 4>(a, wgs, s);
     }
-    if (nw == 1) return launch_mid_t<BF16, 4, 1, false>(a, wgs, s);
-    if (mf == 4) return launch_mid_t<BF16, 4, 2, false>(a, wgs, s);
-    if (mf == 6) return launch_mid_t<BF16, 6, 2, false>(a, wgs, s);
-    return launch_mid_t<BF16, 8, 2, false>(a, wgs, s);
+    if (nw == 1) return launch_mid_t<BF16, 4, 1, false, 4>(a, wgs, s);
+    if (mf == 4) return launch_mid_t<BF16, 4, 2, false, 4>(a, wgs, s);
+    if (mf == 6) return launch_mid_t<BF16, 6, 2, false, 4>(a, wgs, s);
+    return launch_mid_t<BF16, 8, 2, false, 4>(a, wgs, s);
 }
 
 // Rows of x and of W per workgroup for a launch over `rows` rows of W.  One workgroup runs per compute unit; a round of
@@ -542,7 +546,7 @@ double mid_us(const MatDev* mats, int n_mats, int M) {
         int mf, nw;
         pick_mid(M, rows, &mf, &nw);
         LaunchLoad load;
-        for (int i = base; i < end; ++i) load.add((long long)(mats[i].N / (16 * kMidNF * nw)) * ((M + 16 * mf - 1) / (16 * mf)), mats[i].K);
+        for (int i = base; i < end; ++i) load.add((long long)(mats[i].N / (64 * nw)) * ((M + 16 * mf - 1) / (16 * mf)), mats[i].K);
         us += 3.0 + load.columns(0.5) * 1.12 * (36.0 + 8.6 * mf) / 56.0;
     }
     return us;
@@ -552,7 +556,7 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
     for (int base = 0; base < n_mats; base += kMidMaxMats) {
         MidArgs a;
         const int cnt = std::min(kMidMaxMats, n_mats - base);
-        int order[kMidMaxMats], mf, nw;
+        int order[kMidMaxMats], mf, nw, nf = 4;
         long long rows = 0;
         for (int i = 0; i < cnt; ++i) { order[i] = base + i; rows += mats[base + i].N; }
         std::stable_sort(order, order + cnt, [&](int p, int q) { return mats[p].K > mats[q].K; });   // long workgroups first
@@ -560,6 +564,9 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
             const int tiles = (M + 63) / 64;
             nw = 1;
             mf = std::max(2, ((M + tiles - 1) / tiles + 15) / 16);
+            long long narrow = 0;              // workgroups of 32 rows of W: up to one per compute unit they win
+            for (int i = 0; i < cnt; ++i) narrow += (long long)tiles * ((mats[base + i].N + 31) / 32);
+            if (narrow <= 256) nf = 2;
         }
         else pick_mid(M, rows, &mf, &nw);
         a.m_tiles = (M + 16 * mf - 1) / (16 * mf);
@@ -567,7 +574,7 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
         for (int i = 0; i < kMidMaxMats; ++i) {
             if (i < cnt) {
                 const MatDev& m = mats[order[i]];
-                wgs += a.m_tiles * ((m.N + 16 * kMidNF * nw - 1) / (16 * kMidNF * nw));
+                wgs += a.m_tiles * ((m.N + 16 * nf * nw - 1) / (16 * nf * nw));
                 a.m[i] = MidMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, 0};
                 a.wg_end[i] = wgs;
             } else {
@@ -576,7 +583,7 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
             }
         }
         a.M = M; a.ydt = y_dtype; a.pad = 0;
-        const hipError_t e = x_dtype == DT_BF16 ? launch_mid_shape<true>(a, mf, nw, exact, wgs, s) : launch_mid_shape<false>(a, mf, nw, exact, wgs, s);
+        const hipError_t e = x_dtype == DT_BF16 ? launch_mid_shape<true>(a, mf, nw, nf, exact, wgs, s) : launch_mid_shape<false>(a, mf, nw, nf, exact, wgs, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
