@@ -30,17 +30,23 @@ FORCE = {None: B.SMALL_BATCH_AUTO, "stream": B.SMALL_BATCH_STREAM, "mfma": B.SMA
 
 @pytest.fixture(params=["columns-split", "columns-split, table of first workgroups", "256-row-workgroups", "128-row-workgroups"])
 def stretches(request, options):
-    """Batch 2..32 on the streaming kernels has three forms, chosen by the size of the launch: one workgroup per 32
-    rows whose wavefronts split the columns and fetch their activation fragments themselves (small launches, batch
-    <= 16: RWKVQ_OPT_STREAM_SPLIT_MAX_WORK), workgroups of 128 rows that share a staged activation tile, and
-    workgroups of two such stretches (large launches: RWKVQ_OPT_STREAM_TWO_PASS_MIN_WGS).  The test shapes are small
-    launches, so each form is forced in turn.  The column-split form finds matrix and stretch in a two-dimensional grid
-    when the launch holds at most eight matrices, and in the table of first workgroups otherwise: both are forced."""
+    """Batch 2..32 on the streaming path has three forms, chosen by the size of the launch: small launches (RWKVQ_OPT_STREAM_SPLIT_MAX_WORK)
+    split the columns over the wavefronts of a workgroup - up to batch 16 one workgroup per 32 rows whose wavefronts fetch their
+    activation fragments themselves, beyond on the matrix-core kernels that split K - and the others take workgroups of
+    128 rows that share a staged activation tile, or of two such stretches (large launches:
+    RWKVQ_OPT_STREAM_TWO_PASS_MIN_WGS).  The test shapes are small launches, so each form is forced in turn.  The column split
+    of batch <= 16 finds matrix and stretch in a two-dimensional grid when the launch holds at most eight matrices, and in the
+    table of first workgroups otherwise: both are forced (beyond batch 16 there is one grid, and the second is skipped)."""
     form = request.param
     options(B.OPT_STREAM_SPLIT_MAX_WORK, 1000000 if form.startswith("columns-split") else 1)
     options(B.OPT_SPLIT_GRID_2D, 2 if form.endswith("table of first workgroups") else 1)
     options(B.OPT_STREAM_TWO_PASS_MIN_WGS, 1 if form == "256-row-workgroups" else 1000000)
     return form
+
+
+def skip_second_grid(M, stretches):
+    if M > 16 and stretches.endswith("table of first workgroups"):
+        pytest.skip("one grid form beyond 16 rows")
 
 
 SMALL = [("sq", 48, 768), ("sq", 256, 256), ("vq6", 256, 768), ("vq6", 512, 256), ("vq8", 256, 768),
@@ -105,8 +111,9 @@ def test_decode_batched_row_stretches(fmt, N, K, M, xdt, options, stretches):
     """Batch 2..32: a workgroup covers 256 rows of W as two stretches of 128 that share each staged activation
     tile.  Row counts that end inside the first stretch, inside the second, and one row tile into the next
     workgroup (SQ rows come in sixteens; VQ in blocks of 256, here three blocks).  M = 17 and 24 leave the second
-    group of sixteen batch rows of the 32-row instances partly filled.  The streaming kernels are
-    forced (left alone the dispatcher may send M > 16 to the matrix cores, which round the weights)."""
+    group of sixteen batch rows of the 32-row instances partly filled.  The streaming path is
+    forced (left alone the dispatcher may send M > 16 to the kernels that round the weights)."""
+    skip_second_grid(M, stretches)
     print(f"decode row stretches {fmt} N={N} K={K} M={M} x={xdt} two-pass threshold {stretches}", flush=True)
     options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
     mat = make(fmt, N, K, 12)
@@ -337,10 +344,9 @@ def test_prefill_both_tile_heights(fmt, xdt, N, K, M, options):
 @pytest.mark.parametrize("xdt", ["bf16", "f16"])
 @pytest.mark.parametrize("N,K,M", [(512, 2048, 17), (256, 4096, 40), (768, 1024, 128), (256, 512, 100)])
 def test_small_batch_both_paths(fmt, xdt, N, K, M, options):
-    """16 < M <= 128 runs either on the matrix cores (M padded to 128 rows) or as ceil(M / 32) passes
-    of the streaming kernels over row blocks of x (the 17..32-row instance, then one for the rest),
-    whichever the dispatcher estimates cheaper.  Both
-    are forced in turn; each against the oracle with the weights as that path feeds them (matrix
+    """16 < M <= 128 runs either with weights rounded on the matrix cores or on the streaming path, by the sizes of the call.  Both
+    are forced in turn, the second also as ceil(M / 32) passes of the streaming kernels over row blocks of x (the 17..32-row
+    instance, then one for the rest); each against the oracle with the weights as that path feeds them (matrix
     cores: rounded to the type of x; streaming: exact), and the free choice equals one of them."""
     mat = make(fmt, N, K, 9)
     x = acts(M, K, xdt, M + 2)
@@ -355,11 +361,16 @@ def test_small_batch_both_paths(fmt, xdt, N, K, M, options):
     options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_AUTO)
     free = G.gpu_gemm(dm, x, xdt)
     assert np.array_equal(free, ys["stream"]) or np.array_equal(free, ys["mfma"])
-    # fp16 output as well (the row blocks of y are addressed in its element size)
+    # the kernels that split K, then passes over row blocks of x and y; fp16 output as well (the blocks of y are addressed in
+    # its element size)
     options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
-    y16 = G.gpu_gemm(dm, x, xdt, B.F16)
-    back = orc.widen(y16, "f16").astype(np.float64)
-    assert np.abs(back - ys["stream"]).max() <= 2.0 ** -10 * np.abs(ys["stream"]).max()
+    exact = orc.linear(mat, orc.widen(x, xdt), "f64")
+    for never in (0, 1):
+        options(B.OPT_STREAM_SPLIT_MAX_WORK, never)
+        assert G.err_g2(G.gpu_gemm(dm, x, xdt), exact) <= 2e-5, never
+        y16 = G.gpu_gemm(dm, x, xdt, B.F16)
+        back = orc.widen(y16, "f16").astype(np.float64)
+        assert np.abs(back - ys["stream"]).max() <= 2.0 ** -10 * np.abs(ys["stream"]).max(), never
 
 
 def wide_range_rows(M, K, seed):
@@ -400,8 +411,9 @@ def test_bf16_activations_of_any_magnitude(fmt, M, options, stretches):
     """Every finite bf16 activation is in contract.  The streaming kernels multiply fp16 operands: they
     must bring the activations into fp16's range with exact scales, so that a row of tiny values, a
     row of huge ones and rows that mix both all come out as the oracle computes them - row by row,
-    since the rows of a batch are independent requests.  M = 48 runs both ways the dispatcher has
-    for it (two streaming passes; the matrix cores, which multiply bf16 directly)."""
+    since the rows of a batch are independent requests.  M = 48 runs every way the dispatcher has
+    for it (two streaming passes; the kernels that split K and those that round the weights, which multiply bf16 directly)."""
+    skip_second_grid(M, stretches)
     N, K = 512, 1024
     mat = make(fmt, N, K, 21)
     dm = B.upload(mat, native=True)
@@ -439,9 +451,8 @@ def test_bf16_activations_of_any_magnitude_grouped_batch1(fmt):
 
 @pytest.mark.parametrize("M", [17, 50, 128])
 def test_small_batch_rows_not_multiple_of_256(M):
-    """A native-layout matrix whose N is not a multiple of 256 has no matrix-core tiles; up to M = 128
-    it runs as passes of the streaming kernels (exact weights), together with ordinary matrices of
-    the same call."""
+    """A native-layout matrix whose N is not a multiple of 256 has no tiles of the kernels that round the weights; up to M = 128
+    it takes the streaming path (exact weights), together with ordinary matrices of the same call."""
     torch = G.torch_()
     mats = [make("sq", 48, 768, 11), make("vq6", 256, 768, 12), make("sq", 400, 512, 13)]
     xs = [acts(M, m.K, "bf16", M + i) for i, m in enumerate(mats)]
@@ -455,7 +466,7 @@ def test_small_batch_rows_not_multiple_of_256(M):
         exact = orc.linear(m, orc.widen(x, "bf16"), "f64")
         got = y.cpu().numpy().astype(np.float64)
         if m.N % 256:
-            assert G.err_g2(got, exact) <= 2e-5, i          # streaming passes: exact weights
+            assert G.err_g2(got, exact) <= 2e-5, i          # streaming path: exact weights
         elif G.err_g2(got, exact) > 2e-5:                   # the dispatcher chose the matrix cores for this one
             G.check_outputs(got, m, x, "bf16", fed="bf16")
 
@@ -464,7 +475,7 @@ def test_dispatch_randomized_batches_and_paths(options):
     """Seeded sweep over batch sizes 1..300, call compositions and the small-batch override: every
     output against the oracle with the weights as the reported path feeds them (rwkvq_linear_dispatch_plan:
     exact for the streaming kernels and the reference kernel, rounded to the type of x on the matrix
-    cores).  Catches row-block offsets, ragged last passes (M = 33: 32 rows + 1) and mixed calls."""
+    cores).  Catches row-block offsets, ragged last passes (M = 33: 32 rows + 1, in every other case) and mixed calls."""
     torch = G.torch_()
     rng = np.random.default_rng(4242)
     shapes = [(256, 512), (512, 256), (256, 1024), (768, 768), (48, 512), (1024, 256)]
@@ -481,6 +492,7 @@ def test_dispatch_randomized_batches_and_paths(options):
             mats.append(make(fmt, N, K, 100 + 7 * case + j))
         override = (None, "stream", "mfma")[int(rng.integers(0, 3))]
         options(B.OPT_SMALL_BATCH_PATH, FORCE[override])
+        options(B.OPT_STREAM_SPLIT_MAX_WORK, case // 2 % 2)          # 0: the default, 1: passes of the streaming kernels
         dms = [B.upload(m, native=True) for m in mats]
         descs = [d.desc() for d in dms]
         xs = [acts(M, m.K, xdt, 1000 + case * 10 + j) for j, m in enumerate(mats)]
