@@ -429,8 +429,8 @@ def sequential_step(dec, n_layers):
 
 
 def batched_decode(dec, stage_ordered=True):
-    """The decode stack at batches 4, 16 (streaming kernels, 2..16 rows), 32 (their 17..32-row instance) and
-    64 (two passes of it, or the matrix cores: whichever the dispatcher estimates cheaper)."""
+    """The decode stack at batches 4, 16 (streaming kernels, 2..16 rows), 32 and 64 (the whole stack in a
+    call: one and two passes of their 17..32-row instance)."""
     import torch
     from paper_2505_03803_amd import binding as B
     res = {}

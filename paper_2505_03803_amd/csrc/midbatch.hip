@@ -2,8 +2,8 @@
 // feed of prefill.hip (Deq(W) rounded once to the type of x, binary32 accumulate) in another cut.  prefill.hip gives a
 // workgroup 128 or 256 rows of x and 256 of W and all of K; with a few hundred rows of x a projection is then 16 to 48
 // workgroups on 256 compute units, each a chain of K / 64 steps.  Here
-//   * a workgroup of eight wavefronts takes 16 MF rows of x (MF = 4, 6, 8) and 64 NW rows of W (NW = 1, 2): a 4096 x 4096
-//     matrix at 333 rows is 192 workgroups (MF = 4, NW = 2);
+//   * a workgroup of eight wavefronts takes 16 MF rows of x (MF = 4, 6, 8) and 16 NF NW rows of W (NF = 4; NW = 1, 2): a 4096 x
+//     4096 matrix at 333 rows is 192 workgroups (MF = 4, NW = 2);
 //   * the wavefronts split K as well: KW = 8 / NW groups take the 256-column tiles kg, kg + KW, ..., so the chain is KW times
 //     shorter; their partial sums meet in LDS at the end, in group order;
 //   * W never goes through LDS: a lane's packed words hold exactly its operand of v_mfma_f32_16x16x32 (native layout), so
@@ -11,10 +11,12 @@
 //   * activations: copied global -> LDS by the load unit (chunk ^ (row & 7) swizzle as in prefill.hip) into a ring per
 //     K group, 2 to 4 tiles of 64 columns, shared by the group's NW wavefronts; one barrier per step (none for NW = 1);
 //   * formats share a launch (prefill.hip: one launch per format).
-// What bounds it: issue of vector instructions at few rows (the unpack costs the same for 64 rows as for 128: a step of
-// MF = 4 takes 1.2 us, of MF = 8 1.5 us, of which the MFMAs are 0.45 and 0.9), then the activation reads from the L2.
-// Measured (bf16, SQ and 6-bit VQ, us; prefill.hip -> here): 4096 x 4096 at M = 333 83 -> 26, at M = 1024 85 -> 40;
-// 4096 x 14336 at M = 333 266 -> 72, at M = 1024 265 -> 115; four 4096 x 4096 at M = 333 171 -> 64, at M = 1024 184 -> 145.
+// What bounds it: a wavefront's own chain.  Two wavefronts on a SIMD (registers, LDS) issue unpack, fragment reads and MFMAs in
+// order and wait 28 to 42 % of the time; no unit is full (counters at 333 rows: matrix cores 37 to 42 % busy, vector ALU a third
+// of the rate that two wavefronts sustain, LDS 15 to 50 %).  The unpack costs the same for 64 rows of x as for 128: a step of
+// MF = 4 takes 1.2 us, of MF = 8 1.5 us, of which the MFMAs are 0.45 and 0.9.
+// Measured (bf16, SQ and 6-bit VQ, us; prefill.hip -> here): 4096 x 4096 at M = 333 82 -> 27.5, at M = 1024 82 -> 40.5;
+// 4096 x 14336 at M = 333 265 -> 78, at M = 1024 269 -> 120; four 4096 x 4096 at M = 333 170 -> 66, at M = 1024 178 -> 140.
 // EXACT instances (17 <= M <= 128 where the streaming kernels' contract holds: weights unrounded, fp16 or bf16 x multiplied as it
 // is): NW = 1, 32 to 64 rows of x per workgroup, so a call that took ceil(M / 32) passes over W takes one (M <= 64).  SQ: codes as
 // 8 + q with the scale and zero point applied to the group's sums; VQ: the fp16 entries, for bf16 x as the sum of two bf16.

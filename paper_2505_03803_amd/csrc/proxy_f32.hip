@@ -3,8 +3,8 @@
 // the intervals between neighbours are normalised (Eqs. "interval", "interval_norm"), and the
 // entropy and the central moments of the normalised intervals give P_c and P_f (Eqs. "ie",
 // "coarse_proxy", "fine_proxy").  Sixteen-bit matrices take the shortcut of proxy.hip (the set of
-// occurring bit patterns); binary32 weights up to kSetMinCount are really sorted (larger
-// matrices: below, "partition and sets of values"):
+// occurring bit patterns); binary32 matrices of less than kSetMinCount weights are really
+// sorted (larger ones: below, "partition and sets of values"):
 //
 //   * keys: the order-preserving map of the binary32 patterns to unsigned integers;
 //   * least-significant-digit radix sort, four passes of 8 bits, each pass three steps:
@@ -298,9 +298,10 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
-// Bound: LDS (the partition's counters and reordering, the bitmaps' additions), not memory: 16 bytes per weight at 1.7 TB/s
-// for 14336 x 4096.  Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161,
-// 14336 x 4096 1957 -> 550 (count 63, plan 16, partition 239, sum 208, final 12); there with all weights equal 1570 -> 400,
+// Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 1.7 TB/s for 14336 x 4096.  The busiest
+// unit is the LDS (counters at 4096 x 4096: active 41 % in the partition, 28 % in the count, 24 % in the sums, half of it bank
+// conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.  Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161,
+// 14336 x 4096 1957 -> 550 (count 56, plan 15, partition 240, sum 214, final 12); there with all weights equal 1570 -> 400,
 // values of bfloat16 1783 -> 642, half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform
 // from -40 to 20) at 3 x 2^20 weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604
 // (the one kind found that is slower here).  Below kSetMinCount the sort.
