@@ -300,11 +300,12 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
 // Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 1.7 TB/s for 14336 x 4096.  The busiest
 // unit is the LDS (counters at 4096 x 4096: active 41 % in the partition, 28 % in the count, 24 % in the sums, half of it bank
-// conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.  Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161,
-// 14336 x 4096 1957 -> 550 (count 56, plan 15, partition 240, sum 214, final 12); there with all weights equal 1570 -> 400,
-// values of bfloat16 1783 -> 642, half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform
-// from -40 to 20) at 3 x 2^20 weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604
-// (the one kind found that is slower here).  Below kSetMinCount the sort.
+// conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.
+// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161, 14336 x 4096 1957 -> 550
+// (count 56, plan 15, partition 240, sum 214, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
+// half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20
+// weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604 (the one kind found that is slower
+// here).  Below kSetMinCount the sort.
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
 constexpr int kBins = 32768, kBinShift = 17;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
