@@ -112,10 +112,10 @@ const char* rwkvq_status_string(int status);
  *                                 (two stretches that share each staged activation tile) when the launch
  *                                 still has at least this many workgroups that way, and 128 rows otherwise
  *                                 (2048; 1 = always 256 rows, 1000000 = never)
- *   RWKVQ_OPT_STREAM_SPLIT_MAX_WORK    batch 2..16 on the streaming kernels: a launch takes the small-launch form (one
- *                                 workgroup per 32 rows of W, its wavefronts split the columns, every workgroup
- *                                 reads all of x) when (rows of all its matrices / 32) x (16 + M) is at most this
- *                                 (65536: one RWKV-6-7B layer at any M <= 16, two layers up to M = 8; 1 = never,
+ *   RWKVQ_OPT_STREAM_SPLIT_MAX_WORK    batch 2..16 on the streaming kernels: a launch takes the small-launch form (the
+ *                                 wavefronts of a workgroup split the columns, every workgroup reads all of x) where an
+ *                                 estimate of both durations says it is the faster one: one RWKV-6-7B layer at any M <= 16, two
+ *                                 to four by M and format.  The line moves in proportion to the option (65536; 1 = never,
  *                                 1000000 = always).  The streaming path at 17..128 has such a form too (kernels that split
  *                                 K on the matrix cores, weights exact as well): at 17..32 for launches of up to 1792
  *                                 workgroups of 64 rows of W (two such layers), a number that moves in proportion to the

@@ -32,11 +32,14 @@
 //     operand, y += s (acc - (8 + z) X); VQ pairs are LDS gathers.  A wavefront takes two row
 //     tiles of W, and with MT = 32 two groups of 16 batch rows: every unpacked weight operand
 //     feeds one MFMA per group.
+//   * decode_stage_kernel: batch 2..16 for launches too small to fill the device: the wavefronts of a workgroup split the
+//     columns, every one fetches its activations as operands and multiplies one to six row tiles by them.
 //   * bf16 activations are converted to fp16 on load, group by group under an exact power-of-two
 //     scale (see "bf16 activations" below), so their whole range is accepted.
 #include "common.h"
 #include "../../include/rwkvq.h"
 #include <algorithm>
+#include <cmath>
 
 namespace rwkvq {
 
@@ -362,17 +365,11 @@ __device__ __forceinline__ void x_store_wg(const XShared& r, half_t* xs, float* 
 template <class T>
 __device__ __forceinline__ T stream_load(const T* p) { return __builtin_nontemporal_load(p); }
 
-// Batch 2..16, small launches (decode_splitk_batched_kernel): a wavefront takes its A operands straight from global
-// memory in the layout the MFMA wants - lane (m, kg) = (lane % 16, lane / 16) holds, for column half u and k-step t of
-// a 256-column tile, the eight consecutive activations 128 u + 32 t + 8 kg ... of batch row m (rows beyond M repeat
-// row M - 1) - so nothing is staged in LDS and no workgroup barrier is needed: f[4 u + t].
+// Batch 2..16, small launches (decode_stage_kernel): a wavefront takes its A operands straight from global memory in the
+// layout the MFMA wants - lane (m, kg) = (lane % 16, lane / 16) holds, for column half u and k-step t of a 256-column tile, the
+// eight consecutive activations 128 u + 32 t + 8 kg ... of batch row m (rows beyond M repeat row M - 1) - so nothing is staged
+// in LDS and no workgroup barrier is needed: f[4 u + t].
 struct XFrags { uint4_t f[8]; };
-__device__ __forceinline__ void x_load_frags(XFrags& r, const uint16_t* x, int M, int K, int T, int lane, int g = 0) {
-    const int m = 16 * g + (lane & 15) < M ? 16 * g + (lane & 15) : M - 1;     // g: group of 16 batch rows
-    const uint16_t* p = x + (size_t)m * K + 256 * T + 8 * (lane >> 4);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r.f[i] = *(const uint4_t*)(p + 128 * (i >> 2) + 32 * (i & 3));
-}
 // bf16 fragments -> fp16, scaled by the power of two of the batch row's largest magnitude in this tile (the four lanes
 // that hold a row agree through two exchanges); lane m < 16 leaves the row's inverse scale in scw[m].
 __device__ __forceinline__ void x_frags_to_f16(XFrags& r, float* scw, int lane) {
@@ -518,9 +515,9 @@ __device__ __forceinline__ uint4_t vq6_gather4(uint32_t w0, uint32_t w1, uint32_
 
 // G = groups of 16 batch rows (1 for batch <= 16, 2 for batch 17..32)
 constexpr int groups_of(int MT) { return MT <= 16 ? 1 : MT / 16; }
-template <int G> struct SqRegs { uint4_t a[kBRT]; uint2_t b[kBRT]; uint2_t sz[kBRT]; XShared x[G]; XFrags xf[G]; };
-template <int G> struct Vq6Regs { uint4_t a[kBRT]; uint2_t b[kBRT]; uint32_t cb; XShared x[G]; XFrags xf[G]; };
-template <int G> struct Vq8Regs { uint4_t a[kBRT]; uint4_t b[kBRT]; uint4_t cb; XShared x[G]; XFrags xf[G]; };
+template <int G> struct SqRegs { uint4_t a[kBRT]; uint2_t b[kBRT]; uint2_t sz[kBRT]; XShared x[G]; };
+template <int G> struct Vq6Regs { uint4_t a[kBRT]; uint2_t b[kBRT]; uint32_t cb; XShared x[G]; };
+template <int G> struct Vq8Regs { uint4_t a[kBRT]; uint4_t b[kBRT]; uint4_t cb; XShared x[G]; };
 
 // Everything a tile loop needs about its wavefront's position; R[i] are its row tiles (R[i] == R[0]
 // for the tiles past the end of the matrix: worked on again, not stored).
@@ -544,7 +541,7 @@ struct WavePos {
 // SQ: the codes enter as 8 + q (one shift and one and-or per pair).  The group sums of the
 // activations come from the matrix cores too: one more MFMA per k-step with an all-ones B operand
 // leaves X_g[m] in the accumulator layout of the products, and y += s (acc - (8 + z) X_g).
-template <int MT, int DEPTH, bool XB, int P, bool DIRECT = false>
+template <int MT, int DEPTH, bool XB, int P>
 __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, half_t* xs, float* xsc,
                                        float4_t (&out)[P][groups_of(MT)][kBRT]) {
     constexpr int G = groups_of(MT), UB = (G == 1 && RWKVQ_BATCH_UB2) ? 2 : 1;   // one group: the fragments of both column halves up front
@@ -570,10 +567,8 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
     asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
     const uint4_t ones4 = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
     const half8_t ones = __builtin_bit_cast(half8_t, ones4);
-    static_assert(!DIRECT || P == 1, "fragments from global memory: one row pass");
     auto load = [&](Regs& r, int T, auto pass) {
         constexpr int J = decltype(pass)::value;
-        if constexpr (DIRECT) T = wp.t0 + T * wp.ts;     // this wavefront's column tiles
 #pragma unroll
         for (int rt = 0; rt < kBRT; ++rt) {
             const uint32_t* t = codes[J][rt] + (size_t)T * 384;
@@ -581,10 +576,7 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
             r.b[rt] = stream_load((const uint2_t*)(t + 256 + 2 * lane));
             r.sz[rt] = stream_load(sz[J][rt] + (size_t)T * 16 + (lane & 15));
         }
-        if constexpr (DIRECT) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) x_load_frags(r.xf[g], (const uint16_t*)mt.x, M, mt.K, T, lane, g);
-        } else if constexpr (J == 0) {
+        if constexpr (J == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) x_load_wg(r.x[g], (const uint16_t*)mt.x, M, mt.K, T, wp.tid, g);
         }
@@ -593,15 +585,7 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
         constexpr int J = decltype(pass)::value;
         half_t* buf = xs + (T & 1) * (MT * kXStride);
         float* scb = xsc + (T & 1) * (16 * G);
-        XFrags xf[G];
-        if constexpr (DIRECT) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                xf[g] = r.xf[g];
-                if (XB) x_frags_to_f16(xf[g], scb + 16 * g, lane);
-            }
-            if (XB) wave_lds_sync();
-        } else if constexpr (J == 0) {
+        if constexpr (J == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) x_store_wg<MT>(r.x[g], buf, scb, wp.tid, XB, g);
             __syncthreads();
@@ -618,7 +602,7 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
                 for (int g = 0; g < G; ++g)
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
-                        xa[uu][g][t] = DIRECT ? __builtin_bit_cast(half8_t, xf[g].f[4 * (ub + uu) + t]) : *(const half8_t*)(buf + xoff[g] + 128 * (ub + uu) + 32 * t);
+                        xa[uu][g][t] = *(const half8_t*)(buf + xoff[g] + 128 * (ub + uu) + 32 * t);
 #pragma unroll
             for (int uu = 0; uu < UB; ++uu) {
                 const int u = ub + uu;
@@ -652,12 +636,12 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
             }
         }
     };
-    batched_pipeline<DEPTH, P, Regs>(DIRECT ? wp.nt : KT, load, compute);
+    batched_pipeline<DEPTH, P, Regs>(KT, load, compute);
 }
 
 // 6-bit VQ: the codebook of a tile (64 entries, one per lane) goes through a wavefront-private LDS
 // slot and every weight pair is one ds_read_b32 gather (cheaper on this part than ds_bpermute).
-template <int MT, int DEPTH, bool XB, int P, bool DIRECT = false>
+template <int MT, int DEPTH, bool XB, int P>
 __device__ __forceinline__ void run_vq6(const DecodeMat& mt, const WavePos& wp, half_t* xs, float* xsc, uint32_t* cb_lds,
                                         float4_t (&out)[P][groups_of(MT)][kBRT]) {
     constexpr int G = groups_of(MT), UB = (G == 1 && RWKVQ_BATCH_UB2) ? 2 : 1;
@@ -675,21 +659,15 @@ __device__ __forceinline__ void run_vq6(const DecodeMat& mt, const WavePos& wp, 
     const uint32_t base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
     uint32_t m;
     asm("v_mov_b32 %0, 0xfc" : "=v"(m));
-    static_assert(!DIRECT || P == 1, "fragments from global memory: one row pass");
     auto load = [&](Regs& r, int T, auto pass) {
         constexpr int J = decltype(pass)::value;
-        if constexpr (DIRECT) T = wp.t0 + T * wp.ts;     // this wavefront's column tiles
 #pragma unroll
         for (int rt = 0; rt < kBRT; ++rt) {
             const uint32_t* t = codes[J][rt] + (size_t)T * 384;
             r.a[rt] = stream_load((const uint4_t*)(t + 4 * lane));
             r.b[rt] = stream_load((const uint2_t*)(t + 256 + 2 * lane));
         }
-        if constexpr (DIRECT) {
-            r.cb = (cbs + (size_t)T * 64)[lane];
-#pragma unroll
-            for (int g = 0; g < G; ++g) x_load_frags(r.xf[g], (const uint16_t*)mt.x, M, mt.K, T, lane, g);
-        } else if constexpr (J == 0) {
+        if constexpr (J == 0) {
             r.cb = (cbs + (size_t)T * 64)[lane];
 #pragma unroll
             for (int g = 0; g < G; ++g) x_load_wg(r.x[g], (const uint16_t*)mt.x, M, mt.K, T, wp.tid, g);
@@ -699,16 +677,7 @@ __device__ __forceinline__ void run_vq6(const DecodeMat& mt, const WavePos& wp, 
         constexpr int J = decltype(pass)::value;
         half_t* buf = xs + (T & 1) * (MT * kXStride);
         float* scb = xsc + (T & 1) * (16 * G);
-        XFrags xf[G];
-        if constexpr (DIRECT) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                xf[g] = r.xf[g];
-                if (XB) x_frags_to_f16(xf[g], scb + 16 * g, lane);
-            }
-            cb_lds[(T & 1) * 256 + lane] = r.cb;
-            wave_lds_sync();
-        } else if constexpr (J == 0) {
+        if constexpr (J == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) x_store_wg<MT>(r.x[g], buf, scb, wp.tid, XB, g);
             cb_lds[(T & 1) * 256 + lane] = r.cb;     // two slots, 1 KB apart (the gather address ORs the index in)
@@ -733,7 +702,7 @@ __device__ __forceinline__ void run_vq6(const DecodeMat& mt, const WavePos& wp, 
                 for (int g = 0; g < G; ++g)
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
-                        xa[uu][g][t] = DIRECT ? __builtin_bit_cast(half8_t, xf[g].f[4 * (ub + uu) + t]) : *(const half8_t*)(buf + xoff[g] + 128 * (ub + uu) + 32 * t);
+                        xa[uu][g][t] = *(const half8_t*)(buf + xoff[g] + 128 * (ub + uu) + 32 * t);
 #pragma unroll
             for (int uu = 0; uu < UB; ++uu) {
                 const int u = ub + uu;
@@ -766,12 +735,12 @@ __device__ __forceinline__ void run_vq6(const DecodeMat& mt, const WavePos& wp, 
             }
         }
     };
-    batched_pipeline<DEPTH, P, Regs>(DIRECT ? wp.nt : KT, load, compute);
+    batched_pipeline<DEPTH, P, Regs>(KT, load, compute);
 }
 
 // 8-bit VQ: the codebook of a tile (256 entries) goes through a wavefront-private LDS region; the
 // workgroup barrier that publishes the activations also orders that store before the gathers.
-template <int MT, int DEPTH, bool XB, int P, bool DIRECT = false>
+template <int MT, int DEPTH, bool XB, int P>
 __device__ __forceinline__ void run_vq8(const DecodeMat& mt, const WavePos& wp, half_t* xs, float* xsc, uint32_t* cb_lds,
                                         float4_t (&out)[P][groups_of(MT)][kBRT]) {
     constexpr int G = groups_of(MT);
@@ -786,21 +755,15 @@ __device__ __forceinline__ void run_vq8(const DecodeMat& mt, const WavePos& wp, 
     int xoff[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) xoff[g] = (16 * g + (lane & 15) < M ? 16 * g + (lane & 15) : M - 1) * kXStride + 8 * (lane >> 4);
-    static_assert(!DIRECT || P == 1, "fragments from global memory: one row pass");
     auto load = [&](Regs& r, int T, auto pass) {
         constexpr int J = decltype(pass)::value;
-        if constexpr (DIRECT) T = wp.t0 + T * wp.ts;     // this wavefront's column tiles
 #pragma unroll
         for (int rt = 0; rt < kBRT; ++rt) {
             const uint32_t* t = codes[J][rt] + (size_t)T * 512;
             r.a[rt] = stream_load((const uint4_t*)(t + 4 * lane));
             r.b[rt] = stream_load((const uint4_t*)(t + 256 + 4 * lane));
         }
-        if constexpr (DIRECT) {
-            r.cb = (cbs + (size_t)T * 64)[lane];
-#pragma unroll
-            for (int g = 0; g < G; ++g) x_load_frags(r.xf[g], (const uint16_t*)mt.x, M, mt.K, T, lane, g);
-        } else if constexpr (J == 0) {
+        if constexpr (J == 0) {
             r.cb = (cbs + (size_t)T * 64)[lane];
 #pragma unroll
             for (int g = 0; g < G; ++g) x_load_wg(r.x[g], (const uint16_t*)mt.x, M, mt.K, T, wp.tid, g);
@@ -811,16 +774,7 @@ __device__ __forceinline__ void run_vq8(const DecodeMat& mt, const WavePos& wp, 
         half_t* buf = xs + (T & 1) * (MT * kXStride);
         float* scb = xsc + (T & 1) * (16 * G);
         uint32_t* cbuf = cb_lds + (T & 1) * 256;     // two codebook slots, like the activations
-        XFrags xf[G];
-        if constexpr (DIRECT) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                xf[g] = r.xf[g];
-                if (XB) x_frags_to_f16(xf[g], scb + 16 * g, lane);
-            }
-            *(uint4_t*)(cbuf + 4 * lane) = r.cb;
-            wave_lds_sync();
-        } else if constexpr (J == 0) {
+        if constexpr (J == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) x_store_wg<MT>(r.x[g], buf, scb, wp.tid, XB, g);
             *(uint4_t*)(cbuf + 4 * lane) = r.cb;
@@ -841,7 +795,7 @@ __device__ __forceinline__ void run_vq8(const DecodeMat& mt, const WavePos& wp, 
             for (int g = 0; g < G; ++g)
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    xa[g][t] = DIRECT ? __builtin_bit_cast(half8_t, xf[g].f[4 * u + t]) : *(const half8_t*)(buf + xoff[g] + 128 * u + 32 * t);
+                    xa[g][t] = *(const half8_t*)(buf + xoff[g] + 128 * u + 32 * t);
 #pragma unroll
             for (int rt = 0; rt < kBRT; ++rt) {
                 const uint4_t w = u == 0 ? r.a[rt] : r.b[rt];
@@ -867,7 +821,7 @@ __device__ __forceinline__ void run_vq8(const DecodeMat& mt, const WavePos& wp, 
             }
         }
     };
-    batched_pipeline<DEPTH, P, Regs>(DIRECT ? wp.nt : KT, load, compute);
+    batched_pipeline<DEPTH, P, Regs>(KT, load, compute);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1203,18 +1157,18 @@ __device__ __forceinline__ void run_m1(const DecodeMat& mt, const WavePos& wp, u
         else run_vq8_m1<DEPTH, SPLIT, MIXED, false>(mt, wp, cb_lds, part);
     }
 }
-// The same for batch 2..32.  DIRECT: the split-K form (activation fragments from global memory, see XFrags).
-template <int MT, int DEPTH, int P, bool DIRECT = false>
+// The same for batch 2..32.
+template <int MT, int DEPTH, int P>
 __device__ __forceinline__ void run_batched(const DecodeMat& mt, const WavePos& wp, half_t* xs, float* xsc, uint32_t* cb_lds,
                                             float4_t (&out)[P][groups_of(MT)][kBRT]) {
     if (wp.xbf16) {
-        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, true, P, DIRECT>(mt, wp, xs, xsc, out);
-        else if (mt.fmt == FMT_VQ6) run_vq6<MT, DEPTH, true, P, DIRECT>(mt, wp, xs, xsc, cb_lds, out);
-        else run_vq8<MT, DEPTH, true, P, DIRECT>(mt, wp, xs, xsc, cb_lds, out);
+        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, true, P>(mt, wp, xs, xsc, out);
+        else if (mt.fmt == FMT_VQ6) run_vq6<MT, DEPTH, true, P>(mt, wp, xs, xsc, cb_lds, out);
+        else run_vq8<MT, DEPTH, true, P>(mt, wp, xs, xsc, cb_lds, out);
     } else {
-        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, false, P, DIRECT>(mt, wp, xs, xsc, out);
-        else if (mt.fmt == FMT_VQ6) run_vq6<MT, DEPTH, false, P, DIRECT>(mt, wp, xs, xsc, cb_lds, out);
-        else run_vq8<MT, DEPTH, false, P, DIRECT>(mt, wp, xs, xsc, cb_lds, out);
+        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, false, P>(mt, wp, xs, xsc, out);
+        else if (mt.fmt == FMT_VQ6) run_vq6<MT, DEPTH, false, P>(mt, wp, xs, xsc, cb_lds, out);
+        else run_vq8<MT, DEPTH, false, P>(mt, wp, xs, xsc, cb_lds, out);
     }
 }
 
@@ -1382,81 +1336,237 @@ __global__ void __launch_bounds__(64 * S) decode_splitk_kernel(Args a) {
     }
 }
 
-// Batch 2..16 when a launch holds too few rows to fill the device with the kernel above (a single projection, the
-// matrices of one stage of a block): one workgroup per 32 rows of W (two 16-row tiles, which share every activation
-// fragment), its S wavefronts take the column tiles s, s + S, ...; each fetches its activation fragments itself
-// (from the L2: every workgroup reads all of x, which is why this form is for small launches only), nothing is
-// staged for the workgroup and no barrier sits in the tile loop; the partial sums meet in LDS in a fixed order.
-template <int MT, int S, bool GRID2D>
-__global__ void __launch_bounds__(64 * S, 1) decode_splitk_batched_kernel(DecodeArgs a) {
-    static_assert(MT == 16, "one group of sixteen batch rows");
-    constexpr int G = groups_of(MT);
-    __shared__ __attribute__((aligned(1024))) uint32_t cb_all[S][512];
-    __shared__ __attribute__((aligned(16))) float xsc[S][2 * 16 * G];
-    __shared__ __attribute__((aligned(16))) float red[S][G][kBRT][256];
-    // matrix and stretch of rows: from a two-dimensional grid (launches of at most kGrid2DMaxMats matrices, see
-    // decode_splitk_kernel) or from the table of first workgroups
-    int mi = 0, stretch;
-    if constexpr (GRID2D) {
+// ---- batch 2..16, small launches ------------------------------------------------------------
+// What a row tile of a column tile is read into.
+struct StageRegs {
+    uint4_t a, b;                      // packed words; SQ: b = two words, scale and zero of both groups; VQ-6: b.z = codebook entry
+    uint4_t cb;                        // VQ-8: four codebook entries
+};
+// Row tiles in flight.  The sets rotate with the row tiles of one column tile, or of two (MULTI).
+constexpr int stage_sets(int R, bool multi) { return R == 6 ? 3 : multi && R == 1 ? 2 : R; }
+
+template <int FMT, int R, bool MULTI, bool XB>
+struct StageTiles {
+    static constexpr int D = stage_sets(R, MULTI);
+    static constexpr bool kOneBlock = 16 % R == 0;   // the row tiles share a codebook block
+    static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
+    const DecodeMat& mt;
+    int R0, NR, KT, lane, xoff;
+    float* xsc;
+    uint32_t* cb_lds;
+    uint32_t mask, magic, m6, base0;
+    StageRegs w[D];
+    XFrags xf[MULTI ? 2 : 1];
+
+    __device__ __forceinline__ StageTiles(const DecodeMat& mt_, int R0_, int M, int lane_, float* xsc_, uint32_t* cb_)
+        : mt(mt_), R0(R0_), NR(mt_.N >> 4), KT(mt_.K >> 8), lane(lane_), xsc(xsc_), cb_lds(cb_) {
+        xoff = ((lane & 15) < M ? lane & 15 : M - 1) * mt.K + 8 * (lane >> 4);
+        asm("v_mov_b32 %0, 0x03800380" : "=v"(mask));                        // (see run_sq, run_vq6)
+        asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
+        asm("v_mov_b32 %0, 0xfc" : "=v"(m6));
+        base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
+    }
+    // A column tile's activation fragments (see XFrags), a row tile's weights: together and in order (see tile_pipeline).  Past the
+    // end (live = false) every lane asks for lane 0's bytes of a tile that was read already.
+    __device__ __forceinline__ void load_x(XFrags& r, int T, bool live) {
+        const uint16_t* p = (const uint16_t*)mt.x + 256 * T;
+        const uint32_t at = live ? (uint32_t)xoff : 0u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r.f[i] = *(const uint4_t*)(p + at + 128 * (i >> 2) + 32 * (i & 3));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void load_w(StageRegs& r, int T, int rt, bool live) {
+        const int row = R0 + rt < NR ? R0 + rt : NR - 1;                     // past the last row tile: that one again, not stored
+        const uint32_t l = live ? (uint32_t)lane : 0u;
+        const uint32_t* t = mt.codes + ((size_t)row * KT + T) * kWords;
+        r.a = stream_load((const uint4_t*)t + l);
+        if constexpr (FMT == FMT_VQ8) {
+            r.b = stream_load((const uint4_t*)(t + 256) + l);
+            if (!kOneBlock || rt == 0) r.cb = ((const uint4_t*)mt.aux + ((size_t)(row >> 4) * KT + T) * 64)[l];
+        } else {
+            const uint2_t two = stream_load((const uint2_t*)(t + 256) + l);
+            r.b.x = two.x; r.b.y = two.y;
+            if constexpr (FMT == FMT_SQ3) {
+                const uint2_t sz = stream_load((const uint2_t*)mt.aux + ((size_t)row * KT + T) * 16 + (l & 15u));
+                r.b.z = sz.x; r.b.w = sz.y;
+            } else if (!kOneBlock || rt == 0) {
+                r.b.z = ((const uint32_t*)mt.aux + ((size_t)(row >> 4) * KT + T) * 64)[l];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void multiply(const StageRegs& r, const XFrags& x, int rt, const float4_t& sc, const float4_t (&X)[2], float4_t& out) {
+        const uint32_t slot = (uint32_t)(kOneBlock ? 0 : rt & 1);
+        const uint32_t* cbuf = cb_lds + 256 * slot;
+        if constexpr (FMT != FMT_SQ3) {
+            if (!kOneBlock || rt == 0) {
+                if constexpr (FMT == FMT_VQ8) *(uint4_t*)(cb_lds + 256 * slot + 4 * lane) = r.cb;
+                else cb_lds[256 * slot + lane] = r.b.z;
+                wave_lds_sync();
+            }
+        }
+        float4_t part = {0, 0, 0, 0};
+        float4_t& acc = *(XB ? &part : &out);                                // VQ: as in run_vq6
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            half8_t op[4];
+            if constexpr (FMT == FMT_VQ8) {
+                const uint4_t q = u == 0 ? r.a : r.b;
+                op[0] = vq8_operand(q.x, cbuf); op[1] = vq8_operand(q.y, cbuf); op[2] = vq8_operand(q.z, cbuf); op[3] = vq8_operand(q.w, cbuf);
+            } else {
+                const uint32_t w0 = u == 0 ? r.a.x : r.a.w, w1 = u == 0 ? r.a.y : r.b.x, w2 = u == 0 ? r.a.z : r.b.y;
+                if constexpr (FMT == FMT_SQ3) {
+                    op[0] = sq_operand<0>(w0, w1, w2, mask, magic); op[1] = sq_operand<1>(w0, w1, w2, mask, magic);
+                    op[2] = sq_operand<2>(w0, w1, w2, mask, magic); op[3] = sq_operand<3>(w0, w1, w2, mask, magic);
+                } else {
+                    const uint32_t base = base0 + 1024 * slot;
+                    op[0] = __builtin_bit_cast(half8_t, vq6_gather4<0>(w0, w1, w2, m6, base));
+                    op[1] = __builtin_bit_cast(half8_t, vq6_gather4<1>(w0, w1, w2, m6, base));
+                    op[2] = __builtin_bit_cast(half8_t, vq6_gather4<2>(w0, w1, w2, m6, base));
+                    op[3] = __builtin_bit_cast(half8_t, vq6_gather4<3>(w0, w1, w2, m6, base));
+                }
+            }
+            if constexpr (FMT == FMT_SQ3) {
+                const uint32_t szw = u == 0 ? r.b.z : r.b.w;
+                const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu));
+                const float z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
+                float4_t sum = {0, 0, 0, 0};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sum = RWKVQ_MFMA(__builtin_bit_cast(half8_t, x.f[4 * u + t]), op[t], sum);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) out[i] = fmaf(XB ? s * sc[i] : s, fmaf(-z8, X[u][i], sum[i]), out[i]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc = RWKVQ_MFMA(__builtin_bit_cast(half8_t, x.f[4 * u + t]), op[t], acc);
+            }
+        }
+        if (FMT != FMT_SQ3 && XB)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[i] = fmaf(part[i], sc[i], out[i]);
+    }
+    // Column tile T, whose fragments are in xf[J]; the weights of the row tiles D further on and the fragments of the column
+    // tile after next are asked for as the registers become free.
+    template <int J>
+    __device__ __forceinline__ void column(int T, int S, int last, float4_t (&out)[R]) {
+        XFrags& x = xf[J];
+        float4_t sc = {1, 1, 1, 1};
+        if (XB) {
+            x_frags_to_f16(x, xsc, lane);
+            wave_lds_sync();
+            sc = *(const float4_t*)(xsc + 4 * (lane >> 4));
+        }
+        // group sums of the activations, for all row tiles
+        const uint4_t ones4 = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+        float4_t X[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+        if constexpr (FMT == FMT_SQ3) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) X[i >> 2] = RWKVQ_MFMA(__builtin_bit_cast(half8_t, x.f[i]), __builtin_bit_cast(half8_t, ones4), X[i >> 2]);
+        }
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt) {
+            StageRegs& r = w[(J * R + rt) % D];
+            multiply(r, x, rt, sc, X, out[rt]);
+            if (MULTI && rt + 1 == R) load_x(x, T + 2 * S <= last ? T + 2 * S : last, T + 2 * S <= last);
+            constexpr int ahead = D;
+            const int turn = (rt + ahead) / R, to = (rt + ahead) % R;         // the row tile this set serves next
+            if (turn == 0) load_w(r, T, to, true);
+            else if (MULTI) load_w(r, T + turn * S <= last ? T + turn * S : last, to, T + turn * S <= last);
+        }
+    }
+    // y[m][16 row tiles] over the column tiles t0, t0 + S, .. (nt of them; one if not MULTI), added to out.
+    __device__ __forceinline__ void run(int t0, int S, int nt, float4_t (&out)[R]) {
+        const int last = t0 + (nt - 1) * S;
+        __builtin_amdgcn_sched_barrier(0);
+        load_x(xf[0], t0, true);
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            if (MULTI && i == R) load_x(xf[MULTI], nt > 1 ? t0 + S : t0, nt > 1);
+            if (i < R) load_w(w[i], t0, i, true);
+            else load_w(w[i], nt > 1 ? t0 + S : t0, i - R, nt > 1);
+        }
+        if (MULTI && D <= R) load_x(xf[MULTI], nt > 1 ? t0 + S : t0, nt > 1);
+        if constexpr (!MULTI) column<0>(t0, S, last, out);
+        else
+#pragma unroll 1
+            for (int T = t0; T <= last; T += 2 * S) {
+                column<0>(T, S, last, out);
+                if (T + S <= last) column<1>(T + S, S, last, out);
+            }
+    }
+};
+
+// Batch 2..16 when a launch holds too few rows to fill the device with the kernel above (a single projection, the matrices of one
+// stage of a block): a workgroup takes R row tiles of one matrix, its S wavefronts the column tiles s, s + S, ..., and the partial
+// sums meet in LDS in a fixed order.  A wavefront fetches the activations of a column tile once, straight into the operand layout
+// of the MFMA, and they serve R row tiles; nothing is staged for the workgroup, no barrier sits in the loop.
+// What bounds it: start-up (about 4.5 us of a launch that moves nothing), then x: a compute unit reads all of x (131 KB at M = 16,
+// K = 4096) in pieces of 64 bytes per batch row, half of a cache line at a time (whole lines, timing only: o 6.5 -> 5.5 us, v'
+// 19.3 -> 15.3; it would need a transpose through LDS).  With 16 wavefronts of one column tile each every byte of a workgroup is
+// asked for at its start.  Measured (7B shapes, fp16, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
+// wavefronts (what this replaces) -> here: {r, k, v, g} 10.5 / 14.3 -> 8.1 / 9.9, o 5.9 / 8.7 -> 4.8 / 6.5, {k', r'} 13.6 / 19.4
+// -> 9.4 / 11.3, v' 13.3 / 21.4 -> 12.6 / 19.3.
+// most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight
+constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; }
+template <int MATS> struct StageArgs {
+    static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
+    int wg_end[kGrid2D ? 1 : MATS];
+    DecodeMat m[MATS];
+    int M, xdt, ydt, S;
+};
+template <int R, bool MULTI, class Args>
+__global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kernel(Args a) {
+    extern __shared__ __attribute__((aligned(1024))) uint32_t stage_lds[];        // per wavefront: two codebook slots, later its R sums
+    __shared__ __attribute__((aligned(16))) float xsc[16][16];
+    int mi = 0, group;
+    if constexpr (Args::kGrid2D) {
         mi = blockIdx.y;
-        stretch = blockIdx.x;
+        group = blockIdx.x;
     } else {
         const int wg = blockIdx.x;
 #pragma unroll
         for (int j = 0; j < kMaxGroupMats; j += 64)
             mi += __builtin_popcountll(__builtin_amdgcn_ballot_w64(wg >= a.wg_end[j + (threadIdx.x & 63)]));
-        stretch = wg - (mi ? a.wg_end[mi - 1] : 0);                // here wg_end counts stretches of kBRT row tiles
+        group = wg - (mi ? a.wg_end[mi - 1] : 0);
     }
-    const int M = a.M, xdt = a.xdt, ydt = a.ydt;                   // the end of the argument block: asked for with the descriptor
+    const int M = a.M, xdt = a.xdt, ydt = a.ydt, S = a.S;          // the end of the argument block: asked for with the descriptor
     const DecodeMat mt = a.m[mi];
-    asm volatile("" :: "s"(M), "s"(xdt), "s"(ydt), "s"(mt.N));
-    if (GRID2D && stretch >= (mt.N + 16 * kBRT - 1) / (16 * kBRT)) return;
+    asm volatile("" :: "s"(M), "s"(xdt), "s"(ydt), "s"(S), "s"(mt.N));
+    const int R0 = R * group;
+    if (Args::kGrid2D && 16 * R0 >= mt.N) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int KT = mt.K >> 8, NR = mt.N >> 4;
-    WavePos wp;
-    wp.R[0] = kBRT * stretch;
+    const int KT = mt.K >> 8;
+    constexpr int kOwn = R > 2 ? 256 * R : 512;                    // words of LDS per wavefront
+    uint32_t* mine = stage_lds + kOwn * wave;
+    float4_t out[R];
 #pragma unroll
-    for (int rt = 1; rt < 4; ++rt) wp.R[rt] = (rt < kBRT && wp.R[0] + rt < NR) ? wp.R[0] + rt : wp.R[0];
-#pragma unroll
-    for (int rt = 0; rt < 4; ++rt) wp.Rn[rt] = wp.R[0];
-    wp.M = M; wp.lane = lane; wp.tid = threadIdx.x; wp.xbf16 = xdt == DT_BF16;
-    wp.t0 = wave; wp.ts = S; wp.nt = wave < KT ? (KT - wave + S - 1) / S : 0;
-    float4_t out[1][G][kBRT];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int rt = 0; rt < kBRT; ++rt) out[0][g][rt] = float4_t{0, 0, 0, 0};
-    if (wp.nt > 0) run_batched<MT, 1, 1, true>(mt, wp, nullptr, xsc[wave], cb_all[wave], out);
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int rt = 0; rt < kBRT; ++rt) *(float4_t*)&red[wave][g][rt][4 * lane] = out[0][g][rt];
-    __syncthreads();
-    // D layout of the MFMA: lane (n, mg) holds batch rows 4 mg .. 4 mg + 3 (of its group) of output column n;
-    // wavefront rt sums row tile rt
-    static_assert(kBRT <= 2, "the wavefront that sums row tile rt is picked with a select, not an index");
-    const int Rw = wave == 0 ? wp.R[0] : wp.R[1];
-    if (wave < kBRT && (wave == 0 || Rw != wp.R[0])) {
-        const int n = 16 * Rw + (lane & 15);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float4_t t = *(const float4_t*)&red[0][g][wave & 1][4 * lane];
-#pragma unroll
-            for (int s = 1; s < S; ++s) {
-                const float4_t v = *(const float4_t*)&red[s][g][wave & 1][4 * lane];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] += v[i];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = 16 * g + 4 * (lane >> 4) + i;
-                if (m < M) store_from_f32(mt.y, (size_t)m * mt.N + n, ydt, t[i]);
-            }
+    for (int rt = 0; rt < R; ++rt) out[rt] = float4_t{0, 0, 0, 0};
+    if (wave < KT) {
+        const int nt = (KT - wave + S - 1) / S;
+        if (xdt == DT_BF16) {
+            if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        } else {
+            if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else StageTiles<FMT_VQ8, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
         }
     }
+    wave_lds_sync();                                               // (the codebook slots are read)
+#pragma unroll
+    for (int rt = 0; rt < R; ++rt) *(float4_t*)(mine + 256 * rt + 4 * lane) = out[rt];
+    __syncthreads();
+    // D layout of the MFMA: lane (n, mg) holds batch rows 4 mg .. 4 mg + 3 of output column n
+    const float* sums = (const float*)stage_lds;
+    for (int i = threadIdx.x; i < 16 * R * M; i += 64 * S) {
+        const int m = i / (16 * R), n = i - 16 * R * m;
+        const int at = 256 * (n >> 4) + 4 * (16 * (m >> 2) + (n & 15)) + (m & 3);
+        float t = sums[at];
+        for (int s = 1; s < S; ++s) t += sums[kOwn * s + at];
+        if (16 * R0 + n < mt.N) store_from_f32(mt.y, (size_t)m * mt.N + 16 * R0 + n, ydt, t);
+    }
 }
-
 
 // Time mixing's r, k, v and the wkv step in one launch.  The recurrence is per channel, and channel c
 // needs r[c], k[c], v[c]: output row c of three matrices.  A workgroup of 12 wavefronts takes row tile R
@@ -1622,6 +1732,87 @@ hipError_t launch_decode_postmix(const MatDev* mats, const PostDev* posts, const
     return hipSuccess;
 }
 
+// Batch 2..16: is the column split (decode_stage_kernel) the faster of the two?  Both durations in us, fitted to launches of 1 to 32
+// layers of widths 1024 to 5120 in each format (none of 250 took the slower one by more than 12 %): the column split takes its time per tile of 16 x 256 weights and per row tile;
+// decode_kernel takes the longer of one wavefront's way through the longest row and the launch's share of the memory rate.
+// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK moves the line in proportion (1: never split, 1000000: always).
+static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype) {
+    const int max_work = option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK);
+    if (max_work <= 1 || max_work >= 1000000) return max_work > 1;
+    const bool bf16 = x_dtype == DT_BF16;
+    double split = 0.0, rows = 0.0, chain = 0.0;
+    long long stretches = 0;
+    for (int i = 0; i < n_mats; ++i) {
+        const MatDev& m = mats[order[i]];
+        const double row_tiles = m.N / 16, tiles = row_tiles * (m.K / 256);
+        const int f = m.fmt == FMT_SQ3 ? 0 : m.fmt == FMT_VQ6 ? 1 : 2;
+        static const double kSplit[3] = {1.0, 1.0, 1.15}, kRows[3] = {1.0, 1.1, 1.45}, kChain[3] = {0.73, 0.93, 1.15};
+        split += (0.26e-3 * tiles + 1.3e-3 * row_tiles) * kSplit[f];
+        rows += 0.353e-3 * tiles * kRows[f];
+        chain = std::max(chain, (m.K / 256) * (kChain[f] + (bf16 ? 0.2 : 0.0)));
+        stretches += (m.N + 31) / 32;
+    }
+    // stacks beyond the fitted range: every workgroup's own read of x grows with them, half a stack of 14B-class shapes at M = 16 in
+    // bf16 takes 937 us in columns and 752 in rows
+    if (stretches * (16 + M) > 2LL * max_work) return false;
+    split = 8.0 + split * (1.0 + 0.028 * (M - 2)) * (bf16 ? 1.2 - 0.009 * (M - 2) : 1.0);
+    rows *= (1.0 + 0.008 * M) * (bf16 ? 1.05 : 1.0);
+    return split * kStreamSplitMaxWork <= (3.0 + std::pow(std::pow(chain, 6.0) + std::pow(rows, 6.0), 1.0 / 6.0)) * max_work;
+}
+
+template <int R, bool MULTI, class Args>
+static hipError_t launch_stage_kernel(const Args& a, dim3 grid, hipStream_t s) {
+    const int lds = a.S * (R > 2 ? R : 2) * 1024;
+    if (lds > 60 * 1024) {
+        static std::atomic<unsigned long long> raised{0ull};
+        const hipError_t e = raise_lds((const void*)decode_stage_kernel<R, MULTI, Args>, 16 * R * 1024, raised);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((decode_stage_kernel<R, MULTI, Args>), grid, dim3(64 * a.S), lds, s, a);
+    return hipGetLastError();
+}
+// Row tiles R and wavefronts S of a workgroup.  One workgroup per compute unit is best where the launch allows it: the fewest row
+// tiles that make at most 256 workgroups, as many wavefronts as share the columns evenly (of up to sixteen).  Launches of more than
+// 6 x 256 row tiles run in several rounds, which overlap when several small workgroups share a compute unit: four row tiles, four
+// wavefronts.  Measured (7B shapes, fp16, cold weights, us; one round / four wavefronts): {r, k, v, g} at M = 16 9.9 / 11.6,
+// {k', r'} 11.3 / 17.2, v' 19.3 / 24.6; a whole layer, 33.9 / 28.6 at M = 2 and 38.4 / 37.8 at M = 16.
+template <int MATS>
+static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+    StageArgs<MATS> a;
+    int columns = 0, wgs = 0, longest = 0, R = 4;
+    bool one_round = false;
+    for (int i = 0; i < MATS; ++i) {
+        a.m[i] = DecodeMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, POST_NONE, nullptr};
+        if (i >= n_mats) continue;
+        const MatDev& m = mats[order[i]];
+        a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, POST_NONE, nullptr};
+        columns = std::max(columns, m.K >> 8);
+    }
+    auto workgroups = [&](int r) { int n = 0; for (int i = 0; i < n_mats; ++i) n += (mats[order[i]].N + 16 * r - 1) / (16 * r); return n; };
+    if constexpr (StageArgs<MATS>::kGrid2D)
+        for (int r = 1; r <= 6 && !one_round; ++r)
+            if (workgroups(r) <= 256) { one_round = true; R = r; }
+    const int most = one_round ? stage_waves(columns > stage_waves(false, R), R) : 4, turns = (columns + most - 1) / most;
+    a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = (columns + turns - 1) / turns;
+    for (int i = 0; i < n_mats; ++i) {
+        const int n = (mats[order[i]].N + 16 * R - 1) / (16 * R);
+        wgs += n; longest = std::max(longest, n);
+        if constexpr (!StageArgs<MATS>::kGrid2D) a.wg_end[i] = wgs;
+    }
+    if constexpr (!StageArgs<MATS>::kGrid2D) {
+        for (int i = n_mats; i < MATS; ++i) a.wg_end[i] = 0x7FFFFFFF;
+        return launch_stage_kernel<4, true>(a, dim3(wgs), s);
+    } else {
+        const dim3 grid(longest, n_mats);
+#define RWKVQ_STAGE(R_) case R_: return turns > 1 ? launch_stage_kernel<R_, true>(a, grid, s) : launch_stage_kernel<R_, false>(a, grid, s);
+        switch (R) {
+            RWKVQ_STAGE(1) RWKVQ_STAGE(2) RWKVQ_STAGE(3) RWKVQ_STAGE(4) RWKVQ_STAGE(5) RWKVQ_STAGE(6)
+            default: return hipErrorInvalidValue;
+        }
+#undef RWKVQ_STAGE
+    }
+}
+
 hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s,
                          const PostDev* posts) {
     for (int base = 0; base < n_mats; base += kMaxGroupMats) {
@@ -1640,35 +1831,12 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         for (int i = 0; i < cnt; ++i) tiles += (mats[order[i]].N + 15) / 16;
         int split = 0;
         if (M == 1 && tiles < kSplitTarget) split = pick_split(tiles);
-        // batch 2..16 with few rows in the launch: one workgroup per 32 rows, S wavefronts over its column tiles
+        // batch 2..16 with few rows in the launch: the wavefronts of a workgroup split the columns
         if (M > 1 && M <= 16) {
-            long long stretches = 0;
-            for (int i = 0; i < cnt; ++i) stretches += (mats[order[i]].N + 16 * kBRT - 1) / (16 * kBRT);
-            // measured on the RWKV-6-7B shapes: the form wins up to about 2000 stretches at batch 16 and 3500 at batch <= 8
-            // (what it pays is every workgroup's own read of x, which grows with the batch)
-            if (stretches * (16 + M) <= option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK)) {
-                const int S = stretches * 8 >= kSplitTarget ? 4 : 8;      // sixteen wavefronts would leave 128 registers each
-                int wgs = 0;
-                for (int i = 0; i < cnt; ++i) {
-                    const MatDev& m = mats[order[i]];
-                    wgs += (m.N + 16 * kBRT - 1) / (16 * kBRT);
-                    a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, POST_NONE, nullptr};
-                    a.wg_end[i] = wgs;
-                }
-                for (int i = cnt; i < kMaxGroupMats; ++i) {
-                    a.m[i] = DecodeMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, POST_NONE, nullptr};
-                    a.wg_end[i] = 0x7FFFFFFF;
-                }
-                a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.pad = 0;
-                if (cnt <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1) {
-                    int longest = 0;
-                    for (int i = 0; i < cnt; ++i) longest = std::max(longest, a.wg_end[i] - (i ? a.wg_end[i - 1] : 0));
-                    const dim3 grid(longest, cnt);
-                    if (S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 4, true>), grid, dim3(256), 0, s, a);
-                    else hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 8, true>), grid, dim3(512), 0, s, a);
-                } else if (S == 4) hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 4, false>), dim3(wgs), dim3(256), 0, s, a);
-                else hipLaunchKernelGGL((decode_splitk_batched_kernel<16, 8, false>), dim3(wgs), dim3(512), 0, s, a);
-                hipError_t e = hipGetLastError();
+            if (stage_cheaper(mats, order, cnt, M, x_dtype)) {
+                const hipError_t e = cnt <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1
+                                         ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, s)
+                                         : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, s);
                 if (e != hipSuccess) return e;
                 continue;
             }

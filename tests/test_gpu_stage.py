@@ -1,0 +1,37 @@
+"""The column split of batch 2..16 (small launches): every number of row tiles per workgroup, row tiles past the end of W, one and
+several column tiles per wavefront, matrices of different K and format in a launch, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import rwkvq_oracle as orc
+from paper_2505_03803_amd import binding as B
+from paper_2505_03803_amd import synth
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+# R: the fewest row tiles per workgroup that make at most 256 workgroups; 7: none of 1..6 does.  16 and 17 column tiles: the most that
+# wavefronts take one each, and the fewest that they take in turns (9 wavefronts, two each but the last); 25: three turns of nine.
+@pytest.mark.parametrize("R,columns", [(1, 1), (1, 16), (1, 17), (1, 25), (2, 16), (2, 17), (3, 5), (3, 17), (4, 1), (4, 17), (5, 3), (5, 17),
+                                       (6, 2), (6, 17), (7, 1), (7, 9)])
+@pytest.mark.parametrize("M,xdt", [(3, "bf16"), (16, "f16")])
+def test_column_split(R, columns, M, xdt, options):
+    print(f"column split R={R} columns={columns} M={M} x={xdt}", flush=True)
+    options(B.OPT_STREAM_SPLIT_MAX_WORK, 1000000)
+    torch, rng = G.torch_(), np.random.default_rng(R)
+    rows = 3 if R == 1 else 256 * (R - 1) + 1 - 32       # row tiles of the scalar-quantized matrix; the others have 16 each
+    K = 256 * columns
+    few = K if R < 3 or columns == 1 else 256 * max(1, columns // 3)   # another K in the same launch
+    mats = [synth.gen_sq(rng, 16 * rows, few if M == 3 else K), synth.gen_vq(rng, 256, K, 6), synth.gen_vq(rng, 256, few, 8)]
+    xs = [synth.gen_activations(rng, M, m.K, xdt) for m in mats]
+    dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
+    ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
+    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    for m, x, y in zip(mats, xs, ys):
+        got = y.cpu().numpy().astype(np.float64)
+        assert (got[M] == 7.0).all()                      # nothing behind the last row
+        # up to 6400 products in binary32 partial sums: about sqrt(K) 2^-24 of the row's norms
+        assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
