@@ -12,6 +12,8 @@
 // the same decisions.
 #include "common.h"
 
+#include <algorithm>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -161,6 +163,110 @@ __global__ void __launch_bounds__(256) clip_mean_select_kernel(const void* __res
     }
 }
 
+// clip_mean_ends_kernel<NS> (32 < B <= 32 NS): the same where both percentiles are within a few samples of the ends (k_lo + 2 and
+// B - k_hi at most kClipEnds): the distinct values are taken from either end, a minimum and a count over the position's 32 lanes per
+// step, instead of a count per bit.  A minimum above m without a compare: keys up to m wrap to the top in key - (m + 1).
+// What bounds it: start-up (2.5 us of a launch that moves nothing), the trips to memory, and the chain of B binary64 additions.
+// 4096 positions x 128 bf16 samples 8.5 -> 4.9 us, 5120 x 256 15.3 -> 10.5, 2560 x 64 5.7 -> 4.1.  The line: a step costs about as much
+// as two bits of the other way, which has 16 of them for 16-bit samples.
+constexpr int kClipEnds = 6, kClipLanes = 32, kClipThreads = kClipLanes * kClipP;
+__device__ __forceinline__ uint32_t lanes32_min(uint32_t v) {
+    v = row_min(v);
+    const auto both = __builtin_amdgcn_permlane16_swap(v, v, false, false);      // the pair's even row twice, its odd row twice
+    return min((uint32_t)both[0], (uint32_t)both[1]);
+}
+__device__ __forceinline__ int lanes32_sum(int v) {
+    v = row_sum(v);
+    const auto both = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    return (int)both[0] + (int)both[1];
+}
+// The values of ranks k and k + 1 (k + 1 < B, or ignored) among the position's keys, the least first.
+template <int NS>
+__device__ __forceinline__ void lowest(const uint32_t (&key)[NS], int k, int steps, uint32_t& at_k, uint32_t& at_k1) {
+    uint32_t m = 0xFFFFFFFFu;                        // the value taken last
+    int before = 0;                                  // keys up to it
+    for (int s = 0; s < steps; ++s) {
+        uint32_t d[NS], least = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) { d[i] = key[i] - (m + 1u); least = min(least, d[i]); }
+        least = lanes32_min(least);
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) c += d[i] == least ? 1 : 0;
+        c = lanes32_sum(c);
+        m += least + 1u;
+        if (before <= k) at_k = m;
+        if (before <= k + 1) at_k1 = m;
+        before += c;
+    }
+}
+template <int NS>
+__global__ void __launch_bounds__(kClipThreads) clip_mean_ends_kernel(const void* __restrict__ x, int dt, int B, int n, int k_lo, double f_lo,
+                                                                      int k_hi, double f_hi, float* __restrict__ out) {
+    extern __shared__ uint32_t tile[];               // as in clip_mean_select_kernel
+    const int tid = threadIdx.x;
+    // The 32 or 64 bytes that a workgroup reads of a sample are a part of a cache line: neighbours go to one XCD, whose L2 then
+    // fetches the line once (workgroups are dealt to the eight XCDs in turn).
+    const int per_xcd = gridDim.x >> 3, blk = (gridDim.x & 7) ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    const int j0 = blk * kClipP;
+    {
+        const int p = tid % kClipP, j = min(j0 + p, n - 1), b0 = tid / kClipP;
+        uint32_t v[NS];
+        if (dt == DT_F32) {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) v[i] = ((const uint32_t*)x)[(size_t)min(b0 + kClipLanes * i, B - 1) * n + j];
+        } else {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) v[i] = ((const uint16_t*)x)[(size_t)min(b0 + kClipLanes * i, B - 1) * n + j];
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int b = b0 + kClipLanes * i;
+            if (b < B) tile[clip_at(b, p)] = dt == DT_F32 ? v[i] : v[i] << 16;
+        }
+    }
+    __syncthreads();
+    const int p = tid / kClipLanes, l = tid % kClipLanes;
+    uint32_t bits[NS], low[NS], high[NS];            // ranks from below and from above; not a sample: above every one
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int b = l + kClipLanes * i;
+        bits[i] = tile[clip_at(min(b, B - 1), p)];
+        const uint32_t k = (bits[i] & 0x80000000u) ? ~bits[i] & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u) : bits[i] | 0x80000000u;
+        low[i] = b < B ? k : 0xFFFFFFFFu;
+        high[i] = b < B ? ~k : 0xFFFFFFFFu;
+    }
+    auto value = [&](uint32_t k) {
+        const uint32_t v = (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u);
+        return dt == DT_F32 ? __uint_as_float(v) : dt == DT_BF16 ? __uint_as_float(v) : f16_bits_to_f32((uint16_t)(v >> 16));
+    };
+    uint32_t lo = 0u, lo1 = 0u, hi = 0u, hi1 = 0u;
+    const int from_top = B - 1 - k_hi;               // rank of the k_hi-th from above; the next one up is rank from_top - 1
+    lowest<NS>(low, k_lo, k_lo + 2, lo, lo1);
+    lowest<NS>(high, from_top - 1, from_top + 1, hi1, hi);
+    if (k_lo + 1 >= B) lo1 = lo;
+    if (from_top == 0) hi1 = hi;
+    const double f_v = (double)value(lo), f_w = (double)value(~hi);
+    const double dlo = __dadd_rn(f_v, __dmul_rn(f_lo, __dsub_rn((double)value(lo1), f_v)));
+    const double dhi = __dadd_rn(f_w, __dmul_rn(f_hi, __dsub_rn((double)value(~hi1), f_w)));
+    double* const limited = (double*)(tile + B * kClipP);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int b = l + kClipLanes * i;
+        double v = (double)(dt == DT_F16 ? f16_bits_to_f32((uint16_t)(bits[i] >> 16)) : __uint_as_float(bits[i]));
+        v = v < dlo ? dlo : v;
+        v = v > dhi ? dhi : v;
+        if (b < B) limited[clip_at(b, p)] = v;
+    }
+    __syncthreads();
+    if (tid < kClipP && j0 + tid < n) {
+        double acc = 0.0;
+#pragma unroll 32
+        for (int b = 0; b < B; ++b) acc = __dadd_rn(acc, limited[clip_at(b, tid)]);
+        out[j0 + tid] = (float)(acc / (double)B);
+    }
+}
+
 // One thread per position, samples re-read from memory: any batch size.
 __global__ void __launch_bounds__(256) clip_mean_kernel(const void* __restrict__ x, int dt, int B, int n, int k_lo,
                                                         double f_lo, int k_hi, double f_hi, float* __restrict__ out) {
@@ -198,7 +304,12 @@ hipError_t launch_clip_mean(const void* x, int dt, int B, int n, int k_lo, doubl
     // a tile of B x 16 words, and up to B = 256 as many doubles (beyond, two limits per position)
     const dim3 grid((n + kClipP - 1) / kClipP), wg(256);
     const size_t lds = (size_t)B * kClipP * 4 + (B <= 256 ? (size_t)B * kClipP * 8 : 2 * kClipP * 8);
-    if (B <= 16) hipLaunchKernelGGL(clip_mean_select_kernel<1>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    if (B > 2 * kClipP && B <= 256 && k_lo + 2 <= kClipEnds && B - k_hi <= kClipEnds) {
+        const dim3 wide(kClipThreads);
+        if (B <= 64) hipLaunchKernelGGL(clip_mean_ends_kernel<2>, grid, wide, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+        else if (B <= 128) hipLaunchKernelGGL(clip_mean_ends_kernel<4>, grid, wide, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+        else hipLaunchKernelGGL(clip_mean_ends_kernel<8>, grid, wide, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
+    } else if (B <= 16) hipLaunchKernelGGL(clip_mean_select_kernel<1>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     else if (B <= 32) hipLaunchKernelGGL(clip_mean_select_kernel<2>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     else if (B <= 64) hipLaunchKernelGGL(clip_mean_select_kernel<4>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
     else if (B <= 128) hipLaunchKernelGGL(clip_mean_select_kernel<8>, grid, wg, lds, s, x, dt, B, n, k_lo, f_lo, k_hi, f_hi, out);
@@ -244,7 +355,10 @@ __device__ __forceinline__ uint16_t f64_to_f16_bits(double d) {
 // per share counts rounds of 64 with ballots over the entry's bits, a running sum over the entries gives their first slots.
 // A thread then adds only its entry's vectors; scanning the whole share for them (what this replaces) was most of the time:
 // 28 tensors of 4096 weights, 64 entries, 10 iterations 290 -> 131 us (6 iterations with every vector at one entry 183 -> 143;
-// one vector's look-ups after the other there: 198).
+// one vector's look-ups after the other there: 198).  Up to 4096 vectors stay in LDS over the iterations, and a thread compares both of
+// its vectors with an entry that it has read (131 -> 107, 256 entries 395 -> 331).
+// What bounds it: vector ALU of the one compute unit a tensor has, 5.6 of 9.7 us per iteration in the ten instructions per
+// vector and entry, near the rate that four wavefronts per SIMD retire.
 __device__ __forceinline__ unsigned long long same_entry_lanes(uint32_t e, int bits, bool valid) {
     unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
     for (int b = 0; b < bits; ++b) {
@@ -254,15 +368,16 @@ __device__ __forceinline__ unsigned long long same_entry_lanes(uint32_t e, int b
     }
     return m;
 }
+constexpr int kMuChunk = 2048, kMuHeld = 4096;        // vectors of a chunk; most vectors that stay in LDS over the iterations
 template <int E>
-__global__ void __launch_bounds__(1024) mu_kmeans_kernel(MuArgs a) {
+__global__ void __launch_bounds__(1024) mu_kmeans_kernel(MuArgs a, int hold) {
     constexpr int S = 1024 / (2 * E);                 // threads per (entry, coordinate) = shares of a chunk
-    constexpr int kChunk = 2048, kPer = kChunk / S;   // vectors per chunk and per share
-    constexpr int kBits = E == 64 ? 6 : 8;
+    constexpr int kChunk = kMuChunk, kPer = kChunk / S;   // vectors per chunk and per share
+    constexpr int kBits = E == 64 ? 6 : 8, kH = kChunk / 1024;
     static_assert(S <= 16 && kPer % 64 == 0, "a wavefront per share, rounds of 64 vectors");
-    __shared__ float cb[E][2];
+    extern __shared__ float4_t held[];                // the weight's two elements and their two squared activations, per vector
+    __shared__ __attribute__((aligned(16))) float cb[E][2];
     __shared__ uint16_t s_idx[kChunk], s_at[kChunk];  // entry of a vector; vectors of a share in order of their entries
-    __shared__ float s_m[kChunk][2], s_w[kChunk][2];
     __shared__ uint32_t first[S][E];                  // a share's first slot of an entry; while counting: vectors seen
     __shared__ uint32_t count[S][E];
     __shared__ double num[2 * E][S], den[2 * E][S];
@@ -279,26 +394,46 @@ __global__ void __launch_bounds__(1024) mu_kmeans_kernel(MuArgs a) {
         double sn = 0.0, sd = 0.0;
         for (int c0 = 0; c0 < V; c0 += kChunk) {
             const int in_chunk = V - c0 < kChunk ? V - c0 : kChunk;
+            float4_t* const chunk = held + (hold ? c0 : 0);
+            if (it == 0 || !hold) {
+                if (!hold && it + c0 > 0) __syncthreads();
 #pragma unroll
-            for (int h = 0; h < kChunk / 1024; ++h) {
-                const int vl = h * 1024 + tid, v = c0 + vl;
-                if (v < V) {
-                    const float m0 = load_as_f32(t.mu, 2 * (size_t)v, a.dt), m1 = load_as_f32(t.mu, 2 * (size_t)v + 1, a.dt);
+                for (int h = 0; h < kH; ++h) {
+                    const int vl = h * 1024 + tid, v = min(c0 + vl, V - 1);
                     const float x0 = t.xbar[2 * (size_t)v], x1 = t.xbar[2 * (size_t)v + 1];
-                    const float w0 = __fmul_rn(x0, x0), w1 = __fmul_rn(x1, x1);
-                    int best = 0;
-                    float bestc = __builtin_inff();
-#pragma unroll 4
-                    for (int e = 0; e < E; ++e) {
-                        const float t0 = __fsub_rn(m0, cb[e][0]), t1 = __fsub_rn(m1, cb[e][1]);
-                        const float c = __fadd_rn(__fmul_rn(w0, __fmul_rn(t0, t0)), __fmul_rn(w1, __fmul_rn(t1, t1)));
-                        if (c < bestc) { bestc = c; best = e; }
-                    }
-                    if (last) t.idx[v] = (uint8_t)best;
-                    s_idx[vl] = (uint16_t)best;
-                    s_m[vl][0] = m0; s_m[vl][1] = m1; s_w[vl][0] = w0; s_w[vl][1] = w1;
+                    chunk[vl] = float4_t{load_as_f32(t.mu, 2 * (size_t)v, a.dt), load_as_f32(t.mu, 2 * (size_t)v + 1, a.dt),
+                                         __fmul_rn(x0, x0), __fmul_rn(x1, x1)};
                 }
             }
+            auto assign = [&](auto count) {           // a thread's own vectors, the entries read once for all of them
+                constexpr int H = decltype(count)::value;
+                float4_t v[H];
+                int best[H];
+                float bestc[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) { v[h] = chunk[h * 1024 + tid]; best[h] = 0; bestc[h] = __builtin_inff(); }
+#pragma unroll 4
+                for (int e = 0; e < E; e += 2) {
+                    const float4_t two = *(const float4_t*)&cb[e][0];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int h = 0; h < H; ++h) {
+                            const float t0 = __fsub_rn(v[h].x, k ? two.z : two.x), t1 = __fsub_rn(v[h].y, k ? two.w : two.y);
+                            const float c = __fadd_rn(__fmul_rn(v[h].z, __fmul_rn(t0, t0)), __fmul_rn(v[h].w, __fmul_rn(t1, t1)));
+                            if (c < bestc[h]) { bestc[h] = c; best[h] = e + k; }
+                        }
+                }
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const int vl = h * 1024 + tid;
+                    if (vl >= in_chunk) continue;
+                    if (last) t.idx[c0 + vl] = (uint8_t)best[h];
+                    else s_idx[vl] = (uint16_t)best[h];
+                }
+            };
+            if (1024 + 64 * wave < in_chunk) assign(std::integral_constant<int, kH>{});
+            else if (64 * wave < in_chunk) assign(std::integral_constant<int, 1>{});
             if (last) continue;                       // the final pass only assigns
             if (tid < S * E) (&count[0][0])[tid] = 0u;
             __syncthreads();
@@ -347,8 +482,9 @@ __global__ void __launch_bounds__(1024) mu_kmeans_kernel(MuArgs a) {
 #pragma unroll 8
                 for (uint32_t i = 0; i < cnt; ++i) {  // eight vectors' look-ups at a time: an entry may hold a whole share
                     const int vl = s_at[at + i];
-                    const double w = (double)s_w[vl][c];
-                    sn += w * (double)s_m[vl][c];    // the product of two binary32 values is exact in binary64
+                    const float* vec = (const float*)&chunk[vl];
+                    const double w = (double)vec[2 + c];
+                    sn += w * (double)vec[c];    // the product of two binary32 values is exact in binary64
                     sd += w;
                 }
             }
@@ -380,9 +516,15 @@ hipError_t launch_mu_codebook(const void* const* mus, const float* const* xbars,
             a.t[i] = MuTensor{mus[k], xbars[k], (uint16_t*)cbs[k], idx[k], n_elems[k], 0};
         }
         a.dt = dt; a.kbits = kbits; a.iters = iters; a.pad = 0;
-        if (kbits == 6) hipLaunchKernelGGL(mu_kmeans_kernel<64>, dim3(cnt), dim3(1024), 0, s, a);
-        else hipLaunchKernelGGL(mu_kmeans_kernel<256>, dim3(cnt), dim3(1024), 0, s, a);
-        hipError_t e = hipGetLastError();
+        int most = 0;
+        for (int i = 0; i < cnt; ++i) most = std::max(most, n_elems[base + i] / 2);
+        const int hold = most <= kMuHeld, chunks = hold ? (most + kMuChunk - 1) / kMuChunk : 1, lds = chunks * kMuChunk * 16;
+        static std::atomic<unsigned long long> raised[2];
+        hipError_t e = raise_lds(kbits == 6 ? (const void*)mu_kmeans_kernel<64> : (const void*)mu_kmeans_kernel<256>, kMuHeld * 16, raised[kbits == 6]);
+        if (e != hipSuccess) return e;
+        if (kbits == 6) hipLaunchKernelGGL(mu_kmeans_kernel<64>, dim3(cnt), dim3(1024), lds, s, a, hold);
+        else hipLaunchKernelGGL(mu_kmeans_kernel<256>, dim3(cnt), dim3(1024), lds, s, a, hold);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

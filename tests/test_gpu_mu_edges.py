@@ -44,6 +44,42 @@ def test_clip_mean_instances(Bn, dt):
         assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), p
 
 
+# 33 to 256 samples: percentiles on both sides of the line between the selection from the ends (ranks up to 4 and from B - 6 on) and
+# the one by bits, at which the rank is whole and the interpolation weight zero, and with more positions than a multiple of eight
+# workgroups; ties that end the selection early, and signed infinities as extremes
+@pytest.mark.parametrize("Bn,n", [(33, 16), (64, 130), (101, 300), (128, 33), (200, 128), (256, 77)])
+@pytest.mark.parametrize("dt", ["bf16", "f16", "f32"])
+def test_clip_mean_from_the_ends(Bn, n, dt):
+    torch, rng = G.torch_(), np.random.default_rng(Bn)
+    x = synth.gen_calibration(rng, Bn, n, dt)
+    x[:, 5] = x[rng.integers(0, 3, Bn), 5]
+    x[1:, 6] = x[1, 6]
+    x[3, 7], x[9, 7] = (np.inf, -np.inf) if dt == "f32" else {"bf16": (0x7F80, 0xFF80), "f16": (0x7C00, 0xFC00)}[dt]
+    out = torch.empty(n, dtype=torch.float32, device="cuda")
+    for rank in (0.0, 1.0, 3.5, 4.0, 4.99, 5.0, 6.0):
+        p = 100.0 * rank / (Bn - 1)
+        B.rwkvq_clip_mean(dev(x), B.DTYPES[dt], Bn, n, p, out)
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            want = MO.clip_mean(x if dt == "f32" else orc.widen(x, dt), p)
+        known = ~np.isnan(want)                               # (infinities minus themselves: the definition gives no number)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32)[known], want.view(np.uint32)[known]), p
+
+
+# vectors that stay in LDS over the iterations (up to 4096, in chunks of 2048) and those that are read again
+@pytest.mark.parametrize("n", [2, 2046, 2050, 4094, 6000, 8192, 8194])
+@pytest.mark.parametrize("kbits", [6, 8])
+def test_codebook_sizes(n, kbits):
+    torch, rng = G.torch_(), np.random.default_rng(n)
+    mu, xbar, cb = synth.gen_mu(rng, n, "bf16"), rng.standard_normal(n).astype(np.float32), synth.gen_codebook(rng, 1 << kbits)
+    book, idx = dev(cb.copy()), torch.empty(n // 2, dtype=torch.uint8, device="cuda")
+    B.rwkvq_mu_codebook([dev(mu)], [dev(xbar)], [n], B.BF16, kbits, 3, [book], [idx])
+    torch.cuda.synchronize()
+    want, want_idx, _ = MO.mu_codebook(orc.widen(mu, "bf16"), xbar, orc.widen(cb, "f16"), 3)
+    assert np.array_equal(orc.widen(book.cpu().numpy().view(np.uint16), "f16"), want)
+    assert np.array_equal(idx.cpu().numpy(), want_idx)
+
+
 def test_clip_mean_of_1024_samples_takes_the_tile():
     """1024 samples are the most that the kernel with its samples in LDS takes; the one behind it reads them again for every rank
     (16 positions: 0.07 and 180 ms), so a line drawn too low shows as time."""
