@@ -292,8 +292,9 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //                           bin does not matter (and is not fixed), so no ranks are needed;
 //   * set_sum_kernel        a hot bin is 2^17 patterns of one sign and exponent: a bitmap of 16 KB in LDS.  Intervals are
 //                           distances of set bits times the exponent's unit, exact; t ln t of the small distances comes from
-//                           a table made with the same expressions.  A bin of more than 131072 keys is read by several
-//                           workgroups that join their bitmaps in memory, and the last to finish sums.  A group of small bins
+//                           a table made with the same expressions.  A bin of more than 131072 keys and a 64th of all is
+//                           read by several workgroups that join their bitmaps in memory, and the last to finish sums (joined
+//                           beyond 131072 keys in any case, 14336 x 4096 took 552 us instead of 445).  A group of small bins
 //                           is sorted (sort_group);
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
@@ -301,8 +302,8 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 // Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 1.7 TB/s for 14336 x 4096.  The busiest
 // unit is the LDS (counters at 4096 x 4096: active 41 % in the partition, 28 % in the count, 24 % in the sums, half of it bank
 // conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.
-// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161, 14336 x 4096 1957 -> 550
-// (count 56, plan 15, partition 240, sum 214, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
+// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161, 14336 x 4096 1957 -> 445
+// (count 56, plan 15, partition 240, sum 107, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
 // half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20
 // weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604 (the one kind found that is slower
 // here).  Below kSetMinCount the sort.
@@ -435,7 +436,7 @@ __global__ void __launch_bounds__(kSetThreads) set_count_kernel(const uint32_t* 
 }
 
 // One workgroup; a thread takes 32 consecutive bins.
-__global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uint32_t wgs) {
+__global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uint32_t wgs, uint32_t solo) {
     __shared__ uint32_t wave_sum[kSetThreads / 64][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t c[32], occupied = 0u;
@@ -452,7 +453,7 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
         if (c[j] <= kHot) own[0] += c[j];
-        else { own[1] += c[j]; own[2] += (c[j] - 1u) / kPiece + 1u; own[3] += c[j] > kPiece ? 1u : 0u; }
+        else { own[1] += c[j]; own[2] += piece_count(c[j], solo); own[3] += c[j] > solo ? 1u : 0u; }
     }
     uint32_t run[4], total[4];
 #pragma unroll
@@ -482,9 +483,9 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
                 if (run[0] / kHot != at[j] / kHot) b.group_from[run[0] / kHot] = run[0];
             } else {
                 at[j] = total[0] + run[1];
-                for (uint32_t f = 0u; f < n; f += piece_keys(n, f))
-                    b.piece[run[2]++] = uint4_t{(uint32_t)(32 * tid + 4 * q + j), at[j] + f, piece_keys(n, f), n > kPiece ? run[3] : 0xFFFFFFFFu};
-                run[1] += n; run[3] += n > kPiece ? 1u : 0u;
+                for (uint32_t f = 0u; f < n; f += piece_keys(n, f, solo))
+                    b.piece[run[2]++] = uint4_t{(uint32_t)(32 * tid + 4 * q + j), at[j] + f, piece_keys(n, f, solo), n > solo ? run[3] : 0xFFFFFFFFu};
+                run[1] += n; run[3] += n > solo ? 1u : 0u;
             }
         }
         ((uint4_t*)b.start)[8 * tid + q] = uint4_t{at[0], at[1], at[2], at[3]};
@@ -771,7 +772,7 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, u
         if (unit < head.pieces) {
             const uint4_t piece = b.piece[unit];
             const uint32_t bin = piece.x, n = piece.z;
-            const uint32_t* keys = b.keys + piece.y;                          // n <= kPiece: counters from here on cannot wrap
+            const uint32_t* keys = b.keys + piece.y;                          // n <= 2^26: counters from here on cannot wrap
 #pragma unroll
             for (int j = 0; j < kBitmapWords / 4; j += kSumThreads) ((uint4_t*)data)[j + tid] = uint4_t{0u, 0u, 0u, 0u};
             __syncthreads();
@@ -911,7 +912,7 @@ static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, doub
     }
     hipLaunchKernelGGL(set_clear_kernel, dim3(256), dim3(256), 0, s, b, set_joint_max(count));
     hipLaunchKernelGGL(set_count_kernel, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
-    hipLaunchKernelGGL(set_plan_kernel, dim3(1), dim3(kSetThreads), 0, s, b, wgs);
+    hipLaunchKernelGGL(set_plan_kernel, dim3(1), dim3(kSetThreads), 0, s, b, wgs, piece_solo(count));
     if (count > kTiledMinCount) hipLaunchKernelGGL(set_partition_kernel<true>, dim3(wgs), dim3(kSetThreads), lds_partition, s, w, count, b);
     else hipLaunchKernelGGL(set_partition_kernel<false>, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
     hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups), dim3(kSumThreads), 0, s, b, count, terms);

@@ -6,7 +6,7 @@
 namespace rwkvq {
 
 constexpr uint32_t kCountRange = 49152;        // fewest keys per counting workgroup
-constexpr uint32_t kPiece = 131072;            // keys of a hot bin that one workgroup reads
+constexpr uint32_t kPiece = 131072;            // keys of a piece of a hot bin that several workgroups read
 
 constexpr uint32_t set_workgroups(uint32_t count) { return count / kCountRange < 256u ? count / kCountRange : 256u; }
 
@@ -23,7 +23,11 @@ constexpr SetRange set_range(uint32_t count, uint32_t wg, uint32_t wgs) {
     return SetRange{lo, (hi - lo) / 4u, (hi - lo) % 4u};
 }
 
-// Keys of the piece of a hot bin of n keys that begins with its key f < n.
-constexpr uint32_t piece_keys(uint32_t n, uint32_t f) { return n - f < kPiece ? n - f : kPiece; }
+// Most keys of a hot bin that one workgroup reads alone, of `count` in all: joining bitmaps in memory costs a fence over the L2 per
+// piece, which pays only where the bin would be a large part of a launch of 256 compute units.
+constexpr uint32_t piece_solo(uint32_t count) { return count / 64u > kPiece ? count / 64u : kPiece; }
+// Pieces of a hot bin of n keys, and the keys of the one that begins with its key f < n.
+constexpr uint32_t piece_count(uint32_t n, uint32_t solo) { return n > solo ? (n - 1u) / kPiece + 1u : 1u; }
+constexpr uint32_t piece_keys(uint32_t n, uint32_t f, uint32_t solo) { return n <= solo || n - f < kPiece ? n - f : kPiece; }
 
 }  // namespace rwkvq

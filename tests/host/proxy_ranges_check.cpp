@@ -3,6 +3,7 @@
 #include "proxy_ranges.h"
 
 #include <cstdio>
+#include <initializer_list>
 
 using namespace rwkvq;
 typedef unsigned long long u64;
@@ -25,14 +26,18 @@ int main() {
             if (r.quads && (u64)r.quads + 4u * 1024u > 0xFFFFFFFFull) ++bad;
         }
         if (next != count) ++bad;
-        // a bin that holds every key
-        u64 keys = 0;
-        for (uint32_t f = 0; f < count; f += piece_keys(count, f)) {
-            if (f != keys || piece_keys(count, f) > kPiece || piece_keys(count, f) == 0u) ++bad;
-            keys += piece_keys(count, f);
-            if (keys > count) { ++bad; break; }
+        // a bin that holds every key, and the largest that one workgroup reads
+        const uint32_t solo = piece_solo(count);
+        for (const uint32_t n : {count, solo}) {
+            u64 keys = 0, pieces = 0;
+            for (uint32_t f = 0; f < n; f += piece_keys(n, f, solo)) {
+                if (f != keys || piece_keys(n, f, solo) > (n > solo ? kPiece : solo) || piece_keys(n, f, solo) == 0u) ++bad;
+                keys += piece_keys(n, f, solo);
+                ++pieces;
+                if (keys > n) { ++bad; break; }
+            }
+            if (keys != n || pieces != piece_count(n, solo) || (n <= solo && pieces != 1u) || solo > (1u << 26)) ++bad;
         }
-        if (keys != count || (count - 1u) / kPiece + 1u != (u64)(count / kPiece) + (count % kPiece ? 1 : 0)) ++bad;
         ++checked;
     };
     for (uint32_t d = 0; d < 2100u; ++d) check(0xFFFFFFFFu - d);
