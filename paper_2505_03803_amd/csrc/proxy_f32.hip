@@ -302,8 +302,8 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 // Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 1.7 TB/s for 14336 x 4096.  The busiest
 // unit is the LDS (counters at 4096 x 4096: active 41 % in the partition, 28 % in the count, 24 % in the sums, half of it bank
 // conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.
-// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 161, 14336 x 4096 1957 -> 445
-// (count 56, plan 15, partition 240, sum 107, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
+// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 142, 14336 x 4096 1957 -> 358
+// (count 56, plan 15, partition 152, sum 107, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
 // half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20
 // weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604 (the one kind found that is slower
 // here).  Below kSetMinCount the sort.
@@ -316,7 +316,7 @@ constexpr int kSetRow = kGapSums + 1;                        // partial sums and
 constexpr int kSumThreads = 512, kSumWorkgroups = 512;
 constexpr int kTable = 512;
 
-struct SetHead { uint32_t min_key, max_key, groups, pieces, joints; };
+struct SetHead { uint32_t min_key, max_key, groups, pieces, joints, bins; };
 struct SetBuffers {
     uint32_t* keys;          // partitioned: groups of small bins, then the hot bins, each in bin order
     uint32_t* reserved;      // [workgroup][bin]: keys of the bin reserved before
@@ -324,7 +324,7 @@ struct SetBuffers {
     uint32_t* counts;        // [bin]
     uint32_t* least;         // [counting workgroup]: its smallest and largest key
     uint32_t* most;
-    uint32_t* occupied;      // [bin / 32]: bit = the bin holds keys
+    uint2_t* occupied;       // [bin / 32]: bit = the bin holds keys; occupied bins before these 32
     uint32_t* start;         // [bin]: position of the bin in keys
     uint32_t* group_from;    // [group + 1]: position of the group's first key
     uint32_t* bin_min;       // [bin], of occupied bins
@@ -347,7 +347,7 @@ static SetBuffers set_buffers(char* base, uint32_t count) {
     b.counts = (uint32_t*)take(kBins * 4);
     b.least = (uint32_t*)take(256 * 4);
     b.most = (uint32_t*)take(256 * 4);
-    b.occupied = (uint32_t*)take(kBins / 8);
+    b.occupied = (uint2_t*)take(kBins / 4);
     b.start = (uint32_t*)take(kBins * 4);
     b.group_from = (uint32_t*)take(((size_t)count / kHot + 2) * 4);
     b.bin_min = (uint32_t*)take(kBins * 4);
@@ -437,7 +437,7 @@ __global__ void __launch_bounds__(kSetThreads) set_count_kernel(const uint32_t* 
 
 // One workgroup; a thread takes 32 consecutive bins.
 __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uint32_t wgs, uint32_t solo) {
-    __shared__ uint32_t wave_sum[kSetThreads / 64][4];
+    __shared__ uint32_t wave_sum[kSetThreads / 64][5];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t c[32], occupied = 0u;
 #pragma unroll
@@ -447,17 +447,16 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
     }
 #pragma unroll
     for (int j = 0; j < 32; ++j) occupied |= (c[j] ? 1u : 0u) << j;
-    b.occupied[tid] = occupied;
-    // keys in small bins, keys in hot bins, pieces, hot bins of several pieces
-    uint32_t own[4] = {0u, 0u, 0u, 0u};
+    // keys in small bins, keys in hot bins, pieces, hot bins of several pieces, occupied bins
+    uint32_t own[5] = {0u, 0u, 0u, 0u, (uint32_t)__builtin_popcount(occupied)};
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
         if (c[j] <= kHot) own[0] += c[j];
         else { own[1] += c[j]; own[2] += piece_count(c[j], solo); own[3] += c[j] > solo ? 1u : 0u; }
     }
-    uint32_t run[4], total[4];
+    uint32_t run[5], total[5];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
         uint32_t v = own[i];
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)v, off, 64); if (lane >= off) v += a; }
@@ -466,10 +465,11 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
         total[i] = 0u;
         for (int w = 0; w < kSetThreads / 64; ++w) { if (w < wave) run[i] += wave_sum[w][i]; total[i] += wave_sum[w][i]; }
     }
+    b.occupied[tid] = uint2_t{occupied, run[4]};
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         uint32_t at[4];
@@ -504,16 +504,131 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uin
         const uint32_t groups = total[0] ? (total[0] - 1u) / kHot + 1u : 0u;
         b.group_from[0] = 0u;
         if (groups) b.group_from[groups] = total[0];
-        b.head->groups = groups; b.head->pieces = total[2]; b.head->joints = total[3];
+        b.head->groups = groups; b.head->pieces = total[2]; b.head->joints = total[3]; b.head->bins = total[4];
     }
 }
 
-// Stored where it is met, a key is a request of four bytes to a line of its own.  TILED: 4096 keys at a time are brought into
-// the order of their class first (the lower 11 bits of the bin: keys of one bin stand together, whatever else is in the class),
-// so that a wavefront's store meets runs.  Measured (us; not tiled, tiled): 1280 x 1280 35, 44; 2048 x 2048 even; 4096 x 4096
-// 103, 70; 14336 x 4096 460, 239: tiled beyond kTiledMinCount.
+// Stored where it is met, a key is a request of four bytes to a line of its own.  TILED: keys are brought into the order of their
+// bins in LDS first, so that a wavefront's store meets runs.  Up to kRanks occupied bins (near-normal weights occupy about four
+// thousand): 16384 keys at a time, counted by the rank of their bin among the occupied ones; a thread keeps the positions of eight
+// ranks in registers.  More: 4096 keys at a time, in the order of their class (the lower 11 bits of the bin: keys of one bin stand
+// together, whatever else is in the class), positions of all bins in LDS.
+// What bounds it: the LDS (seven accesses per key) and the phases between five barriers per tile.
+// Measured (us; not tiled, by class, by rank): 1280 x 1280 35, 44, 36; 2048 x 2048 even, even, 5 less; 4096 x 4096 103, 70, 48;
+// 14336 x 4096 460, 240, 152: tiled beyond kTiledMinCount.
 constexpr int kClasses = 2048;
-constexpr uint32_t kTiledMinCount = 1u << 22;
+constexpr int kRanks = 8192, kTileKeys = 16 * kSetThreads;
+constexpr uint32_t kTiledMinCount = 3u << 20;
+__device__ __forceinline__ uint32_t bin_rank(const uint2_t* occupied, uint32_t bin) {
+    const uint2_t o = occupied[bin >> 5];
+    return o.y + (uint32_t)__builtin_popcount(o.x & ((1u << (bin & 31u)) - 1u));
+}
+// lds: uint2 occupied[kBins / 32], first[kRanks], to[kRanks], tile[kTileKeys], wave_sum[kSetThreads / 64]
+__device__ __forceinline__ void partition_by_rank(const uint32_t* __restrict__ in, const SetRange& r, const uint32_t* __restrict__ mine,
+                                                  const SetBuffers& b, uint32_t* lds) {
+    uint2_t* const occupied = (uint2_t*)lds;
+    uint32_t* const first = lds + kBins / 16;                    // keys of the rank in the tile, then its first place
+    uint32_t* const to = first + kRanks;                         // position in `keys` of the rank's first key, less its first place
+    uint32_t* const tile = to + kRanks;
+    uint32_t* const wave_sum = tile + kTileKeys;
+    constexpr int kOwn = kRanks / kSetThreads, kQuads = kTileKeys / kSetThreads / 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t* out = b.keys;
+    occupied[tid] = b.occupied[tid];
+    __syncthreads();
+#pragma unroll 8
+    for (int i = 0; i < kBins / kSetThreads; ++i) {              // (bins that the range does not hold: never used)
+        const uint32_t bin = (uint32_t)(tid + i * kSetThreads), at = b.start[bin] + mine[bin];
+        if ((occupied[bin >> 5].x >> (bin & 31u)) & 1u) to[bin_rank(occupied, bin)] = at;
+    }
+#pragma unroll
+    for (int i = 0; i < kOwn; i += 4) *(uint4_t*)(first + kOwn * tid + i) = uint4_t{0u, 0u, 0u, 0u};
+    __syncthreads();
+    uint32_t next[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) next[i] = to[kOwn * tid + i];
+    const uint32_t quads = r.quads;
+    const uint4_t* src = (const uint4_t*)(in + r.lo);
+    uint4_t v[kQuads];
+    auto fetch = [&](uint32_t base) {
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) {
+            const uint32_t i = base + (uint32_t)(tid + q * kSetThreads);
+            v[q] = i < quads ? src[i] : uint4_t{0u, 0u, 0u, 0u};
+        }
+    };
+    fetch(0u);
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t base = 0u; base < quads; base += kTileKeys / 4) {
+        const uint32_t in_tile = 4u * min(quads - base, (uint32_t)(kTileKeys / 4));
+        uint32_t key[4 * kQuads], at[4 * kQuads];                // at: rank of the bin, and among the tile's keys of it, 14 bits
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) {
+            const uint32_t k[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+            if (4u * (uint32_t)(tid + q * kSetThreads) < in_tile)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    key[4 * q + j] = f32_key(k[j]);
+                    const uint32_t rank = bin_rank(occupied, key[4 * q + j] >> kBinShift);
+                    at[4 * q + j] = rank << 14 | count_bin(first, rank);
+                }
+        }
+        fetch(base + kTileKeys / 4);
+        __syncthreads();
+        uint32_t n[kOwn], own = 0u;
+#pragma unroll
+        for (int i = 0; i < kOwn; i += 4) {
+            const uint4_t c = *(const uint4_t*)(first + kOwn * tid + i);
+            n[i] = c.x; n[i + 1] = c.y; n[i + 2] = c.z; n[i + 3] = c.w;
+            own += c.x + c.y + c.z + c.w;
+        }
+        uint32_t place = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)place, off, 64); if (lane >= off) place += a; }
+        if (lane == 63) wave_sum[wave] = place;
+        place -= own;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSetThreads / 64; ++w) place += w < wave ? wave_sum[w] : 0u;
+#pragma unroll
+        for (int i = 0; i < kOwn; i += 4) {
+            uint4_t f, t;
+            f.x = place; t.x = next[i] - place; next[i] += n[i]; place += n[i];
+            f.y = place; t.y = next[i + 1] - place; next[i + 1] += n[i + 1]; place += n[i + 1];
+            f.z = place; t.z = next[i + 2] - place; next[i + 2] += n[i + 2]; place += n[i + 2];
+            f.w = place; t.w = next[i + 3] - place; next[i + 3] += n[i + 3]; place += n[i + 3];
+            *(uint4_t*)(first + kOwn * tid + i) = f;
+            *(uint4_t*)(to + kOwn * tid + i) = t;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q)
+            if (4u * (uint32_t)(tid + q * kSetThreads) < in_tile)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) tile[first[at[4 * q + j] >> 14] + (at[4 * q + j] & 16383u)] = key[4 * q + j];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kOwn; i += 4) *(uint4_t*)(first + kOwn * tid + i) = uint4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int j = 0; j < 4 * kQuads; ++j) {
+            const uint32_t i = (uint32_t)(tid + j * kSetThreads);
+            if (i < in_tile) {
+                const uint32_t k = tile[i];
+                out[to[bin_rank(occupied, k >> kBinShift)] + i] = k;
+            }
+        }
+        __syncthreads();
+    }
+    // the last keys, fewer than four: positions behind those of the tiles
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) to[kOwn * tid + i] = next[i];
+    __syncthreads();
+    if ((uint32_t)tid < r.rest) {
+        const uint32_t k = f32_key(in[r.tail(tid)]);
+        out[atomicAdd(&to[bin_rank(occupied, k >> kBinShift)], 1u)] = k;
+    }
+}
 template <bool TILED>
 __global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32_t* __restrict__ in, uint32_t count, SetBuffers b) {
     extern __shared__ uint32_t next[];                           // [kBins]: position of the workgroup's next key of the bin
@@ -522,9 +637,13 @@ __global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32
     uint32_t* wave_sum = cls + kClasses;                         // [kSetThreads / 64]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
+    const SetRange r = set_range(count, blockIdx.x, gridDim.x);
+    if (TILED && b.head->bins <= (uint32_t)kRanks) {
+        partition_by_rank(in, r, mine, b, next);
+        return;
+    }
     for (int j = tid; j < kBins / 4; j += kSetThreads)           // (bins that the range does not hold: never read)
         ((uint4_t*)next)[j] = ((const uint4_t*)b.start)[j] + ((const uint4_t*)mine)[j];
-    const SetRange r = set_range(count, blockIdx.x, gridDim.x);
     uint32_t* out = b.keys;
     if constexpr (!TILED) {
         __syncthreads();
@@ -863,7 +982,7 @@ __global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetBuffers b, ui
 #pragma unroll
         for (int k = 0; k < kSetRow; ++k) s[k] += b.sums[(size_t)i * kSetRow + k];
     }
-    uint32_t occupied = b.occupied[tid];                                      // of 32 consecutive bins
+    uint32_t occupied = b.occupied[tid].x;                                    // of 32 consecutive bins
     const uint32_t own = __builtin_popcount(occupied);
     uint32_t at = own, bins = 0u;
 #pragma unroll
@@ -902,7 +1021,7 @@ static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, doub
     const SetBuffers b = set_buffers((char*)workspace, count);
     const uint32_t wgs = set_workgroups(count);
     constexpr int lds = kBins * 4, lds_partition = lds + (4 * kSetThreads + kClasses + kSetThreads / 64) * 4;   // 128 and 152 KB
-    static_assert(lds_partition <= 160 * 1024, "LDS of a compute unit");
+    static_assert(lds_partition <= 160 * 1024 && (kBins / 16 + 2 * kRanks + kTileKeys + kSetThreads / 64) * 4 <= lds_partition, "LDS of a compute unit");
     const void* kernels[] = {(const void*)set_count_kernel, (const void*)set_partition_kernel<false>, (const void*)set_partition_kernel<true>,
                              (const void*)set_final_kernel};
     static std::atomic<unsigned long long> raised[4];

@@ -92,3 +92,15 @@ def test_proxy_sets_not_finite():
             out.append(run(w))
         for got in out[1:]:
             assert np.array_equal(np.array(out[0]), np.array(got), equal_nan=True), (bad, out)
+
+
+# occupied bins on both sides of what the partition by rank holds, the keys spread over all of them; the smallest matrix that is
+# reordered in tiles (3 x 2^20 weights is not, one more is), and ranges that end in a part of a tile and in single keys
+@pytest.mark.parametrize("bins", [1, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [(3 << 20) + 1, 4 * 16384 * 64 + 4 * 777 + 3])
+def test_proxy_sets_ranks(bins, n):
+    rng = np.random.default_rng(bins)
+    bin_of = np.concatenate([np.arange(bins), rng.integers(0, bins, n - bins)])
+    keys = ((np.uint32(2000) + bin_of.astype(np.uint32) * np.uint32(3)) << 17) | rng.integers(0, 1 << 17, n).astype(np.uint32)
+    bits = np.where(keys >> 31, keys & np.uint32(0x7FFFFFFF), ~keys).astype(np.uint32)
+    check(rng.permutation(bits).view(np.float32))
