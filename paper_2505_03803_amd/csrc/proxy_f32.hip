@@ -19,10 +19,12 @@
 //     (a partial sum per 16384 intervals, then one workgroup adds the partial sums), with
 //     t_i = G_i / mean(G) as in proxy.hip:  P_c = (1/n) sum t ln t,  v_k |M_k| = |sum (t-1)^k| / (n k (k-1)).
 //
-// Matrices of a call are processed one after another on the stream and share the sort buffers.
+// Matrices of a call share the buffers; large ones are counted and concluded several at a time (SetGroup).
 #include "common.h"
 #include "proxy_ranges.h"
 #include "../../include/rwkvq.h"
+
+#include <algorithm>
 
 namespace rwkvq {
 
@@ -317,8 +319,14 @@ constexpr int kSumThreads = 512, kSumWorkgroups = 512;
 constexpr int kTable = 512;
 
 struct SetHead { uint32_t min_key, max_key, groups, pieces, joints, bins; };
+// One matrix of a call.
 struct SetBuffers {
-    uint32_t* keys;          // partitioned: groups of small bins, then the hot bins, each in bin order
+    const uint32_t* in;      // the weights
+    uint32_t count, wgs;     // of them; counting (and partitioning) workgroups
+    uint32_t solo, joint_max;
+    double* out;             // P_c, P_f
+    int32_t* phi;
+    uint32_t* keys;          // partitioned: groups of small bins, then the hot bins, each in bin order; shared by the matrices
     uint32_t* reserved;      // [workgroup][bin]: keys of the bin reserved before
     SetHead* head;
     uint32_t* counts;        // [bin]
@@ -333,16 +341,21 @@ struct SetBuffers {
     uint32_t* done;          // [joint]: pieces finished
     uint32_t* joint;         // [joint][4096]
     double* sums;            // [workgroups of set_sum_kernel, then joint bins][kSetRow]
-    size_t bytes;
 };
-static uint32_t set_joint_max(uint32_t count) { return count / kPiece; }
+// Matrices that are cleared, counted, planned and concluded in one launch each: four launches of 5, 15 and 13 us for one workgroup's
+// work (and the ends of the counts) once per group instead of once per matrix.
+constexpr int kSetGroup = 8;
+struct SetGroup { SetBuffers b[kSetGroup]; };
+static uint32_t set_joint_max(uint32_t count) { return std::min(count / kPiece, 64u); }       // (a joint bin holds more than a 64th of the keys)
 
-static SetBuffers set_buffers(char* base, uint32_t count) {
-    SetBuffers b;
+static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+static size_t set_key_bytes(uint32_t count) { return align256((size_t)count * 4); }
+// A matrix's own buffers from `base` on; returns their size.
+static size_t set_tables(SetBuffers& b, char* base, uint32_t count) {
     size_t o = 0;
-    auto take = [&](size_t bytes) { char* p = base + o; o += (bytes + 255) & ~(size_t)255; return p; };
-    b.keys = (uint32_t*)take((size_t)count * 4);
-    b.reserved = (uint32_t*)take((size_t)set_workgroups(count) * kBins * 4);
+    auto take = [&](size_t bytes) { char* p = base + o; o += align256(bytes); return p; };
+    b.count = count; b.wgs = set_workgroups(count); b.solo = piece_solo(count); b.joint_max = set_joint_max(count);
+    b.reserved = (uint32_t*)take((size_t)b.wgs * kBins * 4);
     b.head = (SetHead*)take(sizeof(SetHead));
     b.counts = (uint32_t*)take(kBins * 4);
     b.least = (uint32_t*)take(256 * 4);
@@ -352,15 +365,16 @@ static SetBuffers set_buffers(char* base, uint32_t count) {
     b.group_from = (uint32_t*)take(((size_t)count / kHot + 2) * 4);
     b.bin_min = (uint32_t*)take(kBins * 4);
     b.bin_max = (uint32_t*)take(kBins * 4);
-    b.piece = (uint4_t*)take(((size_t)count / kHot + set_joint_max(count)) * 16);
-    b.done = (uint32_t*)take((size_t)set_joint_max(count) * 4);
-    b.joint = (uint32_t*)take((size_t)set_joint_max(count) * kBitmapWords * 4);
-    b.sums = (double*)take((size_t)(kSumWorkgroups + set_joint_max(count)) * kSetRow * 8);
-    b.bytes = o;
-    return b;
+    b.piece = (uint4_t*)take(((size_t)count / kHot + count / kPiece) * 16);
+    b.done = (uint32_t*)take((size_t)b.joint_max * 4);
+    b.joint = (uint32_t*)take((size_t)b.joint_max * kBitmapWords * 4);
+    b.sums = (double*)take((size_t)(kSumWorkgroups + b.joint_max) * kSetRow * 8);
+    return o;
 }
 
-__global__ void __launch_bounds__(256) set_clear_kernel(SetBuffers b, uint32_t joint_max) {
+__global__ void __launch_bounds__(256) set_clear_kernel(SetGroup g) {
+    const SetBuffers& b = g.b[blockIdx.y];
+    const uint32_t joint_max = b.joint_max;
     const uint32_t i = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
     for (uint32_t j = i; j < (uint32_t)kBins; j += step) b.counts[j] = 0u;
     for (uint32_t j = i; j < joint_max; j += step) b.done[j] = 0u;
@@ -396,13 +410,15 @@ __device__ __forceinline__ uint32_t count_bin(uint32_t* counter, uint32_t bin) {
     return atomicAdd(&counter[bin], 1u);
 }
 
-__global__ void __launch_bounds__(kSetThreads) set_count_kernel(const uint32_t* __restrict__ in, uint32_t count, SetBuffers b) {
+__global__ void __launch_bounds__(kSetThreads) set_count_kernel(SetGroup g) {
     extern __shared__ uint32_t h[];                              // [kBins]
+    const SetBuffers& b = g.b[blockIdx.y];
+    if (blockIdx.x >= b.wgs) return;
     const int tid = threadIdx.x;
     for (int j = tid; j < kBins / 4; j += kSetThreads) ((uint4_t*)h)[j] = uint4_t{0u, 0u, 0u, 0u};
     __syncthreads();
     uint32_t least = 0xFFFFFFFFu, most = 0u;
-    for_quads(in, set_range(count, blockIdx.x, gridDim.x), [&](uint32_t bits) {
+    for_quads(b.in, set_range(b.count, blockIdx.x, b.wgs), [&](uint32_t bits) {
         const uint32_t k = f32_key(bits);
         least = min(least, k); most = max(most, k);
         count_bin(h, k >> kBinShift);
@@ -435,8 +451,10 @@ __global__ void __launch_bounds__(kSetThreads) set_count_kernel(const uint32_t* 
     }
 }
 
-// One workgroup; a thread takes 32 consecutive bins.
-__global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetBuffers b, uint32_t wgs, uint32_t solo) {
+// One workgroup per matrix; a thread takes 32 consecutive bins.
+__global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetGroup g) {
+    const SetBuffers& b = g.b[blockIdx.x];
+    const uint32_t wgs = b.wgs, solo = b.solo;
     __shared__ uint32_t wave_sum[kSetThreads / 64][5];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t c[32], occupied = 0u;
@@ -630,14 +648,15 @@ __device__ __forceinline__ void partition_by_rank(const uint32_t* __restrict__ i
     }
 }
 template <bool TILED>
-__global__ void __launch_bounds__(kSetThreads) set_partition_kernel(const uint32_t* __restrict__ in, uint32_t count, SetBuffers b) {
+__global__ void __launch_bounds__(kSetThreads) set_partition_kernel(SetBuffers b) {
+    const uint32_t* __restrict__ in = b.in;
     extern __shared__ uint32_t next[];                           // [kBins]: position of the workgroup's next key of the bin
     uint32_t* tile = next + kBins;                               // [4 kSetThreads]
     uint32_t* cls = tile + 4 * kSetThreads;                      // [kClasses]: keys of the class, then their first place
     uint32_t* wave_sum = cls + kClasses;                         // [kSetThreads / 64]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
-    const SetRange r = set_range(count, blockIdx.x, gridDim.x);
+    const SetRange r = set_range(b.count, blockIdx.x, b.wgs);
     if (TILED && b.head->bins <= (uint32_t)kRanks) {
         partition_by_rank(in, r, mine, b, next);
         return;
@@ -873,7 +892,7 @@ __device__ __forceinline__ const uint32_t* sort_group(uint32_t (&k)[4], uint32_t
     return buf;
 }
 
-__global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, uint32_t count, int terms) {
+__global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, int terms) {
     __shared__ __attribute__((aligned(16))) uint32_t data[kBitmapWords];     // a bitmap or a group's keys
     __shared__ double table[kTable];
     __shared__ double red[kSumThreads / 64][kSetRow];
@@ -881,7 +900,7 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, u
     __shared__ int last_piece;
     const int tid = threadIdx.x;
     const SetHead head = *b.head;
-    const double inv_mean = (double)(count - 1u) / (key_f64(head.max_key) - key_f64(head.min_key));
+    const double inv_mean = (double)(b.count - 1u) / (key_f64(head.max_key) - key_f64(head.min_key));
     double s[kSetRow];                                                        // of the workgroup's units, whose choice is fixed
 #pragma unroll
     for (int k = 0; k < kSetRow; ++k) s[k] = 0.0;
@@ -964,8 +983,9 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, u
     if (tid < kSetRow) b.sums[(size_t)blockIdx.x * kSetRow + tid] = v;
 }
 
-__global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetBuffers b, uint32_t count, int terms, double tau_c, double tau_f,
-                                                                double* __restrict__ out, int32_t* __restrict__ phi) {
+__global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetGroup g, int terms, double tau_c, double tau_f) {
+    const SetBuffers& b = g.b[blockIdx.x];
+    const uint32_t count = b.count;
     extern __shared__ uint32_t next[];
     uint16_t* list = (uint16_t*)next;                                         // [kBins]: the occupied bins
     __shared__ double red[kSetThreads / 64][kSetRow];
@@ -1010,16 +1030,13 @@ __global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetBuffers b, ui
             Pc = tot[0] / n;
             for (int k = 2; k <= terms; ++k) Pf += fabs(tot[k] + (k & 1 ? -equal : equal)) / (n * (double)(k * (k - 1)));
         }
-        out[0] = Pc;
-        out[1] = Pf;
-        *phi = (Pc < tau_c && Pf < tau_f) ? 1 : 0;
+        b.out[0] = Pc;
+        b.out[1] = Pf;
+        *b.phi = (Pc < tau_c && Pf < tau_f) ? 1 : 0;
     }
 }
 
-static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, double tau_c, double tau_f, void* workspace,
-                              double* out, int32_t* phi, hipStream_t s) {
-    const SetBuffers b = set_buffers((char*)workspace, count);
-    const uint32_t wgs = set_workgroups(count);
+static hipError_t launch_sets(const SetGroup& g, int n, int terms, double tau_c, double tau_f, hipStream_t s) {
     constexpr int lds = kBins * 4, lds_partition = lds + (4 * kSetThreads + kClasses + kSetThreads / 64) * 4;   // 128 and 152 KB
     static_assert(lds_partition <= 160 * 1024 && (kBins / 16 + 2 * kRanks + kTileKeys + kSetThreads / 64) * 4 <= lds_partition, "LDS of a compute unit");
     const void* kernels[] = {(const void*)set_count_kernel, (const void*)set_partition_kernel<false>, (const void*)set_partition_kernel<true>,
@@ -1029,17 +1046,20 @@ static hipError_t launch_sets(const uint32_t* w, uint32_t count, int terms, doub
         const hipError_t e = raise_lds(kernels[i], lds_partition, raised[i]);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(set_clear_kernel, dim3(256), dim3(256), 0, s, b, set_joint_max(count));
-    hipLaunchKernelGGL(set_count_kernel, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
-    hipLaunchKernelGGL(set_plan_kernel, dim3(1), dim3(kSetThreads), 0, s, b, wgs, piece_solo(count));
-    if (count > kTiledMinCount) hipLaunchKernelGGL(set_partition_kernel<true>, dim3(wgs), dim3(kSetThreads), lds_partition, s, w, count, b);
-    else hipLaunchKernelGGL(set_partition_kernel<false>, dim3(wgs), dim3(kSetThreads), lds, s, w, count, b);
-    hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups), dim3(kSumThreads), 0, s, b, count, terms);
-    hipLaunchKernelGGL(set_final_kernel, dim3(1), dim3(kSetThreads), kBins * 2, s, b, count, terms, tau_c, tau_f, out, phi);
+    uint32_t wgs = 0;
+    for (int i = 0; i < n; ++i) wgs = std::max(wgs, g.b[i].wgs);
+    hipLaunchKernelGGL(set_clear_kernel, dim3(64, n), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(set_count_kernel, dim3(wgs, n), dim3(kSetThreads), lds, s, g);
+    hipLaunchKernelGGL(set_plan_kernel, dim3(n), dim3(kSetThreads), 0, s, g);
+    for (int i = 0; i < n; ++i) {
+        const SetBuffers& b = g.b[i];
+        if (b.count > kTiledMinCount) hipLaunchKernelGGL(set_partition_kernel<true>, dim3(b.wgs), dim3(kSetThreads), lds_partition, s, b);
+        else hipLaunchKernelGGL(set_partition_kernel<false>, dim3(b.wgs), dim3(kSetThreads), lds, s, b);
+        hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups), dim3(kSumThreads), 0, s, b, terms);
+    }
+    hipLaunchKernelGGL(set_final_kernel, dim3(n), dim3(kSetThreads), kBins * 2, s, g, terms, tau_c, tau_f);
     return hipGetLastError();
 }
-
-static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct F32Layout { size_t keys_a, keys_b, counts, totals, partial, bytes; };
 static F32Layout f32_layout(unsigned long long max_count) {
@@ -1078,16 +1098,35 @@ hipError_t launch_proxy_f32(const void* const* ws, const int* Ns, const int* Ks,
     uint32_t* counts = (uint32_t*)(base + L.counts);
     uint32_t* totals = (uint32_t*)(base + L.totals);
     double* partial = (double*)(base + L.partial);
+    SetGroup g{};
+    int in_group = 0;
+    size_t keys = 0, tables = 0;                   // bytes of the group: the largest matrix's keys, and every one's tables
+    auto flush = [&]() {
+        char* at = base + keys;
+        for (int i = 0; i < in_group; ++i) { g.b[i].keys = (uint32_t*)base; at += set_tables(g.b[i], at, g.b[i].count); }
+        const hipError_t e = in_group ? launch_sets(g, in_group, terms, tau_c, tau_f, s) : hipSuccess;
+        in_group = 0; keys = tables = 0;
+        return e;
+    };
     for (int i = 0; i < n_mats; ++i) {
         const uint32_t count = (uint32_t)((unsigned long long)Ns[i] * (unsigned long long)Ks[i]);
         const uint32_t tiles = (uint32_t)(((unsigned long long)count + kSortTile - 1) / kSortTile);   // count may be 2^32 - 1
         const uint32_t* src = (const uint32_t*)ws[i];
         // (the workspace is sized for the sort's two key buffers and its counts; the sets take less from kSetMinCount on)
-        if (count >= kSetMinCount && set_buffers(nullptr, count).bytes <= L.bytes) {
-            const hipError_t e = launch_sets(src, count, terms, tau_c, tau_f, workspace, out + 2 * i, phi + i, s);
-            if (e != hipSuccess) return e;
+        SetBuffers b{};
+        const size_t own_keys = set_key_bytes(count), own = count >= kSetMinCount ? set_tables(b, nullptr, count) : 0;
+        if (count >= kSetMinCount && own_keys + own <= L.bytes) {
+            if (in_group == kSetGroup || std::max(keys, own_keys) + tables + own > L.bytes) {
+                const hipError_t e = flush();
+                if (e != hipSuccess) return e;
+            }
+            b.in = src; b.out = out + 2 * i; b.phi = phi + i;
+            g.b[in_group++] = b;
+            keys = std::max(keys, own_keys); tables += own;
             continue;
         }
+        const hipError_t flushed = flush();        // (the sort uses the same workspace)
+        if (flushed != hipSuccess) return flushed;
         for (int pass = 0; pass < 4; ++pass) {
             uint32_t* dst = buf[pass & 1];
             if (pass == 0) hipLaunchKernelGGL(sort_hist_kernel<true>, dim3(tiles), dim3(kSortThreads), 0, s, src, count, 0, counts, tiles);
@@ -1107,7 +1146,7 @@ hipError_t launch_proxy_f32(const void* const* ws, const int* Ns, const int* Ks,
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    return flush();
 }
 
 }  // namespace rwkvq

@@ -104,3 +104,17 @@ def test_proxy_sets_ranks(bins, n):
     keys = ((np.uint32(2000) + bin_of.astype(np.uint32) * np.uint32(3)) << 17) | rng.integers(0, 1 << 17, n).astype(np.uint32)
     bits = np.where(keys >> 31, keys & np.uint32(0x7FFFFFFF), ~keys).astype(np.uint32)
     check(rng.permutation(bits).view(np.float32))
+
+
+def test_proxy_sets_groups():
+    """Large matrices share launches in groups, as many as fit the workspace of the largest, with small ones (the sort, in the same
+    workspace) between them: every matrix gives the bits that it gives alone."""
+    import torch
+    from paper_2505_03803_amd import binding as B
+    rng = np.random.default_rng(77)
+    counts = [BIG, BIG + 1, 5000, 3 * BIG, BIG + 7, 9 * BIG + 5, BIG, BIG, BIG, BIG + 2, BIG, BIG, BIG, BIG + 3, BIG, 700, 9 * BIG, 2 * BIG]
+    ws = [torch.from_numpy(synth.gen_dense_weights(rng, 1, n, "f32", outlier_fraction=1e-3)).cuda() for n in counts]
+    got = B.proxy(ws, B.F32, 5, 1.5, 50.0)
+    for w, g in zip(ws, got):
+        assert B.proxy([w], B.F32, 5, 1.5, 50.0)[0] == g, w.numel()
+    assert B.proxy(ws[:2], B.F32, 5, 1.5, 50.0) == got[:2]      # no room for a second one's tables beside the first
