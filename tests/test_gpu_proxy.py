@@ -186,3 +186,29 @@ def test_proxy_f32_full_size(N, K):
     """The two matrix shapes of the RWKV-6-7B-shaped stack as binary32 (16.8 M and 58.7 M keys)."""
     rng = np.random.default_rng(12)
     check32(synth.gen_dense_weights(rng, N, K, "f32", outlier_fraction=1e-4))
+
+
+# Sixteen-bit patterns at every distance around the line between counted intervals (1 to 8 patterns, in one word of 64) and listed
+# ones, from words, exponents and the sign on: every d-th pattern, over subnormals and all exponents, and single words
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("step", [1, 2, 7, 8, 9, 10, 63, 64, 65, 1000])
+def test_proxy_pattern_distances(dtype, step):
+    top = 0x7F00 if dtype == "bf16" else 0x7C00                 # finite patterns
+    for shift in (0, 5):
+        mags = np.arange(shift, top, step, dtype=np.uint16)
+        bits = np.concatenate([mags, mags[::3] | np.uint16(0x8000)])
+        check(np.resize(bits, (1, bits.size + bits.size // 2)), dtype)
+    check(np.arange(0x3F80, 0x3F80 + 64, min(step, 63), dtype=np.uint16).reshape(1, -1), dtype)      # one word
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_proxy_patterns_without_a_value(dtype):
+    """Infinities and NaN among the weights: the definition gives no proxy.  An infinite span makes every interval zero or not a number
+    (which has no t ln t); a span that is not a number has nothing to normalise.  The list of intervals has room for all of them."""
+    inf = 0x7F80 if dtype == "bf16" else 0x7C00
+    every = np.arange(65536, dtype=np.uint16).reshape(256, 256)
+    assert run(every, dtype)[:2] == (0.0, 0.0)
+    w = synth.gen_dense_weights(np.random.default_rng(2), 64, 64, dtype)
+    w[0, 0] = inf
+    Pc, Pf, _ = run(w, dtype)
+    assert Pc == 0.0 and np.isnan(Pf)
