@@ -293,19 +293,18 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //   * set_partition_kernel  every key to its bin: position = start + reservation + an LDS counter per bin.  The order inside a
 //                           bin does not matter (and is not fixed), so no ranks are needed;
 //   * set_sum_kernel        a hot bin is 2^17 patterns of one sign and exponent: a bitmap of 16 KB in LDS.  Intervals are
-//                           distances of set bits times the exponent's unit, exact; t ln t of the small distances comes from
-//                           a table made with the same expressions.  A bin of more than 131072 keys and a 64th of all is
-//                           read by several workgroups that join their bitmaps in memory, and the last to finish sums (joined
-//                           beyond 131072 keys in any case, 14336 x 4096 took 552 us instead of 445).  A group of small bins
-//                           is sorted (sort_group);
+//                           distances of set bits times the exponent's unit, exact, and counted by distance.  A bin of more
+//                           than 131072 keys and a 64th of all is read by several workgroups that join their bitmaps in
+//                           memory, and the last to finish sums (joined beyond 131072 keys in any case, 14336 x 4096 took
+//                           107 us more).  A group of small bins is sorted (sort_group);
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
 // Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 1.7 TB/s for 14336 x 4096.  The busiest
 // unit is the LDS (counters at 4096 x 4096: active 41 % in the partition, 28 % in the count, 24 % in the sums, half of it bank
 // conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.
-// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 142, 14336 x 4096 1957 -> 358
-// (count 56, plan 15, partition 152, sum 107, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
+// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 136, 14336 x 4096 1957 -> 339
+// (count 56, plan 15, partition 152, sum 91, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
 // half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20
 // weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604 (the one kind found that is slower
 // here).  Below kSetMinCount the sort.
@@ -748,10 +747,24 @@ __device__ __forceinline__ double block_sum(const double (&s)[kSetRow], double (
     return v;
 }
 
-// Sums over the intervals inside one hot bin, whose patterns are the bitmap `data`: added to s.
+// Sum over the wavefront, in every lane.
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);      // quad_perm [1, 0, 3, 2]
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);      // quad_perm [2, 3, 0, 1]
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);     // row_half_mirror
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);     // row_mirror
+    const auto rows = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = (uint32_t)rows[0] + (uint32_t)rows[1];
+    const auto halves = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (uint32_t)halves[0] + (uint32_t)halves[1];
+}
+
+// Sums over the intervals inside one hot bin, whose patterns are the bitmap `data`: added to s.  Distances below kTable are counted
+// (`counted`), and their binary64 terms evaluated once per bin, by a thread each (a term per distance met: 4096 x 4096 45 us, now 38).
 __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, double inv_mean, int terms, const SetBuffers& b,
-                                           double* table, int* wave_last, double (&s)[kSetRow]) {
+                                           uint32_t* counted, int* wave_last, double (&s)[kSetRow]) {
     constexpr int kWords = kBitmapWords / kSumThreads;                        // per thread: 256 patterns
+    static_assert(kTable == kSumThreads, "a distance per thread");
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));              // (what follows from it is made again per bin, not kept over the loop around)
     const int lane = tid & 63, wave = tid >> 6;
@@ -759,7 +772,7 @@ __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, d
     const uint32_t base = bin << kBinShift, pattern = (base & 0x80000000u) ? base & 0x7FFFFFFFu : ~base;
     const int ex = (int)((pattern >> 23) & 255u);
     const double unit_gap = ldexp(1.0, (ex ? ex : 1) - 150);
-    for (int d = tid; d < kTable; d += kSumThreads) { const double t = (double)d * unit_gap * inv_mean; table[d] = t > 0.0 ? t * log(t) : 0.0; }
+    counted[tid] = 0u;
     int last = -1;
 #pragma unroll
     for (int j = 0; j < kWords; j += 4) {
@@ -779,7 +792,7 @@ __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, d
     int top = -1;
     for (int v = 0; v < kSumThreads / 64; ++v) { if (v < wave) prev = max(prev, wave_last[v]); top = max(top, wave_last[v]); }
     if (tid == 0) b.bin_max[bin] = base + (uint32_t)top;
-    // distances 1 .. 8 are counted for 32 patterns at once, the others taken bit by bit
+    // distances 1 .. 8 are found for 32 patterns at once, the others bit by bit
     uint32_t near[9], prior = tid ? data[kWords * tid - 1] : 0u, total = 0u;
 #pragma unroll
     for (int d = 1; d <= 8; ++d) near[d] = 0u;
@@ -800,24 +813,32 @@ __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, d
             far &= far - 1u;
             const uint32_t below = x & ((1u << bit) - 1u);
             const int from = below ? 32 * (kWords * tid + j) + 31 - __builtin_clz(below) : prev;
-            if (from >= 0) {
-                const int d = at - from;
-                const double t = (double)d * unit_gap * inv_mean;
-                s[0] += d < kTable ? table[d] : t > 0.0 ? t * log(t) : 0.0;   // (t = 0: an infinite span)
-                add_interval(s, t, terms);
-            } else {
+            if (from < 0) {
                 b.bin_min[bin] = base + (uint32_t)at;
                 total -= 1u;                                                  // no interval in front of the first
+            } else if (at - from < kTable) {
+                atomicAdd(&counted[at - from], 1u);
+            } else {
+                const double t = (double)(at - from) * unit_gap * inv_mean;
+                if (t > 0.0) s[0] += t * log(t);                              // (t = 0: an infinite span)
+                add_interval(s, t, terms);
             }
         }
         if (x) prev = 32 * (kWords * tid + j) + 31 - __builtin_clz(x);
         prior = x;
     }
 #pragma unroll
-    for (int d = 1; d <= 8; ++d) {
-        const double m = (double)near[d], u = (double)d * unit_gap * inv_mean - 1.0;
+    for (int d = 1; d <= 8; d += 2) {                                         // (a thread counts at most 256 of each)
+        const uint32_t two = wave_sum_u32(near[d] | near[d + 1] << 16);
+        if (lane == d) atomicAdd(&counted[d], two & 0xFFFFu);
+        if (lane == d + 1) atomicAdd(&counted[d + 1], two >> 16);
+    }
+    __syncthreads();
+    const uint32_t times = counted[tid];                                      // of distance tid
+    if (times) {
+        const double m = (double)times, t = (double)tid * unit_gap * inv_mean, u = t - 1.0;
         double p = m * u;
-        s[0] += m * table[d];
+        if (t > 0.0) s[0] += m * (t * log(t));
 #pragma unroll
         for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
     }
@@ -894,7 +915,7 @@ __device__ __forceinline__ const uint32_t* sort_group(uint32_t (&k)[4], uint32_t
 
 __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, int terms) {
     __shared__ __attribute__((aligned(16))) uint32_t data[kBitmapWords];     // a bitmap or a group's keys
-    __shared__ double table[kTable];
+    __shared__ uint32_t counted[kTable];                                      // intervals of each distance
     __shared__ double red[kSumThreads / 64][kSetRow];
     __shared__ int wave_last[kSumThreads / 64];
     __shared__ int last_piece;
@@ -906,7 +927,7 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, i
     for (int k = 0; k < kSetRow; ++k) s[k] = 0.0;
 #pragma unroll 1
     for (uint32_t unit = blockIdx.x; unit < head.pieces + head.groups; unit += gridDim.x) {
-        __syncthreads();                                                      // data and table of the unit before are read
+        __syncthreads();                                                      // data and counts of the unit before are read
         if (unit < head.pieces) {
             const uint4_t piece = b.piece[unit];
             const uint32_t bin = piece.x, n = piece.z;
@@ -920,15 +941,22 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, i
                 const bool equal = __builtin_amdgcn_ballot_w64(k == (uint32_t)__builtin_amdgcn_readfirstlane((int)k)) == live;
                 if (!equal || (live & lanes_below(tid & 63)) == 0ull) atomicOr(&data[(k >> 5) & (kBitmapWords - 1)], 1u << (k & 31u));
             };
+            // eight keys at a time, the next eight in flight; past the end the last key again, which changes nothing
+            uint32_t k[8];
+#pragma unroll
+            for (uint32_t j = 0; j < 8u; ++j) k[j] = keys[min(i + j * kSumThreads, n - 1u)];
 #pragma unroll 1
-            for (; i + 7u * kSumThreads < n; i += 8u * kSumThreads) {
-                uint32_t k[8];
+            while (i < n) {
+                uint32_t now[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) k[j] = keys[i + j * kSumThreads];
+                for (int j = 0; j < 8; ++j) now[j] = k[j];
+                i += 8u * kSumThreads;
+                if (i < n)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) set(k[j]);
+                    for (uint32_t j = 0; j < 8u; ++j) k[j] = keys[min(i + j * kSumThreads, n - 1u)];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) set(now[j]);
             }
-            for (; i < n; i += kSumThreads) set(keys[i]);
             __syncthreads();
             const bool joined = piece.w != 0xFFFFFFFFu;
             if (joined) {
@@ -948,7 +976,7 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, i
             double own[kSetRow];
 #pragma unroll
             for (int k = 0; k < kSetRow; ++k) own[k] = 0.0;
-            add_bitmap(data, bin, inv_mean, terms, b, table, wave_last, own);
+            add_bitmap(data, bin, inv_mean, terms, b, counted, wave_last, own);
             if (joined) {                                                     // which workgroup is last is not fixed: a row of its own
                 const double v = block_sum<kSumThreads>(own, red, terms);
                 if (tid < kSetRow) b.sums[(size_t)(kSumWorkgroups + piece.w) * kSetRow + tid] = v;
