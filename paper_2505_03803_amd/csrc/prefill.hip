@@ -7,10 +7,10 @@
 // binary32; VQ: the fp16 codebook entry) rounded once, to nearest even, to the type of x.
 //
 // Tiling: workgroup = 256 threads = 2 x 2 wavefronts, block tile 256 (m) x 256 (n) x 64 (k),
-// wavefront tile 128 x 128 = 8 x 8 MFMA tiles (256 accumulator registers).  A second instance
-// with 128 rows of x per workgroup (wavefront tile 64 x 128) serves launches that would otherwise
-// leave compute units without a tile; the launcher picks per launch (pick_bm).  Both operand tiles
-// live in LDS as 256 rows of 128 bytes (64 k), with the eight 16-byte chunks of a row stored at
+// wavefront tile 128 x 128 = 8 x 8 MFMA tiles (256 accumulator registers).  Two more instances,
+// 256 x 128 (wavefront tile 128 x 64) and 128 x 256, serve launches that would otherwise
+// leave compute units without a tile; the launcher picks per launch (pick_shape).  Both operand tiles
+// live in LDS as rows of 128 bytes (64 k), with the eight 16-byte chunks of a row stored at
 // chunk ^ (row & 7), so that the 16-row fragment reads of the 16 x 16 x 32 MFMAs and the tile
 // writes are free of bank conflicts without padding (the conflict counter reads zero).
 //   * activations: copied global -> LDS by the load unit itself (global_load_lds_dwordx4), no
@@ -33,21 +33,25 @@
 namespace rwkvq {
 
 constexpr int kPfMaxMats = 64;
-constexpr int BN = 256;                        // rows of W of a block tile; the k-step is 64 columns
-constexpr int kTileBytes = 256 * kRowBytes;    // one operand tile (32 KB)
+// A wavefront tile is MF x NB tiles of 16 x 16 (rows of x, rows of W), a block tile twice that in each direction; the k-step is 64
+// columns.
+constexpr int wg_rows_w(int NB) { return 32 * NB; }
+constexpr int kTileBytes = 256 * kRowBytes;    // an activation tile (32 KB)
+constexpr int w_tile_bytes(int NB) { return wg_rows_w(NB) * kRowBytes; }
+constexpr int row_tiles(int NB) { return NB / 2; }         // of 16 rows of W that a wavefront unpacks
 constexpr int kCb8Bytes = 1024;                // converted 8-bit-index codebook
 // Activation tiles in LDS: three (the copy of a k-step is issued two k-steps ahead of its use, so
 // that its round trip to the cache hides behind a whole k-step of MFMAs) except with 8-bit VQ,
-// whose converted codebooks take the room of the third.
-constexpr int x_buffers(int fmt) { return fmt == FMT_VQ8 ? 2 : 3; }
-constexpr int pf_lds_bytes(int fmt) { return (2 + x_buffers(fmt)) * kTileBytes + (fmt == FMT_VQ8 ? 2 * kCb8Bytes : 0); }
+// whose converted codebooks take the room of the third beside tiles of 256 rows of W.
+constexpr int x_buffers(int fmt, int NB) { return fmt == FMT_VQ8 && NB == 8 ? 2 : 3; }
+constexpr int pf_lds_bytes(int fmt, int NB) { return 2 * w_tile_bytes(NB) + x_buffers(fmt, NB) * kTileBytes + (fmt == FMT_VQ8 ? 2 * kCb8Bytes : 0); }
 
 struct PfMat {
     const uint32_t* codes;
     const uint16_t* aux;
     const void* x;
     void* y;
-    int N, K, fmt, pad;
+    int N, K, fmt, first;       // first: row of W at which the launch begins
 };
 struct PfArgs {
     int wg_end[kPfMaxMats];
@@ -55,24 +59,24 @@ struct PfArgs {
     int M, ydt, m_tiles, pad;
 };
 
-// Packed words of one 256-column tile for the 4 row tiles (of 16 rows) a thread unpacks.
-template <int FMT> struct WRegs;
-template <> struct WRegs<FMT_SQ3> { uint4_t a[4]; uint2_t b[4]; uint2_t sz[4]; };   // sz: (scale,zero) x 2 units
-template <> struct WRegs<FMT_VQ6> { uint4_t a[4]; uint2_t b[4]; uint32_t cb; };     // cb: codebook entry `lane`
-template <> struct WRegs<FMT_VQ8> { uint4_t a[4]; uint4_t b[4]; uint4_t cb8; };     // cb8: entries 4*lane..+3
+// Packed words of one 256-column tile for the RT row tiles (of 16 rows) a thread unpacks.
+template <int FMT, int RT> struct WRegs;
+template <int RT> struct WRegs<FMT_SQ3, RT> { uint4_t a[RT]; uint2_t b[RT]; uint2_t sz[RT]; };   // sz: (scale,zero) x 2 units
+template <int RT> struct WRegs<FMT_VQ6, RT> { uint4_t a[RT]; uint2_t b[RT]; uint32_t cb; };     // cb: codebook entry `lane`
+template <int RT> struct WRegs<FMT_VQ8, RT> { uint4_t a[RT]; uint4_t b[RT]; uint4_t cb8; };     // cb8: entries 4*lane..+3
 
-// Where a wavefront finds its packed words: uniform tile pointers for its 4 row tiles.
-struct WSrc {
-    const uint32_t* rows[4];   // start of row tile R0 + 4*wave + i (advance by tile words per T)
-    const uint16_t* aux;       // SQ: scale/zero of row tile R0 + 4*wave (16 uint2 per tile and T); VQ: codebooks of the block row
+// Where a wavefront finds its packed words: uniform tile pointers for its row tiles.
+template <int RT> struct WSrc {
+    const uint32_t* rows[RT];  // start of row tile R0 + RT*wave + i (advance by tile words per T)
+    const uint16_t* aux;       // SQ: scale/zero of row tile R0 + RT*wave (16 uint2 per tile and T); VQ: codebooks of the block row
     int KT;
 };
 
-template <int FMT>
-__device__ __forceinline__ void w_load(WRegs<FMT>& r, const WSrc& src, int T, int lane) {
+template <int FMT, int RT>
+__device__ __forceinline__ void w_load(WRegs<FMT, RT>& r, const WSrc<RT>& src, int T, int lane) {
     constexpr int tw = FMT == FMT_VQ8 ? 512 : 384;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RT; ++i) {
         const uint32_t* tile = src.rows[i] + (size_t)T * tw;
         r.a[i] = *(const uint4_t*)(tile + 4 * lane);
         if constexpr (FMT == FMT_VQ8) r.b[i] = *(const uint4_t*)(tile + 256 + 4 * lane);
@@ -80,7 +84,7 @@ __device__ __forceinline__ void w_load(WRegs<FMT>& r, const WSrc& src, int T, in
     }
     if constexpr (FMT == FMT_SQ3) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < RT; ++i)
             r.sz[i] = ((const uint2_t*)src.aux + ((size_t)i * src.KT + T) * 16)[lane & 15];
     } else if constexpr (FMT == FMT_VQ6) {
         r.cb = ((const uint32_t*)src.aux + (size_t)T * 64)[lane];
@@ -90,17 +94,16 @@ __device__ __forceinline__ void w_load(WRegs<FMT>& r, const WSrc& src, int T, in
 }
 
 // Unpack k-step KQ (0..3: 64 columns) of the tile held in r and write it to the W tile in LDS.
-// Row tiles I0 .. I1-1 of the thread's four (so that the work can be spread over a k-step).
-template <bool BF16, int FMT, int KQ, int I0 = 0, int I1 = 4>
-__device__ __forceinline__ void w_unpack(const WRegs<FMT>& r, char* wt, const uint32_t* cb8, int wave, int lane) {
+template <bool BF16, int FMT, int KQ, int RT>
+__device__ __forceinline__ void w_unpack(const WRegs<FMT, RT>& r, char* wt, const uint32_t* cb8, int wave, int lane) {
     constexpr int u = KQ >> 1, t0 = 2 * (KQ & 1);
-    const int row0 = 64 * wave + (lane & 15), kg = lane >> 4;
-    // rows row0 + 16 i share row & 7, so the two chunk offsets are the same for all four
+    const int row0 = 16 * RT * wave + (lane & 15), kg = lane >> 4;
+    // rows row0 + 16 i share row & 7, so the two chunk offsets are the same for all of them
     char* d0 = wt + tile_off(row0, kg);
     char* d1 = wt + tile_off(row0, 4 + kg);
     if constexpr (FMT == FMT_SQ3) {
 #pragma unroll
-        for (int i = I0; i < I1; ++i) {
+        for (int i = 0; i < RT; ++i) {
             const uint32_t w0 = u == 0 ? r.a[i].x : r.a[i].w, w1 = u == 0 ? r.a[i].y : r.b[i].x,
                            w2 = u == 0 ? r.a[i].z : r.b[i].y;
             const uint32_t szw = u == 0 ? r.sz[i].x : r.sz[i].y;
@@ -111,7 +114,7 @@ __device__ __forceinline__ void w_unpack(const WRegs<FMT>& r, char* wt, const ui
     } else if constexpr (FMT == FMT_VQ6) {
         const uint32_t cb = Elem<BF16>::from_f16x2(r.cb);
 #pragma unroll
-        for (int i = I0; i < I1; ++i) {
+        for (int i = 0; i < RT; ++i) {
             const uint32_t w0 = u == 0 ? r.a[i].x : r.a[i].w, w1 = u == 0 ? r.a[i].y : r.b[i].x,
                            w2 = u == 0 ? r.a[i].z : r.b[i].y;
             *(uint4_t*)(d0 + 16 * i * kRowBytes) = vq6_chunk<t0>(w0, w1, w2, cb);
@@ -119,7 +122,7 @@ __device__ __forceinline__ void w_unpack(const WRegs<FMT>& r, char* wt, const ui
         }
     } else {
 #pragma unroll
-        for (int i = I0; i < I1; ++i) {
+        for (int i = 0; i < RT; ++i) {
             const uint32_t wa = u == 0 ? (t0 == 0 ? r.a[i].x : r.a[i].z) : (t0 == 0 ? r.b[i].x : r.b[i].z);
             const uint32_t wb = u == 0 ? (t0 == 0 ? r.a[i].y : r.a[i].w) : (t0 == 0 ? r.b[i].y : r.b[i].w);
             *(uint4_t*)(d0 + 16 * i * kRowBytes) = vq8_chunk(wa, cb8);
@@ -128,7 +131,7 @@ __device__ __forceinline__ void w_unpack(const WRegs<FMT>& r, char* wt, const ui
     }
 }
 
-// The same work cut into 128 micro-slices, one per MFMA of the previous k-step (see mma_step): a
+// The same work cut into 32 micro-slices per row tile, one per MFMA of the previous k-step (see mma_step): a
 // weight pair takes four of them (mask / address; subtract the zero point or start the look-up;
 // scale; pack and, every fourth pair, store the finished 16-byte chunk).  Micro-slice S works on
 // pair (S / 4) % 4 of chunk (S / 16) % 2 of row tile S / 32.  Each is two or three vector
@@ -142,16 +145,16 @@ template <int FMT> struct UnpackState {
     uint32_t cb;              // VQ6: the lane's codebook entry, converted to the operand type
 };
 
-template <bool BF16, int FMT>
-__device__ __forceinline__ void unpack_begin(UnpackState<FMT>& st, const WRegs<FMT>& r, char* wt, int wave, int lane) {
-    const int row0 = 64 * wave + (lane & 15), kg = lane >> 4;
+template <bool BF16, int FMT, int RT>
+__device__ __forceinline__ void unpack_begin(UnpackState<FMT>& st, const WRegs<FMT, RT>& r, char* wt, int wave, int lane) {
+    const int row0 = 16 * RT * wave + (lane & 15), kg = lane >> 4;
     st.d0 = wt + tile_off(row0, kg);
     st.d1 = wt + tile_off(row0, 4 + kg);
     if constexpr (FMT == FMT_VQ6) st.cb = Elem<BF16>::from_f16x2(r.cb);
 }
 
-template <bool BF16, int FMT, int KQ, int S>
-__device__ __forceinline__ void unpack_micro(UnpackState<FMT>& st, const WRegs<FMT>& r, const uint32_t* cb8) {
+template <bool BF16, int FMT, int KQ, int S, int RT>
+__device__ __forceinline__ void unpack_micro(UnpackState<FMT>& st, const WRegs<FMT, RT>& r, const uint32_t* cb8) {
     constexpr int u = KQ >> 1, t0 = 2 * (KQ & 1);
     constexpr int i = S >> 5, c = (S >> 4) & 1, p = (S >> 2) & 3, q = S & 3, P = 4 * (t0 + c) + p;
     if constexpr (FMT == FMT_SQ3) {
@@ -217,17 +220,14 @@ __device__ __forceinline__ void x_tile_dma(const char* xk, const uint32_t (&xoff
                                          16, 0, 0);
 }
 
-// One k-step (64 columns) of the wavefront tile = 16 rows of 8 MFMAs: x fragment f (f = 0..15:
-// m-subtile f%8 of column half f/8) against the eight W fragments of that half.  x fragments are
-// read kAhead rows ahead of their use and the W fragments of the second half during rows 4..7,
-// so that an LDS round trip is hidden behind several rows of MFMAs.  `early` runs right after
-// the first LDS reads have been issued and `mid` between the halves: vector-ALU work placed
-// there (unpacking the next k-step) covers more latency.
+// One k-step (64 columns) of the wavefront tile = 2 MF rows of NB MFMAs: x fragment f (m-subtile f % MF of column half f / MF)
+// against the NB W fragments of that half.  x fragments are read kAhead rows ahead of their use and the W fragments of the second
+// half during the last four rows of the first, so that an LDS round trip is hidden behind several rows of MFMAs.
 constexpr int kAhead = 3;
 template <int S> struct SliceTag { static constexpr int value = S; };
 
-template <bool BF16, int MF, int F, int NI, class Slice>
-__device__ __forceinline__ void mma_one(const uint4_t (&b)[8], const uint4_t af, float4_t (&acc)[MF][8], Slice& slice) {
+template <bool BF16, int MF, int NB, int F, int NI, class Slice>
+__device__ __forceinline__ void mma_one(const uint4_t (&b)[NB], const uint4_t af, float4_t (&acc)[MF][NB], Slice& slice) {
     // One MFMA of x fragment F, then one micro-slice of vector-ALU work, fenced so that the
     // instruction scheduler leaves it there: a wavefront issues in order, and only the two or
     // three instructions placed right behind an MFMA run while the matrix core is busy with it
@@ -236,59 +236,55 @@ __device__ __forceinline__ void mma_one(const uint4_t (&b)[8], const uint4_t af,
     Elem<BF16>::mfma(b[NI], af, acc[F % MF][NI]);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (MF == 8) {
-        slice(SliceTag<8 * F + NI>{});
-    } else {                                       // half as many MFMAs per k-step: two micro-slices behind each
-        slice(SliceTag<2 * (8 * F + NI)>{});
-        slice(SliceTag<2 * (8 * F + NI) + 1>{});
+        slice(SliceTag<NB * F + NI>{});
+    } else {                                       // half the rows of x, half as many MFMAs: two micro-slices behind each
+        slice(SliceTag<2 * (NB * F + NI)>{});
+        slice(SliceTag<2 * (NB * F + NI) + 1>{});
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (NI < 7) mma_one<BF16, MF, F, NI + 1>(b, af, acc, slice);
+    if constexpr (NI < NB - 1) mma_one<BF16, MF, NB, F, NI + 1>(b, af, acc, slice);
 }
-template <bool BF16, int MF, int F, class Slice>
-__device__ __forceinline__ void mma_row(const uint4_t (&b)[8], const uint4_t af, float4_t (&acc)[MF][8], Slice& slice) {
-    mma_one<BF16, MF, F, 0>(b, af, acc, slice);
+template <bool BF16, int MF, int NB, int F, class Slice>
+__device__ __forceinline__ void mma_row(const uint4_t (&b)[NB], const uint4_t af, float4_t (&acc)[MF][NB], Slice& slice) {
+    mma_one<BF16, MF, NB, F, 0>(b, af, acc, slice);
 }
 
-template <bool BF16, int MF, int F, class Slice>
-__device__ __forceinline__ void mma_rows(const char* const (&xa)[2], const char* wb1, uint4_t (&b)[8], uint4_t (&b1)[8],
-                                         uint4_t (&a)[kAhead + 1], float4_t (&acc)[MF][8], Slice& slice) {
+template <bool BF16, int MF, int NB, int F, class Slice>
+__device__ __forceinline__ void mma_rows(const char* const (&xa)[2], const char* wb1, uint4_t (&b)[NB], uint4_t (&b1)[NB],
+                                         uint4_t (&a)[kAhead + 1], float4_t (&acc)[MF][NB], Slice& slice) {
     if constexpr (F < 2 * MF) {
         if constexpr (F + kAhead < 2 * MF)
             a[(F + kAhead) % (kAhead + 1)] = *(const uint4_t*)(xa[(F + kAhead) / MF] + 16 * ((F + kAhead) % MF) * kRowBytes);
         if constexpr (F >= MF - 4 && F < MF) {                  // the last four rows of the first half
             constexpr int J = F - (MF - 4);
-            b1[2 * J] = *(const uint4_t*)(wb1 + 16 * (2 * J) * kRowBytes);
-            b1[2 * J + 1] = *(const uint4_t*)(wb1 + 16 * (2 * J + 1) * kRowBytes);
+#pragma unroll
+            for (int q = J * NB / 4; q < (J + 1) * NB / 4; ++q) b1[q] = *(const uint4_t*)(wb1 + 16 * q * kRowBytes);
         }
-        if constexpr (F < MF) mma_row<BF16, MF, F>(b, a[F % (kAhead + 1)], acc, slice);
-        else mma_row<BF16, MF, F>(b1, a[F % (kAhead + 1)], acc, slice);
-        mma_rows<BF16, MF, F + 1>(xa, wb1, b, b1, a, acc, slice);
+        if constexpr (F < MF) mma_row<BF16, MF, NB, F>(b, a[F % (kAhead + 1)], acc, slice);
+        else mma_row<BF16, MF, NB, F>(b1, a[F % (kAhead + 1)], acc, slice);
+        mma_rows<BF16, MF, NB, F + 1>(xa, wb1, b, b1, a, acc, slice);
     }
 }
 
-// One k-step (64 columns) of the wavefront tile = 16 rows of 8 MFMAs: x fragment f (f = 0..15:
-// m-subtile f%8 of column half f/8) against the eight W fragments of that half.  x fragments are
-// read kAhead rows ahead of their use and the W fragments of the second half during rows 4..7,
-// so that an LDS round trip is hidden behind several rows of MFMAs.  `slice(SliceTag<S>)`, S =
-// 0..127, is called after MFMA S: the unpacking of the next k-step goes there.
-template <bool BF16, int MF, class Slice>
+// The k-step.  `slice(SliceTag<S>)` is called after MFMA S: the unpacking of the next k-step goes there.
+template <bool BF16, int MF, int NB, class Slice>
 __device__ __forceinline__ void mma_step(const char* xt, const char* wt, int wm, int wn, int lane,
-                                         float4_t (&acc)[MF][8], Slice slice) {
+                                         float4_t (&acc)[MF][NB], Slice slice) {
     const int r = lane & 15, kg = lane >> 4;
     const char* const xa[2] = {xt + tile_off(16 * MF * wm + r, kg), xt + tile_off(16 * MF * wm + r, 4 + kg)};
-    const char* wb0 = wt + tile_off(128 * wn + r, kg);
-    const char* wb1 = wt + tile_off(128 * wn + r, 4 + kg);
-    uint4_t b[8], b1[8], a[kAhead + 1];
+    const char* wb0 = wt + tile_off(16 * NB * wn + r, kg);
+    const char* wb1 = wt + tile_off(16 * NB * wn + r, 4 + kg);
+    uint4_t b[NB], b1[NB], a[kAhead + 1];
 #pragma unroll
-    for (int ni = 0; ni < 8; ++ni) b[ni] = *(const uint4_t*)(wb0 + 16 * ni * kRowBytes);
+    for (int ni = 0; ni < NB; ++ni) b[ni] = *(const uint4_t*)(wb0 + 16 * ni * kRowBytes);
 #pragma unroll
     for (int f = 0; f < kAhead; ++f) a[f] = *(const uint4_t*)(xa[0] + 16 * f * kRowBytes);
-    mma_rows<BF16, MF, 0>(xa, wb1, b, b1, a, acc, slice);
+    mma_rows<BF16, MF, NB, 0>(xa, wb1, b, b1, a, acc, slice);
 }
 
 // Convert and stage the 8-bit-index codebook of a tile (256 entries) into LDS.
-template <bool BF16>
-__device__ __forceinline__ void cb8_store(const WRegs<FMT_VQ8>& r, uint32_t* cb8, int wave, int lane) {
+template <bool BF16, int RT>
+__device__ __forceinline__ void cb8_store(const WRegs<FMT_VQ8, RT>& r, uint32_t* cb8, int wave, int lane) {
     if (wave == 0) {
         uint4_t c = {Elem<BF16>::from_f16x2(r.cb8.x), Elem<BF16>::from_f16x2(r.cb8.y),
                      Elem<BF16>::from_f16x2(r.cb8.z), Elem<BF16>::from_f16x2(r.cb8.w)};
@@ -298,17 +294,18 @@ __device__ __forceinline__ void cb8_store(const WRegs<FMT_VQ8>& r, uint32_t* cb8
 
 // All matrices of one launch have the format FMT.  The k loop has no conditionals: past the last
 // column tile the prefetches simply fetch the last tile again (never used).
-// MF = 16-row m-subtiles per wavefront: 8 (block tile 256 x 256) or 4 (128 x 256, for launches that
-// would leave compute units without a tile: the same W work per workgroup on half the MFMAs).
-template <bool BF16, int FMT, int MF>
+// Block tiles (rows of x x rows of W): 256 x 256 (MF = NB = 8); for launches that would leave compute units without a tile 256 x 128
+// (NB = 4: half the unpack with half the MFMAs) and, where fewer rows of x are padded that way, 128 x 256 (MF = 4: the same
+// unpack on half the MFMAs).  All sum over k in the same order.
+template <bool BF16, int FMT, int MF, int NB>
 __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
-    constexpr int BMk = 32 * MF;                           // rows of x per workgroup
+    constexpr int BMk = 32 * MF, BN = wg_rows_w(NB), RT = row_tiles(NB);      // rows of x and of W per workgroup
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    constexpr int XB = x_buffers(FMT), LA = XB - 1;       // LA = k-steps between a copy and its use
+    constexpr int XB = x_buffers(FMT, NB), LA = XB - 1;       // LA = k-steps between a copy and its use
     char* const wt0 = lds;
-    char* const wt1 = lds + kTileBytes;
-    char* const xbase = lds + 2 * kTileBytes;
-    uint32_t* const cb8base = (uint32_t*)(lds + (2 + XB) * kTileBytes);
+    char* const wt1 = lds + w_tile_bytes(NB);
+    char* const xbase = lds + 2 * w_tile_bytes(NB);
+    uint32_t* const cb8base = (uint32_t*)(xbase + XB * kTileBytes);
 #define CB8(i) (cb8base + ((i) & 1) * (kCb8Bytes / 4))
 
     const int wg = blockIdx.x;
@@ -316,7 +313,7 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
     const int mi_ = __builtin_popcountll(__builtin_amdgcn_ballot_w64(wg >= a.wg_end[threadIdx.x & 63]));
     const PfMat mt = a.m[mi_];
     const int local = wg - (mi_ ? a.wg_end[mi_ - 1] : 0);
-    const int m0 = (local % a.m_tiles) * BMk, n0 = (local / a.m_tiles) * BN;
+    const int m0 = (local % a.m_tiles) * BMk, n0 = mt.first + (local / a.m_tiles) * BN;
     const int M = a.M, K = mt.K, KT = K >> 8, R0 = n0 >> 4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
@@ -332,20 +329,20 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
     }
     const char* xrow0 = (const char*)mt.x + (size_t)m0 * K * 2;
 
-    WSrc src;
+    WSrc<RT> src;
     constexpr int tw = FMT == FMT_VQ8 ? 512 : 384;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) src.rows[i] = mt.codes + (size_t)(R0 + 4 * wave + i) * KT * tw;
+    for (int i = 0; i < RT; ++i) src.rows[i] = mt.codes + (size_t)(R0 + RT * wave + i) * KT * tw;
     src.KT = KT;
-    if constexpr (FMT == FMT_SQ3) src.aux = (const uint16_t*)((const uint2_t*)mt.aux + (size_t)(R0 + 4 * wave) * KT * 16);
+    if constexpr (FMT == FMT_SQ3) src.aux = (const uint16_t*)((const uint2_t*)mt.aux + (size_t)(R0 + RT * wave) * KT * 16);
     else if constexpr (FMT == FMT_VQ6) src.aux = (const uint16_t*)((const uint32_t*)mt.aux + (size_t)(R0 >> 4) * KT * 64);
     else src.aux = (const uint16_t*)((const uint4_t*)mt.aux + (size_t)(R0 >> 4) * KT * 64);
 
-    float4_t acc[MF][8];
+    float4_t acc[MF][NB];
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = float4_t{0, 0, 0, 0};
+        for (int j = 0; j < NB; ++j) acc[i][j] = float4_t{0, 0, 0, 0};
 
     // The activation buffers form a ring (byte offsets from xbase): x0 holds the k-step being
     // multiplied, x1 the next one, x2 (three buffers) the one after.  A k-step's copy is issued LA
@@ -361,9 +358,9 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
     };
 
     // prologue: packed words of tile 0, k-step 0 (and 1) of the activations, k-step 0 of W
-    WRegs<FMT> wr;
+    WRegs<FMT, RT> wr;
     UnpackState<FMT> us;
-    w_load<FMT>(wr, src, 0, lane);
+    w_load<FMT, RT>(wr, src, 0, lane);
     x_tile_dma<MF>(xk(0), xoff, xbase + x0, wave);
     if (LA == 2) x_tile_dma<MF>(xk(1), xoff, xbase + x1, wave);
     if constexpr (FMT == FMT_VQ8) {
@@ -371,7 +368,7 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
         RWKVQ_WAIT_VM0_LGKM0();
         RWKVQ_BARRIER();
     }
-    w_unpack<BF16, FMT, 0>(wr, wt0, CB8(0), wave, lane);
+    w_unpack<BF16, FMT, 0, RT>(wr, wt0, CB8(0), wave, lane);
     RWKVQ_WAIT_VM0_LGKM0();
     RWKVQ_BARRIER();
 
@@ -385,7 +382,7 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
             const char* xsrc = xk(g + LA);
             char* xdst = xbase + (LA == 2 ? x2 : x1);
             unpack_begin<BF16, FMT>(us, wr, wt1, wave, lane);
-            mma_step<BF16, MF>(xbase + x0, wt0, wm, wn, lane, acc, [&](auto tag) {
+            mma_step<BF16, MF, NB>(xbase + x0, wt0, wm, wn, lane, acc, [&](auto tag) {
                 constexpr int S = decltype(tag)::value;
                 if constexpr (S % 8 == 4 && S / 8 < MF) x_tile_dma_one<S / 8>(xsrc, xoff, xdst, wave);
                 unpack_micro<BF16, FMT, 1, S>(us, wr, CB8(T));
@@ -399,7 +396,7 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
             const char* xsrc = xk(g + 1 + LA);
             char* xdst = xbase + (LA == 2 ? x2 : x1);
             unpack_begin<BF16, FMT>(us, wr, wt0, wave, lane);
-            mma_step<BF16, MF>(xbase + x0, wt1, wm, wn, lane, acc, [&](auto tag) {
+            mma_step<BF16, MF, NB>(xbase + x0, wt1, wm, wn, lane, acc, [&](auto tag) {
                 constexpr int S = decltype(tag)::value;
                 if constexpr (S % 8 == 4 && S / 8 < MF) x_tile_dma_one<S / 8>(xsrc, xoff, xdst, wave);
                 unpack_micro<BF16, FMT, 2, S>(us, wr, CB8(T));
@@ -413,7 +410,7 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
             const char* xsrc = xk(g + 2 + LA);
             char* xdst = xbase + (LA == 2 ? x2 : x1);
             unpack_begin<BF16, FMT>(us, wr, wt1, wave, lane);
-            mma_step<BF16, MF>(xbase + x0, wt0, wm, wn, lane, acc, [&](auto tag) {
+            mma_step<BF16, MF, NB>(xbase + x0, wt0, wm, wn, lane, acc, [&](auto tag) {
                 constexpr int S = decltype(tag)::value;
                 if constexpr (S % 8 == 4 && S / 8 < MF) x_tile_dma_one<S / 8>(xsrc, xoff, xdst, wave);
                 unpack_micro<BF16, FMT, 3, S>(us, wr, CB8(T));
@@ -426,11 +423,11 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
         // the packed words of this tile are spent: fetch the next tile's into the same registers
         // (before the activation copy, so that waiting for them leaves the copy in flight); they
         // have a whole MFMA step to arrive
-        w_load<FMT>(wr, src, Tn, lane);
+        w_load<FMT, RT>(wr, src, Tn, lane);
         {
             const char* xsrc = xk(g + 3 + LA);
             char* xdst = xbase + (LA == 2 ? x2 : x1);
-            mma_step<BF16, MF>(xbase + x0, wt1, wm, wn, lane, acc, [&](auto tag) {
+            mma_step<BF16, MF, NB>(xbase + x0, wt1, wm, wn, lane, acc, [&](auto tag) {
                 constexpr int S = decltype(tag)::value;
                 if constexpr (S % 8 == 4 && S / 8 < MF) x_tile_dma_one<S / 8>(xsrc, xoff, xdst, wave);
             });
@@ -442,7 +439,7 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
         } else {
             wait_step();                                   // the packed words have landed
         }
-        w_unpack<BF16, FMT, 0>(wr, wt0, CB8(T + 1), wave, lane);
+        w_unpack<BF16, FMT, 0, RT>(wr, wt0, CB8(T + 1), wave, lane);
         wait_step();
         RWKVQ_BARRIER();
         rotate();
@@ -461,8 +458,8 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
         const int m = m0 + 16 * MF * wm + 16 * mi + (lane & 15);
         if (m < M) {
 #pragma unroll
-            for (int ni = 0; ni < 8; ++ni) {
-                const size_t o = (size_t)m * N + n0 + 128 * wn + 16 * ni + 4 * (lane >> 4);
+            for (int ni = 0; ni < NB; ++ni) {
+                const size_t o = (size_t)m * N + n0 + 16 * NB * wn + 16 * ni + 4 * (lane >> 4);
                 const float4_t v = acc[mi][ni];
                 if (a.ydt == DT_F32) {
                     *(float4_t*)((float*)mt.y + o) = v;
@@ -480,32 +477,41 @@ __global__ void __launch_bounds__(256, 1) prefill_kernel(PfArgs a) {
 
 // The kernels need more dynamic LDS than the default limit: raised once per kernel and device.  Two
 // threads that get here together both raise it, which is harmless.
-template <bool BF16, int FMT, int MF>
-static hipError_t launch_fmt_mf(const PfArgs& a, int wgs, hipStream_t s) {
+template <bool BF16, int FMT, int MF, int NB>
+static hipError_t launch_shape(const PfArgs& a, int wgs, hipStream_t s) {
     static std::atomic<unsigned long long> raised{0ull};
-    const hipError_t e = raise_lds((const void*)prefill_kernel<BF16, FMT, MF>, pf_lds_bytes(FMT), raised);
+    const hipError_t e = raise_lds((const void*)prefill_kernel<BF16, FMT, MF, NB>, pf_lds_bytes(FMT, NB), raised);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((prefill_kernel<BF16, FMT, MF>), dim3(wgs), dim3(256), pf_lds_bytes(FMT), s, a);
+    hipLaunchKernelGGL((prefill_kernel<BF16, FMT, MF, NB>), dim3(wgs), dim3(256), pf_lds_bytes(FMT, NB), s, a);
     return hipGetLastError();
 }
+
+// Rows of x and of W per workgroup, and the duration of a column tile in units of that of 256 x 256.
+struct PfShape { int bm, bn; double cost; };
 template <bool BF16, int FMT>
-static hipError_t launch_fmt(const PfArgs& a, int wgs, int mf, hipStream_t s) {
-    return mf == 8 ? launch_fmt_mf<BF16, FMT, 8>(a, wgs, s) : launch_fmt_mf<BF16, FMT, 4>(a, wgs, s);
+static hipError_t launch_fmt(const PfArgs& a, int wgs, const PfShape& p, hipStream_t s) {
+    return p.bm == 128 ? launch_shape<BF16, FMT, 4, 8>(a, wgs, s) : p.bn == 128 ? launch_shape<BF16, FMT, 8, 4>(a, wgs, s)
+                                                                  : launch_shape<BF16, FMT, 8, 8>(a, wgs, s);
 }
 
-// Rows of x per workgroup for a launch whose matrices have `n_tiles` tiles of 256 rows of W in all.
-// One workgroup runs per compute unit, so a launch takes about ceil(workgroups / 256) rounds; a round
-// of 128-row workgroups does half the MFMAs of a 256-row round at 0.71 of its rate (measured on the
-// 7B stack: the W tile is unpacked once per workgroup either way), i.e. costs 0.705 of it.  The
-// cheaper of the two wins: 128 rows for launches that would leave compute units without a tile
-// (one 4096 x 4096 matrix at M = 2048 is 128 tiles) and for short M.
-// rwkvq_set_option(RWKVQ_OPT_PREFILL_TILE_ROWS, 128 | 256) overrides the choice (tests run both kernels).
-static int pick_bm(int M, long long n_tiles) {
+// The shape for a launch whose matrices have `n_tiles` tiles of 256 rows of W in all.  One workgroup runs per compute unit, so a
+// launch takes about ceil(workgroups / 256) rounds, and the cheapest of the three wins.  Measured on the 7B stack (cost of a
+// column tile): half the rows of x do half the MFMAs at 0.71 of the rate, since the W tile is unpacked once per workgroup either
+// way; half the rows of W, with half the unpack, cost 0.645 (4096 x 4096 at M = 2048 85 -> 74 us,
+// 4096 x 14336 267 -> 232, 6-bit VQ 283 -> 225).
+// rwkvq_set_option(RWKVQ_OPT_PREFILL_TILE_ROWS, 128 | 256) takes 128 x 256 or 256 x 256 (tests run both kernels).
+constexpr PfShape kShapes[3] = {{256, 256, 1.0}, {128, 256, 0.705}, {256, 128, 0.645}};
+static double rounds(long long wgs) { return (double)((wgs + 255) / 256); }
+static PfShape pick_shape(int M, long long n_tiles) {
     const int forced = option(RWKVQ_OPT_PREFILL_TILE_ROWS);
-    if (forced == 128 || forced == 256) return forced;
-    const long long wg256 = n_tiles * ((M + 255) / 256), wg128 = n_tiles * ((M + 127) / 128);
-    const double t256 = (double)((wg256 + 255) / 256), t128 = 0.705 * (double)((wg128 + 255) / 256);
-    return t128 < t256 ? 128 : 256;
+    if (forced == 128 || forced == 256) return kShapes[forced == 128];
+    PfShape best = kShapes[0];
+    double least = 1e30;
+    for (const PfShape& p : kShapes) {
+        const double t = p.cost * rounds(n_tiles * (256 / p.bn) * ((M + p.bm - 1) / p.bm));
+        if (t < least) { least = t; best = p; }
+    }
+    return best;
 }
 
 // Estimated duration here: one launch per format and 64 matrices, 7.4 us per column tile of a 256-row workgroup.
@@ -518,13 +524,13 @@ static double tiles_us(const std::vector<MatDev>& mats, int M) {
             int cnt = 0;
             size_t end = i;
             for (; end < mats.size() && cnt < kPfMaxMats; ++end)
-                if (mats[end].fmt == fmt) { n_tiles += mats[end].N / BN; ++cnt; }
+                if (mats[end].fmt == fmt) { n_tiles += mats[end].N / 256; ++cnt; }
             if (cnt) {
-                const int bm = pick_bm(M, n_tiles);
+                const PfShape p = pick_shape(M, n_tiles);
                 LaunchLoad load;
                 for (size_t j = i; j < end; ++j)
-                    if (mats[j].fmt == fmt) load.add((long long)(mats[j].N / BN) * ((M + bm - 1) / bm), mats[j].K);
-                us += 3.0 + load.columns(0.2) * (bm == 256 ? 7.4 : 0.705 * 7.4);
+                    if (mats[j].fmt == fmt) load.add((long long)(mats[j].N / p.bn) * ((M + p.bm - 1) / p.bm), mats[j].K);
+                us += 3.0 + load.columns(0.2) * p.cost * 7.4;
             }
             i = end;
         }
@@ -544,43 +550,57 @@ static double tiles_us(const std::vector<MatDev>& mats, int M) {
 constexpr int kMidMaxM = 1536;
 static bool mid_takes(const MatDev& m, int M) { return M <= kMidMaxM && m.K <= (1 << 20) && option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0; }
 
+// Tiles t0 .. t1 - 1 of 256 rows of W, counted through the matrices of `batch`, all of one format.
+static hipError_t launch_batch(const std::vector<MatDev>& batch, int t0, int t1, const PfShape& p, int M, int x_dtype, int y_dtype, hipStream_t s) {
+    PfArgs a;
+    int cnt = 0, wgs = 0, at = 0;
+    a.M = M; a.ydt = y_dtype; a.m_tiles = (M + p.bm - 1) / p.bm; a.pad = 0;
+    for (const MatDev& m : batch) {
+        const int from = std::max(t0, at), to = std::min(t1, at + m.N / 256);
+        if (from < to) {
+            wgs += a.m_tiles * (to - from) * (256 / p.bn);
+            a.m[cnt] = PfMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, 256 * (from - at)};
+            a.wg_end[cnt++] = wgs;
+        }
+        at += m.N / 256;
+    }
+    for (int j = cnt; j < kPfMaxMats; ++j) {
+        a.m[j] = PfMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0};
+        a.wg_end[j] = 0x7FFFFFFF;
+    }
+    const bool bf = x_dtype == DT_BF16;
+    switch (batch[0].fmt) {
+        case FMT_SQ3: return bf ? launch_fmt<true, FMT_SQ3>(a, wgs, p, s) : launch_fmt<false, FMT_SQ3>(a, wgs, p, s);
+        case FMT_VQ6: return bf ? launch_fmt<true, FMT_VQ6>(a, wgs, p, s) : launch_fmt<false, FMT_VQ6>(a, wgs, p, s);
+        default: return bf ? launch_fmt<true, FMT_VQ8>(a, wgs, p, s) : launch_fmt<false, FMT_VQ8>(a, wgs, p, s);
+    }
+}
+
 static hipError_t launch_prefill_tiles(const MatDev* mats_in, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
     // Workgroups of a matrix with a long K run long: put those matrices first so that the end of
     // a launch is filled by short workgroups.
     std::vector<MatDev> sorted(mats_in, mats_in + n_mats);
     std::stable_sort(sorted.begin(), sorted.end(), [](const MatDev& a, const MatDev& b) { return a.K > b.K; });
-    const MatDev* mats = sorted.data();
     // one grouped launch per format and per 64 matrices
     for (int fmt = 0; fmt < 3; ++fmt) {
-        int i = 0;
-        while (i < n_mats) {
-            PfArgs a;
-            int cnt = 0, wgs = 0;
-            long long n_tiles = 0;                              // tiles along N of the launch's matrices
-            for (int j = i, c = 0; j < n_mats && c < kPfMaxMats; ++j)
-                if (mats[j].fmt == fmt) { n_tiles += mats[j].N / BN; ++c; }
-            const int bm = pick_bm(M, n_tiles);
-            const int m_tiles = (M + bm - 1) / bm;
-            for (; i < n_mats && cnt < kPfMaxMats; ++i) {
-                const MatDev& m = mats[i];
-                if (m.fmt != fmt) continue;
-                wgs += m_tiles * (m.N / BN);
-                a.m[cnt] = PfMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, 0};
-                a.wg_end[cnt] = wgs;
-                ++cnt;
-            }
-            if (cnt == 0) break;
-            for (int j = cnt; j < kPfMaxMats; ++j) {
-                a.m[j] = PfMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0};
-                a.wg_end[j] = 0x7FFFFFFF;
-            }
-            a.M = M; a.ydt = y_dtype; a.m_tiles = m_tiles; a.pad = 0;
-            hipError_t e;
-            const bool bf = x_dtype == DT_BF16;
-            if (fmt == FMT_SQ3) e = bf ? launch_fmt<true, FMT_SQ3>(a, wgs, bm / 32, s) : launch_fmt<false, FMT_SQ3>(a, wgs, bm / 32, s);
-            else if (fmt == FMT_VQ6) e = bf ? launch_fmt<true, FMT_VQ6>(a, wgs, bm / 32, s) : launch_fmt<false, FMT_VQ6>(a, wgs, bm / 32, s);
-            else e = bf ? launch_fmt<true, FMT_VQ8>(a, wgs, bm / 32, s) : launch_fmt<false, FMT_VQ8>(a, wgs, bm / 32, s);
+        std::vector<MatDev> batch;
+        for (int i = 0; i <= n_mats; ++i) {
+            if (i < n_mats && sorted[i].fmt == fmt) batch.push_back(sorted[i]);
+            if (batch.empty() || ((int)batch.size() < kPfMaxMats && i < n_mats)) continue;
+            int n_tiles = 0;
+            for (const MatDev& m : batch) n_tiles += m.N / 256;
+            const PfShape p = pick_shape(M, n_tiles);
+            // Whole rounds of 256 x 256 tiles and what is left of them in tiles of half the rows of W, where that ends sooner than a
+            // last round with a few tiles ({key, receptance} of the 7B shapes at M = 2048, 576 tiles: 344 -> 306 us).  Matrices of
+            // one K only: elsewhere the shorter ones fill the end.
+            const int m_tiles = (M + 255) / 256, whole = (int)((long long)n_tiles * m_tiles / 256 * 256 / m_tiles);
+            const bool split = option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0 && whole > 0 && whole < n_tiles && batch.front().K == batch.back().K &&
+                               rounds((long long)whole * m_tiles) + kShapes[2].cost * rounds((long long)(n_tiles - whole) * 2 * m_tiles) + 0.05 <
+                                   p.cost * rounds((long long)n_tiles * (256 / p.bn) * ((M + p.bm - 1) / p.bm));
+            hipError_t e = launch_batch(batch, 0, split ? whole : n_tiles, split ? kShapes[0] : p, M, x_dtype, y_dtype, s);
+            if (e == hipSuccess && split) e = launch_batch(batch, whole, n_tiles, kShapes[2], M, x_dtype, y_dtype, s);
             if (e != hipSuccess) return e;
+            batch.clear();
         }
     }
     return hipSuccess;
