@@ -60,75 +60,93 @@ __global__ void __launch_bounds__(64) wkv_kernel(const uint16_t* __restrict__ r,
 
 // Chunks of many tokens (prefill): the recurrence is linear in the carried sums, S_out = exp(-n w) S_in
 // + (the sums of the n tokens alone), so the tokens are cut into kChunks pieces that run side by side.
-// A workgroup owns 16 channels; thread (channel, piece) first runs its piece from the empty state,
-// 16 threads then chain the pieces (64 merges per channel) and leave the state in front of every
-// piece in LDS, and each thread runs its piece again from there, now with outputs.  Twice the
-// arithmetic, 64 times the parallelism.  The merges re-associate the sums: the result agrees with the
-// token-by-token kernel to rounding, not bit for bit.
+// A workgroup owns 16 channels; thread (channel, piece) first runs its piece from the empty state, the
+// sums in front of every piece come from a scan over the pieces in six merges, and each thread runs
+// its piece again from there, now with outputs.  Twice the arithmetic, 64 times the parallelism.
+// The merges re-associate the sums: the result agrees with the token-by-token kernel to rounding, not bit for bit.
+// What bounds it: vector ALU (about 130 instructions per token and channel).  d = 4096, bf16, us: with the pieces chained one after
+// another by 16 threads, both exponentials of a pair, no tokens in flight while others are computed and neighbouring channels on
+// different XCDs (which fetch the lines of r, k and v once each) 23 at M = 333 and 69 at M = 2048, now 12
+// and 36.
 constexpr int kChunks = 64, kWgChannels = 16;
+struct WkvSums { float a, b, p; };
+// Sums of a run of tokens and of the n tokens behind it.
+__device__ __forceinline__ WkvSums wkv_merge(const WkvSums& l, const WkvSums& r, int n, float wc) {
+    WkvSums m;
+    float e1, e2;
+    exp_pair(l.p - (float)n * wc, r.p, m.p, e1, e2);
+    m.a = e1 * l.a + e2 * r.a;
+    m.b = e1 * l.b + e2 * r.b;
+    return m;
+}
 
 template <bool BF16>
 __global__ void __launch_bounds__(kChunks * kWgChannels) wkv_chunked_kernel(
     const uint16_t* __restrict__ r, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int M, int d,
     const float* __restrict__ w, const float* __restrict__ u, float* __restrict__ state, uint16_t* __restrict__ out) {
-    __shared__ float loc[3][kChunks][kWgChannels];        // sums of piece i alone
-    __shared__ float in[3][kChunks][kWgChannels];         // sums in front of piece i
+    __shared__ float sums[2][3][kChunks][kWgChannels];    // of the pieces up to i: two buffers, written in turn
     const int cc = threadIdx.x & (kWgChannels - 1), ch = threadIdx.x / kWgChannels;
-    const int c = blockIdx.x * kWgChannels + cc;
+    const int blk = (gridDim.x & 7) ? (int)blockIdx.x : (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int c = blk * kWgChannels + cc;
     const bool live = c < d;
     const int L = (M + kChunks - 1) / kChunks;
-    const int t0 = ch * L < M ? ch * L : M, t1 = t0 + L < M ? t0 + L : M;      // piece [t0, t1), may be empty
-    const float wc = live ? w[c] : 0.f, uc = live ? u[c] : 0.f;
+    auto begin = [&](int i) { return i * L < M ? i * L : M; };
+    const int t0 = begin(ch), t1 = begin(ch + 1);                              // piece [t0, t1), may be empty
+    const int at = live ? c : 0;
+    const float wc = w[at], uc = u[at];
+    const WkvSums before = {state[at], state[(size_t)d + at], state[2 * (size_t)d + at]};
 
-    float a = 0.f, b = 0.f, p = -1e38f;
-    if (live) {
-        for (int tb = t0; tb < t1; tb += kTok) {
-            float kk[kTok], vv[kTok];
+    // eight tokens in flight while eight are computed (past the end the last one again, not used)
+    auto fetch = [&](const uint16_t* x, uint32_t (&q)[kTok], int tb) {
 #pragma unroll
-            for (int j = 0; j < kTok; ++j) {
-                const int t = tb + j < t1 ? tb + j : t1 - 1;
-                kk[j] = ld16<BF16>(k, (size_t)t * d + c); vv[j] = ld16<BF16>(v, (size_t)t * d + c);
-            }
+        for (int j = 0; j < kTok; ++j) q[j] = x[(size_t)(tb + j < t1 ? tb + j : t1 - 1) * d + at];
+    };
+    auto widen = [](uint32_t q) { return BF16 ? bf16_bits_to_f32((uint16_t)q) : f16_bits_to_f32((uint16_t)q); };
+    WkvSums s = {0.f, 0.f, -1e38f};
+    uint32_t kq[kTok], vq[kTok], rq[kTok], kn[kTok], vn[kTok], rn[kTok];
+    if (t0 < t1) {
+        fetch(k, kn, t0); fetch(v, vn, t0);
+#pragma unroll 1
+        for (int tb = t0; tb < t1; tb += kTok) {
+#pragma unroll
+            for (int j = 0; j < kTok; ++j) { kq[j] = kn[j]; vq[j] = vn[j]; }
+            if (tb + kTok < t1) { fetch(k, kn, tb + kTok); fetch(v, vn, tb + kTok); }
 #pragma unroll
             for (int j = 0; j < kTok; ++j)
-                if (tb + j < t1) wkv_advance(a, b, p, wc, kk[j], vv[j]);
+                if (tb + j < t1) wkv_advance(s.a, s.b, s.p, wc, widen(kq[j]), widen(vq[j]));
+        }
+        fetch(k, kn, t0); fetch(v, vn, t0); fetch(r, rn, t0);                  // for the second run
+    }
+    // sums of the pieces up to this one
+#pragma unroll
+    for (int off = 1, buf = 0; off < kChunks; off *= 2, buf ^= 1) {
+        sums[buf][0][ch][cc] = s.a; sums[buf][1][ch][cc] = s.b; sums[buf][2][ch][cc] = s.p;
+        __syncthreads();
+        if (ch >= off) {
+            const WkvSums l = {sums[buf][0][ch - off][cc], sums[buf][1][ch - off][cc], sums[buf][2][ch - off][cc]};
+            s = wkv_merge(l, s, t1 - begin(ch - off + 1), wc);
         }
     }
-    loc[0][ch][cc] = a; loc[1][ch][cc] = b; loc[2][ch][cc] = p;
-    __syncthreads();
-    if (ch == 0 && live) {
-        float A = state[c], Bs = state[(size_t)d + c], P = state[2 * (size_t)d + c];
-        for (int i = 0; i < kChunks; ++i) {
-            in[0][i][cc] = A; in[1][i][cc] = Bs; in[2][i][cc] = P;
-            const int s0 = i * L < M ? i * L : M, s1 = s0 + L < M ? s0 + L : M;
-            if (s1 > s0) {
-                const float Pd = P - (float)(s1 - s0) * wc;                     // n tokens of decay
-                const float lp = loc[2][i][cc];
-                const float q = fmaxf(Pd, lp);
-                const float e1 = expf(Pd - q), e2 = expf(lp - q);
-                A = e1 * A + e2 * loc[0][i][cc];
-                Bs = e1 * Bs + e2 * loc[1][i][cc];
-                P = q;
-            }
-        }
-        state[c] = A; state[(size_t)d + c] = Bs; state[2 * (size_t)d + c] = P;
-    }
+    sums[0][0][ch][cc] = s.a; sums[0][1][ch][cc] = s.b; sums[0][2][ch][cc] = s.p;
     __syncthreads();
     if (!live) return;
-    a = in[0][ch][cc]; b = in[1][ch][cc]; p = in[2][ch][cc];
+    if (ch == kChunks - 1) {
+        const WkvSums all = wkv_merge(before, s, M, wc);
+        state[c] = all.a; state[(size_t)d + c] = all.b; state[2 * (size_t)d + c] = all.p;
+    }
+    s = before;
+    if (ch > 0) s = wkv_merge(before, WkvSums{sums[0][0][ch - 1][cc], sums[0][1][ch - 1][cc], sums[0][2][ch - 1][cc]}, t0, wc);
+#pragma unroll 1
     for (int tb = t0; tb < t1; tb += kTok) {
-        float rr[kTok], kk[kTok], vv[kTok];
 #pragma unroll
-        for (int j = 0; j < kTok; ++j) {
-            const int t = tb + j < t1 ? tb + j : t1 - 1;
-            const size_t at = (size_t)t * d + c;
-            rr[j] = ld16<BF16>(r, at); kk[j] = ld16<BF16>(k, at); vv[j] = ld16<BF16>(v, at);
-        }
+        for (int j = 0; j < kTok; ++j) { kq[j] = kn[j]; vq[j] = vn[j]; rq[j] = rn[j]; }
+        if (tb + kTok < t1) { fetch(k, kn, tb + kTok); fetch(v, vn, tb + kTok); fetch(r, rn, tb + kTok); }
 #pragma unroll
         for (int j = 0; j < kTok; ++j) {
             if (tb + j < t1) {
-                out[(size_t)(tb + j) * d + c] = st16<BF16>(gate_f32(rr[j], wkv_out(a, b, p, uc, kk[j], vv[j])));
-                wkv_advance(a, b, p, wc, kk[j], vv[j]);
+                const float kk = widen(kq[j]), vv = widen(vq[j]);
+                out[(size_t)(tb + j) * d + c] = st16<BF16>(gate_f32(widen(rq[j]), wkv_out(s.a, s.b, s.p, uc, kk, vv)));
+                wkv_advance(s.a, s.b, s.p, wc, kk, vv);
             }
         }
     }

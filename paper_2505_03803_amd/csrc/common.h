@@ -77,19 +77,25 @@ __device__ __forceinline__ float gate_f32(float r, float y) {
 // wkv_out: the output for the current (k, v) with the bonus u; wkv_advance: the sums decayed by
 // exp(-w) and the current token added without the bonus.  Shared by every kernel that steps the
 // recurrence, so that they store the same bits.
+// One of the two exponentials relative to the larger exponent is exp(0): `larger_exp` is that 1 (not a number for infinite q, as
+// exp(q - q) is), the other is taken of the difference itself.  The same bits as both exponentials.
+__device__ __forceinline__ void exp_pair(float x, float y, float& q, float& ex, float& ey) {
+    q = fmaxf(x, y);
+    const float e = expf(-fabsf(x - y)), larger_exp = 1.0f + (q - q);
+    ex = x >= y ? larger_exp : e;
+    ey = x >= y ? e : larger_exp;
+}
 __device__ __forceinline__ float wkv_out(float a, float b, float p, float uc, float kk, float vv) {
-    const float ww = uc + kk;
-    const float q = fmaxf(p, ww);
-    const float e1 = expf(p - q), e2 = expf(ww - q);
+    float q, e1, e2;
+    exp_pair(p, uc + kk, q, e1, e2);
     return (e1 * a + e2 * vv) / (e1 * b + e2);
 }
 __device__ __forceinline__ void wkv_advance(float& a, float& b, float& p, float wc, float kk, float vv) {
-    const float pw = p - wc;
-    const float q2 = fmaxf(pw, kk);
-    const float f1 = expf(pw - q2), f2 = expf(kk - q2);
+    float q, f1, f2;
+    exp_pair(p - wc, kk, q, f1, f2);
     a = f1 * a + f2 * vv;
     b = f1 * b + f2;
-    p = q2;
+    p = q;
 }
 
 // The SQ inverse of Sec. 2.2 Eq. "SQ": subtract, round, multiply, round.  The intrinsics keep

@@ -535,3 +535,30 @@ def test_rkv_wkv_equals_dispatch_then_wkv(dt, d, K, kinds):
             a_, b_ = host(ga, dt), host(gb, dt)
             assert np.all(np.abs(a_ - b_) <= 4 * ulp * np.maximum(np.abs(a_), 1e-3)), t
     assert not torch.equal(sb, fresh_state(d))
+
+
+@pytest.mark.parametrize("M,d", [(128, 128), (129, 256), (191, 384), (4160, 128)])
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+def test_wkv_pieces(M, d, dt):
+    """The time-parallel kernel where neighbouring channels share an XCD (a multiple of 128 channels), with empty pieces, pieces of one
+    to eight tokens and more, and keys that are not finite: the same tokens are not numbers as token by token, the others agree."""
+    torch = G.torch_()
+    rng = np.random.default_rng(M + d)
+    r, k, v, w, u = synth.gen_block_inputs(rng, M, d, dt)
+    inf = {"f16": 0x7C00, "bf16": 0x7F80}[dt]
+    k[M // 2, 3], k[M // 3, 5], k[1, 7], k[M - 1, 9] = inf, inf | 0x8000, inf + 1, inf
+    rd, kd, vd, wd, ud = dev(r), dev(k), dev(v), dev(w), dev(u)
+    out, seq = torch.zeros((M, d), dtype=torch.int16, device="cuda"), torch.zeros((M, d), dtype=torch.int16, device="cuda")
+    state, st2 = fresh_state(d), fresh_state(d)
+    B.rwkvq_wkv(rd, kd, vd, B.DTYPES[dt], M, d, wd, ud, state, out)
+    for t0 in range(0, M, 96):
+        B.rwkvq_wkv(rd[t0:], kd[t0:], vd[t0:], B.DTYPES[dt], min(96, M - t0), d, wd, ud, st2, seq[t0:])
+    torch.cuda.synchronize()
+    a, b = host(out, dt), host(seq, dt)
+    assert np.array_equal(np.isnan(a), np.isnan(b)) and np.isnan(a[M // 2, 3]) and not np.isnan(a[M // 3:, 5]).any()
+    assert np.array_equal(torch.isnan(state[:2]).cpu().numpy(), torch.isnan(st2[:2]).cpu().numpy())
+    ok = ~np.isnan(a)
+    # both sides are rounded to the output type: values that differ by the bar of check_close before that, by up to an ulp more after
+    # (token by token p is rounded once per token, 2^-18 of the exponents met here)
+    vmax = float(np.abs(orc.widen(v, dt)).max())
+    assert (np.abs(a - b)[ok] <= 2 * 1.01 * HALF_ULP[dt] * np.abs(b[ok]) + 2 * FLOOR[dt] + 1.5e-4 * vmax).all()
