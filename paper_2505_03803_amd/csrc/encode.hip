@@ -266,26 +266,31 @@ __device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const f
 //   3. a pair is compared with its cell's entries in index order (strict comparison: the lowest index wins a tie); unused
 //      places of a list repeat its first entry, which never wins again;
 //   4. pairs outside the cells, or in a cell with more than 16 entries, are queued and compared with every entry: a few by
-//      sixteen lanes each, more by a thread each.  Units of eight pairs that find the queue (a quarter of the block) full are
+//      sixteen lanes for four of them, more by a thread each.  Units of eight pairs that find the queue (a quarter of the block) full are
 //      marked and done over with every entry;
 //   5. blocks for which the cells do not pay (weights far wider than the codebook, equal or crowded entries) compare every pair
 //      with every entry: when a fifth (6 bits) or a third (8 bits) of 128 sampled pairs is outside the cells, before the lists
 //      are made, or when a quarter of the first unit of every thread was queued, from there on (from the start, if half was).
 //      Four entries at a time, the smallest of them against the best, which one it was found out at the end: 6 instructions
 //      per pair and entry instead of 8.
-// Bound: vector ALU of step 2 (20 instructions per cell and entry) and the LDS look-ups of the 2 to 8 listed entries per
+// Bound: vector ALU of step 2 (6 instructions per cell and entry, 12 more for those in reach) and the LDS look-ups of the 2 to 8 listed entries per
 // pair (a wavefront runs to its longest list).
-// Measured (bf16, near-normal weights, every pair against every entry -> here): 4096 x 4096, 64 entries 77 -> 50 us, 256
-// entries 279 -> 92; 14336 x 4096, 256 entries 887 -> 234; 1024 x 1024, 64 entries 36 -> 23.  Without step 5 and the second
-// form of step 4, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 186 and 502 us (now 68 and
-// 219), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the entries
-// zero 162 and 170 (70 and 122).  Registers: 64, for two workgroups on a compute unit (74: 14336 x 4096,
-// 64 entries 126 -> 172).
+// Step 2 keeps the 8 x 8 cells of a wavefront together: entries out of reach of all of them are found by a lane each, the others are
+// tested without branches into a bit each, and a cell's list is written from its bits (a branch and a store per entry that some
+// cell wants took 28 us of a workgroup alone on its compute unit with 256 entries, now 10).  A few queued pairs (step 4) are taken
+// four at a time by sixteen lanes.
+// Measured (bf16, near-normal weights, us; every pair against every entry, with lists built entry by entry, here): 4096 x 4096, 64
+// entries 77, 56, 55, 256 entries 279, 100, 87; 14336 x 4096, 256 entries 887, 238, 219; 1024 x 1024, 256 entries 83, 53, 39.  Without
+// step 5 and the second form of step 4, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 186 and 502
+// (now 68 and 219), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the
+// entries zero 162 and 170 (70 and 122).  Registers: 64, for two workgroups on a compute unit (74: 14336 x 4096, 64 entries
+// 126 -> 172).
 template <int KBITS>
 __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
                                                          const uint16_t* __restrict__ codebooks,
                                                          uint32_t* __restrict__ indices, int parts_log2) {
     constexpr int E = 1 << KBITS, G = 32, kSlots = 16, kQueue = 8192;
+    constexpr int kFewQueued = KBITS == 6 ? 256 : 768;             // a thread per pair: 2 and 8 us whatever their number, four at a time 2 us per 256
     __shared__ __attribute__((aligned(16))) float2 entry[E];
     __shared__ __attribute__((aligned(16))) uint8_t list[G * G][kSlots];
     __shared__ uint8_t listed[G * G];
@@ -369,32 +374,52 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     int from = outside > (KBITS == 6 ? 24 : 40) ? 0 : 4096;         // units from here on: every pair with every entry
     int ahead = 0;                                                 // queued by the first units
     if (from) {
-        {   // the lists, one cell per thread
-            const float cx = x0 + ((float)(tid % G) + 0.5f) / sx, cy = y0 + ((float)(tid / G) + 0.5f) / sy;
+        {   // the lists, one cell per thread, 8 x 8 cells per wavefront: a bit per entry first, and without branches
+            const int gx = 8 * (wave & 3) + (lane & 7), gy = 8 * (wave >> 2) + (lane >> 3), cell = gy * G + gx;
+            const float cx = x0 + ((float)gx + 0.5f) / sx, cy = y0 + ((float)gy + 0.5f) / sy;
             const float hx = 1.1f / sx, hy = 1.1f / sy;              // twice 0.55 of a cell's sides
-            float least = __builtin_inff();
-            float2 r = entry[0];
-#pragma unroll 8
-            for (int e = 0; e < E; ++e) {
-                const float2 c = entry[e];
-                const float d = pair_distance(cx, cy, c.x, c.y);
-                if (d < least) { least = d; r = c; }
-            }
-            const float reach = (sqrtf(least) + 2.f * box[4]) * 1.0001f, limit = reach * reach;
-            const float at_most = least + 1e-5f * limit;
+            uint32_t nearest;
+            nearest_of_all<1>(entry, &cx, &cy, &nearest);
+            const float2 r = entry[nearest];
+            const float least = pair_distance(cx, cy, r.x, r.y);
+            const float reach = (sqrtf(least) + 2.f * box[4]) * 1.0001f, at_most = least + 1e-5f * (reach * reach);
+            // entries farther from the wavefront's centres than the longest reach are left out for all of them
+            float far = reach;
+#pragma unroll
+            for (int off = 32; off; off >>= 1) far = fmaxf(far, __shfl_xor(far, off, 64));
+            const float mx = x0 + (8.f * (wave & 3) + 4.f) / sx, my = y0 + (8.f * (wave >> 2) + 4.f) / sy, ax = 3.5f / sx, ay = 3.5f / sy;
+            uint32_t may[E / 32];
             int n = 0, first = 0;
-#pragma unroll 4
-            for (int e = 0; e < E; ++e) {
-                const float2 c = entry[e];
-                const float d = pair_distance(cx, cy, c.x, c.y);
-                if (d <= limit && d <= at_most + fabsf(r.x - c.x) * hx + fabsf(r.y - c.y) * hy) {
-                    if (n == 0) first = e;
-                    if (n < kSlots) list[tid][n] = (uint8_t)e;
-                    ++n;
+#pragma unroll
+            for (int q = E / 64 - 1; q >= 0; --q) {
+                const float2 c = entry[64 * q + lane];
+                const float ox = fmaxf(fabsf(c.x - mx) - ax, 0.f), oy = fmaxf(fabsf(c.y - my) - ay, 0.f);
+                const unsigned long long near = __builtin_amdgcn_ballot_w64(!(ox * ox + oy * oy > far * far * 1.0001f));
+#pragma unroll
+                for (int half = 1; half >= 0; --half) {
+                    uint32_t bits = 0u;
+#pragma unroll 1
+                    for (uint32_t left = (uint32_t)(near >> (32 * half)); left; left &= left - 1u) {
+                        const int e = __builtin_ctz(left);
+                        const float2 o = entry[64 * q + 32 * half + e];
+                        const float d = pair_distance(cx, cy, o.x, o.y);
+                        bits |= d <= at_most + fabsf(r.x - o.x) * hx + fabsf(r.y - o.y) * hy ? 1u << e : 0u;
+                    }
+                    may[2 * q + half] = bits;
+                    n += __builtin_popcount(bits);
+                    if (bits) first = 64 * q + 32 * half + __builtin_ctz(bits);
                 }
             }
-            listed[tid] = (uint8_t)(n <= kSlots && n > 0 ? n : 255);
-            for (; n < kSlots; ++n) list[tid][n] = (uint8_t)first;
+            const bool fits = n <= kSlots && n > 0;
+            listed[cell] = (uint8_t)(fits ? n : 255);
+            const uint32_t four = (uint32_t)first * 0x01010101u;
+            *(uint4_t*)list[cell] = uint4_t{four, four, four, four};
+            n = 0;
+            if (fits) {
+#pragma unroll
+                for (int q = 0; q < E / 32; ++q)
+                    for (uint32_t m = may[q]; m; m &= m - 1u) list[cell][n++] = (uint8_t)(32 * q + __builtin_ctz(m));
+            }
         }
         __syncthreads();
 
@@ -463,7 +488,7 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
         }
     }
     if (todo) {
-        if (todo > 192) {                                          // a thread per queued pair (a pass costs as much as 192 of the others)
+        if (todo > kFewQueued) {                                   // a thread per queued pair
 #pragma unroll 1
             for (int i = tid; i < todo; i += 1024) {
                 const int id = queue[i];
@@ -474,25 +499,40 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                 found[id] = (uint8_t)arg;
             }
         } else {
-            for (int i = tid >> 4; i < todo; i += 64) {            // sixteen lanes per queued pair
-                const int id = queue[i];
-                float vx, vy;
-                load_pair(id, vx, vy);
-                float bd = __builtin_inff();
-                uint32_t be = 0xFFFFFFFFu;
+#pragma unroll 1
+            for (int i0 = 0; i0 < todo; i0 += 256) {               // sixteen lanes per four queued pairs
+                const int mine = i0 + 4 * (tid >> 4);
+                if (mine >= todo) break;
+                float vx[4], vy[4], bd[4];
+                uint32_t be[4];
+                int id[4];
 #pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    id[p] = queue[min(mine + p, todo - 1)];
+                    load_pair(id[p], vx[p], vy[p]);
+                    bd[p] = __builtin_inff();
+                    be[p] = 0xFFFFFFFFu;
+                }
+#pragma unroll 4
                 for (int k = 0; k < E / 16; ++k) {
                     const float2 ce = entry[(tid & 15) + 16 * k];
-                    const float d = pair_distance(vx, vy, ce.x, ce.y);
-                    if (d < bd) { bd = d; be = (uint32_t)((tid & 15) + 16 * k); }
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        const float d = pair_distance(vx[p], vy[p], ce.x, ce.y);
+                        if (d < bd[p]) { bd[p] = d; be[p] = (uint32_t)((tid & 15) + 16 * k); }
+                    }
                 }
 #pragma unroll
-                for (int off = 8; off; off >>= 1) {
-                    const float od = __shfl_xor(bd, off, 64);
-                    const uint32_t oe = (uint32_t)__shfl_xor((int)be, off, 64);
-                    if (od < bd || (od == bd && oe < be)) { bd = od; be = oe; }
+                for (int p = 0; p < 4; ++p) {
+#pragma unroll
+                    for (int off = 8; off; off >>= 1) {
+                        const float od = __shfl_xor(bd[p], off, 64);
+                        const uint32_t oe = (uint32_t)__shfl_xor((int)be[p], off, 64);
+                        if (od < bd[p] || (od == bd[p] && oe < be[p])) { bd[p] = od; be[p] = oe; }
+                    }
+                    // (every distance infinite or NaN: entry 0; past the end the last pair again)
+                    if ((tid & 15) == 0) found[id[p]] = (uint8_t)(be[p] == 0xFFFFFFFFu ? 0u : be[p]);
                 }
-                if ((tid & 15) == 0) found[id] = (uint8_t)(be == 0xFFFFFFFFu ? 0u : be);   // (every distance infinite or NaN: entry 0)
             }
         }
         if (all > kQueue) {                                     // (the queued pairs of such a unit come out the same again)
