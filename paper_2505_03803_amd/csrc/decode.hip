@@ -150,14 +150,18 @@ struct MixedDecodeArgs {
     MixedMat m[kMaxMixedMats];
     int M, xdt, ydt, pad;
 };
-struct DecodeArgs {                   // 15 KB of kernel arguments
+template <int MATS> struct DecodeTable {
     static constexpr bool kMixed = false;
     static constexpr bool kPostMix = false;
-    static constexpr int kMats = kMaxGroupMats;
-    int wg_end[kMaxGroupMats];        // first workgroup index after matrix i (INT_MAX when unused)
-    DecodeMat m[kMaxGroupMats];
+    static constexpr int kMats = MATS;
+    int wg_end[MATS];                 // first workgroup index after matrix i (INT_MAX when unused)
+    DecodeMat m[MATS];
     int M, xdt, ydt, pad;
 };
+using DecodeArgs = DecodeTable<kMaxGroupMats>;         // 15 KB of kernel arguments
+// The two-dimensional grids of few matrices: filling and handing over the table above is most of what the host does for a launch
+// that lasts 3 us (a 1024 x 1024 matrix at batch 1, call after call: 8.4 us with it, 7.7 with this one).
+using SmallDecodeArgs = DecodeTable<kGrid2DMaxMats>;
 
 // Batch-1 output with the element-wise operator that follows the projection in the block (App. A.1)
 // applied on the way out.  The value is first rounded to the output type, as a separate pass would
@@ -1649,7 +1653,7 @@ static int pick_split(int tiles) { return tiles * 4 >= kSplitTarget ? 4 : tiles 
 template <class Args>
 static hipError_t launch_splitk(int split, int wgs, Args& a, int n_mats, hipStream_t s) {
     a.pad = 0;
-    if (n_mats <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1) {
+    if (Args::kMats == kGrid2DMaxMats || (n_mats <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1)) {
         int longest = 0;
         for (int i = 0; i < n_mats; ++i) longest = std::max(longest, a.wg_end[i] - (i ? a.wg_end[i - 1] : 0));
         const dim3 grid(longest, n_mats);
@@ -1658,11 +1662,14 @@ static hipError_t launch_splitk(int split, int wgs, Args& a, int n_mats, hipStre
         else hipLaunchKernelGGL((decode_splitk_kernel<16, Args, true>), grid, dim3(1024), 0, s, a);
         return hipGetLastError();
     }
-    const dim3 grid(wgs);
-    if (split == 4) hipLaunchKernelGGL((decode_splitk_kernel<4, Args, false>), grid, dim3(256), 0, s, a);
-    else if (split == 8) hipLaunchKernelGGL((decode_splitk_kernel<8, Args, false>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((decode_splitk_kernel<16, Args, false>), grid, dim3(1024), 0, s, a);
-    return hipGetLastError();
+    if constexpr (Args::kMats > kGrid2DMaxMats) {
+        const dim3 grid(wgs);
+        if (split == 4) hipLaunchKernelGGL((decode_splitk_kernel<4, Args, false>), grid, dim3(256), 0, s, a);
+        else if (split == 8) hipLaunchKernelGGL((decode_splitk_kernel<8, Args, false>), grid, dim3(512), 0, s, a);
+        else hipLaunchKernelGGL((decode_splitk_kernel<16, Args, false>), grid, dim3(1024), 0, s, a);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 // Batch 1 with the token-shift mix fused into the activation load: always the split-K kernel
@@ -1816,7 +1823,6 @@ static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats,
 hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s,
                          const PostDev* posts) {
     for (int base = 0; base < n_mats; base += kMaxGroupMats) {
-        DecodeArgs a;
         int cnt = n_mats - base < kMaxGroupMats ? n_mats - base : kMaxGroupMats;
         // Workgroups are handed out in index order and a workgroup's running time grows with K:
         // the matrices of a launch go longest rows first, so that the launch does not end on a
@@ -1831,6 +1837,29 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         for (int i = 0; i < cnt; ++i) tiles += (mats[order[i]].N + 15) / 16;
         int split = 0;
         if (M == 1 && tiles < kSplitTarget) split = pick_split(tiles);
+        auto fill = [&](auto& a, auto rows_of) {               // the matrices in order; workgroups of rows_of rows
+            int wgs = 0;
+            for (int i = 0; i < cnt; ++i) {
+                const MatDev& m = mats[order[i]];
+                wgs += (m.N + rows_of - 1) / rows_of;
+                a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, posts ? posts[order[i]].op : POST_NONE,
+                                   posts ? posts[order[i]].gate : nullptr};
+                a.wg_end[i] = wgs;
+            }
+            for (int i = cnt; i < a.kMats; ++i) {
+                a.m[i] = DecodeMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, POST_NONE, nullptr};
+                a.wg_end[i] = 0x7FFFFFFF;
+            }
+            a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.pad = 0;
+            return wgs;
+        };
+        if (split && cnt <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1) {
+            SmallDecodeArgs a;
+            const int wgs = fill(a, 16);
+            const hipError_t e = launch_splitk(split, wgs, a, cnt, s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         // batch 2..16 with few rows in the launch: the wavefronts of a workgroup split the columns
         if (M > 1 && M <= 16) {
             if (stage_cheaper(mats, order, cnt, M, x_dtype)) {
@@ -1848,20 +1877,8 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
             for (int i = 0; i < cnt; ++i) wgs2 += (mats[order[i]].N + wg_rows(M, 2) - 1) / wg_rows(M, 2);
             if (kTwoPassFits && wgs2 >= option(RWKVQ_OPT_STREAM_TWO_PASS_MIN_WGS)) passes = 2;
         }
-        const int rows = wg_rows(M, passes);
-        int wgs = 0;
-        for (int i = 0; i < cnt; ++i) {
-            const MatDev& m = mats[order[i]];
-            wgs += split ? (m.N + 15) / 16 : (m.N + rows - 1) / rows;
-            a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, posts ? posts[order[i]].op : POST_NONE,
-                               posts ? posts[order[i]].gate : nullptr};
-            a.wg_end[i] = wgs;
-        }
-        for (int i = cnt; i < kMaxGroupMats; ++i) {
-            a.m[i] = DecodeMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, POST_NONE, nullptr};
-            a.wg_end[i] = 0x7FFFFFFF;
-        }
-        a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.pad = 0;
+        DecodeArgs a;
+        const int wgs = fill(a, split ? 16 : wg_rows(M, passes));
         const dim3 grid(wgs), wide(64 * kBW);
         if (split) { hipError_t e = launch_splitk(split, wgs, a, cnt, s); if (e != hipSuccess) return e; }
         else if (M == 1) hipLaunchKernelGGL(decode_kernel<1>, grid, dim3(256), 0, s, a);
