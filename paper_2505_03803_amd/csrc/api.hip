@@ -275,7 +275,9 @@ int rwkvq_linear_dispatch(const rwkvq_matrix* mats, const void* const* xs, void*
         if (e != hipSuccess) return RWKVQ_ERR_DEVICE;
     }
     if (!passes.empty() && split_k_cheaper(passes, M)) {
-        if (launch_mid(passes.data(), (int)passes.size(), M, x_dtype, y_dtype, true, s) != hipSuccess) return RWKVQ_ERR_DEVICE;
+        if (wide_cheaper(passes.data(), (int)passes.size(), M, x_dtype)) {
+            if (launch_wide(passes.data(), (int)passes.size(), M, x_dtype, y_dtype, s) != hipSuccess) return RWKVQ_ERR_DEVICE;
+        } else if (launch_mid(passes.data(), (int)passes.size(), M, x_dtype, y_dtype, true, s) != hipSuccess) return RWKVQ_ERR_DEVICE;
         passes.clear();
     }
     if (!decode.empty()) {

@@ -182,6 +182,8 @@ hipError_t launch_decode_mixed(const MatDev* mats, const MixDev* mixes, int n_ma
                                hipStream_t s, const PostDev* posts = nullptr);
 hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype,
                          hipStream_t s, const PostDev* posts = nullptr);
+bool wide_cheaper(const MatDev* mats, int n_mats, int M, int x_dtype);   // 17 <= M <= 48, weights unrounded: launch_wide or launch_mid
+hipError_t launch_wide(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s);
 hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype,
                           hipStream_t s);
 // Splits K over the wavefronts of a workgroup (midbatch.hip): exact = false, the feed of launch_prefill; true, weights unrounded.

@@ -1572,6 +1572,200 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
     }
 }
 
+// The same for 17 .. 48 rows of x (G = 2, 3 groups of sixteen), eight wavefronts of 256 registers.  The activations of a column tile
+// would take all of them, so a tile goes in its two units of 128 columns: while the R row tiles are multiplied by the fragments of
+// one, those of the next are in flight.
+template <int FMT, int R, int G, bool XB>
+struct StageWide {
+    static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
+    const DecodeMat& mt;
+    int R0, NR, KT, lane;
+    uint32_t xoff[G];
+    float* xsc;                        // [G][16]
+    uint32_t* cb_lds;                  // [R][256]
+    uint32_t mask, magic, m6, base0;
+    StageRegs w[R];
+    uint4_t xf[2][G][4];
+
+    __device__ __forceinline__ StageWide(const DecodeMat& mt_, int R0_, int M, int lane_, float* xsc_, uint32_t* cb_)
+        : mt(mt_), R0(R0_), NR(mt_.N >> 4), KT(mt_.K >> 8), lane(lane_), xsc(xsc_), cb_lds(cb_) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) xoff[g] = (uint32_t)((16 * g + (lane & 15) < M ? 16 * g + (lane & 15) : M - 1) * mt.K + 8 * (lane >> 4));
+        asm("v_mov_b32 %0, 0x03800380" : "=v"(mask));
+        asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
+        asm("v_mov_b32 %0, 0xfc" : "=v"(m6));
+        base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
+    }
+    template <int U>
+    __device__ __forceinline__ void load_x(int T, bool live) {
+        const uint16_t* p = (const uint16_t*)mt.x + 256 * T + 128 * U;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const uint32_t at = live ? xoff[g] : 0u;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) xf[U][g][t] = *(const uint4_t*)(p + at + 32 * t);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void load_w(StageRegs& r, int T, int rt, bool live) {
+        const int row = R0 + rt < NR ? R0 + rt : NR - 1;
+        const uint32_t l = live ? (uint32_t)lane : 0u;
+        const uint32_t* t = mt.codes + ((size_t)row * KT + T) * kWords;
+        r.a = stream_load((const uint4_t*)t + l);
+        if constexpr (FMT == FMT_VQ8) {
+            r.b = stream_load((const uint4_t*)(t + 256) + l);
+            r.cb = ((const uint4_t*)mt.aux + ((size_t)(row >> 4) * KT + T) * 64)[l];
+        } else {
+            const uint2_t two = stream_load((const uint2_t*)(t + 256) + l);
+            r.b.x = two.x; r.b.y = two.y;
+            if constexpr (FMT == FMT_SQ3) {
+                const uint2_t sz = stream_load((const uint2_t*)mt.aux + ((size_t)row * KT + T) * 16 + (l & 15u));
+                r.b.z = sz.x; r.b.w = sz.y;
+            } else {
+                r.b.z = ((const uint32_t*)mt.aux + ((size_t)(row >> 4) * KT + T) * 64)[l];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // Columns 128 U .. of tile T for every row tile; the next tile's fragments of this unit follow, and behind the second unit
+    // every row tile's next weights.
+    template <int U>
+    __device__ __forceinline__ void unit(int T, int Tn, bool more, float4_t (&out)[R][G]) {
+        float4_t sc[G];
+        if (XB) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                uint32_t amax = 0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) amax = max(amax, max(bf16x2_absmax(xf[U][g][t].x, xf[U][g][t].y), bf16x2_absmax(xf[U][g][t].z, xf[U][g][t].w)));
+                amax = max(amax, (uint32_t)__shfl_xor((int)amax, 16, 64));
+                amax = max(amax, (uint32_t)__shfl_xor((int)amax, 32, 64));
+                const int n = bf16_scale_exponent(amax);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    xf[U][g][t].x = bf16x2_to_f16x2(xf[U][g][t].x, n); xf[U][g][t].y = bf16x2_to_f16x2(xf[U][g][t].y, n);
+                    xf[U][g][t].z = bf16x2_to_f16x2(xf[U][g][t].z, n); xf[U][g][t].w = bf16x2_to_f16x2(xf[U][g][t].w, n);
+                }
+                if (lane < 16) xsc[16 * g + lane] = ldexpf(1.0f, -n);
+            }
+        }
+        if (FMT != FMT_SQ3 && U == 0) {
+#pragma unroll
+            for (int rt = 0; rt < R; ++rt) {
+                if constexpr (FMT == FMT_VQ8) *(uint4_t*)(cb_lds + 256 * rt + 4 * lane) = w[rt].cb;
+                else cb_lds[256 * rt + lane] = w[rt].b.z;
+            }
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int g = 0; g < G; ++g) sc[g] = XB ? *(const float4_t*)(xsc + 16 * g + 4 * (lane >> 4)) : float4_t{1, 1, 1, 1};
+        float4_t X[G];
+        if constexpr (FMT == FMT_SQ3) {
+            const uint4_t ones4 = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                X[g] = float4_t{0, 0, 0, 0};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) X[g] = RWKVQ_MFMA(__builtin_bit_cast(half8_t, xf[U][g][t]), __builtin_bit_cast(half8_t, ones4), X[g]);
+            }
+        }
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt) {
+            const StageRegs& r = w[rt];
+            half8_t op[4];
+            if constexpr (FMT == FMT_VQ8) {
+                const uint4_t q = U == 0 ? r.a : r.b;
+                const uint32_t* cbuf = cb_lds + 256 * rt;
+                op[0] = vq8_operand(q.x, cbuf); op[1] = vq8_operand(q.y, cbuf); op[2] = vq8_operand(q.z, cbuf); op[3] = vq8_operand(q.w, cbuf);
+            } else {
+                const uint32_t w0 = U == 0 ? r.a.x : r.a.w, w1 = U == 0 ? r.a.y : r.b.x, w2 = U == 0 ? r.a.z : r.b.y;
+                if constexpr (FMT == FMT_SQ3) {
+                    op[0] = sq_operand<0>(w0, w1, w2, mask, magic); op[1] = sq_operand<1>(w0, w1, w2, mask, magic);
+                    op[2] = sq_operand<2>(w0, w1, w2, mask, magic); op[3] = sq_operand<3>(w0, w1, w2, mask, magic);
+                } else {
+                    const uint32_t base = base0 + 1024 * rt;
+                    op[0] = __builtin_bit_cast(half8_t, vq6_gather4<0>(w0, w1, w2, m6, base));
+                    op[1] = __builtin_bit_cast(half8_t, vq6_gather4<1>(w0, w1, w2, m6, base));
+                    op[2] = __builtin_bit_cast(half8_t, vq6_gather4<2>(w0, w1, w2, m6, base));
+                    op[3] = __builtin_bit_cast(half8_t, vq6_gather4<3>(w0, w1, w2, m6, base));
+                }
+            }
+            const uint32_t szw = U == 0 ? r.b.z : r.b.w;                      // (SQ)
+            const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float4_t sum = {0, 0, 0, 0};
+                if (FMT != FMT_SQ3 && !XB) sum = out[rt][g];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sum = RWKVQ_MFMA(__builtin_bit_cast(half8_t, xf[U][g][t]), op[t], sum);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (FMT == FMT_SQ3) out[rt][g][i] = fmaf(XB ? s * sc[g][i] : s, fmaf(-z8, X[g][i], sum[i]), out[rt][g][i]);
+                    else out[rt][g][i] = XB ? fmaf(sum[i], sc[g][i], out[rt][g][i]) : sum[i];
+                }
+            }
+            if (U == 1) load_w(w[rt], Tn, rt, more);
+        }
+        load_x<U>(Tn, more);
+    }
+    __device__ __forceinline__ void run(int t0, int S, int nt, float4_t (&out)[R][G]) {
+        const int last = t0 + (nt - 1) * S;
+        __builtin_amdgcn_sched_barrier(0);
+        load_x<0>(t0, true);
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt) load_w(w[rt], t0, rt, true);
+        load_x<1>(t0, true);
+#pragma unroll 1
+        for (int T = t0; T <= last; T += S) {
+            const bool more = T + S <= last;
+            unit<0>(T, more ? T + S : last, more, out);
+            unit<1>(T, more ? T + S : last, more, out);
+        }
+    }
+};
+
+constexpr int kWideWaves = 8;
+template <int R, int G, bool XB>
+__global__ void __launch_bounds__(64 * kWideWaves) decode_stage_wide_kernel(StageArgs<kGrid2DMaxMats> a) {
+    extern __shared__ __attribute__((aligned(1024))) uint32_t stage_lds[];        // per wavefront: R codebook slots, later its sums
+    __shared__ __attribute__((aligned(16))) float xsc[kWideWaves][16 * G];
+    const int M = a.M, ydt = a.ydt, S = a.S;
+    const DecodeMat mt = a.m[blockIdx.y];
+    asm volatile("" :: "s"(M), "s"(ydt), "s"(S), "s"(mt.N));
+    const int R0 = R * blockIdx.x;
+    if (16 * R0 >= mt.N) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int KT = mt.K >> 8;
+    constexpr int kOwn = 256 * R * G;                              // words of LDS per wavefront
+    uint32_t* mine = stage_lds + kOwn * wave;
+    float4_t out[R][G];
+#pragma unroll
+    for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+        for (int g = 0; g < G; ++g) out[rt][g] = float4_t{0, 0, 0, 0};
+    if (wave < KT) {
+        const int nt = (KT - wave + S - 1) / S;
+        if (mt.fmt == FMT_SQ3) StageWide<FMT_SQ3, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        else if (mt.fmt == FMT_VQ6) StageWide<FMT_VQ6, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        else StageWide<FMT_VQ8, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+        for (int g = 0; g < G; ++g) *(float4_t*)(mine + 256 * (G * rt + g) + 4 * lane) = out[rt][g];
+    __syncthreads();
+    const float* sums = (const float*)stage_lds;
+    for (int i = threadIdx.x; i < 16 * R * M; i += 64 * S) {
+        const int m = i / (16 * R), n = i - 16 * R * m;
+        const int at = 256 * (G * (n >> 4) + (m >> 4)) + 4 * (16 * ((m & 15) >> 2) + (n & 15)) + (m & 3);
+        float t = sums[at];
+        for (int s = 1; s < S; ++s) t += sums[kOwn * s + at];
+        if (16 * R0 + n < mt.N) store_from_f32(mt.y, (size_t)m * mt.N + 16 * R0 + n, ydt, t);
+    }
+}
+
 // Time mixing's r, k, v and the wkv step in one launch.  The recurrence is per channel, and channel c
 // needs r[c], k[c], v[c]: output row c of three matrices.  A workgroup of 12 wavefronts takes row tile R
 // of all three (four wavefronts per matrix, the column tiles dealt as in the split-K kernel with S = 4,
@@ -1818,6 +2012,46 @@ static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats,
         }
 #undef RWKVQ_STAGE
     }
+}
+
+template <int R, int G, bool XB>
+static hipError_t launch_wide_kernel(const StageArgs<kGrid2DMaxMats>& a, dim3 grid, hipStream_t s) {
+    static std::atomic<unsigned long long> raised{0ull};
+    const hipError_t e = raise_lds((const void*)decode_stage_wide_kernel<R, G, XB>, kWideWaves * R * G * 1024, raised);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((decode_stage_wide_kernel<R, G, XB>), grid, dim3(64 * a.S), a.S * R * G * 1024, s, a);
+    return hipGetLastError();
+}
+// Row tiles of a workgroup (5 or 6; 0: the kernels of midbatch.hip) at 17 <= M <= 48.  Those take 64 rows of W in a workgroup that has
+// a compute unit to itself; from 257 of them on they need a second round, which one round of 80 or 96 rows saves.  Smaller calls stay
+// there: every workgroup reads all of x (4096 x 4096 at M = 32 10.9 us here, 9.3 there; 4096 x 14336 29.7 and 21.3).  Measured (us,
+// there -> here): {k', r'} of the 7B shapes fp16 SQ at M = 17 23.5 -> 15.3, 32 24.7 -> 17.8, 48 27.4 -> 23.3, bf16 8-bit VQ at 32
+// 31.6 -> 21.1; of 14B-class shapes (six row tiles) fp16 SQ 29.1 -> 23.3, 6-bit VQ 27.7 -> 28.4 (at 17 rows 27.0 -> 24.4), bf16 33.0 -> 27.3.  bf16 beyond
+// 32 rows has no registers for it.
+static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
+    if (n_mats > kGrid2DMaxMats || M <= 16 || M > (x_dtype == DT_BF16 ? 32 : 48)) return 0;
+    auto workgroups = [&](int r) { long long n = 0; for (int i = 0; i < n_mats; ++i) n += (mats[i].N + 16 * r - 1) / (16 * r); return n; };
+    return workgroups(4) <= 256 ? 0 : workgroups(5) <= 256 ? 5 : M <= 32 && workgroups(6) <= 256 ? 6 : 0;
+}
+bool wide_cheaper(const MatDev* mats, int n_mats, int M, int x_dtype) { return wide_row_tiles(mats, n_mats, M, x_dtype) > 0; }
+hipError_t launch_wide(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+    StageArgs<kGrid2DMaxMats> a;
+    const int R = wide_row_tiles(mats, n_mats, M, x_dtype);
+    int columns = 0, longest = 0;
+    for (int i = 0; i < kGrid2DMaxMats; ++i) {
+        a.m[i] = DecodeMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, POST_NONE, nullptr};
+        if (i >= n_mats) continue;
+        const MatDev& m = mats[i];
+        a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, POST_NONE, nullptr};
+        columns = std::max(columns, m.K >> 8); longest = std::max(longest, (m.N + 16 * R - 1) / (16 * R));
+    }
+    const int turns = (columns + kWideWaves - 1) / kWideWaves;
+    a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = (columns + turns - 1) / turns;
+    const dim3 grid(longest, n_mats);
+    const bool bf16 = x_dtype == DT_BF16;
+    if (M > 32) return launch_wide_kernel<5, 3, false>(a, grid, s);
+    if (R == 5) return bf16 ? launch_wide_kernel<5, 2, true>(a, grid, s) : launch_wide_kernel<5, 2, false>(a, grid, s);
+    return bf16 ? launch_wide_kernel<6, 2, true>(a, grid, s) : launch_wide_kernel<6, 2, false>(a, grid, s);
 }
 
 hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s,

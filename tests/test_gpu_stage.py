@@ -35,3 +35,26 @@ def test_column_split(R, columns, M, xdt, options):
         assert (got[M] == 7.0).all()                      # nothing behind the last row
         # up to 6400 products in binary32 partial sums: about sqrt(K) 2^-24 of the row's norms
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
+# 17 to 48 rows of x, calls of 257 to 384 workgroups of 64 rows of W: five and six row tiles per workgroup, the last one partly past the
+# end of W, one and several column tiles per wavefront, another K and format in the same launch
+@pytest.mark.parametrize("row_tiles,columns", [(1025, 1), (1060, 9), (1248, 4), (1252, 3), (1500, 2), (1504, 17)])
+@pytest.mark.parametrize("M,xdt", [(17, "bf16"), (32, "f16"), (33, "f16"), (48, "f16"), (32, "bf16")])
+def test_column_split_of_more_rows(row_tiles, columns, M, xdt, options):
+    print(f"column split row tiles={row_tiles} columns={columns} M={M} x={xdt}", flush=True)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    options(B.OPT_STREAM_SPLIT_MAX_WORK, 1000000)
+    torch, rng = G.torch_(), np.random.default_rng(row_tiles)
+    K, few = 256 * columns, 256 * max(1, columns // 2)
+    mats = [synth.gen_sq(rng, 16 * (row_tiles - 32), K if columns < 9 else few), synth.gen_vq(rng, 256, K, 6), synth.gen_vq(rng, 256, few, 8)]
+    xs = [synth.gen_activations(rng, M, m.K, xdt) for m in mats]
+    dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
+    ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
+    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    for m, x, y in zip(mats, xs, ys):
+        got = y.cpu().numpy().astype(np.float64)
+        assert (got[M] == 7.0).all()
+        # as above; the same products
+        assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
