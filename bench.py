@@ -40,7 +40,7 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 DECODE_KERNEL = "rwkvq::decode_kernel<1, 1>"
 DECODE16_KERNEL = "rwkvq::decode_kernel<16, 2>"
-PREFILL_KERNEL = "rwkvq::prefill_kernel<true, FMT, 8>"   # bf16; one instantiation per weight format
+PREFILL_KERNEL = "rwkvq::prefill_kernel<true, FMT, 8, 8>"   # bf16; one instantiation per weight format
 PROXY_KERNEL = "rwkvq::proxy_set_kernel"
 DECODE_MATS_PER_LAUNCH = 256
 # HBM traffic per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch), each scaled by what the
@@ -949,12 +949,12 @@ def main():
         out["proxy_f32"] = {"value": nw32 / (ms32 * 1e-3) / 1e9, "unit": "G weights/s", "ms_per_call": ms32, "calls": 10, "dtype": "f64",
                             "matrices": len(shapes32), "weights_per_call": nw32,
                             "workload": "dense binary32 N(0, 0.02) weights of one RWKV-6-7B-shaped layer (8 matrices), K = 5 terms, "
-                                        "partitioned and reduced to sets of values, one matrix after another",
+                                        "partitioned and reduced to sets of values, up to eight matrices of a size at a time",
                             "roofline": {"kernel": "rwkvq::set_partition_kernel", "bound": "hbm", "achieved": alg32 / (ms32 * 1e-3) / 1e9,
                                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": alg32 / (ms32 * 1e-3) / 1e9 / HBM_PEAK_GBS,
                                          "traffic": None, "algorithmic_bytes_per_call": alg32,
                                          "note": "algorithmic bytes = 16 per weight (count 4, partition 8, sums 4); achieved is over the whole call "
-                                                 "(6 launches per matrix)"}}
+                                                 "(2 launches per matrix and 4 per group of up to eight of a size)"}}
         if not args.skip_cpu:
             from oracle import proxy_oracle as PO
             host32 = mats32[0].cpu().numpy()
