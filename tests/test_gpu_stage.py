@@ -58,3 +58,22 @@ def test_column_split_of_more_rows(row_tiles, columns, M, xdt, options):
         assert (got[M] == 7.0).all()
         # as above; the same products
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
+# The rule's two sides of calls that fit one round, bit for bit the kernel it is to take, and against the oracle
+@pytest.mark.parametrize("N,columns,M,xdt,forced", [(1024, 4, 8, "f16", 1000000), (256, 3, 2, "bf16", 1000000), (1024, 8, 16, "bf16", 1000000),
+                                                    (24576, 3, 16, "f16", 1), (24592, 3, 16, "bf16", 1), (1024, 2, 8, "f16", 1)])
+def test_rule_of_one_round(N, columns, M, xdt, forced, options):
+    print(f"rule N={N} columns={columns} M={M} x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(N + columns)
+    m = synth.gen_sq(rng, N, 256 * columns)
+    x = synth.gen_activations(rng, M, m.K, xdt)
+    dm, dev = B.upload(m, native=True), G.to_dev_bits(x)
+    ys = [torch.full((M, N), 7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for i, y in enumerate(ys):
+        if i:
+            options(B.OPT_STREAM_SPLIT_MAX_WORK, forced)
+        B.rwkvq_linear_dispatch(B.DispatchTable([dm.desc()], [dev], [y]), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
+    assert G.err_g2(ys[0].cpu().numpy().astype(np.float64), orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
