@@ -61,30 +61,24 @@ __global__ void __launch_bounds__(64) wkv_kernel(const uint16_t* __restrict__ r,
 // Chunks of many tokens (prefill): the recurrence is linear in the carried sums, S_out = exp(-n w) S_in
 // + (the sums of the n tokens alone), so the tokens are cut into kChunks pieces that run side by side.
 // A workgroup owns 16 channels; thread (channel, piece) first runs its piece from the empty state, the
-// sums in front of every piece come from a scan over the pieces in six merges, and each thread runs
+// pieces are joined in their order, which leaves the state in front of every piece in LDS, and each thread runs
 // its piece again from there, now with outputs.  Twice the arithmetic, 64 times the parallelism.
 // The merges re-associate the sums: the result agrees with the token-by-token kernel to rounding, not bit for bit.
-// What bounds it: vector ALU (about 130 instructions per token and channel).  d = 4096, bf16, us: with the pieces chained one after
-// another by 16 threads, both exponentials of a pair, no tokens in flight while others are computed and neighbouring channels on
-// different XCDs (which fetch the lines of r, k and v once each) 23 at M = 333 and 69 at M = 2048, now 12
-// and 36.
+// Joining: only a subtraction and a maximum per piece wait for the exponent of the piece before, and only a product and an addition
+// for its sums; the two exponentials of every merge in between are taken by the pieces' own threads.
+// What bounds it: vector ALU (about 130 instructions per token and channel).  d = 4096, bf16, us: with the exponentials in the
+// chain, both of a pair, no tokens in flight while others are computed and neighbouring channels on
+// different XCDs (which fetch the lines of r, k and v once each) 21 at M = 333 and 68 at M = 2048, now 11.6
+// and 40.2 (10.7 and 39.0 with the pieces joined by a tree of merges, which gives other bits).
 constexpr int kChunks = 64, kWgChannels = 16;
 struct WkvSums { float a, b, p; };
-// Sums of a run of tokens and of the n tokens behind it.
-__device__ __forceinline__ WkvSums wkv_merge(const WkvSums& l, const WkvSums& r, int n, float wc) {
-    WkvSums m;
-    float e1, e2;
-    exp_pair(l.p - (float)n * wc, r.p, m.p, e1, e2);
-    m.a = e1 * l.a + e2 * r.a;
-    m.b = e1 * l.b + e2 * r.b;
-    return m;
-}
 
 template <bool BF16>
 __global__ void __launch_bounds__(kChunks * kWgChannels) wkv_chunked_kernel(
     const uint16_t* __restrict__ r, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int M, int d,
     const float* __restrict__ w, const float* __restrict__ u, float* __restrict__ state, uint16_t* __restrict__ out) {
-    __shared__ float sums[2][3][kChunks][kWgChannels];    // of the pieces up to i: two buffers, written in turn
+    __shared__ float loc[3][kChunks][kWgChannels];        // of piece i: its exponent; then exp(..) of what is in front, its own sums under the joint exponent
+    __shared__ float in[3][kChunks][kWgChannels];         // sums in front of piece i
     const int cc = threadIdx.x & (kWgChannels - 1), ch = threadIdx.x / kWgChannels;
     const int blk = (gridDim.x & 7) ? (int)blockIdx.x : (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
     const int c = blk * kWgChannels + cc;
@@ -117,25 +111,38 @@ __global__ void __launch_bounds__(kChunks * kWgChannels) wkv_chunked_kernel(
         }
         fetch(k, kn, t0); fetch(v, vn, t0); fetch(r, rn, t0);                  // for the second run
     }
-    // sums of the pieces up to this one
-#pragma unroll
-    for (int off = 1, buf = 0; off < kChunks; off *= 2, buf ^= 1) {
-        sums[buf][0][ch][cc] = s.a; sums[buf][1][ch][cc] = s.b; sums[buf][2][ch][cc] = s.p;
-        __syncthreads();
-        if (ch >= off) {
-            const WkvSums l = {sums[buf][0][ch - off][cc], sums[buf][1][ch - off][cc], sums[buf][2][ch - off][cc]};
-            s = wkv_merge(l, s, t1 - begin(ch - off + 1), wc);
+    // the state in front of every piece that has tokens, in their order
+    const int pieces = (M + L - 1) / L;
+    loc[2][ch][cc] = s.p;
+    __syncthreads();
+    if (ch == 0) {
+        float P = before.p;
+#pragma unroll 8
+        for (int i = 0; i < pieces; ++i) {
+            in[2][i][cc] = P;
+            P = fmaxf(P - (float)(begin(i + 1) - begin(i)) * wc, loc[2][i][cc]);
         }
+        if (live) state[2 * (size_t)d + c] = P;
     }
-    sums[0][0][ch][cc] = s.a; sums[0][1][ch][cc] = s.b; sums[0][2][ch][cc] = s.p;
+    __syncthreads();
+    if (t0 < t1) {
+        float q, e1, e2;
+        exp_pair(in[2][ch][cc] - (float)(t1 - t0) * wc, s.p, q, e1, e2);
+        loc[0][ch][cc] = e1; loc[1][ch][cc] = e2 * s.a; loc[2][ch][cc] = e2 * s.b;
+    }
+    __syncthreads();
+    if (ch < 2) {
+        float S = ch ? before.b : before.a;
+#pragma unroll 8
+        for (int i = 0; i < pieces; ++i) {
+            in[ch][i][cc] = S;
+            S = loc[0][i][cc] * S + loc[1 + ch][i][cc];
+        }
+        if (live) state[(size_t)ch * d + c] = S;
+    }
     __syncthreads();
     if (!live) return;
-    if (ch == kChunks - 1) {
-        const WkvSums all = wkv_merge(before, s, M, wc);
-        state[c] = all.a; state[(size_t)d + c] = all.b; state[2 * (size_t)d + c] = all.p;
-    }
-    s = before;
-    if (ch > 0) s = wkv_merge(before, WkvSums{sums[0][0][ch - 1][cc], sums[0][1][ch - 1][cc], sums[0][2][ch - 1][cc]}, t0, wc);
+    s = WkvSums{in[0][ch][cc], in[1][ch][cc], in[2][ch][cc]};                  // (a piece without tokens: never used)
 #pragma unroll 1
     for (int tb = t0; tb < t1; tb += kTok) {
 #pragma unroll

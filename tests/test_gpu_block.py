@@ -562,3 +562,28 @@ def test_wkv_pieces(M, d, dt):
     # (token by token p is rounded once per token, 2^-18 of the exponents met here)
     vmax = float(np.abs(orc.widen(v, dt)).max())
     assert (np.abs(a - b)[ok] <= 2 * 1.01 * HALF_ULP[dt] * np.abs(b[ok]) + 2 * FLOOR[dt] + 1.5e-4 * vmax).all()
+
+
+@pytest.mark.parametrize("M", [128, 129, 333, 2048])
+def test_wkv_pieces_are_joined_in_order(M):
+    """A piece of the time-parallel kernel with one token that counts (behind it tokens of weight zero), exponents and decays that are exact
+    in binary32: joining the pieces in their order makes the same products and sums as token by token, so the same bits.  An
+    infinite decay forgets the tokens before; pieces without tokens change nothing."""
+    torch = G.torch_()
+    d, L = 128, -(-M // 64)
+    rng = np.random.default_rng(M)
+    r, k, v, w, u = synth.gen_block_inputs(rng, M, d, "f16")
+    keys = rng.integers(-24, 25, (M, d)) / 8.0
+    keys[np.arange(M) % L != 0] = -60000.0
+    k = np.ascontiguousarray(keys.astype(np.float16).view(np.uint16))
+    w = (rng.integers(0, 9, d) / 8.0).astype(np.float32)
+    w[5:8] = np.inf
+    rd, kd, vd, wd, ud = dev(r), dev(k), dev(v), dev(w), dev(u)
+    out, seq = torch.zeros((M, d), dtype=torch.int16, device="cuda"), torch.zeros((M, d), dtype=torch.int16, device="cuda")
+    state, st2 = fresh_state(d), fresh_state(d)
+    B.rwkvq_wkv(rd, kd, vd, B.F16, M, d, wd, ud, state, out)
+    for t0 in range(0, M, 96):
+        B.rwkvq_wkv(rd[t0:], kd[t0:], vd[t0:], B.F16, min(96, M - t0), d, wd, ud, st2, seq[t0:])
+    torch.cuda.synchronize()
+    assert torch.equal(out, seq)
+    assert torch.equal(state[:2], st2[:2]) and not torch.isnan(state[:2]).any()
