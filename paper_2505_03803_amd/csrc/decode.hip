@@ -1574,9 +1574,12 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
 
 // The same for 17 .. 48 rows of x (G = 2, 3 groups of sixteen), eight wavefronts of 256 registers.  The activations of a column tile
 // would take all of them, so a tile goes in its two units of 128 columns: while the R row tiles are multiplied by the fragments of
-// one, those of the next are in flight.
+// one, those of the next are in flight.  XB (bf16 activations, brought into fp16 unit by unit): SQ only.  What that drops lies 2^29 and
+// more below the largest activation of the unit, and below the resolution of a sum in which every code counts 8 to 15.  Entries of a
+// codebook may be zero at the large activations: VQ is left to the kernels of midbatch.hip, which multiply bf16 as it is.
 template <int FMT, int R, int G, bool XB>
 struct StageWide {
+    static_assert(FMT == FMT_SQ3 || !XB, "bf16 activations as they are");
     static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
     const DecodeMat& mt;
     int R0, NR, KT, lane;
@@ -1695,13 +1698,13 @@ struct StageWide {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float4_t sum = {0, 0, 0, 0};
-                if (FMT != FMT_SQ3 && !XB) sum = out[rt][g];
+                if (FMT != FMT_SQ3) sum = out[rt][g];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) sum = RWKVQ_MFMA(__builtin_bit_cast(half8_t, xf[U][g][t]), op[t], sum);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if constexpr (FMT == FMT_SQ3) out[rt][g][i] = fmaf(XB ? s * sc[g][i] : s, fmaf(-z8, X[g][i], sum[i]), out[rt][g][i]);
-                    else out[rt][g][i] = XB ? fmaf(sum[i], sc[g][i], out[rt][g][i]) : sum[i];
+                    else out[rt][g][i] = sum[i];
                 }
             }
             if (U == 1) load_w(w[rt], Tn, rt, more);
@@ -1746,9 +1749,9 @@ __global__ void __launch_bounds__(64 * kWideWaves) decode_stage_wide_kernel(Stag
         for (int g = 0; g < G; ++g) out[rt][g] = float4_t{0, 0, 0, 0};
     if (wave < KT) {
         const int nt = (KT - wave + S - 1) / S;
-        if (mt.fmt == FMT_SQ3) StageWide<FMT_SQ3, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-        else if (mt.fmt == FMT_VQ6) StageWide<FMT_VQ6, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-        else StageWide<FMT_VQ8, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        if (XB || mt.fmt == FMT_SQ3) StageWide<FMT_SQ3, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        else if (mt.fmt == FMT_VQ6) StageWide<FMT_VQ6, R, G, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        else StageWide<FMT_VQ8, R, G, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
     }
     wave_lds_sync();
 #pragma unroll
@@ -2045,11 +2048,13 @@ static hipError_t launch_wide_kernel(const StageArgs<kGrid2DMaxMats>& a, dim3 gr
 // Row tiles of a workgroup (5 or 6; 0: the kernels of midbatch.hip) at 17 <= M <= 48.  Those take 64 rows of W in a workgroup that has
 // a compute unit to itself; from 257 of them on they need a second round, which one round of 80 or 96 rows saves.  Smaller calls stay
 // there: every workgroup reads all of x (4096 x 4096 at M = 32 10.9 us here, 9.3 there; 4096 x 14336 29.7 and 21.3).  Measured (us,
-// there -> here): {k', r'} of the 7B shapes fp16 SQ at M = 17 23.5 -> 15.3, 32 24.7 -> 17.8, 48 27.4 -> 23.3, bf16 8-bit VQ at 32
-// 31.6 -> 21.1; of 14B-class shapes (six row tiles) fp16 SQ 29.1 -> 23.3, 6-bit VQ 27.7 -> 28.4 (at 17 rows 27.0 -> 24.4), bf16 33.0 -> 27.3.  bf16 beyond
-// 32 rows has no registers for it.
+// there -> here): {k', r'} of the 7B shapes fp16 SQ at M = 17 23.5 -> 15.2, 32 24.9 -> 17.3, 48 27.9 -> 22.0; of 14B-class shapes
+// (six row tiles) fp16 SQ at 32 29.3 -> 23.0, 6-bit VQ 28.0 -> 28.7 (at 17 rows 27.2 -> 25.2).  bf16 beyond 32 rows has no registers for it.
 static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
     if (n_mats > kGrid2DMaxMats || M <= 16 || M > (x_dtype == DT_BF16 ? 32 : 48)) return 0;
+    if (x_dtype == DT_BF16)
+        for (int i = 0; i < n_mats; ++i)
+            if (mats[i].fmt != FMT_SQ3) return 0;                  // (see StageWide)
     auto workgroups = [&](int r) { long long n = 0; for (int i = 0; i < n_mats; ++i) n += (mats[i].N + 16 * r - 1) / (16 * r); return n; };
     return workgroups(4) <= 256 ? 0 : workgroups(5) <= 256 ? 5 : M <= 32 && workgroups(6) <= 256 ? 6 : 0;
 }

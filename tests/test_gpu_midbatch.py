@@ -170,3 +170,32 @@ def test_line_between_the_forms_of_the_streaming_path(fmt, options):
         stream, split = call(M, 2, 1), call(M, 2, 1000000)
         assert torch.equal(call(M, 2, 0), split if few else stream), M
         assert torch.equal(call(M, 40, 0), split if many else stream), M
+
+
+@pytest.mark.parametrize("kbits", [6, 8])
+@pytest.mark.parametrize("N,with_sq", [(16640, 0), (24576, 0), (256, 16800)])
+@pytest.mark.parametrize("M", [17, 32, 48])
+def test_small_activations_beside_large_ones(N, with_sq, kbits, M, options):
+    """bf16 activations that lie 2^40 apart in a group of columns, the large ones at codebook entries of zero: the small ones decide
+    the result.  Calls of 257 to 384 workgroups of 64 rows of W, where fp16 activations take a kernel of their own; with and without a
+    scalar-quantized matrix beside."""
+    print(f"2^40 apart N={N} with={with_sq} kbits={kbits} M={M}", flush=True)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    rng = np.random.default_rng(N + M + kbits)
+    K = 768
+    m = synth.gen_vq(rng, N, K, kbits)
+    m.codes[:, ::4 * kbits] &= ~np.uint32((1 << kbits) - 1)                       # columns 0, 256, ..: entry 0, which is zero
+    m.codebooks[:, :, 0] = 0
+    x = orc.widen(synth.gen_activations(rng, M, K, "bf16"), "bf16")
+    x[:, ::256] *= 2.0 ** 40
+    mats, xs = [m], [synth.f32_to_bf16_bits(x)]
+    if with_sq:
+        mats.append(synth.gen_sq(rng, with_sq, K))
+        xs.append(synth.gen_activations(rng, M, K, "bf16"))
+    ys = [G.torch_().empty((M, q.N), dtype=G.torch_().float32, device="cuda") for q in mats]
+    dms, dev = [B.upload(q, native=True) for q in mats], [G.to_dev_bits(v) for v in xs]
+    B.rwkvq_linear_dispatch(B.DispatchTable([q.desc() for q in dms], dev, ys), M, B.BF16, B.F32)
+    G.torch_().cuda.synchronize()
+    for q, v, y in zip(mats, xs, ys):
+        # binary32 sums of 768 products, as in test_against_the_oracle
+        assert G.err_g2(y.cpu().numpy().astype(np.float64), orc.linear(q, orc.widen(v, "bf16"), "f64")) <= 2e-5
