@@ -1582,12 +1582,12 @@ struct StageWide {
     static_assert(FMT == FMT_SQ3 || !XB, "bf16 activations as they are");
     static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
     const DecodeMat& mt;
-    int R0, NR, KT, lane;
+    int R0, NR, KT, lane, block0, more_blocks;
     uint32_t xoff[G];
     float* xsc;                        // [G][16]
-    uint32_t* cb_lds;                  // [R][256]
+    uint32_t* cb_lds;                  // [2][256]: codebooks of the first and of the last row tile's block
     uint32_t mask, magic, m6, base0;
-    StageRegs w[R];
+    StageRegs w[R];                    // (a codebook in the first two only: R row tiles lie in at most two blocks)
     uint4_t xf[2][G][4];
 
     __device__ __forceinline__ StageWide(const DecodeMat& mt_, int R0_, int M, int lane_, float* xsc_, uint32_t* cb_)
@@ -1597,6 +1597,8 @@ struct StageWide {
         asm("v_mov_b32 %0, 0x03800380" : "=v"(mask));
         asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
         asm("v_mov_b32 %0, 0xfc" : "=v"(m6));
+        block0 = R0 >> 4;
+        more_blocks = ((R0 + R - 1 < NR ? R0 + R - 1 : NR - 1) >> 4) - block0;
         base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
     }
     template <int U>
@@ -1617,15 +1619,15 @@ struct StageWide {
         r.a = stream_load((const uint4_t*)t + l);
         if constexpr (FMT == FMT_VQ8) {
             r.b = stream_load((const uint4_t*)(t + 256) + l);
-            r.cb = ((const uint4_t*)mt.aux + ((size_t)(row >> 4) * KT + T) * 64)[l];
+            if (rt < 2) r.cb = ((const uint4_t*)mt.aux + ((size_t)(block0 + (rt ? more_blocks : 0)) * KT + T) * 64)[l];
         } else {
             const uint2_t two = stream_load((const uint2_t*)(t + 256) + l);
             r.b.x = two.x; r.b.y = two.y;
             if constexpr (FMT == FMT_SQ3) {
                 const uint2_t sz = stream_load((const uint2_t*)mt.aux + ((size_t)row * KT + T) * 16 + (l & 15u));
                 r.b.z = sz.x; r.b.w = sz.y;
-            } else {
-                r.b.z = ((const uint32_t*)mt.aux + ((size_t)(row >> 4) * KT + T) * 64)[l];
+            } else if (rt < 2) {
+                r.b.z = ((const uint32_t*)mt.aux + ((size_t)(block0 + (rt ? more_blocks : 0)) * KT + T) * 64)[l];
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -1654,7 +1656,7 @@ struct StageWide {
         }
         if (FMT != FMT_SQ3 && U == 0) {
 #pragma unroll
-            for (int rt = 0; rt < R; ++rt) {
+            for (int rt = 0; rt < 2; ++rt) {
                 if constexpr (FMT == FMT_VQ8) *(uint4_t*)(cb_lds + 256 * rt + 4 * lane) = w[rt].cb;
                 else cb_lds[256 * rt + lane] = w[rt].b.z;
             }
@@ -1676,9 +1678,10 @@ struct StageWide {
         for (int rt = 0; rt < R; ++rt) {
             const StageRegs& r = w[rt];
             half8_t op[4];
+            const uint32_t slot = (R0 + rt) >> 4 != block0 ? (uint32_t)more_blocks : 0u;
             if constexpr (FMT == FMT_VQ8) {
                 const uint4_t q = U == 0 ? r.a : r.b;
-                const uint32_t* cbuf = cb_lds + 256 * rt;
+                const uint32_t* cbuf = cb_lds + 256 * slot;
                 op[0] = vq8_operand(q.x, cbuf); op[1] = vq8_operand(q.y, cbuf); op[2] = vq8_operand(q.z, cbuf); op[3] = vq8_operand(q.w, cbuf);
             } else {
                 const uint32_t w0 = U == 0 ? r.a.x : r.a.w, w1 = U == 0 ? r.a.y : r.b.x, w2 = U == 0 ? r.a.z : r.b.y;
@@ -1686,7 +1689,7 @@ struct StageWide {
                     op[0] = sq_operand<0>(w0, w1, w2, mask, magic); op[1] = sq_operand<1>(w0, w1, w2, mask, magic);
                     op[2] = sq_operand<2>(w0, w1, w2, mask, magic); op[3] = sq_operand<3>(w0, w1, w2, mask, magic);
                 } else {
-                    const uint32_t base = base0 + 1024 * rt;
+                    const uint32_t base = base0 + 1024 * slot;
                     op[0] = __builtin_bit_cast(half8_t, vq6_gather4<0>(w0, w1, w2, m6, base));
                     op[1] = __builtin_bit_cast(half8_t, vq6_gather4<1>(w0, w1, w2, m6, base));
                     op[2] = __builtin_bit_cast(half8_t, vq6_gather4<2>(w0, w1, w2, m6, base));
@@ -1708,6 +1711,7 @@ struct StageWide {
                 }
             }
             if (U == 1) load_w(w[rt], Tn, rt, more);
+            else if (FMT != FMT_SQ3 && R == 6 && (rt & 1)) __builtin_amdgcn_sched_barrier(0);   // look-ups of two row tiles at a time: more would spill
         }
         load_x<U>(Tn, more);
     }
@@ -2049,7 +2053,7 @@ static hipError_t launch_wide_kernel(const StageArgs<kGrid2DMaxMats>& a, dim3 gr
 // a compute unit to itself; from 257 of them on they need a second round, which one round of 80 or 96 rows saves.  Smaller calls stay
 // there: every workgroup reads all of x (4096 x 4096 at M = 32 10.9 us here, 9.3 there; 4096 x 14336 29.7 and 21.3).  Measured (us,
 // there -> here): {k', r'} of the 7B shapes fp16 SQ at M = 17 23.5 -> 15.2, 32 24.9 -> 17.3, 48 27.9 -> 22.0; of 14B-class shapes
-// (six row tiles) fp16 SQ at 32 29.3 -> 23.0, 6-bit VQ 28.0 -> 28.7 (at 17 rows 27.2 -> 25.2).  bf16 beyond 32 rows has no registers for it.
+// (six row tiles) fp16 SQ at 32 29.3 -> 23.0, 6-bit VQ 28.4 -> 22.7.  bf16 beyond 32 rows has no registers for it.
 static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
     if (n_mats > kGrid2DMaxMats || M <= 16 || M > (x_dtype == DT_BF16 ? 32 : 48)) return 0;
     if (x_dtype == DT_BF16)
