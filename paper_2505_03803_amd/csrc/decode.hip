@@ -2051,16 +2051,28 @@ static hipError_t launch_wide_kernel(const StageArgs<kGrid2DMaxMats>& a, dim3 gr
 }
 // Row tiles of a workgroup (5 or 6; 0: the kernels of midbatch.hip) at 17 <= M <= 48.  Those take 64 rows of W in a workgroup that has
 // a compute unit to itself; from 257 of them on they need a second round, which one round of 80 or 96 rows saves.  Smaller calls stay
-// there: every workgroup reads all of x (4096 x 4096 at M = 32 10.9 us here, 9.3 there; 4096 x 14336 29.7 and 21.3).  Measured (us,
-// there -> here): {k', r'} of the 7B shapes fp16 SQ at M = 17 23.5 -> 15.2, 32 24.9 -> 17.3, 48 27.9 -> 22.0; of 14B-class shapes
-// (six row tiles) fp16 SQ at 32 29.3 -> 23.0, 6-bit VQ 28.4 -> 22.7.  bf16 beyond 32 rows has no registers for it.
+// there: every workgroup reads all of x (4096 x 4096 at M = 32 10.9 us here, 9.3 there; 4096 x 14336 29.7 and 21.3).
+// What the round costs beside its columns grows with M and the row tiles (16 R M sums of up to eight partial ones through LDS), so rows
+// of few columns stay there as M grows.  RWKVQ_OPT_STREAM_SPLIT_MAX_WORK = 1000000 takes every call that fits.
+// Measured (us, there -> here) at K = 256 to 7168, N = 16640 to 24576, M = 17 to 48 in every format: the calls that the line below lets
+// through take 0.55 to 1.02 of the time there.  16640 x 256 SQ at M = 24 9.4 -> 9.7, at 48 10.9 -> 15.4 (not taken); {k', r'} of the 7B
+// shapes fp16 SQ at M = 17 23.5 -> 15.2, 32 24.9 -> 17.3, 48 27.9 -> 22.0; of 14B-class shapes (six row tiles) fp16 SQ at 32
+// 29.3 -> 23.0, 6-bit VQ 28.4 -> 22.7.  bf16 beyond 32 rows has no registers for it.
 static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
-    if (n_mats > kGrid2DMaxMats || M <= 16 || M > (x_dtype == DT_BF16 ? 32 : 48)) return 0;
-    if (x_dtype == DT_BF16)
-        for (int i = 0; i < n_mats; ++i)
-            if (mats[i].fmt != FMT_SQ3) return 0;                  // (see StageWide)
+    const bool bf16 = x_dtype == DT_BF16;
+    if (n_mats > kGrid2DMaxMats || M <= 16 || M > (bf16 ? 32 : 48)) return 0;
+    double row_tiles = 0.0, tiles = 0.0;
+    for (int i = 0; i < n_mats; ++i) {
+        if (bf16 && mats[i].fmt != FMT_SQ3) return 0;              // (see StageWide)
+        row_tiles += mats[i].N / 16;
+        tiles += (double)(mats[i].N / 16) * (mats[i].K / 256);
+    }
     auto workgroups = [&](int r) { long long n = 0; for (int i = 0; i < n_mats; ++i) n += (mats[i].N + 16 * r - 1) / (16 * r); return n; };
-    return workgroups(4) <= 256 ? 0 : workgroups(5) <= 256 ? 5 : M <= 32 && workgroups(6) <= 256 ? 6 : 0;
+    const int R = workgroups(4) <= 256 ? 0 : workgroups(5) <= 256 ? 5 : M <= 32 && workgroups(6) <= 256 ? 6 : 0;
+    if (R == 0 || option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK) >= 1000000) return R;
+    const double columns = tiles / row_tiles;                      // of the average row
+    const double most = R == 6 ? 12.0 + 5.0 * columns : bf16 ? 14.0 + 6.0 * columns : 16.0 + 8.0 * columns;
+    return M <= most ? R : 0;
 }
 bool wide_cheaper(const MatDev* mats, int n_mats, int M, int x_dtype) { return wide_row_tiles(mats, n_mats, M, x_dtype) > 0; }
 hipError_t launch_wide(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {

@@ -77,3 +77,26 @@ def test_rule_of_one_round(N, columns, M, xdt, forced, options):
     torch.cuda.synchronize()
     assert torch.equal(ys[0], ys[1])
     assert G.err_g2(ys[0].cpu().numpy().astype(np.float64), orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
+# Both sides of the rule at 17 to 48 rows, five and six row tiles per workgroup.  Up to eight column tiles a wavefront takes one here and a
+# K group one there, and the partial sums are added in the same order, so the rule changes no bits: a call as the rule takes it, with the
+# column split wherever it fits, and its first 1024 rows alone (too small a call for it)
+@pytest.mark.parametrize("N,columns,M,xdt", [(16656, 2, 32, "f16"), (16656, 2, 33, "f16"), (16656, 2, 26, "bf16"), (16656, 2, 27, "bf16"),
+                                             (24560, 2, 22, "f16"), (24560, 2, 23, "f16"), (24560, 8, 32, "f16"), (16656, 8, 48, "f16")])
+def test_rule_of_more_rows(N, columns, M, xdt, options):
+    print(f"rule N={N} columns={columns} M={M} x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(N + columns)
+    m = synth.gen_sq(rng, N, 256 * columns)
+    few = synth.QMatrix("few", "sq", 1024, m.K, 0, m.codes[:1024].copy(), scales=m.scales[:1024].copy(), zeros=m.zeros[:1024].copy())
+    x = synth.gen_activations(rng, M, m.K, xdt)
+    dev = G.to_dev_bits(x)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    ys = []
+    for q, forced in ((m, 0), (m, 1000000), (few, 0)):
+        options(B.OPT_STREAM_SPLIT_MAX_WORK, forced)
+        ys.append(torch.full((M, q.N), 7.0, dtype=torch.float32, device="cuda"))
+        B.rwkvq_linear_dispatch(B.DispatchTable([B.upload(q, native=True).desc()], [dev], [ys[-1]]), M, B.DTYPES[xdt], B.F32)
+        torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0][:, :1024], ys[2])
+    assert G.err_g2(ys[0].cpu().numpy().astype(np.float64), orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
