@@ -1942,7 +1942,7 @@ hipError_t launch_decode_postmix(const MatDev* mats, const PostDev* posts, const
 
 // A launch that fits one workgroup of at most six row tiles on each of 256 compute units (launch_stage).
 static bool stage_one_round(const MatDev* mats, const int* order, int n_mats) {
-    if (n_mats > kGrid2DMaxMats || option(RWKVQ_OPT_SPLIT_GRID_2D) != 1) return false;
+    if (n_mats > kGrid2DMaxMats) return false;
     int n = 0;
     for (int i = 0; i < n_mats; ++i) n += (mats[order[i]].N + 16 * 6 - 1) / (16 * 6);
     return n <= 256;
@@ -2138,7 +2138,7 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         // batch 2..16 with few rows in the launch: the wavefronts of a workgroup split the columns
         if (M > 1 && M <= 16) {
             if (stage_cheaper(mats, order, cnt, M, x_dtype)) {
-                const hipError_t e = cnt <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1
+                const hipError_t e = cnt <= kGrid2DMaxMats
                                          ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, s)
                                          : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, s);
                 if (e != hipSuccess) return e;

@@ -31,12 +31,12 @@ FORCE = {None: B.SMALL_BATCH_AUTO, "stream": B.SMALL_BATCH_STREAM, "mfma": B.SMA
 @pytest.fixture(params=["columns-split", "columns-split, table of first workgroups", "256-row-workgroups", "128-row-workgroups"])
 def stretches(request, options):
     """Batch 2..32 on the streaming path has three forms, chosen by the size of the launch: small launches (RWKVQ_OPT_STREAM_SPLIT_MAX_WORK)
-    split the columns over the wavefronts of a workgroup - up to batch 16 one workgroup per 32 rows whose wavefronts fetch their
-    activation fragments themselves, beyond on the matrix-core kernels that split K - and the others take workgroups of
+    split the columns over the wavefronts of a workgroup - up to batch 16 workgroups of one to six row tiles whose wavefronts fetch
+    their activation fragments themselves, beyond on the matrix-core kernels that split K - and the others take workgroups of
     128 rows that share a staged activation tile, or of two such stretches (large launches:
-    RWKVQ_OPT_STREAM_TWO_PASS_MIN_WGS).  The test shapes are small launches, so each form is forced in turn.  The column split
-    of batch <= 16 finds matrix and stretch in a two-dimensional grid when the launch holds at most eight matrices, and in the
-    table of first workgroups otherwise: both are forced (beyond batch 16 there is one grid, and the second is skipped)."""
+    RWKVQ_OPT_STREAM_TWO_PASS_MIN_WGS).  The test shapes are small launches, so each form is forced in turn.  At batch 1 the column
+    split finds matrix and row tile in a two-dimensional grid or in the table of first workgroups: both are forced (an option that
+    changes nothing at larger batches, where calls of more than eight matrices take the table)."""
     form = request.param
     options(B.OPT_STREAM_SPLIT_MAX_WORK, 1000000 if form.startswith("columns-split") else 1)
     options(B.OPT_SPLIT_GRID_2D, 2 if form.endswith("table of first workgroups") else 1)

@@ -37,6 +37,22 @@ def test_column_split(R, columns, M, xdt, options):
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
 
 
+# An option of batch 1: batch 2 to 16 takes the same kernel with either value
+@pytest.mark.parametrize("M,xdt", [(2, "f16"), (8, "bf16"), (16, "f16")])
+@pytest.mark.parametrize("N,columns", [(1024, 4), (8192, 16), (4096, 30), (24576, 3)])
+def test_grid_option_changes_nothing(N, columns, M, xdt, options):
+    print(f"grid option N={N} columns={columns} M={M} x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(N + columns)
+    m = synth.gen_sq(rng, N, 256 * columns)
+    dm, dev = B.upload(m, native=True), G.to_dev_bits(synth.gen_activations(rng, M, m.K, xdt))
+    ys = [torch.full((M, N), 7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for i, y in enumerate(ys):
+        options(B.OPT_SPLIT_GRID_2D, 1 + i)
+        B.rwkvq_linear_dispatch(B.DispatchTable([dm.desc()], [dev], [y]), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
+
+
 # 17 to 48 rows of x, calls of 257 to 384 workgroups of 64 rows of W: five and six row tiles per workgroup, the last one partly past the
 # end of W, one and several column tiles per wavefront, another K and format in the same launch
 @pytest.mark.parametrize("row_tiles,columns", [(1025, 1), (1060, 9), (1248, 4), (1252, 3), (1500, 2), (1504, 17)])
