@@ -1506,16 +1506,16 @@ struct StageTiles {
 // What bounds it: start-up (about 4.5 us of a launch that moves nothing), then x: a compute unit reads all of x (131 KB at M = 16,
 // K = 4096) in pieces of 64 bytes per batch row, half of a cache line at a time (whole lines, timing only: o 6.5 -> 5.5 us, v'
 // 19.3 -> 15.3; it would need a transpose through LDS).  With 16 wavefronts of one column tile each every byte of a workgroup is
-// asked for at its start.  Measured (7B shapes, fp16, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
-// wavefronts (what this replaces) -> here: {r, k, v, g} 10.5 / 14.3 -> 8.1 / 9.9, o 5.9 / 8.7 -> 4.8 / 6.5, {k', r'} 13.6 / 19.4
-// -> 9.4 / 11.3, v' 13.3 / 21.4 -> 12.6 / 19.3.
+// asked for at its start.  Measured (7B shapes, fp16 SQ, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
+// wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.5, o 6.1 / 8.9 -> 5.0 / 6.8, {k', r'} 12.6 / 19.1
+// -> 9.3 / 10.7, v' 13.1 / 21.5 -> 11.4 / 18.4.
 // most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight
 constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
     int wg_end[kGrid2D ? 1 : MATS];
     DecodeMat m[MATS];
-    int M, xdt, ydt, S;
+    int M, xdt, ydt, S, waves, pad;
 };
 template <int R, bool MULTI, class Args>
 __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kernel(Args a) {
@@ -1532,9 +1532,9 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
             mi += __builtin_popcountll(__builtin_amdgcn_ballot_w64(wg >= a.wg_end[j + (threadIdx.x & 63)]));
         group = wg - (mi ? a.wg_end[mi - 1] : 0);
     }
-    const int M = a.M, xdt = a.xdt, ydt = a.ydt, S = a.S;          // the end of the argument block: asked for with the descriptor
+    const int M = a.M, xdt = a.xdt, ydt = a.ydt, S = a.S, waves = a.waves;   // the end of the argument block: asked for with the descriptor
     const DecodeMat mt = a.m[mi];
-    asm volatile("" :: "s"(M), "s"(xdt), "s"(ydt), "s"(S), "s"(mt.N));
+    asm volatile("" :: "s"(M), "s"(xdt), "s"(ydt), "s"(S), "s"(waves), "s"(mt.N));
     const int R0 = R * group;
     if (Args::kGrid2D && 16 * R0 >= mt.N) return;
     const int lane = threadIdx.x & 63;
@@ -1545,7 +1545,7 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
     float4_t out[R];
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) out[rt] = float4_t{0, 0, 0, 0};
-    if (wave < KT) {
+    if (wave < KT && wave < S) {
         const int nt = (KT - wave + S - 1) / S;
         if (xdt == DT_BF16) {
             if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
@@ -1558,12 +1558,14 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
         }
     }
     wave_lds_sync();                                               // (the codebook slots are read)
+    if (wave < S) {
 #pragma unroll
-    for (int rt = 0; rt < R; ++rt) *(float4_t*)(mine + 256 * rt + 4 * lane) = out[rt];
+        for (int rt = 0; rt < R; ++rt) *(float4_t*)(mine + 256 * rt + 4 * lane) = out[rt];
+    }
     __syncthreads();
     // D layout of the MFMA: lane (n, mg) holds batch rows 4 mg .. 4 mg + 3 of output column n
     const float* sums = (const float*)stage_lds;
-    for (int i = threadIdx.x; i < 16 * R * M; i += 64 * S) {
+    for (int i = threadIdx.x; i < 16 * R * M; i += 64 * waves) {
         const int m = i / (16 * R), n = i - 16 * R * m;
         const int at = 256 * (n >> 4) + 4 * (16 * (m >> 2) + (n & 15)) + (m & 3);
         float t = sums[at];
@@ -1940,6 +1942,82 @@ hipError_t launch_decode_postmix(const MatDev* mats, const PostDev* posts, const
     return hipSuccess;
 }
 
+template <int R, bool MULTI, class Args>
+static hipError_t launch_stage_kernel(const Args& a, dim3 grid, hipStream_t s) {
+    const int lds = a.S * (R > 2 ? R : 2) * 1024;
+    if (lds > 60 * 1024) {
+        static std::atomic<unsigned long long> raised{0ull};
+        const hipError_t e = raise_lds((const void*)decode_stage_kernel<R, MULTI, Args>, 16 * R * 1024, raised);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((decode_stage_kernel<R, MULTI, Args>), grid, dim3(64 * a.waves), lds, s, a);
+    return hipGetLastError();
+}
+// Launches of more matrices than the two-dimensional grid takes (the table) know one, two and four row tiles per workgroup.
+constexpr int stage_rows(bool grid2d, int r) { return grid2d ? r : r == 3 ? 4 : r > 4 ? 0 : r; }
+enum StageKind { STAGE_SHORT, STAGE_ROUND, STAGE_MIXED, STAGE_ROUNDS, STAGE_MIXED_ROUNDS };
+struct StageShape {
+    int R, S, turns, waves;            // row tiles of a workgroup; wavefronts that split the columns, tiles that one takes; wavefronts in all
+    StageKind kind;
+    int columns;                       // of the longest row
+    double row_tiles;
+};
+// Row tiles R and wavefronts S of a workgroup, swept over R = 1 .. 6 and S = 3 .. 16 at M = 2 to 16 in every format and both types of
+// x (us: fp16 where no type is named, cold weights).  `spread` is the longest row over the average one.
+//   * rows of at most 512 columns: a workgroup is over so soon that small ones, several to a compute unit, are best: 14336 x 256 SQ at
+//     M = 8 4.3 with R = 4 and a workgroup per compute unit, 3.6 with R = 1; 24 of 2048 x 512 6.0 with R = 4, 7.6 with R = 1;
+//   * one round: the fewest row tiles that make at most 256 workgroups, each with a compute unit to itself and, up to sixteen, a
+//     wavefront per column tile: every byte is asked for at the start ({r, k, v, g} of the 7B shapes in SQ at M = 16 9.9, in four
+//     wavefronts 11.2; {k', r'} 11.1 and 12.9).  Longer rows in turns of eight wavefronts (v' in SQ at M = 8 13.9, of fourteen 15.2), of twelve from
+//     three row tiles on and with two in bf16, whose conversion every wavefront repeats (5120 x 5120 6-bit VQ at M = 2 9.1, of seven 9.6);
+//   * one round, mixed lengths: a workgroup of the longest rows would end long after the others: two row tiles instead of three to
+//     six, or one (a layer of d = 2048 in 8-bit VQ at M = 2 20.2 with R = 6, now 13.4; {8192 x 256, 256 x 8192} in SQ at M = 8 12.2 and 9.4);
+//   * several rounds, of one length or of mixed ones: small workgroups overlap ({k', r', v'} of the 14B-class shapes in 8-bit VQ at M = 4
+//     46.0 with R = 4, now 29.1; a 7B layer 38.6 and 31.9).
+// A wavefront takes R M / 4 steps for the sums at the end by itself: four at least take part, eight in one round of R >= 3.
+static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, int x_dtype) {
+    const bool grid2d = n_mats <= kGrid2DMaxMats;
+    int columns = 0, fits = 0;
+    double row_tiles = 0.0, tiles = 0.0, vq8 = 0.0;
+    for (int i = 0; i < n_mats; ++i) {
+        const MatDev& m = mats[order[i]];
+        columns = std::max(columns, m.K >> 8);
+        row_tiles += m.N >> 4; tiles += (double)(m.N >> 4) * (m.K >> 8);
+        if (m.fmt == FMT_VQ8) vq8 += m.N >> 4;
+    }
+    for (int r = 1; r <= 6 && !fits; ++r) {
+        if (stage_rows(grid2d, r) != r) continue;
+        long long n = 0;
+        for (int i = 0; i < n_mats; ++i) n += (mats[order[i]].N + 16 * r - 1) / (16 * r);
+        if (n <= 256) fits = r;
+    }
+    const double spread = columns * row_tiles / tiles;
+    StageShape p;
+    p.columns = columns; p.row_tiles = row_tiles;
+    int most;
+    if (columns <= 2) {
+        p.kind = STAGE_SHORT;
+        p.R = row_tiles <= 1024.0 ? 1 : row_tiles <= 2560.0 ? 2 : 4; most = 2;
+    } else if (fits && (spread <= 1.6 || fits <= (columns <= 16 ? 3 : 2))) {
+        p.kind = STAGE_ROUND;
+        p.R = fits; most = columns <= 16 ? 16 : fits == 1 || (fits == 2 && x_dtype != DT_BF16) ? 8 : 12;
+    } else if (fits) {
+        p.kind = STAGE_MIXED;
+        p.R = spread > 8.0 ? 1 : 2; most = columns <= 16 ? 16 : row_tiles <= 1000.0 ? 8 : 4;
+    } else if (spread <= 1.6) {
+        p.kind = STAGE_ROUNDS;
+        p.R = row_tiles <= 1600.0 ? 2 : 4; most = columns <= 8 ? 8 : 4;
+    } else {
+        p.kind = STAGE_MIXED_ROUNDS;
+        p.R = row_tiles <= 2200.0 || (!grid2d && row_tiles <= 2700.0 && 2.0 * vq8 > row_tiles) ? 2 : grid2d ? 3 : 4;
+        most = spread > 8.0 ? 6 : 4;
+    }
+    p.turns = (columns + most - 1) / most;
+    p.S = (columns + p.turns - 1) / p.turns;
+    p.waves = std::max(p.S, fits >= 3 && p.R == fits ? 8 : 4);
+    return p;
+}
+
 // A launch that fits one workgroup of at most six row tiles on each of 256 compute units (launch_stage).
 static bool stage_one_round(const MatDev* mats, const int* order, int n_mats) {
     if (n_mats > kGrid2DMaxMats) return false;
@@ -1988,57 +2066,29 @@ static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int 
     return split * kStreamSplitMaxWork <= (3.0 + std::pow(std::pow(chain, 6.0) + std::pow(rows, 6.0), 1.0 / 6.0)) * max_work;
 }
 
-template <int R, bool MULTI, class Args>
-static hipError_t launch_stage_kernel(const Args& a, dim3 grid, hipStream_t s) {
-    const int lds = a.S * (R > 2 ? R : 2) * 1024;
-    if (lds > 60 * 1024) {
-        static std::atomic<unsigned long long> raised{0ull};
-        const hipError_t e = raise_lds((const void*)decode_stage_kernel<R, MULTI, Args>, 16 * R * 1024, raised);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((decode_stage_kernel<R, MULTI, Args>), grid, dim3(64 * a.S), lds, s, a);
-    return hipGetLastError();
-}
-// Row tiles R and wavefronts S of a workgroup.  One workgroup per compute unit is best where the launch allows it: the fewest row
-// tiles that make at most 256 workgroups, as many wavefronts as share the columns evenly (of up to sixteen).  Launches of more than
-// 6 x 256 row tiles run in several rounds, which overlap when several small workgroups share a compute unit: four row tiles, four
-// wavefronts.  Measured (7B shapes, fp16, cold weights, us; one round / four wavefronts): {r, k, v, g} at M = 16 9.9 / 11.6,
-// {k', r'} 11.3 / 17.2, v' 19.3 / 24.6; a whole layer, 33.9 / 28.6 at M = 2 and 38.4 / 37.8 at M = 16.
 template <int MATS>
-static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype, int y_dtype, const StageShape& p, hipStream_t s) {
     StageArgs<MATS> a;
-    int columns = 0, wgs = 0, longest = 0, R = 4;
-    bool one_round = false;
+    int wgs = 0, longest = 0;
     for (int i = 0; i < MATS; ++i) {
         a.m[i] = DecodeMat{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, POST_NONE, nullptr};
-        if (i >= n_mats) continue;
-        const MatDev& m = mats[order[i]];
-        a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, POST_NONE, nullptr};
-        columns = std::max(columns, m.K >> 8);
-    }
-    auto workgroups = [&](int r) { int n = 0; for (int i = 0; i < n_mats; ++i) n += (mats[order[i]].N + 16 * r - 1) / (16 * r); return n; };
-    if constexpr (StageArgs<MATS>::kGrid2D)
-        for (int r = 1; r <= 6 && !one_round; ++r)
-            if (workgroups(r) <= 256) { one_round = true; R = r; }
-    const int most = one_round ? stage_waves(columns > stage_waves(false, R), R) : 4, turns = (columns + most - 1) / most;
-    a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = (columns + turns - 1) / turns;
-    for (int i = 0; i < n_mats; ++i) {
-        const int n = (mats[order[i]].N + 16 * R - 1) / (16 * R);
-        wgs += n; longest = std::max(longest, n);
-        if constexpr (!StageArgs<MATS>::kGrid2D) a.wg_end[i] = wgs;
-    }
-    if constexpr (!StageArgs<MATS>::kGrid2D) {
-        for (int i = n_mats; i < MATS; ++i) a.wg_end[i] = 0x7FFFFFFF;
-        return launch_stage_kernel<4, true>(a, dim3(wgs), s);
-    } else {
-        const dim3 grid(longest, n_mats);
-#define RWKVQ_STAGE(R_) case R_: return turns > 1 ? launch_stage_kernel<R_, true>(a, grid, s) : launch_stage_kernel<R_, false>(a, grid, s);
-        switch (R) {
-            RWKVQ_STAGE(1) RWKVQ_STAGE(2) RWKVQ_STAGE(3) RWKVQ_STAGE(4) RWKVQ_STAGE(5) RWKVQ_STAGE(6)
-            default: return hipErrorInvalidValue;
+        if (i < n_mats) {
+            const MatDev& m = mats[order[i]];
+            const int n = (m.N + 16 * p.R - 1) / (16 * p.R);
+            a.m[i] = DecodeMat{m.codes, m.aux, m.x, m.y, m.N, m.K, m.fmt, POST_NONE, nullptr};
+            wgs += n; longest = std::max(longest, n);
         }
-#undef RWKVQ_STAGE
+        if constexpr (!StageArgs<MATS>::kGrid2D) a.wg_end[i] = i < n_mats ? wgs : 0x7FFFFFFF;
     }
+    a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = p.S; a.waves = p.waves; a.pad = 0;
+    const dim3 grid = StageArgs<MATS>::kGrid2D ? dim3(longest, n_mats) : dim3(wgs);
+#define RWKVQ_STAGE(R_) case R_: if constexpr (stage_rows(StageArgs<MATS>::kGrid2D, R_) == R_) \
+        return p.turns > 1 ? launch_stage_kernel<R_, true>(a, grid, s) : launch_stage_kernel<R_, false>(a, grid, s); break;
+    switch (p.R) {
+        RWKVQ_STAGE(1) RWKVQ_STAGE(2) RWKVQ_STAGE(3) RWKVQ_STAGE(4) RWKVQ_STAGE(5) RWKVQ_STAGE(6)
+    }
+#undef RWKVQ_STAGE
+    return hipErrorInvalidValue;
 }
 
 template <int R, int G, bool XB>
@@ -2138,9 +2188,9 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         // batch 2..16 with few rows in the launch: the wavefronts of a workgroup split the columns
         if (M > 1 && M <= 16) {
             if (stage_cheaper(mats, order, cnt, M, x_dtype)) {
-                const hipError_t e = cnt <= kGrid2DMaxMats
-                                         ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, s)
-                                         : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, s);
+                const StageShape p = stage_shape(mats, order, cnt, x_dtype);
+                const hipError_t e = cnt <= kGrid2DMaxMats ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s)
+                                                           : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s);
                 if (e != hipSuccess) return e;
                 continue;
             }

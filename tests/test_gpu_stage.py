@@ -37,6 +37,45 @@ def test_column_split(R, columns, M, xdt, options):
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
 
 
+# More matrices than the two-dimensional grid takes: one, two and four row tiles per workgroup, one column tile per wavefront and several
+@pytest.mark.parametrize("rows,n", [(3, 11), (40, 12), (100, 10), (130, 14)])
+@pytest.mark.parametrize("columns", [2, 3, 17])
+@pytest.mark.parametrize("M,xdt", [(3, "bf16"), (16, "f16")])
+def test_column_split_of_many_matrices(rows, n, columns, M, xdt, options):
+    print(f"column split of {n} matrices of {rows} row tiles columns={columns} M={M} x={xdt}", flush=True)
+    options(B.OPT_STREAM_SPLIT_MAX_WORK, 1000000)
+    torch, rng = G.torch_(), np.random.default_rng(rows + columns)
+    kinds = [synth.gen_sq(rng, 16 * rows, 256 * columns), synth.gen_vq(rng, 256 * max(1, rows // 16), 256, 6),
+             synth.gen_vq(rng, 256 * max(1, rows // 16), 256 * columns, 8)]
+    up, xs = [B.upload(m, native=True) for m in kinds], [synth.gen_activations(rng, M, m.K, xdt) for m in kinds]
+    of = [i % 3 for i in range(n)]
+    dev = [G.to_dev_bits(xs[k]) for k in of]
+    ys = [torch.full((M + 1, kinds[k].N), 7.0, dtype=torch.float32, device="cuda") for k in of]
+    B.rwkvq_linear_dispatch(B.DispatchTable([up[k].desc() for k in of], dev, ys), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    want = [orc.linear(m, orc.widen(x, xdt), "f64") for m, x in zip(kinds, xs)]
+    for k, y in zip(of, ys):
+        got = y.cpu().numpy().astype(np.float64)
+        assert (got[M] == 7.0).all()
+        assert G.err_g2(got[:M], want[k]) <= 2e-5          # as above
+
+
+# An option of batch 1: batch 2 to 16 takes the same kernel with either value
+@pytest.mark.parametrize("M,xdt", [(2, "f16"), (8, "bf16"), (16, "f16")])
+@pytest.mark.parametrize("N,columns", [(1024, 4), (8192, 16), (4096, 30), (24576, 3)])
+def test_grid_option_changes_nothing(N, columns, M, xdt, options):
+    print(f"grid option N={N} columns={columns} M={M} x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(N + columns)
+    m = synth.gen_sq(rng, N, 256 * columns)
+    dm, dev = B.upload(m, native=True), G.to_dev_bits(synth.gen_activations(rng, M, m.K, xdt))
+    ys = [torch.full((M, N), 7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for i, y in enumerate(ys):
+        options(B.OPT_SPLIT_GRID_2D, 1 + i)
+        B.rwkvq_linear_dispatch(B.DispatchTable([dm.desc()], [dev], [y]), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
+
+
 # An option of batch 1: batch 2 to 16 takes the same kernel with either value
 @pytest.mark.parametrize("M,xdt", [(2, "f16"), (8, "bf16"), (16, "f16")])
 @pytest.mark.parametrize("N,columns", [(1024, 4), (8192, 16), (4096, 30), (24576, 3)])
