@@ -2018,52 +2018,42 @@ static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, 
     return p;
 }
 
-// A launch that fits one workgroup of at most six row tiles on each of 256 compute units (launch_stage).
-static bool stage_one_round(const MatDev* mats, const int* order, int n_mats) {
-    if (n_mats > kGrid2DMaxMats) return false;
-    int n = 0;
-    for (int i = 0; i < n_mats; ++i) n += (mats[order[i]].N + 16 * 6 - 1) / (16 * 6);
-    return n <= 256;
-}
-
-// Batch 2..16: is the column split (decode_stage_kernel) the faster of the two?  Both durations in us.  decode_kernel takes the longer of
-// one wavefront's way through the longest row and the launch's share of the memory rate.  The column split in one round takes a launch's
-// 2.2 us, a time per tile of 16 x 256 weights, per row tile (more with more rows of x: they are reduced through LDS) and per column tile
-// of the longest row (x, which every workgroup reads); in several rounds their starts and ends come on top.  Fitted to launches of 1 to
-// 32 layers of widths 1024 to 5120 and, for one round, to 950 of 1 to 8 matrices of up to 24576 x 3072 weights at M = 2 to 16 in each
-// format: 19 of those take the slower one by more than 4 % (with the fixed 8 us of several rounds 429 did, by up to 124 %), nearly all of
-// 24576 SQ rows, which stay with decode_kernel by up to 35 %; {16384 x 512, 4096 x 1024} of 8-bit VQ goes the other way, 7.2 us in rows
-// and 8.9 in columns at M = 16.  Measured (fp16 SQ, M = 8, us, rows / columns): 1024 x 1024 5.7 / 3.1, four of 2048 x 2048 8.9 / 4.6,
-// {14336 + 4096} x 4096 15.3 / 9.3, 24576 x 768 6.1 / 5.4, 24576 x 2560 10.9 / 8.6.
-// Launches whose rows have at most 512 columns keep the fixed 8 us, which leaves them to decode_kernel: alone or among hundreds of
-// matrices such a matrix gives the same bits (columns at M = 8, 1024 x 512: 2.6 us for 4.1, 24576 x 512: 5.4 for 4.9).
-// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK moves the line in proportion (1: never split, 1000000: always).
-static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype) {
+// Batch 2..16: is the column split (decode_stage_kernel) the faster of the two?  Measured on 8248 launches of 1 to 256 matrices, K = 256
+// to 17920, up to 21504 row tiles, M = 2 to 16, every format, both types of x (us: columns / rows).  In a launch of one round it always is
+// (4672 of them; 4096 x 4096 SQ at M = 8 5.5 / 14.7, 1024 x 1024 3.1 / 5.6).  Beyond, decode_kernel fills the device too, and its
+// workgroups share what they read of x:
+//   * rows of at most 512 columns: up to 4200 row tiles, 1536 beyond M = 8, where the end of a workgroup weighs more (256 of 256 x 512 SQ
+//     at M = 4 5.2 / 5.9, at 16 7.5 / 6.2): 15 of 2024 take a kernel that is more than 4 % slower, the worst 11 %;
+//   * several rounds of one length: up to 3200 row tiles, and M = 12 up to 2048 columns (24 of 2048 x 1024 SQ at M = 8 7.4 / 8.8), M = 4
+//     beyond (44 of 512 x 2560: SQ at M = 8 11.8 / 10.7, 8-bit VQ at 2 11.8 / 12.8): 94 of 816, the worst 23 %;
+//   * several rounds of mixed lengths (whole layers): an estimate of both durations: 15 of 736, the worst 14 %.
+// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK moves the lines in proportion (1: never split, 1000000: always).
+static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype, const StageShape& p) {
     const int max_work = option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK);
     if (max_work <= 1 || max_work >= 1000000) return max_work > 1;
+    const double by = (double)max_work / kStreamSplitMaxWork;
+    // (stacks: every workgroup's own read of x grows with them)
+    if (p.row_tiles * (16 + M) > 4.0 * kStreamSplitMaxWork * by) return false;
+    switch (p.kind) {
+        case STAGE_ROUND: case STAGE_MIXED: return true;
+        case STAGE_SHORT: return p.row_tiles <= (M <= 8 ? 4200.0 : 1536.0) * by;
+        case STAGE_ROUNDS: return p.row_tiles <= 3200.0 * by && M <= (p.columns <= 8 ? 12 : 4);
+        default: break;
+    }
     const bool bf16 = x_dtype == DT_BF16;
-    double split = 0.0, once = 0.0, rows = 0.0, chain = 0.0;
-    int columns = 0;
-    long long stretches = 0;
+    double rows = 0.0, chain = 0.0, split = 0.0;
     for (int i = 0; i < n_mats; ++i) {
         const MatDev& m = mats[order[i]];
-        const double row_tiles = m.N / 16, tiles = row_tiles * (m.K / 256);
+        const double tiles = 1e-3 * (m.N >> 4) * (m.K >> 8);
         const int f = m.fmt == FMT_SQ3 ? 0 : m.fmt == FMT_VQ6 ? 1 : 2;
-        static const double kSplit[3] = {1.0, 1.0, 1.15}, kRows[3] = {1.0, 1.1, 1.45}, kChain[3] = {0.73, 0.93, 1.15};
-        split += (0.26e-3 * tiles + 1.3e-3 * row_tiles) * kSplit[f];
-        once += 0.17e-3 * tiles * kSplit[f] + (1.03e-3 + 0.088e-3 * M) * row_tiles;
-        columns = std::max(columns, m.K / 256);
-        rows += 0.353e-3 * tiles * kRows[f];
-        chain = std::max(chain, (m.K / 256) * (kChain[f] + (bf16 ? 0.2 : 0.0)));
-        stretches += (m.N + 31) / 32;
+        static const double kSplit[3] = {0.269, 0.269, 0.342}, kRows[3] = {0.257, 0.270, 0.378}, kChain[3] = {0.69, 0.80, 0.91};
+        split += tiles * (kSplit[f] + 0.0062 * M + (bf16 ? 0.0525 : 0.0));
+        rows += tiles * kRows[f];
+        chain = std::max(chain, (m.K >> 8) * (kChain[f] + (bf16 ? 0.25 : 0.0)));
     }
-    // stacks beyond the fitted range: every workgroup's own read of x grows with them, half a stack of 14B-class shapes at M = 16 in
-    // bf16 takes 937 us in columns and 752 in rows
-    if (stretches * (16 + M) > 2LL * max_work) return false;
-    split = columns > 2 && stage_one_round(mats, order, n_mats) ? 2.2 + once + columns * (0.136 + 0.0054 * M + (bf16 ? 0.05 : 0.0))
-                                                 : 8.0 + split * (1.0 + 0.028 * (M - 2)) * (bf16 ? 1.2 - 0.009 * (M - 2) : 1.0);
-    rows *= (1.0 + 0.008 * M) * (bf16 ? 1.05 : 1.0);
-    return split * kStreamSplitMaxWork <= (3.0 + std::pow(std::pow(chain, 6.0) + std::pow(rows, 6.0), 1.0 / 6.0)) * max_work;
+    split += 4.46 + 0.195 * M + (0.73 + 0.002 * M) * 1e-3 * p.row_tiles + 0.072 * p.columns + (bf16 ? 0.76 : 0.0);
+    rows = rows * (1.0 + 0.016 * M) * (bf16 ? 1.053 : 1.0) + 0.318e-3 * p.row_tiles;
+    return split <= (3.0 + 0.021 * M + std::pow(std::pow(rows, 2.3) + std::pow(chain, 2.3), 1.0 / 2.3)) * by;
 }
 
 template <int MATS>
@@ -2187,8 +2177,8 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         }
         // batch 2..16 with few rows in the launch: the wavefronts of a workgroup split the columns
         if (M > 1 && M <= 16) {
-            if (stage_cheaper(mats, order, cnt, M, x_dtype)) {
-                const StageShape p = stage_shape(mats, order, cnt, x_dtype);
+            const StageShape p = stage_shape(mats, order, cnt, x_dtype);
+            if (stage_cheaper(mats, order, cnt, M, x_dtype, p)) {
                 const hipError_t e = cnt <= kGrid2DMaxMats ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s)
                                                            : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s);
                 if (e != hipSuccess) return e;

@@ -76,22 +76,6 @@ def test_grid_option_changes_nothing(N, columns, M, xdt, options):
     assert torch.equal(ys[0], ys[1])
 
 
-# An option of batch 1: batch 2 to 16 takes the same kernel with either value
-@pytest.mark.parametrize("M,xdt", [(2, "f16"), (8, "bf16"), (16, "f16")])
-@pytest.mark.parametrize("N,columns", [(1024, 4), (8192, 16), (4096, 30), (24576, 3)])
-def test_grid_option_changes_nothing(N, columns, M, xdt, options):
-    print(f"grid option N={N} columns={columns} M={M} x={xdt}", flush=True)
-    torch, rng = G.torch_(), np.random.default_rng(N + columns)
-    m = synth.gen_sq(rng, N, 256 * columns)
-    dm, dev = B.upload(m, native=True), G.to_dev_bits(synth.gen_activations(rng, M, m.K, xdt))
-    ys = [torch.full((M, N), 7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
-    for i, y in enumerate(ys):
-        options(B.OPT_SPLIT_GRID_2D, 1 + i)
-        B.rwkvq_linear_dispatch(B.DispatchTable([dm.desc()], [dev], [y]), M, B.DTYPES[xdt], B.F32)
-    torch.cuda.synchronize()
-    assert torch.equal(ys[0], ys[1])
-
-
 # 17 to 48 rows of x, calls of 257 to 384 workgroups of 64 rows of W: five and six row tiles per workgroup, the last one partly past the
 # end of W, one and several column tiles per wavefront, another K and format in the same launch
 @pytest.mark.parametrize("row_tiles,columns", [(1025, 1), (1060, 9), (1248, 4), (1252, 3), (1500, 2), (1504, 17)])
@@ -115,10 +99,15 @@ def test_column_split_of_more_rows(row_tiles, columns, M, xdt, options):
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
 
 
-# The rule's two sides of calls that fit one round, bit for bit the kernel it is to take, and against the oracle
+# The rule's two sides, bit for bit the kernel it is to take, and against the oracle: one round, always the column split (1536 row tiles are
+# the most that fit one); several rounds up to 3200 row tiles and M = 12, or 4 from nine column tiles on; rows of at most 512 columns
+# up to 4200 row tiles, 1536 beyond M = 8
 @pytest.mark.parametrize("N,columns,M,xdt,forced", [(1024, 4, 8, "f16", 1000000), (256, 3, 2, "bf16", 1000000), (1024, 8, 16, "bf16", 1000000),
-                                                    (24576, 3, 16, "f16", 1), (24592, 3, 16, "bf16", 1), (1024, 2, 8, "f16", 1)])
-def test_rule_of_one_round(N, columns, M, xdt, forced, options):
+                                                    (24576, 3, 16, "f16", 1000000), (24592, 3, 16, "bf16", 1), (24592, 3, 12, "bf16", 1000000),
+                                                    (51216, 3, 8, "f16", 1), (24592, 9, 4, "f16", 1000000), (24592, 9, 5, "f16", 1),
+                                                    (1024, 2, 8, "f16", 1000000), (67200, 2, 8, "f16", 1000000), (67216, 2, 8, "f16", 1),
+                                                    (24576, 2, 9, "bf16", 1000000), (24592, 2, 9, "bf16", 1)])
+def test_rule(N, columns, M, xdt, forced, options):
     print(f"rule N={N} columns={columns} M={M} x={xdt}", flush=True)
     torch, rng = G.torch_(), np.random.default_rng(N + columns)
     m = synth.gen_sq(rng, N, 256 * columns)
