@@ -514,27 +514,60 @@ static PfShape pick_shape(int M, long long n_tiles) {
     return best;
 }
 
-// Estimated duration here: one launch per format and 64 matrices, 7.4 us per column tile of a 256-row workgroup.
-static double tiles_us(const std::vector<MatDev>& mats, int M) {
-    double us = 0.0;
+// A launch over matrices of one format: tiles of 256 rows of W, the shape, and where whole rounds of 256 x 256 tiles with what is left
+// of them in tiles of half the rows of W end sooner than a last round with a few tiles ({key, receptance} of the 7B shapes at M =
+// 2048, 576 tiles: 344 -> 306 us), how many of the tiles the whole rounds take (0: one launch).  Matrices of one K only: elsewhere
+// the shorter ones fill the end.  Longest rows first.
+struct PfPlan { int tiles, whole; PfShape p; };
+static PfPlan plan_tiles(const std::vector<MatDev>& batch, int M) {
+    PfPlan plan{0, 0, {}};
+    for (const MatDev& m : batch) plan.tiles += m.N / 256;
+    plan.p = pick_shape(M, plan.tiles);
+    const PfShape& p = plan.p;
+    const int m_tiles = (M + 255) / 256, whole = (int)((long long)plan.tiles * m_tiles / 256 * 256 / m_tiles);
+    if (option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0 && whole > 0 && whole < plan.tiles && batch.front().K == batch.back().K &&
+        rounds((long long)whole * m_tiles) + kShapes[2].cost * rounds((long long)(plan.tiles - whole) * 2 * m_tiles) + 0.05 <
+            p.cost * rounds((long long)plan.tiles * (256 / p.bn) * ((M + p.bm - 1) / p.bm)))
+        plan.whole = whole;
+    return plan;
+}
+
+// The matrices of one launch after another: one format, at most 64, in order.
+template <class F>
+static void each_batch(const std::vector<MatDev>& sorted, F&& f) {
     for (int fmt = 0; fmt < 3; ++fmt) {
-        size_t i = 0;
-        while (i < mats.size()) {
-            long long n_tiles = 0;
-            int cnt = 0;
-            size_t end = i;
-            for (; end < mats.size() && cnt < kPfMaxMats; ++end)
-                if (mats[end].fmt == fmt) { n_tiles += mats[end].N / 256; ++cnt; }
-            if (cnt) {
-                const PfShape p = pick_shape(M, n_tiles);
-                LaunchLoad load;
-                for (size_t j = i; j < end; ++j)
-                    if (mats[j].fmt == fmt) load.add((long long)(mats[j].N / p.bn) * ((M + p.bm - 1) / p.bm), mats[j].K);
-                us += 3.0 + load.columns(0.2) * p.cost * 7.4;
-            }
-            i = end;
+        std::vector<MatDev> batch;
+        for (size_t i = 0; i <= sorted.size(); ++i) {
+            if (i < sorted.size() && sorted[i].fmt == fmt) batch.push_back(sorted[i]);
+            if (batch.empty() || ((int)batch.size() < kPfMaxMats && i < sorted.size())) continue;
+            f(batch);
+            batch.clear();
         }
     }
+}
+// Workgroups of a matrix with a long K run long: put those matrices first so that the end of a launch is filled by short workgroups.
+static std::vector<MatDev> longest_first(const MatDev* mats, int n_mats) {
+    std::vector<MatDev> sorted(mats, mats + n_mats);
+    std::stable_sort(sorted.begin(), sorted.end(), [](const MatDev& a, const MatDev& b) { return a.K > b.K; });
+    return sorted;
+}
+
+// Estimated duration here: 7.4 us per column tile of a 256-row workgroup, 3 us per launch.
+static double tiles_us(const std::vector<MatDev>& mats, int M) {
+    double us = 0.0;
+    each_batch(longest_first(mats.data(), (int)mats.size()), [&](const std::vector<MatDev>& batch) {
+        const PfPlan plan = plan_tiles(batch, M);
+        const PfShape& p = plan.p;
+        LaunchLoad load;
+        for (const MatDev& m : batch) load.add((long long)(m.N / p.bn) * ((M + p.bm - 1) / p.bm), m.K);
+        double t = load.columns(0.2) * p.cost * 7.4;
+        if (plan.whole) {
+            const int m_tiles = (M + 255) / 256;
+            t = std::min(t, 3.0 + 7.4 * (batch.front().K >> 8) * (rounds((long long)plan.whole * m_tiles) +
+                                                                  kShapes[2].cost * rounds((long long)(plan.tiles - plan.whole) * 2 * m_tiles)));
+        }
+        us += 3.0 + t;
+    });
     return us;
 }
 
@@ -545,7 +578,9 @@ static double tiles_us(const std::vector<MatDev>& mats, int M) {
 // formats; M = 129 .. 1536; us, here / there): none takes the slower one by more than 4 %.  There: {r, k, v, g} of two formats
 // at M = 1024 178 / 140, 4096 x 4096 alone 82 / 41, value 269 / 120, one layer 595 / 454, 32 layers at 333 rows 6047 / 5453.
 // Here: 14336 x 4096 alone 120 / 136, {r, k, v, g} of one format 125 / 142, four layers 1559 / 1722, 32 layers
-// 12435 / 14509.  The order of a matrix's binary32 sums over K differs between the two, so for 128 < M <= kMidMaxM it depends
+// 12435 / 14509.  With whole rounds and a rest in the estimate (1650 calls, widths 1024 to 5120, M = 129 to 1536, bf16) 15 calls take the
+// tiles that took the others, {key, receptance} and key alone: 14336 x 4096 SQ at M = 1536 221 -> 203, {key, receptance} of 14B-class
+// shapes at 900 259 -> 248.  The order of a matrix's binary32 sums over K differs between the two, so for 128 < M <= kMidMaxM it depends
 // on the sizes of the call; a forced tile height (RWKVQ_OPT_PREFILL_TILE_ROWS) stays here, with one order for every M > 128.
 constexpr int kMidMaxM = 1536;
 static bool mid_takes(const MatDev& m, int M) { return M <= kMidMaxM && m.K <= (1 << 20) && option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0; }
@@ -576,34 +611,14 @@ static hipError_t launch_batch(const std::vector<MatDev>& batch, int t0, int t1,
     }
 }
 
-static hipError_t launch_prefill_tiles(const MatDev* mats_in, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
-    // Workgroups of a matrix with a long K run long: put those matrices first so that the end of
-    // a launch is filled by short workgroups.
-    std::vector<MatDev> sorted(mats_in, mats_in + n_mats);
-    std::stable_sort(sorted.begin(), sorted.end(), [](const MatDev& a, const MatDev& b) { return a.K > b.K; });
-    // one grouped launch per format and per 64 matrices
-    for (int fmt = 0; fmt < 3; ++fmt) {
-        std::vector<MatDev> batch;
-        for (int i = 0; i <= n_mats; ++i) {
-            if (i < n_mats && sorted[i].fmt == fmt) batch.push_back(sorted[i]);
-            if (batch.empty() || ((int)batch.size() < kPfMaxMats && i < n_mats)) continue;
-            int n_tiles = 0;
-            for (const MatDev& m : batch) n_tiles += m.N / 256;
-            const PfShape p = pick_shape(M, n_tiles);
-            // Whole rounds of 256 x 256 tiles and what is left of them in tiles of half the rows of W, where that ends sooner than a
-            // last round with a few tiles ({key, receptance} of the 7B shapes at M = 2048, 576 tiles: 344 -> 306 us).  Matrices of
-            // one K only: elsewhere the shorter ones fill the end.
-            const int m_tiles = (M + 255) / 256, whole = (int)((long long)n_tiles * m_tiles / 256 * 256 / m_tiles);
-            const bool split = option(RWKVQ_OPT_PREFILL_TILE_ROWS) == 0 && whole > 0 && whole < n_tiles && batch.front().K == batch.back().K &&
-                               rounds((long long)whole * m_tiles) + kShapes[2].cost * rounds((long long)(n_tiles - whole) * 2 * m_tiles) + 0.05 <
-                                   p.cost * rounds((long long)n_tiles * (256 / p.bn) * ((M + p.bm - 1) / p.bm));
-            hipError_t e = launch_batch(batch, 0, split ? whole : n_tiles, split ? kShapes[0] : p, M, x_dtype, y_dtype, s);
-            if (e == hipSuccess && split) e = launch_batch(batch, whole, n_tiles, kShapes[2], M, x_dtype, y_dtype, s);
-            if (e != hipSuccess) return e;
-            batch.clear();
-        }
-    }
-    return hipSuccess;
+static hipError_t launch_prefill_tiles(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    each_batch(longest_first(mats, n_mats), [&](const std::vector<MatDev>& batch) {
+        const PfPlan plan = plan_tiles(batch, M);
+        if (e == hipSuccess) e = launch_batch(batch, 0, plan.whole ? plan.whole : plan.tiles, plan.whole ? kShapes[0] : plan.p, M, x_dtype, y_dtype, s);
+        if (e == hipSuccess && plan.whole) e = launch_batch(batch, plan.whole, plan.tiles, kShapes[2], M, x_dtype, y_dtype, s);
+    });
+    return e;
 }
 
 hipError_t launch_prefill(const MatDev* mats, int n_mats, int M, int x_dtype, int y_dtype, hipStream_t s) {

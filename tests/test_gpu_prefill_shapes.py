@@ -36,3 +36,19 @@ def test_shapes_give_the_same_bits(fmt, Ns, M, K, xdt, options):
     for a, b in zip(*out):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
         assert (a[M] == 7.0).all()
+
+
+@pytest.mark.parametrize("xdt", ["bf16", "f16"])
+def test_line_below_1536_rows_knows_the_rest(xdt, options):
+    """336 tiles of 256 x 256: one whole round and a rest in tiles of half the rows of W, which is estimated at less than the kernels
+    that split K (and those at less than any one shape): the bits of the large tiles."""
+    print(f"line x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(5)
+    M, N, K = 1536, 14336, 1024
+    m, x = synth.gen_sq(rng, N, K), G.to_dev_bits(synth.gen_activations(rng, M, K, xdt))
+    dm, ys = B.upload(m, native=True), []
+    for rows in (0, 256):
+        options(B.OPT_PREFILL_TILE_ROWS, rows)
+        ys.append(B.gemm(dm, x, M, B.DTYPES[xdt], B.F32))
+        torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
