@@ -1509,7 +1509,9 @@ struct StageTiles {
 // asked for at its start.  Measured (7B shapes, fp16 SQ, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
 // wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.5, o 6.1 / 8.9 -> 5.0 / 6.8, {k', r'} 12.6 / 19.1
 // -> 9.3 / 10.7, v' 13.1 / 21.5 -> 11.4 / 18.4.
-// most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight
+// most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight.  Five and six row tiles spill up
+// to seven of the 168; eight wavefronts of 256 spill none and were no better (us, batch 8, twelve -> eight: 20480 x 8192, fp16 SQ 18.7 ->
+// 17.6 and bf16 VQ 22.3 -> 20.9, but 24576 x 4352 12.5 -> 13.4 and 13.8 -> 16.2: its 17 column tiles take three turns in place of two).
 constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
@@ -1852,19 +1854,21 @@ hipError_t launch_decode_rkv_wkv(const MatDev* rkv, const WkvDev& wkv, int x_dty
 // Smallest S of 4, 8, 16 that brings `tiles` row tiles to kSplitTarget wavefronts.
 static int pick_split(int tiles) { return tiles * 4 >= kSplitTarget ? 4 : tiles * 8 >= kSplitTarget ? 8 : 16; }
 
-// n_mats <= kGrid2DMaxMats: grid (longest matrix's row tiles, matrices); else one row of `wgs` workgroups and the table
+// n_mats <= kGrid2DMaxMats: grid (longest matrix's row tiles, matrices); else one row of `wgs` workgroups and the table.  The tables of
+// eight and of 256 matrices are for one of the two each (launch_decode).
 template <class Args>
 static hipError_t launch_splitk(int split, int wgs, Args& a, int n_mats, hipStream_t s) {
     a.pad = 0;
-    if (Args::kMats == kGrid2DMaxMats || (n_mats <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1)) {
-        int longest = 0;
-        for (int i = 0; i < n_mats; ++i) longest = std::max(longest, a.wg_end[i] - (i ? a.wg_end[i - 1] : 0));
-        const dim3 grid(longest, n_mats);
-        if (split == 4) hipLaunchKernelGGL((decode_splitk_kernel<4, Args, true>), grid, dim3(256), 0, s, a);
-        else if (split == 8) hipLaunchKernelGGL((decode_splitk_kernel<8, Args, true>), grid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL((decode_splitk_kernel<16, Args, true>), grid, dim3(1024), 0, s, a);
-        return hipGetLastError();
-    }
+    if constexpr (Args::kMats < kMaxGroupMats)
+        if (Args::kMats == kGrid2DMaxMats || (n_mats <= kGrid2DMaxMats && option(RWKVQ_OPT_SPLIT_GRID_2D) == 1)) {
+            int longest = 0;
+            for (int i = 0; i < n_mats; ++i) longest = std::max(longest, a.wg_end[i] - (i ? a.wg_end[i - 1] : 0));
+            const dim3 grid(longest, n_mats);
+            if (split == 4) hipLaunchKernelGGL((decode_splitk_kernel<4, Args, true>), grid, dim3(256), 0, s, a);
+            else if (split == 8) hipLaunchKernelGGL((decode_splitk_kernel<8, Args, true>), grid, dim3(512), 0, s, a);
+            else hipLaunchKernelGGL((decode_splitk_kernel<16, Args, true>), grid, dim3(1024), 0, s, a);
+            return hipGetLastError();
+        }
     if constexpr (Args::kMats > kGrid2DMaxMats) {
         const dim3 grid(wgs);
         if (split == 4) hipLaunchKernelGGL((decode_splitk_kernel<4, Args, false>), grid, dim3(256), 0, s, a);
