@@ -219,13 +219,13 @@ __global__ void __launch_bounds__(kFinalThreads, 1) proxy_final_kernel(ProxyArgs
     }
     // fixed-order sums: lanes of a wavefront first, then the wavefronts
 #pragma unroll
-    for (int k = 0; k <= kMaxTerms; ++k) {
-        if (k > terms) break;
-        double v = s[k];
+    for (int k = 0; k <= kMaxTerms; ++k)
+        if (k <= terms) {
+            double v = s[k];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if (lane == 0) red[wave][k] = v;
-    }
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+            if (lane == 0) red[wave][k] = v;
+        }
     __syncthreads();
     if (tid <= terms) {
         double v = 0.0;
