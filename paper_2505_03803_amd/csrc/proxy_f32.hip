@@ -484,6 +484,7 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetGroup g) {
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
         total[i] = 0u;
+#pragma unroll 4                                  // (all eighty looked up at once would spill)
         for (int w = 0; w < kSetThreads / 64; ++w) { if (w < wave) run[i] += wave_sum[w][i]; total[i] += wave_sum[w][i]; }
     }
     b.occupied[tid] = uint2_t{occupied, run[4]};
@@ -936,15 +937,17 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, i
             for (int j = 0; j < kBitmapWords / 4; j += kSumThreads) ((uint4_t*)data)[j + tid] = uint4_t{0u, 0u, 0u, 0u};
             __syncthreads();
             uint32_t i = tid;
+            asm volatile("" : "+v"(i));                                       // (made again per bin, not kept over the loop around: it would spill)
             auto set = [&](uint32_t k) {                                      // (a wavefront of equal keys: one of them)
                 const unsigned long long live = __builtin_amdgcn_ballot_w64(true);
                 const bool equal = __builtin_amdgcn_ballot_w64(k == (uint32_t)__builtin_amdgcn_readfirstlane((int)k)) == live;
                 if (!equal || (live & lanes_below(tid & 63)) == 0ull) atomicOr(&data[(k >> 5) & (kBitmapWords - 1)], 1u << (k & 31u));
             };
             // eight keys at a time, the next eight in flight; past the end the last key again, which changes nothing
+            auto key_at = [&](uint32_t at) { return *(const uint32_t*)((const char*)keys + 4u * min(at, n - 1u)); };   // (32-bit offsets)
             uint32_t k[8];
 #pragma unroll
-            for (uint32_t j = 0; j < 8u; ++j) k[j] = keys[min(i + j * kSumThreads, n - 1u)];
+            for (uint32_t j = 0; j < 8u; ++j) k[j] = key_at(i + j * kSumThreads);
 #pragma unroll 1
             while (i < n) {
                 uint32_t now[8];
@@ -953,7 +956,7 @@ __global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, i
                 i += 8u * kSumThreads;
                 if (i < n)
 #pragma unroll
-                    for (uint32_t j = 0; j < 8u; ++j) k[j] = keys[min(i + j * kSumThreads, n - 1u)];
+                    for (uint32_t j = 0; j < 8u; ++j) k[j] = key_at(i + j * kSumThreads);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) set(now[j]);
             }
