@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 # R: the fewest row tiles per workgroup that make at most 256 workgroups; 7: none of 1..6 does.  16 and 17 column tiles: the most that
-# wavefronts take one each, and the fewest that they take in turns (9 wavefronts, two each but the last); 25: three turns of nine.
+# wavefronts take one each, and the fewest that they take in turns (six wavefronts with R = 1, nine with R >= 3, the last ones with
+# fewer); 25: four turns of seven.  At M = 3 and R >= 3 the rows are of mixed lengths, and a workgroup takes one or two row tiles.
 @pytest.mark.parametrize("R,columns", [(1, 1), (1, 16), (1, 17), (1, 25), (2, 16), (2, 17), (3, 5), (3, 17), (4, 1), (4, 17), (5, 3), (5, 17),
                                        (6, 2), (6, 17), (7, 1), (7, 9)])
 @pytest.mark.parametrize("M,xdt", [(3, "bf16"), (16, "f16")])
@@ -58,6 +59,25 @@ def test_column_split_of_many_matrices(rows, n, columns, M, xdt, options):
         got = y.cpu().numpy().astype(np.float64)
         assert (got[M] == 7.0).all()
         assert G.err_g2(got[:M], want[k]) <= 2e-5          # as above
+
+
+# bf16 rows of one length in one round: three to six row tiles per workgroup, one column tile per wavefront and two
+@pytest.mark.parametrize("R,columns", [(3, 3), (3, 17), (4, 5), (4, 17), (5, 3), (5, 17), (6, 3), (6, 18)])
+def test_column_split_of_one_length_bf16(R, columns):
+    M = 7
+    print(f"column split of one length R={R} columns={columns} M={M}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(R + columns)
+    rows = 256 * (R - 1) + 1 - 32
+    mats = [synth.gen_sq(rng, 16 * rows, 256 * columns), synth.gen_vq(rng, 256, 256 * columns, 6), synth.gen_vq(rng, 256, 256 * columns, 8)]
+    xs = [synth.gen_activations(rng, M, m.K, "bf16") for m in mats]
+    dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
+    ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
+    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.BF16, B.F32)
+    torch.cuda.synchronize()
+    for m, x, y in zip(mats, xs, ys):
+        got = y.cpu().numpy().astype(np.float64)
+        assert (got[M] == 7.0).all()
+        assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, "bf16"), "f64")) <= 2e-5          # as above
 
 
 # An option of batch 1: batch 2 to 16 takes the same kernel with either value
