@@ -113,9 +113,10 @@ const char* rwkvq_status_string(int status);
  *                                 still has at least this many workgroups that way, and 128 rows otherwise
  *                                 (2048; 1 = always 256 rows, 1000000 = never)
  *   RWKVQ_OPT_STREAM_SPLIT_MAX_WORK    batch 2..16 on the streaming kernels: a launch takes the small-launch form (the
- *                                 wavefronts of a workgroup split the columns, every workgroup reads all of x) where an
- *                                 estimate of both durations says it is the faster one: one RWKV-6-7B layer at any M <= 16, two
- *                                 to four by M and format.  The line moves in proportion to the option (65536; 1 = never,
+ *                                 wavefronts of a workgroup split the columns, every workgroup reads all of x) where it was
+ *                                 measured to be the faster one: whenever 256 workgroups of up to 96 rows of W hold it, larger
+ *                                 launches by the lengths of their rows, their number and M.  Those lines move in proportion
+ *                                 to the option (65536; 1 = never,
  *                                 1000000 = always).  The streaming path at 17..128 has such a form too (kernels that split
  *                                 K on the matrix cores, weights exact as well): at 17..32 for launches of up to 1792
  *                                 workgroups of 64 rows of W (two such layers), a number that moves in proportion to the

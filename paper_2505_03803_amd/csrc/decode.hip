@@ -1507,8 +1507,8 @@ struct StageTiles {
 // K = 4096) in pieces of 64 bytes per batch row, half of a cache line at a time (whole lines, timing only: o 6.5 -> 5.5 us, v'
 // 19.3 -> 15.3; it would need a transpose through LDS).  With 16 wavefronts of one column tile each every byte of a workgroup is
 // asked for at its start.  Measured (7B shapes, fp16 SQ, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
-// wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.5, o 6.1 / 8.9 -> 5.0 / 6.8, {k', r'} 12.6 / 19.1
-// -> 9.3 / 10.7, v' 13.1 / 21.5 -> 11.4 / 18.4.
+// wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.8, o 6.1 / 8.9 -> 5.1 / 6.8, {k', r'} 12.6 / 19.1
+// -> 8.8 / 11.1, v' 13.1 / 21.5 -> 11.5 / 18.5.
 // most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight.  Five and six row tiles spill up
 // to seven of the 168; eight wavefronts of 256 spill none and were no better (us, batch 8, twelve -> eight: 20480 x 8192, fp16 SQ 18.7 ->
 // 17.6 and bf16 VQ 22.3 -> 20.9, but 24576 x 4352 12.5 -> 13.4 and 13.8 -> 16.2: its 17 column tiles take three turns in place of two).

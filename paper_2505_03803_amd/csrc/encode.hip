@@ -279,8 +279,9 @@ __device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const f
 // tested without branches into a bit each, and a cell's list is written from its bits (a branch and a store per entry that some
 // cell wants took 28 us of a workgroup alone on its compute unit with 256 entries, now 10).  A few queued pairs (step 4) are taken
 // four at a time by sixteen lanes.
-// Measured (bf16, near-normal weights, us; every pair against every entry, with lists built entry by entry, here): 4096 x 4096, 64
-// entries 77, 56, 55, 256 entries 279, 100, 87; 14336 x 4096, 256 entries 887, 238, 219; 1024 x 1024, 256 entries 83, 53, 39.  Without
+// Measured (bf16, near-normal weights, one in a thousand ten times as wide, one matrix repeated, us; every pair against every entry,
+// with lists built entry by entry, here): 4096 x 4096, 64 entries 77, 56, 55, 256 entries 279, 100, 89; 14336 x 4096, 256 entries 887,
+// 238, 220; 1024 x 1024, 256 entries 83, 53, 39; without the wide ones 53, 80 and 213, 43.  Without
 // step 5 and the second form of step 4, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 186 and 502
 // (now 68 and 219), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the
 // entries zero 162 and 170 (70 and 122).  Registers: 64, for two workgroups on a compute unit (74: 14336 x 4096, 64 entries

@@ -300,14 +300,14 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
-// Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 1.7 TB/s for 14336 x 4096.  The busiest
-// unit is the LDS (counters at 4096 x 4096: active 41 % in the partition, 28 % in the count, 24 % in the sums, half of it bank
-// conflicts); sixteen wavefronts per compute unit run reads, counters and stores between barriers.
-// Measured (us; radix sort -> here): 768 x 768 157 -> 89, 1024 x 1024 163 -> 96, 4096 x 4096 502 -> 136, 14336 x 4096 1957 -> 339
-// (count 56, plan 15, partition 152, sum 91, final 12); there with all weights equal 1570 -> 400, values of bfloat16 1783 -> 642,
-// half the weights zero 1850 -> 490.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20
-// weights 192 -> 152; bit patterns at random, 2^20 163 -> 148, 2^22 213 -> 221, 2^24 503 -> 604 (the one kind found that is slower
-// here).  Below kSetMinCount the sort.
+// Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 2.8 TB/s for 14336 x 4096.  The busiest
+// unit is the LDS (counters at 4096 x 4096 / 14336 x 4096: active 40 / 44 % in the partition, 28 / 24 % in the count, 31 / 23 % in the
+// sums, half of it bank conflicts, two thirds in the count); sixteen wavefronts per compute unit run reads, counters and stores
+// between barriers.
+// Measured (us; radix sort -> here): 768 x 768 157 -> 93, 1024 x 1024 163 -> 98, 4096 x 4096 502 -> 138, 14336 x 4096 1957 -> 340
+// (partition 154, sum 88); there with all weights equal 1570 -> 385, values of bfloat16 1783 -> 549, half the weights zero
+// 1850 -> 404.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20 weights 192 -> 152; bit patterns
+// at random, 2^20 163 -> 148, 2^22 213 -> 232, 2^24 503 -> 605 (the one kind found that is slower here).  Below kSetMinCount the sort.
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
 constexpr int kBins = 32768, kBinShift = 17;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
@@ -850,7 +850,7 @@ __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, d
 // Bitonic sort of a group: thread t holds keys 4 t .. 4 t + 3 of up to 2048 (`size` of them, a power of two from 256 on, the rest
 // of the threads only meet the barriers).  Steps of up to 128 keys stay within a wavefront, in registers (strides 1 and 2) and
 // by lane exchanges; the six longer ones of 2048 keys go through LDS, in two buffers that alternate, a barrier each.
-// With all 66 steps through LDS, 2^24 random patterns took 1070 us instead of 604, 4096 x 4096 normal weights 173 instead of 161.
+// With all 66 steps through LDS, 2^24 random patterns took 1070 us instead of 605, 4096 x 4096 normal weights 173 instead of 161.
 template <int L>
 __device__ __forceinline__ uint32_t from_lane_xor(uint32_t v) {
     if constexpr (L == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);     // quad_perm [1, 0, 3, 2]
