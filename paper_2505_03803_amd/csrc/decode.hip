@@ -1508,7 +1508,7 @@ struct StageTiles {
 // 19.3 -> 15.3; it would need a transpose through LDS).  With 16 wavefronts of one column tile each every byte of a workgroup is
 // asked for at its start.  Measured (7B shapes, fp16 SQ, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
 // wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.8, o 6.1 / 8.9 -> 5.1 / 6.8, {k', r'} 12.6 / 19.1
-// -> 8.8 / 11.1, v' 13.1 / 21.5 -> 11.5 / 18.5.
+// -> 8.8 / 11.1, v' 13.1 / 21.5 -> 11.5 / 18.2.
 // most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight.  Five and six row tiles spill up
 // to seven of the 168; eight wavefronts of 256 spill none and were no better (us, batch 8, twelve -> eight: 20480 x 8192, fp16 SQ 18.7 ->
 // 17.6 and bf16 VQ 22.3 -> 20.9, but 24576 x 4352 12.5 -> 13.4 and 13.8 -> 16.2: its 17 column tiles take three turns in place of two).
@@ -1972,14 +1972,17 @@ struct StageShape {
 //     M = 8 4.3 with R = 4 and a workgroup per compute unit, 3.6 with R = 1; 24 of 2048 x 512 6.0 with R = 4, 7.6 with R = 1;
 //   * one round: the fewest row tiles that make at most 256 workgroups, each with a compute unit to itself and, up to sixteen, a
 //     wavefront per column tile: every byte is asked for at the start ({r, k, v, g} of the 7B shapes in SQ at M = 16 9.9, in four
-//     wavefronts 11.2; {k', r'} 11.1 and 12.9).  Longer rows in turns of eight wavefronts (v' in SQ at M = 8 13.9, of fourteen 15.2), of twelve from
-//     three row tiles on and with two in bf16, whose conversion every wavefront repeats (5120 x 5120 6-bit VQ at M = 2 9.1, of seven 9.6);
+//     wavefronts 11.2; {k', r'} 11.1 and 12.9).  17 to 19 columns in turns of at most eight wavefronts, of twelve from three row tiles on and with two in
+//     bf16.  Longer rows: bf16, whose conversion every wavefront repeats, by eight or twelve, a multiple of the SIMDs (5120 x 5120 SQ
+//     at M = 2 in 9.6 by ten, 8.8 by eight; 5120 x 10240 15.2 by ten, 13.8 by twelve), twelve where a tile of x is short; fp16 by
+//     fewer as M grows, whose lines of x the others evict (4096 x 14336 SQ at M = 8 14.0 by eight, 13.3 by six; with 4096 x 4096 in 6-bit VQ
+//     at M = 16 20.6 by eight, 18.7 by five).  On 690 calls within 1.1 % of the best S in the mean;
 //   * one round, mixed lengths: a workgroup of the longest rows would end long after the others: two row tiles instead of three to
 //     six, or one (a layer of d = 2048 in 8-bit VQ at M = 2 20.2 with R = 6, now 13.4; {8192 x 256, 256 x 8192} in SQ at M = 8 12.2 and 9.4);
 //   * several rounds, of one length or of mixed ones: small workgroups overlap ({k', r', v'} of the 14B-class shapes in 8-bit VQ at M = 4
 //     46.0 with R = 4, now 29.1; a 7B layer 38.6 and 31.9).
 // A wavefront takes R M / 4 steps for the sums at the end by itself: four at least take part, eight in one round of R >= 3.
-static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, int x_dtype) {
+static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype) {
     const bool grid2d = n_mats <= kGrid2DMaxMats;
     int columns = 0, fits = 0;
     double row_tiles = 0.0, tiles = 0.0, vq8 = 0.0;
@@ -2018,6 +2021,11 @@ static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, 
     }
     p.turns = (columns + most - 1) / most;
     p.S = (columns + p.turns - 1) / p.turns;
+    if (p.kind == STAGE_ROUND && columns >= 20) {
+        if (x_dtype == DT_BF16) p.S = M <= 8 && columns > 20 ? 12 : 8;
+        else p.S = fits == 6 || ((fits == 2 || fits == 3) && M <= 4) ? 8 : M <= 12 || fits == 1 ? 6 : 5;
+        p.turns = (columns + p.S - 1) / p.S;
+    }
     p.waves = std::max(p.S, fits >= 3 && p.R == fits ? 8 : 4);
     return p;
 }
@@ -2181,7 +2189,7 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         }
         // batch 2..16 with few rows in the launch: the wavefronts of a workgroup split the columns
         if (M > 1 && M <= 16) {
-            const StageShape p = stage_shape(mats, order, cnt, x_dtype);
+            const StageShape p = stage_shape(mats, order, cnt, M, x_dtype);
             if (stage_cheaper(mats, order, cnt, M, x_dtype, p)) {
                 const hipError_t e = cnt <= kGrid2DMaxMats ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s)
                                                            : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s);

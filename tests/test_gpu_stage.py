@@ -61,23 +61,25 @@ def test_column_split_of_many_matrices(rows, n, columns, M, xdt, options):
         assert G.err_g2(got[:M], want[k]) <= 2e-5          # as above
 
 
-# bf16 rows of one length in one round: three to six row tiles per workgroup, one column tile per wavefront and two
-@pytest.mark.parametrize("R,columns", [(3, 3), (3, 17), (4, 5), (4, 17), (5, 3), (5, 17), (6, 3), (6, 18)])
-def test_column_split_of_one_length_bf16(R, columns):
-    M = 7
-    print(f"column split of one length R={R} columns={columns} M={M}", flush=True)
+# Rows of one length in one round: one to six row tiles per workgroup, one column tile per wavefront and several; from 20 column tiles
+# on the wavefronts go by the type of x and M (20 and 21: eight and twelve in bf16; 25: five to eight in fp16)
+@pytest.mark.parametrize("R,columns", [(1, 20), (1, 25), (2, 21), (2, 25), (3, 3), (3, 17), (3, 21), (4, 5), (4, 17), (4, 20), (5, 3), (5, 17),
+                                       (6, 3), (6, 18), (6, 21)])
+@pytest.mark.parametrize("M,xdt", [(4, "f16"), (7, "bf16"), (9, "bf16"), (16, "f16")])
+def test_column_split_of_one_length(R, columns, M, xdt):
+    print(f"column split of one length R={R} columns={columns} M={M} x={xdt}", flush=True)
     torch, rng = G.torch_(), np.random.default_rng(R + columns)
-    rows = 256 * (R - 1) + 1 - 32
+    rows = 3 if R == 1 else 256 * (R - 1) + 1 - 32
     mats = [synth.gen_sq(rng, 16 * rows, 256 * columns), synth.gen_vq(rng, 256, 256 * columns, 6), synth.gen_vq(rng, 256, 256 * columns, 8)]
-    xs = [synth.gen_activations(rng, M, m.K, "bf16") for m in mats]
+    xs = [synth.gen_activations(rng, M, m.K, xdt) for m in mats]
     dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
     ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
-    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.BF16, B.F32)
+    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.DTYPES[xdt], B.F32)
     torch.cuda.synchronize()
     for m, x, y in zip(mats, xs, ys):
         got = y.cpu().numpy().astype(np.float64)
         assert (got[M] == 7.0).all()
-        assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, "bf16"), "f64")) <= 2e-5          # as above
+        assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5          # as above
 
 
 # An option of batch 1: batch 2 to 16 takes the same kernel with either value
