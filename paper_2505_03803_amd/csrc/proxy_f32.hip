@@ -286,38 +286,40 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 // From kSetMinCount weights on nothing is sorted through memory.  The sums need the distinct values in order and the number of
 // equal neighbours, not the sorted sequence:
 //
-//   * set_count_kernel      32768 bins, a bin being the upper 15 bits of the key (sign, exponent, six bits of fraction): counts
+//   * set_count_kernel      8192 bins, a bin being the upper 13 bits of the key (sign, exponent, four bits of fraction): counts
 //                           per workgroup of a contiguous range in LDS, then one reservation per workgroup and bin;
 //   * set_plan_kernel       where each bin starts.  Bins of more than 1024 keys ("hot", of near-normal weights the ones
 //                           within some octaves of the deviation) stand behind the others, in groups of at most 2047 keys;
 //   * set_partition_kernel  every key to its bin: position = start + reservation + an LDS counter per bin.  The order inside a
 //                           bin does not matter (and is not fixed), so no ranks are needed;
-//   * set_sum_kernel        a hot bin is 2^17 patterns of one sign and exponent: a bitmap of 16 KB in LDS.  Intervals are
+//   * set_sum_kernel        a hot bin is 2^19 patterns of one sign and exponent: a bitmap of 64 KB in LDS.  Intervals are
 //                           distances of set bits times the exponent's unit, exact, and counted by distance.  A bin of more
 //                           than 131072 keys and a 64th of all is read by several workgroups that join their bitmaps in
-//                           memory, and the last to finish sums (joined beyond 131072 keys in any case, 14336 x 4096 took
-//                           107 us more).  A group of small bins is sorted (sort_group);
+//                           memory, and the last to finish sums.  A group of small bins is sorted (sort_group);
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
 // The sums depend only on sets and counts, so the result is the same on every run although the partition's order is not.
-// Bound: the phases of a workgroup one after another, not memory: 16 bytes per weight at 2.8 TB/s for 14336 x 4096.  The busiest
-// unit is the LDS (counters at 4096 x 4096 / 14336 x 4096: active 40 / 44 % in the partition, 28 / 24 % in the count, 31 / 23 % in the
-// sums, half of it bank conflicts, two thirds in the count); sixteen wavefronts per compute unit run reads, counters and stores
-// between barriers.
-// Measured (us; radix sort -> here): 768 x 768 157 -> 93, 1024 x 1024 163 -> 98, 4096 x 4096 502 -> 138, 14336 x 4096 1957 -> 340
-// (partition 154, sum 88); there with all weights equal 1570 -> 385, values of bfloat16 1783 -> 549, half the weights zero
-// 1850 -> 404.  Weights over many octaves are all small bins: 2^(uniform from -40 to 20) at 3 x 2^20 weights 192 -> 152; bit patterns
-// at random, 2^20 163 -> 148, 2^22 213 -> 232, 2^24 503 -> 605 (the one kind found that is slower here).  Below kSetMinCount the sort.
+// Bound: the partition by memory (14336 x 4096: 470 MB in 110 us, 4.3 TB/s); the count by reading (4.9 TB/s); the sums by the LDS, which
+// takes 17 clocks for 64 atomic operations: 626000 keys of the fullest bin of 14336 x 4096 are set in 82 us, by one compute unit, so
+// that matrices share launches (launch_sets).  Bins of 2^17 patterns, of which the sums are better balanced (87 us instead of 105 there),
+// cost the partition 40 us more: runs of a quarter of the length, and a table of ranks in LDS where this one is addressed by the bin.
+// Between the two, 2^18: 142 and 89 us.  Four workgroups for a full bin, of which each reads all keys and keeps a quarter of the patterns, take
+// as long per atomic operation and were slower (4096 x 4096 122 -> 152 us).
+// Measured (us; radix sort, bins of 2^17 -> here): 768 x 768 157, 90 -> 55, 1024 x 1024 163, 95 -> 56, 4096 x 4096 502, 138 -> 122,
+// 14336 x 4096 1957, 350 -> 307; the eight matrices of a layer of the 7B shapes 7060, 1320 -> 1040, of d = 1024 598 -> 331.
+// 2^24 weights: values of bfloat16 178 -> 146, uniform 123 -> 126, all equal 139 -> 141, half zero 167 -> 146; bit patterns at random 569 -> 210
+// (2^20: 122 -> 71), 2^(uniform from -40 to 20) 205 -> 136.  Below kSetMinCount the sort.
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
-constexpr int kBins = 32768, kBinShift = 17;
+constexpr int kBins = 8192, kBinShift = 19;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
-constexpr int kBitmapWords = 1 << (kBinShift - 5);           // 4096
+constexpr int kBitmapWords = 1 << (kBinShift - 5);           // 16384
 constexpr int kSetThreads = 1024;
 constexpr int kSetRow = kGapSums + 1;                        // partial sums and the number of intervals above zero
-constexpr int kSumThreads = 512, kSumWorkgroups = 512;
-constexpr int kTable = 512;
+constexpr int kSumThreads = 512, kSumWorkgroups = 512;       // (two workgroups per compute unit; one of 1024 threads: a call of a layer 85 us more)
+constexpr int kTable = 3072;                                 // distances that are counted: six per thread, 12 KB beside the bitmap
+constexpr uint32_t kDense = 1u << (kBinShift - 3);
 
-struct SetHead { uint32_t min_key, max_key, groups, pieces, joints, bins; };
+struct SetHead { uint32_t min_key, max_key, groups, pieces, joints, pad; };
 // One matrix of a call.
 struct SetBuffers {
     const uint32_t* in;      // the weights
@@ -325,20 +327,20 @@ struct SetBuffers {
     uint32_t solo, joint_max;
     double* out;             // P_c, P_f
     int32_t* phi;
-    uint32_t* keys;          // partitioned: groups of small bins, then the hot bins, each in bin order; shared by the matrices
+    uint32_t* keys;          // partitioned: groups of small bins, then the hot bins, each in bin order; shared by launches
     uint32_t* reserved;      // [workgroup][bin]: keys of the bin reserved before
     SetHead* head;
     uint32_t* counts;        // [bin]
+    double* logs;            // [kTable]: logarithms of 1, 2, ..
     uint32_t* least;         // [counting workgroup]: its smallest and largest key
     uint32_t* most;
-    uint2_t* occupied;       // [bin / 32]: bit = the bin holds keys; occupied bins before these 32
     uint32_t* start;         // [bin]: position of the bin in keys
     uint32_t* group_from;    // [group + 1]: position of the group's first key
     uint32_t* bin_min;       // [bin], of occupied bins
     uint32_t* bin_max;
     uint4_t* piece;          // [piece]: bin, first position, keys, joint bitmap of a bin in several pieces
     uint32_t* done;          // [joint]: pieces finished
-    uint32_t* joint;         // [joint][4096]
+    uint32_t* joint;         // [joint][kBitmapWords]
     double* sums;            // [workgroups of set_sum_kernel, then joint bins][kSetRow]
 };
 // Matrices that are cleared, counted, planned and concluded in one launch each: four launches of 5, 15 and 13 us for one workgroup's
@@ -350,16 +352,16 @@ static uint32_t set_joint_max(uint32_t count) { return std::min(count / kPiece, 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static size_t set_key_bytes(uint32_t count) { return align256((size_t)count * 4); }
 // A matrix's own buffers from `base` on; returns their size.
-static size_t set_tables(SetBuffers& b, char* base, uint32_t count) {
+static size_t set_tables(SetBuffers& b, char* base, uint32_t count, uint32_t range = kCountRange) {
     size_t o = 0;
     auto take = [&](size_t bytes) { char* p = base + o; o += align256(bytes); return p; };
-    b.count = count; b.wgs = set_workgroups(count); b.solo = piece_solo(count); b.joint_max = set_joint_max(count);
+    b.count = count; b.wgs = set_workgroups(count, range); b.solo = piece_solo(count); b.joint_max = set_joint_max(count);
     b.reserved = (uint32_t*)take((size_t)b.wgs * kBins * 4);
     b.head = (SetHead*)take(sizeof(SetHead));
     b.counts = (uint32_t*)take(kBins * 4);
+    b.logs = (double*)take(kTable * 8);
     b.least = (uint32_t*)take(256 * 4);
     b.most = (uint32_t*)take(256 * 4);
-    b.occupied = (uint2_t*)take(kBins / 4);
     b.start = (uint32_t*)take(kBins * 4);
     b.group_from = (uint32_t*)take(((size_t)count / kHot + 2) * 4);
     b.bin_min = (uint32_t*)take(kBins * 4);
@@ -373,11 +375,20 @@ static size_t set_tables(SetBuffers& b, char* base, uint32_t count) {
 
 __global__ void __launch_bounds__(256) set_clear_kernel(SetGroup g) {
     const SetBuffers& b = g.b[blockIdx.y];
-    const uint32_t joint_max = b.joint_max;
     const uint32_t i = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
     for (uint32_t j = i; j < (uint32_t)kBins; j += step) b.counts[j] = 0u;
-    for (uint32_t j = i; j < joint_max; j += step) b.done[j] = 0u;
-    for (size_t j = i; j < (size_t)joint_max * kBitmapWords / 4; j += step) ((uint4_t*)b.joint)[j] = uint4_t{0u, 0u, 0u, 0u};
+    for (uint32_t j = i; j < b.joint_max; j += step) b.done[j] = 0u;
+    for (uint32_t j = i; j < (uint32_t)kTable; j += step) b.logs[j] = j ? log((double)j) : 0.0;
+}
+
+// Inclusive running sum over the lanes of the wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);     // row_shr 1, 2, 4, 8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);    // row_bcast 15 into rows 1 and 3
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast 31 into rows 2 and 3
 }
 
 // Applies f to every pattern of the range, four loads of 16 bytes in flight per thread.
@@ -436,40 +447,38 @@ __global__ void __launch_bounds__(kSetThreads) set_count_kernel(SetGroup g) {
         b.most[blockIdx.x] = most;
     }
     uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
-    // sixteen reservations in flight per thread, each workgroup from another bin on
-#pragma unroll 1
-    for (int i = tid; i < kBins; i += 16 * kSetThreads) {
-        uint32_t c[16], got[16];
-        auto bin = [&](int r) { return (uint32_t)(i + r * kSetThreads + 128 * (int)blockIdx.x) & (kBins - 1); };
+    // eight reservations in flight per thread, each workgroup from another bin on
+    constexpr int kOwn = kBins / kSetThreads;
+    uint32_t c[kOwn], got[kOwn];
+    auto bin = [&](int r) { return (uint32_t)(tid + r * kSetThreads + kBins / 256 * (int)blockIdx.x) & (kBins - 1); };
 #pragma unroll
-        for (int r = 0; r < 16; ++r) c[r] = h[bin(r)];
+    for (int r = 0; r < kOwn; ++r) c[r] = h[bin(r)];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) if (c[r]) got[r] = atomicAdd(&b.counts[bin(r)], c[r]);
+    for (int r = 0; r < kOwn; ++r) if (c[r]) got[r] = atomicAdd(&b.counts[bin(r)], c[r]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) if (c[r]) mine[bin(r)] = got[r];
-    }
+    for (int r = 0; r < kOwn; ++r) if (c[r]) mine[bin(r)] = got[r];
 }
 
-// One workgroup per matrix; a thread takes 32 consecutive bins.
+// One workgroup per matrix; a thread takes kOwn consecutive bins.
 __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetGroup g) {
     const SetBuffers& b = g.b[blockIdx.x];
     const uint32_t wgs = b.wgs, solo = b.solo;
     __shared__ uint32_t wave_sum[kSetThreads / 64][5];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t c[32], occupied = 0u;
+    constexpr int kOwn = kBins / kSetThreads;
+    uint32_t c[kOwn];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint4_t v = ((const uint4_t*)b.counts)[8 * tid + j];
+    for (int j = 0; j < kOwn / 4; ++j) {
+        const uint4_t v = ((const uint4_t*)b.counts)[kOwn / 4 * tid + j];
         c[4 * j] = v.x; c[4 * j + 1] = v.y; c[4 * j + 2] = v.z; c[4 * j + 3] = v.w;
     }
+    // keys in small bins, keys in hot bins, pieces of the fullest bins (they come first), hot bins of several pieces, other pieces
+    uint32_t own[5] = {0u, 0u, 0u, 0u, 0u};
+    const uint32_t full = b.count / 512u;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) occupied |= (c[j] ? 1u : 0u) << j;
-    // keys in small bins, keys in hot bins, pieces, hot bins of several pieces, occupied bins
-    uint32_t own[5] = {0u, 0u, 0u, 0u, (uint32_t)__builtin_popcount(occupied)};
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
+    for (int j = 0; j < kOwn; ++j) {
         if (c[j] <= kHot) own[0] += c[j];
-        else { own[1] += c[j]; own[2] += piece_count(c[j], solo); own[3] += c[j] > solo ? 1u : 0u; }
+        else { own[1] += c[j]; own[c[j] > full ? 2 : 4] += piece_count(c[j], solo); own[3] += c[j] > solo ? 1u : 0u; }
     }
     uint32_t run[5], total[5];
 #pragma unroll
@@ -486,11 +495,10 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetGroup g) {
         total[i] = 0u;
 #pragma unroll
         for (int w = 0; w < kSetThreads / 64; ++w) { if (w < wave) run[i] += wave_sum[w][i]; total[i] += wave_sum[w][i]; }
-        __builtin_amdgcn_sched_barrier(0);        // sixteen at a time: all eighty spilled ten registers, four at a time took 2.7 us more
+        __builtin_amdgcn_sched_barrier(0);        // sixteen at a time
     }
-    b.occupied[tid] = uint2_t{occupied, run[4]};
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < kOwn / 4; ++q) {
         uint32_t at[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -503,11 +511,11 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetGroup g) {
             } else {
                 at[j] = total[0] + run[1];
                 for (uint32_t f = 0u; f < n; f += piece_keys(n, f, solo))
-                    b.piece[run[2]++] = uint4_t{(uint32_t)(32 * tid + 4 * q + j), at[j] + f, piece_keys(n, f, solo), n > solo ? run[3] : 0xFFFFFFFFu};
+                    b.piece[n > full ? run[2]++ : total[2] + run[4]++] = uint4_t{(uint32_t)(kOwn * tid + 4 * q + j), at[j] + f, piece_keys(n, f, solo), n > solo ? run[3] : 0xFFFFFFFFu};
                 run[1] += n; run[3] += n > solo ? 1u : 0u;
             }
         }
-        ((uint4_t*)b.start)[8 * tid + q] = uint4_t{at[0], at[1], at[2], at[3]};
+        ((uint4_t*)b.start)[kOwn / 4 * tid + q] = uint4_t{at[0], at[1], at[2], at[3]};
     }
     if (wave == 0) {
         uint32_t least = 0xFFFFFFFFu, most = 0u;
@@ -523,49 +531,43 @@ __global__ void __launch_bounds__(kSetThreads) set_plan_kernel(SetGroup g) {
         const uint32_t groups = total[0] ? (total[0] - 1u) / kHot + 1u : 0u;
         b.group_from[0] = 0u;
         if (groups) b.group_from[groups] = total[0];
-        b.head->groups = groups; b.head->pieces = total[2]; b.head->joints = total[3]; b.head->bins = total[4];
+        b.head->groups = groups; b.head->pieces = total[2] + total[4]; b.head->joints = total[3];
     }
 }
 
-// Stored where it is met, a key is a request of four bytes to a line of its own.  TILED: keys are brought into the order of their
-// bins in LDS first, so that a wavefront's store meets runs.  Up to kRanks occupied bins (near-normal weights occupy about four
-// thousand): 16384 keys at a time, counted by the rank of their bin among the occupied ones; a thread keeps the positions of eight
-// ranks in registers.  More: 4096 keys at a time, in the order of their class (the lower 11 bits of the bin: keys of one bin stand
-// together, whatever else is in the class), positions of all bins in LDS.
-// What bounds it: the LDS (seven accesses per key) and the phases between five barriers per tile.
-// Measured (us; not tiled, by class, by rank): 1280 x 1280 35, 44, 36; 2048 x 2048 even, even, 5 less; 4096 x 4096 103, 70, 48;
-// 14336 x 4096 460, 240, 152: tiled beyond kTiledMinCount.
-constexpr int kClasses = 2048;
-constexpr int kRanks = 8192, kTileKeys = 16 * kSetThreads;
-constexpr uint32_t kTiledMinCount = 3u << 20;
-__device__ __forceinline__ uint32_t bin_rank(const uint2_t* occupied, uint32_t bin) {
-    const uint2_t o = occupied[bin >> 5];
-    return o.y + (uint32_t)__builtin_popcount(o.x & ((1u << (bin & 31u)) - 1u));
-}
-// lds: uint2 occupied[kBins / 32], first[kRanks], to[kRanks], tile[kTileKeys], wave_sum[kSetThreads / 64]
-__device__ __forceinline__ void partition_by_rank(const uint32_t* __restrict__ in, const SetRange& r, const uint32_t* __restrict__ mine,
-                                                  const SetBuffers& b, uint32_t* lds) {
-    uint2_t* const occupied = (uint2_t*)lds;
-    uint32_t* const first = lds + kBins / 16;                    // keys of the rank in the tile, then its first place
-    uint32_t* const to = first + kRanks;                         // position in `keys` of the rank's first key, less its first place
-    uint32_t* const tile = to + kRanks;
-    uint32_t* const wave_sum = tile + kTileKeys;
-    constexpr int kOwn = kRanks / kSetThreads, kQuads = kTileKeys / kSetThreads / 4;
+// Stored where it is met, a key is a request of four bytes to a line of its own: 16384 keys at a time are brought into the
+// order of their bins in LDS first, so that a wavefront's store meets runs; a thread keeps the positions of eight bins in registers.
+// What bounds it: memory (see above); beside it the LDS, five accesses per key, 76 of 110 us at 14336 x 4096.
+constexpr int kTileKeys = 16 * kSetThreads;
+__global__ void __launch_bounds__(kSetThreads) set_partition_kernel(SetGroup g) {
+    const SetBuffers& b = g.b[blockIdx.y];
+    if (blockIdx.x >= b.wgs) return;
+    extern __shared__ uint32_t first[];                          // [kBins]: keys of the bin in the tile, then its first place
+    constexpr int kOwn = kBins / kSetThreads, kQuads = kTileKeys / kSetThreads / 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t* __restrict__ in = b.in;
+    const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
     uint32_t* out = b.keys;
-    occupied[tid] = b.occupied[tid];
-    __syncthreads();
-#pragma unroll 8
-    for (int i = 0; i < kBins / kSetThreads; ++i) {              // (bins that the range does not hold: never used)
-        const uint32_t bin = (uint32_t)(tid + i * kSetThreads), at = b.start[bin] + mine[bin];
-        if ((occupied[bin >> 5].x >> (bin & 31u)) & 1u) to[bin_rank(occupied, bin)] = at;
+    const SetRange r = set_range(b.count, blockIdx.x, b.wgs);
+    {                                                            // the joint bitmaps that the sums will need
+        const uint32_t quads = b.head->joints * (uint32_t)(kBitmapWords / 4);
+        for (uint32_t j = blockIdx.x * (uint32_t)kSetThreads + tid; j < quads; j += b.wgs * (uint32_t)kSetThreads)
+            ((uint4_t*)b.joint)[j] = uint4_t{0u, 0u, 0u, 0u};
     }
+    uint32_t* const to = first + kBins;                          // [kBins]: position in `keys` of the bin's first key, less its first place
+    uint32_t* const tile = to + kBins;                           // [kTileKeys]
+    uint32_t* const wave_sum = tile + kTileKeys;                 // [kSetThreads / 64]
+    uint32_t pos[kOwn];                                          // (bins that the range does not hold: never used)
 #pragma unroll
-    for (int i = 0; i < kOwn; i += 4) *(uint4_t*)(first + kOwn * tid + i) = uint4_t{0u, 0u, 0u, 0u};
-    __syncthreads();
-    uint32_t next[kOwn];
+    for (int i = 0; i < kOwn; i += 4) {
+        const uint4_t p = *(const uint4_t*)(b.start + kOwn * tid + i) + *(const uint4_t*)(mine + kOwn * tid + i);
+        pos[i] = p.x; pos[i + 1] = p.y; pos[i + 2] = p.z; pos[i + 3] = p.w;
+    }
+    auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < kOwn; ++i) next[i] = to[kOwn * tid + i];
+        for (int i = 0; i < kOwn; i += 4) *(uint4_t*)(first + kOwn * tid + i) = uint4_t{0u, 0u, 0u, 0u};
+    };
+    clear();
     const uint32_t quads = r.quads;
     const uint4_t* src = (const uint4_t*)(in + r.lo);
     uint4_t v[kQuads];
@@ -581,17 +583,15 @@ __device__ __forceinline__ void partition_by_rank(const uint32_t* __restrict__ i
 #pragma unroll 1
     for (uint32_t base = 0u; base < quads; base += kTileKeys / 4) {
         const uint32_t in_tile = 4u * min(quads - base, (uint32_t)(kTileKeys / 4));
-        uint32_t key[4 * kQuads], at[4 * kQuads];                // at: rank of the bin, and among the tile's keys of it, 14 bits
+        uint32_t key[4 * kQuads], at[4 * kQuads];                // at: rank among the tile's keys of the bin
 #pragma unroll
         for (int q = 0; q < kQuads; ++q) {
             const uint32_t k[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { key[4 * q + j] = f32_key(k[j]); at[4 * q + j] = 0u; }
             if (4u * (uint32_t)(tid + q * kSetThreads) < in_tile)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    key[4 * q + j] = f32_key(k[j]);
-                    const uint32_t rank = bin_rank(occupied, key[4 * q + j] >> kBinShift);
-                    at[4 * q + j] = rank << 14 | count_bin(first, rank);
-                }
+                for (int j = 0; j < 4; ++j) at[4 * q + j] = count_bin(first, key[4 * q + j] >> kBinShift);
         }
         fetch(base + kTileKeys / 4);
         __syncthreads();
@@ -602,123 +602,52 @@ __device__ __forceinline__ void partition_by_rank(const uint32_t* __restrict__ i
             n[i] = c.x; n[i + 1] = c.y; n[i + 2] = c.z; n[i + 3] = c.w;
             own += c.x + c.y + c.z + c.w;
         }
-        uint32_t place = own;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)place, off, 64); if (lane >= off) place += a; }
+        uint32_t place = wave_scan(own);
         if (lane == 63) wave_sum[wave] = place;
         place -= own;
         __syncthreads();
+        uint32_t before[kSetThreads / 64];
 #pragma unroll
-        for (int w = 0; w < kSetThreads / 64; ++w) place += w < wave ? wave_sum[w] : 0u;
+        for (int w = 0; w < kSetThreads / 64; ++w) before[w] = wave_sum[w];
+#pragma unroll
+        for (int w = 0; w < kSetThreads / 64; ++w) place += w < wave ? before[w] : 0u;
 #pragma unroll
         for (int i = 0; i < kOwn; i += 4) {
-            uint4_t f, t;
-            f.x = place; t.x = next[i] - place; next[i] += n[i]; place += n[i];
-            f.y = place; t.y = next[i + 1] - place; next[i + 1] += n[i + 1]; place += n[i + 1];
-            f.z = place; t.z = next[i + 2] - place; next[i + 2] += n[i + 2]; place += n[i + 2];
-            f.w = place; t.w = next[i + 3] - place; next[i + 3] += n[i + 3]; place += n[i + 3];
-            *(uint4_t*)(first + kOwn * tid + i) = f;
-            *(uint4_t*)(to + kOwn * tid + i) = t;
+            uint32_t f[4], t[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { f[j] = place; t[j] = pos[i + j] - place; pos[i + j] += n[i + j]; place += n[i + j]; }
+            *(uint4_t*)(first + kOwn * tid + i) = uint4_t{f[0], f[1], f[2], f[3]};
+            *(uint4_t*)(to + kOwn * tid + i) = uint4_t{t[0], t[1], t[2], t[3]};
         }
         __syncthreads();
+        // all look-ups of a thread before its first store, here and below: a trip to the LDS for all of them, not for each
+#pragma unroll
+        for (int j = 0; j < 4 * kQuads; ++j) at[j] += first[key[j] >> kBinShift];
 #pragma unroll
         for (int q = 0; q < kQuads; ++q)
             if (4u * (uint32_t)(tid + q * kSetThreads) < in_tile)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) tile[first[at[4 * q + j] >> 14] + (at[4 * q + j] & 16383u)] = key[4 * q + j];
+                for (int j = 0; j < 4; ++j) tile[at[4 * q + j]] = key[4 * q + j];
         __syncthreads();
+        clear();
 #pragma unroll
-        for (int i = 0; i < kOwn; i += 4) *(uint4_t*)(first + kOwn * tid + i) = uint4_t{0u, 0u, 0u, 0u};
+        for (int j = 0; j < 4 * kQuads; ++j) key[j] = tile[tid + j * kSetThreads];       // (behind the last one: any key, not stored)
+#pragma unroll
+        for (int j = 0; j < 4 * kQuads; ++j) at[j] = to[key[j] >> kBinShift];
 #pragma unroll
         for (int j = 0; j < 4 * kQuads; ++j) {
             const uint32_t i = (uint32_t)(tid + j * kSetThreads);
-            if (i < in_tile) {
-                const uint32_t k = tile[i];
-                out[to[bin_rank(occupied, k >> kBinShift)] + i] = k;
-            }
+            if (i < in_tile) out[at[j] + i] = key[j];
         }
         __syncthreads();
     }
     // the last keys, fewer than four: positions behind those of the tiles
 #pragma unroll
-    for (int i = 0; i < kOwn; ++i) to[kOwn * tid + i] = next[i];
+    for (int i = 0; i < kOwn; ++i) to[kOwn * tid + i] = pos[i];
     __syncthreads();
     if ((uint32_t)tid < r.rest) {
         const uint32_t k = f32_key(in[r.tail(tid)]);
-        out[atomicAdd(&to[bin_rank(occupied, k >> kBinShift)], 1u)] = k;
-    }
-}
-template <bool TILED>
-__global__ void __launch_bounds__(kSetThreads) set_partition_kernel(SetBuffers b) {
-    const uint32_t* __restrict__ in = b.in;
-    extern __shared__ uint32_t next[];                           // [kBins]: position of the workgroup's next key of the bin
-    uint32_t* tile = next + kBins;                               // [4 kSetThreads]
-    uint32_t* cls = tile + 4 * kSetThreads;                      // [kClasses]: keys of the class, then their first place
-    uint32_t* wave_sum = cls + kClasses;                         // [kSetThreads / 64]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t* mine = b.reserved + (size_t)blockIdx.x * kBins;
-    const SetRange r = set_range(b.count, blockIdx.x, b.wgs);
-    if (TILED && b.head->bins <= (uint32_t)kRanks) {
-        partition_by_rank(in, r, mine, b, next);
-        return;
-    }
-    for (int j = tid; j < kBins / 4; j += kSetThreads)           // (bins that the range does not hold: never read)
-        ((uint4_t*)next)[j] = ((const uint4_t*)b.start)[j] + ((const uint4_t*)mine)[j];
-    uint32_t* out = b.keys;
-    if constexpr (!TILED) {
-        __syncthreads();
-        for_quads(in, r, [&](uint32_t bits) {
-            const uint32_t k = f32_key(bits);
-            out[count_bin(next, k >> kBinShift)] = k;
-        });
-        return;
-    }
-    static_assert(kClasses == 2 * kSetThreads, "two classes per thread");
-    *(uint2_t*)(cls + 2 * tid) = uint2_t{0u, 0u};
-    const uint32_t quads = r.quads;
-    const uint4_t* src = (const uint4_t*)(in + r.lo);
-    uint4_t v = tid < (int)min(quads, (uint32_t)kSetThreads) ? src[tid] : uint4_t{0u, 0u, 0u, 0u};
-    __syncthreads();
-#pragma unroll 1
-    for (uint32_t base = 0u; base < quads; base += kSetThreads) {
-        const uint32_t in_tile = 4u * min(quads - base, (uint32_t)kSetThreads);
-        const bool valid = 4u * tid < in_tile;
-        const uint32_t k[4] = {f32_key(v.x), f32_key(v.y), f32_key(v.z), f32_key(v.w)};
-        uint32_t rank[4];
-        if (valid)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) rank[j] = count_bin(cls, (k[j] >> kBinShift) & (kClasses - 1));
-        if (base + kSetThreads + tid < quads) v = src[base + kSetThreads + tid];
-        __syncthreads();
-        const uint2_t n = *(const uint2_t*)(cls + 2 * tid);
-        uint32_t at = n.x + n.y;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)at, off, 64); if (lane >= off) at += a; }
-        if (lane == 63) wave_sum[wave] = at;
-        at -= n.x + n.y;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < kSetThreads / 64; ++w) at += w < wave ? wave_sum[w] : 0u;
-        *(uint2_t*)(cls + 2 * tid) = uint2_t{at, at + n.x};
-        __syncthreads();
-        if (valid)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) tile[cls[(k[j] >> kBinShift) & (kClasses - 1)] + rank[j]] = k[j];
-        __syncthreads();
-        *(uint2_t*)(cls + 2 * tid) = uint2_t{0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t i = (uint32_t)(tid + j * kSetThreads);
-            if (i < in_tile) {
-                const uint32_t key = tile[i];
-                out[count_bin(next, key >> kBinShift)] = key;
-            }
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x < r.rest) {
-        const uint32_t key = f32_key(in[r.tail(threadIdx.x)]);
-        out[count_bin(next, key >> kBinShift)] = key;
+        out[atomicAdd(&to[k >> kBinShift], 1u)] = k;
     }
 }
 
@@ -727,6 +656,19 @@ __device__ __forceinline__ void add_interval(double (&s)[kSetRow], double t, int
     double p = u;
 #pragma unroll
     for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
+}
+
+// t ln t, 0 if t is not above zero.  ln t from the logarithm of the upper eleven bits of its fraction, which the table holds, and four
+// terms of the series of the rest, which is below 2^-10: the error is that of the last addition.  (The library's logarithm has so many constants
+// that keeping them over the loops around it spills a hundred registers.)
+__device__ __forceinline__ double t_log_t(double t, const double* __restrict__ logs) {
+    if (!(t > 0.0)) return 0.0;
+    int e;
+    const double m = frexp(t, &e) * 2048.0;                                   // 1024 <= m < 2048
+    const int q = min(max((int)m, 1024), 2047);                               // (an infinite t, of a matrix of equal weights: within the table)
+    const double x = (m - (double)q) / (double)q;
+    const double series = x * fma(x, fma(x, fma(x, fma(x, fma(x, -1.0 / 6.0, 0.2), -0.25), 1.0 / 3.0), -0.5), 1.0);
+    return t * (fma((double)(e - 11), 0.69314718055994530942, logs[q]) + series);
 }
 
 // Sum over the workgroup in a fixed order; thread i < kSetRow returns with row i's total.
@@ -741,10 +683,12 @@ __device__ __forceinline__ double block_sum(const double (&s)[kSetRow], double (
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
         if (lane == 0) red[wave][k] = v;
+        __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
     double v = 0.0;
     if (tid < kSetRow)
+#pragma unroll 1
         for (int w = 0; w < THREADS / 64; ++w) v += red[w][tid];
     return v;
 }
@@ -761,27 +705,38 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
     return (uint32_t)halves[0] + (uint32_t)halves[1];
 }
 
+// Where a hot bin's bitmap holds 32 of its patterns: a thread's kWords consecutive words, and one that is left out, so that the same word of
+// 64 threads is in 64 banks.
+constexpr int kWords = kBitmapWords / kSumThreads, kBitmapSize = kBitmapWords + kBitmapWords / kWords;
+__device__ __forceinline__ uint32_t bitmap_at(uint32_t word) { return word + word / kWords; }
 // Sums over the intervals inside one hot bin, whose patterns are the bitmap `data`: added to s.  Distances below kTable are counted
-// (`counted`), and their binary64 terms evaluated once per bin, by a thread each (a term per distance met: 4096 x 4096 45 us, now 38).
-__device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, double inv_mean, int terms, const SetBuffers& b,
+// (`counted`), and their binary64 terms evaluated once per bin; ln t of a distance is the table's logarithm of a whole number and the
+// unit's.  A thread has its words of the bitmap one after another: bit by bit where few are set (one loop over all of a thread's words, whose
+// lanes' trips differ less than word by word), 32 patterns at once for distances up to eight where many are (dense).
+struct Scale { double inv_mean, log_fraction; int exponent; };               // inv_mean = fraction 2^exponent
+__device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, const Scale& scale, int terms, bool dense, const SetBuffers& b,
                                            uint32_t* counted, int* wave_last, double (&s)[kSetRow]) {
-    constexpr int kWords = kBitmapWords / kSumThreads;                        // per thread: 256 patterns
-    static_assert(kTable == kSumThreads, "a distance per thread");
+    constexpr int kWaves = kSumThreads / 64;
+    static_assert(kTable % kSumThreads == 0, "distances per thread");
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));              // (what follows from it is made again per bin, not kept over the loop around)
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), word0 = kWords * tid;
+    const uint32_t* const own = data + bitmap_at(word0);
     // one exponent: neighbours d patterns apart differ by d units (exactly, also in binary64)
-    const uint32_t base = bin << kBinShift, pattern = (base & 0x80000000u) ? base & 0x7FFFFFFFu : ~base;
+    const uint32_t bin_key = bin << kBinShift, pattern = (bin_key & 0x80000000u) ? bin_key & 0x7FFFFFFFu : ~bin_key;
     const int ex = (int)((pattern >> 23) & 255u);
     const double unit_gap = ldexp(1.0, (ex ? ex : 1) - 150);
-    counted[tid] = 0u;
+    const double log_unit = fma((double)(scale.exponent + (ex ? ex : 1) - 150), 0.69314718055994530942, scale.log_fraction);   // of unit_gap inv_mean
+#pragma unroll
+    for (int d = 0; d < kTable; d += kSumThreads) counted[d + tid] = 0u;
+    if (tid == 0) counted[kTable] = 0u;
     int last = -1;
+    uint32_t total = 0u;
 #pragma unroll
-    for (int j = 0; j < kWords; j += 4) {
-        const uint4_t v = *(const uint4_t*)(data + kWords * tid + j);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (w[i]) last = 32 * (kWords * tid + j + i) + 31 - __builtin_clz(w[i]);
+    for (int j = 0; j < kWords; ++j) {
+        const uint32_t x = own[j];
+        total += __builtin_popcount(x);
+        if (x) last = 32 * (word0 + j) + 31 - __builtin_clz(x);
     }
     // the last set bit before the thread's comes from the threads before
     int prev = last;
@@ -792,59 +747,104 @@ __device__ __forceinline__ void add_bitmap(const uint32_t* data, uint32_t bin, d
     if (lane == 0) prev = -1;
     __syncthreads();
     int top = -1;
-    for (int v = 0; v < kSumThreads / 64; ++v) { if (v < wave) prev = max(prev, wave_last[v]); top = max(top, wave_last[v]); }
-    if (tid == 0) b.bin_max[bin] = base + (uint32_t)top;
-    // distances 1 .. 8 are found for 32 patterns at once, the others bit by bit
-    uint32_t near[9], prior = tid ? data[kWords * tid - 1] : 0u, total = 0u;
 #pragma unroll
-    for (int d = 1; d <= 8; ++d) near[d] = 0u;
-#pragma unroll 1
-    for (int j = 0; j < kWords; ++j) {
-        const uint32_t x = data[kWords * tid + j];
-        total += __builtin_popcount(x);
-        uint32_t far = x;
+    for (int v = 0; v < kWaves; ++v) { const int l = wave_last[v]; if (v < wave) prev = max(prev, l); top = max(top, l); }
+    if (tid == 0) b.bin_max[bin] = bin_key + (uint32_t)top;
+    const int before = prev;
+    const uint32_t present = total;
+    double logs[kTable / kSumThreads];                                        // asked for here: a trip to memory behind the words
 #pragma unroll
-        for (int d = 1; d <= 8; ++d) {
-            const uint32_t back = (x << d) | (prior >> (32 - d));             // pattern i: is i - d there?
-            near[d] += __builtin_popcount(far & back);
-            far &= ~back;
+    for (int d = 0; d < kTable / kSumThreads; ++d) logs[d] = b.logs[d * kSumThreads + tid];
+    if (!dense) {
+        // bit by bit over the thread's words: the lanes' numbers of bits differ less over all of them than word by word
+        const uint32_t *at = own, *const end = own + kWords;
+        uint32_t x = *at;
+        int base = 32 * word0;
+        if (prev < 0 && last >= 0) {                                          // the first of all: no interval in front of it
+            while (!x) { x = *++at; base += 32; }
+            prev = base + __builtin_ctz(x);
+            x &= x - 1u;
+            b.bin_min[bin] = bin_key + (uint32_t)prev;
+            total -= 1u;
         }
 #pragma unroll 1
-        while (far) {
-            const int bit = __builtin_ctz(far), at = 32 * (kWords * tid + j) + bit;
-            far &= far - 1u;
-            const uint32_t below = x & ((1u << bit) - 1u);
-            const int from = below ? 32 * (kWords * tid + j) + 31 - __builtin_clz(below) : prev;
-            if (from < 0) {
-                b.bin_min[bin] = base + (uint32_t)at;
-                total -= 1u;                                                  // no interval in front of the first
-            } else if (at - from < kTable) {
-                atomicAdd(&counted[at - from], 1u);
-            } else {
-                const double t = (double)(at - from) * unit_gap * inv_mean;
-                if (t > 0.0) s[0] += t * log(t);                              // (t = 0: an infinite span)
-                add_interval(s, t, terms);
+        while (at != end) {
+            if (x) {
+                const int here = base + __builtin_ctz(x);
+                x &= x - 1u;
+                atomicAdd(&counted[min(here - prev, kTable)], 1u);
+                prev = here;
+            }
+            if (!x) {                                                         // (the word behind the last one: left out, not used)
+                x = *++at;
+                base += 32;
             }
         }
-        if (x) prev = 32 * (kWords * tid + j) + 31 - __builtin_clz(x);
-        prior = x;
-    }
+    } else {
+        // distances 1 .. 8 are found for 32 patterns at once, the others bit by bit
+        uint32_t beyond[9], prior = tid ? own[-2] : 0u;    // patterns with none of the d in front of them
 #pragma unroll
-    for (int d = 1; d <= 8; d += 2) {                                         // (a thread counts at most 256 of each)
-        const uint32_t two = wave_sum_u32(near[d] | near[d + 1] << 16);
-        if (lane == d) atomicAdd(&counted[d], two & 0xFFFFu);
-        if (lane == d + 1) atomicAdd(&counted[d + 1], two >> 16);
-    }
-    __syncthreads();
-    const uint32_t times = counted[tid];                                      // of distance tid
-    if (times) {
-        const double m = (double)times, t = (double)tid * unit_gap * inv_mean, u = t - 1.0;
-        double p = m * u;
-        if (t > 0.0) s[0] += m * (t * log(t));
+        for (int d = 0; d <= 8; ++d) beyond[d] = 0u;
+#pragma unroll 1
+        for (int j = 0; j < kWords; ++j) {
+            const uint32_t x = own[j];
+            uint32_t far = x;
 #pragma unroll
-        for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
+            for (int d = 1; d <= 8; ++d) {
+                far &= ~((x << d) | (prior >> (32 - d)));
+                beyond[d] += __builtin_popcount(far);
+            }
+#pragma unroll 1
+            while (far) {
+                const int bit = __builtin_ctz(far), at = 32 * (word0 + j) + bit;
+                far &= far - 1u;
+                const uint32_t below = x & ((1u << bit) - 1u);
+                const int from = below ? 32 * (word0 + j) + 31 - __builtin_clz(below) : prev;
+                if (from < 0) {
+                    b.bin_min[bin] = bin_key + (uint32_t)at;
+                    total -= 1u;                                              // no interval in front of the first
+                } else {
+                    atomicAdd(&counted[min(at - from, kTable)], 1u);
+                }
+            }
+            if (x) prev = 32 * (word0 + j) + 31 - __builtin_clz(x);
+            prior = x;
+        }
+#pragma unroll
+        for (int d = 1; d <= 8; ++d) {
+            const uint32_t all = wave_sum_u32((d == 1 ? present : beyond[d - 1]) - beyond[d]);
+            if (lane == d) atomicAdd(&counted[d], all);
+        }
     }
     s[kGapSums] += (double)total;
+    __syncthreads();
+    if (counted[kTable]) {                                                    // longer ones, a term each: in front of the lowest bit of a word
+        prev = before;
+#pragma unroll 1
+        for (int j = 0; j < kWords; ++j) {
+            const uint32_t x = own[j];
+            if (!x) continue;
+            const int at = 32 * (word0 + j) + __builtin_ctz(x);
+            if (prev >= 0 && at - prev >= kTable) {
+                const double t = (double)(at - prev) * unit_gap * scale.inv_mean;
+                s[0] += t_log_t(t, b.logs);
+                add_interval(s, t, terms);
+            }
+            prev = 32 * (word0 + j) + 31 - __builtin_clz(x);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kTable / kSumThreads; ++i) {
+        const int d = i * kSumThreads + tid;
+        const uint32_t times = counted[d];
+        if (times) {
+            const double m = (double)times, t = (double)d * unit_gap * scale.inv_mean, u = t - 1.0;
+            double p = m * u;
+            if (t > 0.0) s[0] += m * (t * (logs[i] + log_unit));              // (t = 0: an infinite span)
+#pragma unroll
+            for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
+        }
+    }
 }
 
 // Bitonic sort of a group: thread t holds keys 4 t .. 4 t + 3 of up to 2048 (`size` of them, a power of two from 256 on, the rest
@@ -915,111 +915,158 @@ __device__ __forceinline__ const uint32_t* sort_group(uint32_t (&k)[4], uint32_t
     return buf;
 }
 
-__global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetBuffers b, int terms) {
-    __shared__ __attribute__((aligned(16))) uint32_t data[kBitmapWords];     // a bitmap or a group's keys
-    __shared__ uint32_t counted[kTable];                                      // intervals of each distance
+__global__ void __launch_bounds__(kSumThreads, 4) set_sum_kernel(SetGroup g, int terms) {
+    const SetBuffers& b = g.b[blockIdx.y];
+    __shared__ __attribute__((aligned(16))) uint32_t data[kBitmapSize];     // a bitmap or a group's keys
+    __shared__ uint32_t counted[kTable + 1];                                   // intervals of each distance
     __shared__ double red[kSumThreads / 64][kSetRow];
     __shared__ int wave_last[kSumThreads / 64];
     __shared__ int last_piece;
     const int tid = threadIdx.x;
     const SetHead head = *b.head;
-    const double inv_mean = (double)(b.count - 1u) / (key_f64(head.max_key) - key_f64(head.min_key));
-    double s[kSetRow];                                                        // of the workgroup's units, whose choice is fixed
+    Scale scale;
+    scale.inv_mean = (double)(b.count - 1u) / (key_f64(head.max_key) - key_f64(head.min_key));
+    const double fraction = frexp(scale.inv_mean, &scale.exponent);
+    scale.log_fraction = t_log_t(fraction, b.logs) / fraction;
+    double s[kSetRow], sum = 0.0;                                             // of the workgroup's units, whose choice is fixed
 #pragma unroll
     for (int k = 0; k < kSetRow; ++k) s[k] = 0.0;
+    // the groups (a loop of its own: nothing of it is kept in registers over the bitmaps)
 #pragma unroll 1
-    for (uint32_t unit = blockIdx.x; unit < head.pieces + head.groups; unit += gridDim.x) {
-        __syncthreads();                                                      // data and counts of the unit before are read
-        if (unit < head.pieces) {
-            const uint4_t piece = b.piece[unit];
-            const uint32_t bin = piece.x, n = piece.z;
-            const uint32_t* keys = b.keys + piece.y;                          // n <= 2^26: counters from here on cannot wrap
+    for (uint32_t group = gridDim.x - 1u - blockIdx.x; group < head.groups; group += gridDim.x) {
+        __syncthreads();                                                      // the keys of the group before are read
+        const uint32_t from = b.group_from[group], n = b.group_from[group + 1u] - from;      // at most 2047
+        uint32_t size = 256u, own[4];
+        while (size < n) size *= 2u;
 #pragma unroll
-            for (int j = 0; j < kBitmapWords / 4; j += kSumThreads) ((uint4_t*)data)[j + tid] = uint4_t{0u, 0u, 0u, 0u};
-            __syncthreads();
-            uint32_t i = tid;
-            asm volatile("" : "+v"(i));                                       // (made again per bin, not kept over the loop around: it would spill)
-            auto set = [&](uint32_t k) {                                      // (a wavefront of equal keys: one of them)
-                const unsigned long long live = __builtin_amdgcn_ballot_w64(true);
-                const bool equal = __builtin_amdgcn_ballot_w64(k == (uint32_t)__builtin_amdgcn_readfirstlane((int)k)) == live;
-                if (!equal || (live & lanes_below(tid & 63)) == 0ull) atomicOr(&data[(k >> 5) & (kBitmapWords - 1)], 1u << (k & 31u));
-            };
-            // eight keys at a time, the next eight in flight; past the end the last key again, which changes nothing
-            auto key_at = [&](uint32_t at) { return *(const uint32_t*)((const char*)keys + 4u * min(at, n - 1u)); };   // (32-bit offsets)
-            uint32_t k[8];
-#pragma unroll
-            for (uint32_t j = 0; j < 8u; ++j) k[j] = key_at(i + j * kSumThreads);
+        for (uint32_t j = 0; j < 4u; ++j) own[j] = 4u * tid + j < n ? b.keys[from + 4u * tid + j] : 0xFFFFFFFFu;
+        const uint32_t* sorted = sort_group(own, data, size, tid);
 #pragma unroll 1
-            while (i < n) {
-                uint32_t now[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) now[j] = k[j];
-                i += 8u * kSumThreads;
-                if (i < n)
-#pragma unroll
-                    for (uint32_t j = 0; j < 8u; ++j) k[j] = key_at(i + j * kSumThreads);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) set(now[j]);
-            }
-            __syncthreads();
-            const bool joined = piece.w != 0xFFFFFFFFu;
-            if (joined) {
-                uint32_t* joint = b.joint + (size_t)piece.w * kBitmapWords;
-                for (int j = tid; j < kBitmapWords; j += kSumThreads)
-                    if (data[j]) atomicOr(&joint[j], data[j]);
-                __threadfence();
-                __syncthreads();
-                if (tid == 0) last_piece = atomicAdd(&b.done[piece.w], 1u) == (b.counts[bin] - 1u) / kPiece;
-                __syncthreads();
-                if (!last_piece) continue;
-                __threadfence();
-                for (int j = tid; j < kBitmapWords; j += kSumThreads)
-                    data[j] = __hip_atomic_load(&joint[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __syncthreads();
-            }
-            double own[kSetRow];
-#pragma unroll
-            for (int k = 0; k < kSetRow; ++k) own[k] = 0.0;
-            add_bitmap(data, bin, inv_mean, terms, b, counted, wave_last, own);
-            if (joined) {                                                     // which workgroup is last is not fixed: a row of its own
-                const double v = block_sum<kSumThreads>(own, red, terms);
-                if (tid < kSetRow) b.sums[(size_t)(kSumWorkgroups + piece.w) * kSetRow + tid] = v;
-            } else {
-#pragma unroll
-                for (int k = 0; k < kSetRow; ++k) s[k] += own[k];
-            }
-        } else {
-            const uint32_t from = b.group_from[unit - head.pieces], to = b.group_from[unit - head.pieces + 1u];
-            const uint32_t n = to - from;                                     // at most 2047
-            uint32_t size = 256u, own[4], me = tid;
-            asm volatile("" : "+v"(me));                                    // (nothing of it kept in registers over the bitmaps)
-            while (size < n) size *= 2u;
-#pragma unroll
-            for (uint32_t j = 0; j < 4u; ++j) own[j] = 4u * me + j < n ? b.keys[from + 4u * me + j] : 0xFFFFFFFFu;
-            const uint32_t* sorted = sort_group(own, data, size, me);
-#pragma unroll 1
-            for (uint32_t i = me; i < n; i += kSumThreads) {
-                const uint32_t k = sorted[i], bin = k >> kBinShift;
-                if (i == 0u || sorted[i - 1u] >> kBinShift != bin) b.bin_min[bin] = k;
-                if (i + 1u == n || sorted[i + 1u] >> kBinShift != bin) { b.bin_max[bin] = k; continue; }
-                const uint32_t k1 = sorted[i + 1u];
-                if (k1 == k) continue;
-                const double t = (key_f64(k1) - key_f64(k)) * inv_mean;
-                if (t > 0.0) s[0] += t * log(t);
-                s[kGapSums] += 1.0;
-                add_interval(s, t, terms);
-            }
+        for (uint32_t i = tid; i < n; i += kSumThreads) {
+            const uint32_t k = sorted[i], bin = k >> kBinShift;
+            if (i == 0u || sorted[i - 1u] >> kBinShift != bin) b.bin_min[bin] = k;
+            if (i + 1u == n || sorted[i + 1u] >> kBinShift != bin) { b.bin_max[bin] = k; continue; }
+            const uint32_t k1 = sorted[i + 1u];
+            if (k1 == k) continue;
+            const double t = (key_f64(k1) - key_f64(k)) * scale.inv_mean;
+            s[0] += t_log_t(t, b.logs);
+            s[kGapSums] += 1.0;
+            add_interval(s, t, terms);
         }
     }
-    const double v = block_sum<kSumThreads>(s, red, terms);
-    if (tid < kSetRow) b.sums[(size_t)blockIdx.x * kSetRow + tid] = v;
+    // the bitmaps
+    uint32_t row = 0xFFFFFFFFu;                                               // of a joint bin that the sums are of
+#pragma unroll 1
+    for (uint32_t unit = blockIdx.x; ; unit += gridDim.x) {
+        const bool more = unit < head.pieces;
+        const uint4_t piece = more ? b.piece[unit] : uint4_t{0u, 0u, 0u, 0u};
+        const bool joined = more && piece.w != 0xFFFFFFFFu;
+        __syncthreads();                                                      // data and counts of the unit before are read
+        if (!more || joined || row != 0xFFFFFFFFu) {
+            // which workgroup sums a joint bin is not fixed: its sums get a row of their own, what comes before is put aside in
+            // front of every piece, so that the order of additions is the same
+            const double v = block_sum<kSumThreads>(s, red, terms);
+            if (row == 0xFFFFFFFFu) sum += v;
+            else if (tid < kSetRow) b.sums[(size_t)(kSumWorkgroups + row) * kSetRow + tid] = v;
+            row = 0xFFFFFFFFu;
+#pragma unroll
+            for (int k = 0; k < kSetRow; ++k) s[k] = 0.0;
+            if (!more) break;
+        }
+        const uint32_t bin = piece.x, n = piece.z;                            // n <= 2^26: counters from here on cannot wrap
+#pragma unroll
+        for (int j = 0; j < kWords / 4; ++j) ((uint4_t*)data)[j * kSumThreads + tid] = uint4_t{0u, 0u, 0u, 0u};
+        if (tid < (kBitmapSize - kBitmapWords) / 4) ((uint4_t*)data)[kBitmapWords / 4 + tid] = uint4_t{0u, 0u, 0u, 0u};
+        __syncthreads();
+        {
+            // quads of keys, of which a thread has four in flight, and the up to three keys in front of and behind them
+            const uint32_t* own = b.keys + piece.y;
+            const uint32_t lead = min((0u - piece.y) & 3u, n), quads = (n - lead) / 4u;
+            const uint4_t* src = (const uint4_t*)(own + lead);
+            auto set = [&](uint32_t k) { atomicOr(&data[bitmap_at((k >> 5) & (kBitmapWords - 1))], 1u << (k & 31u)); };
+            auto set_new = [&](uint32_t k) {                                  // few different keys: most are there already
+                uint32_t* const at = &data[bitmap_at((k >> 5) & (kBitmapWords - 1))];
+                if (!(*(volatile uint32_t*)at >> (k & 31u) & 1u)) atomicOr(at, 1u << (k & 31u));
+            };
+            uint32_t i = tid;
+            asm volatile("" : "+v"(i));                                       // (made again per bin, not kept over the loop around: it would spill)
+            if (i < lead) set(own[i]);
+            else if (i >= 4u && i - 4u < n - lead - 4u * quads) set(own[n - 1u - (i - 4u)]);
+            // a round: kInFlight quads per thread, those of the next round in flight; past the end the last quad again
+            constexpr uint32_t kInFlight = 4u, kRound = kInFlight * kSumThreads;
+            uint4_t even[kInFlight], odd[kInFlight];
+            bool coarse = false;
+            auto fetch = [&](uint4_t (&k)[kInFlight], uint32_t round) {
+#pragma unroll
+                for (uint32_t j = 0; j < kInFlight; ++j) k[j] = src[min(i + round * kRound + j * kSumThreads, quads - 1u)];
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto use = [&](const uint4_t (&k)[kInFlight], uint32_t round) {
+#pragma unroll
+                for (uint32_t j = 0; j < kInFlight; ++j) {
+                    const uint4_t now = k[j];
+                    if (i + round * kRound + j * kSumThreads < quads) {
+                        // (a wavefront of equal keys: one of them)
+                        const unsigned long long live = __builtin_amdgcn_ballot_w64(true);
+                        if (__builtin_amdgcn_ballot_w64(now.x == (uint32_t)__builtin_amdgcn_readfirstlane((int)now.x)) == live) {
+                            if ((live & lanes_below(i & 63u)) == 0ull) set(now.x);
+                            if (__builtin_amdgcn_ballot_w64(now.x == now.y && now.x == now.z && now.x == now.w) == live) continue;
+                        } else if (coarse) {
+                            set_new(now.x); set_new(now.y); set_new(now.z); set_new(now.w);
+                            continue;
+                        } else {
+                            set(now.x);
+                        }
+                        set(now.y); set(now.z); set(now.w);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)i) < quads) {   // (whole wavefronts)
+                const uint32_t rounds = (quads + kRound - 1u) / kRound;
+                fetch(even, 0u);
+                // values of bfloat16, and others with nothing in their lower bits: 64 lanes would add to a few words one after another
+                coarse = __builtin_amdgcn_ballot_w64((even[0].x ^ (uint32_t)__builtin_amdgcn_readfirstlane((int)even[0].x)) & 0xFFFu) == 0ull;
+                if (rounds == 1u) {
+                    use(even, 0u);
+                } else {
+#pragma unroll 1
+                    for (uint32_t r = 0u; r < rounds; r += 2u) {
+                        fetch(odd, r + 1u);
+                        use(even, r);
+                        fetch(even, r + 2u);
+                        use(odd, r + 1u);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (joined) {
+            uint32_t* joint = b.joint + (size_t)piece.w * kBitmapWords;
+            for (int j = tid; j < kBitmapWords; j += kSumThreads)
+                if (const uint32_t x = data[bitmap_at(j)]) atomicOr(&joint[j], x);
+            // Every access to the joint bitmap is an atomic operation of the device, served where all compute units see it: that they are
+            // done is all the counter below has to wait for.  (A fence would also write back what the L2 holds of other stores: 2^24 uniform
+            // weights took 150 us with one, 126 without.)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) last_piece = atomicAdd(&b.done[piece.w], 1u) == (b.counts[bin] - 1u) / kPiece;
+            __syncthreads();
+            if (!last_piece) continue;
+            for (int j = tid; j < kBitmapWords; j += kSumThreads)
+                data[bitmap_at(j)] = __hip_atomic_load(&joint[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            row = piece.w;
+        }
+        add_bitmap(data, bin, scale, terms, b.counts[bin] >= kDense, b, counted, wave_last, s);
+    }
+    if (tid < kSetRow) b.sums[(size_t)blockIdx.x * kSetRow + tid] = sum;
 }
 
 __global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetGroup g, int terms, double tau_c, double tau_f) {
     const SetBuffers& b = g.b[blockIdx.x];
     const uint32_t count = b.count;
-    extern __shared__ uint32_t next[];
-    uint16_t* list = (uint16_t*)next;                                         // [kBins]: the occupied bins
+    __shared__ uint16_t list[kBins];                                          // the occupied bins
     __shared__ double red[kSetThreads / 64][kSetRow];
     __shared__ double tot[kSetRow];
     __shared__ uint32_t wave_sum[kSetThreads / 64];
@@ -1034,8 +1081,11 @@ __global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetGroup g, int 
 #pragma unroll
         for (int k = 0; k < kSetRow; ++k) s[k] += b.sums[(size_t)i * kSetRow + k];
     }
-    uint32_t occupied = b.occupied[tid].x;                                    // of 32 consecutive bins
-    const uint32_t own = __builtin_popcount(occupied);
+    constexpr int kOwn = kBins / kSetThreads;                                 // consecutive bins of a thread
+    uint32_t own = 0u, occupied = 0u;
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) occupied |= (b.counts[kOwn * tid + j] ? 1u : 0u) << j;
+    own = __builtin_popcount(occupied);
     uint32_t at = own, bins = 0u;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) { const uint32_t a = (uint32_t)__shfl_up((int)at, off, 64); if (lane >= off) at += a; }
@@ -1043,7 +1093,7 @@ __global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetGroup g, int 
     at -= own;
     __syncthreads();
     for (int v = 0; v < kSetThreads / 64; ++v) { if (v < wave) at += wave_sum[v]; bins += wave_sum[v]; }
-    for (; occupied; occupied &= occupied - 1u) list[at++] = (uint16_t)(32 * tid + __builtin_ctz(occupied));
+    for (; occupied; occupied &= occupied - 1u) list[at++] = (uint16_t)(kOwn * tid + __builtin_ctz(occupied));
     __syncthreads();
     // the interval in front of every occupied bin but the first
     for (uint32_t i = tid + 1u; i < bins; i += kSetThreads) {
@@ -1068,28 +1118,41 @@ __global__ void __launch_bounds__(kSetThreads) set_final_kernel(SetGroup g, int 
     }
 }
 
-static hipError_t launch_sets(const SetGroup& g, int n, int terms, double tau_c, double tau_f, hipStream_t s) {
-    constexpr int lds = kBins * 4, lds_partition = lds + (4 * kSetThreads + kClasses + kSetThreads / 64) * 4;   // 128 and 152 KB
-    static_assert(lds_partition <= 160 * 1024 && (kBins / 16 + 2 * kRanks + kTileKeys + kSetThreads / 64) * 4 <= lds_partition, "LDS of a compute unit");
-    const void* kernels[] = {(const void*)set_count_kernel, (const void*)set_partition_kernel<false>, (const void*)set_partition_kernel<true>,
-                             (const void*)set_final_kernel};
-    static std::atomic<unsigned long long> raised[4];
-    for (int i = 0; i < 4; ++i) {
-        const hipError_t e = raise_lds(kernels[i], lds_partition, raised[i]);
-        if (e != hipSuccess) return e;
-    }
+// keys: room for the partitioned keys of the largest matrix at least
+static hipError_t launch_sets(SetGroup& g, int n, char* keys, size_t key_bytes, int terms, double tau_c, double tau_f, hipStream_t s) {
+    constexpr int lds = kBins * 4, lds_partition = (2 * kBins + kTileKeys + kSetThreads / 64) * 4;     // 32 and 128 KB
+    static std::atomic<unsigned long long> raised{0ull};
+    const hipError_t e = raise_lds((const void*)set_partition_kernel, lds_partition, raised);
+    if (e != hipSuccess) return e;
     uint32_t wgs = 0;
     for (int i = 0; i < n; ++i) wgs = std::max(wgs, g.b[i].wgs);
-    hipLaunchKernelGGL(set_clear_kernel, dim3(64, n), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(set_clear_kernel, dim3(8, n), dim3(256), 0, s, g);
     hipLaunchKernelGGL(set_count_kernel, dim3(wgs, n), dim3(kSetThreads), lds, s, g);
     hipLaunchKernelGGL(set_plan_kernel, dim3(n), dim3(kSetThreads), 0, s, g);
-    for (int i = 0; i < n; ++i) {
-        const SetBuffers& b = g.b[i];
-        if (b.count > kTiledMinCount) hipLaunchKernelGGL(set_partition_kernel<true>, dim3(b.wgs), dim3(kSetThreads), lds_partition, s, b);
-        else hipLaunchKernelGGL(set_partition_kernel<false>, dim3(b.wgs), dim3(kSetThreads), lds, s, b);
-        hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups), dim3(kSumThreads), 0, s, b, terms);
+    // Matrices share launches as the keys have room for them, the largest first and then what still fits: the fullest bins of a large
+    // one, which a workgroup reads for long, beside the others' (the layer of the 7B shapes: two launches of a large and two
+    // small matrices and one of two).
+    int order[kSetGroup], left = n;
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order, order + n, [&](int p, int q) { return g.b[p].count > g.b[q].count; });
+    while (left) {
+        SetGroup part{};
+        int in_part = 0, kept = 0;
+        uint32_t part_wgs = 0;
+        size_t at = 0;
+        for (int i = 0; i < left; ++i) {
+            SetBuffers& b = g.b[order[i]];
+            if (in_part && at + set_key_bytes(b.count) > key_bytes) { order[kept++] = order[i]; continue; }
+            b.keys = (uint32_t*)(keys + at);
+            at += set_key_bytes(b.count);
+            part_wgs = std::max(part_wgs, b.wgs);
+            part.b[in_part++] = b;
+        }
+        left = kept;
+        hipLaunchKernelGGL(set_partition_kernel, dim3(part_wgs, in_part), dim3(kSetThreads), lds_partition, s, part);
+        hipLaunchKernelGGL(set_sum_kernel, dim3(kSumWorkgroups, in_part), dim3(kSumThreads), 0, s, part, terms);
     }
-    hipLaunchKernelGGL(set_final_kernel, dim3(n), dim3(kSetThreads), kBins * 2, s, g, terms, tau_c, tau_f);
+    hipLaunchKernelGGL(set_final_kernel, dim3(n), dim3(kSetThreads), 0, s, g, terms, tau_c, tau_f);
     return hipGetLastError();
 }
 
@@ -1134,9 +1197,14 @@ hipError_t launch_proxy_f32(const void* const* ws, const int* Ns, const int* Ks,
     int in_group = 0;
     size_t keys = 0, tables = 0;                   // bytes of the group: the largest matrix's keys, and every one's tables
     auto flush = [&]() {
-        char* at = base + keys;
-        for (int i = 0; i < in_group; ++i) { g.b[i].keys = (uint32_t*)base; at += set_tables(g.b[i], at, g.b[i].count); }
-        const hipError_t e = in_group ? launch_sets(g, in_group, terms, tau_c, tau_f, s) : hipSuccess;
+        // Small matrices by themselves are dealt to more workgroups, where their tables still fit (768 x 768 71 -> 55 us, 2048 x 2048 94 -> 78).
+        uint32_t wgs = 0, range = kCountRange;
+        size_t more = 0;
+        for (int i = 0; i < in_group; ++i) { SetBuffers b{}; more += set_tables(b, nullptr, g.b[i].count, kCountRangeAlone); wgs += set_workgroups(g.b[i].count); }
+        if (wgs < 256u && keys + more <= L.bytes) { range = kCountRangeAlone; tables = more; }
+        char* at = base + (L.bytes - tables);
+        for (int i = 0; i < in_group; ++i) at += set_tables(g.b[i], at, g.b[i].count, range);
+        const hipError_t e = in_group ? launch_sets(g, in_group, base, L.bytes - tables, terms, tau_c, tau_f, s) : hipSuccess;
         in_group = 0; keys = tables = 0;
         return e;
     };

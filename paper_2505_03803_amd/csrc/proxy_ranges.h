@@ -6,9 +6,10 @@
 namespace rwkvq {
 
 constexpr uint32_t kCountRange = 49152;        // fewest keys per counting workgroup
+constexpr uint32_t kCountRangeAlone = 16384;   // the same where the matrices of a launch are too few to fill the device
 constexpr uint32_t kPiece = 131072;            // keys of a piece of a hot bin that several workgroups read
 
-constexpr uint32_t set_workgroups(uint32_t count) { return count / kCountRange < 256u ? count / kCountRange : 256u; }
+constexpr uint32_t set_workgroups(uint32_t count, uint32_t range = kCountRange) { return count / range < 256u ? count / range : 256u; }
 
 // The contiguous range of keys of a counting or partitioning workgroup: quads groups of four from lo (a multiple of four) on,
 // then rest < 4 single keys.

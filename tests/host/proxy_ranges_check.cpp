@@ -11,8 +11,7 @@ typedef unsigned long long u64;
 int main() {
     int bad = 0;
     u64 checked = 0;
-    auto check = [&](uint32_t count) {
-        const uint32_t wgs = set_workgroups(count);
+    auto check_range = [&](uint32_t count, uint32_t wgs) {
         u64 next = 0;
         for (uint32_t wg = 0; wg < wgs; ++wg) {
             const SetRange r = set_range(count, wg, wgs);
@@ -26,6 +25,10 @@ int main() {
             if (r.quads && (u64)r.quads + 4u * 1024u > 0xFFFFFFFFull) ++bad;
         }
         if (next != count) ++bad;
+    };
+    auto check = [&](uint32_t count) {
+        check_range(count, set_workgroups(count));
+        if (set_workgroups(count) < 256u) check_range(count, set_workgroups(count, kCountRangeAlone));
         // a bin that holds every key, and the largest that one workgroup reads
         const uint32_t solo = piece_solo(count);
         for (const uint32_t n : {count, solo}) {

@@ -106,6 +106,21 @@ def test_proxy_sets_ranks(bins, n):
     check(rng.permutation(bits).view(np.float32))
 
 
+# bins of 2^19 patterns with their bits a fixed distance apart (both sides of the distances that are counted, and of what is found word by
+# word), from the first pattern to the last; with as many keys as make a bitmap (1025), and with 65535 and 65536, where the way
+# through it changes; and with nothing in the lower bits, which sets a bit only where it is new
+@pytest.mark.parametrize("apart", [1, 8, 9, 31, 33, 1023, 3071, 3072, 3073, 65536])
+@pytest.mark.parametrize("keys", [1025, 65535, 65536])
+def test_proxy_sets_distances(apart, keys):
+    rng = np.random.default_rng(apart + keys)
+    steps = min(keys, (1 << 19) // apart)
+    fine = np.concatenate([np.arange(steps) * apart, rng.integers(0, steps, keys - steps) * apart]).astype(np.uint32)
+    low = (np.uint32(1000 << 19) | fine).astype(np.uint32)                      # the bin's first pattern among them, and in
+    high = (np.uint32(1003 << 19) | (np.uint32((1 << 19) - 1) - fine)).astype(np.uint32)   # another bin the last one
+    rest = (np.uint32(1001 << 19) + rng.integers(0, 1 << 20, BIG).astype(np.uint32)).astype(np.uint32)
+    check(rng.permutation(np.concatenate([low, high, rest])).view(np.float32))
+
+
 def test_proxy_sets_groups():
     """Large matrices share launches in groups, as many as fit the workspace of the largest, with small ones (the sort, in the same
     workspace) between them: every matrix gives the bits that it gives alone."""
