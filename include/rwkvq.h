@@ -154,13 +154,11 @@ int rwkvq_vq_dequant(const void* indices, const void* codebooks, int layout, int
                      void* stream);
 
 /* y[M][N] = x[M][K] * Deq(W)^T for one matrix (the W. products of App. A.1).
- * x is row-major fp16 or bf16 (any finite values: the streaming kernels multiply fp16 operands and
- * bring bf16 activations into fp16's range group by group with exact power-of-two scales - a
- * group being the columns that share an accumulator, at most 256 consecutive ones of a row of x - so
- * an activation enters its sum exactly unless it is more than 2^29 times smaller than the largest
- * of its group, which is below the resolution of the binary32 sum; the kernels for M > 16 that split K
- * multiply bf16 activations as they are, but for calls of scalar-quantized matrices alone at M <= 32,
- * which may take the streaming kernels' way); y is row-major fp16, bf16 or
+ * x is row-major fp16 or bf16 (any finite values: bf16 activations are multiplied as they are, or, by the
+ * streaming kernels at M = 1 and for vector-quantized matrices, brought into fp16's range group by group
+ * with exact power-of-two scales - a group being the columns that share an accumulator, at most 256
+ * consecutive ones of a row of x - so an activation enters its sum exactly unless it is more than 2^29
+ * times smaller than the largest of its group, which is below the resolution of the binary32 sum); y is row-major fp16, bf16 or
  * fp32; products are accumulated in binary32 and y is rounded to nearest even.  The path is chosen from M and the layout:
  *   canonical layout: a plain reference kernel (any M);
  *   native layout, M <= 16: streaming dequant-GEMV kernels bound by HBM bandwidth;

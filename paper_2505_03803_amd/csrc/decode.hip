@@ -34,9 +34,10 @@
 //     feeds one MFMA per group.
 //   * decode_stage_kernel: batch 2..16 for launches too small to fill the device: the wavefronts of a workgroup split the
 //     columns, every one fetches its activations as operands and multiplies one to six row tiles by them.
-//   * bf16 activations are converted to fp16 on load, group by group under an exact power-of-two
-//     scale (see "bf16 activations" below), so their whole range is accepted.
-#include "common.h"
+//   * bf16 activations: multiplied as they are where the weights have an exact form in bf16 for little (SQ codes beyond batch 1, VQ
+//     entries as two bf16 in decode_stage_kernel with few row tiles); elsewhere converted to fp16 on load, group by group under an
+//     exact power-of-two scale (see "bf16 activations" below).
+#include "matrix_core.h"
 #include "../../include/rwkvq.h"
 #include <algorithm>
 #include <cmath>
@@ -232,28 +233,37 @@ __device__ __forceinline__ void store_post_mix(const PostMixMat& mt, size_t i, i
     }
 }
 
-template <int P>
-__device__ __forceinline__ uint32_t sq_pair_f16(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask,
-                                                uint32_t magic) {
-    // two 3-bit codes -> fp16x2 (8 + q_even, 8 + q_odd); mask = 0x03800380, magic = 0x48004800
+// Two 3-bit codes as a pair of 8 + q: fp16 with the codes at mantissa bits 7 .. 9 (mask 0x03800380, magic 0x48004800), or bf16 with them
+// at bits 4 .. 6 as 2^-12 (8 + q) (mask 0x00700070, magic 0x3B003B00), so that no group's sum overflows before the finite bf16 range of x ends.
+template <bool BF16, int P>
+__device__ __forceinline__ uint32_t sq_pair_code(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask,
+                                                 uint32_t magic) {
+    constexpr int at = BF16 ? 4 : 7;
     if constexpr (P < 15) {
-        constexpr int p = P % 5, sh = 6 - 3 * p;
+        constexpr int p = P % 5, sh = at - 1 - 3 * p;
         uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
         uint32_t v = sh > 0 ? (w << (sh > 0 ? sh : 0)) : sh < 0 ? (w >> (sh < 0 ? -sh : 0)) : w;
         return (v & mask) | magic;
     } else {
         // bit b of the pair's two codes sits at bits 0 and 16 of word b
         uint32_t v = (w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2);
-        return (v << 7) | magic;
+        return (v << at) | magic;
     }
 }
+// Its mask in a VGPR and magic in an SGPR: a VOP3 instruction of this ISA takes no literal and at most one scalar operand.
+template <bool BF16>
+__device__ __forceinline__ void sq_code_constants(uint32_t& mask, uint32_t& magic) {
+    asm("v_mov_b32 %0, %1" : "=v"(mask) : "n"(BF16 ? 0x00700070 : 0x03800380));
+    asm("s_mov_b32 %0, %1" : "=s"(magic) : "n"(BF16 ? 0x3B003B00 : 0x48004800));
+}
+template <bool BF16> constexpr uint32_t kSqOne = BF16 ? 0x39803980u : 0x3C003C00u;     // what sums the activations: 1, bf16 2^-12
+template <bool BF16> constexpr float kSqUnit = BF16 ? 4096.0f : 1.0f;
 
-template <int T>
-__device__ __forceinline__ half8_t sq_operand(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask,
+template <bool BF16, int T>
+__device__ __forceinline__ uint4_t sq_operand(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask,
                                               uint32_t magic) {
-    uint4_t v = {sq_pair_f16<4 * T + 0>(w0, w1, w2, mask, magic), sq_pair_f16<4 * T + 1>(w0, w1, w2, mask, magic),
-                 sq_pair_f16<4 * T + 2>(w0, w1, w2, mask, magic), sq_pair_f16<4 * T + 3>(w0, w1, w2, mask, magic)};
-    return __builtin_bit_cast(half8_t, v);
+    return uint4_t{sq_pair_code<BF16, 4 * T + 0>(w0, w1, w2, mask, magic), sq_pair_code<BF16, 4 * T + 1>(w0, w1, w2, mask, magic),
+                   sq_pair_code<BF16, 4 * T + 2>(w0, w1, w2, mask, magic), sq_pair_code<BF16, 4 * T + 3>(w0, w1, w2, mask, magic)};
 }
 
 __device__ __forceinline__ half8_t vq8_operand(uint32_t w, const uint32_t* cb) {
@@ -286,9 +296,12 @@ __device__ __forceinline__ void x_load_wg(XShared& r, const uint16_t* x, int M, 
 }
 
 // ---- bf16 activations -----------------------------------------------------------------------
-// These kernels multiply fp16 operands (codebook entries are fp16, SQ codes are fp16 subnormals in
-// place), so bf16 activations are converted, and fp16 holds a bf16 value exactly only for
-// magnitudes in [2^-17, 65536).  Activations that share an accumulator (batch 1: the 64 columns a
+// Beyond batch 1 the codes of scalar-quantized matrices are as exact in bf16 as in fp16 (sq_pair_code), and nothing is converted: 36
+// 5120 x 5120 and six 17920 x 5120 and 5120 x 17920 matrices in one call 161.8 -> 147.8 us at batch 2, 191.6 -> 176.0 at 16, 282 -> 243 at
+// 32 (5.7 to 6.2, 4.8 to 5.2 and 3.3 to 3.8 TB/s), what fp16 activations take.  Codebook entries (fp16) take two bf16 each, twice the
+// look-up words and MFMAs: in these calls 170 -> 203 us with 6-bit VQ, so VQ converts, but in launches with a workgroup per row tile or two
+// (see StageTiles).  Batch 1 multiplies fp16 (v_dot2_f32_f16; SQ codes are fp16 subnormals in place).  Where it is
+// converted: fp16 holds a bf16 value exactly only for magnitudes in [2^-17, 65536).  Activations that share an accumulator (batch 1: the 64 columns a
 // row of sixteen lanes multiplies in a tile; batch > 1: the 256 columns of one batch row in a tile)
 // are therefore first multiplied by the power of two that brings the largest magnitude among them to
 // [2^15, 2^16), and their partial sum is multiplied by the inverse power before it joins the running
@@ -333,11 +346,11 @@ __device__ __forceinline__ uint32_t bf16x2_to_f16x2(uint32_t v, int n) {
 
 // bf16: the threads that hold one batch row's 256 columns are one or two DPP rows of sixteen lanes; they agree
 // on the row's scale for this tile, convert, and the first of them leaves the inverse scale in xsc[row].
-template <int MT>
-__device__ __forceinline__ void x_store_wg(const XShared& r, half_t* xs, float* xsc, int tid, bool bf16, int g = 0) {
+template <int MT, bool CONVERT>
+__device__ __forceinline__ void x_store_wg(const XShared& r, half_t* xs, float* xsc, int tid, int g = 0) {
     const int row = 16 * g + tid / kRowThreads;
     uint4_t a = r.a, b = r.b;
-    if (bf16) {
+    if constexpr (CONVERT) {
         const ushort2_t m01 = __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a.x & 0x7FFF7FFFu), __builtin_bit_cast(ushort2_t, a.y & 0x7FFF7FFFu));
         const ushort2_t m23 = __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a.z & 0x7FFF7FFFu), __builtin_bit_cast(ushort2_t, a.w & 0x7FFF7FFFu));
         ushort2_t mm = __builtin_elementwise_max(m01, m23);
@@ -378,10 +391,16 @@ struct XFrags { uint4_t f[8]; };
 // that hold a row agree through two exchanges); lane m < 16 leaves the row's inverse scale in scw[m].
 __device__ __forceinline__ void x_frags_to_f16(XFrags& r, float* scw, int lane) {
     uint32_t amax = 0;
+    ushort2_t most = {0, 0};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) amax = max(amax, max(bf16x2_absmax(r.f[i].x, r.f[i].y), bf16x2_absmax(r.f[i].z, r.f[i].w)));
-    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 16, 64));
-    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 32, 64));
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) most = __builtin_elementwise_max(most, __builtin_bit_cast(ushort2_t, r.f[i][j] & 0x7FFF7FFFu));
+    amax = max((uint32_t)most.x, (uint32_t)most.y);
+    auto both = __builtin_amdgcn_permlane16_swap(amax, amax, false, false);      // the other three lanes of the row
+    amax = max((uint32_t)both[0], (uint32_t)both[1]);
+    both = __builtin_amdgcn_permlane32_swap(amax, amax, false, false);
+    amax = max((uint32_t)both[0], (uint32_t)both[1]);
     const int n = bf16_scale_exponent(amax);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -407,6 +426,11 @@ __device__ __forceinline__ float dpp_add(float v) {
 // ---- per-format tile loops ------------------------------------------------------------------
 
 #define RWKVQ_MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16((a), (b), (c), 0, 0, 0)
+template <bool BF16>
+__device__ __forceinline__ float4_t mfma_bits(uint4_t x, uint4_t w, float4_t c) {
+    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, w), c, 0, 0, 0);
+    else return RWKVQ_MFMA(__builtin_bit_cast(half8_t, x), __builtin_bit_cast(half8_t, w), c);
+}
 
 // Software pipeline over the column tiles T = 0 .. KT-1 with DEPTH tiles in flight from HBM
 // *while* a tile is being consumed: there is one register set more than the depth, and the load
@@ -517,6 +541,37 @@ __device__ __forceinline__ uint4_t vq6_gather4(uint32_t w0, uint32_t w1, uint32_
     return v;
 }
 
+// bf16 activations as they are: a codebook entry (two fp16) as the sum of two bf16 pairs (8 and 3 of the 11 bits, exact), multiplied in turn.
+// In LDS the two pairs of an entry stand side by side, eight bytes per entry.
+struct VqPair { uint4_t high, low; };
+__device__ __forceinline__ uint2_t vq_split(uint32_t e) {
+    const half2_t v = __builtin_bit_cast(half2_t, e);
+    const uint32_t h = Elem<true>::from_f16x2(e);
+    return uint2_t{h, Elem<true>::pack((float)v.x - __uint_as_float(h << 16), (float)v.y - __uint_as_float(h & 0xFFFF0000u))};
+}
+__device__ __forceinline__ uint2_t lds_gather2(uint32_t byte_addr) {
+    return *(const __attribute__((address_space(3))) uint2_t*)(uintptr_t)byte_addr;
+}
+template <int P>                                     // LDS byte address of entry P, eight bytes each; m = 0x1f8
+__device__ __forceinline__ uint32_t vq6_lds_addr8(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t m, uint32_t base) {
+    if constexpr (P < 15) {
+        constexpr int sh = 6 * (P % 5) - 1;
+        const uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
+        return ((sh < 0 ? w << 1 : w >> (sh < 0 ? 0 : sh)) & m) | base;
+    } else {
+        return ((w0 & 3u) << 3) | ((w1 & 3u) << 5) | ((w2 & 3u) << 7) | base;
+    }
+}
+__device__ __forceinline__ VqPair vq_pair(uint2_t a, uint2_t b, uint2_t c, uint2_t d) { return VqPair{uint4_t{a.x, b.x, c.x, d.x}, uint4_t{a.y, b.y, c.y, d.y}}; }
+template <int T4>
+__device__ __forceinline__ VqPair vq6_split4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t m, uint32_t base) {
+    return vq_pair(lds_gather2(vq6_lds_addr8<4 * T4 + 0>(w0, w1, w2, m, base)), lds_gather2(vq6_lds_addr8<4 * T4 + 1>(w0, w1, w2, m, base)),
+                   lds_gather2(vq6_lds_addr8<4 * T4 + 2>(w0, w1, w2, m, base)), lds_gather2(vq6_lds_addr8<4 * T4 + 3>(w0, w1, w2, m, base)));
+}
+__device__ __forceinline__ VqPair vq8_split4(uint32_t w, const uint2_t* cb) {
+    return vq_pair(cb[w & 255u], cb[(w >> 8) & 255u], cb[(w >> 16) & 255u], cb[w >> 24]);
+}
+
 // G = groups of 16 batch rows (1 for batch <= 16, 2 for batch 17..32)
 constexpr int groups_of(int MT) { return MT <= 16 ? 1 : MT / 16; }
 template <int G> struct SqRegs { uint4_t a[kBRT]; uint2_t b[kBRT]; uint2_t sz[kBRT]; XShared x[G]; };
@@ -546,7 +601,7 @@ struct WavePos {
 // activations come from the matrix cores too: one more MFMA per k-step with an all-ones B operand
 // leaves X_g[m] in the accumulator layout of the products, and y += s (acc - (8 + z) X_g).
 template <int MT, int DEPTH, bool XB, int P>
-__device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, half_t* xs, float* xsc,
+__device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, half_t* xs,
                                        float4_t (&out)[P][groups_of(MT)][kBRT]) {
     constexpr int G = groups_of(MT), UB = (G == 1 && RWKVQ_BATCH_UB2) ? 2 : 1;   // one group: the fragments of both column halves up front
     using Regs = SqRegs<G>;
@@ -564,13 +619,9 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
     int xoff[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) xoff[g] = (16 * g + (lane & 15) < M ? 16 * g + (lane & 15) : M - 1) * kXStride + 8 * (lane >> 4);
-    // The and-or that builds 8 + q takes its mask from a VGPR and the fp16 pattern of 8.0 from an
-    // SGPR: a VOP3 instruction of this ISA takes no literal and at most one scalar operand.
     uint32_t mask, magic;
-    asm("v_mov_b32 %0, 0x03800380" : "=v"(mask));
-    asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
-    const uint4_t ones4 = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
-    const half8_t ones = __builtin_bit_cast(half8_t, ones4);
+    sq_code_constants<XB>(mask, magic);
+    const uint4_t ones = {kSqOne<XB>, kSqOne<XB>, kSqOne<XB>, kSqOne<XB>};
     auto load = [&](Regs& r, int T, auto pass) {
         constexpr int J = decltype(pass)::value;
 #pragma unroll
@@ -588,25 +639,21 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
     auto compute = [&](const Regs& r, int T, auto pass) {
         constexpr int J = decltype(pass)::value;
         half_t* buf = xs + (T & 1) * (MT * kXStride);
-        float* scb = xsc + (T & 1) * (16 * G);
         if constexpr (J == 0) {
 #pragma unroll
-            for (int g = 0; g < G; ++g) x_store_wg<MT>(r.x[g], buf, scb, wp.tid, XB, g);
+            for (int g = 0; g < G; ++g) x_store_wg<MT, false>(r.x[g], buf, nullptr, wp.tid, g);
             __syncthreads();
         }
-        float4_t sc[G];                              // bf16: inverse scale of this tile for the lane's batch rows
-#pragma unroll
-        for (int g = 0; g < G; ++g) sc[g] = XB ? *(const float4_t*)(scb + 16 * g + 4 * (lane >> 4)) : float4_t{1, 1, 1, 1};
 #pragma unroll
         for (int ub = 0; ub < 2; ub += UB) {
-            half8_t xa[UB][G][4];
+            uint4_t xa[UB][G][4];
 #pragma unroll
             for (int uu = 0; uu < UB; ++uu)
 #pragma unroll
                 for (int g = 0; g < G; ++g)
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
-                        xa[uu][g][t] = *(const half8_t*)(buf + xoff[g] + 128 * (ub + uu) + 32 * t);
+                        xa[uu][g][t] = *(const uint4_t*)(buf + xoff[g] + 128 * (ub + uu) + 32 * t);
 #pragma unroll
             for (int uu = 0; uu < UB; ++uu) {
                 const int u = ub + uu;
@@ -615,26 +662,26 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
                 for (int g = 0; g < G; ++g) {
                     X[g] = float4_t{0, 0, 0, 0};
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) X[g] = RWKVQ_MFMA(xa[uu][g][t], ones, X[g]);
+                    for (int t = 0; t < 4; ++t) X[g] = mfma_bits<XB>(xa[uu][g][t], ones, X[g]);
                 }
 #pragma unroll
                 for (int rt = 0; rt < kBRT; ++rt) {
                     const uint32_t w0 = u == 0 ? r.a[rt].x : r.a[rt].w, w1 = u == 0 ? r.a[rt].y : r.b[rt].x,
                                    w2 = u == 0 ? r.a[rt].z : r.b[rt].y;
-                    const half8_t op0 = sq_operand<0>(w0, w1, w2, mask, magic), op1 = sq_operand<1>(w0, w1, w2, mask, magic),
-                                  op2 = sq_operand<2>(w0, w1, w2, mask, magic), op3 = sq_operand<3>(w0, w1, w2, mask, magic);
+                    const uint4_t op0 = sq_operand<XB, 0>(w0, w1, w2, mask, magic), op1 = sq_operand<XB, 1>(w0, w1, w2, mask, magic),
+                                  op2 = sq_operand<XB, 2>(w0, w1, w2, mask, magic), op3 = sq_operand<XB, 3>(w0, w1, w2, mask, magic);
                     const uint32_t szw = u == 0 ? r.sz[rt].x : r.sz[rt].y;
-                    const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu));
+                    const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)) * kSqUnit<XB>;
                     const float z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
                         float4_t acc = {0, 0, 0, 0};
-                        acc = RWKVQ_MFMA(xa[uu][g][0], op0, acc);
-                        acc = RWKVQ_MFMA(xa[uu][g][1], op1, acc);
-                        acc = RWKVQ_MFMA(xa[uu][g][2], op2, acc);
-                        acc = RWKVQ_MFMA(xa[uu][g][3], op3, acc);
+                        acc = mfma_bits<XB>(xa[uu][g][0], op0, acc);
+                        acc = mfma_bits<XB>(xa[uu][g][1], op1, acc);
+                        acc = mfma_bits<XB>(xa[uu][g][2], op2, acc);
+                        acc = mfma_bits<XB>(xa[uu][g][3], op3, acc);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) out[J][g][rt][i] = fmaf(XB ? s * sc[g][i] : s, fmaf(-z8, X[g][i], acc[i]), out[J][g][rt][i]);
+                        for (int i = 0; i < 4; ++i) out[J][g][rt][i] = fmaf(s, fmaf(-z8, X[g][i], acc[i]), out[J][g][rt][i]);
                     }
                 }
             }
@@ -683,7 +730,7 @@ __device__ __forceinline__ void run_vq6(const DecodeMat& mt, const WavePos& wp, 
         float* scb = xsc + (T & 1) * (16 * G);
         if constexpr (J == 0) {
 #pragma unroll
-            for (int g = 0; g < G; ++g) x_store_wg<MT>(r.x[g], buf, scb, wp.tid, XB, g);
+            for (int g = 0; g < G; ++g) x_store_wg<MT, XB>(r.x[g], buf, scb, wp.tid, g);
             cb_lds[(T & 1) * 256 + lane] = r.cb;     // two slots, 1 KB apart (the gather address ORs the index in)
             __syncthreads();
         }
@@ -780,7 +827,7 @@ __device__ __forceinline__ void run_vq8(const DecodeMat& mt, const WavePos& wp, 
         uint32_t* cbuf = cb_lds + (T & 1) * 256;     // two codebook slots, like the activations
         if constexpr (J == 0) {
 #pragma unroll
-            for (int g = 0; g < G; ++g) x_store_wg<MT>(r.x[g], buf, scb, wp.tid, XB, g);
+            for (int g = 0; g < G; ++g) x_store_wg<MT, XB>(r.x[g], buf, scb, wp.tid, g);
             *(uint4_t*)(cbuf + 4 * lane) = r.cb;
             __syncthreads();
         }
@@ -1166,11 +1213,11 @@ template <int MT, int DEPTH, int P>
 __device__ __forceinline__ void run_batched(const DecodeMat& mt, const WavePos& wp, half_t* xs, float* xsc, uint32_t* cb_lds,
                                             float4_t (&out)[P][groups_of(MT)][kBRT]) {
     if (wp.xbf16) {
-        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, true, P>(mt, wp, xs, xsc, out);
+        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, true, P>(mt, wp, xs, out);
         else if (mt.fmt == FMT_VQ6) run_vq6<MT, DEPTH, true, P>(mt, wp, xs, xsc, cb_lds, out);
         else run_vq8<MT, DEPTH, true, P>(mt, wp, xs, xsc, cb_lds, out);
     } else {
-        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, false, P>(mt, wp, xs, xsc, out);
+        if (mt.fmt == FMT_SQ3) run_sq<MT, DEPTH, false, P>(mt, wp, xs, out);
         else if (mt.fmt == FMT_VQ6) run_vq6<MT, DEPTH, false, P>(mt, wp, xs, xsc, cb_lds, out);
         else run_vq8<MT, DEPTH, false, P>(mt, wp, xs, xsc, cb_lds, out);
     }
@@ -1349,10 +1396,17 @@ struct StageRegs {
 // Row tiles in flight.  The sets rotate with the row tiles of one column tile, or of two (MULTI).
 constexpr int stage_sets(int R, bool multi) { return R == 6 ? 3 : multi && R == 1 ? 2 : R; }
 
+template <bool DIRECT> constexpr int kStageSlot = DIRECT ? 512 : 256;   // words of a codebook slot
 template <int FMT, int R, bool MULTI, bool XB>
 struct StageTiles {
     static constexpr int D = stage_sets(R, MULTI);
     static constexpr bool kOneBlock = 16 % R == 0;   // the row tiles share a codebook block
+    // bf16 activations: as they are, or brought into fp16.  SQ codes are exact in either type.  VQ entries as two bf16 pairs take two
+    // look-up words and two MFMAs where the conversion takes 235 instructions per column tile, for all row tiles: 6-bit VQ with up to two
+    // of them, 8-bit with one (its look-ups of eight bytes meet in twice the banks).  Measured (us, converted -> as they are): 4096 x 4096
+    // SQ at M = 2 5.8 -> 4.8, at 16 7.2 -> 6.7, 4096 x 14336 at 2 14.8 -> 11.4, 6-bit VQ 14.5 -> 11.7, 8-bit 15.4 -> 13.7; 17920 x 5120 and
+    // 5120 x 5120 SQ (six row tiles) at 2 17.8 -> 12.8.  VQ of five row tiles at 2 10.7 -> 11.1, of two in 8 bits 5.4 -> 5.6 (converted).
+    static constexpr bool kDirect = XB && (FMT == FMT_SQ3 || R <= (FMT == FMT_VQ6 ? 2 : 1)), kConvert = XB && !kDirect;
     static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
     const DecodeMat& mt;
     int R0, NR, KT, lane, xoff;
@@ -1365,9 +1419,8 @@ struct StageTiles {
     __device__ __forceinline__ StageTiles(const DecodeMat& mt_, int R0_, int M, int lane_, float* xsc_, uint32_t* cb_)
         : mt(mt_), R0(R0_), NR(mt_.N >> 4), KT(mt_.K >> 8), lane(lane_), xsc(xsc_), cb_lds(cb_) {
         xoff = ((lane & 15) < M ? lane & 15 : M - 1) * mt.K + 8 * (lane >> 4);
-        asm("v_mov_b32 %0, 0x03800380" : "=v"(mask));                        // (see run_sq, run_vq6)
-        asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
-        asm("v_mov_b32 %0, 0xfc" : "=v"(m6));
+        sq_code_constants<kDirect>(mask, magic);
+        asm("v_mov_b32 %0, %1" : "=v"(m6) : "n"(kDirect ? 0x1f8 : 0xfc));
         base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
     }
     // A column tile's activation fragments (see XFrags), a row tile's weights: together and in order (see tile_pipeline).  Past the
@@ -1401,50 +1454,67 @@ struct StageTiles {
     }
     __device__ __forceinline__ void multiply(const StageRegs& r, const XFrags& x, int rt, const float4_t& sc, const float4_t (&X)[2], float4_t& out) {
         const uint32_t slot = (uint32_t)(kOneBlock ? 0 : rt & 1);
-        const uint32_t* cbuf = cb_lds + 256 * slot;
+        uint32_t* const cbuf = cb_lds + kStageSlot<kDirect> * slot;
         if constexpr (FMT != FMT_SQ3) {
             if (!kOneBlock || rt == 0) {
-                if constexpr (FMT == FMT_VQ8) *(uint4_t*)(cb_lds + 256 * slot + 4 * lane) = r.cb;
-                else cb_lds[256 * slot + lane] = r.b.z;
+                if constexpr (kDirect && FMT == FMT_VQ8) {
+                    const uint2_t e0 = vq_split(r.cb.x), e1 = vq_split(r.cb.y), e2 = vq_split(r.cb.z), e3 = vq_split(r.cb.w);
+                    *(uint4_t*)(cbuf + 8 * lane) = uint4_t{e0.x, e0.y, e1.x, e1.y};
+                    *(uint4_t*)(cbuf + 8 * lane + 4) = uint4_t{e2.x, e2.y, e3.x, e3.y};
+                } else if constexpr (kDirect) {
+                    *(uint2_t*)(cbuf + 2 * lane) = vq_split(r.b.z);
+                } else if constexpr (FMT == FMT_VQ8) {
+                    *(uint4_t*)(cbuf + 4 * lane) = r.cb;
+                } else {
+                    cbuf[lane] = r.b.z;
+                }
                 wave_lds_sync();
             }
         }
         float4_t part = {0, 0, 0, 0};
-        float4_t& acc = *(XB ? &part : &out);                                // VQ: as in run_vq6
+        float4_t& acc = *(kConvert ? &part : &out);                          // (as in run_vq6)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            half8_t op[4];
-            if constexpr (FMT == FMT_VQ8) {
+            const uint32_t w0 = u == 0 ? r.a.x : r.a.w, w1 = u == 0 ? r.a.y : r.b.x, w2 = u == 0 ? r.a.z : r.b.y;
+            if constexpr (FMT == FMT_SQ3) {
+                const uint4_t op[4] = {sq_operand<kDirect, 0>(w0, w1, w2, mask, magic), sq_operand<kDirect, 1>(w0, w1, w2, mask, magic),
+                                       sq_operand<kDirect, 2>(w0, w1, w2, mask, magic), sq_operand<kDirect, 3>(w0, w1, w2, mask, magic)};
+                const uint32_t szw = u == 0 ? r.b.z : r.b.w;
+                const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)) * kSqUnit<kDirect>;
+                const float z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
+                float4_t sum = {0, 0, 0, 0};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sum = mfma_bits<kDirect>(x.f[4 * u + t], op[t], sum);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) out[i] = fmaf(s, fmaf(-z8, X[u][i], sum[i]), out[i]);
+            } else if constexpr (kDirect) {
+                const uint32_t base = base0 + 4 * kStageSlot<kDirect> * slot;
                 const uint4_t q = u == 0 ? r.a : r.b;
-                op[0] = vq8_operand(q.x, cbuf); op[1] = vq8_operand(q.y, cbuf); op[2] = vq8_operand(q.z, cbuf); op[3] = vq8_operand(q.w, cbuf);
+                const uint2_t* const cb = (const uint2_t*)cbuf;
+                VqPair op[4];
+                if constexpr (FMT == FMT_VQ8) { op[0] = vq8_split4(q.x, cb); op[1] = vq8_split4(q.y, cb); op[2] = vq8_split4(q.z, cb); op[3] = vq8_split4(q.w, cb); }
+                else {
+                    op[0] = vq6_split4<0>(w0, w1, w2, m6, base); op[1] = vq6_split4<1>(w0, w1, w2, m6, base);
+                    op[2] = vq6_split4<2>(w0, w1, w2, m6, base); op[3] = vq6_split4<3>(w0, w1, w2, m6, base);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) out = mfma_bits<true>(x.f[4 * u + t], op[t].low, mfma_bits<true>(x.f[4 * u + t], op[t].high, out));
             } else {
-                const uint32_t w0 = u == 0 ? r.a.x : r.a.w, w1 = u == 0 ? r.a.y : r.b.x, w2 = u == 0 ? r.a.z : r.b.y;
-                if constexpr (FMT == FMT_SQ3) {
-                    op[0] = sq_operand<0>(w0, w1, w2, mask, magic); op[1] = sq_operand<1>(w0, w1, w2, mask, magic);
-                    op[2] = sq_operand<2>(w0, w1, w2, mask, magic); op[3] = sq_operand<3>(w0, w1, w2, mask, magic);
-                } else {
-                    const uint32_t base = base0 + 1024 * slot;
+                const uint32_t base = base0 + 4 * kStageSlot<kDirect> * slot;
+                const uint4_t q = u == 0 ? r.a : r.b;
+                half8_t op[4];
+                if constexpr (FMT == FMT_VQ8) { op[0] = vq8_operand(q.x, cbuf); op[1] = vq8_operand(q.y, cbuf); op[2] = vq8_operand(q.z, cbuf); op[3] = vq8_operand(q.w, cbuf); }
+                else {
                     op[0] = __builtin_bit_cast(half8_t, vq6_gather4<0>(w0, w1, w2, m6, base));
                     op[1] = __builtin_bit_cast(half8_t, vq6_gather4<1>(w0, w1, w2, m6, base));
                     op[2] = __builtin_bit_cast(half8_t, vq6_gather4<2>(w0, w1, w2, m6, base));
                     op[3] = __builtin_bit_cast(half8_t, vq6_gather4<3>(w0, w1, w2, m6, base));
                 }
-            }
-            if constexpr (FMT == FMT_SQ3) {
-                const uint32_t szw = u == 0 ? r.b.z : r.b.w;
-                const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu));
-                const float z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
-                float4_t sum = {0, 0, 0, 0};
-#pragma unroll
-                for (int t = 0; t < 4; ++t) sum = RWKVQ_MFMA(__builtin_bit_cast(half8_t, x.f[4 * u + t]), op[t], sum);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) out[i] = fmaf(XB ? s * sc[i] : s, fmaf(-z8, X[u][i], sum[i]), out[i]);
-            } else {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) acc = RWKVQ_MFMA(__builtin_bit_cast(half8_t, x.f[4 * u + t]), op[t], acc);
             }
         }
-        if (FMT != FMT_SQ3 && XB)
+        if (kConvert)
 #pragma unroll
             for (int i = 0; i < 4; ++i) out[i] = fmaf(part[i], sc[i], out[i]);
     }
@@ -1454,17 +1524,17 @@ struct StageTiles {
     __device__ __forceinline__ void column(int T, int S, int last, float4_t (&out)[R]) {
         XFrags& x = xf[J];
         float4_t sc = {1, 1, 1, 1};
-        if (XB) {
+        if (kConvert) {
             x_frags_to_f16(x, xsc, lane);
             wave_lds_sync();
             sc = *(const float4_t*)(xsc + 4 * (lane >> 4));
         }
         // group sums of the activations, for all row tiles
-        const uint4_t ones4 = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+        const uint4_t ones = {kSqOne<kDirect>, kSqOne<kDirect>, kSqOne<kDirect>, kSqOne<kDirect>};
         float4_t X[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
         if constexpr (FMT == FMT_SQ3) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) X[i >> 2] = RWKVQ_MFMA(__builtin_bit_cast(half8_t, x.f[i]), __builtin_bit_cast(half8_t, ones4), X[i >> 2]);
+            for (int i = 0; i < 8; ++i) X[i >> 2] = mfma_bits<kDirect>(x.f[i], ones, X[i >> 2]);
         }
 #pragma unroll
         for (int rt = 0; rt < R; ++rt) {
@@ -1504,8 +1574,8 @@ struct StageTiles {
 // sums meet in LDS in a fixed order.  A wavefront fetches the activations of a column tile once, straight into the operand layout
 // of the MFMA, and they serve R row tiles; nothing is staged for the workgroup, no barrier sits in the loop.
 // What bounds it: start-up (about 4.5 us of a launch that moves nothing), then x: a compute unit reads all of x (131 KB at M = 16,
-// K = 4096) in pieces of 64 bytes per batch row, half of a cache line at a time (whole lines, timing only: o 6.5 -> 5.5 us, v'
-// 19.3 -> 15.3; it would need a transpose through LDS).  With 16 wavefronts of one column tile each every byte of a workgroup is
+// K = 4096) in pieces of 64 bytes per batch row, half of a cache line at a time.  (Whole lines, two of the loads exchanging half of every
+// DPP row in registers, were 0 to 11 % slower: the other half of a line is found in the L1, and the exchange costs.)  With 16 wavefronts of one column tile each every byte of a workgroup is
 // asked for at its start.  Measured (7B shapes, fp16 SQ, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
 // wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.8, o 6.1 / 8.9 -> 5.1 / 6.8, {k', r'} 12.6 / 19.1
 // -> 8.8 / 11.1, v' 13.1 / 21.5 -> 11.5 / 18.2.
@@ -1578,28 +1648,26 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
 
 // The same for 17 .. 48 rows of x (G = 2, 3 groups of sixteen), eight wavefronts of 256 registers.  The activations of a column tile
 // would take all of them, so a tile goes in its two units of 128 columns: while the R row tiles are multiplied by the fragments of
-// one, those of the next are in flight.  XB (bf16 activations, brought into fp16 unit by unit): SQ only.  What that drops lies 2^29 and
-// more below the largest activation of the unit, and below the resolution of a sum in which every code counts 8 to 15.  Entries of a
-// codebook may be zero at the large activations: VQ is left to the kernels of midbatch.hip, which multiply bf16 as it is.
+// one, those of the next are in flight.  XB (bf16 activations, as they are): SQ only.  VQ would need two operands per weight and the
+// registers for them, and is left to the kernels of midbatch.hip.  Without the conversion to fp16 that bf16 took before (us): {k', r'} of
+// the 7B shapes SQ at M = 17 16.8 -> 14.0, at 32 19.7 -> 16.9, and 48 rows fit: 18432 x 4096 at 33 26.4 -> 19.4, at 48 27.7 -> 21.9.
 template <int FMT, int R, int G, bool XB>
 struct StageWide {
-    static_assert(FMT == FMT_SQ3 || !XB, "bf16 activations as they are");
+    static_assert(FMT == FMT_SQ3 || !XB, "one operand per weight");
     static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
     const DecodeMat& mt;
     int R0, NR, KT, lane, block0, more_blocks;
     uint32_t xoff[G];
-    float* xsc;                        // [G][16]
     uint32_t* cb_lds;                  // [2][256]: codebooks of the first and of the last row tile's block
     uint32_t mask, magic, m6, base0;
     StageRegs w[R];                    // (a codebook in the first two only: R row tiles lie in at most two blocks)
     uint4_t xf[2][G][4];
 
-    __device__ __forceinline__ StageWide(const DecodeMat& mt_, int R0_, int M, int lane_, float* xsc_, uint32_t* cb_)
-        : mt(mt_), R0(R0_), NR(mt_.N >> 4), KT(mt_.K >> 8), lane(lane_), xsc(xsc_), cb_lds(cb_) {
+    __device__ __forceinline__ StageWide(const DecodeMat& mt_, int R0_, int M, int lane_, uint32_t* cb_)
+        : mt(mt_), R0(R0_), NR(mt_.N >> 4), KT(mt_.K >> 8), lane(lane_), cb_lds(cb_) {
 #pragma unroll
         for (int g = 0; g < G; ++g) xoff[g] = (uint32_t)((16 * g + (lane & 15) < M ? 16 * g + (lane & 15) : M - 1) * mt.K + 8 * (lane >> 4));
-        asm("v_mov_b32 %0, 0x03800380" : "=v"(mask));
-        asm("s_mov_b32 %0, 0x48004800" : "=s"(magic));
+        sq_code_constants<XB>(mask, magic);
         asm("v_mov_b32 %0, 0xfc" : "=v"(m6));
         block0 = R0 >> 4;
         more_blocks = ((R0 + R - 1 < NR ? R0 + R - 1 : NR - 1) >> 4) - block0;
@@ -1640,24 +1708,6 @@ struct StageWide {
     // every row tile's next weights.
     template <int U>
     __device__ __forceinline__ void unit(int T, int Tn, bool more, float4_t (&out)[R][G]) {
-        float4_t sc[G];
-        if (XB) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                uint32_t amax = 0;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) amax = max(amax, max(bf16x2_absmax(xf[U][g][t].x, xf[U][g][t].y), bf16x2_absmax(xf[U][g][t].z, xf[U][g][t].w)));
-                amax = max(amax, (uint32_t)__shfl_xor((int)amax, 16, 64));
-                amax = max(amax, (uint32_t)__shfl_xor((int)amax, 32, 64));
-                const int n = bf16_scale_exponent(amax);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    xf[U][g][t].x = bf16x2_to_f16x2(xf[U][g][t].x, n); xf[U][g][t].y = bf16x2_to_f16x2(xf[U][g][t].y, n);
-                    xf[U][g][t].z = bf16x2_to_f16x2(xf[U][g][t].z, n); xf[U][g][t].w = bf16x2_to_f16x2(xf[U][g][t].w, n);
-                }
-                if (lane < 16) xsc[16 * g + lane] = ldexpf(1.0f, -n);
-            }
-        }
         if (FMT != FMT_SQ3 && U == 0) {
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
@@ -1665,57 +1715,55 @@ struct StageWide {
                 else cb_lds[256 * rt + lane] = w[rt].b.z;
             }
         }
-        wave_lds_sync();
-#pragma unroll
-        for (int g = 0; g < G; ++g) sc[g] = XB ? *(const float4_t*)(xsc + 16 * g + 4 * (lane >> 4)) : float4_t{1, 1, 1, 1};
+        if (FMT != FMT_SQ3) wave_lds_sync();
         float4_t X[G];
         if constexpr (FMT == FMT_SQ3) {
-            const uint4_t ones4 = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+            const uint4_t ones = {kSqOne<XB>, kSqOne<XB>, kSqOne<XB>, kSqOne<XB>};
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 X[g] = float4_t{0, 0, 0, 0};
 #pragma unroll
-                for (int t = 0; t < 4; ++t) X[g] = RWKVQ_MFMA(__builtin_bit_cast(half8_t, xf[U][g][t]), __builtin_bit_cast(half8_t, ones4), X[g]);
+                for (int t = 0; t < 4; ++t) X[g] = mfma_bits<XB>(xf[U][g][t], ones, X[g]);
             }
         }
 #pragma unroll
         for (int rt = 0; rt < R; ++rt) {
             const StageRegs& r = w[rt];
-            half8_t op[4];
+            uint4_t op[4];
             const uint32_t slot = (R0 + rt) >> 4 != block0 ? (uint32_t)more_blocks : 0u;
             if constexpr (FMT == FMT_VQ8) {
                 const uint4_t q = U == 0 ? r.a : r.b;
                 const uint32_t* cbuf = cb_lds + 256 * slot;
-                op[0] = vq8_operand(q.x, cbuf); op[1] = vq8_operand(q.y, cbuf); op[2] = vq8_operand(q.z, cbuf); op[3] = vq8_operand(q.w, cbuf);
+                op[0] = __builtin_bit_cast(uint4_t, vq8_operand(q.x, cbuf)); op[1] = __builtin_bit_cast(uint4_t, vq8_operand(q.y, cbuf)); op[2] = __builtin_bit_cast(uint4_t, vq8_operand(q.z, cbuf)); op[3] = __builtin_bit_cast(uint4_t, vq8_operand(q.w, cbuf));
             } else {
                 const uint32_t w0 = U == 0 ? r.a.x : r.a.w, w1 = U == 0 ? r.a.y : r.b.x, w2 = U == 0 ? r.a.z : r.b.y;
                 if constexpr (FMT == FMT_SQ3) {
-                    op[0] = sq_operand<0>(w0, w1, w2, mask, magic); op[1] = sq_operand<1>(w0, w1, w2, mask, magic);
-                    op[2] = sq_operand<2>(w0, w1, w2, mask, magic); op[3] = sq_operand<3>(w0, w1, w2, mask, magic);
+                    op[0] = sq_operand<XB, 0>(w0, w1, w2, mask, magic); op[1] = sq_operand<XB, 1>(w0, w1, w2, mask, magic);
+                    op[2] = sq_operand<XB, 2>(w0, w1, w2, mask, magic); op[3] = sq_operand<XB, 3>(w0, w1, w2, mask, magic);
                 } else {
                     const uint32_t base = base0 + 1024 * slot;
-                    op[0] = __builtin_bit_cast(half8_t, vq6_gather4<0>(w0, w1, w2, m6, base));
-                    op[1] = __builtin_bit_cast(half8_t, vq6_gather4<1>(w0, w1, w2, m6, base));
-                    op[2] = __builtin_bit_cast(half8_t, vq6_gather4<2>(w0, w1, w2, m6, base));
-                    op[3] = __builtin_bit_cast(half8_t, vq6_gather4<3>(w0, w1, w2, m6, base));
+                    op[0] = vq6_gather4<0>(w0, w1, w2, m6, base);
+                    op[1] = vq6_gather4<1>(w0, w1, w2, m6, base);
+                    op[2] = vq6_gather4<2>(w0, w1, w2, m6, base);
+                    op[3] = vq6_gather4<3>(w0, w1, w2, m6, base);
                 }
             }
             const uint32_t szw = U == 0 ? r.b.z : r.b.w;                      // (SQ)
-            const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
+            const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)) * kSqUnit<XB>, z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float4_t sum = {0, 0, 0, 0};
                 if (FMT != FMT_SQ3) sum = out[rt][g];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) sum = RWKVQ_MFMA(__builtin_bit_cast(half8_t, xf[U][g][t]), op[t], sum);
+                for (int t = 0; t < 4; ++t) sum = mfma_bits<XB>(xf[U][g][t], op[t], sum);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    if constexpr (FMT == FMT_SQ3) out[rt][g][i] = fmaf(XB ? s * sc[g][i] : s, fmaf(-z8, X[g][i], sum[i]), out[rt][g][i]);
+                    if constexpr (FMT == FMT_SQ3) out[rt][g][i] = fmaf(s, fmaf(-z8, X[g][i], sum[i]), out[rt][g][i]);
                     else out[rt][g][i] = sum[i];
                 }
             }
             if (U == 1) load_w(w[rt], Tn, rt, more);
-            else if (FMT != FMT_SQ3 && R == 6 && (rt & 1)) __builtin_amdgcn_sched_barrier(0);   // look-ups of two row tiles at a time: more would spill
+            else if (XB || (FMT != FMT_SQ3 && R == 6 && (rt & 1))) __builtin_amdgcn_sched_barrier(0);   // operands of one or two row tiles at a time: more would spill
         }
         load_x<U>(Tn, more);
     }
@@ -1739,7 +1787,6 @@ constexpr int kWideWaves = 8;
 template <int R, int G, bool XB>
 __global__ void __launch_bounds__(64 * kWideWaves) decode_stage_wide_kernel(StageArgs<kGrid2DMaxMats> a) {
     extern __shared__ __attribute__((aligned(1024))) uint32_t stage_lds[];        // per wavefront: R codebook slots, later its sums
-    __shared__ __attribute__((aligned(16))) float xsc[kWideWaves][16 * G];
     const int M = a.M, ydt = a.ydt, S = a.S;
     const DecodeMat mt = a.m[blockIdx.y];
     asm volatile("" :: "s"(M), "s"(ydt), "s"(S), "s"(mt.N));
@@ -1757,9 +1804,9 @@ __global__ void __launch_bounds__(64 * kWideWaves) decode_stage_wide_kernel(Stag
         for (int g = 0; g < G; ++g) out[rt][g] = float4_t{0, 0, 0, 0};
     if (wave < KT) {
         const int nt = (KT - wave + S - 1) / S;
-        if (XB || mt.fmt == FMT_SQ3) StageWide<FMT_SQ3, R, G, XB>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-        else if (mt.fmt == FMT_VQ6) StageWide<FMT_VQ6, R, G, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-        else StageWide<FMT_VQ8, R, G, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+        if (XB || mt.fmt == FMT_SQ3) StageWide<FMT_SQ3, R, G, XB>(mt, R0, M, lane, mine).run(wave, S, nt, out);
+        else if (mt.fmt == FMT_VQ6) StageWide<FMT_VQ6, R, G, false>(mt, R0, M, lane, mine).run(wave, S, nt, out);
+        else StageWide<FMT_VQ8, R, G, false>(mt, R0, M, lane, mine).run(wave, S, nt, out);
     }
     wave_lds_sync();
 #pragma unroll
@@ -1973,10 +2020,11 @@ struct StageShape {
 //   * one round: the fewest row tiles that make at most 256 workgroups, each with a compute unit to itself and, up to sixteen, a
 //     wavefront per column tile: every byte is asked for at the start ({r, k, v, g} of the 7B shapes in SQ at M = 16 9.9, in four
 //     wavefronts 11.2; {k', r'} 11.1 and 12.9).  17 to 19 columns in turns of at most eight wavefronts, of twelve from three row tiles on and with two in
-//     bf16.  Longer rows: bf16, whose conversion every wavefront repeats, by eight or twelve, a multiple of the SIMDs (5120 x 5120 SQ
-//     at M = 2 in 9.6 by ten, 8.8 by eight; 5120 x 10240 15.2 by ten, 13.8 by twelve), twelve where a tile of x is short; fp16 by
-//     fewer as M grows, whose lines of x the others evict (4096 x 14336 SQ at M = 8 14.0 by eight, 13.3 by six; with 4096 x 4096 in 6-bit VQ
-//     at M = 16 20.6 by eight, 18.7 by five).  On 690 calls within 1.1 % of the best S in the mean;
+//     bf16.  Longer rows: fp16, and SQ in bf16, by fewer as M grows, whose lines of x the others evict (4096 x 14336 SQ at M = 8 in fp16 14.0
+//     by eight, 13.3 by six, in bf16 14.0 and 13.2; at M = 16 in bf16 18.6 by eight, 18.0 by five); bf16 with VQ, whose conversion or second
+//     operands every wavefront repeats, by eight or twelve, a multiple of the SIMDs (5120 x 17920 6-bit VQ at M = 2 19.6 by seven, 17.5 by
+//     twelve), twelve where a tile of x is short, or with one row tile by ten up to M = 8 and by six beyond (4096 x 14336 6-bit VQ at M = 2
+//     11.9 by twelve, 11.7 by ten; at M = 16 19.8 by eight, 18.2 by six).  In fp16 on 690 calls within 1.1 % of the best S in the mean;
 //   * one round, mixed lengths: a workgroup of the longest rows would end long after the others: two row tiles instead of three to
 //     six, or one (a layer of d = 2048 in 8-bit VQ at M = 2 20.2 with R = 6, now 13.4; {8192 x 256, 256 x 8192} in SQ at M = 8 12.2 and 9.4);
 //   * several rounds, of one length or of mixed ones: small workgroups overlap ({k', r', v'} of the 14B-class shapes in 8-bit VQ at M = 4
@@ -1985,11 +2033,13 @@ struct StageShape {
 static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype) {
     const bool grid2d = n_mats <= kGrid2DMaxMats;
     int columns = 0, fits = 0;
+    bool vq = false;
     double row_tiles = 0.0, tiles = 0.0, vq8 = 0.0;
     for (int i = 0; i < n_mats; ++i) {
         const MatDev& m = mats[order[i]];
         columns = std::max(columns, m.K >> 8);
         row_tiles += m.N >> 4; tiles += (double)(m.N >> 4) * (m.K >> 8);
+        vq = vq || m.fmt != FMT_SQ3;
         if (m.fmt == FMT_VQ8) vq8 += m.N >> 4;
     }
     for (int r = 1; r <= 6 && !fits; ++r) {
@@ -2022,7 +2072,7 @@ static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, 
     p.turns = (columns + most - 1) / most;
     p.S = (columns + p.turns - 1) / p.turns;
     if (p.kind == STAGE_ROUND && columns >= 20) {
-        if (x_dtype == DT_BF16) p.S = M <= 8 && columns > 20 ? 12 : 8;
+        if (x_dtype == DT_BF16 && vq) p.S = fits == 1 ? (M <= 8 ? 10 : 6) : M <= 8 && columns > 20 ? 12 : 8;
         else p.S = fits == 6 || ((fits == 2 || fits == 3) && M <= 4) ? 8 : M <= 12 || fits == 1 ? 6 : 5;
         p.turns = (columns + p.S - 1) / p.S;
     }
@@ -2109,10 +2159,10 @@ static hipError_t launch_wide_kernel(const StageArgs<kGrid2DMaxMats>& a, dim3 gr
 // Measured (us, there -> here) at K = 256 to 7168, N = 16640 to 24576, M = 17 to 48 in every format: the calls that the line below lets
 // through take 0.55 to 1.02 of the time there.  16640 x 256 SQ at M = 24 9.4 -> 9.7, at 48 10.9 -> 15.4 (not taken); {k', r'} of the 7B
 // shapes fp16 SQ at M = 17 23.5 -> 15.2, 32 24.9 -> 17.3, 48 27.9 -> 22.0; of 14B-class shapes (six row tiles) fp16 SQ at 32
-// 29.3 -> 23.0, 6-bit VQ 28.4 -> 22.7.  bf16 beyond 32 rows has no registers for it.
+// 29.3 -> 23.0, 6-bit VQ 28.4 -> 22.7; bf16 SQ 18432 x 2048 at 33 18.5 -> 13.7, at 48 19.3 -> 15.5.
 static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
     const bool bf16 = x_dtype == DT_BF16;
-    if (n_mats > kGrid2DMaxMats || M <= 16 || M > (bf16 ? 32 : 48)) return 0;
+    if (n_mats > kGrid2DMaxMats || M <= 16 || M > 48) return 0;
     double row_tiles = 0.0, tiles = 0.0;
     for (int i = 0; i < n_mats; ++i) {
         if (bf16 && mats[i].fmt != FMT_SQ3) return 0;              // (see StageWide)
@@ -2123,7 +2173,7 @@ static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
     const int R = workgroups(4) <= 256 ? 0 : workgroups(5) <= 256 ? 5 : M <= 32 && workgroups(6) <= 256 ? 6 : 0;
     if (R == 0 || option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK) >= 1000000) return R;
     const double columns = tiles / row_tiles;                      // of the average row
-    const double most = R == 6 ? 12.0 + 5.0 * columns : bf16 ? 14.0 + 6.0 * columns : 16.0 + 8.0 * columns;
+    const double most = R == 6 ? 12.0 + 5.0 * columns : 16.0 + 8.0 * columns;
     return M <= most ? R : 0;
 }
 bool wide_cheaper(const MatDev* mats, int n_mats, int M, int x_dtype) { return wide_row_tiles(mats, n_mats, M, x_dtype) > 0; }
@@ -2142,7 +2192,7 @@ hipError_t launch_wide(const MatDev* mats, int n_mats, int M, int x_dtype, int y
     a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = (columns + turns - 1) / turns;
     const dim3 grid(longest, n_mats);
     const bool bf16 = x_dtype == DT_BF16;
-    if (M > 32) return launch_wide_kernel<5, 3, false>(a, grid, s);
+    if (M > 32) return bf16 ? launch_wide_kernel<5, 3, true>(a, grid, s) : launch_wide_kernel<5, 3, false>(a, grid, s);
     if (R == 5) return bf16 ? launch_wide_kernel<5, 2, true>(a, grid, s) : launch_wide_kernel<5, 2, false>(a, grid, s);
     return bf16 ? launch_wide_kernel<6, 2, true>(a, grid, s) : launch_wide_kernel<6, 2, false>(a, grid, s);
 }

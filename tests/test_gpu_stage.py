@@ -121,6 +121,42 @@ def test_column_split_of_more_rows(row_tiles, columns, M, xdt, options):
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
 
 
+# bf16 activations multiplied as they are by scalar-quantized matrices at 17 to 48 rows
+@pytest.mark.parametrize("row_tiles,columns", [(1025, 1), (1060, 9), (1252, 3), (1280, 17)])
+@pytest.mark.parametrize("M", [17, 33, 48])
+def test_column_split_of_more_rows_bf16(row_tiles, columns, M, options):
+    print(f"column split bf16 row tiles={row_tiles} columns={columns} M={M}", flush=True)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    options(B.OPT_STREAM_SPLIT_MAX_WORK, 1000000)
+    torch, rng = G.torch_(), np.random.default_rng(row_tiles + M)
+    mats = [synth.gen_sq(rng, 16 * (row_tiles - 3), 256 * columns), synth.gen_sq(rng, 48, 256 * max(1, columns // 2))]
+    xs = [synth.gen_activations(rng, M, m.K, "bf16") for m in mats]
+    dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
+    ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
+    B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.BF16, B.F32)
+    torch.cuda.synchronize()
+    for m, x, y in zip(mats, xs, ys):
+        got = y.cpu().numpy().astype(np.float64)
+        assert (got[M] == 7.0).all()
+        assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, "bf16"), "f64")) <= 2e-5   # as above
+
+
+# bf16 activations far from one, every format with one row tile per workgroup (as they are), two (8-bit VQ: converted) and three (VQ:
+# converted), through the column split and the streaming kernels (1: never the split)
+@pytest.mark.parametrize("scale", [1e-30, 1e30])
+@pytest.mark.parametrize("kind", ["sq", "vq6", "vq8"])
+@pytest.mark.parametrize("N,split", [(512, 0), (4352, 0), (8448, 0), (512, 1)])
+def test_bf16_far_from_one(N, split, kind, scale, options):
+    print(f"bf16 far from one N={N} {kind} scale={scale} split={split}", flush=True)
+    options(B.OPT_STREAM_SPLIT_MAX_WORK, split)
+    torch, rng, M = G.torch_(), np.random.default_rng(N), 5
+    m = synth.gen_sq(rng, N, 768) if kind == "sq" else synth.gen_vq(rng, N, 768, int(kind[2:]))
+    x = synth.f32_to_bf16_bits((rng.standard_normal((M, m.K)) * scale).astype(np.float32))
+    y = G.gpu_gemm(B.upload(m, native=True), x, "bf16")
+    # 768 products in binary32 partial sums, as above
+    assert G.err_g2(y / scale, orc.linear(m, orc.widen(x, "bf16"), "f64") / scale) <= 2e-5
+
+
 # The rule's two sides, bit for bit the kernel it is to take, and against the oracle: one round, always the column split (1536 row tiles are
 # the most that fit one); several rounds up to 3200 row tiles and M = 12, or 4 from nine column tiles on; rows of at most 512 columns
 # up to 4200 row tiles, 1536 beyond M = 8
@@ -148,7 +184,7 @@ def test_rule(N, columns, M, xdt, forced, options):
 # Both sides of the rule at 17 to 48 rows, five and six row tiles per workgroup.  Up to eight column tiles a wavefront takes one here and a
 # K group one there, and the partial sums are added in the same order, so the rule changes no bits: a call as the rule takes it, with the
 # column split wherever it fits, and its first 1024 rows alone (too small a call for it)
-@pytest.mark.parametrize("N,columns,M,xdt", [(16656, 2, 32, "f16"), (16656, 2, 33, "f16"), (16656, 2, 26, "bf16"), (16656, 2, 27, "bf16"),
+@pytest.mark.parametrize("N,columns,M,xdt", [(16656, 2, 32, "f16"), (16656, 2, 33, "f16"), (16656, 2, 32, "bf16"), (16656, 2, 33, "bf16"), (16656, 8, 48, "bf16"),
                                              (24560, 2, 22, "f16"), (24560, 2, 23, "f16"), (24560, 8, 32, "f16"), (16656, 8, 48, "f16")])
 def test_rule_of_more_rows(N, columns, M, xdt, options):
     print(f"rule N={N} columns={columns} M={M} x={xdt}", flush=True)
