@@ -6,6 +6,8 @@
 // must come out the same as from any other implementation of these steps.
 #include "common.h"
 
+#include <type_traits>
+
 #ifndef RWKVQ_SQ_ENCODE_PASSES
 #define RWKVQ_SQ_ENCODE_PASSES 1   // stretches of 32 groups per workgroup of the SQ encoder
 #endif
@@ -254,10 +256,35 @@ __device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const f
     }
 }
 
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true); }
+__device__ __forceinline__ float wave_sum(float v) {                // quad_perm [1, 0, 3, 2], [2, 3, 0, 1], row_half_mirror, row_mirror
+    v += __uint_as_float(dpp_move<0xB1>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_move<0x4E>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_move<0x141>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_move<0x140>(__float_as_uint(v)));
+    auto both = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+    both = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(both[0]) + __uint_as_float(both[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ void nearest_first(float& best, uint32_t& arg) {    // the lower index of equal ones
+    const float od = __uint_as_float(dpp_move<CTRL>(__float_as_uint(best)));
+    const uint32_t oe = dpp_move<CTRL>(arg);
+    if (od < best || (od == best && oe < arg)) { best = od; arg = oe; }
+}
+template <int CTRL>
+__device__ __forceinline__ void nearer(float& best, int& arg) {      // of two lanes, as one of the exchanges above pairs them
+    const float od = __uint_as_float(dpp_move<CTRL>(__float_as_uint(best)));
+    const int oe = (int)dpp_move<CTRL>((uint32_t)arg);
+    if (od < best) { best = od; arg = oe; }
+}
+
 // Nearest entries without comparing every pair with every entry.  A workgroup of 1024 threads takes a 256 x 256 block:
-//   1. the plane is cut into 32 x 32 cells over mean +- 3.25 standard deviations of the codebook's entries (those outside are
+//   1. the plane is cut into 32 x 32 cells (256 entries: 64 x 64) over mean +- 3.25 standard deviations of the codebook's entries (those outside are
 //      left out and the box is taken again, twice);
-//   2. one thread per cell lists the entries that can be nearest to a point of the cell: with r the entry nearest to the
+//   2. the entries that can be nearest to a point of a cell are listed: with r the entry nearest to the
 //      centre, at distance |r|, and h the distance from the centre to the cell's farthest point, an entry farther than
 //      |r| + 2 h from the centre is farther than r from every point of the cell, and so is one whose squared distance exceeds
 //      r's at all four corners (the difference is linear over the cell).  The cell is taken 10 % and the limits 1e-5 of the
@@ -265,36 +292,40 @@ __device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const f
 //      entry that wins by the definition's rounded distances is always listed, and so is every entry that ties with it;
 //   3. a pair is compared with its cell's entries in index order (strict comparison: the lowest index wins a tie); unused
 //      places of a list repeat its first entry, which never wins again;
-//   4. pairs outside the cells, or in a cell with more than 16 entries, are queued and compared with every entry: a few by
-//      sixteen lanes for four of them, more by a thread each.  Units of eight pairs that find the queue (a quarter of the block) full are
+//   4. pairs outside the cells, or in a cell with more than 16 entries (256: 8), are queued and compared with every entry: a few by
+//      sixteen lanes for four of them, more by a thread each.  Units of eight pairs that find the queue (a quarter of the block, with 256 entries three sixteenths) full are
 //      marked and done over with every entry;
 //   5. blocks for which the cells do not pay (weights far wider than the codebook, equal or crowded entries) compare every pair
 //      with every entry: when a fifth (6 bits) or a third (8 bits) of 128 sampled pairs is outside the cells, before the lists
 //      are made, or when a quarter of the first unit of every thread was queued, from there on (from the start, if half was).
 //      Four entries at a time, the smallest of them against the best, which one it was found out at the end: 6 instructions
 //      per pair and entry instead of 8.
-// Bound: vector ALU of step 2 (6 instructions per cell and entry, 12 more for those in reach) and the LDS look-ups of the 2 to 8 listed entries per
-// pair (a wavefront runs to its longest list).
-// Step 2 keeps the 8 x 8 cells of a wavefront together: entries out of reach of all of them are found by a lane each, the others are
-// tested without branches into a bit each, and a cell's list is written from its bits (a branch and a store per entry that some
-// cell wants took 28 us of a workgroup alone on its compute unit with 256 entries, now 10).  A few queued pairs (step 4) are taken
-// four at a time by sixteen lanes.
+// Bound: the chains of step 2 in the wavefronts of the middle, and the LDS look-ups of the 2 to 8 listed entries per pair (a wavefront
+// runs to its longest list, in fours).
+// Step 2 goes from 8 x 8 over 16 x 16 to 32 x 32 cells, sixteen lanes, four and one for a cell, a bit per entry: a cell tests only the
+// entries of the cell around it, whose lists hold them all by the same argument.  With 256 entries a thread goes on to the quarters of
+// its cell (32 entries at most): lists of sixteen places in 32 x 32 cells ran to all four fours, those of eight in 64 x 64 run to two, and
+// 366 pairs of a block are queued instead of 543.  With 64 entries the quarters cost what they save (4096 x 4096 50 -> 46 us, 1024 x 1024
+// 20 -> 25, 14336 x 4096 even).  Cycles of a workgroup alone on its compute unit, 256 entries, before -> now: lists 64000 -> 54000, a unit of
+// eight pairs per thread 20000 -> 12000, the queue 21000 -> 17000.  A few queued pairs (step 4) are taken four at a time by sixteen lanes.
 // Measured (bf16, near-normal weights, one in a thousand ten times as wide, one matrix repeated, us; every pair against every entry,
-// with lists built entry by entry, here): 4096 x 4096, 64 entries 77, 56, 55, 256 entries 279, 100, 89; 14336 x 4096, 256 entries 887,
-// 238, 220; 1024 x 1024, 256 entries 83, 53, 39; without the wide ones 53, 80 and 213, 43.  Without
+// with 32 x 32 cells that each looked through the entries near 8 x 8 of them, here): 4096 x 4096, 64 entries 77, 53, 50, 256 entries
+// 279, 81, 64; 14336 x 4096, 64 entries 128 -> 125, 256 entries 887, 218, 177; 1024 x 1024, 64 entries 22 -> 19.5, 256 entries 83, 42, 37.  Without
 // step 5 and the second form of step 4, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 186 and 502
-// (now 68 and 219), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the
+// (now 72 and 227), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the
 // entries zero 162 and 170 (70 and 122).  Registers: 64, for two workgroups on a compute unit (74: 14336 x 4096, 64 entries
 // 126 -> 172).
 template <int KBITS>
 __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
                                                          const uint16_t* __restrict__ codebooks,
                                                          uint32_t* __restrict__ indices, int parts_log2) {
-    constexpr int E = 1 << KBITS, G = 32, kSlots = 16, kQueue = 8192;
+    constexpr int E = 1 << KBITS, kQueue = KBITS == 6 ? 8192 : 6144;
+    constexpr bool kFine = KBITS == 8;                             // 64 x 64 cells of up to eight entries, else 32 x 32 of sixteen
+    constexpr int G = kFine ? 64 : 32, kSlots = kFine ? 8 : 16;
     constexpr int kFewQueued = KBITS == 6 ? 256 : 768;             // a thread per pair: 2 and 8 us whatever their number, four at a time 2 us per 256
     __shared__ __attribute__((aligned(16))) float2 entry[E];
     __shared__ __attribute__((aligned(16))) uint8_t list[G * G][kSlots];
-    __shared__ uint8_t listed[G * G];
+    __shared__ uint8_t listed[kFine ? 1 : G * G];
     __shared__ __attribute__((aligned(16))) uint8_t found[32768];
     __shared__ uint16_t queue[kQueue];
     __shared__ uint32_t over[128];                                 // units to be done over: a bit each
@@ -340,26 +371,24 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                 if (fabsf(dx) <= r0 && fabsf(dy) <= r1) { s[0] += dx; s[1] += dy; s[2] += dx * dx; s[3] += dy * dy; s[4] += 1.f; }
             }
 #pragma unroll
-            for (int off = 32; off; off >>= 1)
-#pragma unroll
-                for (int i = 0; i < 5; ++i) s[i] += __shfl_xor(s[i], off, 64);
+            for (int i = 0; i < 5; ++i) s[i] = wave_sum(s[i]);
             if (s[4] < 1.f) break;
             const float a0 = s[0] / s[4], a1 = s[1] / s[4];
             m0 += a0; m1 += a1;
             // no cell narrower than 6e-6 of its place (the resolution of binary32 there)
-            r0 = fmaxf(fmaxf(3.25f * sqrtf(fmaxf(s[2] / s[4] - a0 * a0, 0.f)), 1e-4f * fabsf(m0)), 1e-6f);
-            r1 = fmaxf(fmaxf(3.25f * sqrtf(fmaxf(s[3] / s[4] - a1 * a1, 0.f)), 1e-4f * fabsf(m1)), 1e-6f);
+            r0 = fmaxf(fmaxf(3.25f * sqrtf(fmaxf(s[2] / s[4] - a0 * a0, 0.f)), (kFine ? 2e-4f : 1e-4f) * fabsf(m0)), 1e-6f);
+            r1 = fmaxf(fmaxf(3.25f * sqrtf(fmaxf(s[3] / s[4] - a1 * a1, 0.f)), (kFine ? 2e-4f : 1e-4f) * fabsf(m1)), 1e-6f);
         }
         if (lane == 0) {
-            box[0] = m0 - r0; box[1] = m1 - r1; box[2] = G / (2.f * r0); box[3] = G / (2.f * r1);
-            box[4] = 0.55f * (2.f / G) * sqrtf(r0 * r0 + r1 * r1);
+            box[0] = m0 - r0; box[1] = m1 - r1; box[2] = 16.f / r0; box[3] = 16.f / r1;
+            box[4] = 0.55f * (1.f / 16.f) * sqrtf(r0 * r0 + r1 * r1);
         }
     }
     __syncthreads();
     auto uniform = [](float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); };   // a scalar register
     const float x0 = uniform(box[0]), y0 = uniform(box[1]), sx = uniform(box[2]), sy = uniform(box[3]);
     auto cell_of = [&](float vx, float vy) {                       // -1: outside
-        const float fx = (vx - x0) * sx, fy = (vy - y0) * sy;
+        const float fx = (vx - x0) * (sx * (G / 32)), fy = (vy - y0) * (sy * (G / 32));
         const bool in = fx >= 0.f && fx < (float)G && fy >= 0.f && fy < (float)G;
         return in ? (int)fy * G + (int)fx : -1;
     };
@@ -375,51 +404,200 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     int from = outside > (KBITS == 6 ? 24 : 40) ? 0 : 4096;         // units from here on: every pair with every entry
     int ahead = 0;                                                 // queued by the first units
     if (from) {
-        {   // the lists, one cell per thread, 8 x 8 cells per wavefront: a bit per entry first, and without branches
-            const int gx = 8 * (wave & 3) + (lane & 7), gy = 8 * (wave >> 2) + (lane >> 3), cell = gy * G + gx;
-            const float cx = x0 + ((float)gx + 0.5f) / sx, cy = y0 + ((float)gy + 0.5f) / sy;
-            const float hx = 1.1f / sx, hy = 1.1f / sy;              // twice 0.55 of a cell's sides
-            uint32_t nearest;
-            nearest_of_all<1>(entry, &cx, &cy, &nearest);
-            const float2 r = entry[nearest];
-            const float least = pair_distance(cx, cy, r.x, r.y);
-            const float reach = (sqrtf(least) + 2.f * box[4]) * 1.0001f, at_most = least + 1e-5f * (reach * reach);
-            // entries farther from the wavefront's centres than the longest reach are left out for all of them
-            float far = reach;
-#pragma unroll
-            for (int off = 32; off; off >>= 1) far = fmaxf(far, __shfl_xor(far, off, 64));
-            const float mx = x0 + (8.f * (wave & 3) + 4.f) / sx, my = y0 + (8.f * (wave >> 2) + 4.f) / sy, ax = 3.5f / sx, ay = 3.5f / sy;
-            uint32_t may[E / 32];
-            int n = 0, first = 0;
-#pragma unroll
-            for (int q = E / 64 - 1; q >= 0; --q) {
-                const float2 c = entry[64 * q + lane];
-                const float ox = fmaxf(fabsf(c.x - mx) - ax, 0.f), oy = fmaxf(fabsf(c.y - my) - ay, 0.f);
-                const unsigned long long near = __builtin_amdgcn_ballot_w64(!(ox * ox + oy * oy > far * far * 1.0001f));
-#pragma unroll
-                for (int half = 1; half >= 0; --half) {
-                    uint32_t bits = 0u;
+        // The lists, from the coarse to the fine: an entry that can be nearest to a point of a cell can be nearest to that point of the
+        // cell around it.  A bit per entry; the bits of the two coarse grids lie where the results will.
+        uint16_t* const coarse = (uint16_t*)found;                  // [8 x 8][E / 16]
+        uint16_t* const middle = coarse + 64 * (E / 16);            // [16 x 16][E / 16]
+        constexpr int kWords = E / 32;
+        // at most this far from the centre of a cell of 32 / g x 32 / g: the limit, and what every unit of distance from r adds
+        auto limits = [&](float g, float least, float& at_most, float& hx, float& hy) {
+            const float reach = (sqrtf(least) + 2.f * g * box[4]) * 1.0001f;
+            at_most = least + 1e-5f * (reach * reach);
+            hx = 1.1f * g / sx; hy = 1.1f * g / sy;                 // twice 0.55 of a cell's sides
+        };
+        // of the entries base + (bits of m): the nearest
+        auto nearest_of = [&](uint32_t m, int base, float cx, float cy, float& best, int& arg) {
 #pragma unroll 1
-                    for (uint32_t left = (uint32_t)(near >> (32 * half)); left; left &= left - 1u) {
-                        const int e = __builtin_ctz(left);
-                        const float2 o = entry[64 * q + 32 * half + e];
-                        const float d = pair_distance(cx, cy, o.x, o.y);
-                        bits |= d <= at_most + fabsf(r.x - o.x) * hx + fabsf(r.y - o.y) * hy ? 1u << e : 0u;
-                    }
-                    may[2 * q + half] = bits;
-                    n += __builtin_popcount(bits);
-                    if (bits) first = 64 * q + 32 * half + __builtin_ctz(bits);
-                }
+            for (; m; m &= m - 1u) {                                 // two at a time
+                const int e0 = base + __builtin_ctz(m);
+                m &= m - 1u;
+                const int e1 = m ? base + __builtin_ctz(m) : e0;
+                const float2 o0 = entry[e0], o1 = entry[e1];
+                const float d0 = pair_distance(cx, cy, o0.x, o0.y), d1 = pair_distance(cx, cy, o1.x, o1.y);
+                if (d0 < best) { best = d0; arg = e0; }
+                if (d1 < best) { best = d1; arg = e1; }
             }
-            const bool fits = n <= kSlots && n > 0;
-            listed[cell] = (uint8_t)(fits ? n : 255);
-            const uint32_t four = (uint32_t)first * 0x01010101u;
-            *(uint4_t*)list[cell] = uint4_t{four, four, four, four};
-            n = 0;
-            if (fits) {
+        };
+        auto within = [&](uint32_t m, int base, float cx, float cy, float2 r, float at_most, float hx, float hy) {
+            uint32_t bits = 0u;
+#pragma unroll 1
+            for (; m; m &= m - 1u) {
+                const int b0 = __builtin_ctz(m);
+                m &= m - 1u;
+                const int b1 = m ? __builtin_ctz(m) : b0;
+                const float2 o0 = entry[base + b0], o1 = entry[base + b1];
+                const float d0 = pair_distance(cx, cy, o0.x, o0.y), d1 = pair_distance(cx, cy, o1.x, o1.y);
+                bits |= d0 <= fmaf(fabsf(r.x - o0.x), hx, fmaf(fabsf(r.y - o0.y), hy, at_most)) ? 1u << b0 : 0u;
+                bits |= d1 <= fmaf(fabsf(r.x - o1.x), hx, fmaf(fabsf(r.y - o1.y), hy, at_most)) ? 1u << b1 : 0u;
+            }
+            return bits;
+        };
+        {   // 8 x 8 cells, sixteen lanes each
+            const int part = tid & 15, at = tid >> 4;
+            const float cx = x0 + (4.f * (float)(at & 7) + 2.f) / sx, cy = y0 + (4.f * (float)(at >> 3) + 2.f) / sy;
+            float best = __builtin_inff(), at_most, hx, hy;
+            int arg = part;
+#pragma unroll 4
+            for (int k = 0; k < E / 16; ++k) {
+                const float2 o = entry[16 * k + part];
+                const float d = pair_distance(cx, cy, o.x, o.y);
+                if (d < best) { best = d; arg = 16 * k + part; }
+            }
+            nearer<0xB1>(best, arg); nearer<0x4E>(best, arg); nearer<0x141>(best, arg); nearer<0x140>(best, arg);
+            limits(4.f, best, at_most, hx, hy);
+            const float2 r = entry[arg];
+            uint32_t mine = 0u;
+#pragma unroll 4
+            for (int k = 0; k < E / 16; ++k) {
+                const float2 o = entry[16 * k + part];
+                const float d = pair_distance(cx, cy, o.x, o.y);
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(d <= fmaf(fabsf(r.x - o.x), hx, fmaf(fabsf(r.y - o.y), hy, at_most)));
+                if (part == k) mine = (uint32_t)(m >> (lane & 48)) & 0xFFFFu;
+            }
+            if (part < E / 16) coarse[at * (E / 16) + part] = (uint16_t)mine;
+        }
+        __syncthreads();
+        {   // 16 x 16 cells, four lanes each
+            const int part = tid & 3, at = tid >> 2, gx = at & 15, gy = at >> 4;
+            const float cx = x0 + (2.f * (float)gx + 1.f) / sx, cy = y0 + (2.f * (float)gy + 1.f) / sy;
+            const uint16_t* const from_bits = coarse + (8 * (gy >> 1) + (gx >> 1)) * (E / 16) + part * (E / 64);
+            uint16_t* const to_bits = middle + at * (E / 16) + part * (E / 64);
+            constexpr int kOwn = E / 128 > 0 ? E / 128 : 1;          // words of a lane (64 entries: half a word)
+            uint32_t own[kOwn];
 #pragma unroll
-                for (int q = 0; q < E / 32; ++q)
-                    for (uint32_t m = may[q]; m; m &= m - 1u) list[cell][n++] = (uint8_t)(32 * q + __builtin_ctz(m));
+            for (int q = 0; q < kOwn; ++q) own[q] = E >= 128 ? ((const uint32_t*)from_bits)[q] : from_bits[0];
+            float best = __builtin_inff(), at_most, hx, hy;
+            int arg = 0;
+#pragma unroll
+            for (int q = 0; q < kOwn; ++q) nearest_of(own[q], part * (E / 4) + 32 * q, cx, cy, best, arg);
+            nearer<0xB1>(best, arg); nearer<0x4E>(best, arg);
+            limits(2.f, best, at_most, hx, hy);
+            const float2 r = entry[arg];
+#pragma unroll
+            for (int q = 0; q < kOwn; ++q) {
+                const uint32_t bits = within(own[q], part * (E / 4) + 32 * q, cx, cy, r, at_most, hx, hy);
+                if constexpr (E >= 128) ((uint32_t*)to_bits)[q] = bits;
+                else to_bits[0] = (uint16_t)bits;
+            }
+        }
+        __syncthreads();
+        {   // 32 x 32 cells, one per thread, 8 x 8 per wavefront; the four wavefronts in the middle, where the entries are, on four SIMDs
+            const int wy = wave >> 2, wx = (wave + (wy == 1 ? 1 : wy == 2 ? 3 : 0)) & 3;
+            const int gx = 8 * wx + (lane & 7), gy = 8 * wy + (lane >> 3);
+            const float cx = x0 + ((float)gx + 0.5f) / sx, cy = y0 + ((float)gy + 0.5f) / sy;
+            const uint32_t* const from_bits = (const uint32_t*)(middle + (16 * (gy >> 1) + (gx >> 1)) * (E / 16));
+            float best = __builtin_inff(), at_most, hx, hy;
+            int arg = 0;
+#pragma unroll
+            for (int q = 0; q < kWords; ++q) nearest_of(from_bits[q], 32 * q, cx, cy, best, arg);
+            limits(1.f, best, at_most, hx, hy);
+            const float2 r = entry[arg];
+            // The entries in order; a place is written until an entry keeps it.  Sixteen places of the cell itself, or, on the way to
+            // finer cells, 32 in those of its four quarters.
+            constexpr int kPlaces = kFine ? 32 : kSlots;
+            uint8_t* const places = kFine ? list[2 * gy * G + 2 * gx] : list[gy * G + gx];
+            auto place = [&](int i) { return places + (kFine && i >= 16 ? G * kSlots + i - 16 : i); };
+            int n = 0;
+#pragma unroll
+            for (int q = 0; q < kWords; ++q)
+#pragma unroll 1
+                for (uint32_t m = from_bits[q]; m; m &= m - 1u) {
+                    const int e0 = 32 * q + __builtin_ctz(m);
+                    m &= m - 1u;
+                    const bool two = m != 0u;
+                    const int e1 = two ? 32 * q + __builtin_ctz(m) : e0;
+                    const float2 o0 = entry[e0], o1 = entry[e1];
+                    const float d0 = pair_distance(cx, cy, o0.x, o0.y), d1 = pair_distance(cx, cy, o1.x, o1.y);
+                    if (n < kPlaces) *place(n) = (uint8_t)e0;
+                    n += d0 <= fmaf(fabsf(r.x - o0.x), hx, fmaf(fabsf(r.y - o0.y), hy, at_most)) ? 1 : 0;
+                    if (two && n < kPlaces) *place(n) = (uint8_t)e1;
+                    n += two && d1 <= fmaf(fabsf(r.x - o1.x), hx, fmaf(fabsf(r.y - o1.y), hy, at_most)) ? 1 : 0;
+                }
+            const bool fits = n > 0 && n <= kPlaces;
+            uint32_t word[kPlaces / 4];                              // unused places repeat the first entry
+            word[0] = *(const uint32_t*)places;
+            const uint32_t four = (word[0] & 255u) * 0x01010101u;
+#pragma unroll
+            for (int q = 0; q < kPlaces / 4; ++q) {
+                const int used = min(max(n - 4 * q, 0), 4);
+                const uint32_t mask = used == 4 ? 0xFFFFFFFFu : (1u << (8 * used)) - 1u;
+                word[q] = (*(const uint32_t*)place(4 * q) & mask) | (four & ~mask);
+            }
+            if constexpr (!kFine) {
+                listed[gy * G + gx] = (uint8_t)(fits ? n : 255);
+                *(uint4_t*)places = uint4_t{word[0], word[1], word[2], word[3]};
+            } else {
+                // The quarters: twice over the list, four distances each time; a bit per place.
+                const float qx[2] = {x0 + ((float)gx + 0.25f) / sx, x0 + ((float)gx + 0.75f) / sx};
+                const float qy[2] = {y0 + ((float)gy + 0.25f) / sy, y0 + ((float)gy + 0.75f) / sy};
+                const int entries = fits ? n : 0;
+                float least[4], ax, ay;
+                int near[4];
+                uint32_t bits[4];
+                auto each = [&](auto f) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        if (__builtin_amdgcn_ballot_w64(entries > 4 * q) == 0) break;
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const int e = (int)((word[q] >> (8 * b)) & 255u);
+                            const float2 o = entry[e];
+                            const float t0 = __fsub_rn(qx[0], o.x), t1 = __fsub_rn(qx[1], o.x), u0 = __fsub_rn(qy[0], o.y), u1 = __fsub_rn(qy[1], o.y);
+                            const float a0 = __fmul_rn(t0, t0), a1 = __fmul_rn(t1, t1), b0 = __fmul_rn(u0, u0), b1 = __fmul_rn(u1, u1);
+                            const float d[4] = {__fadd_rn(a0, b0), __fadd_rn(a1, b0), __fadd_rn(a0, b1), __fadd_rn(a1, b1)};
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) f(c, o, d[c], e, 4 * q + b);
+                        }
+                    }
+                };
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { least[c] = __builtin_inff(); near[c] = 0; bits[c] = 0u; }
+                each([&](int c, const float2&, float d, int e, int) { if (d < least[c]) { least[c] = d; near[c] = e; } });
+                float2 w[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float most;
+                    limits(0.5f, least[c], most, ax, ay);
+                    least[c] = most;
+                    w[c] = entry[near[c]];
+                }
+                each([&](int c, const float2& o, float d, int, int i) {
+                    bits[c] |= d <= fmaf(fabsf(w[c].x - o.x), ax, fmaf(fabsf(w[c].y - o.y), ay, least[c])) ? 1u << i : 0u;
+                });
+                uint2_t to[4];
+                const uint32_t real = entries == 32 ? 0xFFFFFFFFu : (1u << entries) - 1u;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {                        // a list that does not fit starts with 1 and 0
+                    uint32_t m = bits[c] & real;
+                    const int kept = __builtin_popcount(m);
+                    uint32_t out[2] = {0u, 0u}, first = 0u;
+                    if (kept > kSlots) m = 0u;
+#pragma unroll
+                    for (int j = 0; j < kSlots; ++j) {
+                        if (__builtin_amdgcn_ballot_w64(m != 0u) == 0) {
+                            if (j < 4) out[0] |= first * (0x01010101u << (8 * (j & 3)));
+                            out[1] |= j < 4 ? first * 0x01010101u : first * (0x01010101u << (8 * (j & 3)));
+                            break;
+                        }
+                        const uint32_t e = m ? *place(__builtin_ctz(m)) : first;
+                        if (j == 0) first = e;
+                        out[j >> 2] |= e << (8 * (j & 3));
+                        m &= m - 1u;
+                    }
+                    to[c] = kept > kSlots || kept == 0 ? uint2_t{1u, 0u} : uint2_t{out[0], out[1]};
+                }
+                *(uint4_t*)places = uint4_t{to[0].x, to[0].y, to[1].x, to[1].y};
+                *(uint4_t*)(places + G * kSlots) = uint4_t{to[2].x, to[2].y, to[3].x, to[3].y};
             }
         }
         __syncthreads();
@@ -436,29 +614,34 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
             load_unit(u, v0, v1);
 #pragma unroll
             for (int h = 0; h < 8; h += 4) {
-                uint4_t l[4];
+                std::conditional_t<kFine, uint2_t, uint4_t> l[4];
                 float best[4];
-                int longest = 0;
+                int longest = 0;                                   // fine: are there entries in places 4 .. 7?
                 bool again[4];
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     const int at = cell_of(v0[h + p], v1[h + p]), cell = max(at, 0);
-                    const int cnt = listed[cell];
-                    again[p] = at < 0 || cnt == 255;
-                    longest = max(longest, again[p] ? 0 : cnt);
-                    l[p] = *(const uint4_t*)list[cell];
+                    if constexpr (kFine) {
+                        l[p] = *(const uint2_t*)list[cell];
+                        again[p] = at < 0 || (l[p].x & 255u) > ((l[p].x >> 8) & 255u);
+                        longest |= again[p] || l[p].y == (l[p].x & 255u) * 0x01010101u ? 0 : 8;
+                    } else {
+                        const int cnt = listed[cell];
+                        l[p] = *(const uint4_t*)list[cell];
+                        again[p] = at < 0 || cnt == 255;
+                        longest = max(longest, again[p] ? 0 : cnt);
+                    }
                     best[p] = __builtin_inff();
                     arg[h + p] = 0u;
                 }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {                      // four places at a time, up to the longest list of the wavefront
-                    if (__builtin_amdgcn_ballot_w64(longest > 4 * q) == 0) break;
+                for (int q = 0; q < kSlots / 4; ++q) {             // four places at a time, up to the longest list of the wavefront
+                    if ((!kFine || q > 0) && __builtin_amdgcn_ballot_w64(longest > 4 * q) == 0) break;
 #pragma unroll
                     for (int b = 0; b < 4; ++b)
 #pragma unroll
                         for (int p = 0; p < 4; ++p) {
-                            const uint32_t word = q == 0 ? l[p].x : q == 1 ? l[p].y : q == 2 ? l[p].z : l[p].w;
-                            const uint32_t e = (word >> (8 * b)) & 255u;
+                            const uint32_t e = (l[p][q] >> (8 * b)) & 255u;
                             const float2 ce = entry[e];
                             const float d = pair_distance(v0[h + p], v1[h + p], ce.x, ce.y);
                             if (d < best[p]) { best[p] = d; arg[h + p] = e; }
@@ -514,23 +697,30 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                     bd[p] = __builtin_inff();
                     be[p] = 0xFFFFFFFFu;
                 }
-#pragma unroll 4
-                for (int k = 0; k < E / 16; ++k) {
-                    const float2 ce = entry[(tid & 15) + 16 * k];
+#pragma unroll 1
+                for (int k = 0; k < E / 64; ++k) {                 // four entries at a time, as in nearest_of_all
+                    float2 ce[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) ce[q] = entry[(tid & 15) + 16 * (4 * k + q)];
 #pragma unroll
                     for (int p = 0; p < 4; ++p) {
-                        const float d = pair_distance(vx[p], vy[p], ce.x, ce.y);
-                        if (d < bd[p]) { bd[p] = d; be[p] = (uint32_t)((tid & 15) + 16 * k); }
+                        const float least = min3f(min3f(pair_distance(vx[p], vy[p], ce[0].x, ce[0].y), pair_distance(vx[p], vy[p], ce[1].x, ce[1].y),
+                                                        pair_distance(vx[p], vy[p], ce[2].x, ce[2].y)),
+                                                  pair_distance(vx[p], vy[p], ce[3].x, ce[3].y), bd[p]);
+                        if (least < bd[p]) be[p] = (uint32_t)k;
+                        bd[p] = least;
                     }
                 }
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
+                    const int first = (tid & 15) + 64 * (bd[p] < __builtin_inff() ? (int)be[p] : 0);
+                    be[p] = 0xFFFFFFFFu;
 #pragma unroll
-                    for (int off = 8; off; off >>= 1) {
-                        const float od = __shfl_xor(bd[p], off, 64);
-                        const uint32_t oe = (uint32_t)__shfl_xor((int)be[p], off, 64);
-                        if (od < bd[p] || (od == bd[p] && oe < be[p])) { bd[p] = od; be[p] = oe; }
+                    for (int q = 3; q >= 0; --q) {
+                        const float2 c = entry[first + 16 * q];
+                        if (pair_distance(vx[p], vy[p], c.x, c.y) == bd[p] && bd[p] < __builtin_inff()) be[p] = (uint32_t)(first + 16 * q);
                     }
+                    nearest_first<0xB1>(bd[p], be[p]); nearest_first<0x4E>(bd[p], be[p]); nearest_first<0x141>(bd[p], be[p]); nearest_first<0x140>(bd[p], be[p]);
                     // (every distance infinite or NaN: entry 0; past the end the last pair again)
                     if ((tid & 15) == 0) found[id[p]] = (uint8_t)(be[p] == 0xFFFFFFFFu ? 0u : be[p]);
                 }

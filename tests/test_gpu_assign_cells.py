@@ -96,3 +96,24 @@ def test_vq_assign_many_pairs_beside_the_cells(kbits, wdt, rows):
     words = want.shape[1] // len(shares)
     for i, share in enumerate(shares):
         assert np.array_equal(got[:, words * i: words * (i + 1)], want[:, words * i: words * (i + 1)]), share
+
+
+@pytest.mark.parametrize("kbits", [6, 8])
+def test_vq_assign_lists_that_just_fit(kbits):
+    """As many entries in one place as a list holds and one more: eight of a fine cell, sixteen of a cell, 32 of a cell on its way to finer ones;
+    pairs on the place, around it and everywhere else."""
+    from paper_2505_03803_amd import binding as B
+    rng = np.random.default_rng(11)
+    En = 1 << kbits
+    counts = [7, 8, 9, 15, 16, 17, 31, 32, 33]
+    cb = rng.normal(0, 0.02, (len(counts), En, 2)).astype(np.float16)
+    wide = rng.normal(0, 0.02, (256, 256 * len(counts))).astype(np.float32)
+    for i, n in enumerate(counts):
+        at = rng.uniform(-0.02, 0.02, 2)
+        cb[i, rng.permutation(En)[:n]] = at + rng.uniform(-2e-4, 2e-4, (n, 2))
+        b = wide[:, 256 * i: 256 * (i + 1)].reshape(256, 128, 2)
+        b[::2] = at + rng.normal(0, 3e-4, b[::2].shape)
+        b[1::4] = at + rng.normal(0, 3e-3, b[1::4].shape)
+    bits = cb.view(np.uint16)[None]
+    got = B.vq_assign(dev(wide, "f32"), B.F32, dev(bits, "f16"), kbits).codes.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, E.vq_assign_packed(wide, bits, kbits))
