@@ -20,7 +20,11 @@
 // EXACT instances (17 <= M <= 128 where the streaming kernels' contract holds: weights unrounded, fp16 or bf16 x multiplied as it
 // is): NW = 1, 32 to 64 rows of x per workgroup, so a call that took ceil(M / 32) passes over W takes one (M <= 64).  SQ: codes as
 // 8 + q with the scale and zero point applied to the group's sums; VQ: the fp16 entries, for bf16 x as the sum of two bf16.
-// A workgroup takes 32 rows of W (NF = 2) where that gives at most one per compute unit, and 64 otherwise.
+// A workgroup takes 32 rows of W (NF = 2) where that gives at most one per compute unit, and 64 otherwise; 16 (NF = 1) where 32 would
+// leave half of the compute units without one: each then multiplies half as many rows by the x that it reads either way (36 bytes per
+// clock and compute unit, what bounds long rows beyond 32 rows of x).  Of 336 calls of one matrix of 1024 to 4096 rows none got more than
+// 1 % slower; us, 32 rows -> 16: 4096 x 4096 fp16 SQ at M = 17 8.5 -> 7.6, at 48 10.1 -> 9.0, at 64 12.3 -> 11.5; 4096 x 14336 6-bit VQ at 17
+// 19.4 -> 16.9, at 48 26.3 -> 25.8; 1024 x 14336 SQ at 128 31.7 -> 29.2; 2048 x 2048 8-bit VQ at 48 6.8 -> 5.8.
 // Measured (fp16, us; streaming kernels -> here): {r, k, v, g} of 4096 x 4096 at M = 32 21.3 -> 12.6, 48 34.8 -> 15.4, 64
 // 41 -> 17.6, 128 83 -> 31; bf16, 8-bit VQ: 4096 x 4096 at M = 17 10.1 -> 8.4 (64 rows: 11.7), 4096 x 14336 at 17 26.1 -> 18.2
 // (27.6), at 64 75 -> 26 (35); SQ: 61 -> 20 at 48 (28); {r, k, v, g} are 512 workgroups of 32 rows and slower in them (SQ, M = 48
@@ -468,10 +472,11 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
             for (int i = 0; i < NF; ++i) *(float4_t*)(lds + ((wave * PR + f) * NF + i) * 1024 + 16 * lane) = acc[PR * ps + f][i];
         __syncthreads();
         const int f = kg / SH, m = m0 + 16 * (PR * ps + f) + (EXACT ? 4 * (lane >> 4) : lane & 15);
-        if (PR * ps + f < MF && m < a.M) {
+        constexpr int OWN = NF / SH > 0 ? NF / SH : 1;             // (NF = 1: every second group has none)
+        if (PR * ps + f < MF && m < a.M && OWN * (kg % SH) < NF) {
 #pragma unroll
-            for (int ii = 0; ii < NF / SH; ++ii) {
-                const int i = ii + NF / SH * (kg % SH);
+            for (int ii = 0; ii < OWN; ++ii) {
+                const int i = ii + OWN * (kg % SH);
                 float4_t v = *(const float4_t*)(lds + ((nw * PR + f) * NF + i) * 1024 + 16 * lane);
 #pragma unroll
                 for (int g = 1; g < KW; ++g) {
@@ -511,6 +516,8 @@ static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
 template <bool BF16>
 static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, int nf, bool exact, int wgs, hipStream_t s) {
     if (exact) {
+        if (nf == 1) return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 1>(a, wgs, s)
+                            : mf == 3 ? launch_mid_t<BF16, 3, 1, true, 1>(a, wgs, s) : launch_mid_t<BF16, 4, 1, true, 1>(a, wgs, s);
         if (nf == 2) return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 2>(a, wgs, s)
                             : mf == 3 ? launch_mid_t<BF16, 3, 1, true, 2>(a, wgs, s) : launch_mid_t<BF16, 4, 1, true, 2>(a, wgs, s);
         return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 4>(a, wgs, s)
@@ -566,9 +573,9 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
             const int tiles = (M + 63) / 64;
             nw = 1;
             mf = std::max(2, ((M + tiles - 1) / tiles + 15) / 16);
-            long long narrow = 0;              // workgroups of 32 rows of W: up to one per compute unit they win
+            long long narrow = 0;              // workgroups of 32 rows of W: up to one per compute unit they win, up to half of that those of 16
             for (int i = 0; i < cnt; ++i) narrow += (long long)tiles * ((mats[base + i].N + 31) / 32);
-            if (narrow <= 256) nf = 2;
+            if (narrow <= 256) nf = narrow <= 128 ? 1 : 2;
         }
         else pick_mid(M, rows, &mf, &nw);
         a.m_tiles = (M + 16 * mf - 1) / (16 * mf);

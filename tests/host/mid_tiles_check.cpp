@@ -11,7 +11,7 @@ int main() {
     int bad = 0;
     unsigned long long checked = 0;
     const int columns[] = {256, 512, 2304, 14336, 20480};
-    for (int NF : {2, 4})
+    for (int NF : {1, 2, 4})
       for (int N = 16; N <= 640; N += 16)
         for (int K : columns)
             for (int tile_bytes : {1536, 2048, 128}) {      // codes (SQ and 6-bit indices, 8-bit indices), scales and zero points

@@ -123,6 +123,23 @@ def test_unrounded_weights(fmt, N, K, M, xdt, options):
     assert G.err_g2(got, orc.linear(mat, orc.widen(x, xdt), "f64")) <= 2e-5
 
 
+# Workgroups of 16, 32 and 64 rows of W: up to 128 of 32 rows, up to 256, more; scalar-quantized matrices with a last one partly past the end
+@pytest.mark.parametrize("fmt,N", [("sq", 4096), ("sq", 4112), ("sq", 4144), ("sq", 8192), ("sq", 8208), ("vq6", 4096), ("vq6", 4352), ("vq6", 8448),
+                                   ("vq8", 4096), ("vq8", 4352), ("vq8", 8448)])
+@pytest.mark.parametrize("M", [18, 47, 64])
+@pytest.mark.parametrize("xdt", ["bf16", "f16"])
+def test_unrounded_weights_by_rows_of_a_workgroup(fmt, N, M, xdt, options):
+    K = 2304
+    print(f"unrounded {fmt} N={N} M={M} x={xdt}", flush=True)
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    rng = np.random.default_rng(N)
+    m = synth.gen_sq(rng, N, K) if fmt == "sq" else synth.gen_vq(rng, N, K, int(fmt[2:]))
+    x = synth.gen_activations(rng, M, K, xdt)
+    y = G.gpu_gemm(B.upload(m, native=True), x, xdt)
+    # 2304 products in binary32 partial sums
+    assert G.err_g2(y, orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
 @pytest.mark.parametrize("fmt", ["sq", "vq6", "vq8"])
 @pytest.mark.parametrize("scale", [1e-20, 1e30, 1.5e38])
 def test_unrounded_weights_at_the_ends_of_bf16(fmt, scale, options):
