@@ -2118,6 +2118,22 @@ static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int 
     return split <= (3.0 + 0.021 * M + std::pow(std::pow(rows, 2.3) + std::pow(chain, 2.3), 1.0 / 2.3)) * by;
 }
 
+// A launch of one round with up to two row tiles per workgroup: the kernel of midbatch.hip that copies activations into LDS by itself, 64
+// columns in four steps ahead, instead of decode_stage_kernel, whose wavefronts have one or two column tiles of operands in flight?
+// It starts later (a launch of 4096 x 1024 takes 5 to 25 % longer) and wins as rows get longer and x wider.  Measured (us, there -> here)
+// on 120 matrices' shapes and formats at eight values of M, fp16 and bf16: 4096 x 14336 SQ at M = 2 11.5 -> 10.7, at 8 13.3 -> 11.5, at 16 18.3 ->
+// 13.3, 6-bit VQ in fp16 at 8 13.4 -> 11.8, at 16 17.9 -> 13.4, in bf16 at 4 12.5 -> 13.5, at 8 14.4 -> 13.7; 2048 x 5120 SQ at 16 9.0 -> 5.4;
+// 4096 x 4096 SQ at 8 5.5 -> 5.5, at 16 6.7 -> 5.9, 8-bit VQ at 16 7.1 -> 7.4; two row tiles: 5120 x 17920 SQ at 4 16.8 -> 16.6, at 16 24.0
+// -> 19.1, 8-bit VQ in fp16 at 12 21.6 -> 21.1; 8192 x 4096 at 16 4 to 11 % longer.
+static bool staged_cheaper(const MatDev* mats, const int* order, int n_mats, int M, const StageShape& p) {
+    if (p.kind != STAGE_ROUND || p.R > 2 || n_mats > kGrid2DMaxMats) return false;
+    int f = FMT_SQ3;
+    for (int i = 0; i < n_mats; ++i) f = std::max(f, mats[order[i]].fmt);
+    if (p.R == 2) return p.columns > 16 && M >= (f == FMT_SQ3 ? 6 : f == FMT_VQ6 ? 14 : 15);
+    if (p.columns > 16) return f == FMT_SQ3 || p.columns <= 28 || M > 6;
+    return p.columns > 8 && f != FMT_VQ8 && M >= (f == FMT_SQ3 ? 10 : 14);
+}
+
 template <int MATS>
 static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype, int y_dtype, const StageShape& p, hipStream_t s) {
     StageArgs<MATS> a;
@@ -2241,7 +2257,8 @@ hipError_t launch_decode(const MatDev* mats, int n_mats, int M, int x_dtype, int
         if (M > 1 && M <= 16) {
             const StageShape p = stage_shape(mats, order, cnt, M, x_dtype);
             if (stage_cheaper(mats, order, cnt, M, x_dtype, p)) {
-                const hipError_t e = cnt <= kGrid2DMaxMats ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s)
+                const hipError_t e = staged_cheaper(mats, order, cnt, M, p) ? launch_mid(mats + base, cnt, M, x_dtype, y_dtype, true, s)
+                                   : cnt <= kGrid2DMaxMats ? launch_stage<kGrid2DMaxMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s)
                                                            : launch_stage<kMaxGroupMats>(mats, order, cnt, M, x_dtype, y_dtype, p, s);
                 if (e != hipSuccess) return e;
                 continue;

@@ -1,4 +1,4 @@
-// Matrix-core path for 17 to about a thousand rows of x (prompts, chunks of them): y[M][N] = x[M][K] * Deq(W)^T with the
+// Matrix-core path for 17 to about a thousand rows of x (and, EXACT, for 2 to 16 of small launches of long rows) (prompts, chunks of them): y[M][N] = x[M][K] * Deq(W)^T with the
 // feed of prefill.hip (Deq(W) rounded once to the type of x, binary32 accumulate) in another cut.  prefill.hip gives a
 // workgroup 128 or 256 rows of x and 256 of W and all of K; with a few hundred rows of x a projection is then 16 to 48
 // workgroups on 256 compute units, each a chain of K / 64 steps.  Here
@@ -235,14 +235,18 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
         const int rr = m0 + row < a.M ? row : a.M - 1 - m0;
         xoff[i] = (uint32_t)rr * (uint32_t)K * 2u + 16u * c;
     }
-    const __amdgpu_buffer_rsrc_t xbuf = mid_buffer((const char*)mt.x + (size_t)m0 * K * 2, (uint32_t)std::min(a.M - m0, 16 * MF) * (uint32_t)K * 2u);
+    const char* const xrows = (const char*)mt.x + (size_t)m0 * K * 2;
+    const uint32_t xbytes = (uint32_t)std::min(a.M - m0, 16 * MF) * (uint32_t)K * 2u;
     // EXACT: N is any multiple of 16; row tiles past the end repeat the last one and are not stored
     const int tiles = EXACT ? mid_row_tiles(mt.N, R0, NF) : NF;
-    const __amdgpu_buffer_rsrc_t wbuf = mid_buffer(mt.codes + (size_t)R0 * KT * tw, (uint32_t)(tiles * KT * tw * 4));
-    const __amdgpu_buffer_rsrc_t abuf = SQ ? mid_buffer((const uint2_t*)mt.aux + (size_t)R0 * KT * 16, (uint32_t)(tiles * KT * 128))
-                                           : mid_buffer((const char*)mt.aux + (size_t)(R0 >> 4) * KT * kBook, (uint32_t)(KT * kBook));
+    const uint32_t wbytes = (uint32_t)(tiles * KT * tw * 4), abytes = SQ ? (uint32_t)(tiles * KT * 128) : (uint32_t)(KT * kBook);
+    const char* const words = (const char*)(mt.codes + (size_t)R0 * KT * tw);
+    const char* const aux = SQ ? (const char*)mt.aux + (size_t)R0 * KT * 128 : (const char*)mt.aux + (size_t)(R0 >> 4) * KT * kBook;
     const int last = 4 * nt - 1;
-    auto copy = [&](int step, int stage) {     // step = 4 j + KQ of this group's sequence; past its end the last one again
+    // Past the end of a group's sequence a load is still counted by the waits, but a buffer of no bytes makes it no request (the last
+    // step's 48 KB of x and the last tile's words again, as before, were a ninth and a third of what 4096 columns ask for).
+    auto copy = [&](int step, int stage) {     // step = 4 j + KQ of this group's sequence
+        const __amdgpu_buffer_rsrc_t xbuf = mid_buffer(xrows, step <= last ? xbytes : 0u);
         step = step < last ? step : last;
         const int at = 512 * (kg + KW * (step >> 2)) + kRowBytes * (step & 3);
         char* dst = ring + stage * kStage;
@@ -251,7 +255,8 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(dst + (NW * i + nw) * 1024), 16,
                                                      xoff[i], at, 0, 0);
     };
-    auto load = [&](MidRegs<FMT, NF>& r, int j) {  // past the last tile the last one again
+    auto load = [&](MidRegs<FMT, NF>& r, int j) {
+        const __amdgpu_buffer_rsrc_t wbuf = mid_buffer(words, j < nt ? wbytes : 0u), abuf = mid_buffer(aux, j < nt ? abytes : 0u);
         const int T = kg + KW * (j < nt ? j : nt - 1);
         const int at = 16 * lane;
 #pragma unroll
@@ -516,6 +521,7 @@ static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
 template <bool BF16>
 static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, int nf, bool exact, int wgs, hipStream_t s) {
     if (exact) {
+        if (mf == 1) return nf == 1 ? launch_mid_t<BF16, 1, 1, true, 1>(a, wgs, s) : launch_mid_t<BF16, 1, 1, true, 2>(a, wgs, s);
         if (nf == 1) return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 1>(a, wgs, s)
                             : mf == 3 ? launch_mid_t<BF16, 3, 1, true, 1>(a, wgs, s) : launch_mid_t<BF16, 4, 1, true, 1>(a, wgs, s);
         if (nf == 2) return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 2>(a, wgs, s)
@@ -572,7 +578,7 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
         if (exact) {                           // even rows over the fewest workgroups of at most 64
             const int tiles = (M + 63) / 64;
             nw = 1;
-            mf = std::max(2, ((M + tiles - 1) / tiles + 15) / 16);
+            mf = ((M + tiles - 1) / tiles + 15) / 16;
             long long narrow = 0;              // workgroups of 32 rows of W: up to one per compute unit they win, up to half of that those of 16
             for (int i = 0; i < cnt; ++i) narrow += (long long)tiles * ((mats[base + i].N + 31) / 32);
             if (narrow <= 256) nf = narrow <= 128 ? 1 : 2;

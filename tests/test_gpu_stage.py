@@ -82,6 +82,32 @@ def test_column_split_of_one_length(R, columns, M, xdt):
         assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5          # as above
 
 
+# One round with one or two row tiles per workgroup: both sides of the lines between operands straight from memory and activations copied
+# into LDS, by columns, M and format; the last workgroup of 32 rows half empty (4112), two matrices in one launch
+@pytest.mark.parametrize("N,columns,Ms", [(1024, 8, (16,)), (1024, 9, (9, 10, 13, 14)), (4096, 16, (9, 10, 13, 14)), (256, 17, (2, 16)),
+                                          (4096, 17, (2, 3)), (512, 28, (2, 6)), (512, 29, (6, 7)), (4112, 16, (16,)),
+                                          (4112, 17, (5, 6, 13, 14, 15)), (8192, 18, (6, 14, 15))])
+@pytest.mark.parametrize("kind", ["sq", "vq6", "vq8"])
+@pytest.mark.parametrize("xdt", ["f16", "bf16"])
+def test_activations_copied_or_not(N, columns, Ms, kind, xdt):
+    print(f"copied or not N={N} columns={columns} {kind} x={xdt}", flush=True)
+    torch, rng, K = G.torch_(), np.random.default_rng(N + columns), 256 * columns
+    first = N if kind == "sq" else max(256, N // 256 * 256)
+    mats = [synth.gen_sq(rng, first, K) if kind == "sq" else synth.gen_vq(rng, first, K, int(kind[2:]))]
+    if N == 512: mats.append(synth.gen_sq(rng, 48, K))
+    dms = [B.upload(m, native=True) for m in mats]
+    for M in Ms:
+        xs = [synth.gen_activations(rng, M, K, xdt) for _ in mats]
+        dev = [G.to_dev_bits(x) for x in xs]
+        ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
+        B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.DTYPES[xdt], B.F32)
+        torch.cuda.synchronize()
+        for m, x, y in zip(mats, xs, ys):
+            got = y.cpu().numpy().astype(np.float64)
+            assert (got[M] == 7.0).all()
+            assert G.err_g2(got[:M], orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5          # up to 7424 products, as above
+
+
 # An option of batch 1: batch 2 to 16 takes the same kernel with either value
 @pytest.mark.parametrize("M,xdt", [(2, "f16"), (8, "bf16"), (16, "f16")])
 @pytest.mark.parametrize("N,columns", [(1024, 4), (8192, 16), (4096, 30), (24576, 3)])
