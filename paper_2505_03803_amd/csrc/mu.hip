@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(256) clip_mean_select_kernel(const void* __res
 // B - k_hi at most kClipEnds): the distinct values are taken from either end, a minimum and a count over the position's 32 lanes per
 // step, instead of a count per bit.  A minimum above m without a compare: keys up to m wrap to the top in key - (m + 1).
 // What bounds it: start-up (2.5 us of a launch that moves nothing), the trips to memory, and the chain of B binary64 additions.
-// 4096 positions x 128 bf16 samples 8.5 -> 4.9 us, 5120 x 256 15.3 -> 10.5, 2560 x 64 5.7 -> 4.1.  The line: a step costs about as much
+// 4096 positions x 128 bf16 samples 8.5 -> 5.0 us, 5120 x 256 15.3 -> 10.9, 2560 x 64 5.7 -> 3.7.  The line: a step costs about as much
 // as two bits of the other way, which has 16 of them for 16-bit samples.
 constexpr int kClipEnds = 6, kClipLanes = 32, kClipThreads = kClipLanes * kClipP;
 __device__ __forceinline__ uint32_t lanes32_min(uint32_t v) {
@@ -180,24 +180,34 @@ __device__ __forceinline__ int lanes32_sum(int v) {
     const auto both = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
     return (int)both[0] + (int)both[1];
 }
-// The values of ranks k and k + 1 (k + 1 < B, or ignored) among the position's keys, the least first.
+// The values of ranks k and k + 1 (k + 1 < B, or ignored) among the position's keys, the least first, from two sets of keys side by side
+// (each step is a chain of exchanges between lanes; one set after the other: 128 x 4096 5.07 us, here 4.98, 256 x 5120 even, 200 x 3328
+// 7.07 and 6.91); steps past a set's need change nothing.
+struct Ranks { uint32_t m, before, at_k, at_k1; };           // m: the value taken last, before: keys up to it
 template <int NS>
-__device__ __forceinline__ void lowest(const uint32_t (&key)[NS], int k, int steps, uint32_t& at_k, uint32_t& at_k1) {
-    uint32_t m = 0xFFFFFFFFu;                        // the value taken last
-    int before = 0;                                  // keys up to it
+__device__ __forceinline__ void lowest(const uint32_t (&low)[NS], int k_low, Ranks& l, const uint32_t (&high)[NS], int k_high, Ranks& h, int steps) {
+    l = h = Ranks{0xFFFFFFFFu, 0u, 0u, 0u};
     for (int s = 0; s < steps; ++s) {
-        uint32_t d[NS], least = 0xFFFFFFFFu;
+        uint32_t dl[NS], dh[NS], least_l = 0xFFFFFFFFu, least_h = 0xFFFFFFFFu;
 #pragma unroll
-        for (int i = 0; i < NS; ++i) { d[i] = key[i] - (m + 1u); least = min(least, d[i]); }
-        least = lanes32_min(least);
-        int c = 0;
+        for (int i = 0; i < NS; ++i) {
+            dl[i] = low[i] - (l.m + 1u); least_l = min(least_l, dl[i]);
+            dh[i] = high[i] - (h.m + 1u); least_h = min(least_h, dh[i]);
+        }
+        least_l = lanes32_min(least_l);
+        least_h = lanes32_min(least_h);
+        int c = 0;                                   // both counts (up to 256 each) in one sum
 #pragma unroll
-        for (int i = 0; i < NS; ++i) c += d[i] == least ? 1 : 0;
+        for (int i = 0; i < NS; ++i) c += (dl[i] == least_l ? 1 : 0) + (dh[i] == least_h ? 0x10000 : 0);
         c = lanes32_sum(c);
-        m += least + 1u;
-        if (before <= k) at_k = m;
-        if (before <= k + 1) at_k1 = m;
-        before += c;
+        auto take = [](Ranks& r, uint32_t least, uint32_t count, int k) {
+            r.m += least + 1u;
+            if ((int)r.before <= k) r.at_k = r.m;
+            if ((int)r.before <= k + 1) r.at_k1 = r.m;
+            r.before += count;
+        };
+        take(l, least_l, (uint32_t)c & 0xFFFFu, k_low);
+        take(h, least_h, (uint32_t)c >> 16, k_high);
     }
 }
 template <int NS>
@@ -240,10 +250,11 @@ __global__ void __launch_bounds__(kClipThreads) clip_mean_ends_kernel(const void
         const uint32_t v = (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k & (dt == DT_F32 ? 0xFFFFFFFFu : 0xFFFF0000u);
         return dt == DT_F32 ? __uint_as_float(v) : dt == DT_BF16 ? __uint_as_float(v) : f16_bits_to_f32((uint16_t)(v >> 16));
     };
-    uint32_t lo = 0u, lo1 = 0u, hi = 0u, hi1 = 0u;
     const int from_top = B - 1 - k_hi;               // rank of the k_hi-th from above; the next one up is rank from_top - 1
-    lowest<NS>(low, k_lo, k_lo + 2, lo, lo1);
-    lowest<NS>(high, from_top - 1, from_top + 1, hi1, hi);
+    Ranks from_low, from_high;
+    lowest<NS>(low, k_lo, from_low, high, from_top - 1, from_high, max(k_lo + 2, from_top + 1));
+    const uint32_t lo = from_low.at_k, hi = from_high.at_k1;
+    uint32_t lo1 = from_low.at_k1, hi1 = from_high.at_k;
     if (k_lo + 1 >= B) lo1 = lo;
     if (from_top == 0) hi1 = hi;
     const double f_v = (double)value(lo), f_w = (double)value(~hi);
