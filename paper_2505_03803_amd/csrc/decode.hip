@@ -233,39 +233,6 @@ __device__ __forceinline__ void store_post_mix(const PostMixMat& mt, size_t i, i
     }
 }
 
-// Two 3-bit codes as a pair of 8 + q: fp16 with the codes at mantissa bits 7 .. 9 (mask 0x03800380, magic 0x48004800), or bf16 with them
-// at bits 4 .. 6 as 2^-12 (8 + q) (mask 0x00700070, magic 0x3B003B00), so that no group's sum overflows before the finite bf16 range of x ends.
-template <bool BF16, int P>
-__device__ __forceinline__ uint32_t sq_pair_code(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask,
-                                                 uint32_t magic) {
-    constexpr int at = BF16 ? 4 : 7;
-    if constexpr (P < 15) {
-        constexpr int p = P % 5, sh = at - 1 - 3 * p;
-        uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
-        uint32_t v = sh > 0 ? (w << (sh > 0 ? sh : 0)) : sh < 0 ? (w >> (sh < 0 ? -sh : 0)) : w;
-        return (v & mask) | magic;
-    } else {
-        // bit b of the pair's two codes sits at bits 0 and 16 of word b
-        uint32_t v = (w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2);
-        return (v << at) | magic;
-    }
-}
-// Its mask in a VGPR and magic in an SGPR: a VOP3 instruction of this ISA takes no literal and at most one scalar operand.
-template <bool BF16>
-__device__ __forceinline__ void sq_code_constants(uint32_t& mask, uint32_t& magic) {
-    asm("v_mov_b32 %0, %1" : "=v"(mask) : "n"(BF16 ? 0x00700070 : 0x03800380));
-    asm("s_mov_b32 %0, %1" : "=s"(magic) : "n"(BF16 ? 0x3B003B00 : 0x48004800));
-}
-template <bool BF16> constexpr uint32_t kSqOne = BF16 ? 0x39803980u : 0x3C003C00u;     // what sums the activations: 1, bf16 2^-12
-template <bool BF16> constexpr float kSqUnit = BF16 ? 4096.0f : 1.0f;
-
-template <bool BF16, int T>
-__device__ __forceinline__ uint4_t sq_operand(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask,
-                                              uint32_t magic) {
-    return uint4_t{sq_pair_code<BF16, 4 * T + 0>(w0, w1, w2, mask, magic), sq_pair_code<BF16, 4 * T + 1>(w0, w1, w2, mask, magic),
-                   sq_pair_code<BF16, 4 * T + 2>(w0, w1, w2, mask, magic), sq_pair_code<BF16, 4 * T + 3>(w0, w1, w2, mask, magic)};
-}
-
 __device__ __forceinline__ half8_t vq8_operand(uint32_t w, const uint32_t* cb) {
     uint4_t v = {cb[w & 255u], cb[(w >> 8) & 255u], cb[(w >> 16) & 255u], cb[w >> 24]};
     return __builtin_bit_cast(half8_t, v);
@@ -309,8 +276,6 @@ __device__ __forceinline__ void x_load_wg(XShared& r, const uint16_t* x, int M, 
 // sum exactly, whatever the magnitudes are; a smaller one is cut off below 2^-39 of that largest (the
 // conversion rounds toward zero, which only matters there), far below the resolution of the
 // binary32 sum it joins.
-typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
-
 // Larger of the two halves of max(|a|, |b|) taken per bf16 half: the magnitude bits of the largest of four values.
 __device__ __forceinline__ uint32_t bf16x2_absmax(uint32_t a, uint32_t b) {
     const ushort2_t m = __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a & 0x7FFF7FFFu),
@@ -330,20 +295,6 @@ __device__ __forceinline__ uint32_t dpp_row_max(uint32_t v) {
     v = dpp_max<0x141>(v);      // row_half_mirror
     return dpp_max<0x140>(v);   // row_mirror
 }
-// Exponent n of the scale 2^n for a group whose largest bf16 magnitude has the bits `amax`: the
-// largest lands in [2^15, 2^16).  An all-zero (or tiny) group takes the largest n whose inverse
-// 2^-n is still a normal binary32 number.
-__device__ __forceinline__ int bf16_scale_exponent(uint32_t amax) {
-    const int e = (int)(amax >> 7);                 // biased exponent, 0..254 for finite values
-    return 142 - (e > 16 ? e : 16);
-}
-// Two bf16 -> two fp16, each multiplied by 2^n first.  Exact where fp16 can hold the product.
-__device__ __forceinline__ uint32_t bf16x2_to_f16x2(uint32_t v, int n) {
-    const float lo = ldexpf(__builtin_bit_cast(float, v << 16), n);
-    const float hi = ldexpf(__builtin_bit_cast(float, v & 0xFFFF0000u), n);
-    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
-}
-
 // bf16: the threads that hold one batch row's 256 columns are one or two DPP rows of sixteen lanes; they agree
 // on the row's scale for this tile, convert, and the first of them leaves the inverse scale in xsc[row].
 template <int MT, bool CONVERT>
@@ -382,34 +333,6 @@ __device__ __forceinline__ void x_store_wg(const XShared& r, half_t* xs, float* 
 template <class T>
 __device__ __forceinline__ T stream_load(const T* p) { return __builtin_nontemporal_load(p); }
 
-// Batch 2..16, small launches (decode_stage_kernel): a wavefront takes its A operands straight from global memory in the
-// layout the MFMA wants - lane (m, kg) = (lane % 16, lane / 16) holds, for column half u and k-step t of a 256-column tile, the
-// eight consecutive activations 128 u + 32 t + 8 kg ... of batch row m (rows beyond M repeat row M - 1) - so nothing is staged
-// in LDS and no workgroup barrier is needed: f[4 u + t].
-struct XFrags { uint4_t f[8]; };
-// bf16 fragments -> fp16, scaled by the power of two of the batch row's largest magnitude in this tile (the four lanes
-// that hold a row agree through two exchanges); lane m < 16 leaves the row's inverse scale in scw[m].
-__device__ __forceinline__ void x_frags_to_f16(XFrags& r, float* scw, int lane) {
-    uint32_t amax = 0;
-    ushort2_t most = {0, 0};
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) most = __builtin_elementwise_max(most, __builtin_bit_cast(ushort2_t, r.f[i][j] & 0x7FFF7FFFu));
-    amax = max((uint32_t)most.x, (uint32_t)most.y);
-    auto both = __builtin_amdgcn_permlane16_swap(amax, amax, false, false);      // the other three lanes of the row
-    amax = max((uint32_t)both[0], (uint32_t)both[1]);
-    both = __builtin_amdgcn_permlane32_swap(amax, amax, false, false);
-    amax = max((uint32_t)both[0], (uint32_t)both[1]);
-    const int n = bf16_scale_exponent(amax);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        r.f[i].x = bf16x2_to_f16x2(r.f[i].x, n); r.f[i].y = bf16x2_to_f16x2(r.f[i].y, n);
-        r.f[i].z = bf16x2_to_f16x2(r.f[i].z, n); r.f[i].w = bf16x2_to_f16x2(r.f[i].w, n);
-    }
-    if (lane < 16) scw[lane] = ldexpf(1.0f, -n);
-}
-
 // v_dot2_f32_f16 on two packed fp16 pairs.
 __device__ __forceinline__ float dot2(uint32_t w, uint32_t x, float acc) {   // two fp16 pairs, scalars in
     return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, w), __builtin_bit_cast(half2_t, x), acc, false);
@@ -424,13 +347,6 @@ __device__ __forceinline__ float dpp_add(float v) {
 
 
 // ---- per-format tile loops ------------------------------------------------------------------
-
-#define RWKVQ_MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16((a), (b), (c), 0, 0, 0)
-template <bool BF16>
-__device__ __forceinline__ float4_t mfma_bits(uint4_t x, uint4_t w, float4_t c) {
-    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, w), c, 0, 0, 0);
-    else return RWKVQ_MFMA(__builtin_bit_cast(half8_t, x), __builtin_bit_cast(half8_t, w), c);
-}
 
 // Software pipeline over the column tiles T = 0 .. KT-1 with DEPTH tiles in flight from HBM
 // *while* a tile is being consumed: there is one register set more than the depth, and the load
@@ -541,14 +457,8 @@ __device__ __forceinline__ uint4_t vq6_gather4(uint32_t w0, uint32_t w1, uint32_
     return v;
 }
 
-// bf16 activations as they are: a codebook entry (two fp16) as the sum of two bf16 pairs (8 and 3 of the 11 bits, exact), multiplied in turn.
-// In LDS the two pairs of an entry stand side by side, eight bytes per entry.
+// bf16 activations as they are: the two bf16 pairs of a codebook entry (vq_split) stand side by side in LDS, eight bytes per entry.
 struct VqPair { uint4_t high, low; };
-__device__ __forceinline__ uint2_t vq_split(uint32_t e) {
-    const half2_t v = __builtin_bit_cast(half2_t, e);
-    const uint32_t h = Elem<true>::from_f16x2(e);
-    return uint2_t{h, Elem<true>::pack((float)v.x - __uint_as_float(h << 16), (float)v.y - __uint_as_float(h & 0xFFFF0000u))};
-}
 __device__ __forceinline__ uint2_t lds_gather2(uint32_t byte_addr) {
     return *(const __attribute__((address_space(3))) uint2_t*)(uintptr_t)byte_addr;
 }
@@ -671,7 +581,7 @@ __device__ __forceinline__ void run_sq(const DecodeMat& mt, const WavePos& wp, h
                     const uint4_t op0 = sq_operand<XB, 0>(w0, w1, w2, mask, magic), op1 = sq_operand<XB, 1>(w0, w1, w2, mask, magic),
                                   op2 = sq_operand<XB, 2>(w0, w1, w2, mask, magic), op3 = sq_operand<XB, 3>(w0, w1, w2, mask, magic);
                     const uint32_t szw = u == 0 ? r.sz[rt].x : r.sz[rt].y;
-                    const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)) * kSqUnit<XB>;
+                    const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu));
                     const float z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
@@ -1300,6 +1210,18 @@ __global__ void __launch_bounds__(64 * waves_of(MT), min_blocks(MT)) decode_kern
                 for (int rt = 0; rt < RT; ++rt) out[j][g][rt] = float4_t{0, 0, 0, 0};
         run_batched<MT, DEPTH, P>(mt, wp, xs, xsc, cb_all[wave], out);
         if (!live) return;
+        if (xbf16 && mt.fmt == FMT_SQ3 && __builtin_expect(any_infinite(reinterpret_cast<float4_t (&)[P * G * RT]>(out)), 0)) {
+#pragma unroll 1
+            for (int at = 0; at < P * G * RT; ++at) {              // (see sq_scaled_row_tile)
+                const int row_tile = wp.R[0] + RT * waves_of(MT) * (at / (G * RT)) + at % RT;
+                const float4_t v = sq_scaled_row_tile(mt, row_tile < NR ? row_tile : wp.R[0], 16 * (at / RT % G), M, 0, 1, lane);
+#pragma unroll
+                for (int j = 0; j < P * G * RT; ++j) {
+                    float4_t& o = out[j / (G * RT)][j / RT % G][j % RT];
+                    o = j == at ? if_infinite(o, v) : o;
+                }
+            }
+        }
         // D layout of the MFMA: lane (n, mg) holds batch rows 4 mg .. 4 mg + 3 (of its group) of output column n
 #pragma unroll
         for (int j = 0; j < P; ++j)
@@ -1423,7 +1345,7 @@ struct StageTiles {
         asm("v_mov_b32 %0, %1" : "=v"(m6) : "n"(kDirect ? 0x1f8 : 0xfc));
         base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
     }
-    // A column tile's activation fragments (see XFrags), a row tile's weights: together and in order (see tile_pipeline).  Past the
+    // A column tile's activation fragments (XFrags, straight from memory: nothing is staged for the workgroup, no barrier), a row tile's weights: together and in order (see tile_pipeline).  Past the
     // end (live = false) every lane asks for lane 0's bytes of a tile that was read already.
     __device__ __forceinline__ void load_x(XFrags& r, int T, bool live) {
         const uint16_t* p = (const uint16_t*)mt.x + 256 * T;
@@ -1480,7 +1402,7 @@ struct StageTiles {
                 const uint4_t op[4] = {sq_operand<kDirect, 0>(w0, w1, w2, mask, magic), sq_operand<kDirect, 1>(w0, w1, w2, mask, magic),
                                        sq_operand<kDirect, 2>(w0, w1, w2, mask, magic), sq_operand<kDirect, 3>(w0, w1, w2, mask, magic)};
                 const uint32_t szw = u == 0 ? r.b.z : r.b.w;
-                const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)) * kSqUnit<kDirect>;
+                const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu));
                 const float z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
                 float4_t sum = {0, 0, 0, 0};
 #pragma unroll
@@ -1525,7 +1447,10 @@ struct StageTiles {
         XFrags& x = xf[J];
         float4_t sc = {1, 1, 1, 1};
         if (kConvert) {
-            x_frags_to_f16(x, xsc, lane);
+            const int n = x_frags_exponent(x.f);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x.f[i] = x_frag_to_f16(x.f[i], n);
+            if (lane < 16) xsc[lane] = ldexpf(1.0f, -n);
             wave_lds_sync();
             sc = *(const float4_t*)(xsc + 4 * (lane >> 4));
         }
@@ -1614,14 +1539,17 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
     const int KT = mt.K >> 8;
     constexpr int kOwn = R > 2 ? 256 * R : 512;                    // words of LDS per wavefront
     uint32_t* mine = stage_lds + kOwn * wave;
+    bool infinite = false;                                         // (bf16, SQ: see sq_scaled_row_tile)
     float4_t out[R];
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) out[rt] = float4_t{0, 0, 0, 0};
     if (wave < KT && wave < S) {
         const int nt = (KT - wave + S - 1) / S;
         if (xdt == DT_BF16) {
-            if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            if (mt.fmt == FMT_SQ3) {
+                StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+                infinite = any_infinite(out);
+            } else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
             else StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
         } else {
             if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
@@ -1633,6 +1561,14 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
     if (wave < S) {
 #pragma unroll
         for (int rt = 0; rt < R; ++rt) *(float4_t*)(mine + 256 * rt + 4 * lane) = out[rt];
+    }
+    if (__builtin_expect(infinite, 0)) {
+        const int NR = mt.N >> 4;
+#pragma unroll 1
+        for (int rt = 0; rt < R; ++rt) {
+            float4_t* const sum = (float4_t*)(mine + 256 * rt + 4 * lane);
+            *sum = if_infinite(*sum, sq_scaled_row_tile(mt, R0 + rt < NR ? R0 + rt : NR - 1, 0, M, wave, S, lane));
+        }
     }
     __syncthreads();
     // D layout of the MFMA: lane (n, mg) holds batch rows 4 mg .. 4 mg + 3 of output column n
@@ -1749,7 +1685,7 @@ struct StageWide {
                 }
             }
             const uint32_t szw = U == 0 ? r.b.z : r.b.w;                      // (SQ)
-            const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)) * kSqUnit<XB>, z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
+            const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float4_t sum = {0, 0, 0, 0};
@@ -1813,6 +1749,16 @@ __global__ void __launch_bounds__(64 * kWideWaves) decode_stage_wide_kernel(Stag
     for (int rt = 0; rt < R; ++rt)
 #pragma unroll
         for (int g = 0; g < G; ++g) *(float4_t*)(mine + 256 * (G * rt + g) + 4 * lane) = out[rt][g];
+    if constexpr (XB)
+        if (__builtin_expect(any_infinite(reinterpret_cast<float4_t (&)[R * G]>(out)), 0)) {   // (see sq_scaled_row_tile)
+            const int NR = mt.N >> 4;
+#pragma unroll 1
+            for (int at = 0; at < R * G; ++at) {
+                float4_t* const sum = (float4_t*)(mine + 256 * at + 4 * lane);
+                const int row_tile = R0 + at / G;
+                *sum = if_infinite(*sum, sq_scaled_row_tile(mt, row_tile < NR ? row_tile : NR - 1, 16 * (at % G), M, wave, S, lane));
+            }
+        }
     __syncthreads();
     const float* sums = (const float*)stage_lds;
     for (int i = threadIdx.x; i < 16 * R * M; i += 64 * S) {

@@ -1,5 +1,5 @@
-// What the matrix-core kernels for large batches share: operand types, the decoding of packed words into operands
-// (Deq(W) of Sec. 2.2 rounded once to the type of x) and the layout of an activation tile in LDS.
+// What the matrix-core kernels share: operand types, the decoding of packed words into operands (Deq(W) of Sec. 2.2 rounded
+// once to the type of x, or unrounded codes and entries), bf16 activations under a scale and the layout of an activation tile in LDS.
 #pragma once
 #include "common.h"
 
@@ -160,5 +160,148 @@ __device__ __forceinline__ uint4_t vq8_chunk(uint32_t w, const uint32_t* cb) {
 
 // LDS byte offset, inside a tile, of logical 16-byte chunk c (0..7) of row `row`.
 __device__ __forceinline__ int tile_off(int row, int c) { return row * kRowBytes + ((c ^ (row & 7)) << 4); }
+
+// ---- unrounded weights (the streaming kernels' contract) ------------------------------------------------------------
+#define RWKVQ_MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16((a), (b), (c), 0, 0, 0)
+template <bool BF16>
+__device__ __forceinline__ float4_t mfma_bits(uint4_t x, uint4_t w, float4_t c) {
+    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, w), c, 0, 0, 0);
+    else return RWKVQ_MFMA(__builtin_bit_cast(half8_t, x), __builtin_bit_cast(half8_t, w), c);
+}
+
+// Two 3-bit codes as a pair of 8 + q, exact in either type: fp16 with the codes at mantissa bits 7 .. 9 (mask 0x03800380, magic
+// 0x48004800), bf16 at bits 4 .. 6 (0x00700070, 0x41004100).  y += s (acc - (8 + z) X) per group, X from an MFMA against ones.
+template <bool BF16, int P>
+__device__ __forceinline__ uint32_t sq_pair_code(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask, uint32_t magic) {
+    constexpr int at = BF16 ? 4 : 7;
+    if constexpr (P < 15) {
+        constexpr int p = P % 5, sh = at - 1 - 3 * p;
+        uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
+        uint32_t v = sh > 0 ? (w << (sh > 0 ? sh : 0)) : sh < 0 ? (w >> (sh < 0 ? -sh : 0)) : w;
+        return (v & mask) | magic;
+    } else {
+        // bit b of the pair's two codes sits at bits 0 and 16 of word b
+        uint32_t v = (w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2);
+        return (v << at) | magic;
+    }
+}
+// Its mask in a VGPR and magic in an SGPR: a VOP3 instruction of this ISA takes no literal and at most one scalar operand.
+template <bool BF16>
+__device__ __forceinline__ void sq_code_constants(uint32_t& mask, uint32_t& magic) {
+    asm("v_mov_b32 %0, %1" : "=v"(mask) : "n"(BF16 ? 0x00700070 : 0x03800380));
+    asm("s_mov_b32 %0, %1" : "=s"(magic) : "n"(BF16 ? 0x41004100 : 0x48004800));
+}
+template <bool BF16> constexpr uint32_t kSqOne = BF16 ? 0x3F803F80u : 0x3C003C00u;
+
+template <bool BF16, int T>
+__device__ __forceinline__ uint4_t sq_operand(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask, uint32_t magic) {
+    return uint4_t{sq_pair_code<BF16, 4 * T + 0>(w0, w1, w2, mask, magic), sq_pair_code<BF16, 4 * T + 1>(w0, w1, w2, mask, magic),
+                   sq_pair_code<BF16, 4 * T + 2>(w0, w1, w2, mask, magic), sq_pair_code<BF16, 4 * T + 3>(w0, w1, w2, mask, magic)};
+}
+
+// A codebook entry (two fp16) as the sum of two bf16 pairs (8 and 3 of the 11 bits, exact), which are multiplied in turn.
+__device__ __forceinline__ uint2_t vq_split(uint32_t e) {
+    const half2_t v = __builtin_bit_cast(half2_t, e);
+    const uint32_t h = Elem<true>::from_f16x2(e);
+    return uint2_t{h, Elem<true>::pack((float)v.x - __uint_as_float(h << 16), (float)v.y - __uint_as_float(h & 0xFFFF0000u))};
+}
+
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+
+// Exponent n of the scale 2^n for a group whose largest bf16 magnitude has the bits `amax`: the
+// largest lands in [2^15, 2^16).  An all-zero (or tiny) group takes the largest n whose inverse
+// 2^-n is still a normal binary32 number.
+__device__ __forceinline__ int bf16_scale_exponent(uint32_t amax) {
+    const int e = (int)(amax >> 7);                 // biased exponent, 0..254 for finite values
+    return 142 - (e > 16 ? e : 16);
+}
+// Two bf16 -> two fp16, each multiplied by 2^n first.  Exact where fp16 can hold the product.
+__device__ __forceinline__ uint32_t bf16x2_to_f16x2(uint32_t v, int n) {
+    const float lo = ldexpf(__builtin_bit_cast(float, v << 16), n);
+    const float hi = ldexpf(__builtin_bit_cast(float, v & 0xFFFF0000u), n);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
+}
+
+// A 256-column tile of sixteen rows of x as the MFMA's A operands, straight from memory: lane (m, kg) = (lane % 16, lane / 16) holds,
+// for column half u and k-step t, the eight consecutive activations 128 u + 32 t + 8 kg ... of row m in f[4 u + t].
+struct XFrags { uint4_t f[8]; };
+// COUNT bf16 fragments -> fp16: the exponent of the scale is that of the row's largest magnitude among them (the four lanes
+// that hold a row agree through two exchanges).
+template <int COUNT>
+__device__ __forceinline__ int x_frags_exponent(const uint4_t (&f)[COUNT]) {
+    uint32_t amax = 0;
+    ushort2_t most = {0, 0};
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) most = __builtin_elementwise_max(most, __builtin_bit_cast(ushort2_t, f[i][j] & 0x7FFF7FFFu));
+    amax = max((uint32_t)most.x, (uint32_t)most.y);
+    auto both = __builtin_amdgcn_permlane16_swap(amax, amax, false, false);      // the other three lanes of the row
+    amax = max((uint32_t)both[0], (uint32_t)both[1]);
+    both = __builtin_amdgcn_permlane32_swap(amax, amax, false, false);
+    return bf16_scale_exponent(max((uint32_t)both[0], (uint32_t)both[1]));
+}
+__device__ __forceinline__ uint4_t x_frag_to_f16(const uint4_t& f, int n) {
+    return uint4_t{bf16x2_to_f16x2(f.x, n), bf16x2_to_f16x2(f.y, n), bf16x2_to_f16x2(f.z, n), bf16x2_to_f16x2(f.w, n)};
+}
+
+// Sums of bf16 activations as they are that leave binary32.  x goes to 3.4e38, a group's sum is up to 2^7 times as large and (8 + z)
+// times that up to 2^16 times more (z is any fp16), where s times the difference may be any finite number.  Such a sum ends as an
+// infinity or a NaN, whatever follows; the wavefront then takes its column tiles again for the sixteen rows of W and of x, with x
+// brought into fp16 under exact power-of-two scales, and from there the elements that were not finite.  What is finite costs a test
+// per element at the end of the wavefront's work: 1218 calls at 2 to 48 rows of x took 0.997 of the time before in the median.
+// (The codes as 2^-12 (8 + q) kept a group's sums finite, not their products with 8 + z, and lost bits of activations below 2^-114.)
+//
+// Row tile `row_tile` of W (unpacked plainly: this is rare) times rows m0 .. m0 + 15 of x (those past M repeat row M - 1), column
+// tiles t0, t0 + ts, ..; D layout of the MFMA: lane (n, mg) holds rows 4 mg .. 4 mg + 3 of x for row n of W.
+template <class Mat>
+__device__ __forceinline__ float4_t sq_scaled_row_tile(const Mat& mt, int row_tile, int m0, int M, int t0, int ts, int lane) {
+    const int KT = mt.K >> 8, m = m0 + (lane & 15) < M ? m0 + (lane & 15) : M - 1;
+    const uint16_t* const xrow = (const uint16_t*)mt.x + (size_t)m * mt.K + 8 * (lane >> 4);
+    const uint32_t one = kSqOne<false>;
+    float4_t out = {0, 0, 0, 0};
+    // 32 columns at a time: no more in registers than the loops before this have room for
+#pragma unroll 1
+    for (int at = 8 * t0; at < 8 * KT; at += (at & 7) == 7 ? 8 * ts - 7 : 1) {
+        const int T = at >> 3, u = (at >> 2) & 1, k = at & 3;
+        const uint4_t x[1] = {*(const uint4_t*)(xrow + 32 * at)};
+        const uint32_t* const t = mt.codes + ((size_t)row_tile * KT + T) * 384;
+        const uint32_t* const a = t + 4 * lane;                                             // the lane's words: a[0] .. a[3], b[0], b[1]
+        const uint32_t* const b = t + 256 + 2 * lane;
+        const uint32_t w[3] = {u == 0 ? a[0] : a[3], u == 0 ? a[1] : b[0], u == 0 ? a[2] : b[1]};
+        uint32_t op[4];                                                                     // as sq_pair_code
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int P = 4 * k + i;
+            op[i] = P == 15 ? ((w[0] & 0x00010001u) << 7) | ((w[1] & 0x00010001u) << 8) | ((w[2] & 0x00010001u) << 9)
+                            : ((P < 5 ? w[0] : P < 10 ? w[1] : w[2]) >> (3 * (P % 5)) << 6) & 0x03800380u;
+            op[i] |= 0x48004800u;
+        }
+        const int n = x_frags_exponent(x);
+        const uint4_t f = x_frag_to_f16(x[0], n);
+        const float4_t zero = {0, 0, 0, 0};
+        const float4_t X = mfma_bits<false>(f, uint4_t{one, one, one, one}, zero), sum = mfma_bits<false>(f, uint4_t{op[0], op[1], op[2], op[3]}, zero);
+        const uint32_t szw = ((const uint32_t*)mt.aux)[(((size_t)row_tile * KT + T) * 16 + (lane & 15)) * 2 + u];
+        const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f, inverse = ldexpf(1.0f, -n);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = fmaf(s * __shfl(inverse, 4 * (lane >> 4) + i, 64), fmaf(-z8, X[i], sum[i]), out[i]);
+    }
+    return out;
+}
+// Is any of a wavefront's sums not finite?
+template <int COUNT>
+__device__ __forceinline__ bool any_infinite(const float4_t (&out)[COUNT]) {
+    float none = 0.0f;                             // 0, or NaN if one of them is not finite
+#pragma unroll
+    for (int j = 0; j < COUNT; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) none = fmaf(out[j][i], 0.0f, none);
+    return __builtin_amdgcn_ballot_w64(none == 0.0f) != __builtin_amdgcn_ballot_w64(true);
+}
+__device__ __forceinline__ float4_t if_infinite(float4_t v, const float4_t& again) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = fabsf(v[i]) < __builtin_inff() ? v[i] : again[i];
+    return v;
+}
 
 }  // namespace rwkvq

@@ -82,12 +82,6 @@ __device__ __forceinline__ void mid_wait() {
     static_assert(N >= 0 && N < 64, "six bits");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
 }
-template <bool BF16>
-__device__ __forceinline__ float4_t mid_mfma(uint4_t w, uint4_t x, float4_t c) {
-    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, x), c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, w), __builtin_bit_cast(half8_t, x), c, 0, 0, 0);
-}
-
 // Packed words of one 256-column tile for the wavefront's row tiles.
 template <int FMT, int NF> struct MidRegs;
 template <int NF> struct MidRegs<FMT_SQ3, NF> { uint4_t a[NF]; uint2_t b[NF]; uint2_t sz[NF]; };   // sz: (scale, zero) x 2 units
@@ -148,26 +142,13 @@ __device__ __forceinline__ bool mid_small_zero(const void* sz, int bytes, int ti
     return __builtin_amdgcn_readfirstlane(all) != 0;
 }
 
-// EXACT (weights enter unrounded, as in the streaming kernels): SQ codes as 8 + q, exact in either type - fp16 8.0 with the code
-// at mantissa bits 7..9, bf16 2^-9 with the code at bits 4..6, i.e. 2^-12 (8 + q), so that no group's sum overflows before
-// the finite bf16 range of x ends - and y += s (acc - (8 + z) X) per group, X from an MFMA against ones (2^-12 for bf16).
-template <bool BF16, int P>
-__device__ __forceinline__ uint32_t mid_sq_code(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t mask, uint32_t magic) {
-    constexpr int at = BF16 ? 4 : 7;
-    if constexpr (P < 15) {
-        constexpr int sh = at - 1 - 3 * (P % 5);
-        const uint32_t w = (P / 5 == 0) ? w0 : (P / 5 == 1) ? w1 : w2;
-        return ((sh > 0 ? w << (sh > 0 ? sh : 0) : sh < 0 ? w >> (sh < 0 ? -sh : 0) : w) & mask) | magic;
-    } else {                                   // bit b of the pair's two codes sits at bits 0 and 16 of word b
-        return (((w0 & 0x00010001u) | ((w1 & 0x00010001u) << 1) | ((w2 & 0x00010001u) << 2)) << at) | magic;
-    }
-}
+// EXACT (weights enter unrounded, as in the streaming kernels): pair p of step H as 8 + q
 template <bool BF16, int H, int NF>
 __device__ __forceinline__ uint32_t mid_code_pair(const MidRegs<FMT_SQ3, NF>& r, int i, int p, uint32_t mask, uint32_t magic) {
     constexpr int u = H >> 2, t = H & 3;
     const uint32_t w0 = u == 0 ? r.a[i].x : r.a[i].w, w1 = u == 0 ? r.a[i].y : r.b[i].x, w2 = u == 0 ? r.a[i].z : r.b[i].y;
-    return p == 0 ? mid_sq_code<BF16, 4 * t>(w0, w1, w2, mask, magic) : p == 1 ? mid_sq_code<BF16, 4 * t + 1>(w0, w1, w2, mask, magic)
-         : p == 2 ? mid_sq_code<BF16, 4 * t + 2>(w0, w1, w2, mask, magic) : mid_sq_code<BF16, 4 * t + 3>(w0, w1, w2, mask, magic);
+    return p == 0 ? sq_pair_code<BF16, 4 * t>(w0, w1, w2, mask, magic) : p == 1 ? sq_pair_code<BF16, 4 * t + 1>(w0, w1, w2, mask, magic)
+         : p == 2 ? sq_pair_code<BF16, 4 * t + 2>(w0, w1, w2, mask, magic) : sq_pair_code<BF16, 4 * t + 3>(w0, w1, w2, mask, magic);
 }
 // Index of weight pair p of step H, row tile i.
 template <int FMT, int H, int NF>
@@ -282,30 +263,24 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
     };
     constexpr int kLoads = SQ ? 3 * NF : 2 * NF + 1;
     constexpr bool SPLIT = EXACT && BF16 && !SQ;   // fp16 entries as the sum of two bf16 (8 + 3 of the 11 bits, exact), multiplied in turn
-    auto high = [](uint32_t e) { return Elem<true>::from_f16x2(e); };
-    auto low = [](uint32_t e) {
-        const half2_t v = __builtin_bit_cast(half2_t, e);
-        const uint32_t h = Elem<true>::from_f16x2(e);
-        return Elem<true>::pack((float)v.x - __uint_as_float(h << 16), (float)v.y - __uint_as_float(h & 0xFFFF0000u));
-    };
     auto stage_book = [&](const MidRegs<FMT, NF>& r, uint32_t* to) {   // VQ: the tile's codebook as it is multiplied
         if constexpr (FMT == FMT_VQ6) {
-            if constexpr (SPLIT) *(uint2_t*)(to + 2 * lane) = uint2_t{high(r.cb), low(r.cb)};
+            if constexpr (SPLIT) *(uint2_t*)(to + 2 * lane) = vq_split(r.cb);
             else to[lane] = Elem<BF16>::from_f16x2(r.cb);
         }
         if constexpr (FMT == FMT_VQ8) {
             const uint32_t c[4] = {r.cb8.x, r.cb8.y, r.cb8.z, r.cb8.w};
             if constexpr (SPLIT) {
-                *(uint4_t*)(to + 8 * lane) = uint4_t{high(c[0]), low(c[0]), high(c[1]), low(c[1])};
-                *(uint4_t*)(to + 8 * lane + 4) = uint4_t{high(c[2]), low(c[2]), high(c[3]), low(c[3])};
+                const uint2_t e0 = vq_split(c[0]), e1 = vq_split(c[1]), e2 = vq_split(c[2]), e3 = vq_split(c[3]);
+                *(uint4_t*)(to + 8 * lane) = uint4_t{e0.x, e0.y, e1.x, e1.y};
+                *(uint4_t*)(to + 8 * lane + 4) = uint4_t{e2.x, e2.y, e3.x, e3.y};
             } else {
                 *(uint4_t*)(to + 4 * lane) = uint4_t{Elem<BF16>::from_f16x2(c[0]), Elem<BF16>::from_f16x2(c[1]), Elem<BF16>::from_f16x2(c[2]), Elem<BF16>::from_f16x2(c[3])};
             }
         }
     };
     uint32_t mask, magic;                      // EXACT SQ: in registers (the and-or takes no literals)
-    asm("v_mov_b32 %0, %1" : "=v"(mask) : "n"(BF16 ? 0x00700070 : 0x03800380));
-    asm("s_mov_b32 %0, %1" : "=s"(magic) : "n"(BF16 ? 0x3B003B00 : 0x48004800));
+    sq_code_constants<BF16>(mask, magic);
 
     const int row = lane & 15, q = lane >> 4;
     uint32_t b[2][NF][4], bl[SPLIT ? 2 : 1][NF][4];            // operands of the two halves (32 columns) of a step; SPLIT: low parts
@@ -373,19 +348,19 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
                 const bool first = KQ % 2 == 0 && h == 0;
                 const float4_t zero = {0, 0, 0, 0};
 #pragma unroll
-                for (int i = 0; i < NF; ++i) part[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), first ? zero : part[fm][i]);
-                const uint32_t one = BF16 ? 0x39803980u : 0x3C003C00u;
-                X[fm] = mid_mfma<BF16>(af[f], uint4_t{one, one, one, one}, first ? zero : X[fm]);
+                for (int i = 0; i < NF; ++i) part[fm][i] = mfma_bits<BF16>(af[f], operand(b[h][i]), first ? zero : part[fm][i]);
+                const uint32_t one = kSqOne<BF16>;
+                X[fm] = mfma_bits<BF16>(af[f], uint4_t{one, one, one, one}, first ? zero : X[fm]);
             } else if constexpr (EXACT) {      // x first: a lane holds one row of W and four rows of x, as its scale and zero point are laid out
 #pragma unroll
-                for (int i = 0; i < NF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(b[h][i]), acc[fm][i]);
+                for (int i = 0; i < NF; ++i) acc[fm][i] = mfma_bits<BF16>(af[f], operand(b[h][i]), acc[fm][i]);
                 if constexpr (SPLIT) {
 #pragma unroll
-                    for (int i = 0; i < NF; ++i) acc[fm][i] = mid_mfma<BF16>(af[f], operand(bl[h][i]), acc[fm][i]);
+                    for (int i = 0; i < NF; ++i) acc[fm][i] = mfma_bits<BF16>(af[f], operand(bl[h][i]), acc[fm][i]);
                 }
             } else {
 #pragma unroll
-                for (int i = 0; i < NF; ++i) acc[fm][i] = mid_mfma<BF16>(operand(b[h][i]), af[f], acc[fm][i]);
+                for (int i = 0; i < NF; ++i) acc[fm][i] = mfma_bits<BF16>(operand(b[h][i]), af[f], acc[fm][i]);
             }
             const int n0 = 4 * NF * fm / MF, n1 = 4 * NF * (fm + 1) / MF;
             if (h == 0) pairs(std::integral_constant<int, 2 * KQ + 1>{}, 1, r0, n0, n1, book);
@@ -395,7 +370,7 @@ __device__ __forceinline__ void mid_loop(const MidArgs& a, const MidMat& mt, cha
                 if (KQ % 2 == 1 && h == 1) {
 #pragma unroll
                     for (int i = 0; i < NF; ++i) {
-                        const float s = f16_bits_to_f32((uint16_t)(szu[i] & 0xFFFFu)) * (BF16 ? 4096.0f : 1.0f), z8 = f16_bits_to_f32((uint16_t)(szu[i] >> 16)) + 8.0f;
+                        const float s = f16_bits_to_f32((uint16_t)(szu[i] & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szu[i] >> 16)) + 8.0f;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) acc[fm][i][e] = fmaf(s, fmaf(-z8, X[fm][e], part[fm][i][e]), acc[fm][i][e]);
                     }
@@ -447,6 +422,7 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     const int m0 = (local % a.m_tiles) * 16 * MF, n0 = (local / a.m_tiles) * (16 * NF * NW);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = wave % NW, kg = wave / NW;
+    bool infinite = false;                     // (EXACT, bf16, SQ: see sq_scaled_row_tile)
     float4_t acc[MF][NF];
 #pragma unroll
     for (int f = 0; f < MF; ++f)
@@ -457,6 +433,7 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
         if (!EXACT && mid_small_zero((const uint2_t*)mt.aux + (size_t)(n0 >> 4) * KT * 16, NF * NW * KT * 128, threadIdx.x, (uint32_t*)lds))
             mid_loop<BF16, FMT_SQ3, true, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
         else mid_loop<BF16, FMT_SQ3, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
+        if constexpr (EXACT && BF16) infinite = any_infinite(reinterpret_cast<float4_t (&)[MF * NF]>(acc));
     } else if (mt.fmt == FMT_VQ6) {
         mid_loop<BF16, FMT_VQ6, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
     } else {
@@ -475,6 +452,17 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
         for (int f = 0; f < PR && PR * ps + f < MF; ++f)
 #pragma unroll
             for (int i = 0; i < NF; ++i) *(float4_t*)(lds + ((wave * PR + f) * NF + i) * 1024 + 16 * lane) = acc[PR * ps + f][i];
+        if constexpr (EXACT && BF16) {
+            static_assert(!EXACT || MF <= PR, "one pass");
+            if (__builtin_expect(infinite, 0)) {
+                const int R0 = n0 >> 4, tiles = mid_row_tiles(mt.N, R0, NF);
+#pragma unroll 1
+                for (int at = 0; at < MF * NF; ++at) {
+                    float4_t* const sum = (float4_t*)(lds + (wave * PR * NF + at) * 1024 + 16 * lane);
+                    *sum = if_infinite(*sum, sq_scaled_row_tile(mt, R0 + mid_row_tile(at % NF, tiles), m0 + 16 * (at / NF), a.M, kg, KW, lane));
+                }
+            }
+        }
         __syncthreads();
         const int f = kg / SH, m = m0 + 16 * (PR * ps + f) + (EXACT ? 4 * (lane >> 4) : lane & 15);
         constexpr int OWN = NF / SH > 0 ? NF / SH : 1;             // (NF = 1: every second group has none)
