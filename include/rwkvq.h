@@ -158,8 +158,8 @@ int rwkvq_vq_dequant(const void* indices, const void* codebooks, int layout, int
  * streaming kernels at M = 1 and for vector-quantized matrices, brought into fp16's range group by group
  * with exact power-of-two scales - a group being the columns that share an accumulator, at most 256
  * consecutive ones of a row of x - so an activation enters its sum exactly unless it is more than 2^29
- * times smaller than the largest of its group, which is below the resolution of the binary32 sum; where scalar-quantized matrices
- * multiply them as they are and a sum leaves binary32 on the way, that sum is taken again in the second way); y is row-major fp16,
+ * times smaller than the largest of its group, which is below the resolution of the binary32 sum; where activations are
+ * multiplied as they are and a sum leaves binary32 on the way, that sum is taken again in the second way); y is row-major fp16,
  * bf16 or fp32; products are accumulated in binary32 and y is rounded to nearest even.  The path is chosen from M and the layout:
  *   canonical layout: a plain reference kernel (any M);
  *   native layout, M <= 16: streaming dequant-GEMV kernels bound by HBM bandwidth;

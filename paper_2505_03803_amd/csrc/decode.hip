@@ -1212,9 +1212,9 @@ __global__ void __launch_bounds__(64 * waves_of(MT), min_blocks(MT)) decode_kern
         if (!live) return;
         if (xbf16 && mt.fmt == FMT_SQ3 && __builtin_expect(any_infinite(reinterpret_cast<float4_t (&)[P * G * RT]>(out)), 0)) {
 #pragma unroll 1
-            for (int at = 0; at < P * G * RT; ++at) {              // (see sq_scaled_row_tile)
+            for (int at = 0; at < P * G * RT; ++at) {              // (see scaled_row_tile)
                 const int row_tile = wp.R[0] + RT * waves_of(MT) * (at / (G * RT)) + at % RT;
-                const float4_t v = sq_scaled_row_tile(mt, row_tile < NR ? row_tile : wp.R[0], 16 * (at / RT % G), M, 0, 1, lane);
+                const float4_t v = scaled_row_tile(mt, row_tile < NR ? row_tile : wp.R[0], 16 * (at / RT % G), M, 0, 1, lane);
 #pragma unroll
                 for (int j = 0; j < P * G * RT; ++j) {
                     float4_t& o = out[j / (G * RT)][j / RT % G][j % RT];
@@ -1539,18 +1539,17 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
     const int KT = mt.K >> 8;
     constexpr int kOwn = R > 2 ? 256 * R : 512;                    // words of LDS per wavefront
     uint32_t* mine = stage_lds + kOwn * wave;
-    bool infinite = false;                                         // (bf16, SQ: see sq_scaled_row_tile)
+    bool infinite = false;                                         // (bf16: see scaled_row_tile)
     float4_t out[R];
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) out[rt] = float4_t{0, 0, 0, 0};
     if (wave < KT && wave < S) {
         const int nt = (KT - wave + S - 1) / S;
         if (xdt == DT_BF16) {
-            if (mt.fmt == FMT_SQ3) {
-                StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-                infinite = any_infinite(out);
-            } else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
             else StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            infinite = any_infinite(out);
         } else {
             if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
             else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
@@ -1567,7 +1566,7 @@ __global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kerne
 #pragma unroll 1
         for (int rt = 0; rt < R; ++rt) {
             float4_t* const sum = (float4_t*)(mine + 256 * rt + 4 * lane);
-            *sum = if_infinite(*sum, sq_scaled_row_tile(mt, R0 + rt < NR ? R0 + rt : NR - 1, 0, M, wave, S, lane));
+            *sum = if_infinite(*sum, scaled_row_tile(mt, R0 + rt < NR ? R0 + rt : NR - 1, 0, M, wave, S, lane));
         }
     }
     __syncthreads();
@@ -1750,13 +1749,13 @@ __global__ void __launch_bounds__(64 * kWideWaves) decode_stage_wide_kernel(Stag
 #pragma unroll
         for (int g = 0; g < G; ++g) *(float4_t*)(mine + 256 * (G * rt + g) + 4 * lane) = out[rt][g];
     if constexpr (XB)
-        if (__builtin_expect(any_infinite(reinterpret_cast<float4_t (&)[R * G]>(out)), 0)) {   // (see sq_scaled_row_tile)
+        if (__builtin_expect(any_infinite(reinterpret_cast<float4_t (&)[R * G]>(out)), 0)) {   // (see scaled_row_tile)
             const int NR = mt.N >> 4;
 #pragma unroll 1
             for (int at = 0; at < R * G; ++at) {
                 float4_t* const sum = (float4_t*)(mine + 256 * at + 4 * lane);
                 const int row_tile = R0 + at / G;
-                *sum = if_infinite(*sum, sq_scaled_row_tile(mt, row_tile < NR ? row_tile : NR - 1, 16 * (at % G), M, wave, S, lane));
+                *sum = if_infinite(*sum, scaled_row_tile(mt, row_tile < NR ? row_tile : NR - 1, 16 * (at % G), M, wave, S, lane));
             }
         }
     __syncthreads();

@@ -246,7 +246,8 @@ __device__ __forceinline__ uint4_t x_frag_to_f16(const uint4_t& f, int n) {
 }
 
 // Sums of bf16 activations as they are that leave binary32.  x goes to 3.4e38, a group's sum is up to 2^7 times as large and (8 + z)
-// times that up to 2^16 times more (z is any fp16), where s times the difference may be any finite number.  Such a sum ends as an
+// times that up to 2^16 times more (z is any fp16), where s times the difference may be any finite number; the same with entries, whose
+// products may cancel; and an infinite entry is the sum of an infinity and a NaN.  Such a sum ends as an
 // infinity or a NaN, whatever follows; the wavefront then takes its column tiles again for the sixteen rows of W and of x, with x
 // brought into fp16 under exact power-of-two scales, and from there the elements that were not finite.  What is finite costs a test
 // per element at the end of the wavefront's work: 1218 calls at 2 to 48 rows of x took 0.997 of the time before in the median.
@@ -255,36 +256,61 @@ __device__ __forceinline__ uint4_t x_frag_to_f16(const uint4_t& f, int n) {
 // Row tile `row_tile` of W (unpacked plainly: this is rare) times rows m0 .. m0 + 15 of x (those past M repeat row M - 1), column
 // tiles t0, t0 + ts, ..; D layout of the MFMA: lane (n, mg) holds rows 4 mg .. 4 mg + 3 of x for row n of W.
 template <class Mat>
-__device__ __forceinline__ float4_t sq_scaled_row_tile(const Mat& mt, int row_tile, int m0, int M, int t0, int ts, int lane) {
+__device__ __forceinline__ float4_t scaled_row_tile(const Mat& mt, int row_tile, int m0, int M, int t0, int ts, int lane) {
     const int KT = mt.K >> 8, m = m0 + (lane & 15) < M ? m0 + (lane & 15) : M - 1;
     const uint16_t* const xrow = (const uint16_t*)mt.x + (size_t)m * mt.K + 8 * (lane >> 4);
     const uint32_t one = kSqOne<false>;
     float4_t out = {0, 0, 0, 0};
     // 32 columns at a time: no more in registers than the loops before this have room for
 #pragma unroll 1
-    for (int at = 8 * t0; at < 8 * KT; at += (at & 7) == 7 ? 8 * ts - 7 : 1) {
-        const int T = at >> 3, u = (at >> 2) & 1, k = at & 3;
-        const uint4_t x[1] = {*(const uint4_t*)(xrow + 32 * at)};
-        const uint32_t* const t = mt.codes + ((size_t)row_tile * KT + T) * 384;
+    for (int T = t0; T < KT; T += ts) {
+        int n = 142;                                                                        // the tile's scale: the least of the eight
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+            const uint4_t x[1] = {*(const uint4_t*)(xrow + 256 * T + 32 * i)};
+            n = min(n, x_frags_exponent(x));
+        }
+        const uint32_t* const t = mt.codes + ((size_t)row_tile * KT + T) * (mt.fmt == FMT_VQ8 ? 512 : 384);
         const uint32_t* const a = t + 4 * lane;                                             // the lane's words: a[0] .. a[3], b[0], b[1]
         const uint32_t* const b = t + 256 + 2 * lane;
-        const uint32_t w[3] = {u == 0 ? a[0] : a[3], u == 0 ? a[1] : b[0], u == 0 ? a[2] : b[1]};
-        uint32_t op[4];                                                                     // as sq_pair_code
+        const uint32_t* const book = (const uint32_t*)mt.aux + ((size_t)(row_tile >> 4) * KT + T) * (mt.fmt == FMT_VQ8 ? 256 : 64);
+        float4_t part = {0, 0, 0, 0};
+#pragma unroll 1
+        for (int at = 0; at < 8; ++at) {
+            const int u = at >> 2, k = at & 3;
+            uint32_t op[4];
+            if (mt.fmt == FMT_VQ8) {
+                const uint32_t w = a[256 * u + k];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int P = 4 * k + i;
-            op[i] = P == 15 ? ((w[0] & 0x00010001u) << 7) | ((w[1] & 0x00010001u) << 8) | ((w[2] & 0x00010001u) << 9)
-                            : ((P < 5 ? w[0] : P < 10 ? w[1] : w[2]) >> (3 * (P % 5)) << 6) & 0x03800380u;
-            op[i] |= 0x48004800u;
+                for (int i = 0; i < 4; ++i) op[i] = book[(w >> (8 * i)) & 255u];
+            } else {
+                const uint32_t w[3] = {u == 0 ? a[0] : a[3], u == 0 ? a[1] : b[0], u == 0 ? a[2] : b[1]};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {                                               // as vq6_byteaddr and sq_pair_code
+                    const int P = 4 * k + i;
+                    const uint32_t word = P < 5 ? w[0] : P < 10 ? w[1] : w[2];
+                    const uint32_t index = P == 15 ? (w[0] & 3u) | (w[1] & 3u) << 2 | (w[2] & 3u) << 4 : word >> (6 * (P % 5) + 2) & 63u;
+                    const uint32_t codes = P == 15 ? ((w[0] & 0x00010001u) | (w[1] & 0x00010001u) << 1 | (w[2] & 0x00010001u) << 2) << 7
+                                                   : word >> (3 * (P % 5)) << 6 & 0x03800380u;
+                    op[i] = mt.fmt == FMT_SQ3 ? codes | 0x48004800u : book[index];
+                }
+            }
+            const uint4_t f = x_frag_to_f16(*(const uint4_t*)(xrow + 256 * T + 32 * at), n);
+            const float4_t zero = {0, 0, 0, 0};
+            const float4_t sum = mfma_bits<false>(f, uint4_t{op[0], op[1], op[2], op[3]}, mt.fmt == FMT_SQ3 ? zero : part);
+            if (mt.fmt == FMT_SQ3) {
+                const float4_t X = mfma_bits<false>(f, uint4_t{one, one, one, one}, zero);
+                const uint32_t szw = ((const uint32_t*)mt.aux)[(((size_t)row_tile * KT + T) * 16 + (lane & 15)) * 2 + u];
+                const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) part[i] = fmaf(s, fmaf(-z8, X[i], sum[i]), part[i]);
+            } else {
+                part = sum;
+            }
         }
-        const int n = x_frags_exponent(x);
-        const uint4_t f = x_frag_to_f16(x[0], n);
-        const float4_t zero = {0, 0, 0, 0};
-        const float4_t X = mfma_bits<false>(f, uint4_t{one, one, one, one}, zero), sum = mfma_bits<false>(f, uint4_t{op[0], op[1], op[2], op[3]}, zero);
-        const uint32_t szw = ((const uint32_t*)mt.aux)[(((size_t)row_tile * KT + T) * 16 + (lane & 15)) * 2 + u];
-        const float s = f16_bits_to_f32((uint16_t)(szw & 0xFFFFu)), z8 = f16_bits_to_f32((uint16_t)(szw >> 16)) + 8.0f, inverse = ldexpf(1.0f, -n);
+        const float inverse = ldexpf(1.0f, -n);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) out[i] = fmaf(s * __shfl(inverse, 4 * (lane >> 4) + i, 64), fmaf(-z8, X[i], sum[i]), out[i]);
+        for (int i = 0; i < 4; ++i) out[i] = fmaf(part[i], __shfl(inverse, 4 * (lane >> 4) + i, 64), out[i]);
     }
     return out;
 }

@@ -422,7 +422,6 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
     const int m0 = (local % a.m_tiles) * 16 * MF, n0 = (local / a.m_tiles) * (16 * NF * NW);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = wave % NW, kg = wave / NW;
-    bool infinite = false;                     // (EXACT, bf16, SQ: see sq_scaled_row_tile)
     float4_t acc[MF][NF];
 #pragma unroll
     for (int f = 0; f < MF; ++f)
@@ -433,7 +432,6 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
         if (!EXACT && mid_small_zero((const uint2_t*)mt.aux + (size_t)(n0 >> 4) * KT * 16, NF * NW * KT * 128, threadIdx.x, (uint32_t*)lds))
             mid_loop<BF16, FMT_SQ3, true, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
         else mid_loop<BF16, FMT_SQ3, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
-        if constexpr (EXACT && BF16) infinite = any_infinite(reinterpret_cast<float4_t (&)[MF * NF]>(acc));
     } else if (mt.fmt == FMT_VQ6) {
         mid_loop<BF16, FMT_VQ6, false, MF, NW, EXACT, NF>(a, mt, lds, m0, n0, wave, lane, acc);
     } else {
@@ -454,12 +452,12 @@ __global__ void __launch_bounds__(64 * kMidWaves, 2) mid_kernel(MidArgs a) {
             for (int i = 0; i < NF; ++i) *(float4_t*)(lds + ((wave * PR + f) * NF + i) * 1024 + 16 * lane) = acc[PR * ps + f][i];
         if constexpr (EXACT && BF16) {
             static_assert(!EXACT || MF <= PR, "one pass");
-            if (__builtin_expect(infinite, 0)) {
+            if (__builtin_expect(any_infinite(reinterpret_cast<float4_t (&)[MF * NF]>(acc)), 0)) {      // (see scaled_row_tile)
                 const int R0 = n0 >> 4, tiles = mid_row_tiles(mt.N, R0, NF);
 #pragma unroll 1
                 for (int at = 0; at < MF * NF; ++at) {
                     float4_t* const sum = (float4_t*)(lds + (wave * PR * NF + at) * 1024 + 16 * lane);
-                    *sum = if_infinite(*sum, sq_scaled_row_tile(mt, R0 + mid_row_tile(at % NF, tiles), m0 + 16 * (at / NF), a.M, kg, KW, lane));
+                    *sum = if_infinite(*sum, scaled_row_tile(mt, R0 + mid_row_tile(at % NF, tiles), m0 + 16 * (at / NF), a.M, kg, KW, lane));
                 }
             }
         }

@@ -62,3 +62,42 @@ def test_sq_smallest_activations(N, columns, M, split, options):
     y = G.gpu_gemm(B.upload(mat, native=True), x, "bf16")
     # as above; 3e-39 is 2^21 times the smallest binary32 number, and 768 to 4352 products have weights of about 60
     rows_match(y, mat, x, 2e-5)
+
+
+VQ_ROUTES = [(N if N % 256 == 0 else 16640, c, M, s) for N, c, M, s in ROUTES]
+
+
+# Products of a row of x that cancel, beyond 2^128 on the way: a tile's first 128 columns of one sign, the others of the other
+@pytest.mark.parametrize("N,columns,M,split", VQ_ROUTES)
+@pytest.mark.parametrize("kbits", [6, 8])
+def test_vq_sums_that_come_back(N, columns, M, split, kbits, options):
+    print(f"sums that come back N={N} columns={columns} M={M} split={split} kbits={kbits}", flush=True)
+    route(options, split)
+    rng, K = np.random.default_rng(N + M), 256 * columns
+    mat = synth.gen_vq(rng, N, K, kbits)
+    mat.codebooks = synth.f32_to_f16_bits(rng.uniform(8.0, 9.0, mat.codebooks.shape))
+    scale = np.array([2e36 / np.sqrt(columns), 1.0, 1e35, 1e-30])[np.arange(M) % 4]
+    sign = np.where(np.arange(K) % 256 < 128, 1.0, -1.0)
+    x = synth.f32_to_bf16_bits((scale[:, None] * sign * rng.uniform(0.8, 1.2, (M, K))).astype(np.float32))
+    y = G.gpu_gemm(B.upload(mat, native=True), x, "bf16")
+    # eight roundings in a tile of partial sums up to 128 * 8.5 scale, 8 * 2^-24 * 1088 scale at most, next to a y that differs from
+    # row to row of W by 0.29 scale sqrt(256) per tile (0.29: the deviation of the entries): 1.1e-4
+    rows_match(y, mat, x, 2e-4)
+
+
+# An entry that is infinite makes the sums it is in infinite, as with fp16 activations and at one row of x, and no other
+@pytest.mark.parametrize("N,columns,M,split", VQ_ROUTES)
+@pytest.mark.parametrize("kbits", [6, 8])
+def test_vq_infinite_entry(N, columns, M, split, kbits, options):
+    print(f"infinite entry N={N} columns={columns} M={M} split={split} kbits={kbits}", flush=True)
+    route(options, split)
+    rng, K = np.random.default_rng(N + M), 256 * columns
+    mat = synth.gen_vq(rng, N, K, kbits)
+    mat.codebooks[0, 0, 5, 1] = 0x7C00
+    x = synth.f32_to_bf16_bits(rng.uniform(0.5, 1.5, (M, K)).astype(np.float32))
+    y = G.gpu_gemm(B.upload(mat, native=True), x, "bf16")
+    with np.errstate(invalid="ignore"):
+        ref = orc.linear(mat, orc.widen(x, "bf16"), "f64")
+    assert np.isposinf(ref).any() and not np.isnan(ref).any()
+    assert np.array_equal(np.isposinf(y), np.isposinf(ref)) and not np.isnan(y).any()
+    assert G.err_g2(np.where(np.isinf(y), 0.0, y), np.where(np.isinf(ref), 0.0, ref)) <= 2e-5
