@@ -226,7 +226,8 @@ __device__ __forceinline__ float pair_distance(float v0, float v1, float c0, flo
 }
 
 // Index of the nearest of all E entries for each of P pairs (step 5 below): equal distances resolve to the lowest index, an
-// infinite or NaN distance to every entry gives 0.
+// infinite or NaN distance to every entry gives 0.  Eight entries' loads in front of eight entries' arithmetic, nothing moved between:
+// 4096 x 4096 weights against 256 entries 225 -> 210 us, 64 entries 70 -> 66.
 template <int P, int E>
 __device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const float* v0, const float* v1, uint32_t* arg) {
     float best[P];
@@ -235,6 +236,7 @@ __device__ __forceinline__ void nearest_of_all(const float2 (&entry)[E], const f
 #pragma unroll 2
     for (int e = 0; e < E; e += 4) {
         const float4_t a = *(const float4_t*)&entry[e], b = *(const float4_t*)&entry[e + 2];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const float least = min3f(min3f(pair_distance(v0[p], v1[p], a.x, a.y), pair_distance(v0[p], v1[p], a.z, a.w),
@@ -282,20 +284,21 @@ __device__ __forceinline__ void nearer(float& best, int& arg) {      // of two l
 }
 
 // Nearest entries without comparing every pair with every entry.  A workgroup of 1024 threads takes a 256 x 256 block:
-//   1. the plane is cut into 32 x 32 cells (256 entries: 64 x 64) over mean +- 3.25 standard deviations of the codebook's entries (those outside are
-//      left out and the box is taken again, twice);
+//   1. the plane is cut into 32 x 32 cells (256 entries: 64 x 64) over mean +- 3.25 standard deviations of the codebook's entries
+//      (those outside are left out and the box is taken again, twice);
 //   2. the entries that can be nearest to a point of a cell are listed: with r the entry nearest to the
 //      centre, at distance |r|, and h the distance from the centre to the cell's farthest point, an entry farther than
 //      |r| + 2 h from the centre is farther than r from every point of the cell, and so is one whose squared distance exceeds
 //      r's at all four corners (the difference is linear over the cell).  The cell is taken 10 % and the limits 1e-5 of the
 //      squared reach too large, far beyond the rounding of the binary32 distances (4 2^-24) and of the cell of a point, so the
-//      entry that wins by the definition's rounded distances is always listed, and so is every entry that ties with it;
+//      entry that wins by the definition's rounded distances is always listed, and so is every entry that ties with it, but for
+//      entries equal to one of a lower index: they never win, and copies of one entry would fill the lists;
 //   3. a pair is compared with its cell's entries in index order (strict comparison: the lowest index wins a tie); unused
 //      places of a list repeat its first entry, which never wins again;
 //   4. pairs outside the cells, or in a cell with more than 16 entries (256: 8), are queued and compared with every entry: a few by
-//      sixteen lanes for four of them, more by a thread each.  Units of eight pairs that find the queue (a quarter of the block, with 256 entries three sixteenths) full are
-//      marked and done over with every entry;
-//   5. blocks for which the cells do not pay (weights far wider than the codebook, equal or crowded entries) compare every pair
+//      sixteen lanes for four of them, more by a thread each.  Those that find the queue full (a quarter of the block, with 256
+//      entries an eighth: two workgroups share the LDS of a compute unit) are marked, and collected where the lists were;
+//   5. blocks for which the cells do not pay (weights far wider than the codebook, crowded entries) compare every pair
 //      with every entry: when a fifth (6 bits) or a third (8 bits) of 128 sampled pairs is outside the cells, before the lists
 //      are made, or when a quarter of the first unit of every thread was queued, from there on (from the start, if half was).
 //      Four entries at a time, the smallest of them against the best, which one it was found out at the end: 6 instructions
@@ -310,16 +313,16 @@ __device__ __forceinline__ void nearer(float& best, int& arg) {      // of two l
 // eight pairs per thread 20000 -> 12000, the queue 21000 -> 17000.  A few queued pairs (step 4) are taken four at a time by sixteen lanes.
 // Measured (bf16, near-normal weights, one in a thousand ten times as wide, one matrix repeated, us; every pair against every entry,
 // with 32 x 32 cells that each looked through the entries near 8 x 8 of them, here): 4096 x 4096, 64 entries 77, 53, 50, 256 entries
-// 279, 81, 64; 14336 x 4096, 64 entries 128 -> 125, 256 entries 887, 218, 177; 1024 x 1024, 64 entries 22 -> 19.5, 256 entries 83, 42, 37.  Without
-// step 5 and the second form of step 4, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 186 and 502
-// (now 72 and 227), all entries equal 180 and 467 (68 and 219), nine places for all entries 135 and 478 (68 and 269), half of the
-// entries zero 162 and 170 (70 and 122).  Registers: 64, for two workgroups on a compute unit (74: 14336 x 4096, 64 entries
-// 126 -> 172).
+// 279, 81, 64; 14336 x 4096, 64 entries 128 -> 125, 256 entries 887, 218, 171; 1024 x 1024, 64 entries 22 -> 20, 256 entries 83, 42, 39.
+// Where there is little for the cells to find, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 67 and 215,
+// all entries equal 65 and 207, on nine places 30 and 44 (copies on the lists: 65 and 272), half of them zero 65 and 106 (75 and 184),
+// half of them different ones within a thousandth of a deviation 65 and 127.  Registers: 64, for two workgroups on a compute unit (74:
+// 14336 x 4096, 64 entries 126 -> 172).
 template <int KBITS>
 __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
                                                          const uint16_t* __restrict__ codebooks,
                                                          uint32_t* __restrict__ indices, int parts_log2) {
-    constexpr int E = 1 << KBITS, kQueue = KBITS == 6 ? 8192 : 6144;
+    constexpr int E = 1 << KBITS, kQueue = KBITS == 6 ? 8192 : 4096;
     constexpr bool kFine = KBITS == 8;                             // 64 x 64 cells of up to eight entries, else 32 x 32 of sixteen
     constexpr int G = kFine ? 64 : 32, kSlots = kFine ? 8 : 16;
     constexpr int kFewQueued = KBITS == 6 ? 256 : 768;             // a thread per pair: 2 and 8 us whatever their number, four at a time 2 us per 256
@@ -328,9 +331,10 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     __shared__ uint8_t listed[kFine ? 1 : G * G];
     __shared__ __attribute__((aligned(16))) uint8_t found[32768];
     __shared__ uint16_t queue[kQueue];
-    __shared__ uint32_t over[128];                                 // units to be done over: a bit each
+    __shared__ uint32_t over[1024];                                // pairs that the queue had no place for: a bit each, a byte per unit
     __shared__ int queued[2], outside;                             // by the first units, by the others
     __shared__ float box[5];                                       // origin, cells per unit, h
+    __shared__ __attribute__((aligned(8))) uint32_t distinct[E / 32];   // a bit per entry: none of a lower index is equal
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int block = blockIdx.x >> parts_log2, part = blockIdx.x & ((1 << parts_log2) - 1);
     const int bj = block % (K / kBlock), bi = block / (K / kBlock);
@@ -356,9 +360,16 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     const bool sampled = tid < 128;                                // 128 pairs spread over the rows
     if (sampled) load_pair((tid * (units >> 4) & ~127) + (tid * 37 & 127), px, py);
     if (tid < E) entry[tid] = float2{f16_bits_to_f32(cb[2 * tid]), f16_bits_to_f32(cb[2 * tid + 1])};
-    if (tid < 128) over[tid] = 0u;
+    over[tid] = 0u;
     if (tid == 0) { queued[0] = 0; queued[1] = 0; outside = 0; }
+    // Beside the box: the lowest entry of each of 1024 hashes.  An entry equal to it never wins and is on no list.  (One that is equal to
+    // another of its hash stays: it costs a place.)
+    uint32_t* const lowest = (uint32_t*)found;
+    const bool looks = tid >= 512 && tid < 512 + E;
+    const uint32_t hash = looks ? (((const uint32_t*)cb)[tid - 512] * 0x9E3779B1u) >> 22 : 0u;
+    lowest[tid] = E;
     __syncthreads();
+    if (looks) atomicMin(&lowest[hash], (uint32_t)tid - 512u);
     if (wave == 0) {                                               // mean and deviation, twice more without the entries outside
         float m0 = entry[0].x, m1 = entry[0].y, r0 = __builtin_inff(), r1 = __builtin_inff();
 #pragma unroll 1
@@ -399,6 +410,12 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     {
         const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(sampled && cell_of(px, py) < 0));
         if (lane == 0 && n) atomicAdd(&outside, n);
+    }
+    if (looks) {
+        const uint32_t at = (uint32_t)tid - 512u, e = lowest[hash];
+        const float2 a = entry[at], b = entry[e];
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(!(e < at && a.x == b.x && a.y == b.y));
+        if (lane == 0) *(unsigned long long*)&distinct[at >> 5] = m;
     }
     __syncthreads();
     int from = outside > (KBITS == 6 ? 24 : 40) ? 0 : 4096;         // units from here on: every pair with every entry
@@ -464,7 +481,7 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                 const unsigned long long m = __builtin_amdgcn_ballot_w64(d <= fmaf(fabsf(r.x - o.x), hx, fmaf(fabsf(r.y - o.y), hy, at_most)));
                 if (part == k) mine = (uint32_t)(m >> (lane & 48)) & 0xFFFFu;
             }
-            if (part < E / 16) coarse[at * (E / 16) + part] = (uint16_t)mine;
+            if (part < E / 16) coarse[at * (E / 16) + part] = (uint16_t)(mine & ((const uint16_t*)distinct)[part]);
         }
         __syncthreads();
         {   // 16 x 16 cells, four lanes each
@@ -652,7 +669,7 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                     if (again[p]) {
                         const int at = ahead + atomicAdd(&queued[u >= 1024], 1);
                         if (at < kQueue) queue[at] = (uint16_t)(8 * u + h + p);
-                        else atomicOr(&over[u >> 5], 1u << (u & 31));
+                        else ((uint8_t*)over)[u] |= (uint8_t)(1u << (h + p));
                     }
                 }
             }
@@ -660,7 +677,7 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
         }
         __syncthreads();
     }
-    const int all = from ? queued[0] + queued[1] : 0, todo = min(all, kQueue);
+    const int all = from ? __builtin_amdgcn_readfirstlane(queued[0] + queued[1]) : 0, todo = min(all, kQueue);
     if (from < units) {
 #pragma unroll 1
         for (int u = from + tid; u < units; u += 1024) {
@@ -671,17 +688,22 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
             store_found(u, arg);
         }
     }
+    auto each_by_itself = [&](const uint16_t* pairs, int n) {
+        int i = tid;
+        asm volatile("" : "+v"(i));                                // (nothing of it kept in registers over what comes before)
+#pragma unroll 1
+        for (; i < n; i += 1024) {
+            const int id = pairs[i];
+            float vx, vy;
+            uint32_t arg;
+            load_pair(id, vx, vy);
+            nearest_of_all<1>(entry, &vx, &vy, &arg);
+            found[id] = (uint8_t)arg;
+        }
+    };
     if (todo) {
         if (todo > kFewQueued) {                                   // a thread per queued pair
-#pragma unroll 1
-            for (int i = tid; i < todo; i += 1024) {
-                const int id = queue[i];
-                float vx, vy;
-                uint32_t arg;
-                load_pair(id, vx, vy);
-                nearest_of_all<1>(entry, &vx, &vy, &arg);
-                found[id] = (uint8_t)arg;
-            }
+            each_by_itself(queue, todo);
         } else {
 #pragma unroll 1
             for (int i0 = 0; i0 < todo; i0 += 256) {               // sixteen lanes per four queued pairs
@@ -726,17 +748,23 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                 }
             }
         }
-        if (all > kQueue) {                                     // (the queued pairs of such a unit come out the same again)
-            __syncthreads();
+        if (all > kQueue) {                                        // those that it had no place for, a quarter of the block after another
+            uint16_t* const more = (uint16_t*)list[0];
+            static_assert(G * G * kSlots >= 2 * 8192, "a quarter's pairs");
 #pragma unroll 1
-            for (int u = tid; u < units; u += 1024)
-                if ((over[u >> 5] >> (u & 31)) & 1u) {
-                    float v0[8], v1[8];
-                    uint32_t arg[8];
-                    load_unit(u, v0, v1);
-                    nearest_of_all<8>(entry, v0, v1, arg);
-                    store_found(u, arg);
-                }
+            for (int w0 = 0; w0 < units / 4; w0 += 256) {
+                __syncthreads();
+                if (tid == 0) outside = 0;
+                __syncthreads();
+                int word = w0 + tid;
+                asm volatile("" : "+v"(word));
+                uint32_t m = word < w0 + 256 ? over[word] : 0u;
+                int at = m ? atomicAdd(&outside, __builtin_popcount(m)) : 0;
+#pragma unroll 1
+                for (; m; m &= m - 1u) more[at++] = (uint16_t)(32 * word + __builtin_ctz(m));
+                __syncthreads();
+                each_by_itself(more, outside);
+            }
         }
     }
     __syncthreads();

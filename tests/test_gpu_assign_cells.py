@@ -117,3 +117,45 @@ def test_vq_assign_lists_that_just_fit(kbits):
     bits = cb.view(np.uint16)[None]
     got = B.vq_assign(dev(wide, "f32"), B.F32, dev(bits, "f16"), kbits).codes.cpu().numpy().view(np.uint32)
     assert np.array_equal(got, E.vq_assign_packed(wide, bits, kbits))
+
+
+@pytest.mark.parametrize("kbits", [6, 8])
+@pytest.mark.parametrize("rows", [1, 17])                   # quarters of blocks and whole ones
+def test_vq_assign_equal_and_crowded_entries(kbits, rows):
+    """Entries equal to one of a lower index (never nearest, on no list): half of them zero of either sign, pairs of equal ones, a few copies of
+    one, none; and crowds of different entries around one place, on both sides of what a list is made for; more marked units than none."""
+    from paper_2505_03803_amd import binding as B
+    rng = np.random.default_rng(23)
+    En = 1 << kbits
+    kinds = ["half zero", "zeros of both signs", "pairs", "some", "crowd", "crowd just fits", "nine crowds", "half, rows apart", "infinite"]
+    cb = rng.normal(0, 0.02, (len(kinds), En, 2)).astype(np.float16)
+    wide = rng.normal(0, 0.02, (256, 256 * len(kinds))).astype(np.float32)
+    for i, kind in enumerate(kinds):
+        b = wide[:, 256 * i: 256 * (i + 1)]
+        if kind == "half zero":
+            cb[i, ::2] = 0
+        elif kind == "zeros of both signs":
+            cb[i, 1::2] = rng.choice(np.float16([0.0, -0.0]), (En // 2, 2))
+        elif kind == "pairs":
+            cb[i, 1::2] = cb[i, ::2]
+        elif kind == "some":
+            cb[i, rng.permutation(En)[:En // 8]] = cb[i, 3]
+        elif kind.startswith("crowd"):                      # 32 and 96 entries near a cell, and more
+            n = (90 if kbits == 8 else 28) if kind.endswith("fits") else En - En // 8
+            cb[i, rng.permutation(En)[:n]] = [0.004, -0.003] + rng.normal(0, 2e-5, (n, 2))
+        elif kind == "nine crowds":
+            cb[i] = (rng.integers(-1, 2, (En, 2)) * 0.02) * (1 + 1e-3 * rng.standard_normal((En, 2)))
+        elif kind == "half, rows apart":                    # pairs near the crowd in rows that follow the first unit of every thread
+            cb[i, ::2] = rng.normal(0, 2e-5, (En // 2, 2))
+            b[np.arange(256) % 64 > 20] *= 0.1
+        else:
+            cb[i, 5:12] = [np.inf, 0.01]
+            cb[i, 20:24] = -np.inf
+    books = cb.view(np.uint16)[None]
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = np.tile(E.vq_assign_packed(wide, books, kbits), (rows, 1))
+    dm = B.vq_assign(dev(np.tile(wide, (rows, 1)), "f32"), B.F32, dev(np.tile(books, (rows, 1, 1, 1)), "f16"), kbits)
+    got = dm.codes.cpu().numpy().view(np.uint32)
+    words = want.shape[1] // len(kinds)
+    for i, kind in enumerate(kinds):
+        assert np.array_equal(got[:, words * i: words * (i + 1)], want[:, words * i: words * (i + 1)]), kind
