@@ -1507,6 +1507,9 @@ struct StageTiles {
 // most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight.  Five and six row tiles spill up
 // to seven of the 168; eight wavefronts of 256 spill none and were no better (us, batch 8, twelve -> eight: 20480 x 8192, fp16 SQ 18.7 ->
 // 17.6 and bf16 VQ 22.3 -> 20.9, but 24576 x 4352 12.5 -> 13.4 and 13.8 -> 16.2: its 17 column tiles take three turns in place of two).
+// The kernel says that no more of them are wanted on a SIMD: left to itself the compiler gives the loads of fp16 x 126 registers of 168,
+// for a wavefront that never comes, and has fewer in flight (a layer of d = 2048 in SQ, two row tiles, at M = 2 13.7 -> 12.3 us, at 16
+// 19.9 -> 17.4; {14336 x 4096, 4096 x 14336} 6-bit VQ at 8 23.2 -> 22.2).
 constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
@@ -1515,7 +1518,8 @@ template <int MATS> struct StageArgs {
     int M, xdt, ydt, S, waves, pad;
 };
 template <int R, bool MULTI, class Args>
-__global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) decode_stage_kernel(Args a) {
+__global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) __attribute__((amdgpu_waves_per_eu(stage_waves(MULTI, R) / 4, stage_waves(MULTI, R) / 4)))
+decode_stage_kernel(Args a) {
     extern __shared__ __attribute__((aligned(1024))) uint32_t stage_lds[];        // per wavefront: two codebook slots, later its R sums
     __shared__ __attribute__((aligned(16))) float xsc[16][16];
     int mi = 0, group;
