@@ -2125,12 +2125,18 @@ static hipError_t launch_wide_kernel(const StageArgs<kGrid2DMaxMats>& a, dim3 gr
 // through take 0.55 to 1.02 of the time there.  16640 x 256 SQ at M = 24 9.4 -> 9.7, at 48 10.9 -> 15.4 (not taken); {k', r'} of the 7B
 // shapes fp16 SQ at M = 17 23.5 -> 15.2, 32 24.9 -> 17.3, 48 27.9 -> 22.0; of 14B-class shapes (six row tiles) fp16 SQ at 32
 // 29.3 -> 23.0, 6-bit VQ 28.4 -> 22.7; bf16 SQ 18432 x 2048 at 33 18.5 -> 13.7, at 48 19.3 -> 15.5.
+// The round ends with its longest rows, there shorter ones of a second round run beside them: beyond 32 rows of x, where a column costs
+// most, an estimate of both (us, here / there, at M = 48: {14336 x 4096, 4096 x K} SQ 22 / 27 at K = 4096, 29 / 27 at 6144, 54 / 36 at
+// 14336; {9216 x 2048, 9216 x K} 16 / 19 at 2048, 22 / 19 at 4096; at 33 24 / 27 and 19 / 19 in the second of each).  Of 216 calls of
+// 24 kinds at 33, 40 and 48 rows none takes a kernel that is more than 4 % slower.
 static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
     const bool bf16 = x_dtype == DT_BF16;
     if (n_mats > kGrid2DMaxMats || M <= 16 || M > 48) return 0;
     double row_tiles = 0.0, tiles = 0.0;
+    LaunchLoad there;
     for (int i = 0; i < n_mats; ++i) {
         if (bf16 && mats[i].fmt != FMT_SQ3) return 0;              // (see StageWide)
+        there.add((mats[i].N + 63) / 64, mats[i].K);
         row_tiles += mats[i].N / 16;
         tiles += (double)(mats[i].N / 16) * (mats[i].K / 256);
     }
@@ -2139,6 +2145,7 @@ static int wide_row_tiles(const MatDev* mats, int n_mats, int M, int x_dtype) {
     if (R == 0 || option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK) >= 1000000) return R;
     const double columns = tiles / row_tiles;                      // of the average row
     const double most = R == 6 ? 12.0 + 5.0 * columns : 16.0 + 8.0 * columns;
+    if (M > 32 && 7.0 + 0.0667 * M + (0.268 + 0.0107 * M) * there.longest > 11.0 + 0.47 * there.columns(0.5)) return 0;
     return M <= most ? R : 0;
 }
 bool wide_cheaper(const MatDev* mats, int n_mats, int M, int x_dtype) { return wide_row_tiles(mats, n_mats, M, x_dtype) > 0; }

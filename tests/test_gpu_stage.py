@@ -228,3 +228,25 @@ def test_rule_of_more_rows(N, columns, M, xdt, options):
         torch.cuda.synchronize()
     assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0][:, :1024], ys[2])
     assert G.err_g2(ys[0].cpu().numpy().astype(np.float64), orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
+# Matrices of two lengths at 33 and 48 rows, on both sides of the line by the longest rows (the same bits up to eight column tiles, as above)
+@pytest.mark.parametrize("lengths", [(4, 4), (4, 6), (4, 8), (2, 8)])
+@pytest.mark.parametrize("M,xdt", [(33, "f16"), (33, "bf16"), (48, "bf16")])
+def test_rule_of_more_rows_of_two_lengths(lengths, M, xdt, options):
+    print(f"two lengths {lengths} M={M} x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(M)
+    mats = [synth.gen_sq(rng, 16128, 256 * lengths[0]), synth.gen_sq(rng, 528, 256 * lengths[1])]
+    xs = [synth.gen_activations(rng, M, m.K, xdt) for m in mats]
+    dms, dev = [B.upload(m, native=True) for m in mats], [G.to_dev_bits(x) for x in xs]
+    options(B.OPT_SMALL_BATCH_PATH, B.SMALL_BATCH_STREAM)
+    got = []
+    for forced in (0, 1000000):
+        options(B.OPT_STREAM_SPLIT_MAX_WORK, forced)
+        ys = [torch.full((M + 1, m.N), 7.0, dtype=torch.float32, device="cuda") for m in mats]
+        B.rwkvq_linear_dispatch(B.DispatchTable([d.desc() for d in dms], dev, ys), M, B.DTYPES[xdt], B.F32)
+        torch.cuda.synchronize()
+        got.append(ys)
+    for m, x, y, z in zip(mats, xs, *got):
+        assert torch.equal(y, z) and (y[M] == 7.0).all()
+        assert G.err_g2(y[:M].cpu().numpy().astype(np.float64), orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
