@@ -30,7 +30,7 @@ def check(w, terms=5):
 @pytest.mark.parametrize("n", [BIG - 1, BIG, BIG + 1, BIG + 3 * 4096 + 2, 3 * BIG + 5, 8 * BIG, 8 * BIG + 4099])
 def test_proxy_sets_sizes(n):
     rng = np.random.default_rng(n)
-    for terms in (2, 5, 8) if n < 8 * BIG else (5,):          # (8 BIG + 1 on: the keys reordered in tiles)
+    for terms in (2, 5, 8) if n < 8 * BIG else (5,):
         check(synth.gen_dense_weights(rng, 1, n, "f32", outlier_fraction=1e-3), terms)
 
 
@@ -54,12 +54,13 @@ def test_proxy_sets_kinds(kind):
     elif kind == "two":
         w = np.where(rng.random(n) < 0.5, np.float32(1.0), np.float32(2.0))
     elif kind == "one_bin":                                     # one bin of several pieces, dense
-        w = (1.0 + rng.integers(0, 1 << 17, n) * 2.0 ** -23).astype(np.float32)
+        w = (1.0 + rng.integers(0, 1 << 19, n) * 2.0 ** -23).astype(np.float32)
     elif kind == "few_bins":                                    # around 131072 keys per bin, several pieces
         sizes = [4095, 4096, 4097, 8191, 131071, 131072, 131073, 262145]
         m = np.repeat(np.arange(len(sizes)), sizes)
-        fine = rng.integers(0, 1 << 17, m.size)
-        a = (((127 << 6) + m) << 17 | fine).astype(np.uint32)
+        fine = rng.integers(0, 1 << 19, m.size)
+        a = (((127 << 4) + m) << 19 | fine).astype(np.uint32)
+        assert sorted(np.unique(a >> 19, return_counts=True)[1]) == sorted(sizes)
         w = np.concatenate([a, a | np.uint32(0x80000000)]).view(np.float32)
         w = rng.permutation(w)
     elif kind == "small_bins":                                  # around 1024 keys (a bin with more is a bitmap) and groups of
@@ -67,12 +68,13 @@ def test_proxy_sets_kinds(kind):
         sizes = [1023, 1024, 1025, 1024, 1024, 1023, 1, 1024, 255, 769, 256, 768, 257, 767, 511, 512, 1, 1, 1022, 1024, 1025, 1026]
         sizes += [1] * 300 + [1024] * 3 + [3, 5, 7] * 200 + [1000] * 520
         m = np.repeat(np.arange(len(sizes)), sizes)
-        a = (((100 << 6) + m) << 17 | rng.integers(0, 1 << 17, m.size)).astype(np.uint32)
+        a = (((100 << 4) + m) << 19 | rng.integers(0, 1 << 19, m.size)).astype(np.uint32)
+        assert list(np.unique(a >> 19, return_counts=True)[1]) == sizes
         w = rng.permutation(a).view(np.float32)
         check(np.concatenate([w, np.float32([1e-30])]))         # one key in front moves every group
         check(w[: BIG + 5])                                     # a last group of any size
     assert w.size >= BIG
-    if kind != "spaced":                                        # the same kind large enough for the tiled partition, ragged
+    if kind != "spaced":                                        # the same kind with several tiles per workgroup of the partition, ragged
         check(np.concatenate([np.resize(w, 8 * BIG), w[:4099]]))
     if kind == "spaced":
         Pc, Pf, _ = run(w)
@@ -86,7 +88,7 @@ def test_proxy_sets_not_finite():
     rng = np.random.default_rng(8)
     for bad in ([np.inf], [-np.inf], [np.inf, -np.inf], [np.nan], [-np.nan, np.inf]):
         out = []
-        for n in (4096, BIG, 8 * BIG + 3):                      # the radix sort, the partition, the one in tiles
+        for n in (4096, BIG, 8 * BIG + 3):                      # the radix sort, the partition with a tile and with several per workgroup
             w = rng.standard_normal(n).astype(np.float32)
             w[5:5 + len(bad)] = bad
             out.append(run(w))
@@ -94,16 +96,19 @@ def test_proxy_sets_not_finite():
             assert np.array_equal(np.array(out[0]), np.array(got), equal_nan=True), (bad, out)
 
 
-# occupied bins on both sides of what the partition by rank holds, the keys spread over all of them; the smallest matrix that is
-# reordered in tiles (3 x 2^20 weights is not, one more is), and ranges that end in a part of a tile and in single keys
-@pytest.mark.parametrize("bins", [1, 8191, 8192, 8193])
-@pytest.mark.parametrize("n", [(3 << 20) + 1, 4 * 16384 * 64 + 4 * 777 + 3])
-def test_proxy_sets_ranks(bins, n):
+# few bins and all that finite weights have (8160), the keys spread over all of them; ranges of a workgroup of exactly one tile of 16384
+# keys, of a quad more, of two tiles with a single key more, and of tiles and a part of one with three
+@pytest.mark.parametrize("bins", [1, 2, 8160])
+@pytest.mark.parametrize("n", [BIG, BIG + 4 * 32, 2 * 256 * 16384 + 1, 4 * 16384 * 64 + 4 * 777 + 3])
+def test_proxy_sets_partition(bins, n):
     rng = np.random.default_rng(bins)
-    bin_of = np.concatenate([np.arange(bins), rng.integers(0, bins, n - bins)])
-    keys = ((np.uint32(2000) + bin_of.astype(np.uint32) * np.uint32(3)) << 17) | rng.integers(0, 1 << 17, n).astype(np.uint32)
+    used = np.linspace(16, 8175, bins).astype(np.uint32) if bins > 1 else np.array([4500], np.uint32)
+    bin_of = used[np.concatenate([np.arange(bins), rng.integers(0, bins, n - bins)])]
+    keys = (bin_of << np.uint32(19)) | rng.integers(0, 1 << 19, n).astype(np.uint32)
     bits = np.where(keys >> 31, keys & np.uint32(0x7FFFFFFF), ~keys).astype(np.uint32)
-    check(rng.permutation(bits).view(np.float32))
+    w = rng.permutation(bits).view(np.float32)
+    assert np.isfinite(w).all() and np.unique(bin_of).size == bins
+    check(w)
 
 
 # bins of 2^19 patterns with their bits a fixed distance apart (both sides of the distances that are counted, and of what is found word by
