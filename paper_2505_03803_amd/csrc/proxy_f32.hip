@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 //                           bin does not matter (and is not fixed), so no ranks are needed;
 //   * set_sum_kernel        a hot bin is 2^19 patterns of one sign and exponent: a bitmap of 64 KB in LDS.  Intervals are
 //                           distances of set bits times the exponent's unit, exact, and counted by distance.  A bin of more
-//                           than 131072 keys and a 64th of all is read by several workgroups that join their bitmaps in
+//                           than 131072 keys and a 64th of all (piece_solo) is read by several workgroups that join their bitmaps in
 //                           memory, and the last to finish sums.  A group of small bins is sorted (sort_group);
 //   * set_final_kernel      intervals between bins, intervals of zero (t - 1 = -1), the partial sums in a fixed order, P_c, P_f.
 //
@@ -307,8 +307,9 @@ __global__ void __launch_bounds__(256) gap_final_kernel(const uint32_t* __restri
 // as long per atomic operation and were slower (4096 x 4096 122 -> 152 us).
 // Measured (us; radix sort, bins of 2^17 -> here): 768 x 768 157, 90 -> 55, 1024 x 1024 163, 95 -> 56, 4096 x 4096 502, 138 -> 122,
 // 14336 x 4096 1957, 350 -> 307; the eight matrices of a layer of the 7B shapes 7060, 1320 -> 1040, of d = 1024 598 -> 331.
-// 2^24 weights: values of bfloat16 178 -> 146, uniform 123 -> 126, all equal 139 -> 141, half zero 167 -> 146; bit patterns at random 569 -> 210
-// (2^20: 122 -> 71), 2^(uniform from -40 to 20) 205 -> 136.  Below kSetMinCount the sort.
+// 2^24 weights (bins of 2^17 -> here): values of bfloat16 181 -> 147, uniform in [-1/2, 1/2) 132 -> 131, in [0, 1) 125 -> 129, all equal
+// 139 -> 125, half zero 187 -> 160, 2^(uniform from -40 to 20) 207 -> 134; bit patterns at random 569 -> 210 (2^20: 122 -> 71).  14336 x 4096:
+// uniform 325 -> 322 and 325 -> 304, values of bfloat16 536 -> 414, half zero 504 -> 419.  Below kSetMinCount the sort.
 constexpr uint32_t kSetMinCount = 1u << 19;                  // (the line: the workspace, sized for the sort, holds the tables)
 constexpr int kBins = 8192, kBinShift = 19;
 constexpr uint32_t kHot = 1024;                              // keys of a bin that is not hot, and of a group's bins but the last
@@ -347,7 +348,6 @@ struct SetBuffers {
 // work (and the ends of the counts) once per group instead of once per matrix.
 constexpr int kSetGroup = 8;
 struct SetGroup { SetBuffers b[kSetGroup]; };
-static uint32_t set_joint_max(uint32_t count) { return std::min(count / kPiece, 64u); }       // (a joint bin holds more than a 64th of the keys)
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static size_t set_key_bytes(uint32_t count) { return align256((size_t)count * 4); }
@@ -355,7 +355,7 @@ static size_t set_key_bytes(uint32_t count) { return align256((size_t)count * 4)
 static size_t set_tables(SetBuffers& b, char* base, uint32_t count, uint32_t range = kCountRange) {
     size_t o = 0;
     auto take = [&](size_t bytes) { char* p = base + o; o += align256(bytes); return p; };
-    b.count = count; b.wgs = set_workgroups(count, range); b.solo = piece_solo(count); b.joint_max = set_joint_max(count);
+    b.count = count; b.wgs = set_workgroups(count, range); b.solo = piece_solo(count); b.joint_max = piece_joint_max(count);
     b.reserved = (uint32_t*)take((size_t)b.wgs * kBins * 4);
     b.head = (SetHead*)take(sizeof(SetHead));
     b.counts = (uint32_t*)take(kBins * 4);
@@ -658,7 +658,7 @@ __device__ __forceinline__ void add_interval(double (&s)[kSetRow], double t, int
     for (int k = 2; k < kGapSums; ++k) { if (k > terms) break; p *= u; s[k] += p; }
 }
 
-// t ln t, 0 if t is not above zero.  ln t from the logarithm of the upper eleven bits of its fraction, which the table holds, and four
+// t ln t, 0 if t is not above zero.  ln t from the logarithm of the upper eleven bits of its fraction, which the table holds, and six
 // terms of the series of the rest, which is below 2^-10: the error is that of the last addition.  (The library's logarithm has so many constants
 // that keeping them over the loops around it spills a hundred registers.)
 __device__ __forceinline__ double t_log_t(double t, const double* __restrict__ logs) {

@@ -31,6 +31,7 @@ int main() {
         if (set_workgroups(count) < 256u) check_range(count, set_workgroups(count, kCountRangeAlone));
         // a bin that holds every key, and the largest that one workgroup reads
         const uint32_t solo = piece_solo(count);
+        if (count / (solo + 1u) > piece_joint_max(count)) ++bad;            // bins of several pieces at once
         for (const uint32_t n : {count, solo}) {
             u64 keys = 0, pieces = 0;
             for (uint32_t f = 0; f < n; f += piece_keys(n, f, solo)) {
