@@ -11,4 +11,11 @@ constexpr int mid_row_tile(int i, int tiles) { return i < tiles ? i : tiles - 1;
 // Byte offset of column tile T (of KT) of a row tile, each of tile_bytes, from the wavefront's first.
 constexpr int mid_tile_offset(int row_tile, int T, int KT, int tile_bytes) { return (row_tile * KT + T) * tile_bytes; }
 
+// Weights unrounded, M rows of x: 16 MF rows of x in a workgroup, evenly over the fewest workgroups of at most 64; 16 NF rows of W, where
+// `narrow` workgroups of 32 hold the launch: up to one per compute unit 32 win, up to half of that 16 (see midbatch.hip).
+constexpr int mid_exact_mf(int M) { return ((M + (M + 63) / 64 - 1) / ((M + 63) / 64) + 15) / 16; }
+constexpr int mid_exact_nf(int mf, long long narrow) { return narrow <= 128 ? 1 : narrow <= 256 || mf == 1 ? 2 : 4; }
+// The instances that there are.
+constexpr bool mid_exact_instance(int mf, int nf) { return mf >= 1 && mf <= 4 && (nf == 1 || nf == 2 || (nf == 4 && mf > 1)); }
+
 }  // namespace rwkvq

@@ -507,6 +507,7 @@ static hipError_t launch_mid_t(const MidArgs& a, int wgs, hipStream_t s) {
 template <bool BF16>
 static hipError_t launch_mid_shape(const MidArgs& a, int mf, int nw, int nf, bool exact, int wgs, hipStream_t s) {
     if (exact) {
+        if (!mid_exact_instance(mf, nf)) return hipErrorInvalidValue;
         if (mf == 1) return nf == 1 ? launch_mid_t<BF16, 1, 1, true, 1>(a, wgs, s) : launch_mid_t<BF16, 1, 1, true, 2>(a, wgs, s);
         if (nf == 1) return mf == 2   ? launch_mid_t<BF16, 2, 1, true, 1>(a, wgs, s)
                             : mf == 3 ? launch_mid_t<BF16, 3, 1, true, 1>(a, wgs, s) : launch_mid_t<BF16, 4, 1, true, 1>(a, wgs, s);
@@ -561,13 +562,12 @@ hipError_t launch_mid(const MatDev* mats, int n_mats, int M, int x_dtype, int y_
         long long rows = 0;
         for (int i = 0; i < cnt; ++i) { order[i] = base + i; rows += mats[base + i].N; }
         std::stable_sort(order, order + cnt, [&](int p, int q) { return mats[p].K > mats[q].K; });   // long workgroups first
-        if (exact) {                           // even rows over the fewest workgroups of at most 64
-            const int tiles = (M + 63) / 64;
+        if (exact) {
             nw = 1;
-            mf = ((M + tiles - 1) / tiles + 15) / 16;
-            long long narrow = 0;              // workgroups of 32 rows of W: up to one per compute unit they win, up to half of that those of 16
-            for (int i = 0; i < cnt; ++i) narrow += (long long)tiles * ((mats[base + i].N + 31) / 32);
-            if (narrow <= 256) nf = narrow <= 128 ? 1 : 2;
+            mf = mid_exact_mf(M);
+            long long narrow = 0;
+            for (int i = 0; i < cnt; ++i) narrow += (long long)((M + 63) / 64) * ((mats[base + i].N + 31) / 32);
+            nf = mid_exact_nf(mf, narrow);
         }
         else pick_mid(M, rows, &mf, &nw);
         a.m_tiles = (M + 16 * mf - 1) / (16 * mf);

@@ -31,6 +31,13 @@ int main() {
                         }
                 }
             }
+    // every number of rows of x and of workgroups has an instance of the size that the grid is made for, and enough rows of x
+    for (int M = 1; M <= 128; ++M)
+        for (long long narrow : {1ll, 128ll, 129ll, 256ll, 257ll, 100000ll}) {
+            const int mf = mid_exact_mf(M), nf = mid_exact_nf(mf, narrow);
+            if (!mid_exact_instance(mf, nf) || 16 * mf * ((M + 63) / 64) < M || 16 * mf > 64) ++bad;
+            ++checked;
+        }
     std::printf("checked %llu bad %d\n", checked, bad);
     return bad != 0;
 }
