@@ -117,7 +117,8 @@ const char* rwkvq_status_string(int status);
  *                                 measured to be the faster one: whenever 256 workgroups of up to 96 rows of W hold it, larger
  *                                 launches by the lengths of their rows, their number and M.  Those lines move in proportion
  *                                 to the option (65536; 1 = never,
- *                                 1000000 = always).  The streaming path at 17..128 has such a form too (kernels that split
+ *                                 1000000 = always).  Short of 1000000, up to eight matrices of long rows in one round take
+ *                                 another such kernel, which copies x into LDS.  The streaming path at 17..128 has such a form too (kernels that split
  *                                 K on the matrix cores, weights exact as well): at 17..32 for launches of up to 1792
  *                                 workgroups of 64 rows of W (two such layers), a number that moves in proportion to the
  *                                 option, beyond 32 up to 2000 to 20000 of them, by M; 1 keeps the path on passes over 32

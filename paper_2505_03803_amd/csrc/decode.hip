@@ -1327,7 +1327,8 @@ struct StageTiles {
     // look-up words and two MFMAs where the conversion takes 235 instructions per column tile, for all row tiles: 6-bit VQ with up to two
     // of them, 8-bit with one (its look-ups of eight bytes meet in twice the banks).  Measured (us, converted -> as they are): 4096 x 4096
     // SQ at M = 2 5.8 -> 4.8, at 16 7.2 -> 6.7, 4096 x 14336 at 2 14.8 -> 11.4, 6-bit VQ 14.5 -> 11.7, 8-bit 15.4 -> 13.7; 17920 x 5120 and
-    // 5120 x 5120 SQ (six row tiles) at 2 17.8 -> 12.8.  VQ of five row tiles at 2 10.7 -> 11.1, of two in 8 bits 5.4 -> 5.6 (converted).
+    // 5120 x 5120 SQ (six row tiles) at 2 17.8 -> 12.8.  VQ of five row tiles at 2 10.7 -> 11.1, of two in 8 bits 5.4 -> 5.6 (converted);
+    // with four column tiles the split of the codebook is not won back: 4096 x 1024 8-bit VQ at 2 3.6 -> 3.75 (as they are all the same).
     static constexpr bool kDirect = XB && (FMT == FMT_SQ3 || R <= (FMT == FMT_VQ6 ? 2 : 1)), kConvert = XB && !kDirect;
     static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
     const DecodeMat& mt;
@@ -1973,7 +1974,8 @@ struct StageShape {
 //     by eight, 13.3 by six, in bf16 14.0 and 13.2; at M = 16 in bf16 18.6 by eight, 18.0 by five); bf16 with VQ, whose conversion or second
 //     operands every wavefront repeats, by eight or twelve, a multiple of the SIMDs (5120 x 17920 6-bit VQ at M = 2 19.6 by seven, 17.5 by
 //     twelve), twelve where a tile of x is short, or with one row tile by ten up to M = 8 and by six beyond (4096 x 14336 6-bit VQ at M = 2
-//     11.9 by twelve, 11.7 by ten; at M = 16 19.8 by eight, 18.2 by six).  In fp16 on 690 calls within 1.1 % of the best S in the mean;
+//     11.9 by twelve, 11.7 by ten; at M = 16 19.8 by eight, 18.2 by six).  In fp16 on 690 calls within 1.1 % of the best S in the mean.  With
+//     up to two row tiles that is for calls of more than eight matrices and for those that staged_cheaper leaves here;
 //   * one round, mixed lengths: a workgroup of the longest rows would end long after the others: two row tiles instead of three to
 //     six, or one (a layer of d = 2048 in 8-bit VQ at M = 2 20.2 with R = 6, now 13.4; {8192 x 256, 256 x 8192} in SQ at M = 8 12.2 and 9.4);
 //   * several rounds, of one length or of mixed ones: small workgroups overlap ({k', r', v'} of the 14B-class shapes in 8-bit VQ at M = 4
@@ -2038,7 +2040,7 @@ static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, 
 //   * several rounds of one length: up to 3200 row tiles, and M = 12 up to 2048 columns (24 of 2048 x 1024 SQ at M = 8 7.4 / 8.8), M = 4
 //     beyond (44 of 512 x 2560: SQ at M = 8 11.8 / 10.7, 8-bit VQ at 2 11.8 / 12.8): 94 of 816, the worst 23 %;
 //   * several rounds of mixed lengths (whole layers): an estimate of both durations: 15 of 736, the worst 14 %.
-// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK moves the lines in proportion (1: never split, 1000000: always).
+// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK moves the lines in proportion (1: never split, 1000000: always, and always by this kernel).
 static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int M, int x_dtype, const StageShape& p) {
     const int max_work = option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK);
     if (max_work <= 1 || max_work >= 1000000) return max_work > 1;
@@ -2073,14 +2075,18 @@ static bool stage_cheaper(const MatDev* mats, const int* order, int n_mats, int 
 // on 120 matrices' shapes and formats at eight values of M, fp16 and bf16: 4096 x 14336 SQ at M = 2 11.5 -> 10.7, at 8 13.3 -> 11.5, at 16 18.3 ->
 // 13.3, 6-bit VQ in fp16 at 8 13.4 -> 11.8, at 16 17.9 -> 13.4, in bf16 at 4 12.5 -> 13.5, at 8 14.4 -> 13.7; 2048 x 5120 SQ at 16 9.0 -> 5.4;
 // 4096 x 4096 SQ at 8 5.5 -> 5.5, at 16 6.7 -> 5.9, 8-bit VQ at 16 7.1 -> 7.4; two row tiles: 5120 x 17920 SQ at 4 16.8 -> 16.6, at 16 24.0
-// -> 19.1, 8-bit VQ in fp16 at 12 21.6 -> 21.1; 8192 x 4096 at 16 4 to 11 % longer.
+// -> 19.1, 8-bit VQ in fp16 at 12 21.6 -> 21.1; 8192 x 4096 at 16 4 to 11 % longer.  Nine columns are a second turn here for one of eight
+// K groups: 4096 x 2304 SQ at 10 4.4 -> 4.6, at 12 even, 6-bit VQ at 14 4.8 -> 5.1, in bf16 5.2 -> 5.6.  Of 4290 calls (N = 512 to 8192, nine to
+// 70 columns, M = 2 to 16, both types of x) that come here none is more than 4 % slower; what stays there up to M = 6 with more than 28 columns
+// of VQ would be faster here in fp16 (512 x 14336 6-bit at 6 11.8 -> 10.0), not in bf16.
+// RWKVQ_OPT_STREAM_SPLIT_MAX_WORK = 1000000 never comes here.
 static bool staged_cheaper(const MatDev* mats, const int* order, int n_mats, int M, const StageShape& p) {
-    if (p.kind != STAGE_ROUND || p.R > 2 || n_mats > kGrid2DMaxMats) return false;
+    if (p.kind != STAGE_ROUND || p.R > 2 || n_mats > kGrid2DMaxMats || option(RWKVQ_OPT_STREAM_SPLIT_MAX_WORK) >= 1000000) return false;
     int f = FMT_SQ3;
     for (int i = 0; i < n_mats; ++i) f = std::max(f, mats[order[i]].fmt);
     if (p.R == 2) return p.columns > 16 && M >= (f == FMT_SQ3 ? 6 : f == FMT_VQ6 ? 14 : 15);
     if (p.columns > 16) return f == FMT_SQ3 || p.columns <= 28 || M > 6;
-    return p.columns > 8 && f != FMT_VQ8 && M >= (f == FMT_SQ3 ? 10 : 14);
+    return p.columns == 9 ? f == FMT_SQ3 && M >= 12 : p.columns > 9 && f != FMT_VQ8 && M >= (f == FMT_SQ3 ? 10 : 14);
 }
 
 template <int MATS>

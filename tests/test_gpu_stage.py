@@ -84,7 +84,7 @@ def test_column_split_of_one_length(R, columns, M, xdt):
 
 # One round with one or two row tiles per workgroup: both sides of the lines between operands straight from memory and activations copied
 # into LDS, by columns, M and format; the last workgroup of 32 rows half empty (4112), two matrices in one launch
-@pytest.mark.parametrize("N,columns,Ms", [(1024, 8, (16,)), (1024, 9, (9, 10, 13, 14)), (4096, 16, (9, 10, 13, 14)), (256, 17, (2, 16)),
+@pytest.mark.parametrize("N,columns,Ms", [(1024, 8, (16,)), (1024, 9, (9, 10, 11, 12, 14)), (1024, 10, (9, 10, 13, 14)), (4096, 16, (9, 10, 13, 14)), (256, 17, (2, 16)),
                                           (4096, 17, (2, 3)), (512, 28, (2, 6)), (512, 29, (6, 7)), (4112, 16, (16,)),
                                           (4112, 17, (5, 6, 13, 14, 15)), (8192, 18, (6, 14, 15))])
 @pytest.mark.parametrize("kind", ["sq", "vq6", "vq8"])
