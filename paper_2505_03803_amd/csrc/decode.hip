@@ -1346,7 +1346,8 @@ struct StageTiles {
         asm("v_mov_b32 %0, %1" : "=v"(m6) : "n"(kDirect ? 0x1f8 : 0xfc));
         base0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)cb_lds;
     }
-    // A column tile's activation fragments (XFrags, straight from memory: nothing is staged for the workgroup, no barrier), a row tile's weights: together and in order (see tile_pipeline).  Past the
+    // A column tile's activation fragments (XFrags, straight from memory: nothing is staged for the workgroup, no barrier), a row
+    // tile's weights: together and in order (see tile_pipeline).  Past the
     // end (live = false) every lane asks for lane 0's bytes of a tile that was read already.
     __device__ __forceinline__ void load_x(XFrags& r, int T, bool live) {
         const uint16_t* p = (const uint16_t*)mt.x + 256 * T;
@@ -1501,7 +1502,8 @@ struct StageTiles {
 // of the MFMA, and they serve R row tiles; nothing is staged for the workgroup, no barrier sits in the loop.
 // What bounds it: start-up (about 4.5 us of a launch that moves nothing), then x: a compute unit reads all of x (131 KB at M = 16,
 // K = 4096) in pieces of 64 bytes per batch row, half of a cache line at a time.  (Whole lines, two of the loads exchanging half of every
-// DPP row in registers, were 0 to 11 % slower: the other half of a line is found in the L1, and the exchange costs.)  With 16 wavefronts of one column tile each every byte of a workgroup is
+// DPP row in registers, were 0 to 11 % slower: the other half of a line is found in the L1, and the exchange costs.)  With 16
+// wavefronts of one column tile each every byte of a workgroup is
 // asked for at its start.  Measured (7B shapes, fp16 SQ, cold weights, us at M = 2 / 16), a workgroup per 32 rows of W with 4 or 8
 // wavefronts (what this replaces) -> here: {r, k, v, g} 10.0 / 13.6 -> 7.8 / 9.8, o 6.1 / 8.9 -> 5.1 / 6.8, {k', r'} 12.6 / 19.1
 // -> 8.8 / 11.1, v' 13.1 / 21.5 -> 11.5 / 18.2.
