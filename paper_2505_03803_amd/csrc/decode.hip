@@ -1319,7 +1319,8 @@ struct StageRegs {
 constexpr int stage_sets(int R, bool multi) { return R == 6 ? 3 : multi && R == 1 ? 2 : R; }
 
 template <bool DIRECT> constexpr int kStageSlot = DIRECT ? 512 : 256;   // words of a codebook slot
-template <int FMT, int R, bool MULTI, bool XB>
+constexpr bool stage_as_is(int fmt, int R) { return fmt == FMT_SQ3 || R <= (fmt == FMT_VQ6 ? 2 : 1); }
+template <int FMT, int R, bool MULTI, bool XB, bool AS_IS = stage_as_is(FMT, R)>
 struct StageTiles {
     static constexpr int D = stage_sets(R, MULTI);
     static constexpr bool kOneBlock = 16 % R == 0;   // the row tiles share a codebook block
@@ -1328,8 +1329,9 @@ struct StageTiles {
     // of them, 8-bit with one (its look-ups of eight bytes meet in twice the banks).  Measured (us, converted -> as they are): 4096 x 4096
     // SQ at M = 2 5.8 -> 4.8, at 16 7.2 -> 6.7, 4096 x 14336 at 2 14.8 -> 11.4, 6-bit VQ 14.5 -> 11.7, 8-bit 15.4 -> 13.7; 17920 x 5120 and
     // 5120 x 5120 SQ (six row tiles) at 2 17.8 -> 12.8.  VQ of five row tiles at 2 10.7 -> 11.1, of two in 8 bits 5.4 -> 5.6 (converted);
-    // with four column tiles the split of the codebook is not won back: 4096 x 1024 8-bit VQ at 2 3.6 -> 3.75 (as they are all the same).
-    static constexpr bool kDirect = XB && (FMT == FMT_SQ3 || R <= (FMT == FMT_VQ6 ? 2 : 1)), kConvert = XB && !kDirect;
+    // with three and four column tiles the split of the codebook is not won back: 8192 x 768 6-bit VQ at 2 3.7 -> 4.0 (two row tiles:
+    // converted there), 4096 x 1024 8-bit 3.6 -> 3.75, but 512 x 768 2.9 -> 2.8 (one: as they are).
+    static constexpr bool kDirect = XB && AS_IS, kConvert = XB && !kDirect;
     static constexpr int kWords = FMT == FMT_VQ8 ? 512 : 384;
     const DecodeMat& mt;
     int R0, NR, KT, lane, xoff;
@@ -1510,18 +1512,21 @@ struct StageTiles {
 // most wavefronts of a workgroup: 128 registers each, or 168 where several column tiles are in flight.  Five and six row tiles spill up
 // to seven of the 168; eight wavefronts of 256 spill none and were no better (us, batch 8, twelve -> eight: 20480 x 8192, fp16 SQ 18.7 ->
 // 17.6 and bf16 VQ 22.3 -> 20.9, but 24576 x 4352 12.5 -> 13.4 and 13.8 -> 16.2: its 17 column tiles take three turns in place of two).
-// The kernel says that no more of them are wanted on a SIMD: left to itself the compiler gives the loads of fp16 x 126 registers of 168,
-// for a wavefront that never comes, and has fewer in flight (a layer of d = 2048 in SQ, two row tiles, at M = 2 13.7 -> 12.3 us, at 16
-// 19.9 -> 17.4; {14336 x 4096, 4096 x 14336} 6-bit VQ at 8 23.2 -> 22.2).
 constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; }
+// MOST: wavefronts on a SIMD that the compiler may make room for.  With two row tiles and several column tiles in flight it gives the loads
+// 126 registers of 168 to make room for four; rows of mixed lengths, small workgroups side by side, run better with three and more
+// loads in flight (a layer of d = 2048 in SQ at M = 2 13.7 -> 12.2 us, at 14 18.5 -> 16.2; {14336 x 4096, 4096 x 14336} 6-bit VQ at 8 23.4 ->
+// 22.2), a round of rows of one length does not (5120 x 17920 6-bit VQ at 2 15.7 -> 16.3, 8-bit in bf16 at 8 23.8 -> 24.8).  Workgroups of
+// one column tile per wavefront stand side by side in numbers and are not held at all (40960 x 256 SQ at 2 4.0, held to four 4.7).
+constexpr int stage_most(bool multi, int R, bool mixed) { return multi && R == 2 && mixed ? 3 : 8; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
     int wg_end[kGrid2D ? 1 : MATS];
     DecodeMat m[MATS];
     int M, xdt, ydt, S, waves, pad;
 };
-template <int R, bool MULTI, class Args>
-__global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) __attribute__((amdgpu_waves_per_eu(stage_waves(MULTI, R) / 4, stage_waves(MULTI, R) / 4)))
+template <int R, bool MULTI, class Args, int MOST>
+__global__ void __launch_bounds__(64 * stage_waves(MULTI, R)) __attribute__((amdgpu_waves_per_eu(stage_waves(MULTI, R) / 4, MOST)))
 decode_stage_kernel(Args a) {
     extern __shared__ __attribute__((aligned(1024))) uint32_t stage_lds[];        // per wavefront: two codebook slots, later its R sums
     __shared__ __attribute__((aligned(16))) float xsc[16][16];
@@ -1553,10 +1558,13 @@ decode_stage_kernel(Args a) {
     if (wave < KT && wave < S) {
         const int nt = (KT - wave + S - 1) / S;
         if (xdt == DT_BF16) {
+            bool as_is = stage_as_is(mt.fmt, R);
+            if constexpr (R == 2 && !MULTI) as_is = as_is && !(mt.fmt == FMT_VQ6 && (KT == 3 || KT == 4));
             if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            else StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            infinite = any_infinite(out);
+            else if (mt.fmt == FMT_VQ8) StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else if (R != 2 || MULTI || as_is) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            else if constexpr (R == 2 && !MULTI) StageTiles<FMT_VQ6, R, MULTI, true, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+            infinite = as_is && any_infinite(out);
         } else {
             if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
             else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
@@ -1945,15 +1953,16 @@ hipError_t launch_decode_postmix(const MatDev* mats, const PostDev* posts, const
     return hipSuccess;
 }
 
-template <int R, bool MULTI, class Args>
+template <int R, bool MULTI, bool MIXED, class Args>
 static hipError_t launch_stage_kernel(const Args& a, dim3 grid, hipStream_t s) {
+    constexpr int MOST = stage_most(MULTI, R, MIXED);
     const int lds = a.S * (R > 2 ? R : 2) * 1024;
     if (lds > 60 * 1024) {
         static std::atomic<unsigned long long> raised{0ull};
-        const hipError_t e = raise_lds((const void*)decode_stage_kernel<R, MULTI, Args>, 16 * R * 1024, raised);
+        const hipError_t e = raise_lds((const void*)decode_stage_kernel<R, MULTI, Args, MOST>, 16 * R * 1024, raised);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((decode_stage_kernel<R, MULTI, Args>), grid, dim3(64 * a.waves), lds, s, a);
+    hipLaunchKernelGGL((decode_stage_kernel<R, MULTI, Args, MOST>), grid, dim3(64 * a.waves), lds, s, a);
     return hipGetLastError();
 }
 // Launches of more matrices than the two-dimensional grid takes (the table) know one, two and four row tiles per workgroup.
@@ -2107,8 +2116,10 @@ static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats,
     }
     a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = p.S; a.waves = p.waves; a.pad = 0;
     const dim3 grid = StageArgs<MATS>::kGrid2D ? dim3(longest, n_mats) : dim3(wgs);
+    const bool mixed = p.kind == STAGE_MIXED || p.kind == STAGE_MIXED_ROUNDS;
 #define RWKVQ_STAGE(R_) case R_: if constexpr (stage_rows(StageArgs<MATS>::kGrid2D, R_) == R_) \
-        return p.turns > 1 ? launch_stage_kernel<R_, true>(a, grid, s) : launch_stage_kernel<R_, false>(a, grid, s); break;
+        return p.turns <= 1 ? launch_stage_kernel<R_, false, false>(a, grid, s) \
+               : mixed ? launch_stage_kernel<R_, true, true>(a, grid, s) : launch_stage_kernel<R_, true, false>(a, grid, s); break;
     switch (p.R) {
         RWKVQ_STAGE(1) RWKVQ_STAGE(2) RWKVQ_STAGE(3) RWKVQ_STAGE(4) RWKVQ_STAGE(5) RWKVQ_STAGE(6)
     }

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 # rows of W, column tiles, rows of x, work up to which a small launch splits its columns (0: by rule, 1: never, 1000000: always):
 # operands straight from memory with one, two and three row tiles per workgroup; the streaming kernels at batch 4, 16 and 32;
 # activations copied into LDS, 16 and 32 rows of W; 17 to 48 rows in one round; 17 to 128 rows, 16, 32 and 64 rows of W
-ROUTES = [(512, 3, 5, 0), (4352, 3, 5, 0), (8448, 3, 5, 0), (512, 3, 3, 1), (512, 3, 15, 1), (512, 3, 20, 1), (256, 17, 16, 0), (4352, 17, 15, 0),
+ROUTES = [(512, 3, 5, 0), (4352, 3, 5, 0), (4352, 5, 5, 0), (8448, 3, 5, 0), (512, 3, 3, 1), (512, 3, 15, 1), (512, 3, 20, 1), (256, 17, 16, 0), (4352, 17, 15, 0),
           (16640, 1, 17, 1000000), (16640, 2, 33, 1000000), (512, 3, 47, 0), (4352, 3, 100, 0), (8448, 2, 64, 0)]
 
 
