@@ -1513,12 +1513,15 @@ struct StageTiles {
 // to seven of the 168; eight wavefronts of 256 spill none and were no better (us, batch 8, twelve -> eight: 20480 x 8192, fp16 SQ 18.7 ->
 // 17.6 and bf16 VQ 22.3 -> 20.9, but 24576 x 4352 12.5 -> 13.4 and 13.8 -> 16.2: its 17 column tiles take three turns in place of two).
 constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; }
-// MOST: wavefronts on a SIMD that the compiler may make room for.  With two row tiles and several column tiles in flight it gives the loads
-// 126 registers of 168 to make room for four; rows of mixed lengths, small workgroups side by side, run better with three and more
-// loads in flight (a layer of d = 2048 in SQ at M = 2 13.7 -> 12.2 us, at 14 18.5 -> 16.2; {14336 x 4096, 4096 x 14336} 6-bit VQ at 8 23.4 ->
-// 22.2), a round of rows of one length does not (5120 x 17920 6-bit VQ at 2 15.7 -> 16.3, 8-bit in bf16 at 8 23.8 -> 24.8).  Workgroups of
-// one column tile per wavefront stand side by side in numbers and are not held at all (40960 x 256 SQ at 2 4.0, held to four 4.7).
-constexpr int stage_most(bool multi, int R, bool mixed) { return multi && R == 2 && mixed ? 3 : 8; }
+// MOST: wavefronts on a SIMD that the compiler may make room for, which costs registers and so loads in flight.  Left to itself (8) it
+// makes room for four with two row tiles and several column tiles, for six with one column tile.  Rows of mixed lengths, whose long
+// workgroups the launch waits for, run better with more loads in flight as long as nearly all of the launch stands on the device (`few` in
+// launch_stage; us, left to itself -> held): {8192 x 2304, 2304 x 8192} SQ in fp16 at M = 14 16.7 -> 13.2, {4608 x 1280, 1280 x 4608} 6-bit
+// VQ at 8 9.3 -> 7.9, layers of d = 2048 SQ at 2 13.7 -> 12.2, of 3072 (1008 workgroups of four) 8-bit VQ at 16 31.8 -> 28.1, of 768 (one column
+// tile) at 12 7.0 -> 6.2.  Not so beyond (a layer of d = 1280, 424 workgroups of six, at 3 in bf16 9.5 -> 11.5; of 3328, 1096 of four, 28.6 -> 30.1,
+// but five scalar-quantized matrices of 1050 in fp16 at 11 24.4 -> 21.2) and not for rows of one length (5120 x 17920 8-bit VQ in bf16 at
+// 8 23.8 -> 24.8, 40960 x 256 SQ at 2 4.0 -> 4.7).
+constexpr int stage_most(bool multi, int R, bool mixed) { return !mixed ? 8 : multi && R == 2 ? 3 : !multi && R <= 3 ? 5 : 8; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
     int wg_end[kGrid2D ? 1 : MATS];
@@ -1973,6 +1976,7 @@ struct StageShape {
     StageKind kind;
     int columns;                       // of the longest row
     double row_tiles;
+    bool mixed;                        // rows of mixed lengths
 };
 // Row tiles R and wavefronts S of a workgroup, swept over R = 1 .. 6 and S = 3 .. 16 at M = 2 to 16 in every format and both types of
 // x (us: fp16 where no type is named, cold weights).  `spread` is the longest row over the average one.
@@ -2012,7 +2016,7 @@ static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, 
     }
     const double spread = columns * row_tiles / tiles;
     StageShape p;
-    p.columns = columns; p.row_tiles = row_tiles;
+    p.columns = columns; p.row_tiles = row_tiles; p.mixed = spread > 1.6;
     int most;
     if (columns <= 2) {
         p.kind = STAGE_SHORT;
@@ -2116,10 +2120,11 @@ static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats,
     }
     a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = p.S; a.waves = p.waves; a.pad = 0;
     const dim3 grid = StageArgs<MATS>::kGrid2D ? dim3(longest, n_mats) : dim3(wgs);
-    const bool mixed = p.kind == STAGE_MIXED || p.kind == STAGE_MIXED_ROUNDS;
+    const int on_simd = (p.waves + 3) / 4;                          // wavefronts of a workgroup
+    const bool few = p.mixed && (p.turns <= 1 ? (wgs + 255) / 256 * on_simd <= 4 : on_simd == 1 ? wgs <= (x_dtype == DT_BF16 ? 1024 : 1100) : on_simd <= 3 && wgs <= 410);
 #define RWKVQ_STAGE(R_) case R_: if constexpr (stage_rows(StageArgs<MATS>::kGrid2D, R_) == R_) \
-        return p.turns <= 1 ? launch_stage_kernel<R_, false, false>(a, grid, s) \
-               : mixed ? launch_stage_kernel<R_, true, true>(a, grid, s) : launch_stage_kernel<R_, true, false>(a, grid, s); break;
+        return p.turns <= 1 ? (few ? launch_stage_kernel<R_, false, true>(a, grid, s) : launch_stage_kernel<R_, false, false>(a, grid, s)) \
+                            : (few ? launch_stage_kernel<R_, true, true>(a, grid, s) : launch_stage_kernel<R_, true, false>(a, grid, s)); break;
     switch (p.R) {
         RWKVQ_STAGE(1) RWKVQ_STAGE(2) RWKVQ_STAGE(3) RWKVQ_STAGE(4) RWKVQ_STAGE(5) RWKVQ_STAGE(6)
     }

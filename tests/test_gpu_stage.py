@@ -250,3 +250,28 @@ def test_rule_of_more_rows_of_two_lengths(lengths, M, xdt, options):
     for m, x, y, z in zip(mats, xs, *got):
         assert torch.equal(y, z) and (y[M] == 7.0).all()
         assert G.err_g2(y[:M].cpu().numpy().astype(np.float64), orc.linear(m, orc.widen(x, xdt), "f64")) <= 2e-5
+
+
+# Rows of mixed lengths, two row tiles: both sides of the line by what stands on the device at once (one column tile per wavefront: 248
+# workgroups of ten wavefronts, 488 of ten; several: 552 of four in more matrices than the two-dimensional grid takes, 184 of six, 264 of
+# seven, 424 of six, and 1056 of four, which fp16 and bf16 take differently)
+@pytest.mark.parametrize("shapes", [[(768, 768)] * 6 + [(2560, 768), (768, 2560)], [(2048, 768)] * 6 + [(2560, 768), (768, 2560)],
+                                    [(768, 768)] * 12 + [(7680, 768), (768, 2560)],
+                                    [(4608, 1280), (1280, 4608)], [(6912, 1536), (1536, 6912)], [(1280, 1280)] * 6 + [(4608, 1280), (1280, 4608)],
+                                    [(4096, 768)] * 7 + [(4096, 768), (1024, 5120)]])
+@pytest.mark.parametrize("kind", ["sq", "vq6"])
+@pytest.mark.parametrize("M,xdt", [(3, "f16"), (15, "bf16")])
+def test_rows_of_mixed_lengths(shapes, kind, M, xdt):
+    print(f"mixed lengths {len(shapes)} matrices {shapes[0]} .. {shapes[-1]} {kind} M={M} x={xdt}", flush=True)
+    torch, rng = G.torch_(), np.random.default_rng(M)
+    of = {s: (synth.gen_sq(rng, *s) if kind == "sq" else synth.gen_vq(rng, *s, int(kind[2:]))) for s in sorted(set(shapes))}
+    xs = {s: synth.gen_activations(rng, M, s[1], xdt) for s in of}
+    dms, dev = {s: B.upload(m, native=True) for s, m in of.items()}, {s: G.to_dev_bits(x) for s, x in xs.items()}
+    ys = [torch.full((M + 1, s[0]), 7.0, dtype=torch.float32, device="cuda") for s in shapes]
+    B.rwkvq_linear_dispatch(B.DispatchTable([dms[s].desc() for s in shapes], [dev[s] for s in shapes], ys), M, B.DTYPES[xdt], B.F32)
+    torch.cuda.synchronize()
+    want = {s: orc.linear(of[s], orc.widen(xs[s], xdt), "f64") for s in of}
+    for s, y in zip(shapes, ys):
+        got = y.cpu().numpy().astype(np.float64)
+        assert (got[M] == 7.0).all()
+        assert G.err_g2(got[:M], want[s]) <= 2e-5           # up to 6912 products, as above
