@@ -1517,10 +1517,10 @@ constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; 
 // makes room for four with two row tiles and several column tiles, for six with one column tile.  Rows of mixed lengths, whose long
 // workgroups the launch waits for, run better with more loads in flight as long as nearly all of the launch stands on the device (`few` in
 // launch_stage; us, left to itself -> held): {8192 x 2304, 2304 x 8192} SQ in fp16 at M = 14 16.7 -> 13.2, {4608 x 1280, 1280 x 4608} 6-bit
-// VQ at 8 9.3 -> 7.9, layers of d = 2048 SQ at 2 13.7 -> 12.2, of 3072 (1008 workgroups of four) 8-bit VQ at 16 31.8 -> 28.1, of 768 (one column
-// tile) at 12 7.0 -> 6.2.  Not so beyond (a layer of d = 1280, 424 workgroups of six, at 3 in bf16 9.5 -> 11.5; of 3328, 1096 of four, 28.6 -> 30.1,
-// but five scalar-quantized matrices of 1050 in fp16 at 11 24.4 -> 21.2) and not for rows of one length (5120 x 17920 8-bit VQ in bf16 at
-// 8 23.8 -> 24.8, 40960 x 256 SQ at 2 4.0 -> 4.7).
+// VQ at 8 9.3 -> 7.9, layers of d = 2048 SQ at 2 13.7 -> 12.2, of 3072 (1008 workgroups of four) 8-bit VQ in fp16 at 16 31.8 -> 28.1, of 768 (one
+// column tile) at 12 7.0 -> 6.2.  Not so beyond (a layer of d = 1280, 424 workgroups of six, at 3 in bf16 9.5 -> 11.5; of 3328, 1096 of four, 28.6
+// -> 30.1, two of 1536, 1008 of four, at 5 13.9 -> 14.8, but five scalar-quantized matrices, 1050 of four, in fp16 at 11 24.4 -> 21.2) and
+// not for rows of one length (5120 x 17920 8-bit VQ in bf16 at 8 23.8 -> 24.8, 40960 x 256 SQ at 2 4.0 -> 4.7).
 constexpr int stage_most(bool multi, int R, bool mixed) { return !mixed ? 8 : multi && R == 2 ? 3 : !multi && R <= 3 ? 5 : 8; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
@@ -1561,13 +1561,22 @@ decode_stage_kernel(Args a) {
     if (wave < KT && wave < S) {
         const int nt = (KT - wave + S - 1) / S;
         if (xdt == DT_BF16) {
-            bool as_is = stage_as_is(mt.fmt, R);
-            if constexpr (R == 2 && !MULTI) as_is = as_is && !(mt.fmt == FMT_VQ6 && (KT == 3 || KT == 4));
-            if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            else if (mt.fmt == FMT_VQ8) StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            else if (R != 2 || MULTI || as_is) StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            else if constexpr (R == 2 && !MULTI) StageTiles<FMT_VQ6, R, MULTI, true, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
-            infinite = as_is && any_infinite(out);
+            // (asked where it can be: behind all formats it costs the loads of the others, two layers of d = 5120 in 6-bit VQ at M = 6 73 -> 78 us)
+            if (mt.fmt == FMT_SQ3) {
+                StageTiles<FMT_SQ3, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+                infinite = any_infinite(out);
+            } else if (mt.fmt == FMT_VQ6) {
+                if constexpr (R == 2 && !MULTI) {
+                    if (KT == 3 || KT == 4) StageTiles<FMT_VQ6, R, MULTI, true, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+                    else { StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out); infinite = any_infinite(out); }
+                } else {
+                    StageTiles<FMT_VQ6, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+                    if (stage_as_is(FMT_VQ6, R)) infinite = any_infinite(out);
+                }
+            } else {
+                StageTiles<FMT_VQ8, R, MULTI, true>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
+                if (stage_as_is(FMT_VQ8, R)) infinite = any_infinite(out);
+            }
         } else {
             if (mt.fmt == FMT_SQ3) StageTiles<FMT_SQ3, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
             else if (mt.fmt == FMT_VQ6) StageTiles<FMT_VQ6, R, MULTI, false>(mt, R0, M, lane, xsc[wave], mine).run(wave, S, nt, out);
@@ -2121,7 +2130,7 @@ static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats,
     a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = p.S; a.waves = p.waves; a.pad = 0;
     const dim3 grid = StageArgs<MATS>::kGrid2D ? dim3(longest, n_mats) : dim3(wgs);
     const int on_simd = (p.waves + 3) / 4;                          // wavefronts of a workgroup
-    const bool few = p.mixed && (p.turns <= 1 ? (wgs + 255) / 256 * on_simd <= 4 : on_simd == 1 ? wgs <= (x_dtype == DT_BF16 ? 1024 : 1100) : on_simd <= 3 && wgs <= 410);
+    const bool few = p.mixed && (p.turns <= 1 ? (wgs + 255) / 256 * on_simd <= 4 : on_simd == 1 ? wgs <= (x_dtype == DT_BF16 ? 768 : 1100) : on_simd <= 3 && wgs <= 410);
 #define RWKVQ_STAGE(R_) case R_: if constexpr (stage_rows(StageArgs<MATS>::kGrid2D, R_) == R_) \
         return p.turns <= 1 ? (few ? launch_stage_kernel<R_, false, true>(a, grid, s) : launch_stage_kernel<R_, false, false>(a, grid, s)) \
                             : (few ? launch_stage_kernel<R_, true, true>(a, grid, s) : launch_stage_kernel<R_, true, false>(a, grid, s)); break;
