@@ -297,7 +297,9 @@ __device__ __forceinline__ void nearer(float& best, int& arg) {      // of two l
 //      places of a list repeat its first entry, which never wins again;
 //   4. pairs outside the cells, or in a cell with more than 16 entries (256: 8), are queued and compared with every entry: a few by
 //      sixteen lanes for four of them, more by a thread each.  Those that find the queue full (a quarter of the block, with 256
-//      entries an eighth: two workgroups share the LDS of a compute unit) are marked, and collected where the lists were;
+//      entries an eighth: two workgroups share the LDS of a compute unit) are marked, and collected where the lists were, at once
+//      where they fit (4096 x 4096, 256 entries, half of them zero, where some blocks queue a little more: a quarter of the block
+//      after another 105 us, now 98);
 //   5. blocks for which the cells do not pay (weights far wider than the codebook, crowded entries) compare every pair
 //      with every entry: when a fifth (6 bits) or a third (8 bits) of 128 sampled pairs is outside the cells, before the lists
 //      are made, or when a quarter of the first unit of every thread was queued, from there on (from the start, if half was).
@@ -748,17 +750,19 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
                 }
             }
         }
-        if (all > kQueue) {                                        // those that it had no place for, a quarter of the block after another
-            uint16_t* const more = (uint16_t*)list[0];
-            static_assert(G * G * kSlots >= 2 * 8192, "a quarter's pairs");
+        if (all > kQueue) {                                        // those that it had no place for: at once, or, where the room of the
+            uint16_t* const more = (uint16_t*)list[0];             // lists does not hold them, a quarter of the block after another
+            constexpr int kRoom = G * G * kSlots / 2;
+            static_assert(kRoom >= 8192, "a quarter's pairs");
+            const int step = all - kQueue <= kRoom ? 1024 : 256;
 #pragma unroll 1
-            for (int w0 = 0; w0 < units / 4; w0 += 256) {
+            for (int w0 = 0; w0 < units / 4; w0 += step) {
                 __syncthreads();
                 if (tid == 0) outside = 0;
                 __syncthreads();
                 int word = w0 + tid;
                 asm volatile("" : "+v"(word));
-                uint32_t m = word < w0 + 256 ? over[word] : 0u;
+                uint32_t m = tid < step ? over[word] : 0u;
                 int at = m ? atomicAdd(&outside, __builtin_popcount(m)) : 0;
 #pragma unroll 1
                 for (; m; m &= m - 1u) more[at++] = (uint16_t)(32 * word + __builtin_ctz(m));

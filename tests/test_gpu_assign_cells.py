@@ -159,3 +159,35 @@ def test_vq_assign_equal_and_crowded_entries(kbits, rows):
     words = want.shape[1] // len(kinds)
     for i, kind in enumerate(kinds):
         assert np.array_equal(got[:, words * i: words * (i + 1)], want[:, words * i: words * (i + 1)]), kind
+
+
+@pytest.mark.parametrize("kbits", [6, 8])
+@pytest.mark.parametrize("rows", [13, 26])                  # blocks taken in halves and whole
+def test_vq_assign_more_than_the_queue(kbits, rows):
+    """About as many pairs outside the cells as the queue holds, as it and the room of the lists hold together, and nearly all behind the
+    first units, none of them where the sample of 128 looks, so that the block is not given up before."""
+    from paper_2505_03803_amd import binding as B
+    rng = np.random.default_rng(23)
+    En = 1 << kbits
+    queue, room = (8192, 8192) if kbits == 6 else (4096, 16384)
+    counts = [queue - 8, queue + 8, queue + room - 8, queue + room + 8, 24000]
+    cb = rng.normal(0, 0.02, (len(counts), En, 2)).astype(np.float16)
+    cb = np.clip(cb, -0.05, 0.05)
+    wide = np.clip(rng.normal(0, 0.012, (256, 256 * len(counts))), -0.03, 0.03).astype(np.float32)
+    parts = 2 if rows == 13 else 1
+    t = np.arange(128)
+    for i, n in enumerate(counts):
+        b = wide[:, 256 * i: 256 * (i + 1)].reshape(256, 128, 2)
+        free = np.ones((256, 128), bool)
+        for part in range(parts):
+            free[part * 256 // parts + t * 2 // parts, t * 37 & 127] = False
+            free[part * 256 // parts: part * 256 // parts + 64] = False
+        at = np.flatnonzero(free)
+        at = rng.permutation(at)[:min(n, at.size)]
+        b.reshape(-1, 2)[at] = rng.choice([-1, 1], (at.size, 2)) * rng.uniform(0.5, 0.7, (at.size, 2))
+    bits = cb.view(np.uint16)[None]
+    want = np.tile(E.vq_assign_packed(wide, bits, kbits), (rows, 1))
+    got = B.vq_assign(dev(np.tile(wide, (rows, 1)), "f32"), B.F32, dev(np.tile(bits, (rows, 1, 1, 1)), "f16"), kbits).codes.cpu().numpy().view(np.uint32)
+    words = want.shape[1] // len(counts)
+    for i, n in enumerate(counts):
+        assert np.array_equal(got[:, words * i: words * (i + 1)], want[:, words * i: words * (i + 1)]), n
