@@ -317,8 +317,8 @@ __device__ __forceinline__ void nearer(float& best, int& arg) {      // of two l
 // with 32 x 32 cells that each looked through the entries near 8 x 8 of them, here): 4096 x 4096, 64 entries 77, 53, 50, 256 entries
 // 279, 81, 64; 14336 x 4096, 64 entries 128 -> 125, 256 entries 887, 218, 171; 1024 x 1024, 64 entries 22 -> 20, 256 entries 83, 42, 39.
 // Where there is little for the cells to find, 4096 x 4096 with 64 and 256 entries: weights 50 times as wide as the codebook 67 and 215,
-// all entries equal 65 and 207, on nine places 30 and 44 (copies on the lists: 65 and 272), half of them zero 65 and 106 (75 and 184),
-// half of them different ones within a thousandth of a deviation 65 and 127.  Registers: 64, for two workgroups on a compute unit (74:
+// all entries equal 65 and 207, on nine places 30 and 44 (copies on the lists: 65 and 272), half of them zero 65 and 98 (75 and 184),
+// half of them different ones within a thousandth of a deviation 65 and 110.  Registers: 64, for two workgroups on a compute unit (74:
 // 14336 x 4096, 64 entries 126 -> 172).
 template <int KBITS>
 __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restrict__ w, int wdt, int N, int K,
@@ -335,6 +335,8 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     __shared__ uint16_t queue[kQueue];
     __shared__ uint32_t over[1024];                                // pairs that the queue had no place for: a bit each, a byte per unit
     __shared__ int queued[2], outside;                             // by the first units, by the others
+    __shared__ int crowds;                                         // (fine) cells of 16 x 16 that list a crowd, and which
+    __shared__ uint8_t crowded[kFine ? 256 : 1];
     __shared__ float box[5];                                       // origin, cells per unit, h
     __shared__ __attribute__((aligned(8))) uint32_t distinct[E / 32];   // a bit per entry: none of a lower index is equal
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -363,7 +365,7 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
     if (sampled) load_pair((tid * (units >> 4) & ~127) + (tid * 37 & 127), px, py);
     if (tid < E) entry[tid] = float2{f16_bits_to_f32(cb[2 * tid]), f16_bits_to_f32(cb[2 * tid + 1])};
     over[tid] = 0u;
-    if (tid == 0) { queued[0] = 0; queued[1] = 0; outside = 0; }
+    if (tid == 0) { queued[0] = 0; queued[1] = 0; outside = 0; crowds = 0; }
     // Beside the box: the lowest entry of each of 1024 hashes.  An entry equal to it never wins and is on no list.  (One that is equal to
     // another of its hash stays: it costs a place.)
     uint32_t* const lowest = (uint32_t*)found;
@@ -426,7 +428,12 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
         // The lists, from the coarse to the fine: an entry that can be nearest to a point of a cell can be nearest to that point of the
         // cell around it.  A bit per entry; the bits of the two coarse grids lie where the results will.
         uint16_t* const coarse = (uint16_t*)found;                  // [8 x 8][E / 16]
-        uint16_t* const middle = coarse + 64 * (E / 16);            // [16 x 16][E / 16]
+        uint16_t* const middle = coarse + 64 * (E / 16);            // [16 x 16][E / 16], and as much again for the crowds
+        // Fine: a cell of 16 x 16 that lists more than kCrowd entries would hold up the one lane per cell of the step after it, and is
+        // listed by whole wavefronts behind it.  256 entries, a half of them within a thousandth of a deviation of one place: 4096 x 4096
+        // 118 -> 110 us, 1024 x 1024 62 -> 54, a quarter of them 50 -> 46; near-normal ones even.  With 48 near-normal codebooks have such
+        // cells (37.6 -> 38.9), with 110 the second stays at 60.  64 entries hold up less: nothing was gained.
+        constexpr int kCrowd = 64;
         constexpr int kWords = E / 32;
         // at most this far from the centre of a cell of 32 / g x 32 / g: the limit, and what every unit of distance from r adds
         auto limits = [&](float g, float least, float& at_most, float& hx, float& hy) {
@@ -503,10 +510,23 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
             limits(2.f, best, at_most, hx, hy);
             const float2 r = entry[arg];
 #pragma unroll
+            for (int q = 0; q < kOwn; ++q) own[q] = within(own[q], part * (E / 4) + 32 * q, cx, cy, r, at_most, hx, hy);
+            if constexpr (kFine) {
+                int n = 0;
+#pragma unroll
+                for (int q = 0; q < kOwn; ++q) n += __builtin_popcount(own[q]);
+                n += (int)dpp_move<0xB1>((uint32_t)n);
+                n += (int)dpp_move<0x4E>((uint32_t)n);
+                if (n > kCrowd) {
+                    if (part == 0) crowded[atomicAdd(&crowds, 1)] = (uint8_t)at;
+#pragma unroll
+                    for (int q = 0; q < kOwn; ++q) { ((uint32_t*)(to_bits + 256 * (E / 16)))[q] = own[q]; own[q] = 0u; }
+                }
+            }
+#pragma unroll
             for (int q = 0; q < kOwn; ++q) {
-                const uint32_t bits = within(own[q], part * (E / 4) + 32 * q, cx, cy, r, at_most, hx, hy);
-                if constexpr (E >= 128) ((uint32_t*)to_bits)[q] = bits;
-                else to_bits[0] = (uint16_t)bits;
+                if constexpr (E >= 128) ((uint32_t*)to_bits)[q] = own[q];
+                else to_bits[0] = (uint16_t)own[q];
             }
         }
         __syncthreads();
@@ -620,6 +640,56 @@ __global__ void __launch_bounds__(1024, 8) vq_assign_kernel(const void* __restri
             }
         }
         __syncthreads();
+        if constexpr (kFine)
+            if (crowds) {
+                // The sixteen cells within each: a wavefront for one after another, a lane for every 64th entry
+                const int all = 16 * __builtin_amdgcn_readfirstlane(crowds);
+#pragma unroll 1
+                for (int j = wave; j < all; j += 16) {
+                    const int at = __builtin_amdgcn_readfirstlane(crowded[j >> 4]);
+                    const int gx = 4 * (at & 15) + (j & 3), gy = 4 * (at >> 4) + ((j >> 2) & 3);
+                    const float cx = x0 + 0.5f * ((float)gx + 0.5f) / sx, cy = y0 + 0.5f * ((float)gy + 0.5f) / sy;
+                    const uint32_t* const bits = (const uint32_t*)(middle + (256 + at) * (E / 16)) + (lane >> 5);
+                    float d[E / 64], best = __builtin_inff(), at_most, hx, hy;
+                    float2 o[E / 64];
+                    int arg = 0;
+#pragma unroll
+                    for (int q = 0; q < E / 64; ++q) {
+                        o[q] = entry[64 * q + lane];
+                        d[q] = (bits[2 * q] >> (lane & 31)) & 1u ? pair_distance(cx, cy, o[q].x, o[q].y) : __builtin_nanf("");   // (never kept)
+                        if (d[q] < best) { best = d[q]; arg = 64 * q + lane; }
+                    }
+                    nearer<0xB1>(best, arg); nearer<0x4E>(best, arg); nearer<0x141>(best, arg); nearer<0x140>(best, arg);
+                    auto join = [&](auto both, auto which) {
+                        const float d0 = __uint_as_float(both[0]), d1 = __uint_as_float(both[1]);
+                        best = d1 < d0 ? d1 : d0; arg = (int)(d1 < d0 ? which[1] : which[0]);
+                    };
+                    uint32_t b = __float_as_uint(best), a = (uint32_t)arg;
+                    join(__builtin_amdgcn_permlane16_swap(b, b, false, false), __builtin_amdgcn_permlane16_swap(a, a, false, false));
+                    b = __float_as_uint(best); a = (uint32_t)arg;
+                    join(__builtin_amdgcn_permlane32_swap(b, b, false, false), __builtin_amdgcn_permlane32_swap(a, a, false, false));
+                    limits(0.5f, best, at_most, hx, hy);
+                    const float2 r = entry[arg];
+                    unsigned long long keeps[E / 64];
+                    int n = 0, first = 0, before = 0;
+#pragma unroll
+                    for (int q = E / 64 - 1; q >= 0; --q) {
+                        keeps[q] = __builtin_amdgcn_ballot_w64(d[q] <= fmaf(fabsf(r.x - o[q].x), hx, fmaf(fabsf(r.y - o[q].y), hy, at_most)));
+                        n += __builtin_popcountll(keeps[q]);
+                        if (keeps[q]) first = 64 * q + __builtin_ctzll(keeps[q]);
+                    }
+                    const bool fits = n > 0 && n <= kSlots;
+                    uint8_t* const places = list[gy * G + gx];
+                    if (lane < kSlots) places[lane] = (uint8_t)(fits ? first : lane == 0);   // a list that does not fit starts with 1 and 0
+#pragma unroll
+                    for (int q = 0; q < E / 64; ++q) {
+                        const bool mine = fits && ((keeps[q] >> lane) & 1u);
+                        if (mine) places[before + __builtin_popcountll(keeps[q] & ((1ull << lane) - 1u))] = (uint8_t)(64 * q + lane);
+                        before += __builtin_popcountll(keeps[q]);
+                    }
+                }
+                __syncthreads();
+            }
 
 #pragma unroll 1
         for (int u = tid; u < units; u += 1024) {

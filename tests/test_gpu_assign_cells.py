@@ -191,3 +191,25 @@ def test_vq_assign_more_than_the_queue(kbits, rows):
     words = want.shape[1] // len(counts)
     for i, n in enumerate(counts):
         assert np.array_equal(got[:, words * i: words * (i + 1)], want[:, words * i: words * (i + 1)]), n
+
+
+@pytest.mark.parametrize("spread", [2e-4, 2e-3, 6e-3])
+def test_vq_assign_crowds(spread):
+    """256 entries of which n, all different, are crowded at one place or at two: fewer and more than what a cell of 16 x 16 lists before
+    whole wavefronts list the cells within it, of which some keep eight or fewer; pairs on the crowd, around it and everywhere."""
+    from paper_2505_03803_amd import binding as B
+    rng = np.random.default_rng(31)
+    counts = [44, 52, 60, 64, 68, 96, 128, 200, 250]
+    cb = rng.normal(0, 0.02, (len(counts), 256, 2)).astype(np.float16)
+    wide = rng.normal(0, 0.02, (256, 256 * len(counts))).astype(np.float32)
+    for i, n in enumerate(counts):
+        at = rng.uniform(-0.025, 0.025, (2, 2))[rng.integers(0, 1 + i % 2, n)]
+        cb[i, rng.permutation(256)[:n]] = at + rng.uniform(-spread, spread, (n, 2))
+        b = wide[:, 256 * i: 256 * (i + 1)].reshape(256, 128, 2)
+        b[::4] = at[0] + rng.normal(0, spread, b[::4].shape)
+        b[1::8] = at[-1] + rng.normal(0, 4 * spread, b[1::8].shape)
+    bits = cb.view(np.uint16)[None]
+    want = E.vq_assign_packed(wide, bits, 8)
+    for rows in (1, 15):                        # blocks in quarters and whole
+        got = B.vq_assign(dev(np.tile(wide, (rows, 1)), "f32"), B.F32, dev(np.tile(bits, (rows, 1, 1, 1)), "f16"), 8).codes.cpu().numpy().view(np.uint32)
+        assert np.array_equal(got, np.tile(want, (rows, 1))), rows
