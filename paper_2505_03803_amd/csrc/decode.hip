@@ -1696,7 +1696,8 @@ struct StageWide {
             if constexpr (FMT == FMT_VQ8) {
                 const uint4_t q = U == 0 ? r.a : r.b;
                 const uint32_t* cbuf = cb_lds + 256 * slot;
-                op[0] = __builtin_bit_cast(uint4_t, vq8_operand(q.x, cbuf)); op[1] = __builtin_bit_cast(uint4_t, vq8_operand(q.y, cbuf)); op[2] = __builtin_bit_cast(uint4_t, vq8_operand(q.z, cbuf)); op[3] = __builtin_bit_cast(uint4_t, vq8_operand(q.w, cbuf));
+                op[0] = __builtin_bit_cast(uint4_t, vq8_operand(q.x, cbuf)); op[1] = __builtin_bit_cast(uint4_t, vq8_operand(q.y, cbuf));
+                op[2] = __builtin_bit_cast(uint4_t, vq8_operand(q.z, cbuf)); op[3] = __builtin_bit_cast(uint4_t, vq8_operand(q.w, cbuf));
             } else {
                 const uint32_t w0 = U == 0 ? r.a.x : r.a.w, w1 = U == 0 ? r.a.y : r.b.x, w2 = U == 0 ? r.a.z : r.b.y;
                 if constexpr (FMT == FMT_SQ3) {
@@ -1725,7 +1726,8 @@ struct StageWide {
                 }
             }
             if (U == 1) load_w(w[rt], Tn, rt, more);
-            else if (XB || (FMT != FMT_SQ3 && R == 6 && (rt & 1))) __builtin_amdgcn_sched_barrier(0);   // operands of one or two row tiles at a time: more would spill
+            // (operands of one or two row tiles at a time: more would spill)
+            else if (XB || (FMT != FMT_SQ3 && R == 6 && (rt & 1))) __builtin_amdgcn_sched_barrier(0);
         }
         load_x<U>(Tn, more);
     }

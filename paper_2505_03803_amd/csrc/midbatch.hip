@@ -1,7 +1,7 @@
 // Matrix-core path for 17 to about a thousand rows of x (prompts, chunks of them; EXACT: also 2 to 16 in small launches of long
 // rows): y[M][N] = x[M][K] * Deq(W)^T with the feed of prefill.hip (Deq(W) rounded once to the type of x, binary32 accumulate)
-// in another cut.  prefill.hip gives a workgroup 128 or 256 rows of x and 256 of W and all of K; with a few hundred rows of x a projection is then 16 to 48
-// workgroups on 256 compute units, each a chain of K / 64 steps.  Here
+// in another cut.  prefill.hip gives a workgroup 128 or 256 rows of x and 256 of W and all of K; with a few hundred rows of x a
+// projection is then 16 to 48 workgroups on 256 compute units, each a chain of K / 64 steps.  Here
 //   * a workgroup of eight wavefronts takes 16 MF rows of x (MF = 4, 6, 8) and 16 NF NW rows of W (NF = 4; NW = 1, 2): a 4096 x
 //     4096 matrix at 333 rows is 192 workgroups (MF = 4, NW = 2);
 //   * the wavefronts split K as well: KW = 8 / NW groups take the 256-column tiles kg, kg + KW, ..., so the chain is KW times
@@ -18,8 +18,9 @@
 // Measured (bf16, SQ and 6-bit VQ, us; prefill.hip -> here): 4096 x 4096 at M = 333 82 -> 27.5, at M = 1024 82 -> 40.5;
 // 4096 x 14336 at M = 333 265 -> 78, at M = 1024 269 -> 120; four 4096 x 4096 at M = 333 170 -> 66, at M = 1024 178 -> 140.
 // EXACT instances (17 <= M <= 128, and launches of long rows from M = 2 on, where the streaming kernels' contract holds: weights
-// unrounded, fp16 or bf16 x multiplied as it is): NW = 1, 16 to 64 rows of x per workgroup, so a call that took ceil(M / 32) passes over W takes one (M <= 64).  SQ: codes as
-// 8 + q with the scale and zero point applied to the group's sums; VQ: the fp16 entries, for bf16 x as the sum of two bf16.
+// unrounded, fp16 or bf16 x multiplied as it is): NW = 1, 16 to 64 rows of x per workgroup, so a call that took ceil(M / 32) passes
+// over W takes one (M <= 64).  SQ: codes as 8 + q with the scale and zero point applied to the group's sums; VQ: the fp16 entries,
+// for bf16 x as the sum of two bf16.
 // A workgroup takes 32 rows of W (NF = 2) where that gives at most one per compute unit, and 64 otherwise; 16 (NF = 1) where 32 would
 // leave half of the compute units without one: each then multiplies half as many rows by the x that it reads either way (36 bytes per
 // clock and compute unit, what bounds long rows beyond 32 rows of x).  Of 336 calls of one matrix of 1024 to 4096 rows none got more than
