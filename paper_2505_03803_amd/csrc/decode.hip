@@ -1520,7 +1520,11 @@ constexpr int stage_waves(bool multi, int R) { return multi && R > 1 ? 12 : 16; 
 // VQ at 8 9.3 -> 7.9, layers of d = 2048 SQ at 2 13.7 -> 12.2, of 3072 (1008 workgroups of four) 8-bit VQ in fp16 at 16 31.8 -> 28.1, of 768 (one
 // column tile) at 12 7.0 -> 6.2.  Not so beyond (a layer of d = 1280, 424 workgroups of six, at 3 in bf16 9.5 -> 11.5; of 3328, 1096 of four, 28.6
 // -> 30.1, two of 1536, 1008 of four, at 5 13.9 -> 14.8, but five scalar-quantized matrices, 1050 of four, in fp16 at 11 24.4 -> 21.2) and
-// not for rows of one length (5120 x 17920 8-bit VQ in bf16 at 8 23.8 -> 24.8, 40960 x 256 SQ at 2 4.0 -> 4.7).
+// not for rows of one length (5120 x 17920 8-bit VQ in bf16 at 8 23.8 -> 24.8, 40960 x 256 SQ at 2 4.0 -> 4.7).  More than 410 workgroups of five and
+// more wavefronts, 415 to 500 of them: short ones run in the place that is left (`side_by_side`), unless the long ones decide, of many turns or
+// far longer than the others (eight matrices of 2048 in SQ in fp16, turns of six, the longest 2.9 times the average, at 8 16.4 -> 13.5).
+// Held, 169 such calls take 0.65 to 1.22 of the time left to itself; by the line 0.98 of held and 0.96 of left to itself in the mean, fp16 up
+// to 14 % and bf16 up to 11 % from the better of the two.
 constexpr int stage_most(bool multi, int R, bool mixed) { return !mixed ? 8 : multi && R == 2 ? 3 : !multi && R <= 3 ? 5 : 8; }
 template <int MATS> struct StageArgs {
     static constexpr bool kGrid2D = MATS <= kGrid2DMaxMats;
@@ -1987,7 +1991,7 @@ struct StageShape {
     StageKind kind;
     int columns;                       // of the longest row
     double row_tiles;
-    bool mixed;                        // rows of mixed lengths
+    double spread;                     // the longest row over the average one: beyond 1.6 rows of mixed lengths
 };
 // Row tiles R and wavefronts S of a workgroup, swept over R = 1 .. 6 and S = 3 .. 16 at M = 2 to 16 in every format and both types of
 // x (us: fp16 where no type is named, cold weights).  `spread` is the longest row over the average one.
@@ -2027,7 +2031,7 @@ static StageShape stage_shape(const MatDev* mats, const int* order, int n_mats, 
     }
     const double spread = columns * row_tiles / tiles;
     StageShape p;
-    p.columns = columns; p.row_tiles = row_tiles; p.mixed = spread > 1.6;
+    p.columns = columns; p.row_tiles = row_tiles; p.spread = spread;
     int most;
     if (columns <= 2) {
         p.kind = STAGE_SHORT;
@@ -2132,7 +2136,10 @@ static hipError_t launch_stage(const MatDev* mats, const int* order, int n_mats,
     a.M = M; a.xdt = x_dtype; a.ydt = y_dtype; a.S = p.S; a.waves = p.waves; a.pad = 0;
     const dim3 grid = StageArgs<MATS>::kGrid2D ? dim3(longest, n_mats) : dim3(wgs);
     const int on_simd = (p.waves + 3) / 4;                          // wavefronts of a workgroup
-    const bool few = p.mixed && (p.turns <= 1 ? (wgs + 255) / 256 * on_simd <= 4 : on_simd == 1 ? wgs <= (x_dtype == DT_BF16 ? 768 : 1100) : on_simd <= 3 && wgs <= 410);
+    const bool bf16 = x_dtype == DT_BF16;
+    const bool side_by_side = bf16 ? p.spread <= 2.6 || p.turns <= 3 : p.turns <= 3 ? p.spread <= 2.4 : p.turns <= 5 && p.spread <= 2.0;
+    const bool few = p.spread > 1.6 && (p.turns <= 1 ? (wgs + 255) / 256 * on_simd <= 4
+                                        : on_simd == 1 ? wgs <= (bf16 ? 768 : 1100) : wgs <= 410 || !side_by_side);
 #define RWKVQ_STAGE(R_) case R_: if constexpr (stage_rows(StageArgs<MATS>::kGrid2D, R_) == R_) \
         return p.turns <= 1 ? (few ? launch_stage_kernel<R_, false, true>(a, grid, s) : launch_stage_kernel<R_, false, false>(a, grid, s)) \
                             : (few ? launch_stage_kernel<R_, true, true>(a, grid, s) : launch_stage_kernel<R_, true, false>(a, grid, s)); break;

@@ -254,10 +254,11 @@ def test_rule_of_more_rows_of_two_lengths(lengths, M, xdt, options):
 
 # Rows of mixed lengths, two row tiles: both sides of the line by what stands on the device at once (one column tile per wavefront: 248
 # workgroups of ten wavefronts, 488 of ten; several: 552 of four in more matrices than the two-dimensional grid takes, 184 of six, 264 of
-# seven, 424 of six, and 1056 of four, which fp16 and bf16 take differently)
+# seven, 424 of six, 440 of seven and of eight, and 1056 of four, which fp16 and bf16 take differently, as they do the 424)
 @pytest.mark.parametrize("shapes", [[(768, 768)] * 6 + [(2560, 768), (768, 2560)], [(2048, 768)] * 6 + [(2560, 768), (768, 2560)],
                                     [(768, 768)] * 12 + [(7680, 768), (768, 2560)],
                                     [(4608, 1280), (1280, 4608)], [(6912, 1536), (1536, 6912)], [(1280, 1280)] * 6 + [(4608, 1280), (1280, 4608)],
+                                    [(2816, 2560)] * 4 + [(2816, 5120)], [(1280, 1280)] * 6 + [(5120, 1280), (1280, 7424)],
                                     [(4096, 768)] * 7 + [(4096, 768), (1024, 5120)]])
 @pytest.mark.parametrize("kind", ["sq", "vq6"])
 @pytest.mark.parametrize("M,xdt", [(3, "f16"), (15, "bf16")])
